@@ -262,6 +262,20 @@ int forward_single(ssd_ctx* c, const uint8_t* sub, int slot, int slot_out, int p
     return SSD_OK;
 }
 
+// LM head of up to 16 rows and the greedy token of each into SM_TARGET: the launch leaves one maximum per row and 16
+// columns in the attention scratch (idle here), a one-block-per-row kernel folds them.
+int lmhead_argmax(ssd_ctx* c, RowsFused& lm)
+{
+    const Dims& D = c->D;
+    const bool fold = (size_t)lm.M * (D.V / 16) * 2 <= c->lay.part_floats;
+    if (fold) { lm.vmax = reinterpret_cast<float2*>(c->f(c->lay.part)); lm.clamp = c->cfg.conf_clamp; }
+    TIMED(SSD_K_ROWS_LMHEAD, rows_fused(D, lm, c->stream), "rows_lmhead");
+    if (fold) HIPCHK(argmax_tiles(lm.vmax, lm.M, D.V / 16, c->small_i() + SM_TARGET, c->stream), "argmax_tiles");
+    else HIPCHK(vocab_reduce(c->f(c->lay.logits), lm.M, D.V, c->cfg.conf_clamp, c->cfg.conf_eps, c->small_i() + SM_TARGET, 1,
+                             nullptr, nullptr, nullptr, c->stream), "vocab_reduce");
+    return SSD_OK;
+}
+
 // Full-model forward of the M tokens in SM_VTOK (M <= 16, or <= 64 where the wide tiling applies) at positions
 // *pos + pos_off + r; taps into tap rows 0..M-1; logits (when want_logits) into logits rows 0..M-1 and greedy tokens
 // into SM_TARGET -- for a block of more than 16 rows (a prompt block) only the last row's.
@@ -328,9 +342,8 @@ int forward_rows(ssd_ctx* c, int M, int pos_off, int pos_host, bool want_logits,
             lm.w[0] = c->w.lm_head; lm.n[0] = D.V; lm.K = D.d; lm.bh = xh + (size_t)r * D.d; lm.bl = xl + (size_t)r * D.d;
             lm.ldb = D.d; lm.ssq = ssq + (size_t)r * n_ssq; lm.n_ssq = n_ssq; lm.y = c->f(Y.logits);
             lm.ldy = D.V; lm.M = 1; lm.mode = 0;
-            TIMED(SSD_K_ROWS_LMHEAD, rows_fused(D, lm, c->stream), "rows_lmhead");
-            HIPCHK(vocab_reduce(c->f(Y.logits), 1, D.V, c->cfg.conf_clamp, c->cfg.conf_eps,
-                                c->small_i() + SM_TARGET, 1, nullptr, nullptr, nullptr, c->stream), "vocab_reduce");
+            int rc = lmhead_argmax(c, lm);
+            if (rc) return rc;
         }
         return SSD_OK;
     }
@@ -378,9 +391,8 @@ int forward_rows(ssd_ctx* c, int M, int pos_off, int pos_host, bool want_logits,
             RowsFused lm = {};
             lm.w[0] = c->w.lm_head; lm.n[0] = D.V; lm.K = D.d; lm.bh = xh; lm.bl = xl; lm.ldb = D.d; lm.ssq = ssq;
             lm.n_ssq = n_ssq; lm.y = c->f(Y.logits); lm.ldy = D.V; lm.M = M; lm.mode = 0;
-            TIMED(SSD_K_ROWS_LMHEAD, rows_fused(D, lm, c->stream), "rows_lmhead");
-            HIPCHK(vocab_reduce(c->f(Y.logits), M, D.V, c->cfg.conf_clamp, c->cfg.conf_eps, c->small_i() + SM_TARGET, 1,
-                                nullptr, nullptr, nullptr, c->stream), "vocab_reduce");
+            int rc = lmhead_argmax(c, lm);
+            if (rc) return rc;
         }
         return SSD_OK;
     }
@@ -515,8 +527,11 @@ int conf_batch(ssd_ctx* c, const ConfScratch& sc, const float* taps, int nb, flo
             TIMED(SSD_K_ROWS_LMHEAD, gemm_rows(D, lm, c->stream), "gemm conf lmhead");
         }
     }
-    HIPCHK(vocab_reduce(sc.logits, nb, D.V, c->cfg.conf_clamp, c->cfg.conf_eps, nullptr, 1, argmax_dev, maxprob_dev, conf_dev,
-                        c->stream), "vocab_reduce conf");
+    // the normalised rows are done with once their logits exist: their buffer holds the reduction's partial records
+    void* scratch = rows_fused_supported(D) ? (void*)sc.hi : (void*)sc.tapn;
+    const size_t scratch_bytes = (size_t)nb * D.d * (rows_fused_supported(D) ? 2 : 4);
+    HIPCHK(vocab_confidence(sc.logits, nb, D.V, c->cfg.conf_clamp, c->cfg.conf_eps, argmax_dev, maxprob_dev, conf_dev, scratch,
+                            scratch_bytes, c->stream), "vocab_confidence");
     return SSD_OK;
 }
 

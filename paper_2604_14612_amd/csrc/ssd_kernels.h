@@ -124,6 +124,7 @@ struct RowsFused {
     const float* gain_out; float* ssq_out;
     float* kpart; size_t kpart_floats;  // rows_wide / rows_big: scratch for a split along K (may be null: no split)
     int tap_only;                       // > 0: only row tap_only - 1 writes its tap, into tap row 0
+    float2* vmax; float clamp;          // rows_fused mode 0, may be null: [M][n / 16] (maximum of a 16-column tile's clamped results, its lowest column)
 };
 bool rows_fused_supported(const Dims& D);
 hipError_t rows_fused(const Dims& D, const RowsFused& f, hipStream_t s);
@@ -174,6 +175,13 @@ int attention_splits(const Dims& D, int ctx, int M);
 hipError_t vocab_reduce(const float* logits, int M, int V, float clamp, float eps, int32_t* tok_out,
                         int tok_stride, int32_t* argmax_out, float* maxprob_out, float* conf_out,
                         hipStream_t s);
+
+// tok_out[r] = lowest column of the largest clamped logit of row r, from the vmax records of a rows_fused LM-head launch
+hipError_t argmax_tiles(const float2* vmax, int M, int n_tiles, int32_t* tok_out, hipStream_t s);
+// Confidence, max-probability and arg-max of M rows as vocab_reduce gives them, cut along the vocabulary where the rows
+// alone leave the chip idle; scratch (may be null: never cut) takes 16 bytes per row and slice.
+hipError_t vocab_confidence(const float* logits, int M, int V, float clamp, float eps, int32_t* argmax_out, float* maxprob_out,
+                            float* conf_out, void* scratch, size_t scratch_bytes, hipStream_t s);
 
 // means[t] = mean over positions p < n_pos of v[p * n_taps + t] (context-window average of per-row confidences)
 hipError_t window_mean(const float* v, int n_pos, int n_taps, float* means, hipStream_t s);

@@ -1120,6 +1120,7 @@ struct RowsP2 {
     int ksplit; float* kpart;                   // wide RESID only: K cut into ksplit slices (grid.y), raw sums to kpart [ksplit][M][n]
     int tile0, fin_tile0;                       // large tiles: first weight tile of this launch; first 64-column output tile of its finishing launch
     int tap_only;                               // > 0: only row tap_only - 1 writes its tap (a prompt needs the last row's only)
+    float2* vmax; float clamp;                  // 16-row STORE, may be null: per (row, 16-column tile) maximum of the clamped outputs and its lowest column
     int n_tiles;                                // large-tile kernel: weight tiles of the launch
 };
 
@@ -1226,8 +1227,15 @@ __device__ __forceinline__ void m2_epilogue(const RowsP2& p, int t, const float*
             }
         } else {
             const size_t colx = (size_t)t * 16 + rr;
-            if (MODE == RM_STORE) p.y[(size_t)c * p.ldy + colx] = v;
-            else if (MODE == RM_RESID) {
+            if (MODE == RM_STORE) {
+                p.y[(size_t)c * p.ldy + colx] = v;
+                if (p.vmax) {   // the 16 columns of the tile are the 16 lanes of a DPP row, all active together
+                    const float z = fminf(fmaxf(v, -p.clamp), p.clamp);
+                    const float m = row16_max(z);
+                    const unsigned long long eq = __ballot(z == m) >> (threadIdx.x & 48);   // this row's 16 lanes; never empty (z is clamped, no NaN)
+                    if (rr == 0) p.vmax[(size_t)c * gridDim.x + t] = make_float2(m, __int_as_float(t * 16 + __ffsll(eq) - 1));
+                }
+            } else if (MODE == RM_RESID) {
                 float* dst = p.y + (size_t)c * p.ldy + colx;
                 const float tv = *dst + v;
                 *dst = tv;
@@ -2084,7 +2092,7 @@ static void fill_rows_params(const Dims& D, const RowsFused& f, RowsP2& p)
     p.tap = f.tap; p.tap_ld = f.tap_ld; p.M = f.M; p.rope = f.rope; p.pos_dev = f.pos_dev; p.pos_off = f.pos_off;
     p.hd = D.hd; p.dq = D.dq; p.dkv = D.dkv; p.max_seq = D.max_seq; p.kc = f.kc; p.vc = f.vc; p.kt = D.kt;
     p.ssq = f.ssq; p.n_ssq = f.n_ssq; p.eps = D.eps; p.gain_out = f.gain_out; p.ssq_out = f.ssq_out;
-    p.tap_only = f.tap_only;
+    p.tap_only = f.tap_only; p.vmax = f.vmax; p.clamp = f.clamp;
 }
 
 hipError_t rows_wide(const Dims& D, const RowsFused& f, hipStream_t s)
@@ -3450,6 +3458,17 @@ hipError_t attention(const Dims& D, const float* q, int ldq, const void* kc, con
 // ---------------------------------------------------------------------------------------------
 constexpr int VR_THREADS = 1024;
 
+// maximum of a wave and its lowest index
+__device__ __forceinline__ void argmax_wave(float& m, int& mi)
+{
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const float om = __shfl_xor(m, o, 64);
+        const int oi = __shfl_xor(mi, o, 64);
+        if (om > m || (om == m && oi < mi)) { m = om; mi = oi; }
+    }
+}
+
 __global__ __launch_bounds__(VR_THREADS) void vocab_reduce_kernel(const float* __restrict__ logits, int V, float clamp,
                                                                   float eps, int32_t* tok_out, int tok_stride,
                                                                   int32_t* argmax_out, float* maxprob_out, float* conf_out)
@@ -3465,12 +3484,7 @@ __global__ __launch_bounds__(VR_THREADS) void vocab_reduce_kernel(const float* _
         float v = fminf(fmaxf(z[i], -clamp), clamp);
         if (v > m) { m = v; mi = i; }  // ascending i per thread: first occurrence kept
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        float om = __shfl_xor(m, o, 64);
-        int oi = __shfl_xor(mi, o, 64);
-        if (om > m || (om == m && oi < mi)) { m = om; mi = oi; }
-    }
+    argmax_wave(m, mi);
     if (lane == 0) { rv[wave] = m; ri[wave] = mi; }
     __syncthreads();
     m = rv[0]; mi = ri[0];
@@ -3499,6 +3513,138 @@ __global__ __launch_bounds__(VR_THREADS) void vocab_reduce_kernel(const float* _
         float Hs = block_sum<16>(hs, rv);
         if (tid == 0) conf_out[r] = 1.0f - Hs / logf((float)V);
     }
+}
+
+// Greedy token of every row of a 16-row LM-head launch from the per-tile maxima its epilogue left behind: one block per
+// row, lowest column among equal maxima.  (Reading the logits back instead is one block walking 128-513 KB: 18.5 us at
+// 32 000 columns, 65 us at 128 256.)
+__global__ __launch_bounds__(VR_THREADS) void argmax_tiles_kernel(const float2* __restrict__ vmax, int n_tiles,
+                                                                  int32_t* __restrict__ tok_out)
+{
+    __shared__ float rv[16];
+    __shared__ int ri[16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const float2* v = vmax + (size_t)blockIdx.x * n_tiles;
+    float m = -INFINITY;
+    int mi = 0x7fffffff;
+    for (int i = tid; i < n_tiles; i += VR_THREADS) {
+        const float2 e = v[i];
+        if (e.x > m) { m = e.x; mi = __float_as_int(e.y); }   // ascending tiles per thread: first occurrence kept
+    }
+    argmax_wave(m, mi);
+    if (lane == 0) { rv[wave] = m; ri[wave] = mi; }
+    __syncthreads();
+    if (wave == 0) {
+        m = lane < 16 ? rv[lane] : -INFINITY;
+        mi = lane < 16 ? ri[lane] : 0x7fffffff;
+        argmax_wave(m, mi);
+        if (lane == 0) tok_out[blockIdx.x] = mi;
+    }
+}
+hipError_t argmax_tiles(const float2* vmax, int M, int n_tiles, int32_t* tok_out, hipStream_t s)
+{
+    if (M < 1 || n_tiles < 1) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(argmax_tiles_kernel, dim3(M), dim3(VR_THREADS), 0, s, vmax, n_tiles, tok_out);
+    return hipGetLastError();
+}
+
+// Confidence rows, cut along the vocabulary: `ns` blocks per row leave (max, sum of exp relative to it, arg-max) of their
+// slice, a second launch merges a row's records (every block for itself, in slice order) and adds up its slice of the
+// entropy, a third adds the slices.  One block per row walks 32 000 logits three times in 27 us while most CUs idle (16
+// or 64 rows); the three short launches take about 11 us together.
+constexpr int VS_THREADS = 256;
+struct VRec { float m, z; int arg; float h; };
+
+__device__ __forceinline__ void vs_slice(int V, int ns, int sl, int& b, int& e)
+{
+    b = (int)((long)V * sl / ns);
+    e = (int)((long)V * (sl + 1) / ns);
+}
+__global__ __launch_bounds__(VS_THREADS) void vocab_part_kernel(const float* __restrict__ logits, int V, int ns, float clamp,
+                                                                VRec* __restrict__ rec)
+{
+    __shared__ float rv[VS_THREADS / 64];
+    __shared__ int ri[VS_THREADS / 64];
+    const int sl = blockIdx.x, r = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const float* z = logits + (size_t)r * V;
+    int b, e;
+    vs_slice(V, ns, sl, b, e);
+    float m = -INFINITY;
+    int mi = 0x7fffffff;
+    for (int i = b + tid; i < e; i += VS_THREADS) {
+        const float v = fminf(fmaxf(z[i], -clamp), clamp);
+        if (v > m) { m = v; mi = i; }
+    }
+    argmax_wave(m, mi);
+    if (lane == 0) { rv[wave] = m; ri[wave] = mi; }
+    __syncthreads();
+    m = rv[0]; mi = ri[0];
+#pragma unroll
+    for (int w = 1; w < VS_THREADS / 64; w++)
+        if (rv[w] > m || (rv[w] == m && ri[w] < mi)) { m = rv[w]; mi = ri[w]; }
+    float zs = 0.f;
+    for (int i = b + tid; i < e; i += VS_THREADS) zs += expf(fminf(fmaxf(z[i], -clamp), clamp) - m);
+    const float Z = block_sum<VS_THREADS / 64>(zs, rv);
+    if (tid == 0) rec[(size_t)r * ns + sl] = VRec{m, Z, mi, 0.f};
+}
+// merged maximum, its lowest index and sum of exp of the ns records of a row
+__device__ __forceinline__ void vs_merge(const VRec* rec, int ns, float& m, float& Z, int& mi)
+{
+    m = -INFINITY; mi = 0x7fffffff;
+    for (int i = 0; i < ns; i++)
+        if (rec[i].m > m) { m = rec[i].m; mi = rec[i].arg; }   // ascending slices: first occurrence kept
+    Z = 0.f;
+    for (int i = 0; i < ns; i++) Z += rec[i].z * expf(rec[i].m - m);
+}
+__global__ __launch_bounds__(VS_THREADS) void vocab_entropy_kernel(const float* __restrict__ logits, int V, int ns, float clamp,
+                                                                   float eps, VRec* __restrict__ rec)
+{
+    __shared__ float rv[VS_THREADS / 64];
+    const int sl = blockIdx.x, r = blockIdx.y, tid = threadIdx.x;
+    const float* z = logits + (size_t)r * V;
+    VRec* row = rec + (size_t)r * ns;
+    int b, e, mi;
+    float m, Z;
+    vs_slice(V, ns, sl, b, e);
+    vs_merge(row, ns, m, Z, mi);
+    const float invZ = 1.0f / Z;
+    float hs = 0.f;
+    for (int i = b + tid; i < e; i += VS_THREADS) {
+        const float pr = expf(fminf(fmaxf(z[i], -clamp), clamp) - m) * invZ;
+        hs -= pr * logf(pr + eps);
+    }
+    const float H = block_sum<VS_THREADS / 64>(hs, rv);
+    if (tid == 0) row[sl].h = H;   // (the other blocks of the row read m, z and arg only)
+}
+__global__ __launch_bounds__(64) void vocab_sum_kernel(const VRec* __restrict__ rec, int nb, int V, int ns, int32_t* argmax_out,
+                                                       float* maxprob_out, float* conf_out)
+{
+    const int r = blockIdx.x * 64 + threadIdx.x;
+    if (r >= nb) return;
+    const VRec* row = rec + (size_t)r * ns;
+    float m, Z, H = 0.f;
+    int mi;
+    vs_merge(row, ns, m, Z, mi);
+    for (int i = 0; i < ns; i++) H += row[i].h;
+    if (argmax_out) argmax_out[r] = mi;
+    if (maxprob_out) maxprob_out[r] = 1.0f / Z;
+    conf_out[r] = 1.0f - H / logf((float)V);
+}
+
+// Slices per row: 16, or what leaves at least 1024 logits to each and the scratch holds -- whatever the row count, so that
+// batches of different size give the same bits.  More than 256 rows fill the chip by themselves and a short vocabulary
+// is one quick block: those keep the one-block-per-row kernel.
+hipError_t vocab_confidence(const float* logits, int M, int V, float clamp, float eps, int32_t* argmax_out, float* maxprob_out,
+                            float* conf_out, void* scratch, size_t scratch_bytes, hipStream_t s)
+{
+    if (M < 1 || V < 1 || !conf_out) return hipErrorInvalidValue;
+    const int ns = (int)std::min<size_t>(std::min(V / 1024, 16), scratch ? scratch_bytes / ((size_t)M * sizeof(VRec)) : 0);
+    if (M > 256 || ns < 4) return vocab_reduce(logits, M, V, clamp, eps, nullptr, 1, argmax_out, maxprob_out, conf_out, s);
+    VRec* rec = static_cast<VRec*>(scratch);
+    hipLaunchKernelGGL(vocab_part_kernel, dim3(ns, M), dim3(VS_THREADS), 0, s, logits, V, ns, clamp, rec);
+    hipLaunchKernelGGL(vocab_entropy_kernel, dim3(ns, M), dim3(VS_THREADS), 0, s, logits, V, ns, clamp, eps, rec);
+    hipLaunchKernelGGL(vocab_sum_kernel, dim3(ceil_div(M, 64)), dim3(64), 0, s, rec, M, V, ns, argmax_out, maxprob_out, conf_out);
+    return hipGetLastError();
 }
 
 // means[t] = mean over p < n_pos of v[p * n_taps + t], summed in position order (one thread per tap row)

@@ -1,0 +1,48 @@
+"""GPU: kernels and dispatch branches at the sizes where they can go wrong, against the CPU oracle."""
+import numpy as np
+import pytest
+
+from oracle import OracleSSD
+from synth import ModelShape, make_prompt, make_weights
+from tests._parity import CONF_TOL, PROB_RTOL, make_pair, to_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+# vocabularies around the cut of the reduction: one block per row (fewer than four slices of 1024), the fewest slices,
+# ragged slices, sixteen of them; fp32 weights take the same reduction behind their own GEMM
+@pytest.mark.parametrize("vocab,dtype", [(3072, "bf16"), (4096, "bf16"), (4112, "fp16"), (20016, "bf16"), (5136, "fp32")])
+def test_confidence_reduction_over_vocabulary_slices(vocab, dtype):
+    shape = ModelShape(3, 256, 4, 4, 704, vocab, dtype=dtype)
+    orc, ctx = make_pair(shape, 21, 64, max_k=4, norm_gain_std=0.1, init_std=0.2 if dtype == "fp32" else 0.08)
+    prompt = make_prompt(vocab, 20, 3).tolist()
+    o = OracleSSD(orc)
+    o.prefill(prompt)
+    ctx.ssd_prefill(prompt)
+    conf_o, det = o.layer_confidence(0)
+    conf, g = ctx.ssd_layer_confidence(0, 1, detail=True)
+    np.testing.assert_allclose(conf[0], conf_o, atol=CONF_TOL[dtype])
+    np.testing.assert_allclose(g["maxprob"][0], det["maxprob"], rtol=PROB_RTOL[dtype] * 1.25)
+    np.testing.assert_array_equal(ctx.ssd_layer_confidence(0, 1, static=True), conf)
+
+
+@pytest.mark.parametrize("vocab", [512, 4112, 16400])
+def test_equal_maxima_give_the_lowest_token(vocab):
+    """Every row of the LM head exists twice: the greedy token of prompt, verify and decode passes is the lower one."""
+    import paper_2604_14612_amd as ssd
+    shape = ModelShape(2, 256, 4, 4, 704, vocab)
+    w = make_weights(shape, 5)
+    half = vocab // 2
+    w["lm_head"][half:] = w["lm_head"][:half]
+    ctx = ssd.Context(shape, to_gpu(w), 96, 8)
+    for plen in (5, 40):
+        ctx.ssd_reset()
+        toks = [ctx.ssd_prefill(make_prompt(vocab, plen, 4).tolist())]
+        d = ctx.ssd_draft_step(np.array([0, 1], np.uint8), 8)
+        y = ctx.ssd_verify(d)
+        toks += d + y
+        z = ctx.ssd_copy_logits(0, 9)
+        assert y == [int(np.argmax(r)) for r in z]
+        ctx.ssd_accept(d, y)
+        toks.append(ctx.ssd_decode())
+        assert max(toks) < half
