@@ -396,6 +396,40 @@ int forward_rows(ssd_ctx* c, int M, int pos_off, int pos_host, bool want_logits,
         }
         return SSD_OK;
     }
+    if (rows_plain_supported(D)) {
+        // fp32 weights (and fp16 shapes outside the tiling): fp32 rows between the launches, norms, rotary embedding and
+        // cache rows inside them
+        for (int l = 0; l < D.L; l++) {
+            RowsPlain q = {};
+            q.w[0] = c->wq[l]; q.w[1] = c->wk[l]; q.w[2] = c->wv[l]; q.n[0] = D.dq; q.n[1] = D.dkv; q.n[2] = D.dkv;
+            q.K = D.d; q.x = x; q.gain = c->attn_norm[l]; q.y = c->f(Y.qkv); q.ldy = D.dq; q.M = M; q.mode = 3;
+            q.rope = c->f(Y.rope); q.pos_dev = c->pos_dev(); q.pos_off = pos_off; q.kc = c->kcache(l); q.vc = c->vcache(l);
+            TIMED(SSD_K_ROWS_QKV, rows_plain(D, q, c->stream), "plain_qkv");
+            TIMED(SSD_K_ATTENTION, attention(D, c->f(Y.qkv), D.dq, c->kcache(l), c->vcache(l), c->pos_dev(), pos_off, pos_host, M,
+                                             c->f(Y.part), c->f(Y.att), nullptr, nullptr, c->stream), "attention");
+            RowsPlain o = {};
+            o.w[0] = c->wo[l]; o.n[0] = D.d; o.K = D.dq; o.x = c->f(Y.att); o.y = x; o.ldy = D.d; o.M = M; o.mode = 1;
+            o.tap = c->f(Y.taps) + ((size_t)l * 2 + 0) * D.d; o.tap_ld = tap_ld;
+            TIMED(SSD_K_ROWS_O, rows_plain(D, o, c->stream), "plain_o");
+            RowsPlain gu = {};
+            gu.w[0] = c->wg[l]; gu.w[1] = c->wu[l]; gu.n[0] = D.f; gu.n[1] = D.f; gu.K = D.d; gu.x = x; gu.gain = c->mlp_norm[l];
+            gu.y = c->f(Y.act); gu.ldy = D.f; gu.M = M; gu.mode = 2;
+            TIMED(SSD_K_ROWS_GATEUP, rows_plain(D, gu, c->stream), "plain_gateup");
+            RowsPlain dn = {};
+            dn.w[0] = c->wd[l]; dn.n[0] = D.d; dn.K = D.f; dn.x = c->f(Y.act); dn.y = x; dn.ldy = D.d; dn.M = M; dn.mode = 1;
+            dn.tap = c->f(Y.taps) + ((size_t)l * 2 + 1) * D.d; dn.tap_ld = tap_ld;
+            TIMED(SSD_K_ROWS_DOWN, rows_plain(D, dn, c->stream), "plain_down");
+        }
+        if (want_logits) {
+            RowsPlain lm = {};
+            lm.w[0] = c->w.lm_head; lm.n[0] = D.V; lm.K = D.d; lm.x = x; lm.gain = c->w.final_norm; lm.y = c->f(Y.logits);
+            lm.ldy = D.V; lm.M = M; lm.mode = 0;
+            TIMED(SSD_K_ROWS_LMHEAD, rows_plain(D, lm, c->stream), "plain_lmhead");
+            HIPCHK(vocab_reduce(c->f(Y.logits), M, D.V, c->cfg.conf_clamp, c->cfg.conf_eps, c->small_i() + SM_TARGET, 1,
+                                nullptr, nullptr, nullptr, c->stream), "vocab_reduce");
+        }
+        return SSD_OK;
+    }
     for (int l = 0; l < D.L; l++) {
         HIPCHK(rmsnorm_rows(x, c->attn_norm[l], M, D.d, D.eps, h, c->stream), "rmsnorm");
         RowsGemm g = {};
@@ -517,6 +551,13 @@ int conf_batch(ssd_ctx* c, const ConfScratch& sc, const float* taps, int nb, flo
                 lm.M = nb - b < 16 ? nb - b : 16; lm.mode = 0;
                 TIMED(SSD_K_ROWS_LMHEAD, rows_fused(D, lm, c->stream), "rows conf lmhead");
             }
+        }
+    } else if (rows_plain_supported(D)) {
+        for (int b = 0; b < nb; b += 16) {
+            RowsPlain lm = {};
+            lm.w[0] = c->w.lm_head; lm.n[0] = D.V; lm.K = D.d; lm.x = taps + (size_t)b * D.d; lm.gain = c->w.final_norm;
+            lm.y = sc.logits + (size_t)b * D.V; lm.ldy = D.V; lm.M = nb - b < 16 ? nb - b : 16; lm.mode = 0;
+            TIMED(SSD_K_ROWS_LMHEAD, rows_plain(D, lm, c->stream), "plain conf lmhead");
         }
     } else {
         HIPCHK(rmsnorm_rows(taps, c->w.final_norm, nb, D.d, D.eps, sc.tapn, c->stream), "rmsnorm taps");

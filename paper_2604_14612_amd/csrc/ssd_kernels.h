@@ -81,7 +81,7 @@ hipError_t gemv_lmhead_argmax(const Dims& D, const void* wlm, const float* gain,
 // ---- multi-row (verify / prefill / confidence) path ------------------------------------------
 // out[r][:] = rmsnorm(in[r][:], gain) for r < M   (rows of length K)
 hipError_t rmsnorm_rows(const float* in, const float* gain, int M, int K, float eps, float* out, hipStream_t s);
-// Y[r][n] (op)= sum_k W[n][k] X[r][k], r < M <= 16.  bf16 weights use MFMA tiles, fp32 weights plain FMAs.
+// Y[r][n] (op)= sum_k W[n][k] X[r][k], r < M <= 16, on MFMA tiles.
 //   mode 0: store to y (ld = N_total), up to three stacked matrices (QKV) written side by side
 //   mode 1: y += (residual add), optional tap copy (tap row stride tap_ld)
 //   mode 2: y = silu(W0 x) * (W1 x)  (two matrices of n0 rows each)
@@ -97,7 +97,24 @@ struct RowsGemm {
     int M;
     int mode;
 };
-hipError_t gemm_rows(const Dims& D, const RowsGemm& g, hipStream_t s);
+hipError_t gemm_rows(const Dims& D, const RowsGemm& g, hipStream_t s);   // bf16 weights
+// The same for fp32 / fp16 weights in fp32 arithmetic, with the RMSNorm of the input rows folded in (gain), and mode 3:
+// QKV with rotary embedding and cache rows (q -> y [M][dq]).  Modes 0 and 1 take one matrix.
+struct RowsPlain {
+    const void* w[3];
+    int n[3];
+    int K;
+    const float* x;
+    const float* gain;   // null: rows as they are
+    float* y; int ldy;
+    float* tap; int tap_ld;
+    int M;
+    int mode;
+    const float* rope; const int* pos_dev; int pos_off;
+    void* kc; void* vc;
+};
+bool rows_plain_supported(const Dims& D);
+hipError_t rows_plain(const Dims& D, const RowsPlain& g, hipStream_t s);
 // Multi-row MFMA GEMM for bf16 / fp16 weights with K a multiple of 64.  Activations come pre-split into
 // hi/lo arrays of the same 16-bit type [M][ldb] (rows_prep, rows_gain_split, attention with out_hi/out_lo, the SwiGLU mode
 // or a RESID projection with gain_out).

@@ -111,6 +111,30 @@ __device__ __forceinline__ float wave_max(float v)
     return v;
 }
 
+// v summed over the 16 lanes of a DPP row (rotations by 8, 4, 2, 1); every lane of the row gets the sum
+template <int CTRL> __device__ __forceinline__ float dpp_add(float v)
+{
+    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float row16_sum(float v)
+{
+    v = dpp_add<0x128>(v);  // row_ror:8
+    v = dpp_add<0x124>(v);  // row_ror:4
+    v = dpp_add<0x122>(v);  // row_ror:2
+    return dpp_add<0x121>(v);  // row_ror:1
+}
+template <int CTRL> __device__ __forceinline__ float dpp_max(float v)
+{
+    return fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false)));
+}
+__device__ __forceinline__ float row16_max(float v)
+{
+    v = dpp_max<0x128>(v);
+    v = dpp_max<0x124>(v);
+    v = dpp_max<0x122>(v);
+    return dpp_max<0x121>(v);
+}
+
 // Block-wide sum for blocks of NW waves; red must hold NW floats. All threads get the result.
 template <int NW>
 __device__ __forceinline__ float block_sum(float v, float* red)
@@ -993,86 +1017,198 @@ __global__ __launch_bounds__(MF_THREADS) void gemm_rows_mfma_kernel(RowsP p)
     }
 }
 
-// --- fp32 weights (and any dtype as a plain cross-check): FMA rows --------------------------------
-// One wave owns 4 consecutive output rows (RM_SWIGLU: 2 gate + 2 up rows) and up to 4 token rows at a time.
+// --- fp32 weights, and fp16 shapes outside the MFMA tiling: FMA rows ------------------------------------------------
+// One wave owns one pair of output rows (QKV: a rotary pair, or two value rows; SwiGLU: a gate row and its up row) and a
+// group of MG token rows, so that even the projections of a 256-wide model are spread over a few hundred waves, and a wave
+// has the loads of four steps in flight (what bounds these launches is latency, not bytes).  RMSNorm costs no launch: the
+// gain goes into the weights as they are loaded, the sums of squares are taken from the activations that pass by anyway,
+// and the row's scale is applied to the finished sums.  Rotary embedding and the cache rows are written by the epilogue.
+// Measured on the fp32 model of width 256 with five rows: residual projections 13.9 -> 5 us per launch, gate/up 8.3 -> 5,
+// five launches per layer instead of eight.
+constexpr int RM_QKV = 3;
+struct RowsPlainP {
+    const void* w[3];
+    int n[3];       // rows of each matrix (multiples of 16)
+    int K;
+    const float* x; // [M][K]
+    const float* gain; float eps;   // RMSNorm of the rows folded in (null: rows as they are)
+    float* y; int ldy;
+    float* tap; int tap_ld;
+    int M;
+    const float* rope; const int* pos_dev; int pos_off;   // QKV
+    int hd, dq, dkv, max_seq;
+    void* kc; void* vc; int kt;
+};
+
 template <typename WT, int MODE>
-__global__ __launch_bounds__(256) void gemm_rows_fma_kernel(RowsP p)
+__device__ __forceinline__ void plain_rows(const RowsPlainP& p, int u, const WT*& w0, const WT*& w1)
 {
-    constexpr int VEC = Elem<WT>::VEC;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int K = p.K;
-    const int n_out = MODE == RM_SWIGLU ? p.n[0] : p.n[0] + p.n[1] + p.n[2];
-    const int n_units = MODE == RM_SWIGLU ? n_out / 2 : n_out / 4;
-    for (int u = blockIdx.x * 4 + wave; u < n_units; u += gridDim.x * 4) {
-        const WT* wr[4];
-        size_t col[4];
-        if (MODE == RM_SWIGLU) {
-            size_t n = (size_t)u * 2;
-            wr[0] = (const WT*)p.w[0] + n * K; wr[1] = (const WT*)p.w[1] + n * K;
-            wr[2] = (const WT*)p.w[0] + (n + 1) * K; wr[3] = (const WT*)p.w[1] + (n + 1) * K;
-            col[0] = n; col[1] = n; col[2] = n + 1; col[3] = n + 1;
+    const size_t K = p.K;
+    if (MODE == RM_SWIGLU) { w0 = (const WT*)p.w[0] + u * K; w1 = (const WT*)p.w[1] + u * K; return; }
+    if (MODE == RM_QKV) {
+        const int j = 2 * u;
+        if (j < p.dq + p.dkv) {
+            const bool is_q = j < p.dq;
+            const int jj = is_q ? j : j - p.dq, head = jj / p.hd, i = (jj % p.hd) >> 1;
+            w0 = (const WT*)(is_q ? p.w[0] : p.w[1]) + (size_t)(head * p.hd + i) * K;
+            w1 = w0 + (p.hd >> 1) * K;
         } else {
-#pragma unroll
-            for (int r = 0; r < 4; r++) {
-                size_t n = (size_t)u * 4 + r;
-                col[r] = n;
-                if (n < (size_t)p.n[0]) wr[r] = (const WT*)p.w[0] + n * K;
-                else if (n < (size_t)(p.n[0] + p.n[1])) wr[r] = (const WT*)p.w[1] + (n - p.n[0]) * K;
-                else wr[r] = (const WT*)p.w[2] + (n - p.n[0] - p.n[1]) * K;
-            }
+            w0 = (const WT*)p.w[2] + (size_t)(j - p.dq - p.dkv) * K;
+            w1 = w0 + K;
         }
-        for (int m0 = 0; m0 < p.M; m0 += 4) {
-            float acc[4][4] = {};
-            for (int k = lane * VEC; k < K; k += 64 * VEC) {
-                float wv[4][VEC];
+        return;
+    }
+    w0 = (const WT*)p.w[0] + 2 * u * K;   // STORE, RESID: one matrix
+    w1 = w0 + K;
+}
+
+__device__ __forceinline__ float wave_sum_rows(float v)
+{
+    v = row16_sum(v);
+    v += __shfl_xor(v, 16, 64);
+    return v + __shfl_xor(v, 32, 64);
+}
+
+template <typename WT, int MODE, int MG>
+__global__ __launch_bounds__(256) void rows_plain_kernel(RowsPlainP p)
+{
+    constexpr int VEC = Elem<WT>::VEC, STEP = 64 * VEC, U = 4;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int K = p.K, m0 = blockIdx.y * MG, mg = min(MG, p.M - m0);
+    const int n_units = MODE == RM_SWIGLU ? p.n[0] : (p.n[0] + p.n[1] + p.n[2]) / 2;
+    for (int u = blockIdx.x * 4 + wave; u < n_units; u += gridDim.x * 4) {
+        const WT* w0; const WT* w1;
+        plain_rows<WT, MODE>(p, u, w0, w1);
+        float a0[MG], a1[MG], ss[MG];
 #pragma unroll
-                for (int r = 0; r < 4; r++) Elem<WT>::load(wr[r] + k, wv[r]);
+        for (int m = 0; m < MG; m++) a0[m] = a1[m] = ss[m] = 0.f;
+        for (int k0 = 0; k0 < K; k0 += U * STEP) {
+            float wa[U][VEC], wb[U][VEC];
 #pragma unroll
-                for (int m = 0; m < 4; m++) {
-                    if (m0 + m < p.M) {
-                        const float* xr = p.x + (size_t)(m0 + m) * K + k;
+            for (int t = 0; t < U; t++) {
+                const int k = k0 + t * STEP + lane * VEC, kc = min(k, K - VEC);   // lanes past the row re-read its end
+                Elem<WT>::load(w0 + kc, wa[t]);
+                Elem<WT>::load(w1 + kc, wb[t]);
+            }
+            if (p.gain) {
 #pragma unroll
-                        for (int j = 0; j < VEC; j++) {
-                            float xv = xr[j];
+                for (int t = 0; t < U; t++) {
+                    const int kc = min(k0 + t * STEP + lane * VEC, K - VEC);
 #pragma unroll
-                            for (int r = 0; r < 4; r++) acc[r][m] = fmaf(wv[r][j], xv, acc[r][m]);
+                    for (int j = 0; j < VEC; j++) {
+                        const float g = p.gain[kc + j];
+                        wa[t][j] *= g; wb[t][j] *= g;
+                    }
+                }
+            }
+#pragma unroll
+            for (int m = 0; m < MG; m++) {
+                if (m >= mg) break;   // uniform
+                const float* xr = p.x + (size_t)(m0 + m) * K;
+#pragma unroll
+                for (int t = 0; t < U; t++) {
+                    const int k = k0 + t * STEP + lane * VEC;
+                    if (k < K) {
+#pragma unroll
+                        for (int j = 0; j < VEC; j += 4) {
+                            const float4 x = *reinterpret_cast<const float4*>(xr + k + j);
+                            a0[m] = fmaf(wa[t][j], x.x, a0[m]); a0[m] = fmaf(wa[t][j + 1], x.y, a0[m]);
+                            a0[m] = fmaf(wa[t][j + 2], x.z, a0[m]); a0[m] = fmaf(wa[t][j + 3], x.w, a0[m]);
+                            a1[m] = fmaf(wb[t][j], x.x, a1[m]); a1[m] = fmaf(wb[t][j + 1], x.y, a1[m]);
+                            a1[m] = fmaf(wb[t][j + 2], x.z, a1[m]); a1[m] = fmaf(wb[t][j + 3], x.w, a1[m]);
+                            ss[m] += x.x * x.x + x.y * x.y + x.z * x.z + x.w * x.w;
                         }
                     }
                 }
             }
+        }
+        // every lane gets the sums; lane m finishes token row m0 + m
+        float a = 0.f, b = 0.f, sq = 0.f;
 #pragma unroll
-            for (int r = 0; r < 4; r++)
-#pragma unroll
-                for (int m = 0; m < 4; m++) acc[r][m] = wave_sum(acc[r][m]);
-            if (lane == 0) {
-                for (int m = 0; m < 4 && m0 + m < p.M; m++) {
-                    if (MODE == RM_SWIGLU) {
-                        rows_epilogue(p, MODE, m0 + m, col[0], acc[0][m], acc[1][m]);
-                        rows_epilogue(p, MODE, m0 + m, col[2], acc[2][m], acc[3][m]);
-                    } else {
-#pragma unroll
-                        for (int r = 0; r < 4; r++) rows_epilogue(p, MODE, m0 + m, col[r], acc[r][m], 0.f);
-                    }
+        for (int m = 0; m < MG; m++) {
+            const float ta = wave_sum_rows(a0[m]), tb = wave_sum_rows(a1[m]), ts = p.gain ? wave_sum_rows(ss[m]) : 0.f;
+            if (lane == m) { a = ta; b = tb; sq = ts; }
+        }
+        if (lane >= mg) continue;
+        if (p.gain) {
+            const float sc = 1.0f / sqrtf(sq / (float)K + p.eps);
+            a *= sc; b *= sc;
+        }
+        const int r = m0 + lane;
+        if (MODE == RM_SWIGLU) {
+            p.y[(size_t)r * p.ldy + u] = a / (1.0f + __expf(-a)) * b;
+        } else if (MODE == RM_QKV) {
+            const int j = 2 * u, pos = p.pos_dev[0] + p.pos_off + r;
+            if (j < p.dq + p.dkv) {
+                const bool is_q = j < p.dq;
+                const int jj = is_q ? j : j - p.dq, head = jj / p.hd, half = p.hd >> 1, i = (jj % p.hd) >> 1;
+                const float* cs = p.rope + ((size_t)pos * half + i) * 2;
+                const float ra = a * cs[0] - b * cs[1], rb = b * cs[0] + a * cs[1];
+                if (is_q) {
+                    float* q = p.y + (size_t)r * p.ldy + (size_t)head * p.hd + i;
+                    q[0] = ra; q[half] = rb;
+                } else {
+                    const size_t o = ((size_t)head * p.max_seq + pos) * p.hd + i;
+                    kv_put(p.kc, o, ra, p.kt);
+                    kv_put(p.kc, o + half, rb, p.kt);
                 }
+            } else {
+                const int e = j - p.dq - p.dkv;
+                const size_t o = ((size_t)(e / p.hd) * p.max_seq + pos) * p.hd + (e % p.hd);
+                kv_put(p.vc, o, a, p.kt);
+                kv_put(p.vc, o + 1, b, p.kt);
             }
+        } else {
+            float* y = p.y + (size_t)r * p.ldy + 2 * u;
+            if (MODE == RM_RESID) {
+                a += y[0]; b += y[1];
+                if (p.tap) { float* tp = p.tap + (size_t)r * p.tap_ld + 2 * u; tp[0] = a; tp[1] = b; }
+            }
+            y[0] = a; y[1] = b;
         }
     }
+}
+
+template <typename WT, int MODE>
+static hipError_t rows_plain_t(const RowsPlainP& p, hipStream_t s)
+{
+    const int units = MODE == RM_SWIGLU ? p.n[0] : (p.n[0] + p.n[1] + p.n[2]) / 2;
+    const int blocks = std::min(ceil_div(units, 4), 4096);
+    // token rows of a wave: four where that covers the launch, else eight (a second group of waves reads the weights again,
+    // from the caches)
+    if (p.M <= 4) hipLaunchKernelGGL((rows_plain_kernel<WT, MODE, 4>), dim3(blocks, 1), dim3(256), 0, s, p);
+    else hipLaunchKernelGGL((rows_plain_kernel<WT, MODE, 8>), dim3(blocks, ceil_div(p.M, 8)), dim3(256), 0, s, p);
+    return hipGetLastError();
+}
+
+bool rows_plain_supported(const Dims& D) { return D.wt != WT_BF16; }
+
+hipError_t rows_plain(const Dims& D, const RowsPlain& g, hipStream_t s)
+{
+    if (!rows_plain_supported(D) || g.M < 1 || g.M > 16 || g.K % 8) return hipErrorInvalidValue;
+    if (g.mode != RM_QKV && g.mode != RM_SWIGLU && (g.n[1] || g.n[2])) return hipErrorInvalidValue;
+    if (g.mode == RM_QKV && (g.n[0] != D.dq || g.n[1] != D.dkv || g.n[2] != D.dkv)) return hipErrorInvalidValue;
+    RowsPlainP p = {};
+    for (int i = 0; i < 3; i++) { p.w[i] = g.w[i]; p.n[i] = g.n[i]; }
+    p.K = g.K; p.x = g.x; p.gain = g.gain; p.eps = D.eps; p.y = g.y; p.ldy = g.ldy; p.tap = g.tap; p.tap_ld = g.tap_ld; p.M = g.M;
+    p.rope = g.rope; p.pos_dev = g.pos_dev; p.pos_off = g.pos_off; p.hd = D.hd; p.dq = D.dq; p.dkv = D.dkv; p.max_seq = D.max_seq;
+    p.kc = g.kc; p.vc = g.vc; p.kt = D.kt;
+    const bool f16 = D.wt == WT_F16;
+    switch (g.mode) {
+        case RM_STORE: return f16 ? rows_plain_t<f16_t, RM_STORE>(p, s) : rows_plain_t<float, RM_STORE>(p, s);
+        case RM_RESID: return f16 ? rows_plain_t<f16_t, RM_RESID>(p, s) : rows_plain_t<float, RM_RESID>(p, s);
+        case RM_SWIGLU: return f16 ? rows_plain_t<f16_t, RM_SWIGLU>(p, s) : rows_plain_t<float, RM_SWIGLU>(p, s);
+        case RM_QKV: return f16 ? rows_plain_t<f16_t, RM_QKV>(p, s) : rows_plain_t<float, RM_QKV>(p, s);
+    }
+    return hipErrorInvalidValue;
 }
 
 template <int MODE>
 static hipError_t gemm_rows_mode(const Dims& D, const RowsP& p, hipStream_t s)
 {
-    if (D.wt == WT_BF16) {
-        int tiles = MODE == RM_SWIGLU ? p.n[0] / 16 : (p.n[0] + p.n[1] + p.n[2]) / 16;
-        hipLaunchKernelGGL((gemm_rows_mfma_kernel<MODE>), dim3(tiles), dim3(MF_THREADS), 0, s, p);
-    } else {
-        int n_out = MODE == RM_SWIGLU ? p.n[0] : p.n[0] + p.n[1] + p.n[2];
-        int units = MODE == RM_SWIGLU ? n_out / 2 : n_out / 4;
-        int blocks = ceil_div(units, 4);
-        if (blocks > 4096) blocks = 4096;
-        if (D.wt == WT_F16) hipLaunchKernelGGL((gemm_rows_fma_kernel<f16_t, MODE>), dim3(blocks), dim3(256), 0, s, p);
-        else hipLaunchKernelGGL((gemm_rows_fma_kernel<float, MODE>), dim3(blocks), dim3(256), 0, s, p);
-    }
+    if (D.wt != WT_BF16) return hipErrorInvalidValue;   // the other types: rows_plain
+    int tiles = MODE == RM_SWIGLU ? p.n[0] / 16 : (p.n[0] + p.n[1] + p.n[2]) / 16;
+    hipLaunchKernelGGL((gemm_rows_mfma_kernel<MODE>), dim3(tiles), dim3(MF_THREADS), 0, s, p);
     return hipGetLastError();
 }
 
@@ -1101,8 +1237,6 @@ hipError_t gemm_rows(const Dims& D, const RowsGemm& g, hipStream_t s)
 //   * QKV mode orders the 16 rows of a tile as 8 rotary pairs (i, i + hd/2), so the epilogue can
 //     rotate q and k and write k, v straight into the cache; SwiGLU mode writes its result
 //     directly as the hi/lo pair the down projection consumes.
-constexpr int RM_QKV = 3;
-
 struct RowsP2 {
     const void* w[3];
     int n[3];  // rows of each stacked matrix (multiples of 16); SWIGLU: n[0] = n[1] = f
@@ -1160,30 +1294,6 @@ __device__ __forceinline__ const uint16_t* m2_row(const RowsP2& p, int tile, int
     row -= p.n[0];
     if (row < p.n[1]) return (const uint16_t*)p.w[1] + (size_t)row * p.K;
     return (const uint16_t*)p.w[2] + (size_t)(row - p.n[1]) * p.K;
-}
-
-// v summed over the 16 lanes of a DPP row (rotations by 8, 4, 2, 1); every lane of the row gets the sum
-template <int CTRL> __device__ __forceinline__ float dpp_add(float v)
-{
-    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
-}
-__device__ __forceinline__ float row16_sum(float v)
-{
-    v = dpp_add<0x128>(v);  // row_ror:8
-    v = dpp_add<0x124>(v);  // row_ror:4
-    v = dpp_add<0x122>(v);  // row_ror:2
-    return dpp_add<0x121>(v);  // row_ror:1
-}
-template <int CTRL> __device__ __forceinline__ float dpp_max(float v)
-{
-    return fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false)));
-}
-__device__ __forceinline__ float row16_max(float v)
-{
-    v = dpp_max<0x128>(v);
-    v = dpp_max<0x124>(v);
-    v = dpp_max<0x122>(v);
-    return dpp_max<0x121>(v);
 }
 
 // Final step of a tile: sum the KS per-wave partial tiles held in LDS (layout [wave][NT][256], element
