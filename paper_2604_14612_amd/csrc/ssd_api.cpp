@@ -243,10 +243,14 @@ int layer_single(ssd_ctx* c, int l, int pos_off, bool do_attn, bool do_mlp)
 // Single-row forward of the token in tok slot `slot` at position *pos + pos_off; the greedy token goes to
 // tok slot `slot_out`, its logits to logits row `lrow`, its max-probability to SM_MAXPROB[lrow].
 // sub (may be null): two entries per layer, [2l] != 0 leaves out the attention sub-block, [2l+1] != 0 the MLP sub-block.
-int forward_single(ssd_ctx* c, const uint8_t* sub, int slot, int slot_out, int pos_off, int lrow)
+// flags: STEP_CHAINED = the previous step of the same sequence left this token's embedding in x; STEP_CHAIN_NEXT = leave
+// the new token's embedding there; STEP_COMMIT = the new token becomes the pending one and *pos advances.
+enum { STEP_CHAINED = 1, STEP_CHAIN_NEXT = 2, STEP_COMMIT = 4 };
+int forward_single(ssd_ctx* c, const uint8_t* sub, int slot, int slot_out, int pos_off, int lrow, int flags)
 {
     const Dims& D = c->D;
-    HIPCHK(embed_rows(D, c->w.embed, c->small_i() + SM_TOK + slot, 1, c->f(c->lay.x), c->stream), "embed");
+    if (!(flags & STEP_CHAINED))
+        HIPCHK(embed_rows(D, c->w.embed, c->small_i() + SM_TOK + slot, 1, c->f(c->lay.x), c->stream), "embed");
     for (int l = 0; l < D.L; l++) {
         const bool do_attn = !(sub && sub[2 * l]), do_mlp = !(sub && sub[2 * l + 1]);
         if (!do_attn && !do_mlp) continue;
@@ -254,11 +258,15 @@ int forward_single(ssd_ctx* c, const uint8_t* sub, int slot, int slot_out, int p
         if (rc) return rc;
     }
     float* logits = c->f(c->lay.logits) + (size_t)lrow * D.V;
+    StepOut out = {};
+    out.tok_out = c->small_i() + SM_TOK + slot_out;
+    out.maxprob_out = c->small_f() + SM_MAXPROB + lrow;
+    if (flags & STEP_COMMIT) { out.pos_dev = c->pos_dev(); out.tok0 = c->small_i() + SM_TOK; }
+    if (flags & STEP_CHAIN_NEXT) { out.embed = c->w.embed; out.x_next = c->f(c->lay.x); }
     // LM head with the greedy token and its soft-max probability folded in (block statistics in the attention
     // scratch, which is idle here, then a one-block fold)
     TIMED(SSD_K_GEMV_LMHEAD, gemv_lmhead_argmax(D, c->w.lm_head, c->w.final_norm, c->f(c->lay.x), logits, c->cfg.conf_clamp,
-                                                c->f(c->lay.part), c->small_i() + SM_TOK + slot_out,
-                                                c->small_f() + SM_MAXPROB + lrow, c->stream), "gemv_lmhead");
+                                                c->f(c->lay.part), out, c->stream), "gemv_lmhead");
     return SSD_OK;
 }
 
@@ -285,7 +293,7 @@ int forward_rows(ssd_ctx* c, int M, int pos_off, int pos_host, bool want_logits,
     const Layout& Y = c->lay;
     float* x = c->f(Y.x);
     float* h = c->f(Y.h);
-    HIPCHK(embed_rows(D, c->w.embed, tok_dev ? tok_dev : c->small_i() + SM_VTOK, M, x, c->stream), "embed");
+    if (!tok_dev) tok_dev = c->small_i() + SM_VTOK;
     const int tap_ld = D.L * 2 * D.d;
     if (M > 16) {
         // prompt block: the same sequence as the 16-row path below, on 128 x 128 tiles over all rows of the block at
@@ -301,7 +309,7 @@ int forward_rows(ssd_ctx* c, int M, int pos_off, int pos_host, bool want_logits,
         uint16_t* xl = xh + (size_t)Y.rows * D.d;
         float* ssq = c->f(Y.ssq);
         const int n_ssq = D.d / 64;
-        HIPCHK(rows_gain_split(D, x, D.d, c->attn_norm[0], M, D.d, xh, xl, ssq, 64, c->stream), "rows_gain_split");
+        HIPCHK(embed_split(D, c->w.embed, tok_dev, M, c->attn_norm[0], x, xh, xl, ssq, 64, c->stream), "embed_split");
         for (int l = 0; l < D.L; l++) {
             RowsFused q = {};
             q.w[0] = c->wq[l]; q.w[1] = c->wk[l]; q.w[2] = c->wv[l]; q.n[0] = D.dq; q.n[1] = D.dkv; q.n[2] = D.dkv;
@@ -357,7 +365,7 @@ int forward_rows(ssd_ctx* c, int M, int pos_off, int pos_host, bool want_logits,
         uint16_t* xl = xh + (size_t)Y.rows * D.d;
         float* ssq = c->f(Y.ssq);
         const int n_ssq = D.d / 16;
-        HIPCHK(rows_gain_split(D, x, D.d, c->attn_norm[0], M, D.d, xh, xl, ssq, 16, c->stream), "rows_gain_split");
+        HIPCHK(embed_split(D, c->w.embed, tok_dev, M, c->attn_norm[0], x, xh, xl, ssq, 16, c->stream), "embed_split");
         for (int l = 0; l < D.L; l++) {
             RowsFused q = {};
             q.w[0] = c->wq[l]; q.w[1] = c->wk[l]; q.w[2] = c->wv[l]; q.n[0] = D.dq; q.n[1] = D.dkv; q.n[2] = D.dkv;
@@ -396,6 +404,7 @@ int forward_rows(ssd_ctx* c, int M, int pos_off, int pos_host, bool want_logits,
         }
         return SSD_OK;
     }
+    HIPCHK(embed_rows(D, c->w.embed, tok_dev, M, x, c->stream), "embed");
     if (rows_plain_supported(D)) {
         // fp32 weights (and fp16 shapes outside the tiling): fp32 rows between the launches, norms, rotary embedding and
         // cache rows inside them
@@ -810,10 +819,7 @@ int ssd_decode(ssd_ctx* c, int32_t* token_out)
     // pending token sits in tok slot 0; its successor is written to slot 1, then promoted
     std::string key = "D|" + std::to_string(attention_splits(c->D, c->n, 1));
     int rc = run_sequence(c, key, [&]() {
-        int r = forward_single(c, nullptr, 0, 1, 0, 0);
-        if (r) return r;
-        HIPCHK(advance_state(c->pos_dev(), 1, c->small_i() + SM_TOK, c->small_i() + SM_TOK + 1, c->stream), "advance_state");
-        return (int)SSD_OK;
+        return forward_single(c, nullptr, 0, 1, 0, 0, STEP_COMMIT);
     });
     if (rc) return rc;
     rc = readback(c, c->small_i() + SM_TOK + 1, sizeof(int32_t), token_out);
@@ -836,7 +842,7 @@ static int draft_fixed(ssd_ctx* c, const std::vector<uint8_t>& sub, int k, int32
     for (int i = 0; i < k; i++) key += std::to_string(attention_splits(c->D, c->n + i, 1)) + ",";
     int rc = run_sequence(c, key, [&]() {
         for (int i = 0; i < k; i++) {
-            int r = forward_single(c, sub.data(), i, i + 1, i, i);
+            int r = forward_single(c, sub.data(), i, i + 1, i, i, (i ? STEP_CHAINED : 0) | (i + 1 < k ? STEP_CHAIN_NEXT : 0));
             if (r) return r;
         }
         return (int)SSD_OK;
@@ -894,7 +900,7 @@ int ssd_draft_adaptive(ssd_ctx* c, const uint8_t* skip_mask, int k_max, float ga
         // one draft step per submission: the host reads the step's max-probability before deciding on the next
         const int i = k;
         std::string key = "A|" + std::to_string(i) + "|" + mask_key + "|" + std::to_string(attention_splits(c->D, c->n + i, 1));
-        int rc = run_sequence(c, key, [&]() { return forward_single(c, sub.data(), i, i + 1, i, i); });
+        int rc = run_sequence(c, key, [&]() { return forward_single(c, sub.data(), i, i + 1, i, i, 0); });
         if (rc) return rc;
         float p = 0.f;
         rc = readback(c, c->small_f() + SM_MAXPROB + i, sizeof(float), &p);

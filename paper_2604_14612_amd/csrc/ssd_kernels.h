@@ -71,12 +71,18 @@ hipError_t gemv_swiglu(const Dims& D, const void* wg, const void* wu, const floa
 hipError_t gemv_lmhead(const Dims& D, const void* wlm, const float* gain, const float* x, float* logits,
                        hipStream_t s);
 
-// The same with the vocabulary reduction of a greedy step folded in: every block also leaves (max, sum of exp,
-// arg-max) of its clamped logits in vstat (3 floats per block, GEMV_MAX_BLOCKS blocks at most) and a one-block
-// kernel combines them into the greedy token (lowest index among equal maxima) and its soft-max probability.
+// The same with the end of a greedy step folded in: every block also leaves (max, sum of exp, arg-max) of its clamped
+// logits in vstat (3 floats per block, GEMV_MAX_BLOCKS blocks at most) and a one-block kernel combines them into the greedy
+// token (lowest index among equal maxima) and its soft-max probability, and prepares the next step.
+struct StepOut {
+    int32_t* tok_out;
+    float* maxprob_out;        // may be null
+    int* pos_dev; int32_t* tok0;   // decode: *pos_dev += 1, *tok0 = token (both null: left alone)
+    const void* embed; float* x_next;   // x_next set: x_next[0..d) = embedding row of the token
+};
 constexpr int GEMV_MAX_BLOCKS = 1024;
 hipError_t gemv_lmhead_argmax(const Dims& D, const void* wlm, const float* gain, const float* x, float* logits, float clamp,
-                              float* vstat, int32_t* tok_out, float* maxprob_out, hipStream_t s);
+                              float* vstat, const StepOut& out, hipStream_t s);
 
 // ---- multi-row (verify / prefill / confidence) path ------------------------------------------
 // out[r][:] = rmsnorm(in[r][:], gain) for r < M   (rows of length K)
@@ -116,7 +122,7 @@ struct RowsPlain {
 bool rows_plain_supported(const Dims& D);
 hipError_t rows_plain(const Dims& D, const RowsPlain& g, hipStream_t s);
 // Multi-row MFMA GEMM for bf16 / fp16 weights with K a multiple of 64.  Activations come pre-split into
-// hi/lo arrays of the same 16-bit type [M][ldb] (rows_prep, rows_gain_split, attention with out_hi/out_lo, the SwiGLU mode
+// hi/lo arrays of the same 16-bit type [M][ldb] (rows_prep, embed_split, attention with out_hi/out_lo, the SwiGLU mode
 // or a RESID projection with gain_out).
 //   mode 0 store fp32, 1 residual add into y (+ tap), 2 SwiGLU of two matrices written as hi/lo to
 //   oh/ol, 3 QKV: rotary on q and k at positions *pos_dev + pos_off + r, q -> y [M][dq] fp32,
@@ -162,10 +168,11 @@ hipError_t rows_wide(const Dims& D, const RowsFused& f, hipStream_t s);
 // gain first when gain != nullptr
 hipError_t rows_prep(const Dims& D, const float* in, int ldx, const float* gain, int M, int K, float eps, uint16_t* hi,
                      uint16_t* lo, hipStream_t s);
-// hi/lo = split(in * gain) (no norm scale) and ssq[r][t] = sum of in[r][group t .. group (t+1))^2, group = 16
-// (rows_fused) or 64 (rows_wide): the form in which a RESID projection with gain_out hands rows to its consumer
-hipError_t rows_gain_split(const Dims& D, const float* in, int ldx, const float* gain, int M, int K, uint16_t* hi, uint16_t* lo,
-                           float* ssq, int group, hipStream_t s);
+// x[r] = embedding row of token r (16-bit weights, d a multiple of 64), hi/lo = split(x * gain) (no norm scale) and ssq[r][t] = sum of x[r][group t .. group (t+1))^2,
+// group = 16 (rows_fused) or 64 (rows_wide, rows_big): the form in which a RESID projection with gain_out hands rows to
+// its consumer
+hipError_t embed_split(const Dims& D, const void* embed, const int32_t* tok_dev, int M, const float* gain, float* x, uint16_t* hi,
+                       uint16_t* lo, float* ssq, int group, hipStream_t s);
 // rotary on q,k rows + cache write for the multi-row path. qkv: [M][dq + 2 dkv]; q is rotated in place.
 hipError_t rope_kv_rows(const Dims& D, float* qkv, const float* rope, const int* pos_dev, int pos_off, int M,
                         void* kcache_l, void* vcache_l, hipStream_t s);
@@ -196,7 +203,7 @@ hipError_t vocab_reduce(const float* logits, int M, int V, float clamp, float ep
 // tok_out[r] = lowest column of the largest clamped logit of row r, from the vmax records of a rows_fused LM-head launch
 hipError_t argmax_tiles(const float2* vmax, int M, int n_tiles, int32_t* tok_out, hipStream_t s);
 // Confidence, max-probability and arg-max of M rows as vocab_reduce gives them, cut along the vocabulary where the rows
-// alone leave the chip idle; scratch (may be null: never cut) takes 16 bytes per row and slice.
+// alone leave the chip idle; scratch (may be null: never cut) takes 24 bytes per row and slice.
 hipError_t vocab_confidence(const float* logits, int M, int V, float clamp, float eps, int32_t* argmax_out, float* maxprob_out,
                             float* conf_out, void* scratch, size_t scratch_bytes, hipStream_t s);
 

@@ -135,16 +135,17 @@ __device__ __forceinline__ float row16_max(float v)
     return dpp_max<0x121>(v);
 }
 
-// Block-wide sum for blocks of NW waves; red must hold NW floats. All threads get the result.
-template <int NW>
-__device__ __forceinline__ float block_sum(float v, float* red)
+// Block-wide sum for blocks of NW waves; red must hold NW values. All threads get the result.
+template <int NW, typename T>
+__device__ __forceinline__ T block_sum(T v, T* red)
 {
-    v = wave_sum(v);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
     int w = threadIdx.x >> 6;
     __syncthreads();
     if ((threadIdx.x & 63) == 0) red[w] = v;
     __syncthreads();
-    float t = 0.f;
+    T t = 0;
 #pragma unroll
     for (int i = 0; i < NW; i++) t += red[i];
     return t;
@@ -659,33 +660,48 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_kernel(GemvP p)
     }
 }
 
-// Combines the per-block statistics of an LM-head launch: arg-max (lowest index among equal maxima) and the
-// soft-max probability of that token, 1 / sum exp(z - max).
-__global__ __launch_bounds__(256) void vocab_finish_kernel(const float* __restrict__ vstat, int n_blocks, int32_t* tok_out,
-                                                           float* maxprob_out)
+// End of a single-row step: combines the per-block statistics of the LM-head launch into the greedy token (lowest index
+// among equal maxima) and its soft-max probability 1 / sum exp(z - max), and does in the same launch what the next step
+// would otherwise need a launch of its own for (about 4 us each in a replayed sequence): the position and the pending token
+// of a decode step, or the embedding row that the next draft step starts from.
+constexpr int SF_THREADS = 1024;
+template <typename WT>
+__global__ __launch_bounds__(SF_THREADS) void step_finish_kernel(const float* __restrict__ vstat, int n_blocks, int32_t* tok_out,
+                                                                 float* maxprob_out, int* pos_dev, int32_t* tok0,
+                                                                 const WT* __restrict__ E, int d, float* __restrict__ x)
 {
-    __shared__ float sm[256 * 3];
+    __shared__ VStat sm[SF_THREADS / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    auto wave_merge = [](VStat& a) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            const VStat b = {__shfl_xor(a.m, o, 64), __shfl_xor(a.z, o, 64), __shfl_xor(a.arg, o, 64)};
+            vstat_merge(a, b);
+        }
+    };
     VStat a = {-INFINITY, 0.f, 0x7fffffff};
-    for (int i = threadIdx.x; i < n_blocks; i += 256) {
+    for (int i = tid; i < n_blocks; i += SF_THREADS) {
         const VStat b = {vstat[i * 3], vstat[i * 3 + 1], __float_as_int(vstat[i * 3 + 2])};
         vstat_merge(a, b);
     }
-    sm[threadIdx.x * 3] = a.m; sm[threadIdx.x * 3 + 1] = a.z; sm[threadIdx.x * 3 + 2] = __int_as_float(a.arg);
+    wave_merge(a);
+    if (lane == 0) sm[wave] = a;
     __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) {
-            VStat x = {sm[threadIdx.x * 3], sm[threadIdx.x * 3 + 1], __float_as_int(sm[threadIdx.x * 3 + 2])};
-            const int j = threadIdx.x + o;
-            const VStat y = {sm[j * 3], sm[j * 3 + 1], __float_as_int(sm[j * 3 + 2])};
-            vstat_merge(x, y);
-            sm[threadIdx.x * 3] = x.m; sm[threadIdx.x * 3 + 1] = x.z; sm[threadIdx.x * 3 + 2] = __int_as_float(x.arg);
+    if (wave == 0) {
+        a = lane < SF_THREADS / 64 ? sm[lane] : VStat{-INFINITY, 0.f, 0x7fffffff};
+        wave_merge(a);
+        if (lane == 0) {
+            sm[0] = a;
+            tok_out[0] = a.arg;
+            if (maxprob_out) maxprob_out[0] = 1.0f / a.z;
+            if (pos_dev) { pos_dev[0] += 1; tok0[0] = a.arg; }
         }
-        __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        if (tok_out) tok_out[0] = __float_as_int(sm[2]);
-        if (maxprob_out) maxprob_out[0] = 1.0f / sm[1];
-    }
+    if (!x) return;   // uniform
+    __syncthreads();
+    const WT* row = E + (size_t)sm[0].arg * d;
+    for (int i = tid * 4; i < d; i += SF_THREADS * 4)
+        *reinterpret_cast<float4*>(x + i) = make_float4(Elem<WT>::get(row, i), Elem<WT>::get(row, i + 1), Elem<WT>::get(row, i + 2), Elem<WT>::get(row, i + 3));
 }
 
 // Largest dynamic LDS size a kernel has been enabled for.  A process-wide cache of an idempotent runtime call
@@ -852,9 +868,9 @@ hipError_t gemv_lmhead(const Dims& D, const void* wlm, const float* gain, const 
 }
 
 hipError_t gemv_lmhead_argmax(const Dims& D, const void* wlm, const float* gain, const float* x, float* logits, float clamp,
-                              float* vstat, int32_t* tok_out, float* maxprob_out, hipStream_t s)
+                              float* vstat, const StepOut& o, hipStream_t s)
 {
-    if (!vstat) return hipErrorInvalidValue;
+    if (!vstat || !o.tok_out || (o.pos_dev && !o.tok0) || (o.x_next && !o.embed)) return hipErrorInvalidValue;
     GemvP p = {};
     p.w0 = wlm; p.in = x; p.gain = gain; p.eps = D.eps; p.K = D.d; p.n_rows = D.V; p.y = logits;
     p.vstat = vstat; p.clamp = clamp;
@@ -862,7 +878,15 @@ hipError_t gemv_lmhead_argmax(const Dims& D, const void* wlm, const float* gain,
     hipError_t e = launch_gemv<EPI_STORE>(D, p, s, &blocks);
     if (e != hipSuccess) return e;
     if (blocks < 1 || blocks > GEMV_MAX_BLOCKS) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(vocab_finish_kernel, dim3(1), dim3(256), 0, s, vstat, blocks, tok_out, maxprob_out);
+    if (D.wt == WT_BF16)
+        hipLaunchKernelGGL(step_finish_kernel<uint16_t>, dim3(1), dim3(SF_THREADS), 0, s, vstat, blocks, o.tok_out, o.maxprob_out,
+                           o.pos_dev, o.tok0, (const uint16_t*)o.embed, D.d, o.x_next);
+    else if (D.wt == WT_F16)
+        hipLaunchKernelGGL(step_finish_kernel<f16_t>, dim3(1), dim3(SF_THREADS), 0, s, vstat, blocks, o.tok_out, o.maxprob_out,
+                           o.pos_dev, o.tok0, (const f16_t*)o.embed, D.d, o.x_next);
+    else
+        hipLaunchKernelGGL(step_finish_kernel<float>, dim3(1), dim3(SF_THREADS), 0, s, vstat, blocks, o.tok_out, o.maxprob_out,
+                           o.pos_dev, o.tok0, (const float*)o.embed, D.d, o.x_next);
     return hipGetLastError();
 }
 
@@ -2415,37 +2439,52 @@ hipError_t rows_prep(const Dims& D, const float* in, int ldx, const float* gain,
     return hipGetLastError();
 }
 
-// Entry of the fused path (rows straight from the embedding): hi/lo = split(x * gain) without the
-// norm scale, and the sums of squares of every `group` (16 or 64) consecutive elements, i.e. exactly what a
-// RESID projection with tiles of that width leaves behind for its consumer.
-__global__ __launch_bounds__(256) void rows_gain_split_kernel(const float* __restrict__ in, int ldx,
-                                                              const float* __restrict__ gain, int K,
-                                                              uint16_t* __restrict__ hi, uint16_t* __restrict__ lo,
-                                                              float* __restrict__ ssq, bool f16, int group)
+// Entry of the fused path: the embedding rows of M tokens as fp32 rows x and as what a RESID projection leaves behind for
+// its consumer, hi/lo = split(x * gain) without the norm scale and the sums of squares of every GROUP (16 or 64)
+// consecutive elements.  A thread owns four elements, a block 1024 of one row.  (As two launches, a gather and a split in
+// which one thread walked a whole group: 9.7 + 12 us for 512 rows of 4096, 4.5 + 3.6 us for five.)
+template <typename WT, int GROUP>
+__global__ __launch_bounds__(256) void embed_split_kernel(const WT* __restrict__ E, const int32_t* __restrict__ tok_dev, int d, int V,
+                                                          const float* __restrict__ gain, float* __restrict__ x,
+                                                          uint16_t* __restrict__ hi, uint16_t* __restrict__ lo,
+                                                          float* __restrict__ ssq)
 {
-    const float* x = in + (size_t)blockIdx.x * ldx;
-    const int n_t = K / group;
-    for (int t = threadIdx.x; t < n_t; t += 256) {
-        float sq = 0.f;
-        for (int u = 0; u < group; u += 4) {
-            const int i = t * group + u;
-            const float4 v = *reinterpret_cast<const float4*>(x + i);
-            const float4 g = *reinterpret_cast<const float4*>(gain + i);
-            sq += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
-            const size_t o = (size_t)blockIdx.x * K + i;
-            split_store(v.x * g.x, hi, lo, o, f16); split_store(v.y * g.y, hi, lo, o + 1, f16);
-            split_store(v.z * g.z, hi, lo, o + 2, f16); split_store(v.w * g.w, hi, lo, o + 3, f16);
-        }
-        ssq[(size_t)blockIdx.x * n_t + t] = sq;
+    constexpr bool F16 = IsF16<WT>::value;
+    const int r = blockIdx.y, i = (blockIdx.x * 256 + threadIdx.x) * 4;
+    if (i >= d) return;   // whole DPP rows: d is a multiple of 64
+    const int t = min(max(tok_dev[r], 0), V - 1);
+    const uint2 w = *reinterpret_cast<const uint2*>(E + (size_t)t * d + i);
+    const float4 g = *reinterpret_cast<const float4*>(gain + i);
+    const float4 v = make_float4(h16_bits_to_f32(w.x & 0xffff, F16), h16_bits_to_f32(w.x >> 16, F16),
+                                 h16_bits_to_f32(w.y & 0xffff, F16), h16_bits_to_f32(w.y >> 16, F16));
+    const size_t o = (size_t)r * d + i;
+    *reinterpret_cast<float4*>(x + o) = v;
+    const float y[4] = {v.x * g.x, v.y * g.y, v.z * g.z, v.w * g.w};
+    unsigned h[4], l[4];
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        h[j] = f32_to_h16_bits(y[j], F16);
+        l[j] = f32_to_h16_bits(y[j] - h16_bits_to_f32(h[j], F16), F16);
     }
+    *reinterpret_cast<uint2*>(hi + o) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
+    *reinterpret_cast<uint2*>(lo + o) = make_uint2(l[0] | (l[1] << 16), l[2] | (l[3] << 16));
+    float sq = v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+    if (GROUP == 64) sq = row16_sum(sq);                       // 16 lanes of four elements
+    else sq = dpp_add<0x4E>(dpp_add<0xB1>(sq));                // the four lanes of a quad
+    if ((i & (GROUP - 1)) == 0) ssq[(size_t)r * (d / GROUP) + i / GROUP] = sq;
 }
 
-hipError_t rows_gain_split(const Dims& D, const float* in, int ldx, const float* gain, int M, int K, uint16_t* hi, uint16_t* lo,
-                           float* ssq, int group, hipStream_t s)
+hipError_t embed_split(const Dims& D, const void* embed, const int32_t* tok_dev, int M, const float* gain, float* x, uint16_t* hi,
+                       uint16_t* lo, float* ssq, int group, hipStream_t s)
 {
-    if ((group != 16 && group != 64) || K % group || !gain) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(rows_gain_split_kernel, dim3(M), dim3(256), 0, s, in, ldx, gain, K, hi, lo, ssq, D.wt == WT_F16, group);
-    return hipGetLastError();
+    if ((group != 16 && group != 64) || D.d % 64 || D.wt == WT_F32 || !gain || M < 1) return hipErrorInvalidValue;
+    const dim3 grid(ceil_div(D.d, 1024), M);
+    auto go = [&](auto kernel, auto e) {
+        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, e, tok_dev, D.d, D.V, gain, x, hi, lo, ssq);
+        return hipGetLastError();
+    };
+    if (D.wt == WT_F16) return group == 16 ? go(embed_split_kernel<f16_t, 16>, (const f16_t*)embed) : go(embed_split_kernel<f16_t, 64>, (const f16_t*)embed);
+    return group == 16 ? go(embed_split_kernel<uint16_t, 16>, (const uint16_t*)embed) : go(embed_split_kernel<uint16_t, 64>, (const uint16_t*)embed);
 }
 
 // rotary + cache write for the multi-row path: one thread per (row, head slot, pair index)
@@ -3585,6 +3624,7 @@ __global__ __launch_bounds__(VR_THREADS) void vocab_reduce_kernel(const float* _
 {
     __shared__ float rv[16];
     __shared__ int ri[16];
+    __shared__ double rd[16];
     const int r = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const float* z = logits + (size_t)r * V;
     // pass 1: max and its lowest index
@@ -3604,24 +3644,25 @@ __global__ __launch_bounds__(VR_THREADS) void vocab_reduce_kernel(const float* _
         if (om > m || (om == m && oi < mi)) { m = om; mi = oi; }
     }
     // pass 2: Z = sum exp(z - m)
-    float zs = 0.f;
+    // (both sums in 64 bits: a rounding error of Z or H moves every confidence of the row)
+    double zs = 0.0;
     for (int i = tid; i < V; i += VR_THREADS) zs += expf(fminf(fmaxf(z[i], -clamp), clamp) - m);
-    float Z = block_sum<16>(zs, rv);
+    const double Z = block_sum<16>(zs, rd);
     if (tid == 0) {
         if (tok_out) tok_out[(size_t)r * tok_stride] = mi;
         if (argmax_out) argmax_out[r] = mi;
-        if (maxprob_out) maxprob_out[r] = 1.0f / Z;
+        if (maxprob_out) maxprob_out[r] = (float)(1.0 / Z);
     }
     if (conf_out) {
         // pass 3: H = -sum p log(p + eps)
-        float hs = 0.f;
-        const float invZ = 1.0f / Z;
+        double hs = 0.0;
+        const double invZ = 1.0 / Z;
         for (int i = tid; i < V; i += VR_THREADS) {
-            float pr = expf(fminf(fmaxf(z[i], -clamp), clamp) - m) * invZ;
-            hs -= pr * logf(pr + eps);
+            const double pr = expf(fminf(fmaxf(z[i], -clamp), clamp) - m) * invZ;
+            hs -= pr * logf((float)pr + eps);
         }
-        float Hs = block_sum<16>(hs, rv);
-        if (tid == 0) conf_out[r] = 1.0f - Hs / logf((float)V);
+        const double Hs = block_sum<16>(hs, rd);
+        if (tid == 0) conf_out[r] = (float)(1.0 - Hs / log((double)V));
     }
 }
 
@@ -3663,7 +3704,7 @@ hipError_t argmax_tiles(const float2* vmax, int M, int n_tiles, int32_t* tok_out
 // entropy, a third adds the slices.  One block per row walks 32 000 logits three times in 27 us while most CUs idle (16
 // or 64 rows); the three short launches take about 11 us together.
 constexpr int VS_THREADS = 256;
-struct VRec { float m, z; int arg; float h; };
+struct VRec { double z, h; float m; int arg; };   // sums in 64 bits, as above
 
 __device__ __forceinline__ void vs_slice(int V, int ns, int sl, int& b, int& e)
 {
@@ -3675,6 +3716,7 @@ __global__ __launch_bounds__(VS_THREADS) void vocab_part_kernel(const float* __r
 {
     __shared__ float rv[VS_THREADS / 64];
     __shared__ int ri[VS_THREADS / 64];
+    __shared__ double rd[VS_THREADS / 64];
     const int sl = blockIdx.x, r = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const float* z = logits + (size_t)r * V;
     int b, e;
@@ -3692,38 +3734,39 @@ __global__ __launch_bounds__(VS_THREADS) void vocab_part_kernel(const float* __r
 #pragma unroll
     for (int w = 1; w < VS_THREADS / 64; w++)
         if (rv[w] > m || (rv[w] == m && ri[w] < mi)) { m = rv[w]; mi = ri[w]; }
-    float zs = 0.f;
+    double zs = 0.0;
     for (int i = b + tid; i < e; i += VS_THREADS) zs += expf(fminf(fmaxf(z[i], -clamp), clamp) - m);
-    const float Z = block_sum<VS_THREADS / 64>(zs, rv);
-    if (tid == 0) rec[(size_t)r * ns + sl] = VRec{m, Z, mi, 0.f};
+    const double Z = block_sum<VS_THREADS / 64>(zs, rd);
+    if (tid == 0) rec[(size_t)r * ns + sl] = VRec{Z, 0.0, m, mi};
 }
 // merged maximum, its lowest index and sum of exp of the ns records of a row
-__device__ __forceinline__ void vs_merge(const VRec* rec, int ns, float& m, float& Z, int& mi)
+__device__ __forceinline__ void vs_merge(const VRec* rec, int ns, float& m, double& Z, int& mi)
 {
     m = -INFINITY; mi = 0x7fffffff;
     for (int i = 0; i < ns; i++)
         if (rec[i].m > m) { m = rec[i].m; mi = rec[i].arg; }   // ascending slices: first occurrence kept
-    Z = 0.f;
+    Z = 0.0;
     for (int i = 0; i < ns; i++) Z += rec[i].z * expf(rec[i].m - m);
 }
 __global__ __launch_bounds__(VS_THREADS) void vocab_entropy_kernel(const float* __restrict__ logits, int V, int ns, float clamp,
                                                                    float eps, VRec* __restrict__ rec)
 {
-    __shared__ float rv[VS_THREADS / 64];
+    __shared__ double rd[VS_THREADS / 64];
     const int sl = blockIdx.x, r = blockIdx.y, tid = threadIdx.x;
     const float* z = logits + (size_t)r * V;
     VRec* row = rec + (size_t)r * ns;
     int b, e, mi;
-    float m, Z;
+    float m;
+    double Z;
     vs_slice(V, ns, sl, b, e);
     vs_merge(row, ns, m, Z, mi);
-    const float invZ = 1.0f / Z;
-    float hs = 0.f;
+    const double invZ = 1.0 / Z;
+    double hs = 0.0;
     for (int i = b + tid; i < e; i += VS_THREADS) {
-        const float pr = expf(fminf(fmaxf(z[i], -clamp), clamp) - m) * invZ;
-        hs -= pr * logf(pr + eps);
+        const double pr = expf(fminf(fmaxf(z[i], -clamp), clamp) - m) * invZ;
+        hs -= pr * logf((float)pr + eps);
     }
-    const float H = block_sum<VS_THREADS / 64>(hs, rv);
+    const double H = block_sum<VS_THREADS / 64>(hs, rd);
     if (tid == 0) row[sl].h = H;   // (the other blocks of the row read m, z and arg only)
 }
 __global__ __launch_bounds__(64) void vocab_sum_kernel(const VRec* __restrict__ rec, int nb, int V, int ns, int32_t* argmax_out,
@@ -3732,13 +3775,14 @@ __global__ __launch_bounds__(64) void vocab_sum_kernel(const VRec* __restrict__ 
     const int r = blockIdx.x * 64 + threadIdx.x;
     if (r >= nb) return;
     const VRec* row = rec + (size_t)r * ns;
-    float m, Z, H = 0.f;
+    float m;
+    double Z, H = 0.0;
     int mi;
     vs_merge(row, ns, m, Z, mi);
     for (int i = 0; i < ns; i++) H += row[i].h;
     if (argmax_out) argmax_out[r] = mi;
-    if (maxprob_out) maxprob_out[r] = 1.0f / Z;
-    conf_out[r] = 1.0f - H / logf((float)V);
+    if (maxprob_out) maxprob_out[r] = (float)(1.0 / Z);
+    conf_out[r] = (float)(1.0 - H / log((double)V));
 }
 
 // Slices per row: 16, or what leaves at least 1024 logits to each and the scratch holds -- whatever the row count, so that
