@@ -1870,11 +1870,11 @@ __global__ __launch_bounds__(64) void rows_finish_kernel(RowsP2 p)
 // With hundreds of rows the work is a real GEMM and the weights should cross the chip once, not once per 64 rows.
 // A block owns TN logical weight rows (TN / 2 gate + TN / 2 up rows in SwiGLU mode) x 128 activation rows; the blocks
 // that share a weight tile run back to back on one XCD and all but the first find it in that L2.  64-wide K stripes of
-// the weights and of the hi / lo rows go through LDS (register prefetch two stripes ahead; TN = 256 keeps two staging
-// buffers and writes the next stripe while one is multiplied); the waves form a (TN / 64) x 2 grid of 64 x 64
-// sub-tiles, 32 MFMAs (hi and lo) per 12 LDS fragment reads.  The finished tile goes back through LDS in two halves
-// so that the epilogue sees (row, TN consecutive columns): same modes, same RMSNorm folding as the 64-row kernel;
-// weight rows in natural order (a rotary pair e, e + hd/2 sits in one tile).
+// the weights and of the hi / lo rows go through LDS; the waves form a grid of (TN / 4) x 64 sub-tiles (TN = 256, 192:
+// eight waves, one block per CU, two staging buffers) or 64 x 64 ones (TN = 128: four waves, two blocks per CU, one
+// buffer), 32 (24) MFMAs, hi and lo, per 12 (11) LDS fragment reads.  The finished tile goes back through LDS in two
+// halves so that the epilogue sees 64 consecutive columns of a row per wave: the modes, the RMSNorm folding and the order of
+// the weight rows (rotary pairs inside every group of 64) are those of the 64-row kernel, whose epilogue it shares.
 constexpr int MB_TM = 128, MB_CK = 64;
 constexpr int MB_PITCH = MB_CK * 2 + 16;   // bytes per staged row
 
@@ -1883,25 +1883,29 @@ template <int MODE, int TN>
 __device__ __forceinline__ const uint16_t* mb_row(const RowsP2& p, int tile, int r)
 {
     if (MODE == RM_SWIGLU) return (const uint16_t*)p.w[r / (TN / 2)] + (size_t)(tile * (TN / 2) + r % (TN / 2)) * p.K;
-    int row = tile * TN + r;
-    if (row < p.n[0]) return (const uint16_t*)p.w[0] + (size_t)row * p.K;
-    row -= p.n[0];
-    if (row < p.n[1]) return (const uint16_t*)p.w[1] + (size_t)row * p.K;
-    return (const uint16_t*)p.w[2] + (size_t)(row - p.n[1]) * p.K;
+    const int row = tile * TN + r;
+    return m6_row<MODE>(p, row >> 6, row & 63, 0);
 }
 
-// TN = weight rows per tile: 128 (256 threads, two blocks per CU) or 256 (512 threads, one block per CU: a third
-// fewer bytes per MFMA through the CU's memory path, which is what bounds this kernel; used when the launch still
-// has blocks for most CUs)
+// TN = weight rows per tile (see above).  What bounds the 512-thread form is LDS traffic: per stripe the fragment reads
+// and staging writes take as many LDS cycles as the MFMAs take matrix cycles, so both have to run all the time.  Hence
+// the fragments of a k-step are read while the k-step before it is multiplied (two register sets), the next stripe is
+// written to LDS and the one after it requested from memory during the first of a stripe's two k-steps, and the only
+// barrier sits between them: behind it the next stripe is staged and nobody reads this one any more.  Scheduling groups
+// spread the LDS and memory instructions between the MFMAs.  Measured on random data, 512 rows, K = 4096 (both products
+// counted): 256 full tiles 1059 -> 1169 TFLOP/s, 192 tiles 841 -> 941, against reading all fragments at the head of a
+// stripe and writing the next one behind its MFMAs; the matrix cores alone reach 1850 here.
 template <int MODE, bool F16, int TN>
-__global__ __launch_bounds__(TN * 2, 2) void rows_big_kernel(RowsP2 p)
+__global__ __launch_bounds__(TN == 128 ? 256 : 512, 2) void rows_big_kernel(RowsP2 p)
 {
-    constexpr int NTH = TN * 2, WN = TN / 64;   // threads; waves along the weight rows (x 2 along the activation rows)
+    constexpr bool BIG = TN != 128;
+    constexpr int NTH = BIG ? 512 : 256, WN = BIG ? 4 : 2;   // threads; waves along the weight rows (x 2 along the activation rows)
+    constexpr int WR = TN / WN, WNR = WR / 16;               // weight rows of a wave, in 16-row fragments
     constexpr int RPS = NTH / 8;                // rows covered by one load step of the block
-    constexpr int BU = MB_TM / RPS;             // load steps per activation plane
+    constexpr int WU = TN / RPS, BU = MB_TM / RPS;   // load steps of the weights / of one activation plane
     constexpr int EP = TN + 4;                  // floats per row of the epilogue tile
-    constexpr int NBUF = TN == 256 ? 2 : 1;     // staging buffers: the large tile (one block per CU) double-buffers in LDS
     constexpr int BUFB = (TN + 2 * MB_TM) * MB_PITCH;
+    static_assert(MODE != RM_SWIGLU || TN % 128 == 0, "a SwiGLU tile holds whole 64-row groups of both matrices");
     extern __shared__ __align__(16) unsigned char smb[];
     __shared__ float rs[MB_TM];
     unsigned char* Ws = smb;                          // [TN][PITCH]
@@ -1926,27 +1930,28 @@ __global__ __launch_bounds__(TN * 2, 2) void rows_big_kernel(RowsP2 p)
     }
     const int c_begin = (int)((long)NCall * slice / S), NC = (int)((long)NCall * (slice + 1) / S) - c_begin;
     // a stripe is TN + 2 x 128 rows of 8 vectors of 16 bytes; thread takes row tid / 8 + RPS u, vector tid % 8.
-    // Addresses are a block-uniform base plus a 32-bit element offset per thread (few registers: two stripes are in
-    // flight per thread).
-    const int kk = (tid & 7) * 8;
-    const uint16_t* wb[4];   // uniform over the block
-    int boff[BU], dstb[BU];
-    const int woff = (tid >> 3) * K + kk, dstw = (tid >> 3) * MB_PITCH + kk * 2;
+    // Addresses are a block-uniform base plus a 32-bit element offset per thread.  A 64-row group of q or k rows is two
+    // runs of 32 rows, hd / 2 rows apart (woff_rot); every other load step covers consecutive rows.
+    const int kk = (tid & 7) * 8, trow = tid >> 3;
+    const uint16_t* wb[WU];   // uniform over the block
+    bool rot[WU];             // uniform
+    int boff[BU];
+    const int woff = trow * K + kk, dst = trow * MB_PITCH + kk * 2;
+    const int woff_rot = MODE == RM_QKV && BIG ? ((trow & 31) + (trow >> 5) * (p.hd >> 1)) * K + kk : woff;
 #pragma unroll
-    for (int u = 0; u < 4; u++) wb[u] = mb_row<MODE, TN>(p, tile, RPS * u);
-#pragma unroll
-    for (int u = 0; u < BU; u++) {
-        const int row = (tid >> 3) + RPS * u;
-        boff[u] = min(m0 + row, M - 1) * p.ldb + kk;   // rows past M read a valid row, never stored
-        dstb[u] = row * MB_PITCH + kk * 2;
+    for (int u = 0; u < WU; u++) {
+        wb[u] = mb_row<MODE, TN>(p, tile, RPS * u);
+        rot[u] = MODE == RM_QKV && tile * TN + RPS * u < p.dq + p.dkv;
     }
-    constexpr int MB_D = 2;   // stripes in flight
-    u32x4_t rw[MB_D][4], rh[MB_D][BU], rl[MB_D][BU];
-    auto gload = [&](int slot, int ck) {
-        const int k0 = (c_begin + ck) * MB_CK;
 #pragma unroll
-        for (int u = 0; u < 4; u++)   // cached loads: the other row blocks read the same tile
-            rw[slot][u] = *reinterpret_cast<const u32x4_t*>(wb[u] + woff + k0);
+    for (int u = 0; u < BU; u++) boff[u] = min(m0 + trow + RPS * u, M - 1) * p.ldb + kk;   // rows past M read a valid row, never stored
+    constexpr int MB_D = BIG ? 1 : 2;   // stripes in flight in registers
+    u32x4_t rw[MB_D][WU], rh[MB_D][BU], rl[MB_D][BU];
+    auto gload = [&](int slot, int ck) {   // (a stripe past the end re-reads the last one)
+        const int k0 = (c_begin + min(ck, NC - 1)) * MB_CK;
+#pragma unroll
+        for (int u = 0; u < WU; u++)   // cached loads: the other row blocks read the same tile
+            rw[slot][u] = *reinterpret_cast<const u32x4_t*>(wb[u] + (rot[u] ? woff_rot : woff) + k0);
 #pragma unroll
         for (int u = 0; u < BU; u++) {
             rh[slot][u] = *reinterpret_cast<const u32x4_t*>(p.bh + boff[u] + k0);
@@ -1955,79 +1960,79 @@ __global__ __launch_bounds__(TN * 2, 2) void rows_big_kernel(RowsP2 p)
     };
     auto put = [&](int slot, int buf) {   // registers of `slot` -> staging buffer `buf`
 #pragma unroll
-        for (int u = 0; u < 4; u++) *reinterpret_cast<u32x4_t*>(Ws + buf * BUFB + dstw + u * RPS * MB_PITCH) = rw[slot][u];
+        for (int u = 0; u < WU; u++) *reinterpret_cast<u32x4_t*>(Ws + buf * BUFB + dst + u * RPS * MB_PITCH) = rw[slot][u];
 #pragma unroll
         for (int u = 0; u < BU; u++) {
-            *reinterpret_cast<u32x4_t*>(Bh + buf * BUFB + dstb[u]) = rh[slot][u];
-            *reinterpret_cast<u32x4_t*>(Bl + buf * BUFB + dstb[u]) = rl[slot][u];
+            *reinterpret_cast<u32x4_t*>(Bh + buf * BUFB + dst + u * RPS * MB_PITCH) = rh[slot][u];
+            *reinterpret_cast<u32x4_t*>(Bl + buf * BUFB + dst + u * RPS * MB_PITCH) = rl[slot][u];
         }
-    };
-    auto stage = [&](int slot) {
-        lds_barrier();   // the previous stripe is fully consumed
-        put(slot, 0);
-        lds_barrier();
     };
     const int wn = wave % WN, wm = wave / WN;
-    f32x4_t acc[4][4];
+    f32x4_t acc[WNR][4];
 #pragma unroll
-    for (int i = 0; i < 4; i++)
+    for (int i = 0; i < WNR; i++)
 #pragma unroll
         for (int j = 0; j < 4; j++) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    // One stripe = 2 k-steps x 4 groups of 16 activation rows.  The weight fragments of both k-steps are read up
-    // front; the hi / lo fragments of step t + 1 are requested before the eight MFMAs of step t are issued, so the
-    // LDS latency hides behind the matrix pipe.  No conditions inside (row groups past M multiply clamped copies of
-    // the last row; their results are never stored): one straight-line block for the scheduler.
-    const unsigned char* wfrag = Ws + (wn * 64 + r16) * MB_PITCH + g * 16;
+    const unsigned char* wfrag = Ws + (wn * WR + r16) * MB_PITCH + g * 16;
     const unsigned char* hfrag = Bh + (wm * 64 + r16) * MB_PITCH + g * 16;
     const unsigned char* lfrag = Bl + (wm * 64 + r16) * MB_PITCH + g * 16;
-    auto multiply = [&](int buf) {
-        constexpr int KS = MB_CK / 32, NSTEP = KS * 4;
-        u32x4_t a[KS][4], h[2], l[2];
-        const int bo = buf * BUFB;
-#pragma unroll
-        for (int ks = 0; ks < KS; ks++)
-#pragma unroll
-            for (int i = 0; i < 4; i++) a[ks][i] = *reinterpret_cast<const u32x4_t*>(wfrag + bo + i * 16 * MB_PITCH + ks * 64);
-        h[0] = *reinterpret_cast<const u32x4_t*>(hfrag + bo);
-        l[0] = *reinterpret_cast<const u32x4_t*>(lfrag + bo);
-#pragma unroll
-        for (int t = 0; t < NSTEP; t++) {
-            const int ks = t >> 2, j = t & 3;
-            if (t + 1 < NSTEP) {
-                const int o = bo + ((t + 1) & 3) * 16 * MB_PITCH + ((t + 1) >> 2) * 64;
-                h[(t + 1) & 1] = *reinterpret_cast<const u32x4_t*>(hfrag + o);
-                l[(t + 1) & 1] = *reinterpret_cast<const u32x4_t*>(lfrag + o);
-            }
-#pragma unroll
-            for (int i = 0; i < 4; i++) acc[i][j] = mfma_h16<F16>(a[ks][i], h[t & 1], acc[i][j]);
-#pragma unroll
-            for (int i = 0; i < 4; i++) acc[i][j] = mfma_h16<F16>(a[ks][i], l[t & 1], acc[i][j]);
-        }
-    };
-#pragma unroll
-    for (int sl = 0; sl < MB_D; sl++)
-        if (sl < NC) gload(sl, sl);
     // RMS scale of the block's activation rows from the producer's per-tile sums of squares (a K-split launch leaves
     // the scaling to its finishing kernel)
-    if (tid < MB_TM) rs[tid] = 1.0f;
-    if (MODE != RM_RESID && p.ssq && S == 1) {
-        __syncthreads();
-        for (int c = wave; c < MB_TM; c += NTH / 64) {
-            const int m = min(m0 + c, M - 1);
-            float sq = 0.f;
-            for (int i = lane; i < p.n_ssq; i += 64) sq += p.ssq[(size_t)m * p.n_ssq + i];
-            sq = wave_sum(sq);
-            if (lane == 0) rs[c] = 1.0f / sqrtf(sq / (float)K + p.eps);
+    auto row_scales = [&]() {
+        if (tid < MB_TM) rs[tid] = 1.0f;
+        if (MODE != RM_RESID && p.ssq && S == 1) {
+            __syncthreads();
+            for (int c = wave; c < MB_TM; c += NTH / 64) {
+                const int m = min(m0 + c, M - 1);
+                float sq = 0.f;
+                for (int i = lane; i < p.n_ssq; i += 64) sq += p.ssq[(size_t)m * p.n_ssq + i];
+                sq = wave_sum(sq);
+                if (lane == 0) rs[c] = 1.0f / sqrtf(sq / (float)K + p.eps);
+            }
         }
-    }
-    if (NBUF == 1) {
+    };
+    if constexpr (!BIG) {
+        // One stripe = 2 k-steps x 4 groups of 16 activation rows.  The weight fragments of both k-steps are read up
+        // front; the hi / lo fragments of step t + 1 are requested before the eight MFMAs of step t are issued.  No
+        // conditions inside (row groups past M multiply clamped copies of the last row; their results are never stored).
+        auto multiply = [&]() {
+            constexpr int KS = MB_CK / 32, NSTEP = KS * 4;
+            u32x4_t a[KS][WNR], h[2], l[2];
+#pragma unroll
+            for (int ks = 0; ks < KS; ks++)
+#pragma unroll
+                for (int i = 0; i < WNR; i++) a[ks][i] = *reinterpret_cast<const u32x4_t*>(wfrag + i * 16 * MB_PITCH + ks * 64);
+            h[0] = *reinterpret_cast<const u32x4_t*>(hfrag);
+            l[0] = *reinterpret_cast<const u32x4_t*>(lfrag);
+#pragma unroll
+            for (int t = 0; t < NSTEP; t++) {
+                const int ks = t >> 2, j = t & 3;
+                if (t + 1 < NSTEP) {
+                    const int o = ((t + 1) & 3) * 16 * MB_PITCH + ((t + 1) >> 2) * 64;
+                    h[(t + 1) & 1] = *reinterpret_cast<const u32x4_t*>(hfrag + o);
+                    l[(t + 1) & 1] = *reinterpret_cast<const u32x4_t*>(lfrag + o);
+                }
+#pragma unroll
+                for (int i = 0; i < WNR; i++) acc[i][j] = mfma_h16<F16>(a[ks][i], h[t & 1], acc[i][j]);
+#pragma unroll
+                for (int i = 0; i < WNR; i++) acc[i][j] = mfma_h16<F16>(a[ks][i], l[t & 1], acc[i][j]);
+            }
+        };
+        auto stage = [&](int slot) {
+            lds_barrier();   // the previous stripe is fully consumed
+            put(slot, 0);
+            lds_barrier();
+        };
+#pragma unroll
+        for (int sl = 0; sl < MB_D; sl++) gload(sl, sl);
+        row_scales();
         int ck0 = 0;
         for (; ck0 + 2 * MB_D <= NC; ck0 += MB_D) {   // steady state: every step refills its slot, no conditions
 #pragma unroll
             for (int sl = 0; sl < MB_D; sl++) {
                 stage(sl);
                 gload(sl, ck0 + sl + MB_D);
-                multiply(0);
+                multiply();
             }
         }
         for (; ck0 < NC; ck0 += MB_D) {               // drain
@@ -2036,139 +2041,102 @@ __global__ __launch_bounds__(TN * 2, 2) void rows_big_kernel(RowsP2 p)
                 if (ck0 + sl < NC) {   // uniform
                     stage(sl);
                     if (ck0 + sl + MB_D < NC) gload(sl, ck0 + sl + MB_D);
-                    multiply(0);
+                    multiply();
                 }
             }
         }
     } else {
-        // Two staging buffers: stripe c is multiplied out of buffer c % 2 while stripe c + 1 is written into the other
-        // one and stripe c + 2 is on its way from memory; one barrier per stripe.  (Buffer (c + 1) % 2 was last read
-        // for stripe c - 1, which every wave finished before the barrier that ended step c - 1.)
-        if (NC > 0) put(0, 0);
-        lds_barrier();
-        int ck0 = 0;
-        for (; ck0 + 2 * MB_D <= NC; ck0 += MB_D) {   // steady state, no conditions (MB_D = 2: slot = buffer = parity)
+        u32x4_t a[2][WNR], h[2][4], l[2][4];   // fragments of two k-steps
+        auto frags = [&](int q, int buf, int ks) {
+            const int bo = buf * BUFB + ks * 64;
 #pragma unroll
-            for (int sl = 0; sl < MB_D; sl++) {
-                gload(sl, ck0 + sl + MB_D);           // slot sl was stored to LDS one step ago
-                multiply(sl);
-                put(sl ^ 1, sl ^ 1);                  // stripe ck0 + sl + 1, requested two steps ago
-                lds_barrier();
+            for (int i = 0; i < WNR; i++) a[q][i] = *reinterpret_cast<const u32x4_t*>(wfrag + bo + i * 16 * MB_PITCH);
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                h[q][j] = *reinterpret_cast<const u32x4_t*>(hfrag + bo + j * 16 * MB_PITCH);
+                l[q][j] = *reinterpret_cast<const u32x4_t*>(lfrag + bo + j * 16 * MB_PITCH);
             }
-        }
-        for (; ck0 < NC; ck0 += MB_D) {               // drain
+        };
+        auto multiply = [&](int q) {   // row groups past M multiply clamped copies of the last row; never stored
 #pragma unroll
-            for (int sl = 0; sl < MB_D; sl++) {
+            for (int j = 0; j < 4; j++) {
+#pragma unroll
+                for (int i = 0; i < WNR; i++) acc[i][j] = mfma_h16<F16>(a[q][i], h[q][j], acc[i][j]);
+#pragma unroll
+                for (int i = 0; i < WNR; i++) acc[i][j] = mfma_h16<F16>(a[q][i], l[q][j], acc[i][j]);
+            }
+        };
+        constexpr int NR = WNR + 8, NM = WNR * 8, NW = WU + 2 * BU;   // fragment reads, MFMAs, staged vectors of a k-step / stripe
+        gload(0, 0);
+        row_scales();
+        put(0, 0);
+        gload(0, 1);
+        lds_barrier();
+        frags(0, 0, 0);
+        for (int ck0 = 0; ck0 < NC; ck0 += 2) {
+#pragma unroll
+            for (int sl = 0; sl < 2; sl++) {
                 if (ck0 + sl < NC) {   // uniform
-                    if (ck0 + sl + MB_D < NC) gload(sl, ck0 + sl + MB_D);
-                    multiply(sl);
-                    if (ck0 + sl + 1 < NC) put(sl ^ 1, sl ^ 1);
+                    // first k-step: its fragments are in registers (set 0).  Meanwhile read those of the second one, write stripe
+                    // ck0 + sl + 1 into the other buffer (last read before the barrier one stripe ago) and request the one after it
+                    frags(1, sl, 1);
+                    put(0, sl ^ 1);
+                    gload(0, ck0 + sl + 2);
+                    multiply(0);
+#pragma unroll
+                    for (int z = 0; z < NR; z++) {   // DS read, MFMA
+                        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+                    }
+#pragma unroll
+                    for (int z = 0; z < NW; z++) {   // DS write, MFMA, memory read
+                        __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x20, 1, 0);
+                    }
+                    __builtin_amdgcn_sched_group_barrier(0x8, NM - NR - NW, 0);
                     lds_barrier();
+                    // second k-step; meanwhile the first fragments of the next stripe (behind the last one: read, never used)
+                    frags(0, sl ^ 1, 0);
+                    multiply(1);
+#pragma unroll
+                    for (int z = 0; z < NR; z++) {
+                        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+                    }
+                    __builtin_amdgcn_sched_group_barrier(0x8, NM - NR, 0);
                 }
             }
         }
     }
-    // epilogue, 64 activation rows at a time: ep[row][column] through LDS, then thread -> (column n, rows mm, mm + 2, ..)
+    // epilogue, 64 activation rows at a time: ep[row][column] through LDS, then a wave takes 64 consecutive columns of a row
     float* ep = reinterpret_cast<float*>(smb);
-    const int n = tid % TN, mm = tid / TN;
+    constexpr int NG = (MODE == RM_SWIGLU ? TN / 2 : TN) / 64, NWAVE = NTH / 64;   // 64-column groups of the tile's output
     for (int hf = 0; hf < 2; hf++) {
         if (m0 + hf * 64 >= M) break;   // uniform over the block
         __syncthreads();
         if (wm == hf) {
 #pragma unroll
-            for (int i = 0; i < 4; i++)
+            for (int i = 0; i < WNR; i++)
 #pragma unroll
                 for (int j = 0; j < 4; j++)
-                    *reinterpret_cast<f32x4_t*>(ep + (j * 16 + r16) * EP + wn * 64 + i * 16 + 4 * g) = acc[i][j];
+                    *reinterpret_cast<f32x4_t*>(ep + (j * 16 + r16) * EP + wn * WR + i * 16 + 4 * g) = acc[i][j];
         }
         __syncthreads();
-        for (int it = 0; it < 32; it++) {
-            const int ml = mm + 2 * it, m = m0 + hf * 64 + ml;   // uniform over a wave
+        for (int q = wave; q < 64 * NG; q += NWAVE) {
+            const int ml = q / NG, gr = q % NG, m = m0 + hf * 64 + ml;   // uniform over a wave
             if (m >= M) break;
-            float v = ep[ml * EP + n];
+            float v = ep[ml * EP + gr * 64 + lane], v2 = MODE == RM_SWIGLU ? ep[ml * EP + TN / 2 + gr * 64 + lane] : 0.f;
             if (S > 1) {   // raw sums of this K slice: [slice][matrix][M][columns of this launch's tiles]
-                if (MODE == RM_SWIGLU)
-                    p.kpart[(((size_t)slice * 2 + n / (TN / 2)) * M + m) * ((size_t)p.n_tiles * (TN / 2)) +
-                            (size_t)(tile - p.tile0) * (TN / 2) + n % (TN / 2)] = v;
-                else
-                    p.kpart[((size_t)slice * M + m) * ((size_t)p.n_tiles * TN) + (size_t)(tile - p.tile0) * TN + n] = v;
+                constexpr int NMAT = MODE == RM_SWIGLU ? 2 : 1;
+                const size_t nt = (size_t)p.n_tiles * NG * 64, col = (size_t)(tile - p.tile0) * NG * 64 + gr * 64 + lane;
+                p.kpart[(((size_t)slice * NMAT + 0) * M + m) * nt + col] = v;
+                if (MODE == RM_SWIGLU) p.kpart[(((size_t)slice * NMAT + 1) * M + m) * nt + col] = v2;
                 continue;
             }
-            const float sc = rs[hf * 64 + ml];
-            if (MODE == RM_STORE) {
-                p.y[(size_t)m * p.ldy + (size_t)tile * TN + n] = v * sc;
-            } else if (MODE == RM_SWIGLU) {
-                if (n < TN / 2) {
-                    const float gt = v * sc, up = ep[ml * EP + n + TN / 2] * sc;
-                    split_store(gt / (1.0f + __expf(-gt)) * up, p.oh, p.ol, (size_t)m * p.ldo + (size_t)tile * (TN / 2) + n, F16);
-                }
-            } else if (MODE == RM_RESID) {
-                const size_t colx = (size_t)tile * TN + n;
-                float* dsty = p.y + (size_t)m * p.ldy + colx;
-                const float tv = *dsty + v;
-                *dsty = tv;
-                if (p.tap && (p.tap_only <= 0 || m == p.tap_only - 1)) p.tap[(size_t)(p.tap_only > 0 ? 0 : m) * p.tap_ld + colx] = tv;
-                if (p.gain_out) {
-                    split_store(tv * p.gain_out[colx], p.oh, p.ol, (size_t)m * p.ldo + colx, F16);
-                    const float sq = wave_sum(tv * tv);   // the wave holds 64 consecutive columns of row m
-                    if (lane == 0) p.ssq_out[(size_t)m * (p.n[0] >> 6) + tile * WN + (n >> 6)] = sq;
-                }
-            } else {   // QKV: natural row order, the rotary partner of column n is n ^ (hd / 2) of the same tile
-                const int row = tile * TN + n;
-                const int pos = p.pos_dev[0] + p.pos_off + m;
-                v *= sc;
-                if (row < p.dq + p.dkv) {
-                    const bool is_q = row < p.dq;
-                    const int jj = is_q ? row : row - p.dq;
-                    const int head = jj / p.hd, e = jj % p.hd, half = p.hd >> 1, i = e % half;
-                    const float other = ep[ml * EP + (n ^ half)] * sc;
-                    const float* cs = p.rope + ((size_t)pos * half + i) * 2;
-                    const float ov = e < half ? v * cs[0] - other * cs[1] : v * cs[0] + other * cs[1];
-                    if (is_q) p.y[(size_t)m * p.ldy + (size_t)head * p.hd + e] = ov;
-                    else kv_put(p.kc, ((size_t)head * p.max_seq + pos) * p.hd + e, ov, p.kt);
-                } else {
-                    const int e = row - p.dq - p.dkv;
-                    kv_put(p.vc, ((size_t)(e / p.hd) * p.max_seq + pos) * p.hd + (e % p.hd), v, p.kt);
-                }
-            }
+            if (MODE != RM_RESID) { const float sc = rs[hf * 64 + ml]; v *= sc; v2 *= sc; }
+            m6_epilogue<MODE, F16>(p, tile * NG + gr, m, lane, v, v2);
         }
-    }
-}
-
-// Second half of a K-split QKV launch of the large tiles (weight rows in natural order): one wave per (row, 64
-// columns) adds the slices of its column and of the column's rotary partner in a fixed order, scales both by the row's
-// RMS factor, rotates and writes the query row / the cache rows.
-template <bool F16>
-__global__ __launch_bounds__(64) void rows_finish_qkv_kernel(RowsP2 p)
-{
-    const int m = blockIdx.y, lane = threadIdx.x, half = p.hd >> 1;
-    const size_t nt = (size_t)gridDim.x * 64;
-    const int col = blockIdx.x * 64 + lane, row = p.fin_tile0 * 64 + col;
-    const bool rotary = row < p.dq + p.dkv;   // uniform over the wave (dq, dkv are multiples of 128)
-    float v = 0.f, other = 0.f;
-    for (int sl = 0; sl < p.ksplit; sl++) {
-        const float* src = p.kpart + ((size_t)sl * p.M + m) * nt;
-        v += src[col];
-        if (rotary) other += src[col ^ half];
-    }
-    if (p.ssq) {
-        float sq = 0.f;
-        for (int i = lane; i < p.n_ssq; i += 64) sq += p.ssq[(size_t)m * p.n_ssq + i];
-        const float sc = 1.0f / sqrtf(wave_sum(sq) / (float)p.K + p.eps);
-        v *= sc; other *= sc;
-    }
-    const int pos = p.pos_dev[0] + p.pos_off + m;
-    if (rotary) {
-        const bool is_q = row < p.dq;
-        const int jj = is_q ? row : row - p.dq;
-        const int head = jj / p.hd, e = jj % p.hd, i = e % half;
-        const float* cs = p.rope + ((size_t)pos * half + i) * 2;
-        const float ov = e < half ? v * cs[0] - other * cs[1] : v * cs[0] + other * cs[1];
-        if (is_q) p.y[(size_t)m * p.ldy + (size_t)head * p.hd + e] = ov;
-        else kv_put(p.kc, ((size_t)head * p.max_seq + pos) * p.hd + e, ov, p.kt);
-    } else {
-        const int e = row - p.dq - p.dkv;
-        kv_put(p.vc, ((size_t)(e / p.hd) * p.max_seq + pos) * p.hd + (e % p.hd), v, p.kt);
     }
 }
 
@@ -2268,7 +2236,7 @@ hipError_t rows_wide(const Dims& D, const RowsFused& f, hipStream_t s)
 template <int MODE, bool F16, int TN>
 static hipError_t launch_big(const RowsP2& p, hipStream_t s)
 {
-    const size_t lds = (size_t)(TN == 256 ? 2 : 1) * (TN + 2 * MB_TM) * MB_PITCH;
+    const size_t lds = (size_t)(TN == 128 ? 1 : 2) * (TN + 2 * MB_TM) * MB_PITCH;
     static_assert((size_t)64 * (TN + 4) * 4 <= (size_t)(TN + 2 * MB_TM) * MB_PITCH, "epilogue tile fits the staging area");
     static std::atomic<size_t> lds_limit{0};  // per instantiation
     {
@@ -2276,19 +2244,18 @@ static hipError_t launch_big(const RowsP2& p, hipStream_t s)
         if (e != hipSuccess) return e;
     }
     const int S = p.ksplit > 1 ? p.ksplit : 1;
-    hipLaunchKernelGGL((rows_big_kernel<MODE, F16, TN>), dim3(p.n_tiles * ((p.M + MB_TM - 1) / MB_TM) * S), dim3(TN * 2), lds, s, p);
+    hipLaunchKernelGGL((rows_big_kernel<MODE, F16, TN>), dim3(p.n_tiles * ((p.M + MB_TM - 1) / MB_TM) * S), dim3(TN == 128 ? 256 : 512), lds, s, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || S == 1) return e;
-    if (MODE == RM_QKV)   // natural row order: its own finishing kernel
-        hipLaunchKernelGGL((rows_finish_qkv_kernel<F16>), dim3(p.n_tiles * (TN / 64), p.M), dim3(64), 0, s, p);
-    else
-        hipLaunchKernelGGL((rows_finish_kernel<MODE, F16>), dim3(p.n_tiles * (MODE == RM_SWIGLU ? TN / 128 : TN / 64), (p.M + FIN_ROWS - 1) / FIN_ROWS), dim3(64), 0, s, p);
+    hipLaunchKernelGGL((rows_finish_kernel<MODE, F16>), dim3(p.n_tiles * (MODE == RM_SWIGLU ? TN / 128 : TN / 64), (p.M + FIN_ROWS - 1) / FIN_ROWS), dim3(64), 0, s, p);
     return hipGetLastError();
 }
 
 template <int MODE, bool F16>
 static hipError_t launch_big_tn(const RowsP2& p, int tn, hipStream_t s)
 {
+    if constexpr (MODE == RM_QKV)
+        if (tn == 192) return launch_big<MODE, F16, 192>(p, s);
     return tn == 256 ? launch_big<MODE, F16, 256>(p, s) : launch_big<MODE, F16, 128>(p, s);
 }
 
@@ -2309,8 +2276,17 @@ hipError_t rows_big(const Dims& D, const RowsFused& f, hipStream_t s)
     // a launch fills the CUs with the same granularity as two 128-row blocks per CU would) wherever every stacked
     // matrix is a whole number of them; else 128-row tiles
     const int force_tn = D.opt ? D.opt->wide_depth : 0;   // tuning hook: 128 or 256
-    const bool fits256 = f.mode == RM_SWIGLU ? f.n[0] % 128 == 0 : (f.n[0] % 256 == 0 && f.n[1] % 256 == 0 && f.n[2] % 256 == 0);
+    const bool fits256 = n_total % 256 == 0;   // (tiles are made of 64-row groups, which never straddle two matrices)
     int tn = fits256 ? 256 : 128;
+    if (f.mode == RM_QKV && n_total % 192 == 0) {
+        // Rounds of 256 blocks that the launch takes, with the K cut made below; a 192-row tile costs 0.82 of a 256-row one
+        // (more LDS traffic per product).  7B, 512 rows: 192 blocks in one round against 256 in one: 110 -> 91 us.
+        auto cost = [&](int t) {
+            const int blocks = n_total / t * m_blocks, ks = std::min(std::max(256 / blocks, 1), 4);
+            return (double)ceil_div(blocks * ks, 256) / ks * (t == 192 ? 0.82 : 1.0);
+        };
+        if (!fits256 || cost(192) < cost(256)) tn = 192;
+    }
     if (force_tn == 128 || (force_tn == 256 && fits256)) tn = force_tn;
     const int n_tiles = n_total / tn;
     p.n_tiles = n_tiles;
@@ -2321,7 +2297,7 @@ hipError_t rows_big(const Dims& D, const RowsFused& f, hipStream_t s)
     const int force_ks = D.opt ? D.opt->wide_ksplit : 0;
     if (f.kpart && f.mode == RM_RESID && force_ks != 1) {
         const size_t per_slice = (size_t)f.M * n_tiles * tn;
-        int ks = force_ks > 1 ? force_ks : (tn == 256 ? 256 : 512) / (n_tiles * m_blocks);
+        int ks = force_ks > 1 ? force_ks : (tn != 128 ? 256 : 512) / (n_tiles * m_blocks);
         const int nc = f.K / MB_CK;
         if (ks > 8) ks = 8;
         if (ks > nc) ks = nc;
@@ -2331,7 +2307,7 @@ hipError_t rows_big(const Dims& D, const RowsFused& f, hipStream_t s)
     // A QKV launch with blocks for at most half of the slots (prompts of up to 256 rows at the 7B shape) is cut along K
     // as well; its finishing kernel rotates and writes the cache rows.
     if (f.kpart && f.mode == RM_QKV && force_ks != 1) {
-        const int slots = tn == 256 ? 256 : 512, nc = f.K / MB_CK;
+        const int slots = tn != 128 ? 256 : 512, nc = f.K / MB_CK;
         const size_t per_slice = (size_t)f.M * n_tiles * tn;
         int ks = force_ks > 1 ? force_ks : slots / (n_tiles * m_blocks);
         if (ks > 4) ks = 4;
@@ -2344,7 +2320,7 @@ hipError_t rows_big(const Dims& D, const RowsFused& f, hipStream_t s)
     // many slices as fill the slots once more, and the finishing kernel adds the slices and applies SwiGLU
     // (1 + 1/2 block times instead of 2).
     if (f.kpart && f.mode == RM_SWIGLU && force_ks != 1) {
-        const int slots = tn == 256 ? 256 : 512, units = n_tiles * m_blocks;
+        const int slots = tn != 128 ? 256 : 512, units = n_tiles * m_blocks;
         const int whole_tiles = units / slots * slots / m_blocks, tail_tiles = n_tiles - whole_tiles;
         const int tail_units = tail_tiles * m_blocks, nc = f.K / MB_CK;
         if (tail_tiles > 0) {
