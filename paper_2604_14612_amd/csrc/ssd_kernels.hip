@@ -2695,13 +2695,10 @@ __global__ __launch_bounds__(AT_THREADS) void attn_kernel(const float* __restric
 // is therefore staged transposed ([dim][position]) so that a fragment is one 128-bit LDS read.
 constexpr int AM_VPITCH = AT_CHUNK * 2 + 16;   // bytes per row of the transposed V tile
 
-// 8 consecutive fp32 values -> two packed fragments hi = rne(x), lo = rne(x - hi)
+// 8 fp32 values -> two packed fragments hi = rne(x), lo = rne(x - hi)
 template <bool F16>
-__device__ __forceinline__ void split8(const float* x, u32x4_t& hi, u32x4_t& lo)
+__device__ __forceinline__ void pack_hi_lo(const float (&v)[8], u32x4_t& hi, u32x4_t& lo)
 {
-    // two 128-bit reads (x is 32-byte aligned), not eight dependent scalar ones
-    const float4 a = *reinterpret_cast<const float4*>(x), b = *reinterpret_cast<const float4*>(x + 4);
-    const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
     unsigned h[8], l[8];
 #pragma unroll
     for (int i = 0; i < 8; i++) {
@@ -2711,6 +2708,15 @@ __device__ __forceinline__ void split8(const float* x, u32x4_t& hi, u32x4_t& lo)
     }
     hi = u32x4_t{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
     lo = u32x4_t{l[0] | (l[1] << 16), l[2] | (l[3] << 16), l[4] | (l[5] << 16), l[6] | (l[7] << 16)};
+}
+// the same for 8 consecutive values in LDS
+template <bool F16>
+__device__ __forceinline__ void split8(const float* x, u32x4_t& hi, u32x4_t& lo)
+{
+    // two 128-bit reads (x is 32-byte aligned), not eight dependent scalar ones
+    const float4 a = *reinterpret_cast<const float4*>(x), b = *reinterpret_cast<const float4*>(x + 4);
+    const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+    pack_hi_lo<F16>(v, hi, lo);
 }
 
 // fp32 caches take the same kernel: while a chunk is staged every K / V element is split into two bf16 planes
@@ -2931,25 +2937,32 @@ __global__ __launch_bounds__(AT_THREADS) void attn_mfma_kernel(const float* __re
 }
 
 // ---- prompt passes: one block per KV head and 64 query vectors walks the whole causal range -----------------
-// Four waves of 16 query vectors each share the staged K / V^T chunks (64 positions at a time, the same 16-bit
-// planes as above); a wave keeps its 16 x HD output tile and the running maximum / sum of every query vector in
-// registers and rescales them chunk by chunk (online soft-max), so that nothing is written but the finished
-// output: no partials, no fold kernel, and a chunk is staged once per 64 query vectors instead of once per 16.
-// Layouts as in the kernel above: scores D = lane (c = position, g) holds queries 4g .. 4g+3; output tile D = lane
-// (c = dim, g) holds the same queries, so the rescale factors of a lane's queries apply to both.  The exponentials
-// cross from the first layout to the A operand of P.V through a wave-private LDS tile.
+// Eight waves share the staged K / V^T chunks (64 positions at a time, the same 16-bit planes as above): wave w takes the
+// 16 query vectors 16 (w & 3) .. against half w >> 2 of every chunk, so that a SIMD has two waves to switch between although a
+// prompt of 512 rows gives a CU one block only.  A wave keeps its HD x 16 output tile and the running maximum / sum of every
+// query vector in registers and rescales them chunk by chunk (online soft-max); the two halves are merged at the end.
+// Nothing is written but the finished output, and a chunk is staged once per 64 query vectors instead of once per 16.
+// Both products are taken transposed, S^T = K Q^T and O^T = V^T P^T: a lane (c, g) then owns query c in the scores (positions
+// 4g .. 4g+3 of every 16), in the exponentials as the B operand of the second product, and in the output tile (dims
+// 4g .. 4g+3), so the exponentials never leave their registers and the statistics are two shuffles.  The B operand wants
+// eight positions of a 32-wide k-step per lane and the lane has four of either 16-wide half: a contraction does not care
+// about the order of its terms, so V^T is staged in that order (slot 8g + 4h + x of a k-step = position 16h + 4g + x).
+// V is loaded four positions at a time per thread, so that the transpose writes 8 bytes where it wrote 2.  The next chunk is
+// requested before the present one is multiplied; blocks with the longest causal range start first.  What is left is LDS
+// traffic and the conversion of fp32 caches.  512 rows, fp32 cache: 7B 49.6 -> 32 us per layer, 13B (second pass of 1000) 127 -> 52 on average.
 constexpr int AP_Q = 64;                 // query vectors per block
 constexpr int AP_C = 64;                 // cache positions per step
-constexpr int AP_VPITCH = AP_C * 2 + 16; // bytes per row of the transposed V tile
+constexpr int AP_THREADS = 512;
+constexpr int AP_VPITCH = AP_C * 2 + 32; // bytes per row of the transposed V tile (conflict-free 8-byte writes and 16-byte reads)
 
 template <typename KT, int HD>
 static constexpr size_t attn_prompt_lds_bytes()
 {
-    return (sizeof(KT) == 4 ? 2 : 1) * ((size_t)AP_C * (HD * 2 + 16) + (size_t)HD * AP_VPITCH) + (size_t)4 * 16 * HD * 4;
+    return (sizeof(KT) == 4 ? 4 : 2) * ((size_t)AP_C * (HD * 2 + 16) + (size_t)HD * AP_VPITCH);   // two buffers
 }
 
 template <typename KT, int HD>
-__global__ __launch_bounds__(AT_THREADS) void attn_prompt_kernel(const float* __restrict__ q, int ldq,
+__global__ __launch_bounds__(AP_THREADS, 2) void attn_prompt_kernel(const float* __restrict__ q, int ldq,
                                                                  const KT* __restrict__ kc, const KT* __restrict__ vc,
                                                                  const int* pos_dev, int pos_off, int M, int H, int Hkv,
                                                                  int max_seq, float* __restrict__ outp, int dq,
@@ -2963,191 +2976,238 @@ __global__ __launch_bounds__(AT_THREADS) void attn_prompt_kernel(const float* __
     constexpr int EPV = 16 / (int)sizeof(KT);
     constexpr int VPR = HD / EPV;
     constexpr int KSTEPS = HD / 32;
-    constexpr int PT = AP_C / 16;              // position tiles of a chunk (4)
-    constexpr int PS = AP_C / 32;              // k-steps of P.V (2)
+    constexpr int PT = AP_C / 32;              // position tiles of a wave's half of a chunk (2, one k-step of P.V)
     constexpr int DT = HD / 16;                // output dim tiles per wave (8 or 4)
     constexpr int KPLANE = AP_C * ROWB, VPLANE = HD * AP_VPITCH;
+    constexpr int NK = AP_C * VPR / AP_THREADS;                                // K vectors per thread
+    constexpr int VU = AP_C / 4 * VPR, NVU = (VU + AP_THREADS - 1) / AP_THREADS;  // V units of 4 positions x EPV dims; per thread
     extern __shared__ __align__(16) unsigned char smem[];
-    unsigned char* ktile = smem;                                       // [NP][AP_C][ROWB]
-    unsigned char* vT = smem + NP * KPLANE;                            // [NP][HD][AP_VPITCH]
-    float* wbuf = reinterpret_cast<float*>(vT + NP * VPLANE);          // [4 waves][16][HD]: exponentials, then the output tile
+    constexpr int BUF = NP * (KPLANE + VPLANE);   // a buffer: K planes [NP][AP_C][ROWB], V^T planes [NP][HD][AP_VPITCH]
 
-    const int kvh = blockIdx.y;
     const int G = H / Hkv, Q = G * M;
+    // Block id -> (KV head, query block), longest causal range first.  Workgroups go to the eight XCDs round-robin by id: with
+    // a multiple of eight heads every head stays on one XCD, whose L2 then fetches its K and V once for all query blocks.
+    int kvh, qb;
+    {
+        const int id = blockIdx.x, nqb = (int)gridDim.x / Hkv;
+        if (Hkv % 8 == 0) { const int hpx = Hkv >> 3, i = id >> 3; kvh = (id & 7) * hpx + i % hpx; qb = i / hpx; }
+        else { kvh = id % Hkv; qb = id / Hkv; }
+        qb = nqb - 1 - qb;
+    }
     const int p0 = pos_dev[0] + pos_off;
     const int total = p0 + M;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int r16 = lane & 15, g = lane >> 4;
-    const int q0 = blockIdx.x * AP_Q;
+    const int wq = wave & 3, half = wave >> 2;             // query group, half of every chunk
+    const int q0 = qb * AP_Q;
     const int nq = min(AP_Q, Q - q0);
     const int last_vis = p0 + (q0 + nq - 1) / G;          // last position any query vector of the block may see
-    float* pw = wbuf + wave * 16 * HD;
     const float scale = 1.0f / sqrtf((float)HD);
 
-    // the wave's 16 query vectors as hi / lo fragments (A operand: lane (r16 = query, g) holds dims 32 st + 8 g ..)
+    // K / V of the chunk at j0 into registers; positions past the end re-read the last one (zeroed when stored to LDS)
+    u32x4_t kr[NK], vr[NVU][4];
+    const KT* kbase = kc + (size_t)kvh * max_seq * HD;
+    const KT* vbase = vc + (size_t)kvh * max_seq * HD;
+    auto load = [&](int j0) {
+#pragma unroll
+        for (int t = 0; t < NK; t++) {
+            const int v = tid + t * AP_THREADS;
+            kr[t] = *reinterpret_cast<const u32x4_t*>(kbase + (size_t)min(j0 + v / VPR, total - 1) * HD + (v % VPR) * EPV);
+        }
+#pragma unroll
+        for (int t = 0; t < NVU; t++) {
+            const int u = min(tid + t * AP_THREADS, VU - 1);   // 16 lanes = the 16 position groups of one dim group
+#pragma unroll
+            for (int i = 0; i < 4; i++)
+                vr[t][i] = *reinterpret_cast<const u32x4_t*>(vbase + (size_t)min(j0 + (u & 15) * 4 + i, total - 1) * HD + (u >> 4) * EPV);
+        }
+    };
+    auto stage = [&](unsigned char* ktile, int n) {   // registers -> a buffer; n = positions of the chunk that exist
+        unsigned char* vT = ktile + NP * KPLANE;
+        const u32x4_t zero = {0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int t = 0; t < NK; t++) {
+            const int v = tid + t * AP_THREADS, pos = v / VPR, d0 = (v % VPR) * EPV;
+            const u32x4_t kk = pos < n ? kr[t] : zero;
+            if constexpr (F32) {
+                const unsigned kw[4] = {kk.x, kk.y, kk.z, kk.w};
+                unsigned kh[4], kl[4];
+#pragma unroll
+                for (int e = 0; e < 4; e++) {
+                    const float x = __uint_as_float(kw[e]);
+                    kh[e] = f32_to_bf16_bits(x);
+                    kl[e] = f32_to_bf16_bits(x - bf16_bits_to_f32(kh[e]));
+                }
+                *reinterpret_cast<uint2*>(ktile + pos * ROWB + d0 * 2) = make_uint2(kh[0] | (kh[1] << 16), kh[2] | (kh[3] << 16));
+                *reinterpret_cast<uint2*>(ktile + KPLANE + pos * ROWB + d0 * 2) = make_uint2(kl[0] | (kl[1] << 16), kl[2] | (kl[3] << 16));
+            } else {
+                *reinterpret_cast<u32x4_t*>(ktile + pos * ROWB + d0 * 2) = kk;
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < NVU; t++) {
+            const int u = tid + t * AP_THREADS;
+            if (VU % AP_THREADS && u >= VU) break;
+            const int pg = u & 15, d0 = (u >> 4) * EPV;
+            const int slot = (pg >> 3) * 32 + (pg & 3) * 8 + ((pg >> 2) & 1) * 4;   // of positions 4 pg .. 4 pg + 3
+            unsigned char* dst = vT + d0 * AP_VPITCH + slot * 2;
+            unsigned w[4][4];
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                const u32x4_t x = pg * 4 + i < n ? vr[t][i] : zero;
+                w[i][0] = x.x; w[i][1] = x.y; w[i][2] = x.z; w[i][3] = x.w;
+            }
+#pragma unroll
+            for (int e = 0; e < EPV; e++) {
+                if constexpr (F32) {
+                    unsigned h[4], l[4];
+#pragma unroll
+                    for (int i = 0; i < 4; i++) {
+                        const float y = __uint_as_float(w[i][e]);
+                        h[i] = f32_to_bf16_bits(y);
+                        l[i] = f32_to_bf16_bits(y - bf16_bits_to_f32(h[i]));
+                    }
+                    *reinterpret_cast<uint2*>(dst + e * AP_VPITCH) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
+                    *reinterpret_cast<uint2*>(dst + VPLANE + e * AP_VPITCH) = make_uint2(l[0] | (l[1] << 16), l[2] | (l[3] << 16));
+                } else {
+                    unsigned h[4];
+#pragma unroll
+                    for (int i = 0; i < 4; i++) h[i] = (w[i][e >> 1] >> ((e & 1) * 16)) & 0xffffu;
+                    *reinterpret_cast<uint2*>(dst + e * AP_VPITCH) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
+                }
+            }
+        }
+    };
+    load(0);
+
+    // the wave's 16 query vectors as hi / lo fragments (B operand: lane (r16 = query, g) holds dims 32 st + 8 g ..)
+    const int myq = wq * 16 + r16;                           // the lane's query vector within the block
+    const int qv = q0 + min(myq, nq - 1);                      // vectors past nq read a valid one; never stored
     u32x4_t qh[KSTEPS], ql[KSTEPS];
     {
-        const int qv = q0 + min(wave * 16 + r16, nq - 1);      // vectors past nq read a valid one; never stored
         const float* qp = q + (size_t)(qv / G) * ldq + (size_t)(kvh * G + qv % G) * HD;
 #pragma unroll
         for (int st = 0; st < KSTEPS; st++) {
-            float x[8];
             const float4 a = *reinterpret_cast<const float4*>(qp + st * 32 + g * 8), b = *reinterpret_cast<const float4*>(qp + st * 32 + g * 8 + 4);
-            x[0] = a.x * scale; x[1] = a.y * scale; x[2] = a.z * scale; x[3] = a.w * scale;
-            x[4] = b.x * scale; x[5] = b.y * scale; x[6] = b.z * scale; x[7] = b.w * scale;
-            unsigned h[8], l[8];
-#pragma unroll
-            for (int i = 0; i < 8; i++) {
-                const uint16_t hb = f32_to_h16_bits(x[i], F16);
-                h[i] = hb;
-                l[i] = f32_to_h16_bits(x[i] - h16_bits_to_f32(hb, F16), F16);
-            }
-            qh[st] = u32x4_t{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
-            ql[st] = u32x4_t{l[0] | (l[1] << 16), l[2] | (l[3] << 16), l[4] | (l[5] << 16), l[6] | (l[7] << 16)};
+            const float x[8] = {a.x * scale, a.y * scale, a.z * scale, a.w * scale, b.x * scale, b.y * scale, b.z * scale, b.w * scale};
+            pack_hi_lo<F16>(x, qh[st], ql[st]);
         }
     }
-    // causal horizon of the lane's four query vectors (scores layout: queries 4g .. 4g+3 of the wave); -1 = padding
-    int horizon[4];
-#pragma unroll
-    for (int jx = 0; jx < 4; jx++) {
-        const int qi = wave * 16 + g * 4 + jx;
-        horizon[jx] = qi < nq ? p0 + (q0 + qi) / G : -1;
-    }
-    float mrun[4], lrun[4];
-#pragma unroll
-    for (int jx = 0; jx < 4; jx++) { mrun[jx] = -INFINITY; lrun[jx] = 0.f; }
+    const int horizon = myq < nq ? p0 + qv / G : -1;           // last position the lane's query may see; -1 = padding
+    const int wave_vis = wq * 16 < nq ? p0 + (q0 + min(wq * 16 + 15, nq - 1)) / G : -1;   // the same over the wave
+    float mrun = -INFINITY, lrun = 0.f;                        // lrun: the lane's own positions only, folded at the end
     f32x4_t oacc[DT];
 #pragma unroll
     for (int dt = 0; dt < DT; dt++) oacc[dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-    for (int j0 = 0; j0 <= last_vis; j0 += AP_C) {
-        const int n = min(AP_C, total - j0);               // positions of this chunk that exist (>= 1)
-        __syncthreads();                                   // the previous chunk is fully consumed
-        {   // stage K (row-major) and V (transposed); every load is issued before the first is used
-            const KT* kbase = kc + ((size_t)kvh * max_seq + j0) * HD;
-            const KT* vbase = vc + ((size_t)kvh * max_seq + j0) * HD;
-            constexpr int NV = AP_C * VPR / AT_THREADS;
-            u32x4_t kr[NV], vr[NV];
-            const int vmax = n * VPR - 1;
-#pragma unroll
-            for (int t = 0; t < NV; t++) {
-                const int v = min(tid + t * AT_THREADS, vmax);
-                kr[t] = *reinterpret_cast<const u32x4_t*>(kbase + (size_t)(v / VPR) * HD + (v % VPR) * EPV);
-                const int w = tid + t * AT_THREADS;
-                vr[t] = *reinterpret_cast<const u32x4_t*>(vbase + (size_t)min(w % AP_C, n - 1) * HD + (w / AP_C) * EPV);
-            }
-#pragma unroll
-            for (int t = 0; t < NV; t++) {
-                const int v = tid + t * AT_THREADS;
-                const int pos = v / VPR, d0 = (v % VPR) * EPV;
-                const int vpos = v % AP_C, vd0 = (v / AP_C) * EPV;
-                const u32x4_t kk = v <= vmax ? kr[t] : u32x4_t{0u, 0u, 0u, 0u};     // positions past the end: zeros
-                const u32x4_t vv = vpos < n ? vr[t] : u32x4_t{0u, 0u, 0u, 0u};
-                if constexpr (F32) {
-                    const unsigned kw[4] = {kk.x, kk.y, kk.z, kk.w}, vw[4] = {vv.x, vv.y, vv.z, vv.w};
-                    unsigned kh[4], kl[4];
-#pragma unroll
-                    for (int e = 0; e < 4; e++) {
-                        const float x = __uint_as_float(kw[e]);
-                        kh[e] = f32_to_bf16_bits(x);
-                        kl[e] = f32_to_bf16_bits(x - bf16_bits_to_f32(kh[e]));
-                        const float y = __uint_as_float(vw[e]);
-                        const uint16_t yh = f32_to_bf16_bits(y);
-                        *reinterpret_cast<uint16_t*>(vT + (vd0 + e) * AP_VPITCH + vpos * 2) = yh;
-                        *reinterpret_cast<uint16_t*>(vT + VPLANE + (vd0 + e) * AP_VPITCH + vpos * 2) =
-                            f32_to_bf16_bits(y - bf16_bits_to_f32(yh));
-                    }
-                    *reinterpret_cast<uint2*>(ktile + pos * ROWB + d0 * 2) = make_uint2(kh[0] | (kh[1] << 16), kh[2] | (kh[3] << 16));
-                    *reinterpret_cast<uint2*>(ktile + KPLANE + pos * ROWB + d0 * 2) = make_uint2(kl[0] | (kl[1] << 16), kl[2] | (kl[3] << 16));
-                } else {
-                    *reinterpret_cast<u32x4_t*>(ktile + pos * ROWB + d0 * 2) = kk;
-                    const unsigned w4[4] = {vv.x, vv.y, vv.z, vv.w};
-#pragma unroll
-                    for (int e = 0; e < 8; e++)
-                        *reinterpret_cast<uint16_t*>(vT + (vd0 + e) * AP_VPITCH + vpos * 2) = (uint16_t)(w4[e >> 1] >> ((e & 1) * 16));
-                }
-            }
+    // Chunk c is multiplied out of buffer c % 2 while chunk c + 1 goes from registers into the other one.  The first half's
+    // waves store first and multiply then, the second half's the other way round: of the two waves of a SIMD one converts and
+    // stores while the other one multiplies.  One barrier per chunk: behind it this chunk is staged and the last one consumed.
+    stage(smem, min(AP_C, total));
+    if (AP_C <= last_vis) load(AP_C);
+    auto stage_next = [&](int j0) {
+        if (j0 + AP_C <= last_vis) {
+            stage(smem + ((j0 / AP_C + 1) & 1) * BUF, min(AP_C, total - j0 - AP_C));
+            if (j0 + 2 * AP_C <= last_vis) load(j0 + 2 * AP_C);
         }
-        __syncthreads();
-        // scores of the wave's 16 queries against the 64 positions, masked; running maximum
+    };
+    auto multiply = [&](int j0) {
+        const unsigned char* ktile = smem + (j0 / AP_C & 1) * BUF;
+        const unsigned char* vT = ktile + NP * KPLANE;
+        // scores of the half's 32 positions for the lane's query, masked; running maximum
         float sv[PT][4];
-        float mnew[4];
-#pragma unroll
-        for (int jx = 0; jx < 4; jx++) mnew[jx] = mrun[jx];
+        float mnew = mrun;
 #pragma unroll
         for (int pt = 0; pt < PT; pt++) {
             f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int st = 0; st < KSTEPS; st++) {
-                const unsigned char* kp = ktile + (pt * 16 + r16) * ROWB + (st * 32 + g * 8) * 2;
+                const unsigned char* kp = ktile + (half * 32 + pt * 16 + r16) * ROWB + (st * 32 + g * 8) * 2;
                 const u32x4_t kf = *reinterpret_cast<const u32x4_t*>(kp);
-                acc = mfma_h16<F16>(qh[st], kf, acc);
-                acc = mfma_h16<F16>(ql[st], kf, acc);
-                if constexpr (F32) acc = mfma_h16<F16>(qh[st], *reinterpret_cast<const u32x4_t*>(kp + KPLANE), acc);
+                acc = mfma_h16<F16>(kf, qh[st], acc);
+                acc = mfma_h16<F16>(kf, ql[st], acc);
+                if constexpr (F32) acc = mfma_h16<F16>(*reinterpret_cast<const u32x4_t*>(kp + KPLANE), qh[st], acc);
             }
-            const int j = j0 + pt * 16 + r16;
 #pragma unroll
             for (int jx = 0; jx < 4; jx++) {
-                sv[pt][jx] = j <= horizon[jx] ? acc[jx] : -INFINITY;
-                mnew[jx] = fmaxf(mnew[jx], sv[pt][jx]);
+                sv[pt][jx] = j0 + half * 32 + pt * 16 + g * 4 + jx <= horizon ? acc[jx] : -INFINITY;
+                mnew = fmaxf(mnew, sv[pt][jx]);
             }
         }
-        float alpha[4], psum[4];
-#pragma unroll
-        for (int jx = 0; jx < 4; jx++) {
-            mnew[jx] = row16_max(mnew[jx]);                              // over the 16 positions a DPP row holds
-            alpha[jx] = mrun[jx] > -INFINITY ? __expf(mrun[jx] - mnew[jx]) : 0.f;
-            psum[jx] = 0.f;
-        }
-#pragma unroll
-        for (int pt = 0; pt < PT; pt++)
-#pragma unroll
-            for (int jx = 0; jx < 4; jx++) {
-                const float e = sv[pt][jx] > -INFINITY ? __expf(sv[pt][jx] - mnew[jx]) : 0.f;
-                psum[jx] += e;
-                pw[(g * 4 + jx) * AP_C + pt * 16 + r16] = e;
-            }
-#pragma unroll
-        for (int jx = 0; jx < 4; jx++) {
-            lrun[jx] = lrun[jx] * alpha[jx] + row16_sum(psum[jx]);
-            mrun[jx] = mnew[jx];
-        }
+        mnew = fmaxf(mnew, __shfl_xor(mnew, 16, 64));
+        mnew = fmaxf(mnew, __shfl_xor(mnew, 32, 64));
+        const float alpha = mrun > -INFINITY ? __expf(mrun - mnew) : 0.f;
+        mrun = mnew;
+        lrun *= alpha;
 #pragma unroll
         for (int dt = 0; dt < DT; dt++)
 #pragma unroll
-            for (int jx = 0; jx < 4; jx++) oacc[dt][jx] *= alpha[jx];
-        // O += P.V: A = the exponentials (lane (r16 = query, g) holds positions 32 st + 8 g ..), B = V^T fragments
-        u32x4_t ph[PS], pl[PS];
+            for (int jx = 0; jx < 4; jx++) oacc[dt][jx] *= alpha;
+        float e[8];
 #pragma unroll
-        for (int st = 0; st < PS; st++) split8<F16>(pw + r16 * AP_C + st * 32 + g * 8, ph[st], pl[st]);
+        for (int i = 0; i < 8; i++) {
+            const float v = sv[i >> 2][i & 3];
+            e[i] = v > -INFINITY ? __expf(v - mnew) : 0.f;
+            lrun += e[i];
+        }
+        u32x4_t ph, pl;
+        pack_hi_lo<F16>(e, ph, pl);
 #pragma unroll
         for (int dt = 0; dt < DT; dt++) {
+            const unsigned char* vp = vT + (dt * 16 + r16) * AP_VPITCH + (half * 32 + g * 8) * 2;
+            const u32x4_t vf = *reinterpret_cast<const u32x4_t*>(vp);
+            oacc[dt] = mfma_h16<F16>(vf, ph, oacc[dt]);
+            oacc[dt] = mfma_h16<F16>(vf, pl, oacc[dt]);
+            if constexpr (F32) oacc[dt] = mfma_h16<F16>(*reinterpret_cast<const u32x4_t*>(vp + VPLANE), ph, oacc[dt]);
+        }
+    };
+    for (int j0 = 0; j0 <= last_vis; j0 += AP_C) {
+        lds_barrier();
+        if (half == 0) stage_next(j0);
+        if (j0 + half * 32 <= wave_vis) multiply(j0);          // uniform over the wave
+        if (half == 1) stage_next(j0);
+    }
+    lrun += __shfl_xor(lrun, 16, 64);
+    lrun += __shfl_xor(lrun, 32, 64);
+    // the second half's waves hand their tile and statistics over through LDS
+    float4* mo = reinterpret_cast<float4*>(smem) + wq * DT * 64 + lane;                      // [4][DT][64]
+    float2* ms = reinterpret_cast<float2*>(smem + 4 * DT * 64 * 16) + wq * 16 + r16;          // [4][16]
+    static_assert((size_t)4 * DT * 64 * 16 + 4 * 16 * 8 <= attn_prompt_lds_bytes<KT, HD>(), "the merge fits the staging area");
+    lds_barrier();                                             // the last chunk is fully consumed
+    if (half == 1) {
 #pragma unroll
-            for (int st = 0; st < PS; st++) {
-                const unsigned char* vp = vT + (dt * 16 + r16) * AP_VPITCH + (st * 32 + g * 8) * 2;
-                const u32x4_t vf = *reinterpret_cast<const u32x4_t*>(vp);
-                oacc[dt] = mfma_h16<F16>(ph[st], vf, oacc[dt]);
-                oacc[dt] = mfma_h16<F16>(pl[st], vf, oacc[dt]);
-                if constexpr (F32) oacc[dt] = mfma_h16<F16>(ph[st], *reinterpret_cast<const u32x4_t*>(vp + VPLANE), oacc[dt]);
-            }
+        for (int dt = 0; dt < DT; dt++) mo[dt * 64] = make_float4(oacc[dt][0], oacc[dt][1], oacc[dt][2], oacc[dt][3]);
+        if (g == 0) *ms = make_float2(mrun, lrun);
+    }
+    lds_barrier();
+    if (half == 1 || myq >= nq) return;
+    {
+        const float2 s1 = *ms;
+        const float m = fmaxf(mrun, s1.x);                     // position 0 is visible to every query: finite
+        const float w0 = mrun > -INFINITY ? __expf(mrun - m) : 0.f, w1 = s1.x > -INFINITY ? __expf(s1.x - m) : 0.f;
+        lrun = lrun * w0 + s1.y * w1;
+#pragma unroll
+        for (int dt = 0; dt < DT; dt++) {
+            const float4 o1 = mo[dt * 64];
+            oacc[dt][0] = oacc[dt][0] * w0 + o1.x * w1; oacc[dt][1] = oacc[dt][1] * w0 + o1.y * w1;
+            oacc[dt][2] = oacc[dt][2] * w0 + o1.z * w1; oacc[dt][3] = oacc[dt][3] * w0 + o1.w * w1;
         }
     }
-    // finished output: tile -> wave-private LDS ([16 queries][HD]) -> whole rows to memory
+    const size_t oo = (size_t)(qv / G) * dq + (size_t)(kvh * G + qv % G) * HD + g * 4;
 #pragma unroll
-    for (int dt = 0; dt < DT; dt++)
-#pragma unroll
-        for (int jx = 0; jx < 4; jx++) pw[(g * 4 + jx) * HD + dt * 16 + r16] = oacc[dt][jx] / lrun[jx];
-    for (int f = lane; f < 16 * (HD / 4); f += 64) {
-        const int qi = f / (HD / 4), dd = (f % (HD / 4)) * 4;
-        if (wave * 16 + qi >= nq) continue;
-        const float4 o = *reinterpret_cast<const float4*>(pw + qi * HD + dd);
-        const int qg = q0 + wave * 16 + qi, r = qg / G, head = kvh * G + qg % G;
-        const size_t oo = (size_t)r * dq + (size_t)head * HD + dd;
+    for (int dt = 0; dt < DT; dt++) {
+        const float o[4] = {oacc[dt][0] / lrun, oacc[dt][1] / lrun, oacc[dt][2] / lrun, oacc[dt][3] / lrun};
         if (out_hi) {
-            split_store(o.x, out_hi, out_lo, oo, out_f16); split_store(o.y, out_hi, out_lo, oo + 1, out_f16);
-            split_store(o.z, out_hi, out_lo, oo + 2, out_f16); split_store(o.w, out_hi, out_lo, oo + 3, out_f16);
+            unsigned h[4], l[4];
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                h[i] = f32_to_h16_bits(o[i], out_f16);
+                l[i] = f32_to_h16_bits(o[i] - h16_bits_to_f32(h[i], out_f16), out_f16);
+            }
+            *reinterpret_cast<uint2*>(out_hi + oo + dt * 16) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
+            *reinterpret_cast<uint2*>(out_lo + oo + dt * 16) = make_uint2(l[0] | (l[1] << 16), l[2] | (l[3] << 16));
         } else {
-            *reinterpret_cast<float4*>(outp + oo) = o;
+            *reinterpret_cast<float4*>(outp + oo + dt * 16) = make_float4(o[0], o[1], o[2], o[3]);
         }
     }
 }
@@ -3525,7 +3585,7 @@ static hipError_t attention_t(const Dims& D, const float* q, int ldq, const void
         hipError_t e = ensure_lds((const void*)attn_prompt_kernel<KT, HD>, lds, lds_limit);
         if (e != hipSuccess) return e;
         const int Q = (D.H / D.Hkv) * M;
-        hipLaunchKernelGGL((attn_prompt_kernel<KT, HD>), dim3(ceil_div(Q, AP_Q), D.Hkv), dim3(AT_THREADS), lds, s, q, ldq, (const KT*)kc,
+        hipLaunchKernelGGL((attn_prompt_kernel<KT, HD>), dim3(ceil_div(Q, AP_Q) * D.Hkv), dim3(AP_THREADS), lds, s, q, ldq, (const KT*)kc,
                            (const KT*)vc, pos_dev, pos_off, M, D.H, D.Hkv, D.max_seq, out, D.dq, out_hi, out_lo, D.wt == WT_F16);
         return hipGetLastError();
     }
