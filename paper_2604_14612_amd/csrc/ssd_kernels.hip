@@ -1395,10 +1395,13 @@ __device__ __forceinline__ void m2_epilogue(const RowsP2& p, int t, const float*
 constexpr int M3_CK = 512;
 constexpr int M3_PITCH = M3_CK * 2 + 16;  // bytes per LDS row (16-byte pad spreads the banks)
 
-// M3_D = stripes in flight per block; F16: fp16 storage, else bf16; NU = activation vectors per thread and stripe
-// (2 covers up to 8 rows, 3 up to 12, 4 up to 16)
+// M3_D = stripes in flight per block; F16: fp16 storage, else bf16; NU = activation rows (hi and lo counted) per wave and
+// stripe (2 covers up to 8 rows, 3 up to 12, 4 up to 16).  The number of blocks that fit a CU decides how much of the weight
+// stream is in flight, and registers decide that number: every row pointer is wave-uniform and lives in scalar registers, so
+// that three blocks fit (six waves per SIMD) at all row counts; with per-thread pointers nine rows and more had two.  7B, 9
+// rows, fp16: gate/up 42.7 -> 35.0 us, QKV 31.2 -> 23.4, LM head 61 -> 52; 5 rows: QKV 22.5 -> 20.5, gate/up 33.7 -> 32.9.
 template <int MODE, int M3_D, bool F16, int NU>
-__global__ __launch_bounds__(512, (NU <= 2 ? 6 : NU == 3 ? 5 : 4)) void rows_mfma3_kernel(RowsP2 p)
+__global__ __launch_bounds__(512, (M3_D * (MODE == RM_SWIGLU ? 4 + NU : 2 + NU) > 12 ? 4 : 6)) void rows_mfma3_kernel(RowsP2 p)
 {
     constexpr int NT = MODE == RM_SWIGLU ? 2 : 1;
     extern __shared__ __align__(16) unsigned char sm3[];
@@ -1407,7 +1410,8 @@ __global__ __launch_bounds__(512, (NU <= 2 ? 6 : NU == 3 ? 5 : 4)) void rows_mfm
     unsigned char* As = sm3;                          // [NT][16][PITCH]
     unsigned char* Bh = sm3 + NT * 16 * M3_PITCH;     // [M][PITCH]
     unsigned char* Bl = Bh + p.M * M3_PITCH;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform for the compiler: row pointers in scalar registers
     const int r16 = lane & 15, g = lane >> 4;
     const int tile = blockIdx.x;
     const int K = p.K, M = p.M;
@@ -1418,18 +1422,12 @@ __global__ __launch_bounds__(512, (NU <= 2 ? 6 : NU == 3 ? 5 : 4)) void rows_mfm
     for (int t = 0; t < NT; t++)
 #pragma unroll
         for (int j = 0; j < 2; j++) ap[t][j] = m2_row<MODE>(p, tile, 2 * wave + j, t);
-    // activation vectors (16 bytes each) of one stripe: [hi|lo][M][64]; thread takes v = tid, tid+512, ...
-    const int nbv = M * 128;
+    // activation rows of one stripe: hi rows 0 .. M - 1, then the lo rows; wave w takes rows w, w + 8, .. (1 KB each)
     const uint16_t* bsrc[NU];
-    int bdst[NU];
-    int bk[NU];
 #pragma unroll
     for (int u = 0; u < NU; u++) {
-        const int v = min(tid + u * 512, nbv - 1);
-        const int which = v / (M * 64), rem = v % (M * 64), c = rem >> 6, kk = (rem & 63) * 8;
-        bsrc[u] = (which ? p.bl : p.bh) + (size_t)c * p.ldb;
-        bdst[u] = (which ? M : 0) * M3_PITCH + c * M3_PITCH + kk * 2;
-        bk[u] = kk;
+        const int row = min(wave + u * 8, 2 * M - 1);
+        bsrc[u] = row < M ? p.bh + (size_t)row * p.ldb : p.bl + (size_t)(row - M) * p.ldb;
     }
     // Register ring: the loads of the next M3_D stripes are in flight while one stripe is multiplied.  Every load is
     // UNCONDITIONAL: addresses past the end of K (or past the last activation vector) are clamped to valid ones and
@@ -1445,7 +1443,7 @@ __global__ __launch_bounds__(512, (NU <= 2 ? 6 : NU == 3 ? 5 : 4)) void rows_mfm
 #pragma unroll
             for (int j = 0; j < 2; j++) ra[slot][t][j] = gv_load(ap[t][j] + ka);
 #pragma unroll
-        for (int u = 0; u < NU; u++) rb[slot][u] = *reinterpret_cast<const u32x4_t*>(bsrc[u] + min(k0 + bk[u], K - 8));
+        for (int u = 0; u < NU; u++) rb[slot][u] = *reinterpret_cast<const u32x4_t*>(bsrc[u] + ka);
     };
     f32x4_t acc[NT];
 #pragma unroll
@@ -1462,7 +1460,7 @@ __global__ __launch_bounds__(512, (NU <= 2 ? 6 : NU == 3 ? 5 : 4)) void rows_mfm
                 *reinterpret_cast<u32x4_t*>(As + (t * 16 + 2 * wave + j) * M3_PITCH + lane * 16) = ok ? ra[slot][t][j] : zero4;
 #pragma unroll
         for (int u = 0; u < NU; u++)
-            if (tid + u * 512 < nbv) *reinterpret_cast<u32x4_t*>(Bh + bdst[u]) = k0 + bk[u] < K ? rb[slot][u] : zero4;
+            if (wave + u * 8 < 2 * M) *reinterpret_cast<u32x4_t*>(Bh + (wave + u * 8) * M3_PITCH + lane * 16) = ok ? rb[slot][u] : zero4;
         __syncthreads();
     };
     auto multiply = [&](int ck) {
@@ -1561,8 +1559,8 @@ static hipError_t rows_fused_mode(const RowsP2& p, hipStream_t s, const LaunchOp
     const int forced = opt ? opt->rows_depth : 0;
     const int n_tiles = MODE == RM_SWIGLU ? p.n[0] / 16 : (p.n[0] + p.n[1] + p.n[2]) / 16;
     // measured (`KB_ROWS=1 kernel_bench`, and at the 13B / 70B / Llama-3-8B shapes): two stripes in flight are best or
-    // equal everywhere except gate/up, whose ring for two stripes of two matrices does not fit the registers of three
-    // blocks per CU (the kernel is compiled for six waves per SIMD)
+    // equal everywhere (down projection, 5 rows: 18.0 us against 23.3 with one, 18.0 with three) except gate/up, whose ring for
+    // two stripes of two matrices does not fit the registers of three blocks per CU (32.9 us with one stripe, 38.7 with two)
     const int depth = forced > 0 ? forced : (MODE == RM_SWIGLU ? 1 : 2);
     switch (depth) {
         case 1: return launch_mfma3<MODE, 1, F16>(p, n_tiles, s);
