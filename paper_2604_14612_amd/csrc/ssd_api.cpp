@@ -112,7 +112,7 @@ Layout make_layout(const ssd_config& c)
 
 // offsets (in 4-byte words) inside the "small" region
 enum { SM_POS = 0, SM_TOK = 8 /* 17 ints: pending + drafts */, SM_RES = 56 /* 2 */, SM_MAXPROB = 64 /* 16 floats */,
-       SM_SINK = 96, SM_CONF = 128 /* conf_rows floats x3 follow (at most 3 x 2 x SSD_MAX_LAYERS, checked where used) */,
+       SM_SINK = 96, SM_ROPE = 768 /* 128 floats: rotary row of the single-row step's position */, SM_CONF = 128 /* conf_rows floats x3 follow (at most 3 x 2 x SSD_MAX_LAYERS, checked where used) */,
        SM_VTOK = 896 /* 64: tokens of a row block */, SM_TARGET = 960 /* 64: greedy token after each row of a block */ };
 
 }  // namespace
@@ -221,7 +221,7 @@ int layer_single(ssd_ctx* c, int l, int pos_off, bool do_attn, bool do_mlp)
     const Dims& D = c->D;
     float* x = c->f(c->lay.x);
     if (do_attn) {
-    TIMED(SSD_K_GEMV_QKV, gemv_qkv(D, c->wq[l], c->wk[l], c->wv[l], c->attn_norm[l], x, c->f(c->lay.rope), c->pos_dev(),
+    TIMED(SSD_K_GEMV_QKV, gemv_qkv(D, c->wq[l], c->wk[l], c->wv[l], c->attn_norm[l], x, c->small_f() + SM_ROPE, c->pos_dev(),
                                    pos_off, c->f(c->lay.qkv), c->kcache(l), c->vcache(l), c->stream), "gemv_qkv");
     int fold = 0;  // > 0: attention left that many partials per head for the output projection to fold
     TIMED(SSD_K_ATTENTION, attention(D, c->f(c->lay.qkv), D.dq, c->kcache(l), c->vcache(l), c->pos_dev(), pos_off,
@@ -250,7 +250,8 @@ int forward_single(ssd_ctx* c, const uint8_t* sub, int slot, int slot_out, int p
 {
     const Dims& D = c->D;
     if (!(flags & STEP_CHAINED))
-        HIPCHK(embed_rows(D, c->w.embed, c->small_i() + SM_TOK + slot, 1, c->f(c->lay.x), c->stream), "embed");
+        HIPCHK(embed_rows(D, c->w.embed, c->small_i() + SM_TOK + slot, 1, c->f(c->lay.x), c->stream, c->f(c->lay.rope),
+                          c->pos_dev(), pos_off, c->small_f() + SM_ROPE), "embed");
     for (int l = 0; l < D.L; l++) {
         const bool do_attn = !(sub && sub[2 * l]), do_mlp = !(sub && sub[2 * l + 1]);
         if (!do_attn && !do_mlp) continue;
@@ -262,7 +263,10 @@ int forward_single(ssd_ctx* c, const uint8_t* sub, int slot, int slot_out, int p
     out.tok_out = c->small_i() + SM_TOK + slot_out;
     out.maxprob_out = c->small_f() + SM_MAXPROB + lrow;
     if (flags & STEP_COMMIT) { out.pos_dev = c->pos_dev(); out.tok0 = c->small_i() + SM_TOK; }
-    if (flags & STEP_CHAIN_NEXT) { out.embed = c->w.embed; out.x_next = c->f(c->lay.x); }
+    if (flags & STEP_CHAIN_NEXT) {
+        out.embed = c->w.embed; out.x_next = c->f(c->lay.x);
+        out.rope = c->f(c->lay.rope); out.rope_pos = c->pos_dev(); out.rope_off = pos_off + 1; out.rope_row = c->small_f() + SM_ROPE;
+    }
     // LM head with the greedy token and its soft-max probability folded in (block statistics in the attention
     // scratch, which is idle here, then a one-block fold)
     TIMED(SSD_K_GEMV_LMHEAD, gemv_lmhead_argmax(D, c->w.lm_head, c->w.final_norm, c->f(c->lay.x), logits, c->cfg.conf_clamp,

@@ -37,7 +37,9 @@ struct Dims {
 
 // x[r][:] = embed[tok_dev[r]][:] widened to fp32 (token ids in device memory, clamped to the vocabulary).
 struct TokArg { int32_t t[64]; };
-hipError_t embed_rows(const Dims& D, const void* embed, const int32_t* tok_dev, int M, float* x, hipStream_t s);
+// rope_row (may be null): hd floats, receives row *pos_dev + pos_off of the rotary table (what gemv_qkv takes).
+hipError_t embed_rows(const Dims& D, const void* embed, const int32_t* tok_dev, int M, float* x, hipStream_t s,
+                      const float* rope = nullptr, const int* pos_dev = nullptr, int pos_off = 0, float* rope_row = nullptr);
 // dst[i] = toks.t[i] for i < n, except dst[0] = first_dev[0] when first_dev != nullptr
 hipError_t set_tokens(TokArg toks, int n, const int32_t* first_dev, int32_t* dst, hipStream_t s);
 
@@ -52,10 +54,11 @@ struct Chain {
 };
 
 // ---- single-row (draft / vanilla decode) path: weight-streaming GEMV kernels ----------------
-// h = rmsnorm(x, gain); q,k,v = Wq h, Wk h, Wv h; rotary on q,k at position *pos_dev + pos_off;
+// h = rmsnorm(x, gain); q,k,v = Wq h, Wk h, Wv h; rotary on q,k at position *pos_dev + pos_off, whose row of the
+// table is rope_row (hd floats);
 // q -> qbuf (fp32), k,v -> cache rows of this layer.
 hipError_t gemv_qkv(const Dims& D, const void* wq, const void* wk, const void* wv, const float* gain,
-                    const float* x, const float* rope, const int* pos_dev, int pos_off, float* qbuf,
+                    const float* x, const float* rope_row, const int* pos_dev, int pos_off, float* qbuf,
                     void* kcache_l, void* vcache_l, hipStream_t s, const Chain* ch = nullptr, int* blocks_out = nullptr);
 // x[n] += W[n][:] . in[:]   (N x K), optional tap copy of the updated x
 hipError_t gemv_resid(const Dims& D, const void* w, int N, int K, const float* in, float* x, float* tap,
@@ -79,6 +82,7 @@ struct StepOut {
     float* maxprob_out;        // may be null
     int* pos_dev; int32_t* tok0;   // decode: *pos_dev += 1, *tok0 = token (both null: left alone)
     const void* embed; float* x_next;   // x_next set: x_next[0..d) = embedding row of the token
+    const float* rope; const int* rope_pos; int rope_off; float* rope_row;   // rope_row set: rotary row *rope_pos + rope_off of the next step
 };
 constexpr int GEMV_MAX_BLOCKS = 1024;
 hipError_t gemv_lmhead_argmax(const Dims& D, const void* wlm, const float* gain, const float* x, float* logits, float clamp,
@@ -189,7 +193,7 @@ hipError_t attention(const Dims& D, const float* q, int ldq, const void* kcache_
 // out already holds the result.
 size_t attention_scratch_floats(const Dims& D, int max_rows);
 // launch shape attention() uses when the last of M rows sees ctx positions: the number of position ranges,
-// negated for the register-resident kernel (two calls with equal values enqueue identical launches)
+// negated and joined with their length for the register-resident kernel (two calls with equal values enqueue identical launches)
 int attention_splits(const Dims& D, int ctx, int M);
 
 // ---- vocabulary reduction ------------------------------------------------------------------------

@@ -164,26 +164,36 @@ static inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 // ---------------------------------------------------------------------------------------------
 // embedding gather
 // ---------------------------------------------------------------------------------------------
+// The rotary row of a single-row step's position is copied to a fixed place by whatever starts the step, so that the QKV
+// launches of its layers do not have to fetch the position before they can fetch the row.
+struct RopeRow {
+    const float* table; const int* pos_dev; int pos_off; int hd; float* out;   // out null: nothing to copy
+    __device__ __forceinline__ void copy(int t) const { out[t] = table[(size_t)(pos_dev[0] + pos_off) * hd + t]; }
+};
+
 template <typename WT>
 __global__ void embed_kernel(const WT* __restrict__ E, const int32_t* __restrict__ tok_dev, int d, int V,
-                             float* __restrict__ x)
+                             float* __restrict__ x, RopeRow rr)
 {
     int r = blockIdx.y;
+    if (rr.out && blockIdx.x == 0 && r == 0 && (int)threadIdx.x < rr.hd) rr.copy(threadIdx.x);
     int t = tok_dev[r];
     t = min(max(t, 0), V - 1);
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < d; i += gridDim.x * blockDim.x)
         x[(size_t)r * d + i] = Elem<WT>::get(E, (size_t)t * d + i);
 }
 
-hipError_t embed_rows(const Dims& D, const void* embed, const int32_t* tok_dev, int M, float* x, hipStream_t s)
+hipError_t embed_rows(const Dims& D, const void* embed, const int32_t* tok_dev, int M, float* x, hipStream_t s, const float* rope,
+                      const int* pos_dev, int pos_off, float* rope_row)
 {
+    const RopeRow rr = {rope, pos_dev, pos_off, D.hd, rope_row};
     dim3 grid(ceil_div(D.d, 256), M);
     if (D.wt == WT_BF16)
-        hipLaunchKernelGGL(embed_kernel<uint16_t>, grid, dim3(256), 0, s, (const uint16_t*)embed, tok_dev, D.d, D.V, x);
+        hipLaunchKernelGGL(embed_kernel<uint16_t>, grid, dim3(256), 0, s, (const uint16_t*)embed, tok_dev, D.d, D.V, x, rr);
     else if (D.wt == WT_F16)
-        hipLaunchKernelGGL(embed_kernel<f16_t>, grid, dim3(256), 0, s, (const f16_t*)embed, tok_dev, D.d, D.V, x);
+        hipLaunchKernelGGL(embed_kernel<f16_t>, grid, dim3(256), 0, s, (const f16_t*)embed, tok_dev, D.d, D.V, x, rr);
     else
-        hipLaunchKernelGGL(embed_kernel<float>, grid, dim3(256), 0, s, (const float*)embed, tok_dev, D.d, D.V, x);
+        hipLaunchKernelGGL(embed_kernel<float>, grid, dim3(256), 0, s, (const float*)embed, tok_dev, D.d, D.V, x, rr);
     return hipGetLastError();
 }
 
@@ -227,7 +237,7 @@ struct GemvP {
     float* y;           // QKV: qbuf; RESID: residual (+=); SWIGLU: act; STORE: logits
     float* tap;
     void* kc; void* vc; int kt;   // cache rows of this layer and their element type (WeightType code)
-    const float* rope;  // [max_seq][hd/2][2] (cos, sin)
+    const float* rope_row;  // [hd/2][2] (cos, sin) of the row's position
     const int* pos_dev; int pos_off;
     int hd, dq, dkv, max_seq;
     float* vstat;       // STORE only, may be null: per block (max, sum of exp relative to it, arg-max) of the clamped outputs
@@ -448,6 +458,39 @@ __device__ __forceinline__ void gv_epilogue(const GemvP& p, int j0, const float 
     }
 }
 
+// staged input of a projection that folds attention partials: element i = sum_s e^(m_s - m) o_s[i] / sum_s e^(m_s - m) l_s
+template <int VEC, int NF>
+__device__ __forceinline__ void gv_fold(const GemvP& p, int K, float* xs)
+{
+    const int hs = p.hd + 4, ns = p.n_splits;
+    for (int i = threadIdx.x * 4; i < K; i += GV_THREADS * 4) {
+        const float* base = p.part + (size_t)(i / p.hd) * ns * hs;
+        const int d = i % p.hd;
+        float mm[NF], ll[NF];
+        float4 oo[NF];
+#pragma unroll
+        for (int sp = 0; sp < NF; sp++) {
+            const float* ps = base + min(sp, ns - 1) * hs;
+            mm[sp] = ps[p.hd];
+            ll[sp] = ps[p.hd + 1];
+            oo[sp] = *reinterpret_cast<const float4*>(ps + d);
+        }
+        float gm = -INFINITY;
+#pragma unroll
+        for (int sp = 0; sp < NF; sp++) gm = fmaxf(gm, mm[sp]);   // clamped duplicates do not change the max
+        float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
+        float den = 0.f;
+#pragma unroll
+        for (int sp = 0; sp < NF; sp++) {
+            const float w = (sp < ns && ll[sp] > 0.f) ? __expf(mm[sp] - gm) : 0.f;
+            num.x = fmaf(w, oo[sp].x, num.x); num.y = fmaf(w, oo[sp].y, num.y);
+            num.z = fmaf(w, oo[sp].z, num.z); num.w = fmaf(w, oo[sp].w, num.w);
+            den = fmaf(w, ll[sp], den);
+        }
+        *reinterpret_cast<float4*>(xs + gv_xpos<VEC>(i)) = make_float4(num.x / den, num.y / den, num.z / den, num.w / den);
+    }
+}
+
 template <typename WT, int EPI, int R, int D, int KS>
 __global__ __launch_bounds__(GV_THREADS) void gemv_kernel(GemvP p)
 {
@@ -519,33 +562,10 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_kernel(GemvP p)
         // attention output folded on the fly: out = sum_s e^(m_s - m) o_s / sum_s e^(m_s - m) l_s per head.
         // All partials of an element are fetched by independent, unconditional loads (index clamped, weight
         // zeroed past n_splits) so that the fold costs one cache round trip, not one per partial.
-        const int hs = p.hd + 4, ns = p.n_splits;
-        for (int i = threadIdx.x * 4; i < K; i += GV_THREADS * 4) {
-            const float* base = p.part + (size_t)(i / p.hd) * ns * hs;
-            const int d = i % p.hd;
-            float mm[GV_FOLD_MAX], ll[GV_FOLD_MAX];
-            float4 oo[GV_FOLD_MAX];
-#pragma unroll
-            for (int sp = 0; sp < GV_FOLD_MAX; sp++) {
-                const float* ps = base + min(sp, ns - 1) * hs;
-                mm[sp] = ps[p.hd];
-                ll[sp] = ps[p.hd + 1];
-                oo[sp] = *reinterpret_cast<const float4*>(ps + d);
-            }
-            float gm = -INFINITY;
-#pragma unroll
-            for (int sp = 0; sp < GV_FOLD_MAX; sp++) gm = fmaxf(gm, mm[sp]);   // clamped duplicates do not change the max
-            float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
-            float den = 0.f;
-#pragma unroll
-            for (int sp = 0; sp < GV_FOLD_MAX; sp++) {
-                const float w = (sp < ns && ll[sp] > 0.f) ? __expf(mm[sp] - gm) : 0.f;
-                num.x = fmaf(w, oo[sp].x, num.x); num.y = fmaf(w, oo[sp].y, num.y);
-                num.z = fmaf(w, oo[sp].z, num.z); num.w = fmaf(w, oo[sp].w, num.w);
-                den = fmaf(w, ll[sp], den);
-            }
-            *reinterpret_cast<float4*>(xs + gv_xpos<VEC>(i)) = make_float4(num.x / den, num.y / den, num.z / den, num.w / den);
-        }
+        // (two, four or eight per element: the smallest that covers n_splits)
+        if (p.n_splits <= 2) gv_fold<VEC, 2>(p, K, xs);
+        else if (p.n_splits <= 4) gv_fold<VEC, 4>(p, K, xs);
+        else gv_fold<VEC, GV_FOLD_MAX>(p, K, xs);
     } else
     for (int i = threadIdx.x * 4; i < K; i += GV_THREADS * 4) {
         float4 v = p.wait_flag ? coh_load4(p.in + i) : *reinterpret_cast<const float4*>(p.in + i);
@@ -559,7 +579,7 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_kernel(GemvP p)
     int pos = 0;
     if (EPI == EPI_QKV) {
         pos = p.pos_dev[0] + p.pos_off;
-        if ((int)threadIdx.x < p.hd) rope_row[threadIdx.x] = p.rope[(size_t)pos * p.hd + threadIdx.x];   // hd / 2 pairs
+        if ((int)threadIdx.x < p.hd) rope_row[threadIdx.x] = p.rope_row[threadIdx.x];   // hd / 2 pairs
     }
     if (EPI == EPI_RESID) {
         for (int i = threadIdx.x; i < GPB * GV_RES_ROUNDS * R; i += GV_THREADS) {
@@ -668,10 +688,11 @@ constexpr int SF_THREADS = 1024;
 template <typename WT>
 __global__ __launch_bounds__(SF_THREADS) void step_finish_kernel(const float* __restrict__ vstat, int n_blocks, int32_t* tok_out,
                                                                  float* maxprob_out, int* pos_dev, int32_t* tok0,
-                                                                 const WT* __restrict__ E, int d, float* __restrict__ x)
+                                                                 const WT* __restrict__ E, int d, float* __restrict__ x, RopeRow rr)
 {
     __shared__ VStat sm[SF_THREADS / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (rr.out && tid < rr.hd) rr.copy(tid);   // of the next step
     auto wave_merge = [](VStat& a) {
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) {
@@ -819,7 +840,7 @@ static void set_chain(GemvP& p, const Chain* ch)
 }
 
 hipError_t gemv_qkv(const Dims& D, const void* wq, const void* wk, const void* wv, const float* gain, const float* x,
-                    const float* rope, const int* pos_dev, int pos_off, float* qbuf, void* kc, void* vc, hipStream_t s,
+                    const float* rope_row, const int* pos_dev, int pos_off, float* qbuf, void* kc, void* vc, hipStream_t s,
                     const Chain* ch, int* blocks_out)
 {
     if (D.hd > 128 || D.hd % 2) return hipErrorInvalidValue;   // the kernel stages one rotary row of hd floats in a 128-float LDS array
@@ -827,7 +848,7 @@ hipError_t gemv_qkv(const Dims& D, const void* wq, const void* wk, const void* w
     set_chain(p, ch);
     p.w0 = wq; p.w1 = wk; p.w2 = wv; p.in = x; p.gain = gain; p.eps = D.eps; p.K = D.d;
     p.n_rows = D.dq + 2 * D.dkv;
-    p.y = qbuf; p.kc = kc; p.vc = vc; p.kt = D.kt; p.rope = rope; p.pos_dev = pos_dev; p.pos_off = pos_off;
+    p.y = qbuf; p.kc = kc; p.vc = vc; p.kt = D.kt; p.rope_row = rope_row; p.pos_dev = pos_dev; p.pos_off = pos_off;
     p.hd = D.hd; p.dq = D.dq; p.dkv = D.dkv; p.max_seq = D.max_seq;
     return launch_gemv<EPI_QKV>(D, p, s, blocks_out);
 }
@@ -878,15 +899,16 @@ hipError_t gemv_lmhead_argmax(const Dims& D, const void* wlm, const float* gain,
     hipError_t e = launch_gemv<EPI_STORE>(D, p, s, &blocks);
     if (e != hipSuccess) return e;
     if (blocks < 1 || blocks > GEMV_MAX_BLOCKS) return hipErrorInvalidValue;
+    const RopeRow rr = {o.rope, o.rope_pos, o.rope_off, D.hd, o.rope_row};
     if (D.wt == WT_BF16)
         hipLaunchKernelGGL(step_finish_kernel<uint16_t>, dim3(1), dim3(SF_THREADS), 0, s, vstat, blocks, o.tok_out, o.maxprob_out,
-                           o.pos_dev, o.tok0, (const uint16_t*)o.embed, D.d, o.x_next);
+                           o.pos_dev, o.tok0, (const uint16_t*)o.embed, D.d, o.x_next, rr);
     else if (D.wt == WT_F16)
         hipLaunchKernelGGL(step_finish_kernel<f16_t>, dim3(1), dim3(SF_THREADS), 0, s, vstat, blocks, o.tok_out, o.maxprob_out,
-                           o.pos_dev, o.tok0, (const f16_t*)o.embed, D.d, o.x_next);
+                           o.pos_dev, o.tok0, (const f16_t*)o.embed, D.d, o.x_next, rr);
     else
         hipLaunchKernelGGL(step_finish_kernel<float>, dim3(1), dim3(SF_THREADS), 0, s, vstat, blocks, o.tok_out, o.maxprob_out,
-                           o.pos_dev, o.tok0, (const float*)o.embed, D.d, o.x_next);
+                           o.pos_dev, o.tok0, (const float*)o.embed, D.d, o.x_next, rr);
     return hipGetLastError();
 }
 
@@ -1323,9 +1345,32 @@ __device__ __forceinline__ const uint16_t* m2_row(const RowsP2& p, int tile, int
 // Final step of a tile: sum the KS per-wave partial tiles held in LDS (layout [wave][NT][256], element
 // row*16 + column) and apply the mode's epilogue.  Executed by the whole block (it contains barriers in QKV mode).
 // rs: per-column (= activation row) RMS scale in LDS, 1 where no norm applies.
+// pre: what the epilogue reads from memory besides the sums, loaded by m2_preload while the weights stream (a load there
+// costs its whole latency, about 1 us, and for the rotary pair two: the position comes first).
+struct M2Pre { float a, b; int pos; };
+template <int MODE>
+__device__ __forceinline__ M2Pre m2_preload(const RowsP2& p, int t)
+{
+    M2Pre r = {0.f, 0.f, 0};
+    const int tid = threadIdx.x, rr = tid & 15, c = min((tid >> 4) & 15, p.M - 1);
+    if (MODE == RM_QKV) {
+        const int tq = p.dq >> 4, tk = p.dkv >> 4;
+        r.pos = p.pos_dev[0] + p.pos_off + c;
+        if (t < tq + tk) {
+            const int tt = t < tq ? t : t - tq, th = tt % (p.hd >> 4), half = p.hd >> 1;
+            const float* cs = p.rope + ((size_t)r.pos * half + th * 8 + (rr & 7)) * 2;
+            r.a = cs[0]; r.b = cs[1];
+        }
+    } else if (MODE == RM_RESID) {
+        const size_t colx = (size_t)t * 16 + rr;
+        r.a = p.y[(size_t)c * p.ldy + colx];
+        if (p.gain_out) r.b = p.gain_out[colx];
+    }
+    return r;
+}
 template <int MODE, bool F16>
 __device__ __forceinline__ void m2_epilogue(const RowsP2& p, int t, const float* red, int KS, int ts, float* fin,
-                                            const float* rs)
+                                            const float* rs, const M2Pre& pre)
 {
     constexpr int NT = MODE == RM_SWIGLU ? 2 : 1;
     const int tid = threadIdx.x;
@@ -1343,15 +1388,14 @@ __device__ __forceinline__ void m2_epilogue(const RowsP2& p, int t, const float*
     if (tid < 256 && c < p.M) {
         if (MODE == RM_QKV) {
             const int tq = p.dq >> 4, tk = p.dkv >> 4;
-            const int pos = p.pos_dev[0] + p.pos_off + c;
+            const int pos = pre.pos;
             if (t < tq + tk) {
                 const bool is_q = t < tq;
                 const int tt = is_q ? t : t - tq;
                 const int tph = p.hd >> 4, head = tt / tph, th = tt % tph, half = p.hd >> 1;
                 const int i = th * 8 + (rr & 7);
                 const float av = fin[(rr & 7) * 16 + c], bv = fin[((rr & 7) + 8) * 16 + c];
-                const float* cs = p.rope + ((size_t)pos * half + i) * 2;
-                const float o = rr < 8 ? av * cs[0] - bv * cs[1] : bv * cs[0] + av * cs[1];
+                const float o = rr < 8 ? av * pre.a - bv * pre.b : bv * pre.a + av * pre.b;
                 const int e = rr < 8 ? i : i + half;
                 if (is_q) p.y[(size_t)c * p.ldy + (size_t)head * p.hd + e] = o;
                 else kv_put(p.kc, ((size_t)head * p.max_seq + pos) * p.hd + e, o, p.kt);
@@ -1370,12 +1414,11 @@ __device__ __forceinline__ void m2_epilogue(const RowsP2& p, int t, const float*
                     if (rr == 0) p.vmax[(size_t)c * gridDim.x + t] = make_float2(m, __int_as_float(t * 16 + __ffsll(eq) - 1));
                 }
             } else if (MODE == RM_RESID) {
-                float* dst = p.y + (size_t)c * p.ldy + colx;
-                const float tv = *dst + v;
-                *dst = tv;
+                const float tv = pre.a + v;
+                p.y[(size_t)c * p.ldy + colx] = tv;
                 if (p.tap) p.tap[(size_t)c * p.tap_ld + colx] = tv;
                 if (p.gain_out) {
-                    split_store(tv * p.gain_out[colx], p.oh, p.ol, (size_t)c * p.ldo + colx, F16);
+                    split_store(tv * pre.b, p.oh, p.ol, (size_t)c * p.ldo + colx, F16);
                     // the 16 threads of one column are the 16 lanes of a DPP row, all active together
                     const float sq = row16_sum(tv * tv);
                     if (rr == 0) p.ssq_out[(size_t)c * (p.n[0] >> 4) + t] = sq;
@@ -1487,6 +1530,7 @@ __global__ __launch_bounds__(512, (M3_D * (MODE == RM_SWIGLU ? 4 + NU : 2 + NU) 
     auto sidx = [&](int i) { const int c = min(i, NC - 1) + rot; return c >= NC ? c - NC : c; };
 #pragma unroll
     for (int sl = 0; sl < M3_D; sl++) gload(sl, sidx(sl));
+    const M2Pre pre = m2_preload<MODE>(p, tile);
     // RMS scale of every activation row from the producer's per-tile sums of squares (read by the epilogue).
     // Measured per mode: gate/up (long-lived blocks, two stripes in flight) loses least when the partials are
     // summed after the weight stream, the short-lived blocks of QKV and the LM head when it happens up front.
@@ -1528,7 +1572,7 @@ __global__ __launch_bounds__(512, (M3_D * (MODE == RM_SWIGLU ? 4 + NU : 2 + NU) 
 #pragma unroll
         for (int j = 0; j < 4; j++) red[(wave * NT + t) * 256 + (g * 4 + j) * 16 + r16] = acc[t][j];
     __syncthreads();
-    m2_epilogue<MODE, F16>(p, tile, red, 8, 0, fin, rs);
+    m2_epilogue<MODE, F16>(p, tile, red, 8, 0, fin, rs, pre);
 }
 
 template <int MODE, int DEPTH, bool F16, int NU>
@@ -2566,9 +2610,8 @@ __global__ __launch_bounds__(AT_THREADS) void attn_kernel(const float* __restric
     const int G = H / Hkv, Q = G * M;
     const int p0 = pos_dev[0] + pos_off;
     const int total = p0 + M;                                  // positions the last row sees
-    const int chunk = min((total + n_splits - 1) / n_splits, AT_CHUNK);  // host sizes n_splits so this is <= AT_CHUNK
-    const int j0 = split * chunk;
-    const int n = min(chunk, total - j0);                      // may be <= 0
+    const int j0 = split * AT_CHUNK;
+    const int n = min(AT_CHUNK, total - j0);                   // may be <= 0
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 
     if (n > 0) {  // stage K and V of the chunk: every load is issued before the first is used
@@ -2750,16 +2793,39 @@ __global__ __launch_bounds__(AT_THREADS) void attn_mfma_kernel(const float* __re
 
     const int split = blockIdx.x, kvh = blockIdx.y;
     const int G = H / Hkv, Q = G * M;
-    const int p0 = pos_dev[0] + pos_off;
-    const int total = p0 + M;
-    const int chunk = min((total + n_splits - 1) / n_splits, AT_CHUNK);
-    const int j0 = split * chunk;
-    const int n = min(chunk, total - j0);                      // may be <= 0
+    const int j0 = split * AT_CHUNK;   // chunks of fixed length: where they lie does not depend on the position
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int r16 = lane & 15, g = lane >> 4;
-    // the block's group of 16 query vectors (blockIdx.z): loads issued first, they are the furthest away
+    // the block's group of 16 query vectors (blockIdx.z)
     const int q0 = blockIdx.z * AT_QPASS;
     const int nq = min(AT_QPASS, Q - q0);
+    constexpr int QPT = AT_QPASS * HD / AT_THREADS;   // query elements per thread
+    float qreg[QPT];
+    constexpr int NV = (AT_CHUNK * VPR + AT_THREADS - 1) / AT_THREADS;
+    u32x4_t kr[NV], vr[NV];
+    // Query vectors, K and V are all requested before the position is known (one memory latency less on the way through the
+    // kernel): cache rows past it may hold anything and are replaced by zeros when they are stored to LDS.
+    // K: consecutive lanes take consecutive vectors of a row.  V: consecutive lanes take consecutive POSITIONS
+    // (vector v -> position v % AT_CHUNK, dims EPV (v / AT_CHUNK) ..), so that the 2-byte stores of the transpose
+    // below fall on consecutive addresses of one V^T row instead of colliding in two banks.
+    {
+#pragma unroll
+        for (int t = 0; t < QPT; t++) {
+            const int e = tid + t * AT_THREADS, qg = q0 + min(e / HD, nq - 1);
+            qreg[t] = q[(size_t)(qg / G) * ldq + (size_t)(kvh * G + qg % G) * HD + (e % HD)];
+        }
+        const KT* kbase = kc + (size_t)kvh * max_seq * HD;
+        const KT* vbase = vc + (size_t)kvh * max_seq * HD;
+#pragma unroll
+        for (int t = 0; t < NV; t++) {
+            const int v = min(tid + t * AT_THREADS, AT_CHUNK * VPR - 1);
+            kr[t] = *reinterpret_cast<const u32x4_t*>(kbase + (size_t)min(j0 + v / VPR, max_seq - 1) * HD + (v % VPR) * EPV);
+            vr[t] = *reinterpret_cast<const u32x4_t*>(vbase + (size_t)min(j0 + v % AT_CHUNK, max_seq - 1) * HD + (v / AT_CHUNK) * EPV);
+        }
+    }
+    const int p0 = pos_dev[0] + pos_off;
+    const int total = p0 + M;
+    const int n = min(AT_CHUNK, total - j0);                   // may be <= 0
     // A chunk that lies wholly behind the causal horizon of the block's LAST query row contributes nothing (in a
     // prompt pass that is half of all blocks): leave empty partials and go.  Uniform over the block.
     if (n_splits > 1 && (n <= 0 || j0 > p0 + (q0 + nq - 1) / G)) {
@@ -2772,29 +2838,8 @@ __global__ __launch_bounds__(AT_THREADS) void attn_mfma_kernel(const float* __re
         }
         return;
     }
-    constexpr int QPT = AT_QPASS * HD / AT_THREADS;   // query elements per thread
-    float qreg[QPT];
-#pragma unroll
-    for (int t = 0; t < QPT; t++) {
-        const int e = tid + t * AT_THREADS, qg = q0 + min(e / HD, nq - 1);
-        qreg[t] = q[(size_t)(qg / G) * ldq + (size_t)(kvh * G + qg % G) * HD + (e % HD)];
-    }
-    if (n > 0) {  // stage K (row-major) and V (transposed); every load is issued before the first is used
-        const KT* kbase = kc + ((size_t)kvh * max_seq + j0) * HD;
-        const KT* vbase = vc + ((size_t)kvh * max_seq + j0) * HD;
-        constexpr int NV = (AT_CHUNK * VPR + AT_THREADS - 1) / AT_THREADS;
-        u32x4_t kr[NV], vr[NV];
+    if (n > 0) {  // stage K (row-major) and V (transposed)
         const int vmax = n * VPR - 1;
-        // K: consecutive lanes take consecutive vectors of a row.  V: consecutive lanes take consecutive POSITIONS
-        // (vector v -> position v % AT_CHUNK, dims EPV (v / AT_CHUNK) ..), so that the 2-byte stores of the transpose
-        // below fall on consecutive addresses of one V^T row instead of colliding in two banks.
-#pragma unroll
-        for (int t = 0; t < NV; t++) {
-            const int v = min(tid + t * AT_THREADS, vmax);
-            kr[t] = *reinterpret_cast<const u32x4_t*>(kbase + (size_t)(v / VPR) * HD + (v % VPR) * EPV);
-            const int w = min(tid + t * AT_THREADS, AT_CHUNK * VPR - 1);
-            vr[t] = *reinterpret_cast<const u32x4_t*>(vbase + (size_t)min(w % AT_CHUNK, n - 1) * HD + (w / AT_CHUNK) * EPV);
-        }
 #pragma unroll
         for (int t = 0; t < NV; t++) {
             const int v = tid + t * AT_THREADS;
@@ -3315,7 +3360,7 @@ template <typename KT, int HD, int NQ, int NW, int NL>
 __global__ __launch_bounds__(NW * 64) void attn_wide_kernel(const float* __restrict__ q, int ldq,
                                                             const KT* __restrict__ kc, const KT* __restrict__ vc,
                                                             const int* pos_dev, int pos_off, int M, int H, int Hkv,
-                                                            int max_seq, int n_splits, float* __restrict__ part,
+                                                            int max_seq, int n_splits, int chunk, float* __restrict__ part,
                                                             float* __restrict__ outp, int dq,
                                                             uint16_t* __restrict__ out_hi, uint16_t* __restrict__ out_lo,
                                                             bool out_f16)
@@ -3327,19 +3372,17 @@ __global__ __launch_bounds__(NW * 64) void attn_wide_kernel(const float* __restr
     __shared__ float wml[NW * NQ * 2];              // per-wave (max, sum)
     const int split = blockIdx.x, kvh = blockIdx.y, q0 = blockIdx.z * NQ;
     const int G = H / Hkv, Q = G * M, nq = min(NQ, Q - q0);
-    const int p0 = pos_dev[0] + pos_off, total = p0 + M;
-    const int chunk = (total + n_splits - 1) / n_splits;
-    const int j0 = split * chunk, n = min(chunk, total - j0);  // may be <= 0
+    const int j0 = split * chunk;    // ranges of fixed length: where they lie does not depend on the position
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int seg = lane / LPP, sl = (lane % LPP) * EPV;
-    const int jlast = j0 + n - 1;
-    const int n_pass = n > 0 ? (n + PASS - 1) / PASS : 0;
+    const int jlast = min(j0 + chunk, max_seq) - 1;   // last cache row of the range (may lie past the position)
     const KT* kbase = kc + (size_t)kvh * max_seq * HD + sl;
     const KT* vbase = vc + (size_t)kvh * max_seq * HD + sl;
 
     u32x4_t kr[NL], vr[NL];
-    // addresses are clamped to the last position of the range, never predicated: all loads of a pass stay in
-    // flight together, and the positions past the range are masked out of the scores instead
+    // addresses are clamped to the last row of the range, never predicated: all loads of a pass stay in flight together.  The
+    // first pass is requested before the position is known (one memory latency less on the way through the kernel):
+    // rows past it may hold anything, their scores are masked and their values replaced by zeros.
     auto issue_k = [&](int pass) {
 #pragma unroll
         for (int t = 0; t < NL; t++) {
@@ -3354,7 +3397,11 @@ __global__ __launch_bounds__(NW * 64) void attn_wide_kernel(const float* __restr
             vr[t] = *reinterpret_cast<const u32x4_t*>(vbase + (size_t)j * HD);
         }
     };
-    if (n_pass > 0) { issue_k(0); issue_v(0); }
+    issue_k(0);
+    issue_v(0);
+    const int p0 = pos_dev[0] + pos_off, total = p0 + M;
+    const int n = min(chunk, total - j0);  // may be <= 0
+    const int n_pass = n > 0 ? (n + PASS - 1) / PASS : 0;
 
     const float scale = 1.0f / sqrtf((float)HD);
     for (int e = tid; e < NQ * HD; e += NT) {
@@ -3423,7 +3470,8 @@ __global__ __launch_bounds__(NW * 64) void attn_wide_kernel(const float* __restr
 #pragma unroll
         for (int t = 0; t < NL; t++) {
             float vf[EPV];
-            aw_unpack<KT>(vr[t], vf);
+            const bool live = ((pass * NL + t) * NW + wave) * PPL + seg < n;
+            aw_unpack<KT>(live ? vr[t] : u32x4_t{0u, 0u, 0u, 0u}, vf);
 #pragma unroll
             for (int qi = 0; qi < NQ; qi++)
 #pragma unroll
@@ -3473,14 +3521,14 @@ __global__ __launch_bounds__(NW * 64) void attn_wide_kernel(const float* __restr
 }
 
 // Launch plan.  Few query vectors per KV head (Q = M x group size <= AW_MAXQ_TOTAL): the register-resident
-// kernel over ranges of about AW_RANGE positions -- a single CU pulls only a few tens of GB/s, so a head's
+// kernel over ranges of 64 to 256 positions -- a single CU pulls only a few tens of GB/s, so a head's
 // cache is spread over many blocks even though that costs the fold of the partial results.  Many query
 // vectors (prompt blocks, wide GQA groups): the LDS-staged kernel, which fetches K/V once for all of them.
 constexpr int AW_MAXQ_TOTAL = 4;
 constexpr int AW_MAX_ROWS = 8;
-constexpr int AW_RANGE = 128;
+constexpr int AW_RANGE_BYTES = 32 * 1024;   // K bytes of a range: one pass of the narrowest block shape (8 waves, 4 loads each)
 constexpr int AW_MAX_RANGES = 16;
-struct AttnPlan { bool wide; int n_splits; bool defer_fold; };
+struct AttnPlan { bool wide; int n_splits; int chunk; bool defer_fold; };   // chunk: cache rows per range
 
 static AttnPlan attn_plan(const Dims& D, int ctx, int M)
 {
@@ -3497,19 +3545,24 @@ static AttnPlan attn_plan(const Dims& D, int ctx, int M)
               (D.kt == WT_F32 && D.wt == WT_F32 && (G == 1 || G == 2 || G == 4 || G == 8) && M <= AW_MAX_ROWS);
     if (force_kernel == 1 || force_kernel == 3) pl.wide = false;
     if (pl.wide) {
-        // ranges of AW_RANGE positions (one pass of the narrowest block shape), at most AW_MAX_RANGES of them; an fp32
-        // cache has twice the bytes per position, so its ranges are shorter (more blocks pulling from the cache)
-        int ns = ceil_div(ctx, D.kt == WT_F32 ? AW_RANGE * 5 / 8 : AW_RANGE);
+        // ranges of one pass of the narrowest block shape (128 positions of 16-bit 128-wide heads, 64 of fp32 ones), at most
+        // AW_MAX_RANGES of them
+        const int range = AW_RANGE_BYTES / (D.hd * (D.kt == WT_F32 ? 4 : 2));
+        int ns = ceil_div(ctx, range);
         // single row: up to 4 K positions, ranges grow rather than exceed what the output projection folds itself
         // (a longer range costs the attention kernel about 1 us, a separate fold launch 5)
         if (M == 1 && ns > GV_FOLD_MAX && ctx <= GV_FOLD_MAX * 512) ns = GV_FOLD_MAX;
         if (ns > AW_MAX_RANGES) ns = AW_MAX_RANGES;
         if (force_splits > 0) ns = force_splits;
         if (ns > ctx) ns = ctx;
-        pl.n_splits = ns;
+        // The length of a range is part of the launch, not computed from the position on the device: whole ranges while their
+        // number grows with the context, beyond that steps of 32 (a captured launch sequence then lasts for 32 ns positions).
+        pl.chunk = std::max(range, ceil_div(ceil_div(ctx, ns), 32) * 32);
+        if (force_splits > 0) pl.chunk = ceil_div(ctx, ns);
+        pl.n_splits = ceil_div(ctx, pl.chunk);
     } else {
-        const int need = ceil_div(ctx, AT_CHUNK);  // a block owns at most AT_CHUNK positions
-        pl.n_splits = force_splits > need ? force_splits : need;
+        pl.n_splits = ceil_div(ctx, AT_CHUNK);     // a block owns AT_CHUNK positions
+        pl.chunk = AT_CHUNK;
     }
     return pl;
 }
@@ -3517,7 +3570,7 @@ static AttnPlan attn_plan(const Dims& D, int ctx, int M)
 int attention_splits(const Dims& D, int ctx, int M)
 {
     const AttnPlan pl = attn_plan(D, ctx, M);
-    return pl.wide ? -pl.n_splits : pl.n_splits;  // distinct values for distinct launch shapes
+    return pl.wide ? -(pl.n_splits + 64 * pl.chunk) : pl.n_splits;  // distinct values for distinct launch shapes
 }
 
 size_t attention_scratch_floats(const Dims& D, int max_rows)
@@ -3529,11 +3582,11 @@ size_t attention_scratch_floats(const Dims& D, int max_rows)
 
 template <typename KT, int HD, int NQ, int NW, int NL>
 static void launch_attn_wide(const Dims& D, const float* q, int ldq, const void* kc, const void* vc, const int* pos_dev,
-                             int pos_off, int n_splits, int zq, int M, float* part, float* out, uint16_t* out_hi,
+                             int pos_off, int n_splits, int chunk, int zq, int M, float* part, float* out, uint16_t* out_hi,
                              uint16_t* out_lo, hipStream_t s)
 {
     hipLaunchKernelGGL((attn_wide_kernel<KT, HD, NQ, NW, NL>), dim3(n_splits, D.Hkv, zq), dim3(NW * 64), 0, s, q, ldq,
-                       (const KT*)kc, (const KT*)vc, pos_dev, pos_off, M, D.H, D.Hkv, D.max_seq, n_splits, part, out, D.dq,
+                       (const KT*)kc, (const KT*)vc, pos_dev, pos_off, M, D.H, D.Hkv, D.max_seq, n_splits, chunk, part, out, D.dq,
                        out_hi, out_lo, D.wt == WT_F16);
 }
 
@@ -3594,13 +3647,13 @@ static hipError_t attention_t(const Dims& D, const float* q, int ldq, const void
             Q = G > 4 ? 4 : G;
             zq = M * (G / Q);
         }
-        const int span = ceil_div(ctx, n_splits) * (HD / (16 / (int)sizeof(KT)));  // lanes' worth of 16-byte vectors per range
-        if (Q == 1 && span <= 8 * 64 * 4) launch_attn_wide<KT, HD, 1, 8, 4>(D, q, ldq, kc, vc, pos_dev, pos_off, n_splits, zq, M, part, out, out_hi, out_lo, s);
-        else if (Q == 1 && span <= 16 * 64 * 4) launch_attn_wide<KT, HD, 1, 16, 4>(D, q, ldq, kc, vc, pos_dev, pos_off, n_splits, zq, M, part, out, out_hi, out_lo, s);
-        else if (Q == 1) launch_attn_wide<KT, HD, 1, 8, 16>(D, q, ldq, kc, vc, pos_dev, pos_off, n_splits, zq, M, part, out, out_hi, out_lo, s);
-        else if (Q == 2) launch_attn_wide<KT, HD, 2, 16, 4>(D, q, ldq, kc, vc, pos_dev, pos_off, n_splits, zq, M, part, out, out_hi, out_lo, s);
-        else if (span <= 8 * 64 * 4) launch_attn_wide<KT, HD, 4, 8, 4>(D, q, ldq, kc, vc, pos_dev, pos_off, n_splits, zq, M, part, out, out_hi, out_lo, s);
-        else launch_attn_wide<KT, HD, 4, 8, 8>(D, q, ldq, kc, vc, pos_dev, pos_off, n_splits, zq, M, part, out, out_hi, out_lo, s);
+        const int span = pl.chunk * (HD / (16 / (int)sizeof(KT)));  // lanes' worth of 16-byte vectors per range
+        if (Q == 1 && span <= 8 * 64 * 4) launch_attn_wide<KT, HD, 1, 8, 4>(D, q, ldq, kc, vc, pos_dev, pos_off, n_splits, pl.chunk, zq, M, part, out, out_hi, out_lo, s);
+        else if (Q == 1 && span <= 16 * 64 * 4) launch_attn_wide<KT, HD, 1, 16, 4>(D, q, ldq, kc, vc, pos_dev, pos_off, n_splits, pl.chunk, zq, M, part, out, out_hi, out_lo, s);
+        else if (Q == 1) launch_attn_wide<KT, HD, 1, 8, 16>(D, q, ldq, kc, vc, pos_dev, pos_off, n_splits, pl.chunk, zq, M, part, out, out_hi, out_lo, s);
+        else if (Q == 2) launch_attn_wide<KT, HD, 2, 16, 4>(D, q, ldq, kc, vc, pos_dev, pos_off, n_splits, pl.chunk, zq, M, part, out, out_hi, out_lo, s);
+        else if (span <= 8 * 64 * 4) launch_attn_wide<KT, HD, 4, 8, 4>(D, q, ldq, kc, vc, pos_dev, pos_off, n_splits, pl.chunk, zq, M, part, out, out_hi, out_lo, s);
+        else launch_attn_wide<KT, HD, 4, 8, 8>(D, q, ldq, kc, vc, pos_dev, pos_off, n_splits, pl.chunk, zq, M, part, out, out_hi, out_lo, s);
     } else {
         launch_attn_staged<KT, HD>(D, q, ldq, kc, vc, pos_dev, pos_off, n_splits, M, part, out, out_hi, out_lo, s);
     }

@@ -4,7 +4,7 @@ import pytest
 
 from oracle import OracleSSD
 from synth import ModelShape, make_prompt, make_weights
-from tests._parity import CONF_TOL, PROB_RTOL, make_pair, to_gpu
+from tests._parity import CONF_TOL, PROB_RTOL, assert_logits_close, make_pair, to_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -46,3 +46,31 @@ def test_equal_maxima_give_the_lowest_token(vocab):
         ctx.ssd_accept(d, y)
         toks.append(ctx.ssd_decode())
         assert max(toks) < half
+
+
+# Single-row attention: contexts at the edges of its position ranges (64 to 256 rows by head size and cache type, at most eight
+# of them, then longer ones) and the MFMA kernel's chunks of 96 behind them; rows past the position hold NaN, as the
+# kernels request whole ranges before they know it.
+@pytest.mark.parametrize("heads,kv_heads,kv", [(4, 4, "fp32"), (4, 2, "bf16"), (2, 2, "fp32"), (2, 1, "fp16")])
+@pytest.mark.parametrize("plen", [63, 95, 127, 255, 511, 1030])
+def test_attention_ranges_at_their_edges(heads, kv_heads, kv, plen):
+    shape = ModelShape(2, 256, heads, kv_heads, 704, 1024)      # head_dim 64 (4 heads) or 128 (2 heads)
+    orc, ctx = make_pair(shape, 31, plen + 24, max_k=4, norm_gain_std=0.1, kv_dtype=kv)
+    prompt = make_prompt(1024, plen, 7).tolist()
+    o = OracleSSD(orc)
+    o.prefill(prompt)
+    ctx.ssd_prefill(prompt)
+    for _ in range(3):
+        ctx.ssd_kv_poison_stale()
+        o.decode()
+        t = ctx.ssd_decode()
+        assert_logits_close(ctx.ssd_copy_logits(0, 1)[0], o.last_logits[0], shape.dtype, "decode")
+        if t != o.tokens[-1]:
+            return      # a sub-tolerance tie: the sequences part
+    ctx.ssd_kv_poison_stale()
+    zero = np.zeros(2, np.uint8)
+    d = o.draft(zero, 4)
+    ctx.ssd_draft_step(zero, 4)
+    o.verify(d)
+    ctx.ssd_verify(d)
+    assert_logits_close(ctx.ssd_copy_logits(0, 5), o.last_logits, shape.dtype, "verify")
