@@ -809,20 +809,38 @@ static hipError_t launch_gemv_t(const GemvP& p, hipStream_t s, LaunchOpts* opt, 
             default: break;
         }
     }
-    // measured (work-split sweeps at the 7B shape, `KB_GEMV=1` / `KB_RESID=1 kernel_bench`): row pairs with four steps
-    // in flight everywhere; QKV and gate/up gain 0.5-0.8 us from two waves sharing a pair, the down projection 0.4 us
-    // from four, the LM head and the projection that folds the attention partials are best with a wave per pair
-    if (p.n_rows >= 8192) {
-        if constexpr (sizeof(WT) == 2 && (EPI == EPI_QKV || EPI == EPI_SWIGLU)) return launch_gemv_cfg<WT, EPI, 2, 4, 2>(p, s, opt, blocks_out);
-        return launch_gemv_cfg<WT, EPI, 2, 4, 1>(p, s, opt, blocks_out);
+    if constexpr (sizeof(WT) == 2) {
+        // 16-bit weights: row pairs everywhere (four rows per wave lose 5-20 %); graph replays of one launch per layer, us.
+        if constexpr (EPI == EPI_RESID) {
+            // Few chunks: two waves per pair.  Folding the attention partials: a wave per pair with four steps in flight, since
+            // every block re-reads the partials and there is one block per CU only (7B 9.4 against 10.9 with four waves per
+            // pair; at 8192 rows, where a block has two rounds, 27.2 against 28.5 the other way round).  Everything else: four
+            // waves per pair, two steps each in flight (down projection: Llama-3-8B 22.9 -> 21.4, 13B 26.7 -> 25.7, 70B 75.4 ->
+            // 72.8, 1024-wide 5.4 -> 5.0, 7B equal; against four steps in flight or two waves per pair).
+            if (ch <= 4) return launch_gemv_cfg<WT, EPI, 2, 2, 2>(p, s, opt, blocks_out);
+            if (p.part && p.n_rows < 8192) return launch_gemv_cfg<WT, EPI, 2, 4, 1>(p, s, opt, blocks_out);
+            return launch_gemv_cfg<WT, EPI, 2, 2, 4>(p, s, opt, blocks_out);
+        } else if constexpr (EPI == EPI_QKV) {
+            // a wave per pair where there are pairs for every wave slot or hardly any chunks (7B 19.9 -> 19.4, 13B 29.3 -> 28.6,
+            // 1024-wide 6.1 -> 5.3), else two (Llama-3-8B, 6144 rows: 11.9 against 13.1)
+            if (p.n_rows >= 8192 || ch <= 2) return launch_gemv_cfg<WT, EPI, 2, 2, 1>(p, s, opt, blocks_out);
+            return launch_gemv_cfg<WT, EPI, 2, 2, 2>(p, s, opt, blocks_out);
+        } else if constexpr (EPI == EPI_SWIGLU) {
+            // two waves per pair with four steps in flight where a pair is a multiple of four steps (7B 28.7 against 30.2 with
+            // two), else two: the item count is padded to the pipeline's depth (13B, five steps per pair: 48.0 -> 45.9)
+            if (ch <= 2) return launch_gemv_cfg<WT, EPI, 2, 2, 1>(p, s, opt, blocks_out);
+            if (p.n_rows >= 8192 && ch % 8 == 0) return launch_gemv_cfg<WT, EPI, 2, 4, 2>(p, s, opt, blocks_out);
+            return launch_gemv_cfg<WT, EPI, 2, 2, 2>(p, s, opt, blocks_out);
+        } else {   // LM head: a wave per pair
+            if (p.n_rows >= 8192) return launch_gemv_cfg<WT, EPI, 2, 4, 1>(p, s, opt, blocks_out);
+            return launch_gemv_cfg<WT, EPI, 2, 2, 2>(p, s, opt, blocks_out);
+        }
+    } else {
+        if (p.n_rows >= 8192) return launch_gemv_cfg<WT, EPI, 2, 4, 1>(p, s, opt, blocks_out);
+        if (ch <= 12) return launch_gemv_cfg<WT, EPI, 2, 2, 2>(p, s, opt, blocks_out);
+        if (ch <= 40) return launch_gemv_cfg<WT, EPI, 4, 2, 4>(p, s, opt, blocks_out);
+        return launch_gemv_cfg<WT, EPI, 4, 2, 8>(p, s, opt, blocks_out);
     }
-    if constexpr (EPI == EPI_RESID && sizeof(WT) == 2) {
-        if (p.part && ch <= 12) return launch_gemv_cfg<WT, EPI, 2, 4, 1>(p, s, opt, blocks_out);
-        if (ch > 12 && ch <= 40) return launch_gemv_cfg<WT, EPI, 2, 4, 4>(p, s, opt, blocks_out);
-    }
-    if (ch <= 12) return launch_gemv_cfg<WT, EPI, 2, 2, 2>(p, s, opt, blocks_out);
-    if (ch <= 40) return launch_gemv_cfg<WT, EPI, 4, 2, 4>(p, s, opt, blocks_out);
-    return launch_gemv_cfg<WT, EPI, 4, 2, 8>(p, s, opt, blocks_out);
 }
 
 template <int EPI>
