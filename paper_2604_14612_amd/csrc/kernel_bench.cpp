@@ -498,7 +498,7 @@ int main(int argc, char** argv)
     opts.attn_splits = 0;
     opts.gemv_block_cap = 0;
     timeit("vocab_reduce 1 row", 32000 * 4.0, n, [&](int) {
-        CK(vocab_reduce(logits, 1, 32000, 1e4f, 1e-10f, pos + 8, 1, nullptr, sink, nullptr, 0)); });
+        CK(vocab_reduce(logits, 1, 32000, 1e4f, 1e-10f, pos + 8, pos + 9, nullptr, sink, nullptr, 0)); });
 
     // multi-row (verify) kernels, M rows
     bool with_ssq = false;

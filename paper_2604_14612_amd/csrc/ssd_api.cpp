@@ -23,7 +23,7 @@ constexpr size_t ALIGN = 256;
 size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 
 struct Layout {
-    size_t rope, kv, x, h, qkv, att, act, part, logits, taps, tapn, hi, lo, ssq, small, vtok, ring, ring_conf, total;
+    size_t rope, kv, x, h, qkv, att, act, part, logits, taps, tapn, hi, lo, ssq, small, ring, ring_conf, total;
     int rows;       // activation rows: max(max_k + 1, prompt rows per pass)
     int prefill_rows;  // prompt rows per pass: SSD_PREFILL_ROWS where the shape fits the 128 x 128 tiling, 64 where only the
                        // 64-row one, else 16
@@ -101,19 +101,24 @@ Layout make_layout(const ssd_config& c)
     }
     l.ssq = o;    o += align_up((size_t)l.rows * (D.d / 16 + 1) * sizeof(float));  // per-tile sums of squares of the residual rows
     l.small = o;  o += align_up(4096);
-    l.vtok = o;   o += align_up((size_t)l.rows * sizeof(int32_t));   // token ids of a prompt block
     // context window of the confidence extraction: hidden-state taps [window][2L][d] of the last `window` processed
     // positions, and one confidence value per tap row of the window
     l.ring = o;       o += align_up((size_t)c.conf_window * 2 * D.L * D.d * sizeof(float));
-    l.ring_conf = o;  o += align_up(((size_t)c.conf_window * 2 * D.L + 2 * D.L) * sizeof(float));
+    l.ring_conf = o;  o += align_up((size_t)c.conf_window * 2 * D.L * sizeof(float));
     l.total = o;
     return l;
 }
 
 // offsets (in 4-byte words) inside the "small" region
-enum { SM_POS = 0, SM_TOK = 8 /* 17 ints: pending + drafts */, SM_RES = 56 /* 2 */, SM_MAXPROB = 64 /* 16 floats */,
-       SM_SINK = 96, SM_ROPE = 768 /* 128 floats: rotary row of the single-row step's position */, SM_CONF = 128 /* conf_rows floats x3 follow (at most 3 x 2 x SSD_MAX_LAYERS, checked where used) */,
-       SM_VTOK = 896 /* 64: tokens of a row block */, SM_TARGET = 960 /* 64: greedy token after each row of a block */ };
+enum { SM_POS = 0, SM_TOK = 8 /* 17 ints: pending + drafts */, SM_SINK = 96, SM_ROPE = 768 /* 128 floats: rotary row of the single-row step's position */,
+       SM_TARGET = 960 /* 64: greedy token after each row of a block */ };
+
+// word offsets in the context's host-pinned buffer.  Kernels read the token ids of a pass from it and write the few words
+// a call returns into it, so that a call costs no copy in either direction, only the synchronisation at its end; every
+// call that uses a region synchronises before it returns, so the next one may write it.
+enum { PIN_TOK = 0 /* 17: slot i + 1 = token of draft step i */, PIN_PROB = 32 /* 16 */, PIN_TARGET = 64 /* 64 */,
+       PIN_VTOK = 128 /* 17: row 0 unused, drafts */, PIN_RES = 256 /* 3 x 2 x SSD_MAX_LAYERS */,
+       PIN_PROMPT = 256 + 6 * SSD_MAX_LAYERS /* max_seq */ };
 
 }  // namespace
 
@@ -137,7 +142,7 @@ struct ssd_ctx {
     long ring_count;   // positions pushed into the context-window ring since the last prefill
     int tap_row0;      // index of the first valid tap row inside the tap buffer
     int logit_rows;    // rows with valid logits
-    int32_t* pinned;   // host-pinned readback buffer
+    int32_t* pinned;   // host-pinned tokens and results (PIN_*)
     int device;        // device that was current when the workspace was set
     void* static_scratch;  // this device's copy of the library's static scratch array (resolved at set_workspace)
     ssd_stats st;
@@ -151,6 +156,7 @@ struct ssd_ctx {
     uint16_t* h16(size_t off) const { return reinterpret_cast<uint16_t*>(ws + off); }
     int32_t* small_i() const { return reinterpret_cast<int32_t*>(ws + lay.small); }
     float* small_f() const { return reinterpret_cast<float*>(ws + lay.small); }
+    float* pin_f(int word) const { return reinterpret_cast<float*>(pinned + word); }
     int* pos_dev() const { return small_i() + SM_POS; }
     void* kcache(int l) const
     {
@@ -241,7 +247,7 @@ int layer_single(ssd_ctx* c, int l, int pos_off, bool do_attn, bool do_mlp)
 }
 
 // Single-row forward of the token in tok slot `slot` at position *pos + pos_off; the greedy token goes to
-// tok slot `slot_out`, its logits to logits row `lrow`, its max-probability to SM_MAXPROB[lrow].
+// tok slot `slot_out` (device and PIN_TOK), its logits to logits row `lrow`, its max-probability to PIN_PROB[lrow].
 // sub (may be null): two entries per layer, [2l] != 0 leaves out the attention sub-block, [2l+1] != 0 the MLP sub-block.
 // flags: STEP_CHAINED = the previous step of the same sequence left this token's embedding in x; STEP_CHAIN_NEXT = leave
 // the new token's embedding there; STEP_COMMIT = the new token becomes the pending one and *pos advances.
@@ -250,7 +256,7 @@ int forward_single(ssd_ctx* c, const uint8_t* sub, int slot, int slot_out, int p
 {
     const Dims& D = c->D;
     if (!(flags & STEP_CHAINED))
-        HIPCHK(embed_rows(D, c->w.embed, c->small_i() + SM_TOK + slot, 1, c->f(c->lay.x), c->stream, c->f(c->lay.rope),
+        HIPCHK(embed_rows(D, c->w.embed, Tokens{c->small_i() + SM_TOK + slot, nullptr}, 1, c->f(c->lay.x), c->stream, c->f(c->lay.rope),
                           c->pos_dev(), pos_off, c->small_f() + SM_ROPE), "embed");
     for (int l = 0; l < D.L; l++) {
         const bool do_attn = !(sub && sub[2 * l]), do_mlp = !(sub && sub[2 * l + 1]);
@@ -261,7 +267,8 @@ int forward_single(ssd_ctx* c, const uint8_t* sub, int slot, int slot_out, int p
     float* logits = c->f(c->lay.logits) + (size_t)lrow * D.V;
     StepOut out = {};
     out.tok_out = c->small_i() + SM_TOK + slot_out;
-    out.maxprob_out = c->small_f() + SM_MAXPROB + lrow;
+    out.tok_host = c->pinned + PIN_TOK + slot_out;
+    out.maxprob_host = c->pin_f(PIN_PROB + lrow);
     if (flags & STEP_COMMIT) { out.pos_dev = c->pos_dev(); out.tok0 = c->small_i() + SM_TOK; }
     if (flags & STEP_CHAIN_NEXT) {
         out.embed = c->w.embed; out.x_next = c->f(c->lay.x);
@@ -282,22 +289,21 @@ int lmhead_argmax(ssd_ctx* c, RowsFused& lm)
     const bool fold = (size_t)lm.M * (D.V / 16) * 2 <= c->lay.part_floats;
     if (fold) { lm.vmax = reinterpret_cast<float2*>(c->f(c->lay.part)); lm.clamp = c->cfg.conf_clamp; }
     TIMED(SSD_K_ROWS_LMHEAD, rows_fused(D, lm, c->stream), "rows_lmhead");
-    if (fold) HIPCHK(argmax_tiles(lm.vmax, lm.M, D.V / 16, c->small_i() + SM_TARGET, c->stream), "argmax_tiles");
-    else HIPCHK(vocab_reduce(c->f(c->lay.logits), lm.M, D.V, c->cfg.conf_clamp, c->cfg.conf_eps, c->small_i() + SM_TARGET, 1,
+    if (fold) HIPCHK(argmax_tiles(lm.vmax, lm.M, D.V / 16, c->small_i() + SM_TARGET, c->pinned + PIN_TARGET, c->stream), "argmax_tiles");
+    else HIPCHK(vocab_reduce(c->f(c->lay.logits), lm.M, D.V, c->cfg.conf_clamp, c->cfg.conf_eps, c->small_i() + SM_TARGET, c->pinned + PIN_TARGET,
                              nullptr, nullptr, nullptr, c->stream), "vocab_reduce");
     return SSD_OK;
 }
 
-// Full-model forward of the M tokens in SM_VTOK (M <= 16, or <= 64 where the wide tiling applies) at positions
+// Full-model forward of M tokens (M <= 16, or <= 64 where the wide tiling applies) at positions
 // *pos + pos_off + r; taps into tap rows 0..M-1; logits (when want_logits) into logits rows 0..M-1 and greedy tokens
 // into SM_TARGET -- for a block of more than 16 rows (a prompt block) only the last row's.
-int forward_rows(ssd_ctx* c, int M, int pos_off, int pos_host, bool want_logits, const int32_t* tok_dev = nullptr)
+int forward_rows(ssd_ctx* c, int M, int pos_off, int pos_host, bool want_logits, Tokens tok)
 {
     const Dims& D = c->D;
     const Layout& Y = c->lay;
     float* x = c->f(Y.x);
     float* h = c->f(Y.h);
-    if (!tok_dev) tok_dev = c->small_i() + SM_VTOK;
     const int tap_ld = D.L * 2 * D.d;
     if (M > 16) {
         // prompt block: the same sequence as the 16-row path below, on 128 x 128 tiles over all rows of the block at
@@ -313,7 +319,7 @@ int forward_rows(ssd_ctx* c, int M, int pos_off, int pos_host, bool want_logits,
         uint16_t* xl = xh + (size_t)Y.rows * D.d;
         float* ssq = c->f(Y.ssq);
         const int n_ssq = D.d / 64;
-        HIPCHK(embed_split(D, c->w.embed, tok_dev, M, c->attn_norm[0], x, xh, xl, ssq, 64, c->stream), "embed_split");
+        HIPCHK(embed_split(D, c->w.embed, tok, M, c->attn_norm[0], x, xh, xl, ssq, 64, c->stream), "embed_split");
         for (int l = 0; l < D.L; l++) {
             RowsFused q = {};
             q.w[0] = c->wq[l]; q.w[1] = c->wk[l]; q.w[2] = c->wv[l]; q.n[0] = D.dq; q.n[1] = D.dkv; q.n[2] = D.dkv;
@@ -369,7 +375,7 @@ int forward_rows(ssd_ctx* c, int M, int pos_off, int pos_host, bool want_logits,
         uint16_t* xl = xh + (size_t)Y.rows * D.d;
         float* ssq = c->f(Y.ssq);
         const int n_ssq = D.d / 16;
-        HIPCHK(embed_split(D, c->w.embed, tok_dev, M, c->attn_norm[0], x, xh, xl, ssq, 16, c->stream), "embed_split");
+        HIPCHK(embed_split(D, c->w.embed, tok, M, c->attn_norm[0], x, xh, xl, ssq, 16, c->stream), "embed_split");
         for (int l = 0; l < D.L; l++) {
             RowsFused q = {};
             q.w[0] = c->wq[l]; q.w[1] = c->wk[l]; q.w[2] = c->wv[l]; q.n[0] = D.dq; q.n[1] = D.dkv; q.n[2] = D.dkv;
@@ -408,7 +414,7 @@ int forward_rows(ssd_ctx* c, int M, int pos_off, int pos_host, bool want_logits,
         }
         return SSD_OK;
     }
-    HIPCHK(embed_rows(D, c->w.embed, tok_dev, M, x, c->stream), "embed");
+    HIPCHK(embed_rows(D, c->w.embed, tok, M, x, c->stream), "embed");
     if (rows_plain_supported(D)) {
         // fp32 weights (and fp16 shapes outside the tiling): fp32 rows between the launches, norms, rotary embedding and
         // cache rows inside them
@@ -438,7 +444,7 @@ int forward_rows(ssd_ctx* c, int M, int pos_off, int pos_host, bool want_logits,
             lm.w[0] = c->w.lm_head; lm.n[0] = D.V; lm.K = D.d; lm.x = x; lm.gain = c->w.final_norm; lm.y = c->f(Y.logits);
             lm.ldy = D.V; lm.M = M; lm.mode = 0;
             TIMED(SSD_K_ROWS_LMHEAD, rows_plain(D, lm, c->stream), "plain_lmhead");
-            HIPCHK(vocab_reduce(c->f(Y.logits), M, D.V, c->cfg.conf_clamp, c->cfg.conf_eps, c->small_i() + SM_TARGET, 1,
+            HIPCHK(vocab_reduce(c->f(Y.logits), M, D.V, c->cfg.conf_clamp, c->cfg.conf_eps, c->small_i() + SM_TARGET, c->pinned + PIN_TARGET,
                                 nullptr, nullptr, nullptr, c->stream), "vocab_reduce");
         }
         return SSD_OK;
@@ -474,7 +480,7 @@ int forward_rows(ssd_ctx* c, int M, int pos_off, int pos_host, bool want_logits,
         lm.w[0] = c->w.lm_head; lm.n[0] = D.V; lm.K = D.d; lm.x = h; lm.y = c->f(Y.logits); lm.ldy = D.V; lm.M = M;
         lm.mode = 0;
         TIMED(SSD_K_ROWS_LMHEAD, gemm_rows(D, lm, c->stream), "gemm_lmhead");
-        HIPCHK(vocab_reduce(c->f(Y.logits), M, D.V, c->cfg.conf_clamp, c->cfg.conf_eps, c->small_i() + SM_TARGET, 1,
+        HIPCHK(vocab_reduce(c->f(Y.logits), M, D.V, c->cfg.conf_clamp, c->cfg.conf_eps, c->small_i() + SM_TARGET, c->pinned + PIN_TARGET,
                             nullptr, nullptr, nullptr, c->stream), "vocab_reduce");
     }
     return SSD_OK;
@@ -519,17 +525,15 @@ int run_sequence(ssd_ctx* c, const std::string& key, F&& body)
     return SSD_OK;
 }
 
-int readback(ssd_ctx* c, const void* dev, size_t bytes, void* host)
+// Waits for the results a call's kernels leave in the pinned buffer.
+int sync_results(ssd_ctx* c)
 {
-    HIPCHK(hipMemcpyAsync(c->pinned, dev, bytes, hipMemcpyDeviceToHost, c->stream), "readback copy");
-    HIPCHK(hipStreamSynchronize(c->stream), "readback sync");
-    memcpy(host, c->pinned, bytes);
+    HIPCHK(hipStreamSynchronize(c->stream), "result sync");
     return SSD_OK;
 }
 
-
 // Device buffers one confidence pass works in: hi/lo pairs of the normalised tap rows (16-bit weights), the normalised
-// rows themselves (fp32 weights), their logits, and 3 result values per row; `batch` tap rows go through per pass.
+// rows themselves (fp32 weights), their logits, and 3 result values per row in the pinned buffer; `batch` tap rows go through per pass.
 struct ConfScratch {
     uint16_t* hi; uint16_t* lo; float* tapn; float* logits; float* res; int batch;
     bool one_gemm;   // the context-window pass: a batch of more than 64 rows goes through the 128 x 128-tile GEMM in
@@ -608,9 +612,9 @@ int confidence_rows(ssd_ctx* c, const ConfScratch& sc, int row_begin, int n_rows
             int rc = conf_batch(c, sc, taps_row + (size_t)b0 * D.d, nb, sc.res, sc.res + nb,
                                 reinterpret_cast<int32_t*>(sc.res + 2 * nb));
             if (rc) return rc;
-            float tmp[3 * 64 > 3 * 2 * SSD_MAX_LAYERS ? 3 * 64 : 3 * 2 * SSD_MAX_LAYERS];
-            rc = readback(c, sc.res, sizeof(float) * 3 * nb, tmp);
+            rc = sync_results(c);
             if (rc) return rc;
+            const float* tmp = sc.res;
             for (int i = 0; i < nb; i++) {   // regroup as [R] conf, [R] maxprob, [R] argmax
                 hb[b0 + i] = tmp[i]; hb[R + b0 + i] = tmp[nb + i]; hb[2 * R + b0 + i] = tmp[2 * nb + i];
             }
@@ -695,7 +699,7 @@ int ssd_set_workspace(ssd_ctx* c, void* dev, size_t bytes)
             tab[((size_t)p * half + i) * 2 + 0] = (float)std::cos(ang);
             tab[((size_t)p * half + i) * 2 + 1] = (float)std::sin(ang);
         }
-    if (!c->pinned) HIPCHK(hipHostMalloc((void**)&c->pinned, 64 * 1024, hipHostMallocDefault), "hipHostMalloc");
+    if (!c->pinned) HIPCHK(hipHostMalloc((void**)&c->pinned, ((size_t)PIN_PROMPT + c->D.max_seq) * 4, hipHostMallocMapped | hipHostMallocCoherent), "hipHostMalloc");
     HIPCHK(hipGetDevice(&c->device), "hipGetDevice");
     HIPCHK(static_scratch_for_device(c->device, &c->static_scratch), "static scratch address");
     c->ws = static_cast<char*>(dev);
@@ -778,17 +782,11 @@ int ssd_prefill(ssd_ctx* c, const int32_t* tokens, int n, int32_t* first_token_o
     HIPCHK(set_state(c->small_i() + SM_TOK, 0, c->pos_dev(), 0, c->stream), "set_state");
     int last_M = 0;
     const int block = c->lay.prefill_rows;
-    int32_t* vtok = reinterpret_cast<int32_t*>(c->ws + c->lay.vtok);
+    memcpy(c->pinned + PIN_PROMPT, tokens, (size_t)n * sizeof(int32_t));
     for (int p0 = 0; p0 < n; p0 += block) {
         int M = n - p0 < block ? n - p0 : block;
-        for (int r0 = 0; r0 < M; r0 += 64) {   // token ids travel as kernel arguments, 64 at a time
-            TokArg t = {};
-            const int nr = M - r0 < 64 ? M - r0 : 64;
-            for (int r = 0; r < nr; r++) t.t[r] = tokens[p0 + r0 + r];
-            HIPCHK(set_tokens(t, nr, nullptr, vtok + r0, c->stream), "set_tokens");
-        }
         bool last = p0 + M == n;
-        int rc = forward_rows(c, M, p0, 0, last, vtok);
+        int rc = forward_rows(c, M, p0, 0, last, Tokens{c->pinned + PIN_PROMPT + p0, nullptr});
         if (rc) return rc;
         last_M = M;
     }
@@ -797,8 +795,9 @@ int ssd_prefill(ssd_ctx* c, const int32_t* tokens, int n, int32_t* first_token_o
     // pending token = greedy token after the last prompt row; n_cached positions = n
     HIPCHK(advance_state(c->pos_dev(), n, c->small_i() + SM_TOK, c->small_i() + SM_TARGET + res_row, c->stream),
            "advance_state");
-    int rc = readback(c, c->small_i() + SM_TARGET + res_row, sizeof(int32_t), first_token_out);
+    int rc = sync_results(c);
     if (rc) return rc;
+    *first_token_out = c->pinned[PIN_TARGET + res_row];
     c->n = n + 1;
     c->state = ST_IDLE;
     c->tap_rows = 1; c->tap_row0 = res_row;
@@ -826,8 +825,9 @@ int ssd_decode(ssd_ctx* c, int32_t* token_out)
         return forward_single(c, nullptr, 0, 1, 0, 0, STEP_COMMIT);
     });
     if (rc) return rc;
-    rc = readback(c, c->small_i() + SM_TOK + 1, sizeof(int32_t), token_out);
+    rc = sync_results(c);
     if (rc) return rc;
+    *token_out = c->pinned[PIN_TOK + 1];
     c->n += 1;
     c->logit_rows = 1;
     c->tap_rows = 0;
@@ -852,12 +852,10 @@ static int draft_fixed(ssd_ctx* c, const std::vector<uint8_t>& sub, int k, int32
         return (int)SSD_OK;
     });
     if (rc) return rc;
-    rc = readback(c, c->small_i() + SM_TOK + 1, sizeof(int32_t) * k, draft_out);
+    rc = sync_results(c);
     if (rc) return rc;
-    if (draft_maxprob_out) {
-        rc = readback(c, c->small_f() + SM_MAXPROB, sizeof(float) * k, draft_maxprob_out);
-        if (rc) return rc;
-    }
+    memcpy(draft_out, c->pinned + PIN_TOK + 1, sizeof(int32_t) * k);
+    if (draft_maxprob_out) memcpy(draft_maxprob_out, c->pinned + PIN_PROB, sizeof(float) * k);
     c->state = ST_DRAFTED;
     c->k_pending = k;
     c->logit_rows = k;
@@ -906,15 +904,14 @@ int ssd_draft_adaptive(ssd_ctx* c, const uint8_t* skip_mask, int k_max, float ga
         std::string key = "A|" + std::to_string(i) + "|" + mask_key + "|" + std::to_string(attention_splits(c->D, c->n + i, 1));
         int rc = run_sequence(c, key, [&]() { return forward_single(c, sub.data(), i, i + 1, i, i, 0); });
         if (rc) return rc;
-        float p = 0.f;
-        rc = readback(c, c->small_f() + SM_MAXPROB + i, sizeof(float), &p);
+        rc = sync_results(c);
         if (rc) return rc;
+        const float p = c->pin_f(PIN_PROB)[i];
+        draft_out[i] = c->pinned[PIN_TOK + 1 + i];
         k++;
         if (draft_maxprob_out) draft_maxprob_out[i] = p;
         if (p < gamma) break;
     }
-    int rc = readback(c, c->small_i() + SM_TOK + 1, sizeof(int32_t) * k, draft_out);
-    if (rc) return rc;
     *k_out = k;
     c->state = ST_DRAFTED;
     c->k_pending = k;
@@ -931,14 +928,13 @@ int ssd_verify(ssd_ctx* c, const int32_t* draft, int k, int32_t* target_out)
     if (k != c->k_pending) return fail(c, SSD_EINVAL, "verify: k differs from the draft's");
     for (int i = 0; i < k; i++)
         if (draft[i] < 0 || draft[i] >= c->D.V) return fail(c, SSD_EINVAL, "draft token id out of range");
-    TokArg t = {};
-    for (int i = 0; i < k; i++) t.t[i + 1] = draft[i];
-    HIPCHK(set_tokens(t, k + 1, c->small_i() + SM_TOK, c->small_i() + SM_VTOK, c->stream), "set_tokens");
+    for (int i = 0; i < k; i++) c->pinned[PIN_VTOK + 1 + i] = draft[i];
     std::string key = "V|" + std::to_string(k) + "|" + std::to_string(attention_splits(c->D, c->n + k, k + 1));
-    int rc = run_sequence(c, key, [&]() { return forward_rows(c, k + 1, 0, c->n - 1, true); });
+    int rc = run_sequence(c, key, [&]() { return forward_rows(c, k + 1, 0, c->n - 1, true, Tokens{c->pinned + PIN_VTOK, c->small_i() + SM_TOK}); });
     if (rc) return rc;
-    rc = readback(c, c->small_i() + SM_TARGET, sizeof(int32_t) * (k + 1), target_out);
+    rc = sync_results(c);
     if (rc) return rc;
+    memcpy(target_out, c->pinned + PIN_TARGET, sizeof(int32_t) * (k + 1));
     c->state = ST_VERIFIED;
     c->tap_rows = k + 1; c->tap_row0 = 0;
     c->logit_rows = k + 1;
@@ -1012,10 +1008,9 @@ int ssd_layer_confidence(ssd_ctx* c, int row_begin, int n_rows, float* conf_out,
     if (c->state < ST_IDLE || c->tap_rows == 0) return fail(c, SSD_ESTATE, "no hidden-state taps: call after prefill or verify");
     if (row_begin + n_rows > c->tap_rows) return fail(c, SSD_EINVAL, "layer_confidence: rows out of range");
     const Layout& Y = c->lay;
-    static_assert(SM_CONF + 3 * 2 * SSD_MAX_LAYERS <= SM_VTOK, "confidence results of 2 x SSD_MAX_LAYERS rows must end before the token slots");
     ConfScratch sc;
     sc.hi = c->h16(Y.hi); sc.lo = c->h16(Y.lo); sc.tapn = c->f(Y.tapn); sc.logits = c->f(Y.logits);
-    sc.res = c->small_f() + SM_CONF; sc.batch = 2 * c->D.L;     // all tap rows of a position in one pass
+    sc.res = c->pin_f(PIN_RES); sc.batch = 2 * c->D.L;     // all tap rows of a position in one pass
     sc.one_gemm = false;
     int rc = confidence_rows(c, sc, row_begin, n_rows, conf_out, tap_conf_out, tap_maxprob_out, tap_argmax_out, true);
     if (rc) return rc;
@@ -1044,7 +1039,8 @@ int ssd_layer_confidence_static(ssd_ctx* c, int row_begin, int n_rows, float* co
     sc.lo = reinterpret_cast<uint16_t*>(base + o);   o += align_up((size_t)B * D.d * 2);
     sc.tapn = reinterpret_cast<float*>(base + o);    o += align_up(rows_fused_supported(D) ? 0 : (size_t)B * D.d * 4);
     sc.logits = reinterpret_cast<float*>(base + o);  o += align_up((size_t)B * D.V * 4);
-    sc.res = reinterpret_cast<float*>(base + o);     o += align_up((size_t)3 * B * 4);
+    o += align_up((size_t)3 * B * 4);
+    sc.res = c->pin_f(PIN_RES);
     sc.batch = B; sc.one_gemm = false;
     if (o > static_scratch_bytes())
         return fail(c, SSD_ECAPACITY, "layer_confidence_static: 64 rows of this vocabulary / width exceed SSD_STATIC_SCRATCH_BYTES");
@@ -1069,16 +1065,15 @@ int ssd_window_confidence(ssd_ctx* c, float* conf_out, float* tap_conf_out, int3
     if (B > Y.logit_rows) B = Y.logit_rows;
     if (B > Y.conf_rows && B > Y.rows) B = Y.conf_rows > Y.rows ? Y.conf_rows : Y.rows;
     sc.batch = B;
-    float* conf_all = c->f(Y.ring_conf);                  // [nv * R], then R means
+    float* conf_all = c->f(Y.ring_conf);                  // [nv * R]
     for (long r0 = 0; r0 < rows; r0 += B) {
         const int nb = rows - r0 < B ? (int)(rows - r0) : B;
         int rc = conf_batch(c, sc, c->f(Y.ring) + (size_t)r0 * D.d, nb, conf_all + r0, nullptr, nullptr);
         if (rc) return rc;
     }
-    float* means = conf_all + (size_t)c->cfg.conf_window * R;
-    HIPCHK(window_mean(conf_all, nv, R, means, c->stream), "window mean");
-    float hb[2 * SSD_MAX_LAYERS];
-    int rc = readback(c, means, sizeof(float) * R, hb);
+    const float* hb = c->pin_f(PIN_RES);
+    HIPCHK(window_mean(conf_all, nv, R, c->pin_f(PIN_RES), c->stream), "window mean");
+    int rc = sync_results(c);
     if (rc) return rc;
     for (int l = 0; l < D.L; l++) {
         conf_out[l] = c->cfg.conf_taps == 2 ? 0.5f * (hb[2 * l] + hb[2 * l + 1]) : hb[2 * l + 1];

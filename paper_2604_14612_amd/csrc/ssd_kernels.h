@@ -35,13 +35,13 @@ struct Dims {
     LaunchOpts* opt = nullptr;  // may be null: library defaults, no timing
 };
 
-// x[r][:] = embed[tok_dev[r]][:] widened to fp32 (token ids in device memory, clamped to the vocabulary).
-struct TokArg { int32_t t[64]; };
+// Token ids of a row block: ids[r], in host-pinned memory (read once per row, over the bus) or on the device; row 0 takes
+// first[0] instead when first is set (the pending token, which only the device knows).
+struct Tokens { const int32_t* ids; const int32_t* first; };
+// x[r][:] = embed[token r][:] widened to fp32 (ids clamped to the vocabulary).
 // rope_row (may be null): hd floats, receives row *pos_dev + pos_off of the rotary table (what gemv_qkv takes).
-hipError_t embed_rows(const Dims& D, const void* embed, const int32_t* tok_dev, int M, float* x, hipStream_t s,
-                      const float* rope = nullptr, const int* pos_dev = nullptr, int pos_off = 0, float* rope_row = nullptr);
-// dst[i] = toks.t[i] for i < n, except dst[0] = first_dev[0] when first_dev != nullptr
-hipError_t set_tokens(TokArg toks, int n, const int32_t* first_dev, int32_t* dst, hipStream_t s);
+hipError_t embed_rows(const Dims& D, const void* embed, Tokens tok, int M, float* x, hipStream_t s, const float* rope = nullptr,
+                      const int* pos_dev = nullptr, int pos_off = 0, float* rope_row = nullptr);
 
 // Links of a chained launch (experimental overlap of consecutive kernels on two streams): the kernel waits, after its
 // first weight loads are in flight, until *wait_flag >= wait_count * *gen, and every one of its blocks adds 1 to
@@ -78,8 +78,8 @@ hipError_t gemv_lmhead(const Dims& D, const void* wlm, const float* gain, const 
 // logits in vstat (3 floats per block, GEMV_MAX_BLOCKS blocks at most) and a one-block kernel combines them into the greedy
 // token (lowest index among equal maxima) and its soft-max probability, and prepares the next step.
 struct StepOut {
-    int32_t* tok_out;
-    float* maxprob_out;        // may be null
+    int32_t* tok_out;                            // device slot
+    int32_t* tok_host; float* maxprob_host;      // host-pinned: the host reads them after synchronising, no copy is enqueued
     int* pos_dev; int32_t* tok0;   // decode: *pos_dev += 1, *tok0 = token (both null: left alone)
     const void* embed; float* x_next;   // x_next set: x_next[0..d) = embedding row of the token
     const float* rope; const int* rope_pos; int rope_off; float* rope_row;   // rope_row set: rotary row *rope_pos + rope_off of the next step
@@ -175,7 +175,7 @@ hipError_t rows_prep(const Dims& D, const float* in, int ldx, const float* gain,
 // x[r] = embedding row of token r (16-bit weights, d a multiple of 64), hi/lo = split(x * gain) (no norm scale) and ssq[r][t] = sum of x[r][group t .. group (t+1))^2,
 // group = 16 (rows_fused) or 64 (rows_wide, rows_big): the form in which a RESID projection with gain_out hands rows to
 // its consumer
-hipError_t embed_split(const Dims& D, const void* embed, const int32_t* tok_dev, int M, const float* gain, float* x, uint16_t* hi,
+hipError_t embed_split(const Dims& D, const void* embed, Tokens tok, int M, const float* gain, float* x, uint16_t* hi,
                        uint16_t* lo, float* ssq, int group, hipStream_t s);
 // rotary on q,k rows + cache write for the multi-row path. qkv: [M][dq + 2 dkv]; q is rotated in place.
 hipError_t rope_kv_rows(const Dims& D, float* qkv, const float* rope, const int* pos_dev, int pos_off, int M,
@@ -198,14 +198,14 @@ int attention_splits(const Dims& D, int ctx, int M);
 
 // ---- vocabulary reduction ------------------------------------------------------------------------
 // Per row of logits [M][V]: arg-max (lowest index on ties), softmax max-probability and, when
-// conf != nullptr, the entropy confidence of Eq. 1-4 (clamp applied first).  tok_out[r*tok_stride]
-// receives the arg-max when tok_out != nullptr.
+// conf != nullptr, the entropy confidence of Eq. 1-4 (clamp applied first).  tok_out[r] and tok_host[r] (host-pinned)
+// receive the arg-max when tok_out != nullptr.
 hipError_t vocab_reduce(const float* logits, int M, int V, float clamp, float eps, int32_t* tok_out,
-                        int tok_stride, int32_t* argmax_out, float* maxprob_out, float* conf_out,
+                        int32_t* tok_host, int32_t* argmax_out, float* maxprob_out, float* conf_out,
                         hipStream_t s);
 
-// tok_out[r] = lowest column of the largest clamped logit of row r, from the vmax records of a rows_fused LM-head launch
-hipError_t argmax_tiles(const float2* vmax, int M, int n_tiles, int32_t* tok_out, hipStream_t s);
+// tok_out[r] = tok_host[r] (host-pinned) = lowest column of the largest clamped logit of row r, from the vmax records of a rows_fused LM-head launch
+hipError_t argmax_tiles(const float2* vmax, int M, int n_tiles, int32_t* tok_out, int32_t* tok_host, hipStream_t s);
 // Confidence, max-probability and arg-max of M rows as vocab_reduce gives them, cut along the vocabulary where the rows
 // alone leave the chip idle; scratch (may be null: never cut) takes 24 bytes per row and slice.
 hipError_t vocab_confidence(const float* logits, int M, int V, float clamp, float eps, int32_t* argmax_out, float* maxprob_out,

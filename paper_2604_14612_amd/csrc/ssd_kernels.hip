@@ -171,40 +171,30 @@ struct RopeRow {
     __device__ __forceinline__ void copy(int t) const { out[t] = table[(size_t)(pos_dev[0] + pos_off) * hd + t]; }
 };
 
+__device__ __forceinline__ int token_of(const Tokens& t, int r) { return r == 0 && t.first ? t.first[0] : t.ids[r]; }
+
 template <typename WT>
-__global__ void embed_kernel(const WT* __restrict__ E, const int32_t* __restrict__ tok_dev, int d, int V,
-                             float* __restrict__ x, RopeRow rr)
+__global__ void embed_kernel(const WT* __restrict__ E, Tokens tok, int d, int V, float* __restrict__ x, RopeRow rr)
 {
     int r = blockIdx.y;
     if (rr.out && blockIdx.x == 0 && r == 0 && (int)threadIdx.x < rr.hd) rr.copy(threadIdx.x);
-    int t = tok_dev[r];
+    int t = token_of(tok, r);
     t = min(max(t, 0), V - 1);
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < d; i += gridDim.x * blockDim.x)
         x[(size_t)r * d + i] = Elem<WT>::get(E, (size_t)t * d + i);
 }
 
-hipError_t embed_rows(const Dims& D, const void* embed, const int32_t* tok_dev, int M, float* x, hipStream_t s, const float* rope,
+hipError_t embed_rows(const Dims& D, const void* embed, Tokens tok, int M, float* x, hipStream_t s, const float* rope,
                       const int* pos_dev, int pos_off, float* rope_row)
 {
     const RopeRow rr = {rope, pos_dev, pos_off, D.hd, rope_row};
     dim3 grid(ceil_div(D.d, 256), M);
     if (D.wt == WT_BF16)
-        hipLaunchKernelGGL(embed_kernel<uint16_t>, grid, dim3(256), 0, s, (const uint16_t*)embed, tok_dev, D.d, D.V, x, rr);
+        hipLaunchKernelGGL(embed_kernel<uint16_t>, grid, dim3(256), 0, s, (const uint16_t*)embed, tok, D.d, D.V, x, rr);
     else if (D.wt == WT_F16)
-        hipLaunchKernelGGL(embed_kernel<f16_t>, grid, dim3(256), 0, s, (const f16_t*)embed, tok_dev, D.d, D.V, x, rr);
+        hipLaunchKernelGGL(embed_kernel<f16_t>, grid, dim3(256), 0, s, (const f16_t*)embed, tok, D.d, D.V, x, rr);
     else
-        hipLaunchKernelGGL(embed_kernel<float>, grid, dim3(256), 0, s, (const float*)embed, tok_dev, D.d, D.V, x, rr);
-    return hipGetLastError();
-}
-
-__global__ void set_tokens_kernel(TokArg toks, int n, const int32_t* first_dev, int32_t* dst)
-{
-    int i = threadIdx.x;
-    if (i < n) dst[i] = (i == 0 && first_dev) ? first_dev[0] : toks.t[i];
-}
-hipError_t set_tokens(TokArg toks, int n, const int32_t* first_dev, int32_t* dst, hipStream_t s)
-{
-    hipLaunchKernelGGL(set_tokens_kernel, dim3(1), dim3(64), 0, s, toks, n, first_dev, dst);
+        hipLaunchKernelGGL(embed_kernel<float>, grid, dim3(256), 0, s, (const float*)embed, tok, D.d, D.V, x, rr);
     return hipGetLastError();
 }
 
@@ -686,9 +676,7 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_kernel(GemvP p)
 // of a decode step, or the embedding row that the next draft step starts from.
 constexpr int SF_THREADS = 1024;
 template <typename WT>
-__global__ __launch_bounds__(SF_THREADS) void step_finish_kernel(const float* __restrict__ vstat, int n_blocks, int32_t* tok_out,
-                                                                 float* maxprob_out, int* pos_dev, int32_t* tok0,
-                                                                 const WT* __restrict__ E, int d, float* __restrict__ x, RopeRow rr)
+__global__ __launch_bounds__(SF_THREADS) void step_finish_kernel(const float* __restrict__ vstat, int n_blocks, StepOut o, int d, RopeRow rr)
 {
     __shared__ VStat sm[SF_THREADS / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -713,14 +701,16 @@ __global__ __launch_bounds__(SF_THREADS) void step_finish_kernel(const float* __
         wave_merge(a);
         if (lane == 0) {
             sm[0] = a;
-            tok_out[0] = a.arg;
-            if (maxprob_out) maxprob_out[0] = 1.0f / a.z;
-            if (pos_dev) { pos_dev[0] += 1; tok0[0] = a.arg; }
+            o.tok_out[0] = a.arg;
+            o.tok_host[0] = a.arg;
+            o.maxprob_host[0] = 1.0f / a.z;
+            if (o.pos_dev) { o.pos_dev[0] += 1; o.tok0[0] = a.arg; }
         }
     }
-    if (!x) return;   // uniform
+    if (!o.x_next) return;   // uniform
     __syncthreads();
-    const WT* row = E + (size_t)sm[0].arg * d;
+    const WT* row = static_cast<const WT*>(o.embed) + (size_t)sm[0].arg * d;
+    float* x = o.x_next;
     for (int i = tid * 4; i < d; i += SF_THREADS * 4)
         *reinterpret_cast<float4*>(x + i) = make_float4(Elem<WT>::get(row, i), Elem<WT>::get(row, i + 1), Elem<WT>::get(row, i + 2), Elem<WT>::get(row, i + 3));
 }
@@ -909,7 +899,7 @@ hipError_t gemv_lmhead(const Dims& D, const void* wlm, const float* gain, const 
 hipError_t gemv_lmhead_argmax(const Dims& D, const void* wlm, const float* gain, const float* x, float* logits, float clamp,
                               float* vstat, const StepOut& o, hipStream_t s)
 {
-    if (!vstat || !o.tok_out || (o.pos_dev && !o.tok0) || (o.x_next && !o.embed)) return hipErrorInvalidValue;
+    if (!vstat || !o.tok_out || !o.tok_host || !o.maxprob_host || (o.pos_dev && !o.tok0) || (o.x_next && !o.embed)) return hipErrorInvalidValue;
     GemvP p = {};
     p.w0 = wlm; p.in = x; p.gain = gain; p.eps = D.eps; p.K = D.d; p.n_rows = D.V; p.y = logits;
     p.vstat = vstat; p.clamp = clamp;
@@ -918,15 +908,9 @@ hipError_t gemv_lmhead_argmax(const Dims& D, const void* wlm, const float* gain,
     if (e != hipSuccess) return e;
     if (blocks < 1 || blocks > GEMV_MAX_BLOCKS) return hipErrorInvalidValue;
     const RopeRow rr = {o.rope, o.rope_pos, o.rope_off, D.hd, o.rope_row};
-    if (D.wt == WT_BF16)
-        hipLaunchKernelGGL(step_finish_kernel<uint16_t>, dim3(1), dim3(SF_THREADS), 0, s, vstat, blocks, o.tok_out, o.maxprob_out,
-                           o.pos_dev, o.tok0, (const uint16_t*)o.embed, D.d, o.x_next, rr);
-    else if (D.wt == WT_F16)
-        hipLaunchKernelGGL(step_finish_kernel<f16_t>, dim3(1), dim3(SF_THREADS), 0, s, vstat, blocks, o.tok_out, o.maxprob_out,
-                           o.pos_dev, o.tok0, (const f16_t*)o.embed, D.d, o.x_next, rr);
-    else
-        hipLaunchKernelGGL(step_finish_kernel<float>, dim3(1), dim3(SF_THREADS), 0, s, vstat, blocks, o.tok_out, o.maxprob_out,
-                           o.pos_dev, o.tok0, (const float*)o.embed, D.d, o.x_next, rr);
+    if (D.wt == WT_BF16) hipLaunchKernelGGL(step_finish_kernel<uint16_t>, dim3(1), dim3(SF_THREADS), 0, s, vstat, blocks, o, D.d, rr);
+    else if (D.wt == WT_F16) hipLaunchKernelGGL(step_finish_kernel<f16_t>, dim3(1), dim3(SF_THREADS), 0, s, vstat, blocks, o, D.d, rr);
+    else hipLaunchKernelGGL(step_finish_kernel<float>, dim3(1), dim3(SF_THREADS), 0, s, vstat, blocks, o, D.d, rr);
     return hipGetLastError();
 }
 
@@ -2480,7 +2464,7 @@ hipError_t rows_prep(const Dims& D, const float* in, int ldx, const float* gain,
 // consecutive elements.  A thread owns four elements, a block 1024 of one row.  (As two launches, a gather and a split in
 // which one thread walked a whole group: 9.7 + 12 us for 512 rows of 4096, 4.5 + 3.6 us for five.)
 template <typename WT, int GROUP>
-__global__ __launch_bounds__(256) void embed_split_kernel(const WT* __restrict__ E, const int32_t* __restrict__ tok_dev, int d, int V,
+__global__ __launch_bounds__(256) void embed_split_kernel(const WT* __restrict__ E, Tokens tok, int d, int V,
                                                           const float* __restrict__ gain, float* __restrict__ x,
                                                           uint16_t* __restrict__ hi, uint16_t* __restrict__ lo,
                                                           float* __restrict__ ssq)
@@ -2488,7 +2472,7 @@ __global__ __launch_bounds__(256) void embed_split_kernel(const WT* __restrict__
     constexpr bool F16 = IsF16<WT>::value;
     const int r = blockIdx.y, i = (blockIdx.x * 256 + threadIdx.x) * 4;
     if (i >= d) return;   // whole DPP rows: d is a multiple of 64
-    const int t = min(max(tok_dev[r], 0), V - 1);
+    const int t = min(max(token_of(tok, r), 0), V - 1);
     const uint2 w = *reinterpret_cast<const uint2*>(E + (size_t)t * d + i);
     const float4 g = *reinterpret_cast<const float4*>(gain + i);
     const float4 v = make_float4(h16_bits_to_f32(w.x & 0xffff, F16), h16_bits_to_f32(w.x >> 16, F16),
@@ -2510,13 +2494,13 @@ __global__ __launch_bounds__(256) void embed_split_kernel(const WT* __restrict__
     if ((i & (GROUP - 1)) == 0) ssq[(size_t)r * (d / GROUP) + i / GROUP] = sq;
 }
 
-hipError_t embed_split(const Dims& D, const void* embed, const int32_t* tok_dev, int M, const float* gain, float* x, uint16_t* hi,
+hipError_t embed_split(const Dims& D, const void* embed, Tokens tok, int M, const float* gain, float* x, uint16_t* hi,
                        uint16_t* lo, float* ssq, int group, hipStream_t s)
 {
     if ((group != 16 && group != 64) || D.d % 64 || D.wt == WT_F32 || !gain || M < 1) return hipErrorInvalidValue;
     const dim3 grid(ceil_div(D.d, 1024), M);
     auto go = [&](auto kernel, auto e) {
-        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, e, tok_dev, D.d, D.V, gain, x, hi, lo, ssq);
+        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, e, tok, D.d, D.V, gain, x, hi, lo, ssq);
         return hipGetLastError();
     };
     if (D.wt == WT_F16) return group == 16 ? go(embed_split_kernel<f16_t, 16>, (const f16_t*)embed) : go(embed_split_kernel<f16_t, 64>, (const f16_t*)embed);
@@ -3724,7 +3708,7 @@ __device__ __forceinline__ void argmax_wave(float& m, int& mi)
 }
 
 __global__ __launch_bounds__(VR_THREADS) void vocab_reduce_kernel(const float* __restrict__ logits, int V, float clamp,
-                                                                  float eps, int32_t* tok_out, int tok_stride,
+                                                                  float eps, int32_t* tok_out, int32_t* tok_host,
                                                                   int32_t* argmax_out, float* maxprob_out, float* conf_out)
 {
     __shared__ float rv[16];
@@ -3754,7 +3738,7 @@ __global__ __launch_bounds__(VR_THREADS) void vocab_reduce_kernel(const float* _
     for (int i = tid; i < V; i += VR_THREADS) zs += expf(fminf(fmaxf(z[i], -clamp), clamp) - m);
     const double Z = block_sum<16>(zs, rd);
     if (tid == 0) {
-        if (tok_out) tok_out[(size_t)r * tok_stride] = mi;
+        if (tok_out) { tok_out[r] = mi; tok_host[r] = mi; }
         if (argmax_out) argmax_out[r] = mi;
         if (maxprob_out) maxprob_out[r] = (float)(1.0 / Z);
     }
@@ -3775,7 +3759,7 @@ __global__ __launch_bounds__(VR_THREADS) void vocab_reduce_kernel(const float* _
 // row, lowest column among equal maxima.  (Reading the logits back instead is one block walking 128-513 KB: 18.5 us at
 // 32 000 columns, 65 us at 128 256.)
 __global__ __launch_bounds__(VR_THREADS) void argmax_tiles_kernel(const float2* __restrict__ vmax, int n_tiles,
-                                                                  int32_t* __restrict__ tok_out)
+                                                                  int32_t* __restrict__ tok_out, int32_t* __restrict__ tok_host)
 {
     __shared__ float rv[16];
     __shared__ int ri[16];
@@ -3794,13 +3778,13 @@ __global__ __launch_bounds__(VR_THREADS) void argmax_tiles_kernel(const float2* 
         m = lane < 16 ? rv[lane] : -INFINITY;
         mi = lane < 16 ? ri[lane] : 0x7fffffff;
         argmax_wave(m, mi);
-        if (lane == 0) tok_out[blockIdx.x] = mi;
+        if (lane == 0) { tok_out[blockIdx.x] = mi; tok_host[blockIdx.x] = mi; }
     }
 }
-hipError_t argmax_tiles(const float2* vmax, int M, int n_tiles, int32_t* tok_out, hipStream_t s)
+hipError_t argmax_tiles(const float2* vmax, int M, int n_tiles, int32_t* tok_out, int32_t* tok_host, hipStream_t s)
 {
-    if (M < 1 || n_tiles < 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(argmax_tiles_kernel, dim3(M), dim3(VR_THREADS), 0, s, vmax, n_tiles, tok_out);
+    if (M < 1 || n_tiles < 1 || !tok_host) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(argmax_tiles_kernel, dim3(M), dim3(VR_THREADS), 0, s, vmax, n_tiles, tok_out, tok_host);
     return hipGetLastError();
 }
 
@@ -3898,7 +3882,7 @@ hipError_t vocab_confidence(const float* logits, int M, int V, float clamp, floa
 {
     if (M < 1 || V < 1 || !conf_out) return hipErrorInvalidValue;
     const int ns = (int)std::min<size_t>(std::min(V / 1024, 16), scratch ? scratch_bytes / ((size_t)M * sizeof(VRec)) : 0);
-    if (M > 256 || ns < 4) return vocab_reduce(logits, M, V, clamp, eps, nullptr, 1, argmax_out, maxprob_out, conf_out, s);
+    if (M > 256 || ns < 4) return vocab_reduce(logits, M, V, clamp, eps, nullptr, nullptr, argmax_out, maxprob_out, conf_out, s);
     VRec* rec = static_cast<VRec*>(scratch);
     hipLaunchKernelGGL(vocab_part_kernel, dim3(ns, M), dim3(VS_THREADS), 0, s, logits, V, ns, clamp, rec);
     hipLaunchKernelGGL(vocab_entropy_kernel, dim3(ns, M), dim3(VS_THREADS), 0, s, logits, V, ns, clamp, eps, rec);
@@ -3922,10 +3906,10 @@ hipError_t window_mean(const float* v, int n_pos, int n_taps, float* means, hipS
     return hipGetLastError();
 }
 
-hipError_t vocab_reduce(const float* logits, int M, int V, float clamp, float eps, int32_t* tok_out, int tok_stride,
+hipError_t vocab_reduce(const float* logits, int M, int V, float clamp, float eps, int32_t* tok_out, int32_t* tok_host,
                         int32_t* argmax_out, float* maxprob_out, float* conf_out, hipStream_t s)
 {
-    hipLaunchKernelGGL(vocab_reduce_kernel, dim3(M), dim3(VR_THREADS), 0, s, logits, V, clamp, eps, tok_out, tok_stride,
+    hipLaunchKernelGGL(vocab_reduce_kernel, dim3(M), dim3(VR_THREADS), 0, s, logits, V, clamp, eps, tok_out, tok_host,
                        argmax_out, maxprob_out, conf_out);
     return hipGetLastError();
 }
