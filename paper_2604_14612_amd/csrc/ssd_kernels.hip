@@ -2762,6 +2762,33 @@ __device__ __forceinline__ void split8(const float* x, u32x4_t& hi, u32x4_t& lo)
     pack_hi_lo<F16>(v, hi, lo);
 }
 
+// Four cache vectors (the same EPV dims of four consecutive positions) into a V^T tile: dim e of them as 8 bytes at
+// dst + e * pitch; fp32 elements as hi = rne(x) there and lo = rne(x - hi) `plane` bytes further on.
+template <typename KT>
+__device__ __forceinline__ void store_v4(const u32x4_t (&v)[4], unsigned char* dst, int pitch, int plane)
+{
+    unsigned w[4][4];
+#pragma unroll
+    for (int i = 0; i < 4; i++) { w[i][0] = v[i].x; w[i][1] = v[i].y; w[i][2] = v[i].z; w[i][3] = v[i].w; }
+#pragma unroll
+    for (int e = 0; e < 16 / (int)sizeof(KT); e++) {
+        unsigned h[4], l[4];
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            if constexpr (sizeof(KT) == 4) {
+                const float y = __uint_as_float(w[i][e]);
+                h[i] = f32_to_bf16_bits(y);
+                l[i] = f32_to_bf16_bits(y - bf16_bits_to_f32(h[i]));
+            } else {
+                h[i] = (w[i][e >> 1] >> ((e & 1) * 16)) & 0xffffu;
+            }
+        }
+        *reinterpret_cast<uint2*>(dst + e * pitch) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
+        if constexpr (sizeof(KT) == 4)
+            *reinterpret_cast<uint2*>(dst + plane + e * pitch) = make_uint2(l[0] | (l[1] << 16), l[2] | (l[3] << 16));
+    }
+}
+
 // fp32 caches take the same kernel: while a chunk is staged every K / V element is split into two bf16 planes
 // (hi = rne(x), lo = rne(x - hi), 16 mantissa bits together), and each contraction becomes three MFMAs
 // (hi.hi + lo.hi + hi.lo; the lo.lo term is below the 16 bits the planes carry).
@@ -2804,12 +2831,14 @@ __global__ __launch_bounds__(AT_THREADS) void attn_mfma_kernel(const float* __re
     constexpr int QPT = AT_QPASS * HD / AT_THREADS;   // query elements per thread
     float qreg[QPT];
     constexpr int NV = (AT_CHUNK * VPR + AT_THREADS - 1) / AT_THREADS;
-    u32x4_t kr[NV], vr[NV];
+    constexpr int VU = AT_CHUNK / 4 * VPR, NVU = (VU + AT_THREADS - 1) / AT_THREADS;   // V units of 4 positions x EPV dims; per thread
+    u32x4_t kr[NV], vr[NVU][4];
     // Query vectors, K and V are all requested before the position is known (one memory latency less on the way through the
     // kernel): cache rows past it may hold anything and are replaced by zeros when they are stored to LDS.
-    // K: consecutive lanes take consecutive vectors of a row.  V: consecutive lanes take consecutive POSITIONS
-    // (vector v -> position v % AT_CHUNK, dims EPV (v / AT_CHUNK) ..), so that the 2-byte stores of the transpose
-    // below fall on consecutive addresses of one V^T row instead of colliding in two banks.
+    // K: consecutive lanes take consecutive vectors of a row.  V: a thread takes the vectors of four consecutive positions, so
+    // that the transpose stores 8 bytes at a time; four lanes share a row's 64 bytes.  (2-byte stores with a lane per position:
+    // 11.4 us against 9.5, 7B, 5 rows behind 540 positions of an fp32 cache.)
+    auto v_unit = [](int u, int& pg, int& dg) { const int w = u >> 2; pg = w % (AT_CHUNK / 4); dg = w / (AT_CHUNK / 4) * 4 + (u & 3); };
     {
 #pragma unroll
         for (int t = 0; t < QPT; t++) {
@@ -2822,7 +2851,14 @@ __global__ __launch_bounds__(AT_THREADS) void attn_mfma_kernel(const float* __re
         for (int t = 0; t < NV; t++) {
             const int v = min(tid + t * AT_THREADS, AT_CHUNK * VPR - 1);
             kr[t] = *reinterpret_cast<const u32x4_t*>(kbase + (size_t)min(j0 + v / VPR, max_seq - 1) * HD + (v % VPR) * EPV);
-            vr[t] = *reinterpret_cast<const u32x4_t*>(vbase + (size_t)min(j0 + v % AT_CHUNK, max_seq - 1) * HD + (v / AT_CHUNK) * EPV);
+        }
+#pragma unroll
+        for (int t = 0; t < NVU; t++) {
+            int pg, dg;
+            v_unit(min(tid + t * AT_THREADS, VU - 1), pg, dg);
+#pragma unroll
+            for (int i = 0; i < 4; i++)
+                vr[t][i] = *reinterpret_cast<const u32x4_t*>(vbase + (size_t)min(j0 + pg * 4 + i, max_seq - 1) * HD + dg * EPV);
         }
     }
     const int p0 = pos_dev[0] + pos_off;
@@ -2842,38 +2878,38 @@ __global__ __launch_bounds__(AT_THREADS) void attn_mfma_kernel(const float* __re
     }
     if (n > 0) {  // stage K (row-major) and V (transposed)
         const int vmax = n * VPR - 1;
+        const u32x4_t zero = {0u, 0u, 0u, 0u};   // positions past the chunk: zero keys and values
 #pragma unroll
         for (int t = 0; t < NV; t++) {
             const int v = tid + t * AT_THREADS;
             if (v < AT_CHUNK * VPR) {
                 const int pos = v / VPR, d0 = (v % VPR) * EPV;
-                const int vpos = v % AT_CHUNK, vd0 = (v / AT_CHUNK) * EPV;
-                // positions past the chunk: zero keys and values
-                const u32x4_t kk = v <= vmax ? kr[t] : u32x4_t{0u, 0u, 0u, 0u};
-                const u32x4_t vv = vpos < n ? vr[t] : u32x4_t{0u, 0u, 0u, 0u};
+                const u32x4_t kk = v <= vmax ? kr[t] : zero;
                 if constexpr (F32) {
-                    const unsigned kw[4] = {kk.x, kk.y, kk.z, kk.w}, vw[4] = {vv.x, vv.y, vv.z, vv.w};
+                    const unsigned kw[4] = {kk.x, kk.y, kk.z, kk.w};
                     unsigned kh[4], kl[4];
 #pragma unroll
                     for (int e = 0; e < 4; e++) {
                         const float x = __uint_as_float(kw[e]);
                         kh[e] = f32_to_bf16_bits(x);
                         kl[e] = f32_to_bf16_bits(x - bf16_bits_to_f32(kh[e]));
-                        const float y = __uint_as_float(vw[e]);
-                        const uint16_t yh = f32_to_bf16_bits(y);
-                        *reinterpret_cast<uint16_t*>(vT + (vd0 + e) * AM_VPITCH + vpos * 2) = yh;
-                        *reinterpret_cast<uint16_t*>(vT + VPLANE + (vd0 + e) * AM_VPITCH + vpos * 2) =
-                            f32_to_bf16_bits(y - bf16_bits_to_f32(yh));
                     }
                     *reinterpret_cast<uint2*>(ktile + pos * ROWB + d0 * 2) = make_uint2(kh[0] | (kh[1] << 16), kh[2] | (kh[3] << 16));
                     *reinterpret_cast<uint2*>(ktile + KPLANE + pos * ROWB + d0 * 2) = make_uint2(kl[0] | (kl[1] << 16), kl[2] | (kl[3] << 16));
                 } else {
                     *reinterpret_cast<u32x4_t*>(ktile + pos * ROWB + d0 * 2) = kk;
-                    const unsigned w4[4] = {vv.x, vv.y, vv.z, vv.w};
-#pragma unroll
-                    for (int e = 0; e < 8; e++)
-                        *reinterpret_cast<uint16_t*>(vT + (vd0 + e) * AM_VPITCH + vpos * 2) = (uint16_t)(w4[e >> 1] >> ((e & 1) * 16));
                 }
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < NVU; t++) {
+            const int u = tid + t * AT_THREADS;
+            if (VU % AT_THREADS == 0 || u < VU) {
+                int pg, dg;
+                v_unit(u, pg, dg);
+                const u32x4_t w4[4] = {pg * 4 < n ? vr[t][0] : zero, pg * 4 + 1 < n ? vr[t][1] : zero, pg * 4 + 2 < n ? vr[t][2] : zero,
+                                       pg * 4 + 3 < n ? vr[t][3] : zero};
+                store_v4<KT>(w4, vT + dg * EPV * AM_VPITCH + pg * 8, AM_VPITCH, VPLANE);
             }
         }
     }
@@ -3095,32 +3131,9 @@ __global__ __launch_bounds__(AP_THREADS, 2) void attn_prompt_kernel(const float*
             if (VU % AP_THREADS && u >= VU) break;
             const int pg = u & 15, d0 = (u >> 4) * EPV;
             const int slot = (pg >> 3) * 32 + (pg & 3) * 8 + ((pg >> 2) & 1) * 4;   // of positions 4 pg .. 4 pg + 3
-            unsigned char* dst = vT + d0 * AP_VPITCH + slot * 2;
-            unsigned w[4][4];
-#pragma unroll
-            for (int i = 0; i < 4; i++) {
-                const u32x4_t x = pg * 4 + i < n ? vr[t][i] : zero;
-                w[i][0] = x.x; w[i][1] = x.y; w[i][2] = x.z; w[i][3] = x.w;
-            }
-#pragma unroll
-            for (int e = 0; e < EPV; e++) {
-                if constexpr (F32) {
-                    unsigned h[4], l[4];
-#pragma unroll
-                    for (int i = 0; i < 4; i++) {
-                        const float y = __uint_as_float(w[i][e]);
-                        h[i] = f32_to_bf16_bits(y);
-                        l[i] = f32_to_bf16_bits(y - bf16_bits_to_f32(h[i]));
-                    }
-                    *reinterpret_cast<uint2*>(dst + e * AP_VPITCH) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
-                    *reinterpret_cast<uint2*>(dst + VPLANE + e * AP_VPITCH) = make_uint2(l[0] | (l[1] << 16), l[2] | (l[3] << 16));
-                } else {
-                    unsigned h[4];
-#pragma unroll
-                    for (int i = 0; i < 4; i++) h[i] = (w[i][e >> 1] >> ((e & 1) * 16)) & 0xffffu;
-                    *reinterpret_cast<uint2*>(dst + e * AP_VPITCH) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
-                }
-            }
+            const u32x4_t w4[4] = {pg * 4 < n ? vr[t][0] : zero, pg * 4 + 1 < n ? vr[t][1] : zero, pg * 4 + 2 < n ? vr[t][2] : zero,
+                                   pg * 4 + 3 < n ? vr[t][3] : zero};
+            store_v4<KT>(w4, vT + d0 * AP_VPITCH + slot * 2, AP_VPITCH, VPLANE);
         }
     };
     load(0);
@@ -3791,7 +3804,7 @@ hipError_t argmax_tiles(const float2* vmax, int M, int n_tiles, int32_t* tok_out
 // Confidence rows, cut along the vocabulary: `ns` blocks per row leave (max, sum of exp relative to it, arg-max) of their
 // slice, a second launch merges a row's records (every block for itself, in slice order) and adds up its slice of the
 // entropy, a third adds the slices.  One block per row walks 32 000 logits three times in 27 us while most CUs idle (16
-// or 64 rows); the three short launches take about 11 us together.
+// or 64 rows); the three short launches take 22 us together for 64 rows of 32 000 and fewer for 16.
 constexpr int VS_THREADS = 256;
 struct VRec { double z, h; float m; int arg; };   // sums in 64 bits, as above
 
@@ -3858,20 +3871,23 @@ __global__ __launch_bounds__(VS_THREADS) void vocab_entropy_kernel(const float* 
     const double H = block_sum<VS_THREADS / 64>(hs, rd);
     if (tid == 0) row[sl].h = H;   // (the other blocks of the row read m, z and arg only)
 }
-__global__ __launch_bounds__(64) void vocab_sum_kernel(const VRec* __restrict__ rec, int nb, int V, int ns, int32_t* argmax_out,
+__global__ __launch_bounds__(64) void vocab_sum_kernel(const VRec* __restrict__ rec, int V, int ns, int32_t* argmax_out,
                                                        float* maxprob_out, float* conf_out)
 {
-    const int r = blockIdx.x * 64 + threadIdx.x;
-    if (r >= nb) return;
-    const VRec* row = rec + (size_t)r * ns;
-    float m;
-    double Z, H = 0.0;
-    int mi;
-    vs_merge(row, ns, m, Z, mi);
-    for (int i = 0; i < ns; i++) H += row[i].h;
-    if (argmax_out) argmax_out[r] = mi;
-    if (maxprob_out) maxprob_out[r] = (float)(1.0 / Z);
-    conf_out[r] = (float)(1.0 - H / log((double)V));
+    const int r = blockIdx.x, lane = threadIdx.x;   // one wave per row, a lane per slice
+    const VRec v = rec[(size_t)r * ns + min(lane, ns - 1)];
+    const bool own = lane < ns;
+    float m = own ? v.m : -INFINITY;
+    int mi = own ? v.arg : 0x7fffffff;
+    argmax_wave(m, mi);
+    double Z = own ? v.z * expf(v.m - m) : 0.0, H = own ? v.h : 0.0;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) { Z += __shfl_xor(Z, o, 64); H += __shfl_xor(H, o, 64); }
+    if (lane == 0) {
+        if (argmax_out) argmax_out[r] = mi;
+        if (maxprob_out) maxprob_out[r] = (float)(1.0 / Z);
+        conf_out[r] = (float)(1.0 - H / log((double)V));
+    }
 }
 
 // Slices per row: 16, or what leaves at least 1024 logits to each and the scratch holds -- whatever the row count, so that
@@ -3886,7 +3902,7 @@ hipError_t vocab_confidence(const float* logits, int M, int V, float clamp, floa
     VRec* rec = static_cast<VRec*>(scratch);
     hipLaunchKernelGGL(vocab_part_kernel, dim3(ns, M), dim3(VS_THREADS), 0, s, logits, V, ns, clamp, rec);
     hipLaunchKernelGGL(vocab_entropy_kernel, dim3(ns, M), dim3(VS_THREADS), 0, s, logits, V, ns, clamp, eps, rec);
-    hipLaunchKernelGGL(vocab_sum_kernel, dim3(ceil_div(M, 64)), dim3(64), 0, s, rec, M, V, ns, argmax_out, maxprob_out, conf_out);
+    hipLaunchKernelGGL(vocab_sum_kernel, dim3(M), dim3(64), 0, s, rec, V, ns, argmax_out, maxprob_out, conf_out);
     return hipGetLastError();
 }
 
