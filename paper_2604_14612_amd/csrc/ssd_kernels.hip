@@ -1071,8 +1071,8 @@ __global__ __launch_bounds__(MF_THREADS) void gemm_rows_mfma_kernel(RowsP p)
 // has the loads of four steps in flight (what bounds these launches is latency, not bytes).  RMSNorm costs no launch: the
 // gain goes into the weights as they are loaded, the sums of squares are taken from the activations that pass by anyway,
 // and the row's scale is applied to the finished sums.  Rotary embedding and the cache rows are written by the epilogue.
-// Measured on the fp32 model of width 256 with five rows: residual projections 13.9 -> 5 us per launch, gate/up 8.3 -> 5,
-// five launches per layer instead of eight.
+// Measured on the fp32 model of width 256 with five rows, us per launch: output projection 13.9 -> 4.8, down 13.9 -> 7.7,
+// gate/up 8.3 -> 5.4, QKV 7.4 -> 6.1 with norm and rotary embedding; five launches per layer instead of eight.
 constexpr int RM_QKV = 3;
 struct RowsPlainP {
     const void* w[3];
@@ -1117,10 +1117,12 @@ __device__ __forceinline__ float wave_sum_rows(float v)
     return v + __shfl_xor(v, 32, 64);
 }
 
-template <typename WT, int MODE, int MG>
+// U = load steps of a wave that are in flight together (1 where a row is no longer than that: a quarter of the code, which a
+// short launch fetches cold)
+template <typename WT, int MODE, int MG, int U>
 __global__ __launch_bounds__(256) void rows_plain_kernel(RowsPlainP p)
 {
-    constexpr int VEC = Elem<WT>::VEC, STEP = 64 * VEC, U = 4;
+    constexpr int VEC = Elem<WT>::VEC, STEP = 64 * VEC;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int K = p.K, m0 = blockIdx.y * MG, mg = min(MG, p.M - m0);
     const int n_units = MODE == RM_SWIGLU ? p.n[0] : (p.n[0] + p.n[1] + p.n[2]) / 2;
@@ -1174,6 +1176,7 @@ __global__ __launch_bounds__(256) void rows_plain_kernel(RowsPlainP p)
         float a = 0.f, b = 0.f, sq = 0.f;
 #pragma unroll
         for (int m = 0; m < MG; m++) {
+            if (m >= mg) break;   // uniform
             const float ta = wave_sum_rows(a0[m]), tb = wave_sum_rows(a1[m]), ts = p.gain ? wave_sum_rows(ss[m]) : 0.f;
             if (lane == m) { a = ta; b = tb; sq = ts; }
         }
@@ -1224,8 +1227,11 @@ static hipError_t rows_plain_t(const RowsPlainP& p, hipStream_t s)
     const int blocks = std::min(ceil_div(units, 4), 4096);
     // token rows of a wave: four where that covers the launch, else eight (a second group of waves reads the weights again,
     // from the caches)
-    if (p.M <= 4) hipLaunchKernelGGL((rows_plain_kernel<WT, MODE, 4>), dim3(blocks, 1), dim3(256), 0, s, p);
-    else hipLaunchKernelGGL((rows_plain_kernel<WT, MODE, 8>), dim3(blocks, ceil_div(p.M, 8)), dim3(256), 0, s, p);
+    const bool one = p.K <= 64 * Elem<WT>::VEC;
+    if (p.M <= 4 && one) hipLaunchKernelGGL((rows_plain_kernel<WT, MODE, 4, 1>), dim3(blocks, 1), dim3(256), 0, s, p);
+    else if (p.M <= 4) hipLaunchKernelGGL((rows_plain_kernel<WT, MODE, 4, 4>), dim3(blocks, 1), dim3(256), 0, s, p);
+    else if (one) hipLaunchKernelGGL((rows_plain_kernel<WT, MODE, 8, 1>), dim3(blocks, ceil_div(p.M, 8)), dim3(256), 0, s, p);
+    else hipLaunchKernelGGL((rows_plain_kernel<WT, MODE, 8, 4>), dim3(blocks, ceil_div(p.M, 8)), dim3(256), 0, s, p);
     return hipGetLastError();
 }
 
@@ -3804,7 +3810,7 @@ hipError_t argmax_tiles(const float2* vmax, int M, int n_tiles, int32_t* tok_out
 // Confidence rows, cut along the vocabulary: `ns` blocks per row leave (max, sum of exp relative to it, arg-max) of their
 // slice, a second launch merges a row's records (every block for itself, in slice order) and adds up its slice of the
 // entropy, a third adds the slices.  One block per row walks 32 000 logits three times in 27 us while most CUs idle (16
-// or 64 rows); the three short launches take 22 us together for 64 rows of 32 000 and fewer for 16.
+// or 64 rows); the three short launches take 22 us together for 64 rows of 32 000 logits, 19 us for 16.
 constexpr int VS_THREADS = 256;
 struct VRec { double z, h; float m; int arg; };   // sums in 64 bits, as above
 
