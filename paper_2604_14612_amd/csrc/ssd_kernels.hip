@@ -727,32 +727,35 @@ static hipError_t ensure_lds(const void* fn, size_t lds, std::atomic<size_t>& li
     return hipSuccess;
 }
 
+constexpr int gemv_lds_floats(int K, int vec) { return (K + 64 * vec - 1) / (64 * vec) * (64 * vec); }   // whole chunks of one load step
+
+// Rounds of row groups that every block of a launch walks.  Up to four blocks fit a CU (registers: eight waves per SIMD;
+// LDS: the staged vector): persistent blocks that are all resident at once leave no second, partial round of blocks.
+// Measured: three per CU are best for the layer's GEMVs, four for the LM head.  The variant that folds attention partials
+// in its prologue re-reads them per block, so it runs one block per CU.
+template <typename WT, int EPI, int R, int KS>
+static int gemv_rounds(const GemvP& p, const LaunchOpts* opt)
+{
+    const size_t lds = (size_t)gemv_lds_floats(p.K, Elem<WT>::VEC) * sizeof(float);
+    const int per_cu = (int)std::min<size_t>(EPI == EPI_STORE ? 4 : 3, std::max<size_t>(1, ((size_t)160 << 10) / (lds + 1024)));
+    int cap = p.part ? 256 : 256 * per_cu;
+    if (opt && opt->gemv_block_cap > 0) cap = opt->gemv_block_cap;
+    return std::max(1, ceil_div(ceil_div(p.n_rows / R, GV_WAVES / KS), cap));
+}
+
 // blocks_out (may be null) receives the grid size of the launch
 template <typename WT, int EPI, int R, int D, int KS>
 static hipError_t launch_gemv_cfg(const GemvP& p, hipStream_t s, LaunchOpts* opt, int* blocks_out)
 {
-    constexpr int CHF = 64 * Elem<WT>::VEC;   // the staged vector is laid out in whole chunks of one load step
-    size_t lds = (size_t)ceil_div(p.K, CHF) * CHF * sizeof(float);
+    const size_t lds = (size_t)gemv_lds_floats(p.K, Elem<WT>::VEC) * sizeof(float);
     static std::atomic<size_t> lds_limit{0};  // per instantiation
     {
         hipError_t e = ensure_lds((const void*)gemv_kernel<WT, EPI, R, D, KS>, lds, lds_limit);
         if (e != hipSuccess) return e;
     }
-    constexpr int GPB = GV_WAVES / KS;
-    int blocks = ceil_div(p.n_rows / R, GPB);
-    // up to four blocks fit a CU (registers: eight waves per SIMD; LDS: the staged vector): persistent blocks that are
-    // all resident at once leave no second, partial round of blocks.  Measured: three per CU are best for the
-    // layer's GEMVs, four for the LM head.  The variant that folds attention partials in its prologue re-reads them
-    // per block, so it runs one block per CU.
-    const int per_cu = (int)std::min<size_t>(EPI == EPI_STORE ? 4 : 3, std::max<size_t>(1, ((size_t)160 << 10) / (lds + 1024)));
-    int cap = p.part ? 256 : 256 * per_cu;
-    if (opt && opt->gemv_block_cap > 0) cap = opt->gemv_block_cap;
-    if (blocks > cap) {
-        // equal work per block: with r rounds needed, use just enough blocks for r full rounds (gate/up at 7B:
-        // 1376 block-rounds -> 688 blocks x 2 rather than 768 blocks of which 160 would do one round only)
-        const int rounds = ceil_div(blocks, cap);
-        blocks = ceil_div(blocks, rounds);
-    }
+    // equal work per block: with r rounds needed, use just enough blocks for r full rounds (gate/up at 7B:
+    // 1376 block-rounds -> 688 blocks x 2 rather than 768 blocks of which 160 would do one round only)
+    const int blocks = ceil_div(ceil_div(p.n_rows / R, GV_WAVES / KS), gemv_rounds<WT, EPI, R, KS>(p, opt));
     if (blocks_out) *blocks_out = blocks;
     if (opt && opt->time_start) {
         // timing request for this one launch: the events take the kernel's own begin and end timestamps
@@ -805,10 +808,14 @@ static hipError_t launch_gemv_t(const GemvP& p, hipStream_t s, LaunchOpts* opt, 
             // Few chunks: two waves per pair.  Folding the attention partials: a wave per pair with four steps in flight, since
             // every block re-reads the partials and there is one block per CU only (7B 9.4 against 10.9 with four waves per
             // pair; at 8192 rows, where a block has two rounds, 27.2 against 28.5 the other way round).  Everything else: four
-            // waves per pair, two steps each in flight (down projection: Llama-3-8B 22.9 -> 21.4, 13B 26.7 -> 25.7, 70B 75.4 ->
-            // 72.8, 1024-wide 5.4 -> 5.0, 7B equal; against four steps in flight or two waves per pair).
+            // waves per pair; four steps in flight where a wave's share of a pair is longer than that and its items need no
+            // padding (7B down projection, 12 items: 18.1 against 18.8 with two, behind the gate/up launch; 70B, 112: 71.8
+            // against 72.8), else two (Llama-3-8B, 14 items: 22.9 -> 21.4, 13B, 21: 26.7 -> 25.7, 1024-wide, 2: 5.4 -> 5.0; 70B
+            // output projection, four steps per pair: 25.3 against 29.4).
             if (ch <= 4) return launch_gemv_cfg<WT, EPI, 2, 2, 2>(p, s, opt, blocks_out);
             if (p.part && p.n_rows < 8192) return launch_gemv_cfg<WT, EPI, 2, 4, 1>(p, s, opt, blocks_out);
+            const int steps = ceil_div(ch, 4);
+            if (steps > 4 && steps * gemv_rounds<WT, EPI, 2, 4>(p, opt) % 4 == 0) return launch_gemv_cfg<WT, EPI, 2, 4, 4>(p, s, opt, blocks_out);
             return launch_gemv_cfg<WT, EPI, 2, 2, 4>(p, s, opt, blocks_out);
         } else if constexpr (EPI == EPI_QKV) {
             // a wave per pair where there are pairs for every wave slot or hardly any chunks (7B 19.9 -> 19.4, 13B 29.3 -> 28.6,
@@ -3577,8 +3584,8 @@ static AttnPlan attn_plan(const Dims& D, int ctx, int M)
         if (force_splits > 0) ns = force_splits;
         if (ns > ctx) ns = ctx;
         // The length of a range is part of the launch, not computed from the position on the device: whole ranges while their
-        // number grows with the context, beyond that steps of 32 (a captured launch sequence then lasts for 32 ns positions).
-        pl.chunk = std::max(range, ceil_div(ceil_div(ctx, ns), 32) * 32);
+        // number grows with the context, beyond that steps of 16 (a captured launch sequence then lasts for 16 ns positions).
+        pl.chunk = std::max(range, ceil_div(ceil_div(ctx, ns), 16) * 16);
         if (force_splits > 0) pl.chunk = ceil_div(ctx, ns);
         pl.n_splits = ceil_div(ctx, pl.chunk);
     } else {
