@@ -3582,7 +3582,7 @@ static AttnPlan attn_plan(const Dims& D, int ctx, int M)
         if (M == 1 && ns > GV_FOLD_MAX && ctx <= GV_FOLD_MAX * 512) ns = GV_FOLD_MAX;
         if (ns > AW_MAX_RANGES) ns = AW_MAX_RANGES;
         // Several query vectors per block: the registers leave one block per CU, so no more ranges than one round of blocks
-        // takes (two rows, 32 heads, 550 positions: 8.0 us with 7 ranges, 12.7 with 9).
+        // takes (two rows, 32 heads, about 550 positions: 7.9 us with 7 ranges, 12.7 with 9).
         if (M > 1 && Q <= AW_MAXQ_TOTAL) ns = std::min(ns, std::max(4, 256 / D.Hkv));
         if (force_splits > 0) ns = force_splits;
         if (ns > ctx) ns = ctx;
