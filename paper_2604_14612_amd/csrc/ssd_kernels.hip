@@ -11,6 +11,7 @@
 // of the producing and the consuming projection.  Models whose shapes do not fit the MFMA tiling
 // (and fp32 models) take a plain FMA path with separate norm / rotary kernels.
 #include "ssd_kernels.h"
+#include "ssd_rules.h"
 
 #include <hip/hip_ext.h>
 
@@ -1549,16 +1550,20 @@ __global__ __launch_bounds__(512, (M3_D * (MODE == RM_SWIGLU ? 4 + NU : 2 + NU) 
     // RMS scale of every activation row from the producer's per-tile sums of squares (read by the epilogue).
     // Measured per mode: gate/up (long-lived blocks, two stripes in flight) loses least when the partials are
     // summed after the weight stream, the short-lived blocks of QKV and the LM head when it happens up front.
+    // Every entry, the 1 of a row without a scale included, has a single writer (rows_of_wave): no initial pass by other
+    // threads, which would need a barrier of its own before the scales go in.
     auto row_scales = [&]() {
-        for (int c = wave; c < M; c += 8) {
-            float sq = 0.f;
-            for (int i = lane; i < p.n_ssq; i += 64) sq += p.ssq[(size_t)c * p.n_ssq + i];
-            sq = wave_sum(sq);
-            if (lane == 0) rs[c] = 1.0f / sqrtf(sq / (float)K + p.eps);
-        }
+        rows_of_wave(wave, [&](int c) {
+            float s = 1.0f;
+            if (MODE != RM_RESID && p.ssq && c < M) {
+                float sq = 0.f;
+                for (int i = lane; i < p.n_ssq; i += 64) sq += p.ssq[(size_t)c * p.n_ssq + i];
+                s = 1.0f / sqrtf(wave_sum(sq) / (float)K + p.eps);
+            }
+            if (lane == 0) rs[c] = s;
+        });
     };
-    if (tid < 16) rs[tid] = 1.0f;
-    if (MODE != RM_RESID && MODE != RM_SWIGLU && p.ssq) row_scales();
+    if (MODE != RM_SWIGLU) row_scales();
     // steady state: every step stores its slot's stripe, refills the slot and multiplies; the stripe count is padded
     // to a multiple of M3_D (a padding request re-reads the last stripe and is never stored); the last M3_D steps
     // request nothing
@@ -1579,7 +1584,7 @@ __global__ __launch_bounds__(512, (M3_D * (MODE == RM_SWIGLU ? 4 + NU : 2 + NU) 
             multiply(sidx(ck0 + sl));
         }
     }
-    if (MODE == RM_SWIGLU && p.ssq) row_scales();
+    if (MODE == RM_SWIGLU) row_scales();
     __syncthreads();
     float* red = reinterpret_cast<float*>(sm3);  // [8][NT][256] floats fit inside the weight stripe area
 #pragma unroll
