@@ -179,10 +179,9 @@ __global__ void embed_kernel(const WT* __restrict__ E, Tokens tok, int d, int V,
 {
     int r = blockIdx.y;
     if (rr.out && blockIdx.x == 0 && r == 0 && (int)threadIdx.x < rr.hd) rr.copy(threadIdx.x);
-    int t = token_of(tok, r);
-    t = min(max(t, 0), V - 1);
+    const size_t row = embed_row(token_of(tok, r), V) * d;
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < d; i += gridDim.x * blockDim.x)
-        x[(size_t)r * d + i] = Elem<WT>::get(E, (size_t)t * d + i);
+        x[(size_t)r * d + i] = Elem<WT>::get(E, row + i);
 }
 
 hipError_t embed_rows(const Dims& D, const void* embed, Tokens tok, int M, float* x, hipStream_t s, const float* rope,
@@ -677,7 +676,7 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_kernel(GemvP p)
 // of a decode step, or the embedding row that the next draft step starts from.
 constexpr int SF_THREADS = 1024;
 template <typename WT>
-__global__ __launch_bounds__(SF_THREADS) void step_finish_kernel(const float* __restrict__ vstat, int n_blocks, StepOut o, int d, RopeRow rr)
+__global__ __launch_bounds__(SF_THREADS) void step_finish_kernel(const float* __restrict__ vstat, int n_blocks, StepOut o, int d, int V, RopeRow rr)
 {
     __shared__ VStat sm[SF_THREADS / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -710,7 +709,7 @@ __global__ __launch_bounds__(SF_THREADS) void step_finish_kernel(const float* __
     }
     if (!o.x_next) return;   // uniform
     __syncthreads();
-    const WT* row = static_cast<const WT*>(o.embed) + (size_t)sm[0].arg * d;
+    const WT* row = static_cast<const WT*>(o.embed) + embed_row(sm[0].arg, V) * d;   // (logits that are all NaN leave no arg-max)
     float* x = o.x_next;
     for (int i = tid * 4; i < d; i += SF_THREADS * 4)
         *reinterpret_cast<float4*>(x + i) = make_float4(Elem<WT>::get(row, i), Elem<WT>::get(row, i + 1), Elem<WT>::get(row, i + 2), Elem<WT>::get(row, i + 3));
@@ -916,9 +915,9 @@ hipError_t gemv_lmhead_argmax(const Dims& D, const void* wlm, const float* gain,
     if (e != hipSuccess) return e;
     if (blocks < 1 || blocks > GEMV_MAX_BLOCKS) return hipErrorInvalidValue;
     const RopeRow rr = {o.rope, o.rope_pos, o.rope_off, D.hd, o.rope_row};
-    if (D.wt == WT_BF16) hipLaunchKernelGGL(step_finish_kernel<uint16_t>, dim3(1), dim3(SF_THREADS), 0, s, vstat, blocks, o, D.d, rr);
-    else if (D.wt == WT_F16) hipLaunchKernelGGL(step_finish_kernel<f16_t>, dim3(1), dim3(SF_THREADS), 0, s, vstat, blocks, o, D.d, rr);
-    else hipLaunchKernelGGL(step_finish_kernel<float>, dim3(1), dim3(SF_THREADS), 0, s, vstat, blocks, o, D.d, rr);
+    if (D.wt == WT_BF16) hipLaunchKernelGGL(step_finish_kernel<uint16_t>, dim3(1), dim3(SF_THREADS), 0, s, vstat, blocks, o, D.d, D.V, rr);
+    else if (D.wt == WT_F16) hipLaunchKernelGGL(step_finish_kernel<f16_t>, dim3(1), dim3(SF_THREADS), 0, s, vstat, blocks, o, D.d, D.V, rr);
+    else hipLaunchKernelGGL(step_finish_kernel<float>, dim3(1), dim3(SF_THREADS), 0, s, vstat, blocks, o, D.d, D.V, rr);
     return hipGetLastError();
 }
 
@@ -2490,8 +2489,7 @@ __global__ __launch_bounds__(256) void embed_split_kernel(const WT* __restrict__
     constexpr bool F16 = IsF16<WT>::value;
     const int r = blockIdx.y, i = (blockIdx.x * 256 + threadIdx.x) * 4;
     if (i >= d) return;   // whole DPP rows: d is a multiple of 64
-    const int t = min(max(token_of(tok, r), 0), V - 1);
-    const uint2 w = *reinterpret_cast<const uint2*>(E + (size_t)t * d + i);
+    const uint2 w = *reinterpret_cast<const uint2*>(E + embed_row(token_of(tok, r), V) * d + i);
     const float4 g = *reinterpret_cast<const float4*>(gain + i);
     const float4 v = make_float4(h16_bits_to_f32(w.x & 0xffff, F16), h16_bits_to_f32(w.x >> 16, F16),
                                  h16_bits_to_f32(w.y & 0xffff, F16), h16_bits_to_f32(w.y >> 16, F16));

@@ -74,3 +74,21 @@ def test_attention_ranges_at_their_edges(heads, kv_heads, kv, plen):
     o.verify(d)
     ctx.ssd_verify(d)
     assert_logits_close(ctx.ssd_copy_logits(0, 5), o.last_logits, shape.dtype, "verify")
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp16", "fp32"])
+def test_logits_without_a_maximum_give_a_token_that_verification_refuses(dtype):
+    """One NaN weight makes every logit NaN; an infinite clamp turns them into -inf, which no arg-max picks.  The draft steps
+    chain on that token: the next one must read a row of the embedding table, and the id itself is no valid draft."""
+    import paper_2604_14612_amd as ssd
+    shape = ModelShape(2, 256, 4, 4, 704, 1024, dtype=dtype)
+    w = make_weights(shape, 5)
+    w["wd"][0][7, 11] = float("nan")
+    ctx = ssd.Context(shape, to_gpu(w), 96, 8, conf_clamp=float("inf"))
+    none = 0x7fffffff
+    assert ctx.ssd_prefill(make_prompt(1024, 20, 4).tolist()) == none
+    d = ctx.ssd_draft_step(np.zeros(2, np.uint8), 6)
+    assert d == [none] * 6
+    assert np.isnan(ctx.ssd_copy_logits(0, 6)).all()
+    with pytest.raises(ssd.SsdError):
+        ctx.ssd_verify(d)

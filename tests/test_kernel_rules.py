@@ -14,6 +14,7 @@ WRAPPERS = r"""
 #include "ssd_rules.h"
 using namespace ssdk;
 extern "C" {
+size_t embedding_row(int tok, int V) { return embed_row(tok, V); }
 int row_writers(int row) { int n = 0; for (int w = 0; w < 8; w++) rows_of_wave(w, [&](int c) { n += c == row; }); return n; }
 }
 """
@@ -29,7 +30,9 @@ def rules(tmp_path_factory):
         f.write(WRAPPERS)
     r = subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I" + CSRC, "-o", lib, src], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
-    return C.CDLL(lib)
+    l = C.CDLL(lib)
+    l.embedding_row.restype = C.c_size_t
+    return l
 
 
 def kernel_source(name):
@@ -44,3 +47,14 @@ def test_every_row_scale_of_the_16_row_kernel_has_one_writer(rules):
     """Two writers without a barrier between them leave the scale to chance: the 1 of one may land on the factor of the other."""
     assert [rules.row_writers(c) for c in range(-1, 17)] == [0] + [1] * 16 + [0]
     assert len(re.findall(r"\brs\[[^]]*\]\s*=[^=]", kernel_source("rows_mfma3_kernel"))) == 1
+
+
+@pytest.mark.parametrize("vocab", [16, 1024, 128256])
+def test_embedding_gathers_stay_inside_the_table(rules, vocab):
+    """An id is a row, any other value reads the first or the last one: 0x7fffffff is what a row of NaN logits leaves as arg-max."""
+    for tok in (0, 1, vocab - 1):
+        assert rules.embedding_row(tok, vocab) == tok
+    assert rules.embedding_row(0x7fffffff, vocab) == rules.embedding_row(vocab, vocab) == vocab - 1
+    assert rules.embedding_row(-1, vocab) == rules.embedding_row(-0x80000000, vocab) == 0
+    for kernel in ("embed_kernel", "embed_split_kernel", "step_finish_kernel"):
+        assert "embed_row(" in kernel_source(kernel), kernel
