@@ -3856,7 +3856,8 @@ __global__ __launch_bounds__(VS_THREADS) void vocab_part_kernel(const float* __r
     for (int w = 1; w < VS_THREADS / 64; w++)
         if (rv[w] > m || (rv[w] == m && ri[w] < mi)) { m = rv[w]; mi = ri[w]; }
     double zs = 0.0;
-    for (int i = b + tid; i < e; i += VS_THREADS) zs += expf(fminf(fmaxf(z[i], -clamp), clamp) - m);
+    if (m > -INFINITY)   // (infinite clamp: a slice of -inf only has no terms; exp(-inf - -inf) would be NaN.  Uniform.)
+        for (int i = b + tid; i < e; i += VS_THREADS) zs += expf(fminf(fmaxf(z[i], -clamp), clamp) - m);
     const double Z = block_sum<VS_THREADS / 64>(zs, rd);
     if (tid == 0) rec[(size_t)r * ns + sl] = VRec{Z, 0.0, m, mi};
 }

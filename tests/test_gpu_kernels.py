@@ -92,3 +92,29 @@ def test_logits_without_a_maximum_give_a_token_that_verification_refuses(dtype):
     assert np.isnan(ctx.ssd_copy_logits(0, 6)).all()
     with pytest.raises(ssd.SsdError):
         ctx.ssd_verify(d)
+
+
+# 8208 logits are eight slices of 1026 in the confidence reduction: the first, an inner and the last one without any finite logit
+@pytest.mark.parametrize("dead", [(0, 1040), (2000, 3100), (7100, 8208)])
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+def test_a_vocabulary_slice_of_minus_infinity_adds_nothing(dtype, dead):
+    """NaN rows of the LM head under an infinite clamp: logits of -inf, probability 0.  Held against Eq. 1-4 over the finite
+    logits of the same row (the last tap is what the prompt's logits are taken from), in 64 bits."""
+    import paper_2604_14612_amd as ssd
+    vocab = 8208
+    shape = ModelShape(2, 256, 4, 4, 704, vocab, dtype=dtype)
+    w = make_weights(shape, 5, init_std=0.08)
+    w["lm_head"][dead[0]:dead[1]] = float("nan")
+    ctx = ssd.Context(shape, to_gpu(w), 96, 4, conf_clamp=float("inf"))
+    first = ctx.ssd_prefill(make_prompt(vocab, 20, 4).tolist())
+    z = ctx.ssd_copy_logits(0, 1)[0].astype(np.float64)
+    live = np.isfinite(z)
+    assert (~live).sum() == dead[1] - dead[0] and first == int(np.nanargmax(z))
+    p = np.exp(z[live] - z[live].max())
+    p /= p.sum()
+    for static in (False, True):
+        conf, g = ctx.ssd_layer_confidence(0, 1, detail=True, static=static)
+        assert np.isfinite(conf).all() and np.isfinite(g["maxprob"]).all()
+        np.testing.assert_allclose(g["conf"][0, -1, 1], 1.0 + (p * np.log(p + 1e-10)).sum() / np.log(vocab), atol=CONF_TOL[dtype])
+        np.testing.assert_allclose(g["maxprob"][0, -1, 1], p.max(), rtol=PROB_RTOL[dtype])
+        assert g["argmax"][0, -1, 1] == first
