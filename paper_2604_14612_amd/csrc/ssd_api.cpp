@@ -6,6 +6,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -63,6 +64,12 @@ Dims make_dims(const ssd_config& c)
     return D;
 }
 
+// Tap rows of one LM-head pass of the context-window confidence: what the staging buffers hold.
+int window_batch_rows(const Dims& D, int rows, int conf_rows)
+{
+    return std::min(rows_big_supported(D) ? SSD_PREFILL_ROWS : 64, std::max(rows, conf_rows));
+}
+
 Layout make_layout(const ssd_config& c)
 {
     Dims D = make_dims(c);
@@ -91,7 +98,10 @@ Layout make_layout(const ssd_config& c)
     l.part = o;   o += align_up(l.part_floats * sizeof(float));
     l.logits = o; o += align_up((size_t)l.logit_rows * D.V * sizeof(float));
     l.taps = o;   o += align_up((size_t)l.tap_rows * D.L * 2 * D.d * sizeof(float));
-    l.tapn = o;   o += align_up((size_t)l.conf_rows * D.d * sizeof(float));
+    // normalised fp32 rows and the reduction's records of one confidence pass, where the tiled kernels are not used: the 2L
+    // rows of a position, or a batch of the context window
+    l.tapn = o;   o += align_up((size_t)(rows_fused_supported(D) ? l.conf_rows : std::max(l.conf_rows, window_batch_rows(D, l.rows, l.conf_rows))) *
+                                D.d * sizeof(float));
     {   // bf16 hi/lo staging of activation rows for the MFMA path: rows x max(d, dq, f), or the confidence rows x d
         size_t kbig = (size_t)(D.f > (int)kmax ? D.f : (int)kmax);
         size_t a = (size_t)l.rows * kbig, b = (size_t)l.conf_rows * D.d;
@@ -1060,10 +1070,7 @@ int ssd_window_confidence(ssd_ctx* c, float* conf_out, float* tap_conf_out, int3
     ConfScratch sc;
     sc.hi = c->h16(Y.hi); sc.lo = c->h16(Y.lo); sc.tapn = c->f(Y.tapn); sc.logits = c->f(Y.logits); sc.res = nullptr;
     sc.one_gemm = true;
-    // rows per pass of the LM head: what the staging buffers were sized for (at least the 2L rows of one position)
-    int B = rows_big_supported(D) ? SSD_PREFILL_ROWS : 64;
-    if (B > Y.logit_rows) B = Y.logit_rows;
-    if (B > Y.conf_rows && B > Y.rows) B = Y.conf_rows > Y.rows ? Y.conf_rows : Y.rows;
+    const int B = window_batch_rows(D, Y.rows, Y.conf_rows);
     sc.batch = B;
     float* conf_all = c->f(Y.ring_conf);                  // [nv * R]
     for (long r0 = 0; r0 < rows; r0 += B) {
