@@ -3,6 +3,7 @@
 // hot path lives in the kernels (ssd_kernels.hip); this file only orders them.
 #include "../../include/ssd.h"
 #include "ssd_kernels.h"
+#include "ssd_rules.h"
 
 #include <hip/hip_runtime.h>
 
@@ -231,8 +232,9 @@ static inline bool is_gemv_kid(int kid)
         }                                                                                  \
     } while (0)
 
-// One decoder layer for a single row (draft / vanilla decode path); either sub-block may be left out.
-int layer_single(ssd_ctx* c, int l, int pos_off, bool do_attn, bool do_mlp)
+// One decoder layer for a single row (draft / vanilla decode path); either sub-block may be left out.  plan_ctx: the context
+// attention's launch is planned for, at least the positions the row sees.
+int layer_single(ssd_ctx* c, int l, int pos_off, int plan_ctx, bool do_attn, bool do_mlp)
 {
     const Dims& D = c->D;
     float* x = c->f(c->lay.x);
@@ -241,7 +243,7 @@ int layer_single(ssd_ctx* c, int l, int pos_off, bool do_attn, bool do_mlp)
                                    pos_off, c->f(c->lay.qkv), c->kcache(l), c->vcache(l), c->stream), "gemv_qkv");
     int fold = 0;  // > 0: attention left that many partials per head for the output projection to fold
     TIMED(SSD_K_ATTENTION, attention(D, c->f(c->lay.qkv), D.dq, c->kcache(l), c->vcache(l), c->pos_dev(), pos_off,
-                                     c->n - 1, 1, c->f(c->lay.part), c->f(c->lay.att), nullptr, nullptr, c->stream, &fold),
+                                     plan_ctx - 1 - pos_off, 1, c->f(c->lay.part), c->f(c->lay.att), nullptr, nullptr, c->stream, &fold),
           "attention");
     if (fold > 0) {
         TIMED(SSD_K_GEMV_O, gemv_resid_attn(D, c->wo[l], c->f(c->lay.part), fold, x, nullptr, c->stream), "gemv_o");
@@ -262,7 +264,7 @@ int layer_single(ssd_ctx* c, int l, int pos_off, bool do_attn, bool do_mlp)
 // flags: STEP_CHAINED = the previous step of the same sequence left this token's embedding in x; STEP_CHAIN_NEXT = leave
 // the new token's embedding there; STEP_COMMIT = the new token becomes the pending one and *pos advances.
 enum { STEP_CHAINED = 1, STEP_CHAIN_NEXT = 2, STEP_COMMIT = 4 };
-int forward_single(ssd_ctx* c, const uint8_t* sub, int slot, int slot_out, int pos_off, int lrow, int flags)
+int forward_single(ssd_ctx* c, const uint8_t* sub, int slot, int slot_out, int pos_off, int plan_ctx, int lrow, int flags)
 {
     const Dims& D = c->D;
     if (!(flags & STEP_CHAINED))
@@ -271,7 +273,7 @@ int forward_single(ssd_ctx* c, const uint8_t* sub, int slot, int slot_out, int p
     for (int l = 0; l < D.L; l++) {
         const bool do_attn = !(sub && sub[2 * l]), do_mlp = !(sub && sub[2 * l + 1]);
         if (!do_attn && !do_mlp) continue;
-        int rc = layer_single(c, l, pos_off, do_attn, do_mlp);
+        int rc = layer_single(c, l, pos_off, plan_ctx, do_attn, do_mlp);
         if (rc) return rc;
     }
     float* logits = c->f(c->lay.logits) + (size_t)lrow * D.V;
@@ -832,7 +834,7 @@ int ssd_decode(ssd_ctx* c, int32_t* token_out)
     // pending token sits in tok slot 0; its successor is written to slot 1, then promoted
     std::string key = "D|" + std::to_string(attention_splits(c->D, c->n, 1));
     int rc = run_sequence(c, key, [&]() {
-        return forward_single(c, nullptr, 0, 1, 0, 0, STEP_COMMIT);
+        return forward_single(c, nullptr, 0, 1, 0, c->n, 0, STEP_COMMIT);
     });
     if (rc) return rc;
     rc = sync_results(c);
@@ -845,6 +847,16 @@ int ssd_decode(ssd_ctx* c, int32_t* token_out)
     return SSD_OK;
 }
 
+// Keys of the replayed sequences of a draft, sub having two entries per layer: all k steps, and step i of an adaptive one.
+static std::string draft_key(const Dims& D, const std::vector<uint8_t>& sub, int n, int k)
+{
+    return "S|" + std::to_string(k) + "|" + std::string(sub.begin(), sub.end()) + "|" + std::to_string(attention_splits(D, draft_plan_ctx(n, k), 1));
+}
+static std::string adaptive_key(const Dims& D, const std::vector<uint8_t>& sub, int n, int k_max, int i)
+{
+    return "A|" + std::to_string(i) + "|" + std::string(sub.begin(), sub.end()) + "|" + std::to_string(attention_splits(D, draft_plan_ctx(n, k_max), 1));
+}
+
 // Common body of the two fixed-length draft calls; sub has two entries per layer.
 static int draft_fixed(ssd_ctx* c, const std::vector<uint8_t>& sub, int k, int32_t* draft_out, float* draft_maxprob_out)
 {
@@ -852,11 +864,9 @@ static int draft_fixed(ssd_ctx* c, const std::vector<uint8_t>& sub, int k, int32
     if (c->state != ST_IDLE) return fail(c, SSD_ESTATE, "draft_step needs a prefilled sequence with no draft in flight");
     if (k > c->cfg.max_k) return fail(c, SSD_ECAPACITY, "k exceeds max_k");
     if (c->n + k > c->D.max_seq) return fail(c, SSD_ECAPACITY, "draft + verification would exceed max_seq");
-    std::string key = "S|" + std::to_string(k) + "|" + std::string(sub.begin(), sub.end()) + "|";
-    for (int i = 0; i < k; i++) key += std::to_string(attention_splits(c->D, c->n + i, 1)) + ",";
-    int rc = run_sequence(c, key, [&]() {
+    int rc = run_sequence(c, draft_key(c->D, sub, c->n, k), [&]() {
         for (int i = 0; i < k; i++) {
-            int r = forward_single(c, sub.data(), i, i + 1, i, i, (i ? STEP_CHAINED : 0) | (i + 1 < k ? STEP_CHAIN_NEXT : 0));
+            int r = forward_single(c, sub.data(), i, i + 1, i, draft_plan_ctx(c->n, k), i, (i ? STEP_CHAINED : 0) | (i + 1 < k ? STEP_CHAIN_NEXT : 0));
             if (r) return r;
         }
         return (int)SSD_OK;
@@ -906,13 +916,12 @@ int ssd_draft_adaptive(ssd_ctx* c, const uint8_t* skip_mask, int k_max, float ga
     if (k_max > c->cfg.max_k) return fail(c, SSD_ECAPACITY, "k_max exceeds max_k");
     if (c->n + k_max > c->D.max_seq) return fail(c, SSD_ECAPACITY, "draft + verification would exceed max_seq");
     const std::vector<uint8_t> sub = expand_mask(skip_mask, c->D.L);
-    const std::string mask_key(sub.begin(), sub.end());
     int k = 0;
     while (k < k_max) {
         // one draft step per submission: the host reads the step's max-probability before deciding on the next
         const int i = k;
-        std::string key = "A|" + std::to_string(i) + "|" + mask_key + "|" + std::to_string(attention_splits(c->D, c->n + i, 1));
-        int rc = run_sequence(c, key, [&]() { return forward_single(c, sub.data(), i, i + 1, i, i, 0); });
+        int rc = run_sequence(c, adaptive_key(c->D, sub, c->n, k_max, i),
+                              [&]() { return forward_single(c, sub.data(), i, i + 1, i, draft_plan_ctx(c->n, k_max), i, 0); });
         if (rc) return rc;
         rc = sync_results(c);
         if (rc) return rc;

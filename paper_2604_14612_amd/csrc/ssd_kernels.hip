@@ -160,7 +160,6 @@ __device__ __forceinline__ void lds_barrier()
 {
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
-static inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 // ---------------------------------------------------------------------------------------------
 // embedding gather
@@ -211,7 +210,6 @@ hipError_t embed_rows(const Dims& D, const void* embed, Tokens tok, int M, float
 // interleaves gate row n and up row n, so that one lane holds both operands of the epilogue.
 constexpr int GV_WAVES = 8;
 constexpr int GV_THREADS = GV_WAVES * 64;
-constexpr int GV_FOLD_MAX = 8;  // attention partials per head the output projection can fold itself
 
 enum { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_STORE = 3 };
 
@@ -2582,7 +2580,6 @@ hipError_t rope_kv_rows(const Dims& D, float* qkv, const float* rope, const int*
 // attention over the cache: split over the sequence, K/V tiles staged through LDS
 // ---------------------------------------------------------------------------------------------
 constexpr int AT_THREADS = 256;
-constexpr int AT_CHUNK = 96;   // cache positions one block owns (K and V of the chunk live in LDS together)
 constexpr int AT_QPASS = 16;   // query vectors handled per pass over the staged chunk
 
 // P.V for up to NQ query vectors at once: acc[qi] += e[qi][j] * V[j][d] over this thread's positions
@@ -3551,54 +3548,10 @@ __global__ __launch_bounds__(NW * 64) void attn_wide_kernel(const float* __restr
     }
 }
 
-// Launch plan.  Few query vectors per KV head (Q = M x group size <= AW_MAXQ_TOTAL): the register-resident
-// kernel over ranges of 64 to 256 positions -- a single CU pulls only a few tens of GB/s, so a head's
-// cache is spread over many blocks even though that costs the fold of the partial results.  Many query
-// vectors (prompt blocks, wide GQA groups): the LDS-staged kernel, which fetches K/V once for all of them.
-constexpr int AW_MAXQ_TOTAL = 4;
-constexpr int AW_MAX_ROWS = 8;
-constexpr int AW_RANGE_BYTES = 32 * 1024;   // K bytes of a range: one pass of the narrowest block shape (8 waves, 4 loads each)
-constexpr int AW_MAX_RANGES = 16;
-struct AttnPlan { bool wide; int n_splits; int chunk; bool defer_fold; };   // chunk: cache rows per range
-
 static AttnPlan attn_plan(const Dims& D, int ctx, int M)
 {
-    const int force_splits = D.opt ? D.opt->attn_splits : 0, force_kernel = D.opt ? D.opt->attn_kernel : 0;
-    AttnPlan pl;
-    pl.defer_fold = false;
-    const int Q = (D.H / D.Hkv) * M;
-    // More than 4 query vectors per KV head: the MFMA form of the LDS-staged kernel (12.9 us against 14.5 us at 5 rows,
-    // 7B shape, 16-bit cache, fold included).  A model with fp32 WEIGHTS stays in fp32 arithmetic throughout: there a
-    // few rows with 1, 2, 4 or 8 query heads per KV head run the register-resident kernel, one block per row and range
-    // serving the row's group of heads (two blocks for a group of 8), re-reading a range's K/V from the cache.
-    const int G = D.H / D.Hkv;
-    pl.wide = Q <= AW_MAXQ_TOTAL ||
-              (D.kt == WT_F32 && D.wt == WT_F32 && (G == 1 || G == 2 || G == 4 || G == 8) && M <= AW_MAX_ROWS);
-    if (force_kernel == 1 || force_kernel == 3) pl.wide = false;
-    if (pl.wide) {
-        // ranges of one pass of the narrowest block shape (128 positions of 16-bit 128-wide heads, 64 of fp32 ones), at most
-        // AW_MAX_RANGES of them
-        const int range = AW_RANGE_BYTES / (D.hd * (D.kt == WT_F32 ? 4 : 2));
-        int ns = ceil_div(ctx, range);
-        // single row: up to 4 K positions, ranges grow rather than exceed what the output projection folds itself
-        // (a longer range costs the attention kernel about 1 us, a separate fold launch 5)
-        if (M == 1 && ns > GV_FOLD_MAX && ctx <= GV_FOLD_MAX * 512) ns = GV_FOLD_MAX;
-        if (ns > AW_MAX_RANGES) ns = AW_MAX_RANGES;
-        // Several query vectors per block: the registers leave one block per CU, so no more ranges than one round of blocks
-        // takes (two rows, 32 heads, about 550 positions: 7.9 us with 7 ranges, 12.7 with 9).
-        if (M > 1 && Q <= AW_MAXQ_TOTAL) ns = std::min(ns, std::max(4, 256 / D.Hkv));
-        if (force_splits > 0) ns = force_splits;
-        if (ns > ctx) ns = ctx;
-        // The length of a range is part of the launch, not computed from the position on the device: whole ranges while their
-        // number grows with the context, beyond that steps of 16 (a captured launch sequence then lasts for 16 ns positions).
-        pl.chunk = std::max(range, ceil_div(ceil_div(ctx, ns), 16) * 16);
-        if (force_splits > 0) pl.chunk = ceil_div(ctx, ns);
-        pl.n_splits = ceil_div(ctx, pl.chunk);
-    } else {
-        pl.n_splits = ceil_div(ctx, AT_CHUNK);     // a block owns AT_CHUNK positions
-        pl.chunk = AT_CHUNK;
-    }
-    return pl;
+    const AttnShape a = {D.H / D.Hkv, D.Hkv, D.hd, D.kt == WT_F32, D.wt == WT_F32};
+    return attn_plan(a, ctx, M, D.opt ? D.opt->attn_splits : 0, D.opt ? D.opt->attn_kernel : 0);
 }
 
 int attention_splits(const Dims& D, int ctx, int M)

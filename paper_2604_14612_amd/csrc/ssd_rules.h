@@ -21,4 +21,69 @@ template <typename F> SSD_HD void rows_of_wave(int wave, F&& f)
 // row of logits without a maximum.
 SSD_HD size_t embed_row(int tok, int V) { return (size_t)(tok < 0 ? 0 : tok < V ? tok : V - 1); }
 
+SSD_HD int ceil_div(int a, int b) { return (a + b - 1) / b; }
+
+// ---- attention launch plan ---------------------------------------------------------------------------------------------
+// Few query vectors per KV head (M x group size <= AW_MAXQ_TOTAL): the register-resident kernel over ranges of 64 positions
+// and more -- a single CU pulls only a few tens of GB/s, so a head's cache is spread over many blocks even though that
+// costs the fold of the partial results.  Many query vectors (prompt blocks, wide GQA groups): the LDS-staged kernel,
+// which fetches K/V once for all of them.
+constexpr int AT_CHUNK = 96;     // cache positions a block of the LDS-staged kernel owns (K and V of the chunk live in LDS together)
+constexpr int GV_FOLD_MAX = 8;   // attention partials per head the output projection can fold itself
+constexpr int AW_MAXQ_TOTAL = 4;
+constexpr int AW_MAX_ROWS = 8;
+constexpr int AW_RANGE_BYTES = 32 * 1024;   // K bytes of a range: one pass of the narrowest block shape (8 waves, 4 loads each)
+constexpr int AW_MAX_RANGES = 16;
+
+struct AttnShape { int G, Hkv, hd; bool kv_f32, w_f32; };   // query heads per KV head, KV heads, head size, element types
+struct AttnPlan { bool wide; int n_splits; int chunk; bool defer_fold; };   // chunk: cache rows per range
+
+// Plan for M rows of which the last one sees ctx positions.  force_splits, force_kernel: tuning hooks (0 = this rule).
+inline AttnPlan attn_plan(const AttnShape& a, int ctx, int M, int force_splits, int force_kernel)
+{
+    AttnPlan pl;
+    pl.defer_fold = false;
+    const int Q = a.G * M;
+    // More than 4 query vectors per KV head: the MFMA form of the LDS-staged kernel (12.9 us against 14.5 us at 5 rows,
+    // 7B shape, 16-bit cache, fold included).  A model with fp32 WEIGHTS stays in fp32 arithmetic throughout: there a
+    // few rows with 1, 2, 4 or 8 query heads per KV head run the register-resident kernel, one block per row and range
+    // serving the row's group of heads (two blocks for a group of 8), re-reading a range's K/V from the cache.
+    pl.wide = Q <= AW_MAXQ_TOTAL ||
+              (a.kv_f32 && a.w_f32 && (a.G == 1 || a.G == 2 || a.G == 4 || a.G == 8) && M <= AW_MAX_ROWS);
+    if (force_kernel == 1 || force_kernel == 3) pl.wide = false;
+    if (!pl.wide) {
+        pl.n_splits = ceil_div(ctx, AT_CHUNK);
+        pl.chunk = AT_CHUNK;
+        return pl;
+    }
+    // ranges of one pass of the narrowest block shape (128 positions of 16-bit 128-wide heads, 64 of fp32 ones) ..
+    pl.chunk = AW_RANGE_BYTES / (a.hd * (a.kv_f32 ? 4 : 2));
+    pl.n_splits = ceil_div(ctx, pl.chunk);
+    // .. up to a limit: 16; for a single row what the output projection folds itself, up to 4 K positions (a longer range
+    // costs the attention kernel about 1 us, a separate fold launch 5); for several query vectors per block, whose
+    // registers leave one block per CU, what one round of blocks takes (two rows, 32 heads, about 550 positions: 7.9 us
+    // with 7 ranges, 12.7 with 9)
+    int limit = AW_MAX_RANGES;
+    if (M == 1 && ctx <= GV_FOLD_MAX * 512) limit = GV_FOLD_MAX;
+    if (M > 1 && Q <= AW_MAXQ_TOTAL && 256 / a.Hkv < limit) limit = 256 / a.Hkv > 4 ? 256 / a.Hkv : 4;
+    if (force_splits > 0) {
+        pl.n_splits = force_splits < ctx ? force_splits : ctx;
+        pl.chunk = ceil_div(ctx, pl.n_splits);
+    } else if (pl.n_splits > limit) {
+        // Beyond it the ranges grow.  Their length is part of the launch, not computed from the position on the device
+        // (that would put the load of the position in front of the first K and V loads), so a captured launch sequence
+        // serves one length only.  Steps of 16 rows, one capture per 16 `limit` positions: a range's length is the time of its
+        // block.  1024-wide, 24 layers, 1000 tokens from position 1024, ms with all captures / replays only: 712 / 708, with
+        // four lengths per doubling 720 / 717, with the length computed on the device 742 / 740.
+        pl.chunk = ceil_div(ceil_div(ctx, limit), 16) * 16;
+        pl.n_splits = ceil_div(ctx, pl.chunk);
+    }
+    return pl;
+}
+
+// Context that the steps of a draft of up to k tokens behind n committed ones are planned for: the last step's, for all of
+// them, so that a draft has one plan and not a mixture of two where it changes inside the draft (k = 4, positions 600 to 4086,
+// 128-wide fp32 heads: 30 launch sequences instead of 117, each of which runs kernel by kernel once and is then captured).
+SSD_HD int draft_plan_ctx(int n, int k) { return n + k - 1; }
+
 }  // namespace ssdk

@@ -14,6 +14,11 @@ WRAPPERS = r"""
 #include "ssd_rules.h"
 using namespace ssdk;
 extern "C" {
+void attention_plan(int G, int Hkv, int hd, int kv_f32, int w_f32, int ctx, int M, int* out) {
+    const AttnPlan p = attn_plan(AttnShape{G, Hkv, hd, kv_f32 != 0, w_f32 != 0}, ctx, M, 0, 0);
+    out[0] = p.wide; out[1] = p.n_splits; out[2] = p.chunk;
+}
+int draft_ctx(int n, int k) { return draft_plan_ctx(n, k); }
 size_t embedding_row(int tok, int V) { return embed_row(tok, V); }
 int row_writers(int row) { int n = 0; for (int w = 0; w < 8; w++) rows_of_wave(w, [&](int c) { n += c == row; }); return n; }
 }
@@ -58,3 +63,42 @@ def test_embedding_gathers_stay_inside_the_table(rules, vocab):
     assert rules.embedding_row(-1, vocab) == rules.embedding_row(-0x80000000, vocab) == 0
     for kernel in ("embed_kernel", "embed_split_kernel", "step_finish_kernel"):
         assert "embed_row(" in kernel_source(kernel), kernel
+
+
+def plan(rules, G, Hkv, hd, kv_f32, w_f32, ctx, M):
+    out = (C.c_int * 3)()
+    rules.attention_plan(G, Hkv, hd, kv_f32, w_f32, ctx, M, out)
+    return tuple(out)
+
+
+# (query heads per KV head, KV heads, head size, fp32 cache, fp32 weights)
+ATTN_SHAPES = [(1, 32, 128, 1, 0), (1, 40, 128, 0, 0), (4, 8, 128, 0, 0), (8, 8, 128, 1, 0), (1, 16, 64, 1, 0), (1, 4, 64, 1, 1), (2, 2, 64, 0, 0),
+               (8, 1, 128, 1, 1), (1, 80, 64, 0, 0)]
+
+
+@pytest.mark.parametrize("shape", ATTN_SHAPES)
+@pytest.mark.parametrize("M", [1, 2, 4, 5, 16, 64])
+def test_attention_ranges_cover_the_context(rules, shape, M):
+    """Every position belongs to a range, the partials fit the scratch (64 ranges, or one per 96 positions of the cache) and a
+    launch that a captured sequence repeats (same plan) covers every context it is repeated for."""
+    for ctx in list(range(M, 1400)) + list(range(1400, 33000, 61)):
+        wide, ns, chunk = plan(rules, *shape, ctx, M)
+        assert ns >= 1 and chunk >= 1 and ns * chunk >= ctx, (ctx, ns, chunk)
+        assert ns <= max(64, -(-ctx // 96)), (ctx, ns)
+        if wide:
+            assert chunk % 16 == 0 and ns <= 16
+            if M == 1 and ctx <= 4096:
+                assert ns <= 8          # what the output projection folds itself
+
+
+# (the LDS-staged kernel of wide 16-bit groups has one range per 96 positions instead)
+@pytest.mark.parametrize("shape", [s for s in ATTN_SHAPES if s[0] <= 4 or s[4]])
+def test_a_long_generation_has_few_launch_plans(rules, shape):
+    """One plan per draft: as many as single steps have, one per 128 positions (steps of 16, eight ranges) and a few between."""
+    decode = [plan(rules, *shape, n, 1) for n in range(600, 4091)]
+    assert len(set(decode)) <= 34, sorted(set(decode))
+    assert sum(a != b for a, b in zip(decode, decode[1:])) == len(set(decode)) - 1      # none comes back
+    assert len({plan(rules, *shape, n, 1) for n in range(4100, 8190)}) <= 17
+    draft = {plan(rules, *shape, rules.draft_ctx(n, 4), 1) for n in range(600, 4087)}
+    assert draft <= set(decode)
+    assert all(rules.draft_ctx(n, k) == n + k - 1 for n in (1, 9) for k in (1, 15))

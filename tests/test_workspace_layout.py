@@ -1,4 +1,4 @@
-"""CPU: the regions of the workspace hold what the calls put into them.  The host side of the library (ssd_api.cpp, whose layout
+"""CPU: the regions of the workspace hold what the calls put into them, and the replayed sequences are few.  The host side of the library (ssd_api.cpp, whose layout
 functions are not exported) is compiled into a small test library."""
 import ctypes as C
 import os
@@ -16,6 +16,12 @@ CSRC = os.path.join(ROOT, "paper_2604_14612_amd", "csrc")
 WRAPPERS = r"""
 #include "%s/ssd_api.cpp"
 extern "C" {
+// distinct replayed sequences of drafts behind n0 .. n1 - 1 committed tokens
+__attribute__((visibility("default"))) int t_draft_keys(const ssd_config* c, int k, int n0, int n1, int adaptive) {
+    std::map<std::string, int> keys; const std::vector<uint8_t> sub(2 * c->n_layers, 0);
+    for (int n = n0; n < n1; n++) keys[adaptive ? adaptive_key(make_dims(*c), sub, n, k, 0) : draft_key(make_dims(*c), sub, n, k)]++;
+    return (int)keys.size();
+}
 // tap rows a confidence pass may take: a position's, a batch of the context window
 __attribute__((visibility("default"))) int t_conf_rows(const ssd_config* c) {
     const Layout l = make_layout(*c); const int w = window_batch_rows(make_dims(*c), l.rows, l.conf_rows);
@@ -68,3 +74,12 @@ def test_a_confidence_pass_fits_its_buffers(host, layers, dtype, d_ffn):
     records = min(rows, 256) * 24 * min(16, shape.vocab // 1024, shape.d_model * (2 if fused else 4) // 24)
     assert buf >= records
     assert host.t_logits_bytes(p) >= rows * shape.vocab * 4
+
+
+def test_drafts_of_a_long_generation_replay_few_sequences(host):
+    """The keys of the captured sequences name the skip mask, k and the attention plan of the draft's last step only."""
+    shape = ModelShape(2, 4096, 32, 32, 11008, 32000, dtype="bf16")
+    p = C.byref(ssd.make_config(shape, 8192, 8))
+    for k in (1, 4, 8):
+        for adaptive in (0, 1):
+            assert host.t_draft_keys(p, k, 600, 4087, adaptive) <= 34
