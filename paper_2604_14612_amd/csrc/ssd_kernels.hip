@@ -2334,19 +2334,10 @@ hipError_t rows_big(const Dims& D, const RowsFused& f, hipStream_t s)
     // 256-row tiles (one 512-thread block per CU, staging double-buffered in LDS: measured 20-30 % faster per MFMA, and
     // a launch fills the CUs with the same granularity as two 128-row blocks per CU would) wherever every stacked
     // matrix is a whole number of them; else 128-row tiles
-    const int force_tn = D.opt ? D.opt->wide_depth : 0;   // tuning hook: 128 or 256
+    const int force_tn = D.opt ? D.opt->wide_depth : 0;   // tuning hook: 128, 192 (QKV) or 256
     const bool fits256 = n_total % 256 == 0;   // (tiles are made of 64-row groups, which never straddle two matrices)
-    int tn = fits256 ? 256 : 128;
-    if (f.mode == RM_QKV && n_total % 192 == 0) {
-        // Rounds of 256 blocks that the launch takes, with the K cut made below; a 192-row tile costs 0.82 of a 256-row one
-        // (more LDS traffic per product).  7B, 512 rows: 192 blocks in one round against 256 in one: 110 -> 91 us.
-        auto cost = [&](int t) {
-            const int blocks = n_total / t * m_blocks, ks = std::min(std::max(256 / blocks, 1), 4);
-            return (double)ceil_div(blocks * ks, 256) / ks * (t == 192 ? 0.82 : 1.0);
-        };
-        if (!fits256 || cost(192) < cost(256)) tn = 192;
-    }
-    if (force_tn == 128 || (force_tn == 256 && fits256)) tn = force_tn;
+    int tn = f.mode == RM_QKV ? qkv_tile_rows(n_total, m_blocks) : fits256 ? 256 : 128;
+    if (force_tn == 128 || (force_tn == 192 && f.mode == RM_QKV && n_total % 192 == 0) || (force_tn == 256 && fits256)) tn = force_tn;
     const int n_tiles = n_total / tn;
     p.n_tiles = n_tiles;
     const bool f16 = D.wt == WT_F16;

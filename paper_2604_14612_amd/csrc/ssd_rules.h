@@ -23,6 +23,28 @@ SSD_HD size_t embed_row(int tok, int V) { return (size_t)(tok < 0 ? 0 : tok < V 
 
 SSD_HD int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
+// Weight rows per tile of the large-tile QKV launch: n_total rows (a multiple of 128), m_blocks blocks of 128 activation rows.
+// What decides is the number of rounds that the blocks take on the CUs' slots -- one block per CU for 256- and 192-row
+// tiles, two for 128-row ones -- after the cut along K that fills idle slots (up to four slices).  Time of a round, in
+// those of 256-row tiles: 192-row ones 0.88 (whole launches of as many rounds, rotary epilogue and cache rows included, random
+// data: 0.86 to 0.92), 128-row ones (two per slot) 1.2 to 1.6.  Measured, us: 7B, 512 rows: 256-row tiles 136.5, 192 121; 13B,
+// 320 rows: 158, 138; 512 rows: 167, 256; width 4992, 512 rows: 192-row tiles 246, 128 217; 320 rows: 136, 203; width 3200, 384
+// rows: 99.6, 87.1; 512 rows: 100.8, 141.
+SSD_HD int qkv_tile_rows(int n_total, int m_blocks)
+{
+    int best = 128;
+    double best_cost = 0.0;
+    for (int t = 128; t <= 256; t += 64) {
+        if (n_total % t) continue;
+        const int slots = t == 128 ? 512 : 256, blocks = n_total / t * m_blocks;
+        int ks = slots / blocks;
+        ks = ks < 1 ? 1 : ks > 4 ? 4 : ks;
+        const double cost = (double)ceil_div(blocks * ks, slots) / ks * (t == 128 ? 1.5 : t == 192 ? 0.88 : 1.0);
+        if (t == 128 || cost <= best_cost) { best = t; best_cost = cost; }
+    }
+    return best;
+}
+
 // ---- attention launch plan ---------------------------------------------------------------------------------------------
 // Few query vectors per KV head (M x group size <= AW_MAXQ_TOTAL): the register-resident kernel over ranges of 64 positions
 // and more -- a single CU pulls only a few tens of GB/s, so a head's cache is spread over many blocks even though that

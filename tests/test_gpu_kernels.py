@@ -131,10 +131,11 @@ def _first_layer_kv(ctx):
     return [kv[i * size:(i + 1) * size].view(s.n_kv_heads, n, s.head_dim) for i in (0, 1)]
 
 
-# Tiles of the QKV launch of a prompt: 192 weight rows in 136 blocks (no K cut; all rows, and a ragged last block), 192 rows cut
-# along K by two (102 and 128 blocks) and by four (34), 256 rows uncut (160 blocks) and cut (30)
-@pytest.mark.parametrize("d,kv_heads,rows,dtype", [(2176, 17, 512, "bf16"), (2176, 17, 449, "fp16"), (2176, 17, 333, "bf16"), (2048, 16, 512, "bf16"),
-                                                   (2176, 17, 70, "fp16"), (5120, 20, 512, "bf16"), (2048, 2, 300, "fp16")])
+# Tiles of the QKV launch of a prompt: 192 weight rows in 200 blocks (no K cut; all rows, and a ragged last block), 192 rows cut
+# along K by two (102 and 128 blocks) and by four (34), 256 rows uncut (160 blocks) and cut (30), 128 rows uncut (468) and cut (204)
+@pytest.mark.parametrize("d,kv_heads,rows,dtype", [(3200, 25, 512, "bf16"), (3200, 25, 449, "fp16"), (2176, 17, 333, "bf16"), (2048, 16, 512, "bf16"),
+                                                   (2176, 17, 70, "fp16"), (5120, 20, 512, "bf16"), (2048, 2, 300, "fp16"), (4992, 39, 500, "fp16"),
+                                                   (2176, 17, 450, "bf16")])
 def test_prompt_qkv_launch_element_by_element(d, kv_heads, rows, dtype):
     """Every cached K and V element of the first layer against 64 bits: rotate(Wk norm(x)) and Wv norm(x) of the embedding rows.
     Bound per element: activations enter as hi + lo (2^-17 relative, fp16 better) and the fp32 sums of 2 x K products add

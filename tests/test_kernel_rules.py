@@ -18,6 +18,7 @@ void attention_plan(int G, int Hkv, int hd, int kv_f32, int w_f32, int ctx, int 
     const AttnPlan p = attn_plan(AttnShape{G, Hkv, hd, kv_f32 != 0, w_f32 != 0}, ctx, M, 0, 0);
     out[0] = p.wide; out[1] = p.n_splits; out[2] = p.chunk;
 }
+int qkv_tile(int n_total, int m_blocks) { return qkv_tile_rows(n_total, m_blocks); }
 int draft_ctx(int n, int k) { return draft_plan_ctx(n, k); }
 size_t embedding_row(int tok, int V) { return embed_row(tok, V); }
 int row_writers(int row) { int n = 0; for (int w = 0; w < 8; w++) rows_of_wave(w, [&](int c) { n += c == row; }); return n; }
@@ -102,3 +103,17 @@ def test_a_long_generation_has_few_launch_plans(rules, shape):
     draft = {plan(rules, *shape, rules.draft_ctx(n, 4), 1) for n in range(600, 4087)}
     assert draft <= set(decode)
     assert all(rules.draft_ctx(n, k) == n + k - 1 for n in (1, 9) for k in (1, 15))
+
+
+def test_qkv_tiles_are_the_faster_ones_where_both_were_measured(rules):
+    """(stacked weight rows, prompt rows) -> rows per tile of the faster launch."""
+    measured = {(12288, 128): 192, (12288, 256): 192, (12288, 320): 192, (12288, 512): 192, (15360, 192): 256, (15360, 320): 192, (15360, 512): 256,
+                (6144, 256): 192, (6144, 512): 192, (9216, 384): 256, (9216, 512): 192, (6528, 384): 192, (6528, 512): 128, (9600, 256): 192,
+                (9600, 320): 128, (9600, 384): 128, (9600, 512): 192, (14976, 128): 192, (14976, 256): 128, (14976, 320): 192, (14976, 512): 128,
+                (1152, 512): 192, (1920, 320): 192, (3456, 65): 192}
+    for (n, rows), tile in measured.items():
+        assert rules.qkv_tile(n, -(-rows // 128)) == tile, (n, rows)
+    for n in range(128, 40000, 128):
+        for mb in (1, 2, 3, 4):
+            t = rules.qkv_tile(n, mb)
+            assert t in (128, 192, 256) and n % t == 0
