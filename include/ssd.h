@@ -210,10 +210,10 @@ SSD_API int ssd_window_confidence(ssd_ctx *ctx, float *conf_out, float *tap_conf
 
 /* For callers that cannot allocate device memory while they run (code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc): the same computation and results as ssd_layer_confidence, but every device
- * buffer the pass needs beyond the context's taps and weights -- the normalised rows, their logits, the per-row
- * results -- lives in a fixed array inside the library image (SSD_STATIC_SCRATCH_BYTES per GPU, held until the process
- * ends) instead of the workspace, 64 tap rows at a time.  Calls nothing that allocates.  SSD_ECAPACITY if 64 rows of
- * this model exceed the array (64 * (4 * vocab + 8 * d_model) bytes, e.g. a 128 256-entry vocabulary); SSD_EINVAL if
+ * buffer the pass needs beyond the context's taps and weights -- the normalised rows, their logits, the reduction's
+ * records -- lives in a fixed array inside the library image (SSD_STATIC_SCRATCH_BYTES per GPU, held until the process
+ * ends) instead of the workspace, 64 tap rows at a time; results come back through the context's host-pinned buffer.  Calls nothing that allocates.  SSD_ECAPACITY if 64 rows of
+ * this model exceed the array (64 * (4 * vocab + 8 * d_model + 12) bytes, e.g. a 128 256-entry vocabulary); SSD_EINVAL if
  * the context's device is not the current one.  All calls on one GPU share that GPU's array: calls that overlap in
  * time on one GPU (two contexts, two streams) race; the array keeps the last call's contents. */
 #define SSD_STATIC_SCRATCH_BYTES (12u << 20)

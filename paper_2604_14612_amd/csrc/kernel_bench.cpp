@@ -468,11 +468,11 @@ int main(int argc, char** argv)
     for (int kind : {1, 0}) {   // 1 = LDS-staged kernel forced, 0 = launch plan (register-resident kernel for few queries)
         opts.attn_kernel = kind;
         for (int sp : {0, 1, 2, 4, 8}) {
-            if (kind == 1 && sp != 0 && sp < 8) continue;   // the LDS-staged kernel needs ctx / 96 ranges at least
+            if (kind == 1 && sp != 0) continue;   // the LDS-staged kernel has one range per 96 positions, whatever is asked
             opts.attn_splits = sp;
             char nm[96];
             std::snprintf(nm, sizeof nm, "attention 1 row ctx 641, %s, splits %s%d", kind ? "lds-staged" : "planned",
-                          sp ? "" : "auto=", sp ? sp : std::abs(attention_splits(D, ctx + 1, 1)));
+                          sp ? "" : "auto=", attention_ranges(D, ctx + 1, 1));
             timeit(nm, 2.0 * 641 * 4096 * kvb, n, [&](int i) {
                 CK(attention(D, q, 4096, kc + (size_t)i * kv_layer * kvb, vc + (size_t)i * kv_layer * kvb, pos, 0, ctx, 1, part, act, nullptr,
                              nullptr, 0)); });
@@ -578,11 +578,11 @@ int main(int argc, char** argv)
     for (int kind : {1, 0}) {
         opts.attn_kernel = kind;
         for (int sp : {0, 2, 4, 8, 16}) {
-            if (kind == 1 && sp != 0) continue;
+            if (sp != 0 && (kind == 1 || attention_splits(D, ctx + M, M) > 0)) continue;   // LDS-staged (more than four rows here): as above
             opts.attn_splits = sp;
             char nm[96];
             std::snprintf(nm, sizeof nm, "attention M rows ctx 640+M, %s, splits %s%d", kind ? "lds-staged" : "planned",
-                          sp ? "" : "auto=", sp ? sp : std::abs(attention_splits(D, ctx + M, M)));
+                          sp ? "" : "auto=", attention_ranges(D, ctx + M, M));
             timeit(nm, 2.0 * (640 + M) * 4096 * kvb, n, [&](int i) {
                 CK(attention(D, q, 4096, kc + (size_t)i * kv_layer * kvb, vc + (size_t)i * kv_layer * kvb, pos, 0, ctx, M, part, nullptr, hi,
                              lo, 0)); });
@@ -590,17 +590,15 @@ int main(int argc, char** argv)
     }
     opts.attn_splits = 0;
     opts.attn_kernel = 0;
-    for (int kind : {3, 1}) for (int rows : {9, 16, 64}) for (int sp : {0, 16}) {
-        if (sp && (kind == 3 || rows != 64)) continue;
+    for (int kind : {3, 1}) for (int rows : {9, 16, 64}) {
         opts.attn_kernel = kind;
-        opts.attn_splits = sp;
         char nm[96];
-        std::snprintf(nm, sizeof nm, "attention %d rows ctx 640+rows, LDS-staged %s, splits %d", rows, kind == 3 ? "plain" : "MFMA", sp);
+        std::snprintf(nm, sizeof nm, "attention %d rows ctx 640+rows, LDS-staged %s, splits %d", rows, kind == 3 ? "plain" : "MFMA",
+                      attention_ranges(D, ctx + rows, rows));
         timeit(nm, 2.0 * (640 + rows) * 4096 * kvb, n, [&](int i) {
             CK(attention(D, big_a, 4096, kc + (size_t)i * kv_layer * kvb, vc + (size_t)i * kv_layer * kvb, pos, 0, ctx, rows, part, nullptr,
                          hi64, lo64, 0)); });
     }
     opts.attn_kernel = 0;
-    opts.attn_splits = 0;
     return 0;
 }

@@ -1058,7 +1058,7 @@ int ssd_layer_confidence_static(ssd_ctx* c, int row_begin, int n_rows, float* co
     sc.lo = reinterpret_cast<uint16_t*>(base + o);   o += align_up((size_t)B * D.d * 2);
     sc.tapn = reinterpret_cast<float*>(base + o);    o += align_up(rows_fused_supported(D) ? 0 : (size_t)B * D.d * 4);
     sc.logits = reinterpret_cast<float*>(base + o);  o += align_up((size_t)B * D.V * 4);
-    o += align_up((size_t)3 * B * 4);
+    o += align_up((size_t)3 * B * 4);   // (three values per row count towards the limit, though the results go to the pinned buffer)
     sc.res = c->pin_f(PIN_RES);
     sc.batch = B; sc.one_gemm = false;
     if (o > static_scratch_bytes())

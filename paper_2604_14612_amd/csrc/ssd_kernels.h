@@ -15,10 +15,10 @@ struct LaunchOpts {
     int gemv_block_cap = 0;     // > 0 overrides the block cap of the GEMV launches
     int gemv_resid_cfg = 0;     // residual projections: 100 R + 10 D + KS forces rows per group / steps in flight / K split
     int rows_depth = 0;         // > 0 forces the number of weight stripes a 16-row block keeps in flight
-    int wide_depth = 0;         // the same for the 64-row blocks
+    int wide_depth = 0;         // the same for the 64-row blocks; large tiles: weight rows per tile
     int gemv_cfg = 0;           // single-row GEMVs other than the residual projections: 100 R + 10 D + KS of a work split (kernel_bench sweeps)
     int wide_ksplit = 0;        // 64-row blocks: 1 = never cut K, > 1 forces the number of K slices
-    int attn_splits = 0;        // > 0 forces the attention split count (scratch must have been sized for it)
+    int attn_splits = 0;        // > 0 forces the number of ranges of the register-resident attention kernel (scratch must have been sized for it)
     int attn_kernel = 0;        // 0 heuristic, 1 LDS-staged kernel always, 3 the same in its plain (non-MFMA) form
     // When set, the next GEMV launch records its own begin / end timestamps into the two events (kernel time as a
     // profiler reports it, without the dispatch latency a pair of stream events around the launch would include)
@@ -195,6 +195,7 @@ size_t attention_scratch_floats(const Dims& D, int max_rows);
 // launch shape attention() uses when the last of M rows sees ctx positions: the number of position ranges,
 // negated and joined with their length for the register-resident kernel (two calls with equal values enqueue identical launches)
 int attention_splits(const Dims& D, int ctx, int M);
+int attention_ranges(const Dims& D, int ctx, int M);   // the number of position ranges itself
 
 // ---- vocabulary reduction ------------------------------------------------------------------------
 // Per row of logits [M][V]: arg-max (lowest index on ties), softmax max-probability and, when

@@ -1456,6 +1456,8 @@ constexpr int M3_PITCH = M3_CK * 2 + 16;  // bytes per LDS row (16-byte pad spre
 // stream is in flight, and registers decide that number: every row pointer is wave-uniform and lives in scalar registers, so
 // that three blocks fit (six waves per SIMD) at all row counts; with per-thread pointers nine rows and more had two.  7B, 9
 // rows, fp16: gate/up 42.7 -> 35.0 us, QKV 31.2 -> 23.4, LM head 61 -> 52; 5 rows: QKV 22.5 -> 20.5, gate/up 33.7 -> 32.9.
+// 13 to 16 rows: QKV and the residual projections keep 16 bytes per lane in scratch for the third block; two blocks without
+// are as fast (verify of 14 / 16 rows, four 7B layers: 0.58 / 0.60 ms either way, 0.67 / 0.68 with per-thread pointers).
 template <int MODE, int M3_D, bool F16, int NU>
 __global__ __launch_bounds__(512, (M3_D * (MODE == RM_SWIGLU ? 4 + NU : 2 + NU) > 12 ? 4 : 6)) void rows_mfma3_kernel(RowsP2 p)
 {
@@ -3550,6 +3552,8 @@ int attention_splits(const Dims& D, int ctx, int M)
     const AttnPlan pl = attn_plan(D, ctx, M);
     return pl.wide ? -(pl.n_splits + 64 * pl.chunk) : pl.n_splits;  // distinct values for distinct launch shapes
 }
+
+int attention_ranges(const Dims& D, int ctx, int M) { return attn_plan(D, ctx, M).n_splits; }
 
 size_t attention_scratch_floats(const Dims& D, int max_rows)
 {

@@ -84,7 +84,7 @@ inline AttnPlan attn_plan(const AttnShape& a, int ctx, int M, int force_splits, 
     // .. up to a limit: 16; for a single row what the output projection folds itself, up to 4 K positions (a longer range
     // costs the attention kernel about 1 us, a separate fold launch 5); for several query vectors per block, whose
     // registers leave one block per CU, what one round of blocks takes (two rows, 32 heads, about 550 positions: 7.9 us
-    // with 7 ranges, 12.7 with 9)
+    // with 7 ranges, as many as where the length comes from the position on the device; 12.7 with 9)
     int limit = AW_MAX_RANGES;
     if (M == 1 && ctx <= GV_FOLD_MAX * 512) limit = GV_FOLD_MAX;
     if (M > 1 && Q <= AW_MAXQ_TOTAL && 256 / a.Hkv < limit) limit = 256 / a.Hkv > 4 ? 256 / a.Hkv : 4;
