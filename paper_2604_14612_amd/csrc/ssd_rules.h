@@ -89,8 +89,8 @@ inline AttnPlan attn_plan(const AttnShape& a, int ctx, int M, int force_splits, 
     if (M == 1 && ctx <= GV_FOLD_MAX * 512) limit = GV_FOLD_MAX;
     if (M > 1 && Q <= AW_MAXQ_TOTAL && 256 / a.Hkv < limit) limit = 256 / a.Hkv > 4 ? 256 / a.Hkv : 4;
     if (force_splits > 0) {
-        pl.n_splits = force_splits < ctx ? force_splits : ctx;
-        pl.chunk = ceil_div(ctx, pl.n_splits);
+        pl.chunk = ceil_div(ctx, force_splits < ctx ? force_splits : ctx);
+        pl.n_splits = ceil_div(ctx, pl.chunk);
     } else if (pl.n_splits > limit) {
         // Beyond it the ranges grow.  Their length is part of the launch, not computed from the position on the device
         // (that would put the load of the position in front of the first K and V loads), so a captured launch sequence
