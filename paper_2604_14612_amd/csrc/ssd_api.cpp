@@ -8,6 +8,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -25,7 +26,7 @@ constexpr size_t ALIGN = 256;
 size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 
 struct Layout {
-    size_t rope, kv, x, h, qkv, att, act, part, logits, taps, tapn, hi, lo, ssq, small, ring, ring_conf, total;
+    size_t rope, kv, x, h, qkv, att, act, part, logits, taps, tapn, hi, lo, ssq, small, ring, ring_conf, step, total;
     int rows;       // activation rows: max(max_k + 1, prompt rows per pass)
     int prefill_rows;  // prompt rows per pass: SSD_PREFILL_ROWS where the shape fits the 128 x 128 tiling, 64 where only the
                        // 64-row one, else 16
@@ -116,6 +117,7 @@ Layout make_layout(const ssd_config& c)
     // positions, and one confidence value per tap row of the window
     l.ring = o;       o += align_up((size_t)c.conf_window * 2 * D.L * D.d * sizeof(float));
     l.ring_conf = o;  o += align_up((size_t)c.conf_window * 2 * D.L * sizeof(float));
+    l.step = o;       o += align_up(step_scratch_bytes(D));   // hand-over words and weight table of the single-row step in one launch
     l.total = o;
     return l;
 }
@@ -127,7 +129,7 @@ enum { SM_POS = 0, SM_TOK = 8 /* 17 ints: pending + drafts */, SM_SINK = 96, SM_
 // word offsets in the context's host-pinned buffer.  Kernels read the token ids of a pass from it and write the few words
 // a call returns into it, so that a call costs no copy in either direction, only the synchronisation at its end; every
 // call that uses a region synchronises before it returns, so the next one may write it.
-enum { PIN_TOK = 0 /* 17: slot i + 1 = token of draft step i */, PIN_PROB = 32 /* 16 */, PIN_TARGET = 64 /* 64 */,
+enum { PIN_TOK = 0 /* 17: slot i + 1 = token of draft step i */, PIN_PROB = 32 /* 16 */, PIN_STEP = 48 /* 1: a wait of the step in one launch gave up */, PIN_TARGET = 64 /* 64 */,
        PIN_VTOK = 128 /* 17: row 0 unused, drafts */, PIN_RES = 256 /* 3 x 2 x SSD_MAX_LAYERS */,
        PIN_PROMPT = 256 + 6 * SSD_MAX_LAYERS /* max_seq */ };
 
@@ -157,6 +159,11 @@ struct ssd_ctx {
     int device;        // device that was current when the workspace was set
     void* static_scratch;  // this device's copy of the library's static scratch array (resolved at set_workspace)
     ssd_stats st;
+    int step_blocks;   // blocks of a single-row step in one launch, 0 = not for this shape or device
+    bool step_table;   // its weight table is on the device
+    bool step_off;     // a wait gave up since the last reset: launches per matrix
+    bool step_now;     // the sequence being enqueued takes it
+    std::vector<StepWeights> step_rows;   // host copy of the table
     bool use_graphs;   // replay captured launch sequences instead of launching kernel by kernel
     std::map<std::string, hipGraphExec_t> graphs;  // nullptr = sequence seen once, not captured yet
     int prof_kid;      // kernel id being timed, -1 = off
@@ -232,6 +239,24 @@ static inline bool is_gemv_kid(int kid)
         }                                                                                  \
     } while (0)
 
+// One launch whose blocks wait for each other may be in flight per device: two of them would each hold CUs that the other
+// one needs.  Whoever finds the device's slot taken uses the launches per matrix.
+std::atomic<bool> step_slots[64];
+struct StepSlot {
+    ssd_ctx* c;
+    std::atomic<bool>* slot;
+    StepSlot(ssd_ctx* ctx, bool wanted) : c(ctx), slot(nullptr)
+    {
+        if (wanted && c->device >= 0 && c->device < 64 && !step_slots[c->device].exchange(true, std::memory_order_acquire)) slot = &step_slots[c->device];
+        c->step_now = slot != nullptr;
+    }
+    ~StepSlot()
+    {
+        c->step_now = false;
+        if (slot) slot->store(false, std::memory_order_release);
+    }
+};
+
 // One decoder layer for a single row (draft / vanilla decode path); either sub-block may be left out.  plan_ctx: the context
 // attention's launch is planned for, at least the positions the row sees.
 int layer_single(ssd_ctx* c, int l, int pos_off, int plan_ctx, bool do_attn, bool do_mlp)
@@ -270,12 +295,6 @@ int forward_single(ssd_ctx* c, const uint8_t* sub, int slot, int slot_out, int p
     if (!(flags & STEP_CHAINED))
         HIPCHK(embed_rows(D, c->w.embed, Tokens{c->small_i() + SM_TOK + slot, nullptr}, 1, c->f(c->lay.x), c->stream, c->f(c->lay.rope),
                           c->pos_dev(), pos_off, c->small_f() + SM_ROPE), "embed");
-    for (int l = 0; l < D.L; l++) {
-        const bool do_attn = !(sub && sub[2 * l]), do_mlp = !(sub && sub[2 * l + 1]);
-        if (!do_attn && !do_mlp) continue;
-        int rc = layer_single(c, l, pos_off, plan_ctx, do_attn, do_mlp);
-        if (rc) return rc;
-    }
     float* logits = c->f(c->lay.logits) + (size_t)lrow * D.V;
     StepOut out = {};
     out.tok_out = c->small_i() + SM_TOK + slot_out;
@@ -286,8 +305,26 @@ int forward_single(ssd_ctx* c, const uint8_t* sub, int slot, int slot_out, int p
         out.embed = c->w.embed; out.x_next = c->f(c->lay.x);
         out.rope = c->f(c->lay.rope); out.rope_pos = c->pos_dev(); out.rope_off = pos_off + 1; out.rope_row = c->small_f() + SM_ROPE;
     }
-    // LM head with the greedy token and its soft-max probability folded in (block statistics in the attention
-    // scratch, which is idle here, then a one-block fold)
+    // (block statistics of the LM head in the attention scratch, which is idle there)
+    if (c->step_now) {
+        out.step_ctrl = reinterpret_cast<unsigned*>(c->ws + c->lay.step);
+        out.step_err_host = c->pinned + PIN_STEP;
+        StepLaunch a = {};
+        a.blocks = c->step_blocks; a.scratch = c->ws + c->lay.step; a.sub = sub;
+        a.lm_head = c->w.lm_head; a.final_norm = c->w.final_norm;
+        a.x = c->f(c->lay.x); a.rope_row = c->small_f() + SM_ROPE; a.pos_dev = c->pos_dev(); a.pos_off = pos_off; a.plan_ctx = plan_ctx;
+        a.kv = c->ws + c->lay.kv; a.kv_layer = c->lay.kv_layer_elems * (c->cfg.kv_dtype == 0 ? 4 : 2);
+        a.logits = logits; a.vstat = c->f(c->lay.part); a.clamp = c->cfg.conf_clamp;
+        HIPCHK(step_fused(D, a, out, c->stream), "step");
+        return SSD_OK;
+    }
+    for (int l = 0; l < D.L; l++) {
+        const bool do_attn = !(sub && sub[2 * l]), do_mlp = !(sub && sub[2 * l + 1]);
+        if (!do_attn && !do_mlp) continue;
+        int rc = layer_single(c, l, pos_off, plan_ctx, do_attn, do_mlp);
+        if (rc) return rc;
+    }
+    // LM head with the greedy token and its soft-max probability folded in, then a one-block fold
     TIMED(SSD_K_GEMV_LMHEAD, gemv_lmhead_argmax(D, c->w.lm_head, c->w.final_norm, c->f(c->lay.x), logits, c->cfg.conf_clamp,
                                                 c->f(c->lay.part), out, c->stream), "gemv_lmhead");
     return SSD_OK;
@@ -544,6 +581,31 @@ int sync_results(ssd_ctx* c)
     return SSD_OK;
 }
 
+// Runs the launch sequence of a call of single-row steps and waits for its results.  plan_ctx: the context its steps are
+// planned for; sub (may be null): their mask.  Where the steps take one launch each and a wait inside gave up, everything from the pending token on is done
+// again by the launches per matrix (nothing was committed, cache rows of uncommitted positions are written anew).
+template <typename F>
+int run_steps(ssd_ctx* c, const std::string& key, int plan_ctx, const uint8_t* sub, F&& body)
+{
+    bool whole = true;   // the step in one launch knows whole layers only
+    for (int l = 0; sub && l < c->D.L; l++) whole = whole && !sub[2 * l] == !sub[2 * l + 1];
+    {
+        StepSlot slot(c, c->step_blocks > 0 && c->step_table && !c->step_off && whole && c->prof_kid < 0 && step_plan_fits(c->D, plan_ctx, c->step_blocks));
+        if (c->step_now) {
+            c->pinned[PIN_STEP] = 0;
+            int rc = run_sequence(c, "P" + key, body);
+            const int rs = sync_results(c);   // the slot is free again when the launches are done
+            if (rc) return rc;
+            if (rs) return rs;
+            if (!c->pinned[PIN_STEP]) return SSD_OK;
+            c->step_off = true;
+            HIPCHK(hipMemsetAsync(c->ws + c->lay.step + 4, 0, 4, c->stream), "step error clear");
+        }
+    }
+    int rc = run_sequence(c, key, body);
+    return rc ? rc : sync_results(c);
+}
+
 // Device buffers one confidence pass works in: hi/lo pairs of the normalised tap rows (16-bit weights), the normalised
 // rows themselves (fp32 weights), their logits, and 3 result values per row in the pinned buffer; `batch` tap rows go through per pass.
 struct ConfScratch {
@@ -684,6 +746,7 @@ int ssd_create(const ssd_config* cfg, void* hip_stream, ssd_ctx** out)
     c->n = 0; c->k_pending = 0; c->tap_rows = 0; c->tap_row0 = 0; c->logit_rows = 0; c->ring_count = 0; c->pinned = nullptr; c->device = -1; c->static_scratch = nullptr;
     memset(&c->st, 0, sizeof(c->st));
     memset(&c->w, 0, sizeof(c->w));
+    c->step_blocks = 0; c->step_table = c->step_off = c->step_now = false;
     c->prof_kid = -1; c->prof_used = 0;
     c->use_graphs = true;
     *out = c;
@@ -719,6 +782,9 @@ int ssd_set_workspace(ssd_ctx* c, void* dev, size_t bytes)
     HIPCHK(hipMemcpyAsync(c->ws + c->lay.rope, tab.data(), tab.size() * sizeof(float), hipMemcpyHostToDevice, c->stream),
            "rope upload");
     HIPCHK(hipMemsetAsync(c->ws + c->lay.small, 0, 4096, c->stream), "state clear");
+    HIPCHK(step_device_blocks(c->D, c->device, &c->step_blocks), "step occupancy");
+    c->step_table = false;
+    if (c->step_blocks > 0) HIPCHK(hipMemsetAsync(c->ws + c->lay.step, 0, step_scratch_bytes(c->D), c->stream), "step clear");
     HIPCHK(hipStreamSynchronize(c->stream), "workspace sync");  // tab goes out of scope
     if (c->have_w) c->state = ST_READY;
     return SSD_OK;
@@ -749,6 +815,7 @@ int ssd_load_weights(ssd_ctx* c, const ssd_weights* w)
     c->wo.assign(w->wo, w->wo + L); c->wg.assign(w->wg, w->wg + L); c->wu.assign(w->wu, w->wu + L);
     c->wd.assign(w->wd, w->wd + L);
     c->have_w = true;
+    c->step_table = false;
     if (c->ws) c->state = ST_READY;
     return SSD_OK;
 }
@@ -759,6 +826,7 @@ int ssd_reset(ssd_ctx* c)
     if (c->state == ST_CREATED) return fail(c, SSD_ESTATE, "nothing to reset");
     c->state = ST_READY;
     c->n = 0; c->k_pending = 0; c->tap_rows = 0; c->logit_rows = 0; c->ring_count = 0;
+    c->step_off = false;
     memset(&c->st, 0, sizeof(c->st));
     return SSD_OK;
 }
@@ -792,6 +860,14 @@ int ssd_prefill(ssd_ctx* c, const int32_t* tokens, int n, int32_t* first_token_o
     for (int i = 0; i < n; i++)
         if (tokens[i] < 0 || tokens[i] >= c->D.V) return fail(c, SSD_EINVAL, "prompt token id out of range");
     HIPCHK(set_state(c->small_i() + SM_TOK, 0, c->pos_dev(), 0, c->stream), "set_state");
+    if (c->step_blocks > 0 && !c->step_table) {   // once per set of weights
+        c->step_rows.resize(c->D.L);
+        for (int l = 0; l < c->D.L; l++)
+            c->step_rows[l] = {{c->attn_norm[l], c->wq[l], c->wk[l], c->wv[l], c->wo[l], c->mlp_norm[l], c->wg[l], c->wu[l], c->wd[l]}};
+        HIPCHK(hipMemcpyAsync(c->ws + c->lay.step + step_table_offset(c->D), c->step_rows.data(), c->step_rows.size() * sizeof(StepWeights),
+                              hipMemcpyHostToDevice, c->stream), "step table");
+        c->step_table = true;
+    }
     int last_M = 0;
     const int block = c->lay.prefill_rows;
     memcpy(c->pinned + PIN_PROMPT, tokens, (size_t)n * sizeof(int32_t));
@@ -833,11 +909,7 @@ int ssd_decode(ssd_ctx* c, int32_t* token_out)
     if (c->n + 1 > c->D.max_seq) return fail(c, SSD_ECAPACITY, "sequence would exceed max_seq");
     // pending token sits in tok slot 0; its successor is written to slot 1, then promoted
     std::string key = "D|" + std::to_string(attention_splits(c->D, c->n, 1));
-    int rc = run_sequence(c, key, [&]() {
-        return forward_single(c, nullptr, 0, 1, 0, c->n, 0, STEP_COMMIT);
-    });
-    if (rc) return rc;
-    rc = sync_results(c);
+    int rc = run_steps(c, key, c->n, nullptr, [&]() { return forward_single(c, nullptr, 0, 1, 0, c->n, 0, STEP_COMMIT); });
     if (rc) return rc;
     *token_out = c->pinned[PIN_TOK + 1];
     c->n += 1;
@@ -864,15 +936,13 @@ static int draft_fixed(ssd_ctx* c, const std::vector<uint8_t>& sub, int k, int32
     if (c->state != ST_IDLE) return fail(c, SSD_ESTATE, "draft_step needs a prefilled sequence with no draft in flight");
     if (k > c->cfg.max_k) return fail(c, SSD_ECAPACITY, "k exceeds max_k");
     if (c->n + k > c->D.max_seq) return fail(c, SSD_ECAPACITY, "draft + verification would exceed max_seq");
-    int rc = run_sequence(c, draft_key(c->D, sub, c->n, k), [&]() {
+    int rc = run_steps(c, draft_key(c->D, sub, c->n, k), draft_plan_ctx(c->n, k), sub.data(), [&]() {
         for (int i = 0; i < k; i++) {
             int r = forward_single(c, sub.data(), i, i + 1, i, draft_plan_ctx(c->n, k), i, (i ? STEP_CHAINED : 0) | (i + 1 < k ? STEP_CHAIN_NEXT : 0));
             if (r) return r;
         }
         return (int)SSD_OK;
     });
-    if (rc) return rc;
-    rc = sync_results(c);
     if (rc) return rc;
     memcpy(draft_out, c->pinned + PIN_TOK + 1, sizeof(int32_t) * k);
     if (draft_maxprob_out) memcpy(draft_maxprob_out, c->pinned + PIN_PROB, sizeof(float) * k);
@@ -920,10 +990,8 @@ int ssd_draft_adaptive(ssd_ctx* c, const uint8_t* skip_mask, int k_max, float ga
     while (k < k_max) {
         // one draft step per submission: the host reads the step's max-probability before deciding on the next
         const int i = k;
-        int rc = run_sequence(c, adaptive_key(c->D, sub, c->n, k_max, i),
-                              [&]() { return forward_single(c, sub.data(), i, i + 1, i, draft_plan_ctx(c->n, k_max), i, 0); });
-        if (rc) return rc;
-        rc = sync_results(c);
+        int rc = run_steps(c, adaptive_key(c->D, sub, c->n, k_max, i), draft_plan_ctx(c->n, k_max), sub.data(),
+                           [&]() { return forward_single(c, sub.data(), i, i + 1, i, draft_plan_ctx(c->n, k_max), i, 0); });
         if (rc) return rc;
         const float p = c->pin_f(PIN_PROB)[i];
         draft_out[i] = c->pinned[PIN_TOK + 1 + i];

@@ -83,10 +83,33 @@ struct StepOut {
     int* pos_dev; int32_t* tok0;   // decode: *pos_dev += 1, *tok0 = token (both null: left alone)
     const void* embed; float* x_next;   // x_next set: x_next[0..d) = embedding row of the token
     const float* rope; const int* rope_pos; int rope_off; float* rope_row;   // rope_row set: rotary row *rope_pos + rope_off of the next step
+    unsigned* step_ctrl; unsigned step_hops; int32_t* step_err_host;   // of step_fused: its control words, the hand-overs of the step, set to 1 (host-pinned) where a wait gave up
 };
 constexpr int GEMV_MAX_BLOCKS = 1024;
 hipError_t gemv_lmhead_argmax(const Dims& D, const void* wlm, const float* gain, const float* x, float* logits, float clamp,
                               float* vstat, const StepOut& out, hipStream_t s);
+
+// ---- a whole single-row step in one launch (narrow models) ---------------------------------------------------
+// Layers, LM head and the end of the step as gemv_lmhead_argmax leaves it, by resident blocks that hand the activations to
+// each other through memory.  Blocks wait for each other: at most one such launch may be in flight per device.  A wait that
+// takes longer than 50 ms (blocks that are not resident, CUs held by others) ends the launch with *step_err_host = 1, nothing
+// committed; scratch[1] (32-bit words) has to be cleared before the next launch then.
+struct StepWeights { const void* p[9]; };   // attention norm gain, wq, wk, wv, wo, MLP norm gain, wg, wu, wd of a layer (device table)
+size_t step_scratch_bytes(const Dims& D);   // 0: shape not supported.  Cleared to zero before the first launch, weight table excepted
+size_t step_table_offset(const Dims& D);    // bytes from the scratch's start to the weight table [L]
+hipError_t step_device_blocks(const Dims& D, int device, int* blocks_out);   // blocks of a launch on this device, 0: not supported there
+bool step_plan_fits(const Dims& D, int ctx, int blocks);   // attention over ctx positions has enough blocks
+struct StepLaunch {
+    int blocks;
+    void* scratch;
+    const uint8_t* sub;         // host, may be null: two entries per layer, [2l] != 0 leaves out the attention sub-block, [2l+1] the MLP
+    const void* lm_head; const float* final_norm;
+    const float* x; const float* rope_row; const int* pos_dev; int pos_off;
+    int plan_ctx;               // positions attention is planned for, at least those the row sees
+    void* kv; size_t kv_layer;  // cache, bytes of K (or V) of one layer
+    float* logits; float* vstat; float clamp;
+};
+hipError_t step_fused(const Dims& D, const StepLaunch& a, const StepOut& o, hipStream_t s);
 
 // ---- multi-row (verify / prefill / confidence) path ------------------------------------------
 // out[r][:] = rmsnorm(in[r][:], gain) for r < M   (rows of length K)

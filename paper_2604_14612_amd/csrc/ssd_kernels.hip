@@ -702,7 +702,13 @@ __global__ __launch_bounds__(SF_THREADS) void step_finish_kernel(const float* __
             o.tok_out[0] = a.arg;
             o.tok_host[0] = a.arg;
             o.maxprob_host[0] = 1.0f / a.z;
-            if (o.pos_dev) { o.pos_dev[0] += 1; o.tok0[0] = a.arg; }
+            bool ok = true;
+            if (o.step_ctrl) {   // of a step in one launch: the next launch's tags start behind this one's; a step that gave up commits nothing
+                ok = o.step_ctrl[1] == 0;
+                o.step_ctrl[0] += o.step_hops;
+                if (!ok) o.step_err_host[0] = 1;
+            }
+            if (o.pos_dev && ok) { o.pos_dev[0] += 1; o.tok0[0] = a.arg; }
         }
     }
     if (!o.x_next) return;   // uniform
@@ -711,6 +717,15 @@ __global__ __launch_bounds__(SF_THREADS) void step_finish_kernel(const float* __
     float* x = o.x_next;
     for (int i = tid * 4; i < d; i += SF_THREADS * 4)
         *reinterpret_cast<float4*>(x + i) = make_float4(Elem<WT>::get(row, i), Elem<WT>::get(row, i + 1), Elem<WT>::get(row, i + 2), Elem<WT>::get(row, i + 3));
+}
+
+static hipError_t step_finish(const Dims& D, const float* vstat, int blocks, const StepOut& o, hipStream_t s)
+{
+    const RopeRow rr = {o.rope, o.rope_pos, o.rope_off, D.hd, o.rope_row};
+    if (D.wt == WT_BF16) hipLaunchKernelGGL(step_finish_kernel<uint16_t>, dim3(1), dim3(SF_THREADS), 0, s, vstat, blocks, o, D.d, D.V, rr);
+    else if (D.wt == WT_F16) hipLaunchKernelGGL(step_finish_kernel<f16_t>, dim3(1), dim3(SF_THREADS), 0, s, vstat, blocks, o, D.d, D.V, rr);
+    else hipLaunchKernelGGL(step_finish_kernel<float>, dim3(1), dim3(SF_THREADS), 0, s, vstat, blocks, o, D.d, D.V, rr);
+    return hipGetLastError();
 }
 
 // Largest dynamic LDS size a kernel has been enabled for.  A process-wide cache of an idempotent runtime call
@@ -912,11 +927,7 @@ hipError_t gemv_lmhead_argmax(const Dims& D, const void* wlm, const float* gain,
     hipError_t e = launch_gemv<EPI_STORE>(D, p, s, &blocks);
     if (e != hipSuccess) return e;
     if (blocks < 1 || blocks > GEMV_MAX_BLOCKS) return hipErrorInvalidValue;
-    const RopeRow rr = {o.rope, o.rope_pos, o.rope_off, D.hd, o.rope_row};
-    if (D.wt == WT_BF16) hipLaunchKernelGGL(step_finish_kernel<uint16_t>, dim3(1), dim3(SF_THREADS), 0, s, vstat, blocks, o, D.d, D.V, rr);
-    else if (D.wt == WT_F16) hipLaunchKernelGGL(step_finish_kernel<f16_t>, dim3(1), dim3(SF_THREADS), 0, s, vstat, blocks, o, D.d, D.V, rr);
-    else hipLaunchKernelGGL(step_finish_kernel<float>, dim3(1), dim3(SF_THREADS), 0, s, vstat, blocks, o, D.d, D.V, rr);
-    return hipGetLastError();
+    return step_finish(D, vstat, blocks, o, s);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -3669,6 +3680,617 @@ hipError_t attention(const Dims& D, const float* q, int ldq, const void* kc, con
         if (D.hd == 64) return attention_t<float, 64>(D, q, ldq, kc, vc, pos_dev, pos_off, pl, ctx, M, part, out, out_hi, out_lo, s);
     }
     return hipErrorInvalidValue;
+}
+
+// ---- whole single-row steps of narrow models in one launch ---------------------------------------------------------------
+// A layer of a 1024-wide model is 26 MB: its five launches cost their fixed time, not their bytes.  Here the blocks of ONE
+// launch, one per CU and all resident, walk the layers.  What bounds it is the hand-over of a stage's output vector to all
+// blocks, five per layer, and the arithmetic of the few waves that own rows in between.  Hence:
+//  * the vectors travel as 64-bit words (value, tag): a reader polls the data itself until every word carries the tag of the
+//    hand-over it waits for, so there is no counter, no second round trip, and nothing has to be reset;
+//  * a reader first waits ST_FIRST_POLL: polls that arrive while the words are being written take the line away from the
+//    writers again and again.  With the pause a hand-over is 0.8 to 0.9 us, without 2 to 2.6 (step below: 443 -> 351 us);
+//  * a block's outputs leave in one store where several waves own them;
+//  * the weights do not wait for anything: a wave holds its rows of all of a layer's stages in registers and requests those
+//    of the next layer when it no longer needs the present ones and has the input of the stage it is in (loads return in order:
+//    requested before a poll they delay it: 351 -> 333 us);
+//  * a wave owns whole rows, so that no sum crosses waves; K and V of the cached positions are requested before the query is there.
+// Measured, 24 layers of 1024 (FFN 2816), 300 positions, 32000-row LM head: 620 us with a launch per matrix, 333 so.
+// Every wait is bounded (wait_ticks of the 100 MHz clock): when blocks are not all resident -- another stream or process holds
+// CUs for that long -- the launch drains, the error flag tells the host, and the step is run again by the launches per matrix.
+// Tags are 32 bits of a running number and could only be mistaken after 2^32 hand-overs without a write to the word.
+constexpr int ST_THREADS = ST_WAVES * 64;
+constexpr int ST_FIRST_POLL = 18;         // x 64 clocks (10: 344 us, 13: 340, 16: 333 to 335, 19: 333, 22: 334)
+constexpr long ST_WAIT_TICKS = 5000000;   // 50 ms: longer than what other streams' kernels usually hold CUs for
+
+struct StepP {
+    const StepWeights* layers; int L;
+    uint64_t mask[2];           // bit l: layer l is executed
+    const void* lm_head; const float* final_norm;
+    const float* x; const float* rope_row; const int* pos_dev; int pos_off;
+    char* kv; size_t kv_layer;  // cache, bytes of K (or V) of one layer
+    float* logits; float* vstat; float clamp;
+    unsigned long long* mail; StepMail off;
+    int d, dq, dkv, f, V, H, Hkv, max_seq; float eps;
+    int n_splits, chunk;
+    long wait_ticks;
+};
+
+__device__ __forceinline__ void mail_put(unsigned long long* p, float v, unsigned tag)
+{
+    __hip_atomic_store(p, ((unsigned long long)tag << 32) | __float_as_uint(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// next set bit of a 128-bit mask (low, high word) at l or above, -1 if there is none
+__device__ __forceinline__ int next_layer(uint64_t lo, uint64_t hi, int l)
+{
+    if (l < 64) {
+        const unsigned long long b = lo >> l << l;
+        if (b) return __ffsll(b) - 1;
+        l = 64;
+    }
+    const unsigned long long b = l < 128 ? hi >> (l - 64) << (l - 64) : 0;
+    return b ? 63 + __ffsll(b) : -1;
+}
+// exchanges between the 16-lane rows of a wave without the LDS crossbar: sum / max over rows 0 + 1 and 2 + 3, over both halves
+__device__ __forceinline__ float rows_swap_sum(float v)
+{
+    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float rows_swap_max(float v)
+{
+    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float wave_sum_fast(float v) { return rows_swap_sum(row16_sum(v)); }
+// the same over the segments of LPP lanes of a wave, for values that are uniform inside each segment or belong to its lanes
+template <int LPP> __device__ __forceinline__ float seg_sum_fast(float v)
+{
+    if (LPP == 8) v = dpp_add<0x128>(v);    // the other half of the row
+    if (LPP <= 16) return rows_swap_sum(v);
+    auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+template <int LPP> __device__ __forceinline__ float seg_max_fast(float v)
+{
+    if (LPP == 8) v = dpp_max<0x128>(v);
+    if (LPP <= 16) return rows_swap_max(v);
+    auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
+template <typename WT, typename KT, int HD>
+__global__ __launch_bounds__(ST_THREADS) void step_kernel(StepP p)
+{
+    constexpr int VEC = Elem<WT>::VEC, CH = 64 * VEC, CD = ST_CD, CF = ST_CF, XF = CF * CH;
+    constexpr int EPV = 16 / (int)sizeof(KT), LPP = HD / EPV, PPL = 64 / LPP, NL = 4, PASS = NL * ST_WAVES * PPL;
+    constexpr int NX = (CD * CH + 2 * ST_THREADS - 1) / (2 * ST_THREADS), NF = (XF + 2 * ST_THREADS - 1) / (2 * ST_THREADS);   // pairs of elements of a d- or dq-, of an f-vector per thread
+    extern __shared__ __align__(16) float st_sm[];
+    float* xs = st_sm;                                                   // [2][XF] input vector of a stage, alternating
+    const unsigned long long* tab = reinterpret_cast<const unsigned long long*>(st_sm + 2 * XF);   // weight pointers [L][9]
+    __shared__ float red[2][ST_WAVES];
+    __shared__ float rope[HD];
+    __shared__ __align__(16) float qs[3 * HD];                           // query (scaled), new key and value of the head
+    __shared__ float outs[2 * ST_WAVES];                                 // outputs of the block's rows, handed over by one store
+    __shared__ float wacc[ST_WAVES * HD], wml[ST_WAVES * 2];
+    // What depends on the lane is worked out anew in every stage (fresh): kept over the layers it would not fit beside the
+    // weights and go to scratch memory.
+    int tid = threadIdx.x, lane = tid & 63;
+    auto fresh = [&]() { asm volatile("" : "+v"(tid)); lane = tid & 63; };
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int b = blockIdx.x, NB = gridDim.x;
+    const int d = p.d, dq = p.dq, dkv = p.dkv, f = p.f;
+    unsigned* ctrl = reinterpret_cast<unsigned*>(p.mail);
+    unsigned long long* const mx = p.mail + p.off.x;
+    unsigned long long* const mqkv = p.mail + p.off.qkv;
+    unsigned long long* const mpart = p.mail + p.off.part;
+    unsigned long long* const mact = p.mail + p.off.act;
+
+    {
+        unsigned long long* t = reinterpret_cast<unsigned long long*>(st_sm + 2 * XF);
+        const unsigned long long* src = reinterpret_cast<const unsigned long long*>(p.layers);
+        for (int i = tid; i < p.L * 9; i += ST_THREADS) t[i] = src[i];
+        if (tid < HD) rope[tid] = p.rope_row[tid];
+    }
+    unsigned tag = ctrl[0];
+    bool alive = ctrl[1] == 0;                  // an earlier launch of the sequence has given up: drain
+    const int p0 = p.pos_dev[0] + p.pos_off;
+    // what this block and wave own: rows of the residual stream, pairs of q / k / v rows, gate / up pairs, pairs of LM-head rows
+    const int xr0 = step_begin(d, b, NB) + wave;
+    const bool has_x = xr0 < step_begin(d, b + 1, NB);
+    const int nqp = (dq + 2 * dkv) / 2;
+    const int qp = step_begin(nqp, b, NB) + wave;
+    const bool has_q = qp < step_begin(nqp, b + 1, NB);
+    const int gp0 = step_begin(f, b, NB) + wave, gp_end = step_begin(f, b + 1, NB);
+    const int lp_end = step_begin(p.V / 2, b + 1, NB), lp0 = step_begin(p.V / 2, b, NB) + wave;
+    // rows of the q / k / v pair: the two rows of a rotary pair, or consecutive rows of v
+    auto qkv_rows = [&](int pair, int& m, int& r0, int& r1) {
+        const int j = 2 * pair;
+        if (j < dq + dkv) {
+            m = j < dq ? 0 : 1;
+            const int jj = m ? j - dq : j, head = jj / HD, i = (jj % HD) >> 1;
+            r0 = head * HD + i; r1 = r0 + HD / 2;
+        } else {
+            m = 2; r0 = j - dq - dkv; r1 = r0 + 1;
+        }
+    };
+    int qm, qr0, qr1;
+    qkv_rows(qp, qm, qr0, qr1);
+    float xr = has_x ? p.x[xr0] : 0.f;          // residual value of this wave's row
+    __syncthreads();
+
+    auto ptr = [&](int l, int which) -> const char* {   // uniform: scalar registers
+        const unsigned long long v = tab[l * 9 + which];
+        return reinterpret_cast<const char*>(((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32) |
+                                             (unsigned)__builtin_amdgcn_readfirstlane((int)v));
+    };
+    enum { P_AN = 0, P_Q, P_K, P_V, P_O, P_MN, P_G, P_U, P_D };
+    // Weights of the next executed layer.  Loads are unconditional, through a buffer descriptor that is empty where there is
+    // nothing to load (such lanes get zeros and cost no memory request): behind a branch the compiler merges old and new
+    // registers by copies, which wait for the loads just issued (1 to 3 us per stage).
+    u32x4_t bq[2][CD], bo[CD], bg[ST_GU][2][CD], bd[CF];
+    auto row_load = [&](u32x4_t* w, int C, const char* m, size_t row, int K, bool ok) {
+        auto r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(m) + row * K * sizeof(WT), 0, ok ? K * (int)sizeof(WT) : 0, 0x00020000);
+#pragma unroll
+        for (int c = 0; c < CF; c++)
+            if (c < C) w[c] = __builtin_amdgcn_raw_buffer_load_b128(r, (c * CH + lane * VEC) * (int)sizeof(WT), 0, 2 /* nt */);
+    };
+    auto lm_load = [&](u32x4_t (*w)[CD], int pair) {
+        row_load(w[0], CD, static_cast<const char*>(p.lm_head), (size_t)pair * 2, d, pair < lp_end);
+        row_load(w[1], CD, static_cast<const char*>(p.lm_head), (size_t)pair * 2 + 1, d, pair < lp_end);
+    };
+    float2 gq[NX], gg[NX];                      // norm gains of this thread's elements: next attention sub-block (or LM head), next MLP
+    auto xe = [&](int u) { return min(2 * (u * ST_THREADS + tid), d - 2); };
+    auto gain = [&](float2 (&o)[NX], const char* g) {
+        const auto r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(g), 0, d * 4, 0x00020000);
+#pragma unroll
+        for (int u = 0; u < NX; u++) {
+            const auto w = __builtin_amdgcn_raw_buffer_load_b64(r, (u * ST_THREADS + tid) * 8, 0, 0);
+            o[u] = make_float2(__uint_as_float(w[0]), __uint_as_float(w[1]));
+        }
+    };
+    auto load_qkv = [&](int l) {                // of layer l, or, l < 0, the first pair of LM-head rows
+        const int t = max(l, 0);
+        const char* m = l < 0 ? static_cast<const char*>(p.lm_head) : ptr(t, P_Q + qm);
+        const bool ok = l < 0 ? lp0 < lp_end : has_q;
+        row_load(bq[0], CD, m, l < 0 ? (size_t)lp0 * 2 : (size_t)qr0, d, ok);
+        row_load(bq[1], CD, m, l < 0 ? (size_t)lp0 * 2 + 1 : (size_t)qr1, d, ok);
+        gain(gq, l < 0 ? reinterpret_cast<const char*>(p.final_norm) : ptr(t, P_AN));
+    };
+    auto load_o = [&](int l) { row_load(bo, CD, ptr(max(l, 0), P_O), xr0, dq, l >= 0 && has_x); };
+    auto load_gu = [&](int l) {                 // or the next pairs of LM-head rows
+        const int t = max(l, 0);
+        const char* lh = static_cast<const char*>(p.lm_head);
+        const char* wg = l < 0 ? lh : ptr(t, P_G);
+        const char* wu = l < 0 ? lh : ptr(t, P_U);
+#pragma unroll
+        for (int u = 0; u < ST_GU; u++) {
+            const int pair = lp0 + (u + 1) * ST_WAVES, gp = gp0 + u * ST_WAVES;
+            const bool ok = l < 0 ? pair < lp_end : gp < gp_end;
+            row_load(bg[u][0], CD, wg, l < 0 ? (size_t)pair * 2 : (size_t)gp, d, ok);
+            row_load(bg[u][1], CD, wu, l < 0 ? (size_t)pair * 2 + 1 : (size_t)gp, d, ok);
+        }
+        gain(gg, ptr(t, P_MN));
+    };
+    auto load_d = [&](int l) { row_load(bd, CF, ptr(max(l, 0), P_D), xr0, f, l >= 0 && has_x); };
+
+    // Waits until the word pairs at pair[0..N) below n_pairs all carry `tag` (those at n_pairs and above count as there); v
+    // receives their values.  Called by whole waves.  A word is written by one 8-byte store, so the halves of a 16-byte load are
+    // each whole.
+    auto mail_wait = [&](const auto& pair, auto& v, unsigned long long* base, int n_pairs) {
+        constexpr int N = sizeof(v) / sizeof(v[0]);
+        const auto r = __builtin_amdgcn_make_buffer_rsrc(base, 0, n_pairs * 16, 0x00020000);
+        u32x4_t w[N];
+        int spins = 0;
+        long t0 = 0;
+        __builtin_amdgcn_s_sleep(ST_FIRST_POLL);
+        while (true) {
+            bool ok = true;
+            asm volatile("" ::: "memory");   // the words change under the loop
+#pragma unroll
+            for (int u = 0; u < N; u++) w[u] = __builtin_amdgcn_raw_buffer_load_b128(r, pair[u] * 16, 0, 16 /* sc1: device scope */);
+#pragma unroll
+            for (int u = 0; u < N; u++) ok = ok && ((w[u].y == tag && w[u].w == tag) || pair[u] >= n_pairs);
+            if (__all(ok) || !alive) break;
+            if ((++spins & 63) == 0) {
+                const long now = wall_clock64();
+                if (t0 == 0) t0 = now;
+                if (__hip_atomic_load(ctrl + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) alive = false;
+                else if (now - t0 > p.wait_ticks) {
+                    __hip_atomic_store(ctrl + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    alive = false;
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < N; u++) v[u] = make_float2(__uint_as_float(w[u].x), __uint_as_float(w[u].z));
+    };
+
+    int buf = 0, xpar = 0;
+    bool first = true;                          // the residual stream is still the embedding row in memory
+    // residual stream into LDS, times the gain; returns the RMS scale
+    auto take_x = [&](const float2 (&gain)[NX]) -> float {
+        fresh();
+        float2 v[NX];
+        if (first) {
+#pragma unroll
+            for (int u = 0; u < NX; u++) v[u] = *reinterpret_cast<const float2*>(p.x + xe(u));
+        } else {
+            int pr[NX];
+#pragma unroll
+            for (int u = 0; u < NX; u++) pr[u] = u * ST_THREADS + tid;
+            mail_wait(pr, v, mx + (size_t)xpar * d, d / 2);
+        }
+        buf ^= 1;
+        float ss = 0.f;
+#pragma unroll
+        for (int u = 0; u < NX; u++) {
+            const int i = 2 * (u * ST_THREADS + tid);
+            if (i < d) {
+                *reinterpret_cast<float2*>(xs + buf * XF + gv_xpos<VEC>(i)) = make_float2(v[u].x * gain[u].x, v[u].y * gain[u].y);
+                ss += v[u].x * v[u].x + v[u].y * v[u].y;
+            }
+        }
+        ss = wave_sum_fast(ss);
+        if (lane == 0) red[buf][wave] = ss;
+        lds_barrier();
+        float t = 0.f;
+#pragma unroll
+        for (int i = 0; i < ST_WAVES; i++) t += red[buf][i];
+        return 1.0f / sqrtf(t / (float)d + p.eps);
+    };
+    auto dot = [&](const u32x4_t* w, int C, int K) -> float {
+        const float* x = xs + buf * XF + lane * (VEC == 8 ? 4 : VEC);
+        float a = 0.f;
+#pragma unroll
+        for (int c = 0; c < CF; c++)
+            if (c < C && c * CH + lane * VEC < K) a = gv_dot<WT>(w[c], x + c * CH, a);
+        return wave_sum_fast(a);
+    };
+    // the block's share of the residual stream to everybody
+    auto give_x = [&]() {
+        tag++; xpar ^= 1; first = false;
+        if (lane == 0) outs[wave] = xr;
+        lds_barrier();
+        const int x0 = step_begin(d, b, NB), i = tid;
+        if (i < step_begin(d, b + 1, NB) - x0) mail_put(mx + (size_t)xpar * d + x0 + i, outs[i], tag);
+    };
+
+    int ln = next_layer(p.mask[0], p.mask[1], 0);
+    load_qkv(ln); load_o(ln); load_gu(ln); load_d(ln);
+    while (ln >= 0) {
+        const int l = ln;
+        ln = next_layer(p.mask[0], p.mask[1], l + 1);
+        KT* kc = reinterpret_cast<KT*>(p.kv + (size_t)(2 * l) * p.kv_layer);
+        KT* vc = reinterpret_cast<KT*>(p.kv + (size_t)(2 * l + 1) * p.kv_layer);
+        // ---- q, k, v ----
+        {
+            const float sc = take_x(gq);
+            tag++;
+            if (has_q) {
+                const float a = dot(bq[0], CD, d) * sc, c = dot(bq[1], CD, d) * sc;
+                float o0 = a, o1 = c;
+                if (qm < 2) {
+                    const int i = qr0 % HD;
+                    const float cs = rope[2 * i], sn = rope[2 * i + 1];
+                    o0 = a * cs - c * sn; o1 = c * cs + a * sn;
+                }
+                if (lane < 2) {
+                    float o = lane == 0 ? o0 : o1;
+                    if (qm > 0) {
+                        const int r = lane == 0 ? qr0 : qr1;
+                        KT* row = (qm == 1 ? kc : vc) + ((size_t)(r / HD) * p.max_seq + p0) * HD;
+                        Elem<KT>::put(row, r % HD, o);
+                        if (sizeof(KT) == 2) { KT t; Elem<KT>::put(&t, 0, o); o = Elem<KT>::get(&t, 0); }   // attention sees what the cache holds
+                    }
+                    outs[lane * ST_WAVES + wave] = o;
+                }
+            }
+            lds_barrier();
+            if (wave == 0 && lane < 2 * ST_WAVES) {   // lane: pair lane % ST_WAVES of the block, its row lane / ST_WAVES
+                const int pr = step_begin(nqp, b, NB) + lane % ST_WAVES;
+                int m, r0, r1;
+                qkv_rows(pr, m, r0, r1);
+                if (pr < step_begin(nqp, b + 1, NB))
+                    mail_put(mqkv + (m == 0 ? 0 : m == 1 ? dq : dq + dkv) + (lane < ST_WAVES ? r0 : r1), outs[lane], tag);
+            }
+        }
+        // ---- attention: one block per query head and range of positions ----
+        if (b < p.H * p.n_splits) {
+            fresh();
+            const int head = b / p.n_splits, split = b % p.n_splits, kvh = head / (p.H / p.Hkv);
+            const int j0 = split * p.chunk, jlast = min(j0 + p.chunk, p.max_seq) - 1;
+            const int n = min(p.chunk, p0 + 1 - j0);   // may be <= 0
+            const int n_pass = n > 0 ? (n + PASS - 1) / PASS : 0;
+            const bool has_cur = n > 0 && j0 + n == p0 + 1;
+            const int seg = lane / LPP, sl = (lane % LPP) * EPV;
+            const KT* kb = kc + (size_t)kvh * p.max_seq * HD + sl;
+            const KT* vb = vc + (size_t)kvh * p.max_seq * HD + sl;
+            u32x4_t kr[NL], vr[NL];
+            auto issue = [&](int pass) {
+#pragma unroll
+                for (int t = 0; t < NL; t++) {
+                    const int j = min(j0 + ((pass * NL + t) * ST_WAVES + wave) * PPL + seg, jlast);
+                    kr[t] = *reinterpret_cast<const u32x4_t*>(kb + (size_t)j * HD);
+                    vr[t] = *reinterpret_cast<const u32x4_t*>(vb + (size_t)j * HD);
+                }
+            };
+            issue(0);
+            if (wave < 3 && (wave == 0 || has_cur)) {   // wave 0: the query, waves 1 and 2: the position's key and value
+                const int pr[1] = {(wave == 0 ? head * HD : dq + (wave - 1) * dkv + kvh * HD) / 2 + min(lane, HD / 2 - 1)};
+                const float sc = wave == 0 ? 1.0f / sqrtf((float)HD) : 1.0f;
+                float2 v[1];
+                mail_wait(pr, v, mqkv, (dq + 2 * dkv) / 2);
+                if (lane < HD / 2) *reinterpret_cast<float2*>(qs + wave * HD + 2 * lane) = make_float2(v[0].x * sc, v[0].y * sc);
+            }
+            lds_barrier();
+            float m = -INFINITY, lsum = 0.f, acc[EPV];
+#pragma unroll
+            for (int u = 0; u < EPV; u++) acc[u] = 0.f;
+            for (int pass = 0; pass < n_pass; pass++) {
+                if (pass) issue(pass);
+                float s[NL];
+#pragma unroll
+                for (int t = 0; t < NL; t++) {
+                    const int j = j0 + ((pass * NL + t) * ST_WAVES + wave) * PPL + seg;
+                    float kf[EPV];
+                    aw_unpack<KT>(kr[t], kf);
+                    if (has_cur && j == p0) {
+#pragma unroll
+                        for (int u = 0; u < EPV; u++) kf[u] = qs[HD + sl + u];
+                    }
+                    float a = 0.f;
+#pragma unroll
+                    for (int u = 0; u < EPV; u++) a = fmaf(kf[u], qs[sl + u], a);
+                    a = aw_seg_sum<LPP>(a);
+                    s[t] = j <= p0 && j < j0 + n ? a : -INFINITY;
+                }
+                float mt = s[0];
+#pragma unroll
+                for (int t = 1; t < NL; t++) mt = fmaxf(mt, s[t]);
+                mt = seg_max_fast<LPP>(mt);
+                const float mn = fmaxf(m, mt);
+                const bool live = mn > -INFINITY;
+                const float c = live ? __expf(m - mn) : 1.0f;
+                lsum *= c;
+#pragma unroll
+                for (int u = 0; u < EPV; u++) acc[u] *= c;
+                m = mn;
+#pragma unroll
+                for (int t = 0; t < NL; t++) {
+                    const int j = j0 + ((pass * NL + t) * ST_WAVES + wave) * PPL + seg;
+                    const float e = live ? __expf(s[t] - mn) : 0.f;
+                    lsum += e;
+                    float vf[EPV];
+                    aw_unpack<KT>(j < j0 + n ? vr[t] : u32x4_t{0u, 0u, 0u, 0u}, vf);   // rows past the position may hold anything
+                    if (has_cur && j == p0) {
+#pragma unroll
+                        for (int u = 0; u < EPV; u++) vf[u] = qs[2 * HD + sl + u];
+                    }
+#pragma unroll
+                    for (int u = 0; u < EPV; u++) acc[u] = fmaf(e, vf[u], acc[u]);
+                }
+            }
+            lsum = seg_sum_fast<LPP>(lsum);
+#pragma unroll
+            for (int u = 0; u < EPV; u++) {
+                acc[u] = seg_sum_fast<LPP>(acc[u]);
+                if (seg == 0) wacc[wave * HD + sl + u] = acc[u];
+            }
+            if (lane == 0) { wml[wave * 2] = m; wml[wave * 2 + 1] = lsum; }
+            lds_barrier();
+            if (tid < HD) {
+                float gm = -INFINITY, num = 0.f, den = 0.f;
+#pragma unroll
+                for (int w = 0; w < ST_WAVES; w++) gm = fmaxf(gm, wml[w * 2]);
+#pragma unroll
+                for (int w = 0; w < ST_WAVES; w++) {
+                    const float mw = wml[w * 2], c = mw > -INFINITY ? __expf(mw - gm) : 0.f;
+                    num = fmaf(c, wacc[w * HD + tid], num);
+                    den = fmaf(c, wml[w * 2 + 1], den);
+                }
+                unsigned long long* o = mpart + (size_t)b * (HD + 2);
+                mail_put(o + tid, num, tag + 1);
+                if (tid < 2) mail_put(o + HD + tid, tid == 0 ? gm : den, tag + 1);
+            }
+        }
+        // ---- output projection: its input is the fold of the heads' partials ----
+        {
+            fresh();
+            tag++;
+            const int ns = p.n_splits, np = p.H * ns * (HD / 2 + 1);
+            float gm[NX], den[NX];
+            float2 num[NX];
+#pragma unroll
+            for (int x = 0; x < NX; x++) { gm[x] = -INFINITY; den[x] = 0.f; num[x] = make_float2(0.f, 0.f); }
+            for (int s0 = 0; s0 < ns; s0 += 4) {
+                int pr[8 * NX];
+                float2 v[8 * NX];   // per split: two elements of the output, (maximum, sum)
+#pragma unroll
+                for (int x = 0; x < NX; x++) {
+                    const int e = 2 * (x * ST_THREADS + tid);
+#pragma unroll
+                    for (int u = 0; u < 4; u++) {
+                        const int r = e < dq && s0 + u < ns ? ((e / HD) * ns + s0 + u) * (HD / 2 + 1) : np;   // np: nothing to wait for
+                        pr[8 * x + 2 * u] = r + (e % HD) / 2; pr[8 * x + 2 * u + 1] = r + HD / 2;
+                    }
+                }
+                mail_wait(pr, v, mpart, np);
+#pragma unroll
+                for (int x = 0; x < NX; x++) {
+                    const float2* w = v + 8 * x;
+                    float mn = gm[x];
+#pragma unroll
+                    for (int u = 0; u < 4; u++) mn = s0 + u < ns ? fmaxf(mn, w[2 * u + 1].x) : mn;
+                    const float c = gm[x] > -INFINITY ? __expf(gm[x] - mn) : 0.f;
+                    num[x].x *= c; num[x].y *= c; den[x] *= c;
+                    gm[x] = mn;
+#pragma unroll
+                    for (int u = 0; u < 4; u++) {
+                        const float q = s0 + u < ns && w[2 * u + 1].y > 0.f ? __expf(w[2 * u + 1].x - mn) : 0.f;
+                        num[x].x = fmaf(q, w[2 * u].x, num[x].x); num[x].y = fmaf(q, w[2 * u].y, num[x].y);
+                        den[x] = fmaf(q, w[2 * u + 1].y, den[x]);
+                    }
+                }
+            }
+            load_qkv(ln);
+            buf ^= 1;
+#pragma unroll
+            for (int x = 0; x < NX; x++) {
+                const int i = 2 * (x * ST_THREADS + tid);
+                if (i < dq) *reinterpret_cast<float2*>(xs + buf * XF + gv_xpos<VEC>(i)) = make_float2(num[x].x / den[x], num[x].y / den[x]);
+            }
+            lds_barrier();
+            if (has_x) xr += dot(bo, CD, dq);
+            give_x();
+            fresh();
+            load_o(ln);
+        }
+        // ---- gate and up ----
+        {
+            const float sc = take_x(gg);
+            tag++;
+#pragma unroll
+            for (int u = 0; u < ST_GU; u++) {
+                const int gp = gp0 + u * ST_WAVES;
+                if (gp < gp_end) {
+                    const float a = dot(bg[u][0], CD, d) * sc, c = dot(bg[u][1], CD, d) * sc;
+                    if (lane == 0) outs[u * ST_WAVES + wave] = a / (1.0f + __expf(-a)) * c;
+                }
+            }
+            lds_barrier();
+            if (wave == 0 && lane < gp_end - gp0) mail_put(mact + gp0 + lane, outs[lane], tag);
+        }
+        // ---- down projection ----
+        {
+            fresh();
+            int pr[NF];
+            float2 v[NF];
+#pragma unroll
+            for (int u = 0; u < NF; u++) pr[u] = u * ST_THREADS + tid;
+            mail_wait(pr, v, mact, f / 2);
+            load_gu(ln);
+            buf ^= 1;
+#pragma unroll
+            for (int u = 0; u < NF; u++) {
+                const int i = 2 * (u * ST_THREADS + tid);
+                if (i < f) *reinterpret_cast<float2*>(xs + buf * XF + gv_xpos<VEC>(i)) = v[u];
+            }
+            lds_barrier();
+            if (has_x) xr += dot(bd, CF, f);
+            give_x();
+            fresh();
+            load_d(ln);
+        }
+    }
+    // ---- LM head: the first three row pairs of every wave are in registers, a used one is replaced by the third next ----
+    const float sc = take_x(gq);
+    VStat vs = {-INFINITY, 0.f, 0x7fffffff};
+    auto lm_rows = [&](const u32x4_t (*w)[CD], int pair) {
+        const float a = dot(w[0], CD, d) * sc, c = dot(w[1], CD, d) * sc;
+        if (lane == 0) *reinterpret_cast<float2*>(p.logits + (size_t)pair * 2) = make_float2(a, c);
+        vstat_add(vs, fminf(fmaxf(a, -p.clamp), p.clamp), pair * 2);
+        vstat_add(vs, fminf(fmaxf(c, -p.clamp), p.clamp), pair * 2 + 1);
+    };
+    constexpr int LR = (1 + ST_GU) * ST_WAVES;   // pairs that the block's registers hold
+    for (int i = lp0; i < lp_end; i += LR) {
+        lm_rows(bq, i);
+        lm_load(bq, i + LR);
+#pragma unroll
+        for (int u = 0; u < ST_GU; u++) {
+            const int j = i + (u + 1) * ST_WAVES;
+            if (j < lp_end) lm_rows(bg[u], j);
+            lm_load(bg[u], j + LR);
+        }
+    }
+    __shared__ VStat vred[ST_WAVES];
+    if (lane == 0) vred[wave] = vs;
+    lds_barrier();
+    if (tid == 0) {
+        VStat a = vred[0];
+#pragma unroll
+        for (int w = 1; w < ST_WAVES; w++) vstat_merge(a, vred[w]);
+        p.vstat[b * 3] = a.m; p.vstat[b * 3 + 1] = a.z; p.vstat[b * 3 + 2] = __int_as_float(a.arg);
+    }
+}
+
+static StepShape step_shape(const Dims& D) { return {D.d, D.dq, D.dkv, D.f, D.V, D.hd, D.H, D.Hkv, D.wt, D.kt}; }
+
+size_t step_scratch_bytes(const Dims& D)
+{
+    const StepShape s = step_shape(D);
+    return step_blocks(s, ST_BLOCKS) ? step_mail(s).total * 8 + (size_t)D.L * sizeof(StepWeights) : 0;
+}
+
+size_t step_table_offset(const Dims& D) { return step_mail(step_shape(D)).total * 8; }
+
+template <typename WT, typename KT>
+static const void* step_fn(const Dims& D)
+{
+    return D.hd == 64 ? (const void*)step_kernel<WT, KT, 64> : (const void*)step_kernel<WT, KT, 128>;
+}
+static const void* step_fn(const Dims& D)
+{
+    if (D.wt == WT_F32) return step_fn<float, float>(D);
+    if (D.wt == WT_BF16) return D.kt == WT_F32 ? step_fn<uint16_t, float>(D) : step_fn<uint16_t, uint16_t>(D);
+    return D.kt == WT_F32 ? step_fn<f16_t, float>(D) : step_fn<f16_t, f16_t>(D);
+}
+static size_t step_lds_bytes(const Dims& D)
+{
+    return (size_t)2 * ST_CF * 64 * (D.wt == WT_F32 ? 4 : 8) * sizeof(float) + (size_t)D.L * sizeof(StepWeights);
+}
+
+hipError_t step_device_blocks(const Dims& D, int device, int* blocks_out)
+{
+    *blocks_out = 0;
+    if (!step_scratch_bytes(D)) return hipSuccess;
+    int cus = 0, per_cu = 0;
+    hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
+    if (e != hipSuccess) return e;
+    const size_t lds = step_lds_bytes(D);   // below 64 KB
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, step_fn(D), ST_THREADS, lds);
+    if (e != hipSuccess) return e;
+    if (per_cu >= 1) *blocks_out = step_blocks(step_shape(D), cus);
+    return hipSuccess;
+}
+
+bool step_plan_fits(const Dims& D, int ctx, int blocks)
+{
+    const AttnPlan pl = attn_plan(D, ctx, 1);
+    return pl.wide && pl.n_splits <= AW_MAX_RANGES && D.H * pl.n_splits <= blocks;
+}
+
+hipError_t step_fused(const Dims& D, const StepLaunch& a, const StepOut& o, hipStream_t s)
+{
+    const int ctx = a.plan_ctx;
+    if (a.blocks < 1 || !step_plan_fits(D, ctx, a.blocks) || a.blocks != step_blocks(step_shape(D), a.blocks) || ctx < 1 || ctx > D.max_seq)
+        return hipErrorInvalidValue;
+    if (!o.tok_out || !o.tok_host || !o.maxprob_host || (o.pos_dev && !o.tok0) || (o.x_next && !o.embed) || !o.step_ctrl) return hipErrorInvalidValue;
+    const AttnPlan pl = attn_plan(D, ctx, 1);
+    StepP p = {};
+    p.off = step_mail(step_shape(D));
+    p.mail = static_cast<unsigned long long*>(a.scratch);
+    p.layers = reinterpret_cast<const StepWeights*>(p.mail + p.off.total); p.L = D.L;
+    StepOut out = o;
+    out.step_hops = 0;
+    for (int l = 0; l < D.L; l++) {
+        if (a.sub && a.sub[2 * l] != a.sub[2 * l + 1]) return hipErrorInvalidValue;
+        if (!(a.sub && a.sub[2 * l])) { p.mask[l >> 6] |= 1ull << (l & 63); out.step_hops += 5; }
+    }
+    p.lm_head = a.lm_head; p.final_norm = a.final_norm; p.x = a.x; p.rope_row = a.rope_row; p.pos_dev = a.pos_dev; p.pos_off = a.pos_off;
+    p.kv = static_cast<char*>(a.kv); p.kv_layer = a.kv_layer;
+    p.logits = a.logits; p.vstat = a.vstat; p.clamp = a.clamp;
+    p.d = D.d; p.dq = D.dq; p.dkv = D.dkv; p.f = D.f; p.V = D.V; p.H = D.H; p.Hkv = D.Hkv; p.max_seq = D.max_seq; p.eps = D.eps;
+    p.n_splits = pl.n_splits; p.chunk = pl.chunk;
+    p.wait_ticks = ST_WAIT_TICKS;
+    void* args[] = {&p};
+    hipError_t e = hipLaunchKernel(step_fn(D), dim3(a.blocks), dim3(ST_THREADS), args, step_lds_bytes(D), s);
+    if (e != hipSuccess) return e;
+    return step_finish(D, a.vstat, a.blocks, out, s);
 }
 
 // ---------------------------------------------------------------------------------------------

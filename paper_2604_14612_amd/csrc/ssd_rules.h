@@ -108,4 +108,50 @@ inline AttnPlan attn_plan(const AttnShape& a, int ctx, int M, int force_splits, 
 // 128-wide fp32 heads: 30 launch sequences instead of 117, each of which runs kernel by kernel once and is then captured).
 SSD_HD int draft_plan_ctx(int n, int k) { return n + k - 1; }
 
+// ---- whole single-row steps in one launch --------------------------------------------------------------------------------
+// Narrow 16-bit and fp32 models: every launch of a decode layer moves a few MB, so the five launches cost their fixed time
+// (about 5 us each) and not their bytes.  There one launch of resident blocks walks the layers, see step_kernel.
+constexpr int ST_WAVES = 8;
+constexpr int ST_GU = 2;                // gate / up pairs of a wave
+constexpr int ST_CD = 2, ST_CF = 6;     // 16-byte loads per lane and row that a wave keeps of matrices with d or dq columns, with f columns
+constexpr int ST_BLOCKS = 256;
+constexpr int ST_WAIT_WORDS = 8;        // control words in front of the hand-over words: launch number, error flag
+
+struct StepShape { int d, dq, dkv, f, V, hd, H, Hkv; int wt, kt; };   // wt, kt: WeightType codes
+
+// First of the n units (row pairs, rows) that block b of nb owns; it owns those up to the next block's first.
+SSD_HD int step_begin(int n, int b, int nb) { return (int)((long)n * b / nb); }
+
+// Blocks of the launch on a device with `cus` compute units, 0 where the launches per matrix are used.  A wave
+// owns at most one row (pair) of every stage, two of gate / up, and holds their weights in registers (80 of 256), hence the limits
+// on the widths; every block owns a row of the residual stream, so that a block that has seen
+// the whole of it knows that every other block has finished what went before.
+inline int step_blocks(const StepShape& s, int cus)
+{
+    const int ch = 64 * (s.wt == 0 ? 4 : 8);
+    if (s.d > ST_CD * ch || s.dq > ST_CD * ch || s.f > ST_CF * ch) return 0;
+    if (s.hd != 64 && s.hd != 128) return 0;
+    if (s.dq % 64 || s.dkv % 64) return 0;
+    if (s.kt != 0 && s.kt != s.wt) return 0;   // caches of the other 16-bit type
+    int nb = cus < ST_BLOCKS ? cus : ST_BLOCKS;
+    if (nb > s.d) nb = s.d;
+    if (nb < 1) return 0;
+    if (ceil_div(s.d, nb) > ST_WAVES || ceil_div((s.dq + 2 * s.dkv) / 2, nb) > ST_WAVES || ceil_div(s.f, nb) > ST_GU * ST_WAVES) return 0;
+    return nb;
+}
+
+// Hand-over words of a step: residual stream twice, q / k / v of the position, attention partials, FFN activations.
+struct StepMail { size_t x, qkv, part, act, total; };
+inline StepMail step_mail(const StepShape& s)
+{
+    StepMail m;
+    size_t o = ST_WAIT_WORDS;
+    m.x = o;    o += (size_t)2 * s.d;
+    m.qkv = o;  o += (size_t)s.dq + 2 * s.dkv;
+    m.part = o; o += (size_t)s.H * AW_MAX_RANGES * (s.hd + 2);
+    m.act = o;  o += (size_t)s.f;
+    m.total = o;
+    return m;
+}
+
 }  // namespace ssdk

@@ -1,0 +1,80 @@
+"""CPU: who owns what in a single-row step that is one launch (csrc/ssd_rules.h): every unit of every stage has one owner, no
+wave more than its registers hold, and the hand-over words of the stages do not overlap."""
+import ctypes as C
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2604_14612_amd", "csrc")
+
+WRAPPERS = r"""
+#include "ssd_rules.h"
+using namespace ssdk;
+extern "C" {
+int blocks(const int* s, int cus) { return step_blocks(StepShape{s[0], s[1], s[2], s[3], s[4], s[5], s[6], s[7], s[8], s[9]}, cus); }
+int begin(int n, int b, int nb) { return step_begin(n, b, nb); }
+void mail(const int* s, long* o) {
+    const StepMail m = step_mail(StepShape{s[0], s[1], s[2], s[3], s[4], s[5], s[6], s[7], s[8], s[9]});
+    o[0] = m.x; o[1] = m.qkv; o[2] = m.part; o[3] = m.act; o[4] = m.total;
+}
+int limits(int i) { const int v[] = {ST_WAVES, ST_GU, ST_CD, ST_CF, AW_MAX_RANGES, ST_WAIT_WORDS}; return v[i]; }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    if shutil.which("g++") is None:
+        pytest.skip("needs g++")
+    d = tmp_path_factory.mktemp("step_rules")
+    src, lib = str(d / "rules.cpp"), str(d / "librules.so")
+    with open(src, "w") as f:
+        f.write(WRAPPERS)
+    r = subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I" + CSRC, "-o", lib, src], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    return C.CDLL(lib)
+
+
+# d, dq, dkv, f, V, hd, H, Hkv, weight type, cache type (0 fp32, 1 bf16, 2 fp16)
+SHAPES = [
+    (256, 256, 256, 688, 1024, 64, 4, 4, 0, 0), (512, 512, 512, 1536, 16, 64, 8, 8, 0, 0), (1024, 1024, 1024, 2816, 32000, 64, 16, 16, 1, 0),
+    (1024, 1024, 256, 3072, 4112, 128, 8, 2, 1, 1), (64, 64, 64, 48, 272, 64, 1, 1, 2, 2), (528, 512, 64, 1040, 48, 64, 8, 1, 2, 0),
+    (16, 1024, 1024, 16, 16, 64, 16, 16, 1, 0), (1024, 64, 64, 16, 128256, 64, 1, 1, 1, 0),
+]
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("cus", [256, 255, 200, 64])
+def test_every_unit_has_one_owner_within_the_limits(rules, shape, cus):
+    s = (C.c_int * 10)(*shape)
+    nb = rules.blocks(s, cus)
+    d, dq, dkv, f, V, hd, H, Hkv, wt, kt = shape
+    waves, gu, cd, cf, ranges, ctrl = (rules.limits(i) for i in range(6))
+    if nb == 0:
+        assert cus < 256 or d < 256, "a full device takes shapes of at least 256 rows"
+        return
+    assert nb <= min(cus, d)
+    chunk = 64 * (4 if wt == 0 else 8)
+    assert d <= cd * chunk and dq <= cd * chunk and f <= cf * chunk
+    for n, most in ((d, waves), ((dq + 2 * dkv) // 2, waves), (f, gu * waves), (V // 2, None)):
+        edges = [rules.begin(n, b, nb) for b in range(nb + 1)]
+        assert edges[0] == 0 and edges[-1] == n and all(a <= b for a, b in zip(edges, edges[1:]))
+        if most is not None:
+            assert max(b - a for a, b in zip(edges, edges[1:])) <= most
+    # every block owns a row of the residual stream
+    assert all(rules.begin(d, b, nb) < rules.begin(d, b + 1, nb) for b in range(nb))
+    o = (C.c_long * 5)()
+    rules.mail(s, o)
+    sizes = (2 * d, dq + 2 * dkv, H * ranges * (hd + 2), f)
+    assert o[0] >= ctrl and all(o[i] + sizes[i] <= o[i + 1] for i in range(4))
+    assert all(v % 2 == 0 for v in o[:4]), "word pairs are read by 16-byte loads"
+
+
+@pytest.mark.parametrize("shape", [(1040, 1024, 1024, 2816, 32000, 64, 16, 16, 1, 0), (1024, 1024, 1024, 3088, 32000, 64, 16, 16, 1, 0),
+                                   (528, 512, 512, 688, 1024, 64, 8, 8, 0, 0), (1024, 1024, 1024, 2816, 32000, 64, 16, 16, 1, 2),
+                                   (4096, 4096, 4096, 11008, 32000, 128, 32, 32, 1, 0)])
+def test_wider_shapes_and_mixed_types_take_the_launches_per_matrix(rules, shape):
+    assert rules.blocks((C.c_int * 10)(*shape), 256) == 0
