@@ -535,6 +535,23 @@ int forward_rows(ssd_ctx* c, int M, int pos_off, int pos_host, bool want_logits,
     return SSD_OK;
 }
 
+// Verification of M rows of a narrow model: two launches behind the embedding rows, with the results of forward_rows.
+int verify_fused(ssd_ctx* c, int M, Tokens tok)
+{
+    const Dims& D = c->D;
+    HIPCHK(embed_rows(D, c->w.embed, tok, M, c->f(c->lay.x), c->stream), "embed");
+    RowsStepLaunch a = {};
+    a.blocks = c->step_blocks; a.scratch = c->ws + c->lay.step; a.M = M; a.ctx = c->n - 1 + M;
+    a.lm_head = c->w.lm_head; a.final_norm = c->w.final_norm;
+    a.x = c->f(c->lay.x); a.rope = c->f(c->lay.rope); a.pos_dev = c->pos_dev();
+    a.kv = c->ws + c->lay.kv; a.kv_layer = c->lay.kv_layer_elems * (c->cfg.kv_dtype == 0 ? 4 : 2);
+    a.logits = c->f(c->lay.logits); a.taps = c->f(c->lay.taps);
+    a.vmax = reinterpret_cast<float2*>(c->f(c->lay.part)); a.clamp = c->cfg.conf_clamp;   // (the attention scratch is idle)
+    a.tok_out = c->small_i() + SM_TARGET; a.tok_host = c->pinned + PIN_TARGET; a.err_host = c->pinned + PIN_STEP;
+    HIPCHK(rows_step_fused(D, a, c->stream), "verify");
+    return SSD_OK;
+}
+
 // Runs a launch sequence.  The first time a key is seen the sequence runs kernel by kernel; the
 // second time it is captured into a HIP graph, and from then on the graph is replayed (one
 // submission instead of hundreds of launches).  Everything position-dependent is read from
@@ -581,16 +598,22 @@ int sync_results(ssd_ctx* c)
     return SSD_OK;
 }
 
-// Runs the launch sequence of a call of single-row steps and waits for its results.  plan_ctx: the context its steps are
-// planned for; sub (may be null): their mask.  Where the steps take one launch each and a wait inside gave up, everything from the pending token on is done
+// The steps in one launch know whole layers only.
+bool whole_layers(const ssd_ctx* c, const uint8_t* sub)
+{
+    for (int l = 0; sub && l < c->D.L; l++)
+        if (!sub[2 * l] != !sub[2 * l + 1]) return false;
+    return true;
+}
+
+// Runs the launch sequence of a call of single-row steps or of a verification and waits for its results.  fits: it can take
+// one launch per step.  Where it does and a wait inside gave up, everything from the pending token on is done
 // again by the launches per matrix (nothing was committed, cache rows of uncommitted positions are written anew).
 template <typename F>
-int run_steps(ssd_ctx* c, const std::string& key, int plan_ctx, const uint8_t* sub, F&& body)
+int run_steps(ssd_ctx* c, const std::string& key, bool fits, F&& body)
 {
-    bool whole = true;   // the step in one launch knows whole layers only
-    for (int l = 0; sub && l < c->D.L; l++) whole = whole && !sub[2 * l] == !sub[2 * l + 1];
     {
-        StepSlot slot(c, c->step_blocks > 0 && c->step_table && !c->step_off && whole && c->prof_kid < 0 && step_plan_fits(c->D, plan_ctx, c->step_blocks));
+        StepSlot slot(c, c->step_blocks > 0 && c->step_table && !c->step_off && fits && c->prof_kid < 0);
         if (c->step_now) {
             c->pinned[PIN_STEP] = 0;
             int rc = run_sequence(c, "P" + key, body);
@@ -909,7 +932,7 @@ int ssd_decode(ssd_ctx* c, int32_t* token_out)
     if (c->n + 1 > c->D.max_seq) return fail(c, SSD_ECAPACITY, "sequence would exceed max_seq");
     // pending token sits in tok slot 0; its successor is written to slot 1, then promoted
     std::string key = "D|" + std::to_string(attention_splits(c->D, c->n, 1));
-    int rc = run_steps(c, key, c->n, nullptr, [&]() { return forward_single(c, nullptr, 0, 1, 0, c->n, 0, STEP_COMMIT); });
+    int rc = run_steps(c, key, step_plan_fits(c->D, c->n, c->step_blocks), [&]() { return forward_single(c, nullptr, 0, 1, 0, c->n, 0, STEP_COMMIT); });
     if (rc) return rc;
     *token_out = c->pinned[PIN_TOK + 1];
     c->n += 1;
@@ -936,7 +959,7 @@ static int draft_fixed(ssd_ctx* c, const std::vector<uint8_t>& sub, int k, int32
     if (c->state != ST_IDLE) return fail(c, SSD_ESTATE, "draft_step needs a prefilled sequence with no draft in flight");
     if (k > c->cfg.max_k) return fail(c, SSD_ECAPACITY, "k exceeds max_k");
     if (c->n + k > c->D.max_seq) return fail(c, SSD_ECAPACITY, "draft + verification would exceed max_seq");
-    int rc = run_steps(c, draft_key(c->D, sub, c->n, k), draft_plan_ctx(c->n, k), sub.data(), [&]() {
+    int rc = run_steps(c, draft_key(c->D, sub, c->n, k), whole_layers(c, sub.data()) && step_plan_fits(c->D, draft_plan_ctx(c->n, k), c->step_blocks), [&]() {
         for (int i = 0; i < k; i++) {
             int r = forward_single(c, sub.data(), i, i + 1, i, draft_plan_ctx(c->n, k), i, (i ? STEP_CHAINED : 0) | (i + 1 < k ? STEP_CHAIN_NEXT : 0));
             if (r) return r;
@@ -990,7 +1013,7 @@ int ssd_draft_adaptive(ssd_ctx* c, const uint8_t* skip_mask, int k_max, float ga
     while (k < k_max) {
         // one draft step per submission: the host reads the step's max-probability before deciding on the next
         const int i = k;
-        int rc = run_steps(c, adaptive_key(c->D, sub, c->n, k_max, i), draft_plan_ctx(c->n, k_max), sub.data(),
+        int rc = run_steps(c, adaptive_key(c->D, sub, c->n, k_max, i), whole_layers(c, sub.data()) && step_plan_fits(c->D, draft_plan_ctx(c->n, k_max), c->step_blocks),
                            [&]() { return forward_single(c, sub.data(), i, i + 1, i, draft_plan_ctx(c->n, k_max), i, 0); });
         if (rc) return rc;
         const float p = c->pin_f(PIN_PROB)[i];
@@ -1017,9 +1040,9 @@ int ssd_verify(ssd_ctx* c, const int32_t* draft, int k, int32_t* target_out)
         if (draft[i] < 0 || draft[i] >= c->D.V) return fail(c, SSD_EINVAL, "draft token id out of range");
     for (int i = 0; i < k; i++) c->pinned[PIN_VTOK + 1 + i] = draft[i];
     std::string key = "V|" + std::to_string(k) + "|" + std::to_string(attention_splits(c->D, c->n + k, k + 1));
-    int rc = run_sequence(c, key, [&]() { return forward_rows(c, k + 1, 0, c->n - 1, true, Tokens{c->pinned + PIN_VTOK, c->small_i() + SM_TOK}); });
-    if (rc) return rc;
-    rc = sync_results(c);
+    const Tokens tok = {c->pinned + PIN_VTOK, c->small_i() + SM_TOK};
+    const bool fits = rows_step_fits(c->D, k + 1, c->n + k, c->step_blocks) && (size_t)2 * (k + 1) * c->step_blocks <= c->lay.part_floats;
+    int rc = run_steps(c, key, fits, [&]() { return c->step_now ? verify_fused(c, k + 1, tok) : forward_rows(c, k + 1, 0, c->n - 1, true, tok); });
     if (rc) return rc;
     memcpy(target_out, c->pinned + PIN_TARGET, sizeof(int32_t) * (k + 1));
     c->state = ST_VERIFIED;

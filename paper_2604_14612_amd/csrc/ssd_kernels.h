@@ -111,6 +111,20 @@ struct StepLaunch {
 };
 hipError_t step_fused(const Dims& D, const StepLaunch& a, const StepOut& o, hipStream_t s);
 
+// The M rows of a verification in one launch and their greedy tokens in a second one: x holds the embedding rows; K and V rows
+// *pos_dev .. + M - 1, taps [M][L][2][d], logits [M][V] are written.  Blocks, scratch, waits and *err_host as above.
+bool rows_step_fits(const Dims& D, int M, int ctx, int blocks);   // ctx: positions the last row sees
+struct RowsStepLaunch {
+    int blocks; void* scratch;
+    int M, ctx;
+    const void* lm_head; const float* final_norm;
+    const float* x; const float* rope; const int* pos_dev;   // rope: the whole table
+    void* kv; size_t kv_layer;
+    float* logits; float* taps; float2* vmax; float clamp;   // vmax: [M][blocks]
+    int32_t* tok_out; int32_t* tok_host; int32_t* err_host;
+};
+hipError_t rows_step_fused(const Dims& D, const RowsStepLaunch& a, hipStream_t s);
+
 // ---- multi-row (verify / prefill / confidence) path ------------------------------------------
 // out[r][:] = rmsnorm(in[r][:], gain) for r < M   (rows of length K)
 hipError_t rmsnorm_rows(const float* in, const float* gain, int M, int K, float eps, float* out, hipStream_t s);
@@ -229,7 +243,8 @@ hipError_t vocab_reduce(const float* logits, int M, int V, float clamp, float ep
                         hipStream_t s);
 
 // tok_out[r] = tok_host[r] (host-pinned) = lowest column of the largest clamped logit of row r, from the vmax records of a rows_fused LM-head launch
-hipError_t argmax_tiles(const float2* vmax, int M, int n_tiles, int32_t* tok_out, int32_t* tok_host, hipStream_t s);
+hipError_t argmax_tiles(const float2* vmax, int M, int n_tiles, int32_t* tok_out, int32_t* tok_host, hipStream_t s, unsigned* step_ctrl = nullptr,
+                        unsigned step_hops = 0, int32_t* step_err_host = nullptr);
 // Confidence, max-probability and arg-max of M rows as vocab_reduce gives them, cut along the vocabulary where the rows
 // alone leave the chip idle; scratch (may be null: never cut) takes 24 bytes per row and slice.
 hipError_t vocab_confidence(const float* logits, int M, int V, float clamp, float eps, int32_t* argmax_out, float* maxprob_out,

@@ -3778,6 +3778,39 @@ __device__ __forceinline__ void mail_put(unsigned long long* p, float v, unsigne
 {
     __hip_atomic_store(p, ((unsigned long long)tag << 32) | __float_as_uint(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+// Waits until the word pairs at pair[0..N) below n_pairs all carry `tag` (those at n_pairs and above count as there); v
+// receives their values.  Called by whole waves.  A word is written by one 8-byte store, so the halves of a 16-byte load are
+// each whole.
+template <int N>
+__device__ __forceinline__ void mail_take(const int (&pair)[N], float2 (&v)[N], unsigned long long* base, int n_pairs, unsigned tag, unsigned* ctrl,
+                                          bool& alive, long wait_ticks, bool pause = true)
+{
+    const auto r = __builtin_amdgcn_make_buffer_rsrc(base, 0, n_pairs * 16, 0x00020000);
+    u32x4_t w[N];
+    int spins = 0;
+    long t0 = 0;
+    if (pause) __builtin_amdgcn_s_sleep(ST_FIRST_POLL);
+    while (true) {
+        bool ok = true;
+        asm volatile("" ::: "memory");   // the words change under the loop
+#pragma unroll
+        for (int u = 0; u < N; u++) w[u] = __builtin_amdgcn_raw_buffer_load_b128(r, pair[u] * 16, 0, 16 /* sc1: device scope */);
+#pragma unroll
+        for (int u = 0; u < N; u++) ok = ok && ((w[u].y == tag && w[u].w == tag) || pair[u] >= n_pairs);
+        if (__all(ok) || !alive) break;
+        if ((++spins & 63) == 0) {
+            const long now = wall_clock64();
+            if (t0 == 0) t0 = now;
+            if (__hip_atomic_load(ctrl + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) alive = false;
+            else if (now - t0 > wait_ticks) {
+                __hip_atomic_store(ctrl + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                alive = false;
+            }
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < N; u++) v[u] = make_float2(__uint_as_float(w[u].x), __uint_as_float(w[u].z));
+}
 // next set bit of a 128-bit mask (low, high word) at l or above, -1 if there is none
 __device__ __forceinline__ int next_layer(uint64_t lo, uint64_t hi, int l)
 {
@@ -3936,36 +3969,8 @@ __global__ __launch_bounds__(ST_THREADS) void step_kernel(StepP p)
     };
     auto load_d = [&](int l) { row_load(bd, CF, ptr(max(l, 0), P_D), xr0, f, l >= 0 && has_x); };
 
-    // Waits until the word pairs at pair[0..N) below n_pairs all carry `tag` (those at n_pairs and above count as there); v
-    // receives their values.  Called by whole waves.  A word is written by one 8-byte store, so the halves of a 16-byte load are
-    // each whole.
     auto mail_wait = [&](const auto& pair, auto& v, unsigned long long* base, int n_pairs) {
-        constexpr int N = sizeof(v) / sizeof(v[0]);
-        const auto r = __builtin_amdgcn_make_buffer_rsrc(base, 0, n_pairs * 16, 0x00020000);
-        u32x4_t w[N];
-        int spins = 0;
-        long t0 = 0;
-        __builtin_amdgcn_s_sleep(ST_FIRST_POLL);
-        while (true) {
-            bool ok = true;
-            asm volatile("" ::: "memory");   // the words change under the loop
-#pragma unroll
-            for (int u = 0; u < N; u++) w[u] = __builtin_amdgcn_raw_buffer_load_b128(r, pair[u] * 16, 0, 16 /* sc1: device scope */);
-#pragma unroll
-            for (int u = 0; u < N; u++) ok = ok && ((w[u].y == tag && w[u].w == tag) || pair[u] >= n_pairs);
-            if (__all(ok) || !alive) break;
-            if ((++spins & 63) == 0) {
-                const long now = wall_clock64();
-                if (t0 == 0) t0 = now;
-                if (__hip_atomic_load(ctrl + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) alive = false;
-                else if (now - t0 > p.wait_ticks) {
-                    __hip_atomic_store(ctrl + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    alive = false;
-                }
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < N; u++) v[u] = make_float2(__uint_as_float(w[u].x), __uint_as_float(w[u].z));
+        mail_take(pair, v, base, n_pairs, tag, ctrl, alive, p.wait_ticks);
     };
 
     int buf = 0, xpar = 0;
@@ -4276,15 +4281,532 @@ __global__ __launch_bounds__(ST_THREADS) void step_kernel(StepP p)
     }
 }
 
+// ---- whole verifications of narrow models in one launch -------------------------------------------------------------------
+// The step above for the k + 1 rows of a verification, and for the same reason: the six launches of a layer of 26 MB take 35 us
+// (5 rows, the gaps between them not counted), most of it their fixed time.  Same blocks, same owners, same hand-overs; what is different:
+//  * every word exists once per row, so a hand-over moves R times the bytes (5 rows of 2816 activations: 28 MB over all blocks);
+//  * a wave multiplies its weights with all rows: a vector of activations is read from LDS once for all the weight rows a wave
+//    owns in a stage, and R (3, 5 or 9: the smallest that holds the rows) is part of the kernel so that these reads are
+//    independent; rows past M are zeros that nobody hands over;
+//  * attention is one block per head and row over all positions, without partials: a fold would be another hand-over, of more
+//    bytes.  The position's own K and V and those of the rows before it come by hand-over, the earlier ones from the cache.
+// fp32 arithmetic throughout, in the order of the single-row step: a draft of the full model and its verification agree in
+// every bit.
+struct RowsStepP {
+    const StepWeights* layers; int L, M;
+    const void* lm_head; const float* final_norm;
+    const float* x; const float* rope; const int* pos_dev;
+    char* kv; size_t kv_layer;  // cache, bytes of K (or V) of one layer
+    float* logits; float* taps; size_t tap_ld; float2* vmax; float clamp;
+    unsigned* ctrl; unsigned long long* mail; RowsMail off;
+    int d, dq, dkv, f, V, H, Hkv, max_seq; float eps;
+    long wait_ticks;
+};
+
+// o[j][r] = weight row j (C vectors of this lane) . row r in LDS, over the wave
+template <typename WT, int J, int C, int R>
+__device__ __forceinline__ void rows_dots(const u32x4_t (&w)[J][C], const float* xs, int lane, int K, float (&o)[J][R])
+{
+    constexpr int VEC = Elem<WT>::VEC, CH = 64 * VEC, XF = ST_CF * CH;
+#pragma unroll
+    for (int j = 0; j < J; j++)
+#pragma unroll
+        for (int r = 0; r < R; r++) o[j][r] = 0.f;
+#pragma unroll
+    for (int c = 0; c < C; c++) {
+        if (c * CH + lane * VEC < K) {
+            float wf[J][VEC];
+#pragma unroll
+            for (int j = 0; j < J; j++) aw_unpack<WT>(w[j][c], wf[j]);
+#pragma unroll
+            for (int r = 0; r < R; r++) {
+                const float* x = xs + r * XF + c * CH + lane * 4;
+                float xv[8];
+                *reinterpret_cast<float4*>(xv) = *reinterpret_cast<const float4*>(x);
+                if (VEC == 8) *reinterpret_cast<float4*>(xv + 4) = *reinterpret_cast<const float4*>(x + GV_XB);
+#pragma unroll
+                for (int j = 0; j < J; j++)
+#pragma unroll
+                    for (int e = 0; e < VEC; e++) o[j][r] = fmaf(wf[j][e], xv[e], o[j][r]);
+            }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < J; j++)
+#pragma unroll
+        for (int r = 0; r < R; r++) o[j][r] = wave_sum_fast(o[j][r]);
+}
+
+template <typename WT, typename KT, int HD, int R>
+__global__ __launch_bounds__(ST_THREADS) void rows_step_kernel(RowsStepP p)
+{
+    constexpr int VEC = Elem<WT>::VEC, CH = 64 * VEC, CD = ST_CD, CF = ST_CF, XF = CF * CH;
+    constexpr int EPV = 16 / (int)sizeof(KT), LPP = HD / EPV, PPL = 64 / LPP, NL = 8, PASS = NL * ST_WAVES * PPL;
+    constexpr int NX = (CD * CH + 2 * ST_THREADS - 1) / (2 * ST_THREADS), NF = (XF + 2 * ST_THREADS - 1) / (2 * ST_THREADS);   // pairs of elements of a d- or dq-, of an f-vector per thread
+    constexpr int NQ = ((2 * R + 1) * HD / 2 + ST_THREADS - 1) / ST_THREADS;
+    extern __shared__ __align__(16) float st_sm[];
+    float* xs = st_sm;                                                   // [R][XF] input rows of a stage
+    const unsigned long long* tab = reinterpret_cast<const unsigned long long*>(st_sm + R * XF);   // weight pointers [L][9]
+    __shared__ float red[R * ST_WAVES];
+    __shared__ float rope[R * HD];
+    __shared__ __align__(16) float qs[(2 * R + 1) * HD];                 // query (scaled), new keys, new values of the head
+    __shared__ float outs[2 * ST_WAVES * R];                             // outputs of the block, [unit][row]
+    __shared__ float wacc[ST_WAVES * HD], wml[ST_WAVES * 2];
+    static_assert(ST_GU <= 2 && 2 * ST_WAVES * R <= ST_THREADS, "one thread per output");
+    int tid = threadIdx.x, lane = tid & 63;
+    auto fresh = [&]() { asm volatile("" : "+v"(tid)); lane = tid & 63; };   // as above
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int b = blockIdx.x, NB = gridDim.x;
+    const int d = p.d, dq = p.dq, dkv = p.dkv, f = p.f, M = p.M, nqkv = dq + 2 * dkv;
+    unsigned* ctrl = p.ctrl;
+    unsigned long long* const mx = p.mail + p.off.x;
+    unsigned long long* const mqkv = p.mail + p.off.qkv;
+    unsigned long long* const matt = p.mail + p.off.att;
+    unsigned long long* const mact = p.mail + p.off.act;
+
+    const int p0 = p.pos_dev[0];
+    {
+        unsigned long long* t = reinterpret_cast<unsigned long long*>(st_sm + R * XF);
+        const unsigned long long* src = reinterpret_cast<const unsigned long long*>(p.layers);
+        for (int i = tid; i < p.L * 9; i += ST_THREADS) t[i] = src[i];
+        for (int i = tid; i < M * HD; i += ST_THREADS) rope[i] = p.rope[(size_t)p0 * HD + i];
+    }
+    unsigned tag = ctrl[0];
+    bool alive = ctrl[1] == 0;
+    // what this block and wave own, as above
+    const int xb0 = step_begin(d, b, NB), xb1 = step_begin(d, b + 1, NB), xr0 = xb0 + wave;
+    const bool has_x = xr0 < xb1;
+    const int nqp = nqkv / 2;
+    const int qp = step_begin(nqp, b, NB) + wave;
+    const bool has_q = qp < step_begin(nqp, b + 1, NB);
+    const int gb0 = step_begin(f, b, NB), gp0 = gb0 + wave, gp_end = step_begin(f, b + 1, NB);
+    const int lp_end = step_begin(p.V / 2, b + 1, NB), lp0 = step_begin(p.V / 2, b, NB) + wave;
+    auto qkv_rows = [&](int pair, int& m, int& r0, int& r1) {
+        const int j = 2 * pair;
+        if (j < dq + dkv) {
+            m = j < dq ? 0 : 1;
+            const int jj = m ? j - dq : j, head = jj / HD, i = (jj % HD) >> 1;
+            r0 = head * HD + i; r1 = r0 + HD / 2;
+        } else {
+            m = 2; r0 = j - dq - dkv; r1 = r0 + 1;
+        }
+    };
+    int qm, qr0, qr1;
+    qkv_rows(qp, qm, qr0, qr1);
+    float xr[R];                                // residual values of this wave's row
+#pragma unroll
+    for (int r = 0; r < R; r++) xr[r] = has_x && r < M ? p.x[(size_t)r * d + xr0] : 0.f;
+    __syncthreads();
+
+    auto ptr = [&](int l, int which) -> const char* {   // uniform: scalar registers
+        const unsigned long long v = tab[l * 9 + which];
+        return reinterpret_cast<const char*>(((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32) |
+                                             (unsigned)__builtin_amdgcn_readfirstlane((int)v));
+    };
+    enum { P_AN = 0, P_Q, P_K, P_V, P_O, P_MN, P_G, P_U, P_D };
+    // weights of the next layer: loads are unconditional, as above
+    u32x4_t bq[2][CD], bo[1][CD], bg[2 * ST_GU][CD], bd[1][CF];   // bg: gate, up, gate, up
+    auto row_load = [&](u32x4_t* w, int C, const char* m, size_t row, int K, bool ok) {
+        auto r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(m) + row * K * sizeof(WT), 0, ok ? K * (int)sizeof(WT) : 0, 0x00020000);
+#pragma unroll
+        for (int c = 0; c < CF; c++)
+            if (c < C) w[c] = __builtin_amdgcn_raw_buffer_load_b128(r, (c * CH + lane * VEC) * (int)sizeof(WT), 0, 2 /* nt */);
+    };
+    float2 gq[NX], gg[NX];                      // norm gains of this thread's elements
+    auto gain = [&](float2 (&o)[NX], const char* g) {
+        const auto r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(g), 0, d * 4, 0x00020000);
+#pragma unroll
+        for (int u = 0; u < NX; u++) {
+            const auto w = __builtin_amdgcn_raw_buffer_load_b64(r, (u * ST_THREADS + tid) * 8, 0, 0);
+            o[u] = make_float2(__uint_as_float(w[0]), __uint_as_float(w[1]));
+        }
+    };
+    const char* const lh = static_cast<const char*>(p.lm_head);
+    auto load_qkv = [&](int l) {                // of layer l, or, l == L, the first pair of LM-head rows
+        const bool lm = l >= p.L;
+        const char* m = lm ? lh : ptr(l, P_Q + qm);
+        const bool ok = lm ? lp0 < lp_end : has_q;
+        row_load(bq[0], CD, m, lm ? (size_t)lp0 * 2 : (size_t)qr0, d, ok);
+        row_load(bq[1], CD, m, lm ? (size_t)lp0 * 2 + 1 : (size_t)qr1, d, ok);
+        gain(gq, lm ? reinterpret_cast<const char*>(p.final_norm) : ptr(l, P_AN));
+    };
+    auto load_o = [&](int l) { row_load(bo[0], CD, ptr(min(l, p.L - 1), P_O), xr0, dq, l < p.L && has_x); };
+    auto load_gu = [&](int l) {                 // or the next pairs of LM-head rows
+        const bool lm = l >= p.L;
+        const int t = min(l, p.L - 1);
+        const char* wg = lm ? lh : ptr(t, P_G);
+        const char* wu = lm ? lh : ptr(t, P_U);
+#pragma unroll
+        for (int u = 0; u < ST_GU; u++) {
+            const int pair = lp0 + (u + 1) * ST_WAVES, gp = gp0 + u * ST_WAVES;
+            const bool ok = lm ? pair < lp_end : gp < gp_end;
+            row_load(bg[2 * u], CD, wg, lm ? (size_t)pair * 2 : (size_t)gp, d, ok);
+            row_load(bg[2 * u + 1], CD, wu, lm ? (size_t)pair * 2 + 1 : (size_t)gp, d, ok);
+        }
+        gain(gg, ptr(t, P_MN));
+    };
+    auto load_d = [&](int l) { row_load(bd[0], CF, ptr(min(l, p.L - 1), P_D), xr0, f, l < p.L && has_x); };
+
+    int xpar = 0;
+    bool first = true;                          // the residual rows are still the embedding rows in memory
+    // pair u of this thread of a row of n elements into LDS
+    auto put_row = [&](int r, int u, float2 v, int n) {
+        const int i = 2 * (u * ST_THREADS + tid);
+        if (i < n) *reinterpret_cast<float2*>(xs + r * XF + gv_xpos<VEC>(i)) = v;
+    };
+    // residual rows into LDS, times the gain; sc = their RMS scales
+    auto take_x = [&](const float2 (&gain)[NX], float (&sc)[R]) {
+        fresh();
+        float2 v[R * NX];
+        if (first) {
+#pragma unroll
+            for (int r = 0; r < R; r++)
+#pragma unroll
+                for (int u = 0; u < NX; u++) {
+                    const int i = 2 * (u * ST_THREADS + tid);
+                    v[r * NX + u] = r < M && i < d ? *reinterpret_cast<const float2*>(p.x + (size_t)r * d + i) : make_float2(0.f, 0.f);
+                }
+        } else {
+            const int np = M * (d / 2);
+            int pr[R * NX];
+#pragma unroll
+            for (int r = 0; r < R; r++)
+#pragma unroll
+                for (int u = 0; u < NX; u++) {
+                    const int i = u * ST_THREADS + tid;
+                    pr[r * NX + u] = r < M && 2 * i < d ? r * (d / 2) + i : np;
+                }
+            mail_take(pr, v, mx + (size_t)xpar * RS_ROWS * d, np, tag, ctrl, alive, p.wait_ticks);
+        }
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            float ss = 0.f;
+#pragma unroll
+            for (int u = 0; u < NX; u++) {
+                const float2 x = v[r * NX + u];
+                put_row(r, u, make_float2(x.x * gain[u].x, x.y * gain[u].y), d);
+                ss += x.x * x.x + x.y * x.y;
+            }
+            ss = wave_sum_fast(ss);
+            if (lane == 0) red[r * ST_WAVES + wave] = ss;
+        }
+        lds_barrier();
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            float t = 0.f;
+#pragma unroll
+            for (int i = 0; i < ST_WAVES; i++) t += red[r * ST_WAVES + i];
+            sc[r] = 1.0f / sqrtf(t / (float)d + p.eps);
+        }
+    };
+    // the block's share of the residual rows to everybody, and into the taps
+    auto give_x = [&](int l, int which) {
+        tag++; xpar ^= 1; first = false;
+        if (lane == 0) {
+#pragma unroll
+            for (int r = 0; r < R; r++) outs[wave * R + r] = xr[r];
+        }
+        lds_barrier();
+        const int i = tid / R, r = tid % R;
+        if (i < xb1 - xb0 && r < M) {
+            const float v = outs[tid];
+            mail_put(mx + ((size_t)xpar * RS_ROWS + r) * d + xb0 + i, v, tag);
+            p.taps[r * p.tap_ld + (size_t)(2 * l + which) * d + xb0 + i] = v;
+        }
+    };
+
+    load_qkv(0); load_o(0); load_gu(0); load_d(0);
+    for (int l = 0; l < p.L; l++) {
+        KT* kc = reinterpret_cast<KT*>(p.kv + (size_t)(2 * l) * p.kv_layer);
+        KT* vc = reinterpret_cast<KT*>(p.kv + (size_t)(2 * l + 1) * p.kv_layer);
+        float sc[R];
+        // ---- q, k, v ----
+        {
+            take_x(gq, sc);
+            tag++;
+            float o[2][R];
+            rows_dots<WT>(bq, xs, lane, d, o);
+            const int i = qr0 % HD;
+#pragma unroll
+            for (int r = 0; r < R; r++) {
+                const float a = o[0][r] * sc[r], c = o[1][r] * sc[r];
+                float o0 = a, o1 = c;
+                if (qm < 2) {
+                    const float cs = rope[r * HD + 2 * i], sn = rope[r * HD + 2 * i + 1];   // (rows past M: nobody takes the result)
+                    o0 = a * cs - c * sn; o1 = c * cs + a * sn;
+                }
+                if (lane == 0) { outs[wave * R + r] = o0; outs[(ST_WAVES + wave) * R + r] = o1; }
+            }
+            lds_barrier();
+            const int unit = tid / R, r = tid % R, pr = step_begin(nqp, b, NB) + unit % ST_WAVES;
+            if (unit < 2 * ST_WAVES && r < M && pr < step_begin(nqp, b + 1, NB)) {
+                int m, r0, r1;
+                qkv_rows(pr, m, r0, r1);
+                const int row = unit < ST_WAVES ? r0 : r1;
+                float v = outs[tid];
+                if (m > 0) {
+                    KT* c = (m == 1 ? kc : vc) + ((size_t)(row / HD) * p.max_seq + p0 + r) * HD;
+                    Elem<KT>::put(c, row % HD, v);
+                    if (sizeof(KT) == 2) { KT t; Elem<KT>::put(&t, 0, v); v = Elem<KT>::get(&t, 0); }   // attention sees what the cache holds
+                }
+                mail_put(mqkv + (size_t)r * nqkv + (m == 0 ? 0 : m == 1 ? dq : dq + dkv) + row, v, tag);
+            }
+        }
+        // ---- attention: one block per query head and row; the blocks of a head run on as few XCDs as the head count allows ----
+        if (b < p.H * M) {
+            fresh();
+            const int head = b % p.H, row = b / p.H, kvh = head / (p.H / p.Hkv);
+            const int n = p0 + row + 1, jlast = max(p0 - 1, 0);   // positions the row sees; the last one that is in the cache
+            const int n_pass = (n + PASS - 1) / PASS;
+            const int seg = lane / LPP, sl = (lane % LPP) * EPV;
+            const KT* kb = kc + (size_t)kvh * p.max_seq * HD + sl;
+            const KT* vb = vc + (size_t)kvh * p.max_seq * HD + sl;
+            u32x4_t kr[NL], vr[NL];
+            auto issue = [&](int pass) {
+#pragma unroll
+                for (int t = 0; t < NL; t++) {
+                    const int j = min(((pass * NL + t) * ST_WAVES + wave) * PPL + seg, jlast);
+                    kr[t] = *reinterpret_cast<const u32x4_t*>(kb + (size_t)j * HD);
+                    vr[t] = *reinterpret_cast<const u32x4_t*>(vb + (size_t)j * HD);
+                }
+            };
+            issue(0);
+            {   // the query, then the keys and the values of rows 0 .. row
+                const int units = 2 * row + 3, np = M * nqkv / 2;
+                const float qsc = 1.0f / sqrtf((float)HD);
+                int pr[NQ];
+                float2 v[NQ];
+#pragma unroll
+                for (int u = 0; u < NQ; u++) {
+                    const int i = u * ST_THREADS + tid, unit = i / (HD / 2), e = i % (HD / 2);
+                    const int rr = unit == 0 ? row : unit <= row + 1 ? unit - 1 : unit - row - 2;
+                    const int at = unit == 0 ? head * HD : unit <= row + 1 ? dq + kvh * HD : dq + dkv + kvh * HD;
+                    pr[u] = unit < units ? (rr * nqkv + at) / 2 + e : np;
+                }
+                mail_take(pr, v, mqkv, np, tag, ctrl, alive, p.wait_ticks);
+#pragma unroll
+                for (int u = 0; u < NQ; u++) {
+                    const int i = u * ST_THREADS + tid, unit = i / (HD / 2);
+                    const float s = unit == 0 ? qsc : 1.0f;
+                    if (unit < units) *reinterpret_cast<float2*>(qs + 2 * i) = make_float2(v[u].x * s, v[u].y * s);
+                }
+            }
+            lds_barrier();
+            float m = -INFINITY, lsum = 0.f, acc[EPV];
+#pragma unroll
+            for (int u = 0; u < EPV; u++) acc[u] = 0.f;
+            for (int pass = 0; pass < n_pass; pass++) {
+                if (pass) issue(pass);
+                float s[NL];
+#pragma unroll
+                for (int t = 0; t < NL; t++) {
+                    const int j = ((pass * NL + t) * ST_WAVES + wave) * PPL + seg;
+                    float kf[EPV];
+                    aw_unpack<KT>(kr[t], kf);
+                    if (j >= p0 && j < n) {
+#pragma unroll
+                        for (int u = 0; u < EPV; u++) kf[u] = qs[(1 + j - p0) * HD + sl + u];
+                    }
+                    float a = 0.f;
+#pragma unroll
+                    for (int u = 0; u < EPV; u++) a = fmaf(kf[u], qs[sl + u], a);
+                    a = aw_seg_sum<LPP>(a);
+                    s[t] = j < n ? a : -INFINITY;
+                }
+                float mt = s[0];
+#pragma unroll
+                for (int t = 1; t < NL; t++) mt = fmaxf(mt, s[t]);
+                mt = seg_max_fast<LPP>(mt);
+                const float mn = fmaxf(m, mt);
+                const bool live = mn > -INFINITY;
+                const float c = live ? __expf(m - mn) : 1.0f;
+                lsum *= c;
+#pragma unroll
+                for (int u = 0; u < EPV; u++) acc[u] *= c;
+                m = mn;
+#pragma unroll
+                for (int t = 0; t < NL; t++) {
+                    const int j = ((pass * NL + t) * ST_WAVES + wave) * PPL + seg;
+                    const float e = live ? __expf(s[t] - mn) : 0.f;
+                    lsum += e;
+                    float vf[EPV];
+                    aw_unpack<KT>(j < p0 ? vr[t] : u32x4_t{0u, 0u, 0u, 0u}, vf);   // rows from the position on may hold anything
+                    if (j >= p0 && j < n) {
+#pragma unroll
+                        for (int u = 0; u < EPV; u++) vf[u] = qs[(2 + row + j - p0) * HD + sl + u];
+                    }
+#pragma unroll
+                    for (int u = 0; u < EPV; u++) acc[u] = fmaf(e, vf[u], acc[u]);
+                }
+            }
+            lsum = seg_sum_fast<LPP>(lsum);
+#pragma unroll
+            for (int u = 0; u < EPV; u++) {
+                acc[u] = seg_sum_fast<LPP>(acc[u]);
+                if (seg == 0) wacc[wave * HD + sl + u] = acc[u];
+            }
+            if (lane == 0) { wml[wave * 2] = m; wml[wave * 2 + 1] = lsum; }
+            lds_barrier();
+            if (tid < HD) {
+                float gm = -INFINITY, num = 0.f, den = 0.f;
+#pragma unroll
+                for (int w = 0; w < ST_WAVES; w++) gm = fmaxf(gm, wml[w * 2]);
+#pragma unroll
+                for (int w = 0; w < ST_WAVES; w++) {
+                    const float mw = wml[w * 2], c = mw > -INFINITY ? __expf(mw - gm) : 0.f;
+                    num = fmaf(c, wacc[w * HD + tid], num);
+                    den = fmaf(c, wml[w * 2 + 1], den);
+                }
+                mail_put(matt + (size_t)row * dq + head * HD + tid, num / den, tag + 1);
+            }
+        }
+        // ---- output projection ----
+        {
+            fresh();
+            tag++;
+            const int np = M * (dq / 2);
+            int pr[R * NX];
+            float2 v[R * NX];
+#pragma unroll
+            for (int r = 0; r < R; r++)
+#pragma unroll
+                for (int u = 0; u < NX; u++) {
+                    const int i = u * ST_THREADS + tid;
+                    pr[r * NX + u] = r < M && 2 * i < dq ? r * (dq / 2) + i : np;
+                }
+            mail_take(pr, v, matt, np, tag, ctrl, alive, p.wait_ticks);
+            load_qkv(l + 1);
+#pragma unroll
+            for (int r = 0; r < R; r++)
+#pragma unroll
+                for (int u = 0; u < NX; u++) put_row(r, u, v[r * NX + u], dq);
+            lds_barrier();
+            float o[1][R];
+            rows_dots<WT>(bo, xs, lane, dq, o);
+#pragma unroll
+            for (int r = 0; r < R; r++) xr[r] += o[0][r];
+            give_x(l, 0);
+            fresh();
+            load_o(l + 1);
+        }
+        // ---- gate and up ----
+        {
+            take_x(gg, sc);
+            tag++;
+            float o[2 * ST_GU][R];
+            rows_dots<WT>(bg, xs, lane, d, o);
+#pragma unroll
+            for (int u = 0; u < ST_GU; u++)
+#pragma unroll
+                for (int r = 0; r < R; r++) {
+                    const float a = o[2 * u][r] * sc[r], c = o[2 * u + 1][r] * sc[r];
+                    if (lane == 0) outs[(u * ST_WAVES + wave) * R + r] = a / (1.0f + __expf(-a)) * c;
+                }
+            lds_barrier();
+            const int unit = tid / R, r = tid % R;
+            if (unit < gp_end - gb0 && r < M) mail_put(mact + (size_t)r * f + gb0 + unit, outs[tid], tag);
+        }
+        // ---- down projection ----
+        {
+            fresh();
+            constexpr int RG = R > 5 ? (R + 1) / 2 : R;   // rows per wait: what the registers hold
+            const int np = M * (f / 2);
+#pragma unroll
+            for (int r0 = 0; r0 < R; r0 += RG) {
+                int pr[RG * NF];
+                float2 v[RG * NF];
+#pragma unroll
+                for (int r = 0; r < RG; r++)
+#pragma unroll
+                    for (int u = 0; u < NF; u++) {
+                        const int i = u * ST_THREADS + tid;
+                        pr[r * NF + u] = r0 + r < M && 2 * i < f ? (r0 + r) * (f / 2) + i : np;
+                    }
+                mail_take(pr, v, mact, np, tag, ctrl, alive, p.wait_ticks, r0 == 0);
+#pragma unroll
+                for (int r = 0; r < RG; r++)
+#pragma unroll
+                    for (int u = 0; u < NF; u++)
+                        if (r0 + r < R) put_row(r0 + r, u, v[r * NF + u], f);
+            }
+            load_gu(l + 1);
+            lds_barrier();
+            float o[1][R];
+            rows_dots<WT>(bd, xs, lane, f, o);
+#pragma unroll
+            for (int r = 0; r < R; r++) xr[r] += o[0][r];
+            give_x(l, 1);
+            fresh();
+            load_d(l + 1);
+        }
+    }
+    // ---- LM head: the first three row pairs of every wave are in registers, a used one is replaced by the third next ----
+    float sc[R];
+    take_x(gq, sc);
+    float best[R];
+    int arg[R];
+#pragma unroll
+    for (int r = 0; r < R; r++) { best[r] = -INFINITY; arg[r] = 0x7fffffff; }
+    auto lm_rows = [&](const u32x4_t (&w)[2][CD], int pair) {
+        float o[2][R];
+        rows_dots<WT>(w, xs, lane, d, o);
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            const float a = o[0][r] * sc[r], c = o[1][r] * sc[r];
+            if (lane == 0 && r < M) *reinterpret_cast<float2*>(p.logits + (size_t)r * p.V + (size_t)pair * 2) = make_float2(a, c);
+            const float ca = fminf(fmaxf(a, -p.clamp), p.clamp), cc = fminf(fmaxf(c, -p.clamp), p.clamp);
+            if (ca > best[r]) { best[r] = ca; arg[r] = pair * 2; }         // ascending columns: the first of equal maxima stays
+            if (cc > best[r]) { best[r] = cc; arg[r] = pair * 2 + 1; }
+        }
+    };
+    auto lm_load = [&](u32x4_t* w0, u32x4_t* w1, int pair) {
+        row_load(w0, CD, lh, (size_t)pair * 2, d, pair < lp_end);
+        row_load(w1, CD, lh, (size_t)pair * 2 + 1, d, pair < lp_end);
+    };
+    constexpr int LR = (1 + ST_GU) * ST_WAVES;   // pairs that the block's registers hold
+    for (int i = lp0; i < lp_end; i += LR) {
+        lm_rows(bq, i);
+        lm_load(bq[0], bq[1], i + LR);
+#pragma unroll
+        for (int u = 0; u < ST_GU; u++) {
+            const int j = i + (u + 1) * ST_WAVES;
+            u32x4_t w[2][CD];
+#pragma unroll
+            for (int c = 0; c < CD; c++) { w[0][c] = bg[2 * u][c]; w[1][c] = bg[2 * u + 1][c]; }
+            if (j < lp_end) lm_rows(w, j);
+            lm_load(bg[2 * u], bg[2 * u + 1], j + LR);
+        }
+    }
+    __shared__ float2 vred[ST_WAVES * R];
+    if (lane == 0) {
+#pragma unroll
+        for (int r = 0; r < R; r++) vred[wave * R + r] = make_float2(best[r], __int_as_float(arg[r]));
+    }
+    lds_barrier();
+    if (tid < M) {
+        float2 a = vred[tid];
+        for (int w = 1; w < ST_WAVES; w++) {
+            const float2 e = vred[w * R + tid];
+            if (e.x > a.x || (e.x == a.x && __float_as_int(e.y) < __float_as_int(a.y))) a = e;
+        }
+        p.vmax[(size_t)tid * NB + b] = a;
+    }
+}
+
 static StepShape step_shape(const Dims& D) { return {D.d, D.dq, D.dkv, D.f, D.V, D.hd, D.H, D.Hkv, D.wt, D.kt}; }
 
 size_t step_scratch_bytes(const Dims& D)
 {
     const StepShape s = step_shape(D);
-    return step_blocks(s, ST_BLOCKS) ? step_mail(s).total * 8 + (size_t)D.L * sizeof(StepWeights) : 0;
+    return step_blocks(s, ST_BLOCKS) ? step_table_offset(D) + (size_t)D.L * sizeof(StepWeights) : 0;
 }
 
-size_t step_table_offset(const Dims& D) { return step_mail(step_shape(D)).total * 8; }
+// control words and words of the single-row step, words of the verification, weight table
+size_t step_table_offset(const Dims& D)
+{
+    const StepShape s = step_shape(D);
+    return (step_mail(s).total + rows_mail(s).total) * 8;
+}
 
 template <typename WT, typename KT>
 static const void* step_fn(const Dims& D)
@@ -4332,7 +4854,7 @@ hipError_t step_fused(const Dims& D, const StepLaunch& a, const StepOut& o, hipS
     StepP p = {};
     p.off = step_mail(step_shape(D));
     p.mail = static_cast<unsigned long long*>(a.scratch);
-    p.layers = reinterpret_cast<const StepWeights*>(p.mail + p.off.total); p.L = D.L;
+    p.layers = reinterpret_cast<const StepWeights*>(static_cast<char*>(a.scratch) + step_table_offset(D)); p.L = D.L;
     StepOut out = o;
     out.step_hops = 0;
     for (int l = 0; l < D.L; l++) {
@@ -4349,6 +4871,50 @@ hipError_t step_fused(const Dims& D, const StepLaunch& a, const StepOut& o, hipS
     hipError_t e = hipLaunchKernel(step_fn(D), dim3(a.blocks), dim3(ST_THREADS), args, step_lds_bytes(D), s);
     if (e != hipSuccess) return e;
     return step_finish(D, a.vstat, a.blocks, out, s);
+}
+
+template <typename WT, typename KT, int HD>
+static hipError_t rows_step_launch(const RowsStepP& p, int blocks, hipStream_t s)
+{
+    constexpr size_t XF = (size_t)ST_CF * 64 * Elem<WT>::VEC;
+    const int R = p.M <= 3 ? 3 : p.M <= 5 ? 5 : RS_ROWS;
+    const size_t lds = R * XF * sizeof(float) + (size_t)p.L * sizeof(StepWeights);
+    const void* fn = R == 3 ? (const void*)rows_step_kernel<WT, KT, HD, 3> : R == 5 ? (const void*)rows_step_kernel<WT, KT, HD, 5>
+                                                                                    : (const void*)rows_step_kernel<WT, KT, HD, RS_ROWS>;
+    static std::atomic<size_t> lds_limit[3];   // per instantiation
+    hipError_t e = ensure_lds(fn, lds, lds_limit[R == 3 ? 0 : R == 5 ? 1 : 2]);
+    if (e != hipSuccess) return e;
+    void* args[] = {const_cast<RowsStepP*>(&p)};
+    return hipLaunchKernel(fn, dim3(blocks), dim3(ST_THREADS), args, lds, s);
+}
+template <typename WT, typename KT>
+static hipError_t rows_step_launch(const Dims& D, const RowsStepP& p, int blocks, hipStream_t s)
+{
+    return D.hd == 64 ? rows_step_launch<WT, KT, 64>(p, blocks, s) : rows_step_launch<WT, KT, 128>(p, blocks, s);
+}
+
+bool rows_step_fits(const Dims& D, int M, int ctx, int blocks) { return ctx <= D.max_seq && rows_step_fits(step_shape(D), M, ctx, blocks); }
+
+hipError_t rows_step_fused(const Dims& D, const RowsStepLaunch& a, hipStream_t s)
+{
+    if (!rows_step_fits(D, a.M, a.ctx, a.blocks) || a.blocks != step_blocks(step_shape(D), a.blocks) || !a.tok_out || !a.tok_host || !a.err_host ||
+        !a.taps || !a.vmax) return hipErrorInvalidValue;
+    RowsStepP p = {};
+    p.ctrl = static_cast<unsigned*>(a.scratch);
+    p.mail = static_cast<unsigned long long*>(a.scratch) + step_mail(step_shape(D)).total;
+    p.off = rows_mail(step_shape(D));
+    p.layers = reinterpret_cast<const StepWeights*>(static_cast<char*>(a.scratch) + step_table_offset(D)); p.L = D.L; p.M = a.M;
+    p.lm_head = a.lm_head; p.final_norm = a.final_norm; p.x = a.x; p.rope = a.rope; p.pos_dev = a.pos_dev;
+    p.kv = static_cast<char*>(a.kv); p.kv_layer = a.kv_layer;
+    p.logits = a.logits; p.taps = a.taps; p.tap_ld = (size_t)D.L * 2 * D.d; p.vmax = a.vmax; p.clamp = a.clamp;
+    p.d = D.d; p.dq = D.dq; p.dkv = D.dkv; p.f = D.f; p.V = D.V; p.H = D.H; p.Hkv = D.Hkv; p.max_seq = D.max_seq; p.eps = D.eps;
+    p.wait_ticks = ST_WAIT_TICKS;
+    hipError_t e;
+    if (D.wt == WT_F32) e = rows_step_launch<float, float>(D, p, a.blocks, s);
+    else if (D.wt == WT_BF16) e = D.kt == WT_F32 ? rows_step_launch<uint16_t, float>(D, p, a.blocks, s) : rows_step_launch<uint16_t, uint16_t>(D, p, a.blocks, s);
+    else e = D.kt == WT_F32 ? rows_step_launch<f16_t, float>(D, p, a.blocks, s) : rows_step_launch<f16_t, f16_t>(D, p, a.blocks, s);
+    if (e != hipSuccess) return e;
+    return argmax_tiles(a.vmax, a.M, a.blocks, a.tok_out, a.tok_host, s, p.ctrl, 5 * D.L, a.err_host);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -4419,8 +4985,13 @@ __global__ __launch_bounds__(VR_THREADS) void vocab_reduce_kernel(const float* _
 // row, lowest column among equal maxima.  (Reading the logits back instead is one block walking 128-513 KB: 18.5 us at
 // 32 000 columns, 65 us at 128 256.)
 __global__ __launch_bounds__(VR_THREADS) void argmax_tiles_kernel(const float2* __restrict__ vmax, int n_tiles,
-                                                                  int32_t* __restrict__ tok_out, int32_t* __restrict__ tok_host)
+                                                                  int32_t* __restrict__ tok_out, int32_t* __restrict__ tok_host,
+                                                                  unsigned* step_ctrl, unsigned step_hops, int32_t* step_err_host)
 {
+    if (step_ctrl && blockIdx.x == 0 && threadIdx.x == 0) {   // end of a verification in one launch, as in step_finish_kernel
+        step_ctrl[0] += step_hops;
+        if (step_ctrl[1]) step_err_host[0] = 1;
+    }
     __shared__ float rv[16];
     __shared__ int ri[16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -4441,10 +5012,11 @@ __global__ __launch_bounds__(VR_THREADS) void argmax_tiles_kernel(const float2* 
         if (lane == 0) { tok_out[blockIdx.x] = mi; tok_host[blockIdx.x] = mi; }
     }
 }
-hipError_t argmax_tiles(const float2* vmax, int M, int n_tiles, int32_t* tok_out, int32_t* tok_host, hipStream_t s)
+hipError_t argmax_tiles(const float2* vmax, int M, int n_tiles, int32_t* tok_out, int32_t* tok_host, hipStream_t s, unsigned* step_ctrl,
+                        unsigned step_hops, int32_t* step_err_host)
 {
     if (M < 1 || n_tiles < 1 || !tok_host) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(argmax_tiles_kernel, dim3(M), dim3(VR_THREADS), 0, s, vmax, n_tiles, tok_out, tok_host);
+    hipLaunchKernelGGL(argmax_tiles_kernel, dim3(M), dim3(VR_THREADS), 0, s, vmax, n_tiles, tok_out, tok_host, step_ctrl, step_hops, step_err_host);
     return hipGetLastError();
 }
 

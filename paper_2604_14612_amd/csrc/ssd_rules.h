@@ -154,4 +154,29 @@ inline StepMail step_mail(const StepShape& s)
     return m;
 }
 
+// ---- whole verifications in one launch -----------------------------------------------------------------------------------
+// The same for the k + 1 rows of a verification, see rows_step_kernel.
+constexpr int RS_ROWS = 9;                     // rows that fit LDS beside each other (16-bit weights: 12 KB each) and the registers
+constexpr int RS_KEY_BYTES = 128 * 1024;       // K bytes of a head that one block walks
+
+// One block per head and row walks the whole context.
+inline bool rows_step_fits(const StepShape& s, int M, int ctx, int blocks)
+{
+    return M >= 2 && M <= RS_ROWS && ctx >= M && s.H * M <= blocks && (long)ctx * s.hd * (s.kt == 0 ? 4 : 2) <= RS_KEY_BYTES;
+}
+
+// Hand-over words, RS_ROWS of each: residual rows twice, q / k / v, attention output, FFN activations.
+struct RowsMail { size_t x, qkv, att, act, total; };
+inline RowsMail rows_mail(const StepShape& s)
+{
+    RowsMail m;
+    size_t o = 0;
+    m.x = o;    o += (size_t)2 * RS_ROWS * s.d;
+    m.qkv = o;  o += (size_t)RS_ROWS * (s.dq + 2 * s.dkv);
+    m.att = o;  o += (size_t)RS_ROWS * s.dq;
+    m.act = o;  o += (size_t)RS_ROWS * s.f;
+    m.total = o;
+    return m;
+}
+
 }  // namespace ssdk

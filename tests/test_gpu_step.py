@@ -34,6 +34,25 @@ def test_drafts_and_verification_at_the_limits(name, plen):
     assert st["unpinned_cycles"] <= 1 and st["draft_rows"] >= 5
 
 
+# rows of a verification around what the kernel is compiled for (3, 5, 9; 10 take the launches per matrix), contexts of one pass over
+# the cache, several passes, and on both sides of the longest one (128 KB of keys: 512 rows of 64 fp32 values, 1024 of 16 bits)
+@pytest.mark.parametrize("kv,plen", [("fp32", 1), ("fp32", 300), ("fp32", 490), ("bf16", 700), ("bf16", 1003)])
+def test_verification_of_two_to_ten_rows(kv, plen):
+    shape = ModelShape(2, 512, 8, 2, 1408, 528)
+    orc, ctx = make_pair(shape, 11, plen + 70, max_k=9, norm_gain_std=0.1, kv_dtype=kv)
+    prompt = make_prompt(shape.vocab, plen, 6).tolist()
+    st = lockstep_ssd(ctx, orc, prompt, 0, [8, 1, 2, 3, 4, 5, 7, 9], np.array([0, 1], np.uint8), shape.dtype)
+    assert st["unpinned_cycles"] <= 1 and st["draft_rows"] >= 20
+
+
+def test_verification_with_128_wide_heads_and_nine_rows():
+    shape = ModelShape(2, 1024, 8, 2, 3072, 528)    # LDS and the registers are full
+    orc, ctx = make_pair(shape, 12, 300, max_k=8, norm_gain_std=0.1)
+    prompt = make_prompt(shape.vocab, 230, 6).tolist()   # up to 256 positions of 128 fp32 values
+    st = lockstep_ssd(ctx, orc, prompt, 0, [8, 8, 6, 8], np.array([0, 1], np.uint8), shape.dtype)
+    assert st["unpinned_cycles"] <= 1 and st["draft_rows"] >= 14
+
+
 @pytest.mark.parametrize("kv", ["fp32", "bf16"])
 @pytest.mark.parametrize("plen", [511, 1300])    # up to eight ranges of one pass; longer ranges, several passes
 def test_decoding_over_several_ranges(kv, plen):

@@ -20,7 +20,12 @@ void mail(const int* s, long* o) {
     const StepMail m = step_mail(StepShape{s[0], s[1], s[2], s[3], s[4], s[5], s[6], s[7], s[8], s[9]});
     o[0] = m.x; o[1] = m.qkv; o[2] = m.part; o[3] = m.act; o[4] = m.total;
 }
-int limits(int i) { const int v[] = {ST_WAVES, ST_GU, ST_CD, ST_CF, AW_MAX_RANGES, ST_WAIT_WORDS}; return v[i]; }
+void rmail(const int* s, long* o) {
+    const RowsMail m = rows_mail(StepShape{s[0], s[1], s[2], s[3], s[4], s[5], s[6], s[7], s[8], s[9]});
+    o[0] = m.x; o[1] = m.qkv; o[2] = m.att; o[3] = m.act; o[4] = m.total;
+}
+int rows_fit(const int* s, int M, int ctx, int nb) { return rows_step_fits(StepShape{s[0], s[1], s[2], s[3], s[4], s[5], s[6], s[7], s[8], s[9]}, M, ctx, nb); }
+int limits(int i) { const int v[] = {ST_WAVES, ST_GU, ST_CD, ST_CF, AW_MAX_RANGES, ST_WAIT_WORDS, RS_ROWS}; return v[i]; }
 }
 """
 
@@ -70,7 +75,13 @@ def test_every_unit_has_one_owner_within_the_limits(rules, shape, cus):
     rules.mail(s, o)
     sizes = (2 * d, dq + 2 * dkv, H * ranges * (hd + 2), f)
     assert o[0] >= ctrl and all(o[i] + sizes[i] <= o[i + 1] for i in range(4))
-    assert all(v % 2 == 0 for v in o[:4]), "word pairs are read by 16-byte loads"
+    assert all(v % 2 == 0 for v in o), "word pairs are read by 16-byte loads"
+    rows = rules.limits(6)
+    rules.rmail(s, o)
+    sizes = (2 * rows * d, rows * (dq + 2 * dkv), rows * dq, rows * f)
+    assert o[0] == 0 and all(o[i] + sizes[i] <= o[i + 1] for i in range(4)) and all(v % 2 == 0 for v in o[:4])
+    for M in range(rows + 2):   # a block per head and row; no row count beyond the layout
+        assert rules.rows_fit(s, M, 64, nb) == int(2 <= M <= rows and H * M <= nb)
 
 
 @pytest.mark.parametrize("shape", [(1040, 1024, 1024, 2816, 32000, 64, 16, 16, 1, 0), (1024, 1024, 1024, 3088, 32000, 64, 16, 16, 1, 0),
