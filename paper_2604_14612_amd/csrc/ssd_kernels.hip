@@ -4290,8 +4290,9 @@ __global__ __launch_bounds__(ST_THREADS) void step_kernel(StepP p)
 //    independent; rows past M are zeros that nobody hands over;
 //  * attention is one block per head and row over all positions, without partials: a fold would be another hand-over, of more
 //    bytes.  The position's own K and V and those of the rows before it come by hand-over, the earlier ones from the cache.
-// fp32 arithmetic throughout, in the order of the single-row step: a draft of the full model and its verification agree in
-// every bit.
+//  * a lane finishes one row's sum (wave_sums): reduced one by one, the sums of a stage and what is done with them took longer
+//    than the products.
+// fp32 arithmetic throughout.
 struct RowsStepP {
     const StepWeights* layers; int L, M;
     const void* lm_head; const float* final_norm;
@@ -4303,7 +4304,7 @@ struct RowsStepP {
     long wait_ticks;
 };
 
-// o[j][r] = weight row j (C vectors of this lane) . row r in LDS, over the wave
+// o[j][r] = this lane's part of weight row j (C vectors) . row r in LDS
 template <typename WT, int J, int C, int R>
 __device__ __forceinline__ void rows_dots(const u32x4_t (&w)[J][C], const float* xs, int lane, int K, float (&o)[J][R])
 {
@@ -4331,10 +4332,27 @@ __device__ __forceinline__ void rows_dots(const u32x4_t (&w)[J][C], const float*
             }
         }
     }
+}
+
+// Sums of N values over the wave; sum v is returned in the lane whose wave_slot is v.  Four values share a register after two
+// exchanges, so that the adds inside the rows of 16 lanes are done once for all four: 11 instructions instead of 40.
+__device__ __forceinline__ int wave_slot(int lane) { return 4 * (lane & 15) + (lane >> 4); }
+template <int N>
+__device__ __forceinline__ float wave_sums(const float (&v)[N], int lane)
+{
+    static_assert(N <= 64, "one lane per sum");
+    float out = 0.f;
 #pragma unroll
-    for (int j = 0; j < J; j++)
-#pragma unroll
-        for (int r = 0; r < R; r++) o[j][r] = wave_sum_fast(o[j][r]);
+    for (int q = 0; q < (N + 3) / 4; q++) {
+        auto at = [&](int i) { return i < N ? __float_as_uint(v[i < N ? i : 0]) : 0u; };
+        auto a = __builtin_amdgcn_permlane32_swap(at(4 * q), at(4 * q + 2), false, false);         // halves: 4q, 4q + 2
+        auto b = __builtin_amdgcn_permlane32_swap(at(4 * q + 1), at(4 * q + 3), false, false);     // 4q + 1, 4q + 3
+        const float x = __uint_as_float(a[0]) + __uint_as_float(a[1]), y = __uint_as_float(b[0]) + __uint_as_float(b[1]);
+        auto c = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);   // rows: 4q .. 4q + 3
+        const float z = row16_sum(__uint_as_float(c[0]) + __uint_as_float(c[1]));
+        out = q == 0 || (lane & 15) == q ? z : out;
+    }
+    return out;
 }
 
 template <typename WT, typename KT, int HD, int R>
@@ -4393,9 +4411,7 @@ __global__ __launch_bounds__(ST_THREADS) void rows_step_kernel(RowsStepP p)
     };
     int qm, qr0, qr1;
     qkv_rows(qp, qm, qr0, qr1);
-    float xr[R];                                // residual values of this wave's row
-#pragma unroll
-    for (int r = 0; r < R; r++) xr[r] = has_x && r < M ? p.x[(size_t)r * d + xr0] : 0.f;
+    float xr = has_x && wave_slot(lane) < M ? p.x[(size_t)wave_slot(lane) * d + xr0] : 0.f;   // of this wave's row: lane of slot r, residual row r
     __syncthreads();
 
     auto ptr = [&](int l, int which) -> const char* {   // uniform: scalar registers
@@ -4454,8 +4470,8 @@ __global__ __launch_bounds__(ST_THREADS) void rows_step_kernel(RowsStepP p)
         const int i = 2 * (u * ST_THREADS + tid);
         if (i < n) *reinterpret_cast<float2*>(xs + r * XF + gv_xpos<VEC>(i)) = v;
     };
-    // residual rows into LDS, times the gain; sc = their RMS scales
-    auto take_x = [&](const float2 (&gain)[NX], float (&sc)[R]) {
+    // residual rows into LDS, times the gain, and their sums of squares
+    auto take_x = [&](const float2 (&gain)[NX]) {
         fresh();
         float2 v[R * NX];
         if (first) {
@@ -4478,34 +4494,31 @@ __global__ __launch_bounds__(ST_THREADS) void rows_step_kernel(RowsStepP p)
                 }
             mail_take(pr, v, mx + (size_t)xpar * RS_ROWS * d, np, tag, ctrl, alive, p.wait_ticks);
         }
+        float ss[R];
 #pragma unroll
         for (int r = 0; r < R; r++) {
-            float ss = 0.f;
+            ss[r] = 0.f;
 #pragma unroll
             for (int u = 0; u < NX; u++) {
                 const float2 x = v[r * NX + u];
                 put_row(r, u, make_float2(x.x * gain[u].x, x.y * gain[u].y), d);
-                ss += x.x * x.x + x.y * x.y;
+                ss[r] += x.x * x.x + x.y * x.y;
             }
-            ss = wave_sum_fast(ss);
-            if (lane == 0) red[r * ST_WAVES + wave] = ss;
         }
+        const float sum = wave_sums(ss, lane);
+        if (wave_slot(lane) < R) red[wave_slot(lane) * ST_WAVES + wave] = sum;
         lds_barrier();
+    };
+    auto scale = [&](int r) -> float {          // RMS scale of residual row r, behind take_x
+        float t = 0.f;
 #pragma unroll
-        for (int r = 0; r < R; r++) {
-            float t = 0.f;
-#pragma unroll
-            for (int i = 0; i < ST_WAVES; i++) t += red[r * ST_WAVES + i];
-            sc[r] = 1.0f / sqrtf(t / (float)d + p.eps);
-        }
+        for (int i = 0; i < ST_WAVES; i++) t += red[r * ST_WAVES + i];
+        return 1.0f / sqrtf(t / (float)d + p.eps);
     };
     // the block's share of the residual rows to everybody, and into the taps
     auto give_x = [&](int l, int which) {
         tag++; xpar ^= 1; first = false;
-        if (lane == 0) {
-#pragma unroll
-            for (int r = 0; r < R; r++) outs[wave * R + r] = xr[r];
-        }
+        if (wave_slot(lane) < R) outs[wave * R + wave_slot(lane)] = xr;
         lds_barrier();
         const int i = tid / R, r = tid % R;
         if (i < xb1 - xb0 && r < M) {
@@ -4519,24 +4532,20 @@ __global__ __launch_bounds__(ST_THREADS) void rows_step_kernel(RowsStepP p)
     for (int l = 0; l < p.L; l++) {
         KT* kc = reinterpret_cast<KT*>(p.kv + (size_t)(2 * l) * p.kv_layer);
         KT* vc = reinterpret_cast<KT*>(p.kv + (size_t)(2 * l + 1) * p.kv_layer);
-        float sc[R];
         // ---- q, k, v ----
         {
-            take_x(gq, sc);
+            take_x(gq);
             tag++;
             float o[2][R];
             rows_dots<WT>(bq, xs, lane, d, o);
-            const int i = qr0 % HD;
-#pragma unroll
-            for (int r = 0; r < R; r++) {
-                const float a = o[0][r] * sc[r], c = o[1][r] * sc[r];
-                float o0 = a, o1 = c;
-                if (qm < 2) {
-                    const float cs = rope[r * HD + 2 * i], sn = rope[r * HD + 2 * i + 1];   // (rows past M: nobody takes the result)
-                    o0 = a * cs - c * sn; o1 = c * cs + a * sn;
-                }
-                if (lane == 0) { outs[wave * R + r] = o0; outs[(ST_WAVES + wave) * R + r] = o1; }
+            const int slot = wave_slot(lane), sr = min(slot, R - 1), hi = qr0 % HD;
+            const float sc = scale(sr), a = wave_sums(o[0], lane) * sc, c = wave_sums(o[1], lane) * sc;
+            float o0 = a, o1 = c;
+            if (qm < 2) {
+                const float cs = rope[sr * HD + 2 * hi], sn = rope[sr * HD + 2 * hi + 1];   // (rows past M: nobody takes the result)
+                o0 = a * cs - c * sn; o1 = c * cs + a * sn;
             }
+            if (slot < R) { outs[wave * R + slot] = o0; outs[(ST_WAVES + wave) * R + slot] = o1; }
             lds_barrier();
             const int unit = tid / R, r = tid % R, pr = step_begin(nqp, b, NB) + unit % ST_WAVES;
             if (unit < 2 * ST_WAVES && r < M && pr < step_begin(nqp, b + 1, NB)) {
@@ -4683,25 +4692,24 @@ __global__ __launch_bounds__(ST_THREADS) void rows_step_kernel(RowsStepP p)
             lds_barrier();
             float o[1][R];
             rows_dots<WT>(bo, xs, lane, dq, o);
-#pragma unroll
-            for (int r = 0; r < R; r++) xr[r] += o[0][r];
+            xr += wave_sums(o[0], lane);
             give_x(l, 0);
             fresh();
             load_o(l + 1);
         }
         // ---- gate and up ----
         {
-            take_x(gg, sc);
+            take_x(gg);
             tag++;
-            float o[2 * ST_GU][R];
+            float o[2 * ST_GU][R], og[ST_GU * R], ou[ST_GU * R];
             rows_dots<WT>(bg, xs, lane, d, o);
 #pragma unroll
             for (int u = 0; u < ST_GU; u++)
 #pragma unroll
-                for (int r = 0; r < R; r++) {
-                    const float a = o[2 * u][r] * sc[r], c = o[2 * u + 1][r] * sc[r];
-                    if (lane == 0) outs[(u * ST_WAVES + wave) * R + r] = a / (1.0f + __expf(-a)) * c;
-                }
+                for (int r = 0; r < R; r++) { og[u * R + r] = o[2 * u][r]; ou[u * R + r] = o[2 * u + 1][r]; }
+            const int slot = wave_slot(lane);
+            const float sc = scale(slot % R), a = wave_sums(og, lane) * sc, c = wave_sums(ou, lane) * sc;
+            if (slot < ST_GU * R) outs[(slot / R * ST_WAVES + wave) * R + slot % R] = a / (1.0f + __expf(-a)) * c;
             lds_barrier();
             const int unit = tid / R, r = tid % R;
             if (unit < gp_end - gb0 && r < M) mail_put(mact + (size_t)r * f + gb0 + unit, outs[tid], tag);
@@ -4733,31 +4741,26 @@ __global__ __launch_bounds__(ST_THREADS) void rows_step_kernel(RowsStepP p)
             lds_barrier();
             float o[1][R];
             rows_dots<WT>(bd, xs, lane, f, o);
-#pragma unroll
-            for (int r = 0; r < R; r++) xr[r] += o[0][r];
+            xr += wave_sums(o[0], lane);
             give_x(l, 1);
             fresh();
             load_d(l + 1);
         }
     }
     // ---- LM head: the first three row pairs of every wave are in registers, a used one is replaced by the third next ----
-    float sc[R];
-    take_x(gq, sc);
-    float best[R];
-    int arg[R];
-#pragma unroll
-    for (int r = 0; r < R; r++) { best[r] = -INFINITY; arg[r] = 0x7fffffff; }
+    take_x(gq);
+    const int slot = wave_slot(lane);           // row of the logits that this lane finishes
+    const float sc = scale(min(slot, R - 1));
+    float best = -INFINITY;
+    int arg = 0x7fffffff;
     auto lm_rows = [&](const u32x4_t (&w)[2][CD], int pair) {
         float o[2][R];
         rows_dots<WT>(w, xs, lane, d, o);
-#pragma unroll
-        for (int r = 0; r < R; r++) {
-            const float a = o[0][r] * sc[r], c = o[1][r] * sc[r];
-            if (lane == 0 && r < M) *reinterpret_cast<float2*>(p.logits + (size_t)r * p.V + (size_t)pair * 2) = make_float2(a, c);
-            const float ca = fminf(fmaxf(a, -p.clamp), p.clamp), cc = fminf(fmaxf(c, -p.clamp), p.clamp);
-            if (ca > best[r]) { best[r] = ca; arg[r] = pair * 2; }         // ascending columns: the first of equal maxima stays
-            if (cc > best[r]) { best[r] = cc; arg[r] = pair * 2 + 1; }
-        }
+        const float a = wave_sums(o[0], lane) * sc, c = wave_sums(o[1], lane) * sc;
+        if (slot < M) *reinterpret_cast<float2*>(p.logits + (size_t)slot * p.V + (size_t)pair * 2) = make_float2(a, c);
+        const float ca = fminf(fmaxf(a, -p.clamp), p.clamp), cc = fminf(fmaxf(c, -p.clamp), p.clamp);
+        if (ca > best) { best = ca; arg = pair * 2; }         // ascending columns: the first of equal maxima stays
+        if (cc > best) { best = cc; arg = pair * 2 + 1; }
     };
     auto lm_load = [&](u32x4_t* w0, u32x4_t* w1, int pair) {
         row_load(w0, CD, lh, (size_t)pair * 2, d, pair < lp_end);
@@ -4778,10 +4781,7 @@ __global__ __launch_bounds__(ST_THREADS) void rows_step_kernel(RowsStepP p)
         }
     }
     __shared__ float2 vred[ST_WAVES * R];
-    if (lane == 0) {
-#pragma unroll
-        for (int r = 0; r < R; r++) vred[wave * R + r] = make_float2(best[r], __int_as_float(arg[r]));
-    }
+    if (slot < R) vred[wave * R + slot] = make_float2(best, __int_as_float(arg));
     lds_barrier();
     if (tid < M) {
         float2 a = vred[tid];
