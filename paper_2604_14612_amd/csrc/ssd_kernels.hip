@@ -4290,9 +4290,14 @@ __global__ __launch_bounds__(ST_THREADS) void step_kernel(StepP p)
 //    independent; rows past M are zeros that nobody hands over;
 //  * attention is one block per head and row over all positions, without partials: a fold would be another hand-over, of more
 //    bytes.  The position's own K and V and those of the rows before it come by hand-over, the earlier ones from the cache.
+//    They are requested behind the block's own q, k and v: in front of its products they delay the words it hands over
+//    (8 layers: 179 -> 185 us);
 //  * a lane finishes one row's sum (wave_sums): reduced one by one, the sums of a stage and what is done with them took longer
 //    than the products.
-// fp32 arithmetic throughout.
+// fp32 arithmetic throughout.  Measured, 5 rows, embedding and arg-max launches not counted: 8 layers of 1024 (FFN 2816, 32000-row
+// LM head) at 200 to 260 positions: 300 us with a launch per matrix, 207 with every sum reduced by itself, 179, now 175;
+// 4 layers of 256 in fp32: 105, 84, 67, 64.  A layer of the former spends 1.8 us waiting for the residual rows, twice, 1 for q, k, v,
+// 2 for attention's output and 4 for the activations (112 KB per block: what a CU pulls in 2 us), and 8 on arithmetic.
 struct RowsStepP {
     const StepWeights* layers; int L, M;
     const void* lm_head; const float* final_norm;
@@ -4359,7 +4364,7 @@ template <typename WT, typename KT, int HD, int R>
 __global__ __launch_bounds__(ST_THREADS) void rows_step_kernel(RowsStepP p)
 {
     constexpr int VEC = Elem<WT>::VEC, CH = 64 * VEC, CD = ST_CD, CF = ST_CF, XF = CF * CH;
-    constexpr int EPV = 16 / (int)sizeof(KT), LPP = HD / EPV, PPL = 64 / LPP, NL = 8, PASS = NL * ST_WAVES * PPL;
+    constexpr int EPV = 16 / (int)sizeof(KT), LPP = HD / EPV, PPL = 64 / LPP, NL = 4, PASS = NL * ST_WAVES * PPL;
     constexpr int NX = (CD * CH + 2 * ST_THREADS - 1) / (2 * ST_THREADS), NF = (XF + 2 * ST_THREADS - 1) / (2 * ST_THREADS);   // pairs of elements of a d- or dq-, of an f-vector per thread
     constexpr int NQ = ((2 * R + 1) * HD / 2 + ST_THREADS - 1) / ST_THREADS;
     extern __shared__ __align__(16) float st_sm[];
@@ -4570,8 +4575,8 @@ __global__ __launch_bounds__(ST_THREADS) void rows_step_kernel(RowsStepP p)
             const int seg = lane / LPP, sl = (lane % LPP) * EPV;
             const KT* kb = kc + (size_t)kvh * p.max_seq * HD + sl;
             const KT* vb = vc + (size_t)kvh * p.max_seq * HD + sl;
-            u32x4_t kr[NL], vr[NL];
-            auto issue = [&](int pass) {
+            u32x4_t kr[2][NL], vr[2][NL];   // two passes: their loads are in flight together (one of twice the length: tiny contexts pay for all of it)
+            auto issue = [&](u32x4_t (&kr)[NL], u32x4_t (&vr)[NL], int pass) {
 #pragma unroll
                 for (int t = 0; t < NL; t++) {
                     const int j = min(((pass * NL + t) * ST_WAVES + wave) * PPL + seg, jlast);
@@ -4579,7 +4584,8 @@ __global__ __launch_bounds__(ST_THREADS) void rows_step_kernel(RowsStepP p)
                     vr[t] = *reinterpret_cast<const u32x4_t*>(vb + (size_t)j * HD);
                 }
             };
-            issue(0);
+            issue(kr[0], vr[0], 0);
+            if (n_pass > 1) issue(kr[1], vr[1], 1);
             {   // the query, then the keys and the values of rows 0 .. row
                 const int units = 2 * row + 3, np = M * nqkv / 2;
                 const float qsc = 1.0f / sqrtf((float)HD);
@@ -4604,8 +4610,7 @@ __global__ __launch_bounds__(ST_THREADS) void rows_step_kernel(RowsStepP p)
             float m = -INFINITY, lsum = 0.f, acc[EPV];
 #pragma unroll
             for (int u = 0; u < EPV; u++) acc[u] = 0.f;
-            for (int pass = 0; pass < n_pass; pass++) {
-                if (pass) issue(pass);
+            auto attend = [&](const u32x4_t (&kr)[NL], const u32x4_t (&vr)[NL], int pass) {
                 float s[NL];
 #pragma unroll
                 for (int t = 0; t < NL; t++) {
@@ -4647,6 +4652,13 @@ __global__ __launch_bounds__(ST_THREADS) void rows_step_kernel(RowsStepP p)
 #pragma unroll
                     for (int u = 0; u < EPV; u++) acc[u] = fmaf(e, vf[u], acc[u]);
                 }
+            };
+            for (int pass = 0; pass < n_pass; pass += 2) {
+                attend(kr[0], vr[0], pass);
+                if (pass + 2 < n_pass) issue(kr[0], vr[0], pass + 2);
+                if (pass + 1 >= n_pass) break;
+                attend(kr[1], vr[1], pass + 1);
+                if (pass + 3 < n_pass) issue(kr[1], vr[1], pass + 3);
             }
             lsum = seg_sum_fast<LPP>(lsum);
 #pragma unroll
