@@ -4296,7 +4296,7 @@ __global__ __launch_bounds__(ST_THREADS) void step_kernel(StepP p)
 //    than the products.
 // fp32 arithmetic throughout.  Measured, 5 rows, embedding and arg-max launches not counted: 8 layers of 1024 (FFN 2816, 32000-row
 // LM head) at 200 to 260 positions: 300 us with a launch per matrix, 207 with every sum reduced by itself, 179, now 175;
-// 4 layers of 256 in fp32: 105, 84, 67, 64.  A layer of the former spends 1.8 us waiting for the residual rows, twice, 1 for q, k, v,
+// 4 layers of 256 in fp32: 112, 84, 67, 64.  A layer of the former spends 1.8 us waiting for the residual rows, twice, 1 for q, k, v,
 // 2 for attention's output and 4 for the activations (112 KB per block: what a CU pulls in 2 us), and 8 on arithmetic.
 struct RowsStepP {
     const StepWeights* layers; int L, M;
