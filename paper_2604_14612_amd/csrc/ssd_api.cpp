@@ -552,6 +552,15 @@ int verify_fused(ssd_ctx* c, int M, Tokens tok)
     return SSD_OK;
 }
 
+// Captured sequences hold the addresses of the weights and of the workspace: whoever changes those drops the sequences.  None is
+// in flight then, every call that replays one waits for it.
+void drop_graphs(ssd_ctx* c)
+{
+    for (auto& e : c->graphs)
+        if (e.second) (void)hipGraphExecDestroy(e.second);
+    c->graphs.clear();
+}
+
 // Runs a launch sequence.  The first time a key is seen the sequence runs kernel by kernel; the
 // second time it is captured into a HIP graph, and from then on the graph is replayed (one
 // submission instead of hundreds of launches).  Everything position-dependent is read from
@@ -563,11 +572,7 @@ int run_sequence(ssd_ctx* c, const std::string& key, F&& body)
     if (!c->use_graphs || c->prof_kid >= 0 || c->stream == nullptr) return body();
     auto it = c->graphs.find(key);
     if (it == c->graphs.end()) {
-        if (c->graphs.size() >= 256) {  // masks change during the search: keep the cache bounded
-            for (auto& e : c->graphs)
-                if (e.second) (void)hipGraphExecDestroy(e.second);
-            c->graphs.clear();
-        }
+        if (c->graphs.size() >= 256) drop_graphs(c);   // masks change during the search: keep the cache bounded
         c->graphs[key] = nullptr;
         return body();
     }
@@ -800,6 +805,7 @@ int ssd_set_workspace(ssd_ctx* c, void* dev, size_t bytes)
     if (!c->pinned) HIPCHK(hipHostMalloc((void**)&c->pinned, ((size_t)PIN_PROMPT + c->D.max_seq) * 4, hipHostMallocMapped | hipHostMallocCoherent), "hipHostMalloc");
     HIPCHK(hipGetDevice(&c->device), "hipGetDevice");
     HIPCHK(static_scratch_for_device(c->device, &c->static_scratch), "static scratch address");
+    drop_graphs(c);
     c->ws = static_cast<char*>(dev);
     c->ws_bytes = bytes;
     HIPCHK(hipMemcpyAsync(c->ws + c->lay.rope, tab.data(), tab.size() * sizeof(float), hipMemcpyHostToDevice, c->stream),
@@ -831,6 +837,7 @@ int ssd_load_weights(ssd_ctx* c, const ssd_weights* w)
         ok = chk(w->attn_norm[l]) && chk(w->wq[l]) && chk(w->wk[l]) && chk(w->wv[l]) && chk(w->wo[l]) &&
              chk(w->mlp_norm[l]) && chk(w->wg[l]) && chk(w->wu[l]) && chk(w->wd[l]);
     if (!ok) return fail(c, SSD_EINVAL, "weight pointers must be 16-byte aligned");
+    drop_graphs(c);
     c->w = *w;
     c->attn_norm.assign(w->attn_norm, w->attn_norm + L);
     c->mlp_norm.assign(w->mlp_norm, w->mlp_norm + L);
@@ -859,8 +866,7 @@ void ssd_destroy(ssd_ctx* c)
     if (!c) return;
     if (c->pinned) (void)hipHostFree(c->pinned);
     for (auto& e : c->prof_ev) { (void)hipEventDestroy(e.first); (void)hipEventDestroy(e.second); }
-    for (auto& e : c->graphs)
-        if (e.second) (void)hipGraphExecDestroy(e.second);
+    drop_graphs(c);
     delete c;
 }
 
