@@ -310,6 +310,21 @@ SSD_API int ssd_profile_select(ssd_ctx *ctx, int kernel_id);
 SSD_API int ssd_set_graphs(ssd_ctx *ctx, int enable);
 SSD_API int ssd_profile_read(ssd_ctx *ctx, int64_t *launches_out, double *total_ms_out);
 
+/* Narrow models (16-bit weights: d_model and n_heads * head_dim up to 1024, d_ffn up to 3072; fp32: half of that) run a decode
+ * or draft step, and a short verification, as ONE launch whose blocks wait for each other.  It needs every CU of the device, so
+ * one may be in flight per device and process: a call that finds another context's uses a launch per matrix instead, as does
+ * every call while ssd_profile_select times a kernel.  The two add in different orders, so the last bits of a call's logits, and a
+ * token whose arg-max hangs on them, can depend on what other contexts do at that time.  A wait inside that takes longer than
+ * wait_us (CUs held by another process or stream) ends the launch; the call then does its work again with a launch per
+ * matrix and returns those results, and so do the calls behind it until ssd_reset.
+ *   enable   0: this context always uses a launch per matrix (the same bits whatever runs beside it; other streams' kernels find
+ *            free CUs sooner); 1 (default): one launch where the shape allows it
+ *   wait_us  bound of one wait; 0: 50 ms (default); < 0: whoever does not find its data at the first look gives up (tests)
+ * Forgets earlier waits that took too long.  Not while another call of the context runs, as everywhere. */
+SSD_API int ssd_set_one_launch(ssd_ctx *ctx, int enable, int wait_us);
+/* Since ssd_create: single-row steps and verifications that ran as one launch, and calls whose launch gave up. */
+SSD_API int ssd_get_one_launch(const ssd_ctx *ctx, int64_t *steps_out, int64_t *verifications_out, int64_t *gave_up_out);
+
 /* Test hook: overwrite every cache entry at positions >= the number of valid positions
  * (n - 1) with NaN, to prove stale entries are never read. */
 SSD_API int ssd_kv_poison_stale(ssd_ctx *ctx);

@@ -101,6 +101,8 @@ SYMBOLS = {
     "ssd_profile_select": (C.c_int, [_P, C.c_int]),
     "ssd_profile_read": (C.c_int, [_P, _P, _P]),
     "ssd_set_graphs": (C.c_int, [_P, C.c_int]),
+    "ssd_set_one_launch": (C.c_int, [_P, C.c_int, C.c_int]),
+    "ssd_get_one_launch": (C.c_int, [_P, _P, _P, _P]),
 }
 
 _lib = None
@@ -428,6 +430,15 @@ class Context:
 
     def ssd_set_graphs(self, enable: bool):
         self._check(self._l.ssd_set_graphs(self._h, 1 if enable else 0))
+
+    def ssd_set_one_launch(self, enable: bool, wait_us: int = 0):
+        self._check(self._l.ssd_set_one_launch(self._h, 1 if enable else 0, int(wait_us)))
+
+    def ssd_get_one_launch(self):
+        """-> (single-row steps, verifications) that ran as one launch, calls whose launch gave up"""
+        v = [C.c_int64() for _ in range(3)]
+        self._check(self._l.ssd_get_one_launch(self._h, *(C.addressof(x) for x in v)))
+        return tuple(x.value for x in v)
 
     def ssd_profile_select(self, kernel_id: int):
         self._check(self._l.ssd_profile_select(self._h, int(kernel_id)))

@@ -162,6 +162,9 @@ struct ssd_ctx {
     int step_blocks;   // blocks of a single-row step in one launch, 0 = not for this shape or device
     bool step_table;   // its weight table is on the device
     bool step_off;     // a wait gave up since the last reset: launches per matrix
+    bool step_on;      // the caller wants it (ssd_set_one_launch)
+    long step_ticks;   // bound of its waits
+    int64_t step_count, step_verify_count, step_gave_up;   // steps and verifications that ran so, calls that did not end so
     bool step_now;     // the sequence being enqueued takes it
     std::vector<StepWeights> step_rows;   // host copy of the table
     bool use_graphs;   // replay captured launch sequences instead of launching kernel by kernel
@@ -239,8 +242,10 @@ static inline bool is_gemv_kid(int kid)
         }                                                                                  \
     } while (0)
 
-// One launch whose blocks wait for each other may be in flight per device: two of them would each hold CUs that the other
-// one needs.  Whoever finds the device's slot taken uses the launches per matrix.
+// One launch whose blocks wait for each other may be in flight per device and process: two of them would each hold CUs that the
+// other one needs.  Whoever finds the device's slot taken uses the launches per matrix.  Other processes are not seen: against
+// theirs there is the bound of the waits.
+constexpr int STEP_WAIT_US = 50000;   // longer than what other streams' kernels usually hold CUs for
 std::atomic<bool> step_slots[64];
 struct StepSlot {
     ssd_ctx* c;
@@ -310,7 +315,7 @@ int forward_single(ssd_ctx* c, const uint8_t* sub, int slot, int slot_out, int p
         out.step_ctrl = reinterpret_cast<unsigned*>(c->ws + c->lay.step);
         out.step_err_host = c->pinned + PIN_STEP;
         StepLaunch a = {};
-        a.blocks = c->step_blocks; a.scratch = c->ws + c->lay.step; a.sub = sub;
+        a.blocks = c->step_blocks; a.scratch = c->ws + c->lay.step; a.wait_ticks = c->step_ticks; a.sub = sub;
         a.lm_head = c->w.lm_head; a.final_norm = c->w.final_norm;
         a.x = c->f(c->lay.x); a.rope_row = c->small_f() + SM_ROPE; a.pos_dev = c->pos_dev(); a.pos_off = pos_off; a.plan_ctx = plan_ctx;
         a.kv = c->ws + c->lay.kv; a.kv_layer = c->lay.kv_layer_elems * (c->cfg.kv_dtype == 0 ? 4 : 2);
@@ -541,7 +546,7 @@ int verify_fused(ssd_ctx* c, int M, Tokens tok)
     const Dims& D = c->D;
     HIPCHK(embed_rows(D, c->w.embed, tok, M, c->f(c->lay.x), c->stream), "embed");
     RowsStepLaunch a = {};
-    a.blocks = c->step_blocks; a.scratch = c->ws + c->lay.step; a.M = M; a.ctx = c->n - 1 + M;
+    a.blocks = c->step_blocks; a.scratch = c->ws + c->lay.step; a.wait_ticks = c->step_ticks; a.M = M; a.ctx = c->n - 1 + M;
     a.lm_head = c->w.lm_head; a.final_norm = c->w.final_norm;
     a.x = c->f(c->lay.x); a.rope = c->f(c->lay.rope); a.pos_dev = c->pos_dev();
     a.kv = c->ws + c->lay.kv; a.kv_layer = c->lay.kv_layer_elems * (c->cfg.kv_dtype == 0 ? 4 : 2);
@@ -614,18 +619,23 @@ bool whole_layers(const ssd_ctx* c, const uint8_t* sub)
 // Runs the launch sequence of a call of single-row steps or of a verification and waits for its results.  fits: it can take
 // one launch per step.  Where it does and a wait inside gave up, everything from the pending token on is done
 // again by the launches per matrix (nothing was committed, cache rows of uncommitted positions are written anew).
+// counter += n where the call ended as one launch per step.
 template <typename F>
-int run_steps(ssd_ctx* c, const std::string& key, bool fits, F&& body)
+int run_steps(ssd_ctx* c, const std::string& key, bool fits, int64_t& counter, int n, F&& body)
 {
     {
-        StepSlot slot(c, c->step_blocks > 0 && c->step_table && !c->step_off && fits && c->prof_kid < 0);
+        StepSlot slot(c, c->step_on && c->step_blocks > 0 && c->step_table && !c->step_off && fits && c->prof_kid < 0);
         if (c->step_now) {
             c->pinned[PIN_STEP] = 0;
             int rc = run_sequence(c, "P" + key, body);
             const int rs = sync_results(c);   // the slot is free again when the launches are done
             if (rc) return rc;
             if (rs) return rs;
-            if (!c->pinned[PIN_STEP]) return SSD_OK;
+            if (!c->pinned[PIN_STEP]) {
+                counter += n;
+                return SSD_OK;
+            }
+            c->step_gave_up++;
             c->step_off = true;
             HIPCHK(hipMemsetAsync(c->ws + c->lay.step + 4, 0, 4, c->stream), "step error clear");
         }
@@ -775,6 +785,8 @@ int ssd_create(const ssd_config* cfg, void* hip_stream, ssd_ctx** out)
     memset(&c->st, 0, sizeof(c->st));
     memset(&c->w, 0, sizeof(c->w));
     c->step_blocks = 0; c->step_table = c->step_off = c->step_now = false;
+    c->step_on = true; c->step_ticks = STEP_WAIT_US * STEP_TICKS_PER_US;
+    c->step_count = c->step_verify_count = c->step_gave_up = 0;
     c->prof_kid = -1; c->prof_used = 0;
     c->use_graphs = true;
     *out = c;
@@ -938,7 +950,8 @@ int ssd_decode(ssd_ctx* c, int32_t* token_out)
     if (c->n + 1 > c->D.max_seq) return fail(c, SSD_ECAPACITY, "sequence would exceed max_seq");
     // pending token sits in tok slot 0; its successor is written to slot 1, then promoted
     std::string key = "D|" + std::to_string(attention_splits(c->D, c->n, 1));
-    int rc = run_steps(c, key, step_plan_fits(c->D, c->n, c->step_blocks), [&]() { return forward_single(c, nullptr, 0, 1, 0, c->n, 0, STEP_COMMIT); });
+    int rc = run_steps(c, key, step_plan_fits(c->D, c->n, c->step_blocks), c->step_count, 1,
+                       [&]() { return forward_single(c, nullptr, 0, 1, 0, c->n, 0, STEP_COMMIT); });
     if (rc) return rc;
     *token_out = c->pinned[PIN_TOK + 1];
     c->n += 1;
@@ -965,7 +978,8 @@ static int draft_fixed(ssd_ctx* c, const std::vector<uint8_t>& sub, int k, int32
     if (c->state != ST_IDLE) return fail(c, SSD_ESTATE, "draft_step needs a prefilled sequence with no draft in flight");
     if (k > c->cfg.max_k) return fail(c, SSD_ECAPACITY, "k exceeds max_k");
     if (c->n + k > c->D.max_seq) return fail(c, SSD_ECAPACITY, "draft + verification would exceed max_seq");
-    int rc = run_steps(c, draft_key(c->D, sub, c->n, k), whole_layers(c, sub.data()) && step_plan_fits(c->D, draft_plan_ctx(c->n, k), c->step_blocks), [&]() {
+    const bool fits = whole_layers(c, sub.data()) && step_plan_fits(c->D, draft_plan_ctx(c->n, k), c->step_blocks);
+    int rc = run_steps(c, draft_key(c->D, sub, c->n, k), fits, c->step_count, k, [&]() {
         for (int i = 0; i < k; i++) {
             int r = forward_single(c, sub.data(), i, i + 1, i, draft_plan_ctx(c->n, k), i, (i ? STEP_CHAINED : 0) | (i + 1 < k ? STEP_CHAIN_NEXT : 0));
             if (r) return r;
@@ -1019,7 +1033,8 @@ int ssd_draft_adaptive(ssd_ctx* c, const uint8_t* skip_mask, int k_max, float ga
     while (k < k_max) {
         // one draft step per submission: the host reads the step's max-probability before deciding on the next
         const int i = k;
-        int rc = run_steps(c, adaptive_key(c->D, sub, c->n, k_max, i), whole_layers(c, sub.data()) && step_plan_fits(c->D, draft_plan_ctx(c->n, k_max), c->step_blocks),
+        const bool fits = whole_layers(c, sub.data()) && step_plan_fits(c->D, draft_plan_ctx(c->n, k_max), c->step_blocks);
+        int rc = run_steps(c, adaptive_key(c->D, sub, c->n, k_max, i), fits, c->step_count, 1,
                            [&]() { return forward_single(c, sub.data(), i, i + 1, i, draft_plan_ctx(c->n, k_max), i, 0); });
         if (rc) return rc;
         const float p = c->pin_f(PIN_PROB)[i];
@@ -1048,7 +1063,7 @@ int ssd_verify(ssd_ctx* c, const int32_t* draft, int k, int32_t* target_out)
     std::string key = "V|" + std::to_string(k) + "|" + std::to_string(attention_splits(c->D, c->n + k, k + 1));
     const Tokens tok = {c->pinned + PIN_VTOK, c->small_i() + SM_TOK};
     const bool fits = rows_step_fits(c->D, k + 1, c->n + k, c->step_blocks) && (size_t)2 * (k + 1) * c->step_blocks <= c->lay.part_floats;
-    int rc = run_steps(c, key, fits, [&]() { return c->step_now ? verify_fused(c, k + 1, tok) : forward_rows(c, k + 1, 0, c->n - 1, true, tok); });
+    int rc = run_steps(c, key, fits, c->step_verify_count, 1, [&]() { return c->step_now ? verify_fused(c, k + 1, tok) : forward_rows(c, k + 1, 0, c->n - 1, true, tok); });
     if (rc) return rc;
     memcpy(target_out, c->pinned + PIN_TARGET, sizeof(int32_t) * (k + 1));
     c->state = ST_VERIFIED;
@@ -1202,6 +1217,24 @@ int ssd_set_graphs(ssd_ctx* c, int enable)
 {
     if (!c) return SSD_EINVAL;
     c->use_graphs = enable != 0;
+    return SSD_OK;
+}
+
+int ssd_set_one_launch(ssd_ctx* c, int enable, int wait_us)
+{
+    if (!c) return SSD_EINVAL;
+    const long ticks = wait_us == 0 ? STEP_WAIT_US * STEP_TICKS_PER_US : wait_us < 0 ? -1 : wait_us * STEP_TICKS_PER_US;
+    if (ticks != c->step_ticks) drop_graphs(c);   // the bound is an argument of the captured launches
+    c->step_ticks = ticks;
+    c->step_on = enable != 0;
+    c->step_off = false;
+    return SSD_OK;
+}
+
+int ssd_get_one_launch(const ssd_ctx* c, int64_t* steps_out, int64_t* verifications_out, int64_t* gave_up_out)
+{
+    if (!c || !steps_out || !verifications_out || !gave_up_out) return SSD_EINVAL;
+    *steps_out = c->step_count; *verifications_out = c->step_verify_count; *gave_up_out = c->step_gave_up;
     return SSD_OK;
 }
 

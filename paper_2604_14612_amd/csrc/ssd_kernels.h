@@ -91,9 +91,10 @@ hipError_t gemv_lmhead_argmax(const Dims& D, const void* wlm, const float* gain,
 
 // ---- a whole single-row step in one launch (narrow models) ---------------------------------------------------
 // Layers, LM head and the end of the step as gemv_lmhead_argmax leaves it, by resident blocks that hand the activations to
-// each other through memory.  Blocks wait for each other: at most one such launch may be in flight per device.  A wait that
-// takes longer than 50 ms (blocks that are not resident, CUs held by others) ends the launch with *step_err_host = 1, nothing
-// committed; scratch[1] (32-bit words) has to be cleared before the next launch then.
+// each other through memory.  Blocks wait for each other: two such launches in flight on a device would each hold CUs that the other
+// one needs.  A wait that takes longer than wait_ticks (blocks that are not resident, CUs held by others) ends the launch with
+// *step_err_host = 1, nothing committed; scratch[1] (32-bit words) has to be cleared before the next launch then.
+constexpr long STEP_TICKS_PER_US = 100;   // of wait_ticks; < 0: whoever does not find its words at the first look gives up
 struct StepWeights { const void* p[9]; };   // attention norm gain, wq, wk, wv, wo, MLP norm gain, wg, wu, wd of a layer (device table)
 size_t step_scratch_bytes(const Dims& D);   // 0: shape not supported.  Cleared to zero before the first launch, weight table excepted
 size_t step_table_offset(const Dims& D);    // bytes from the scratch's start to the weight table [L]
@@ -102,6 +103,7 @@ bool step_plan_fits(const Dims& D, int ctx, int blocks);   // attention over ctx
 struct StepLaunch {
     int blocks;
     void* scratch;
+    long wait_ticks;
     const uint8_t* sub;         // host, may be null: two entries per layer, [2l] != 0 leaves out the attention sub-block, [2l+1] the MLP
     const void* lm_head; const float* final_norm;
     const float* x; const float* rope_row; const int* pos_dev; int pos_off;
@@ -115,7 +117,7 @@ hipError_t step_fused(const Dims& D, const StepLaunch& a, const StepOut& o, hipS
 // *pos_dev .. + M - 1, taps [M][L][2][d], logits [M][V] are written.  Blocks, scratch, waits and *err_host as above.
 bool rows_step_fits(const Dims& D, int M, int ctx, int blocks);   // ctx: positions the last row sees
 struct RowsStepLaunch {
-    int blocks; void* scratch;
+    int blocks; void* scratch; long wait_ticks;
     int M, ctx;
     const void* lm_head; const float* final_norm;
     const float* x; const float* rope; const int* pos_dev;   // rope: the whole table

@@ -3759,7 +3759,6 @@ hipError_t attention(const Dims& D, const float* q, int ldq, const void* kc, con
 // Tags are 32 bits of a running number and could only be mistaken after 2^32 hand-overs without a write to the word.
 constexpr int ST_THREADS = ST_WAVES * 64;
 constexpr int ST_FIRST_POLL = 18;         // x 64 clocks (10: 344 us, 13: 340, 16: 333 to 335, 19: 333, 22: 334)
-constexpr long ST_WAIT_TICKS = 5000000;   // 50 ms: longer than what other streams' kernels usually hold CUs for
 
 struct StepP {
     const StepWeights* layers; int L;
@@ -3798,7 +3797,7 @@ __device__ __forceinline__ void mail_take(const int (&pair)[N], float2 (&v)[N], 
 #pragma unroll
         for (int u = 0; u < N; u++) ok = ok && ((w[u].y == tag && w[u].w == tag) || pair[u] >= n_pairs);
         if (__all(ok) || !alive) break;
-        if ((++spins & 63) == 0) {
+        if ((++spins & 63) == 0 || wait_ticks < 0) {   // (negative: nobody waits longer than one look)
             const long now = wall_clock64();
             if (t0 == 0) t0 = now;
             if (__hip_atomic_load(ctrl + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) alive = false;
@@ -4878,7 +4877,7 @@ hipError_t step_fused(const Dims& D, const StepLaunch& a, const StepOut& o, hipS
     p.logits = a.logits; p.vstat = a.vstat; p.clamp = a.clamp;
     p.d = D.d; p.dq = D.dq; p.dkv = D.dkv; p.f = D.f; p.V = D.V; p.H = D.H; p.Hkv = D.Hkv; p.max_seq = D.max_seq; p.eps = D.eps;
     p.n_splits = pl.n_splits; p.chunk = pl.chunk;
-    p.wait_ticks = ST_WAIT_TICKS;
+    p.wait_ticks = a.wait_ticks;
     void* args[] = {&p};
     hipError_t e = hipLaunchKernel(step_fn(D), dim3(a.blocks), dim3(ST_THREADS), args, step_lds_bytes(D), s);
     if (e != hipSuccess) return e;
@@ -4920,7 +4919,7 @@ hipError_t rows_step_fused(const Dims& D, const RowsStepLaunch& a, hipStream_t s
     p.kv = static_cast<char*>(a.kv); p.kv_layer = a.kv_layer;
     p.logits = a.logits; p.taps = a.taps; p.tap_ld = (size_t)D.L * 2 * D.d; p.vmax = a.vmax; p.clamp = a.clamp;
     p.d = D.d; p.dq = D.dq; p.dkv = D.dkv; p.f = D.f; p.V = D.V; p.H = D.H; p.Hkv = D.Hkv; p.max_seq = D.max_seq; p.eps = D.eps;
-    p.wait_ticks = ST_WAIT_TICKS;
+    p.wait_ticks = a.wait_ticks;
     hipError_t e;
     if (D.wt == WT_F32) e = rows_step_launch<float, float>(D, p, a.blocks, s);
     else if (D.wt == WT_BF16) e = D.kt == WT_F32 ? rows_step_launch<uint16_t, float>(D, p, a.blocks, s) : rows_step_launch<uint16_t, uint16_t>(D, p, a.blocks, s);
