@@ -160,6 +160,7 @@ struct ssd_ctx {
     void* static_scratch;  // this device's copy of the library's static scratch array (resolved at set_workspace)
     ssd_stats st;
     int step_blocks;   // blocks of a single-row step in one launch, 0 = not for this shape or device
+    int step_max_rows; // most rows of a verification in one launch there
     bool step_table;   // its weight table is on the device
     bool step_off;     // a wait gave up since the last reset: launches per matrix
     bool step_on;      // the caller wants it (ssd_set_one_launch)
@@ -784,7 +785,7 @@ int ssd_create(const ssd_config* cfg, void* hip_stream, ssd_ctx** out)
     c->n = 0; c->k_pending = 0; c->tap_rows = 0; c->tap_row0 = 0; c->logit_rows = 0; c->ring_count = 0; c->pinned = nullptr; c->device = -1; c->static_scratch = nullptr;
     memset(&c->st, 0, sizeof(c->st));
     memset(&c->w, 0, sizeof(c->w));
-    c->step_blocks = 0; c->step_table = c->step_off = c->step_now = false;
+    c->step_blocks = c->step_max_rows = 0; c->step_table = c->step_off = c->step_now = false;
     c->step_on = true; c->step_ticks = STEP_WAIT_US * STEP_TICKS_PER_US;
     c->step_count = c->step_verify_count = c->step_gave_up = 0;
     c->prof_kid = -1; c->prof_used = 0;
@@ -823,7 +824,7 @@ int ssd_set_workspace(ssd_ctx* c, void* dev, size_t bytes)
     HIPCHK(hipMemcpyAsync(c->ws + c->lay.rope, tab.data(), tab.size() * sizeof(float), hipMemcpyHostToDevice, c->stream),
            "rope upload");
     HIPCHK(hipMemsetAsync(c->ws + c->lay.small, 0, 4096, c->stream), "state clear");
-    HIPCHK(step_device_blocks(c->D, c->device, &c->step_blocks), "step occupancy");
+    HIPCHK(step_device_blocks(c->D, c->device, &c->step_blocks, &c->step_max_rows), "step occupancy");
     c->step_table = false;
     if (c->step_blocks > 0) HIPCHK(hipMemsetAsync(c->ws + c->lay.step, 0, step_scratch_bytes(c->D), c->stream), "step clear");
     HIPCHK(hipStreamSynchronize(c->stream), "workspace sync");  // tab goes out of scope
@@ -1062,7 +1063,7 @@ int ssd_verify(ssd_ctx* c, const int32_t* draft, int k, int32_t* target_out)
     for (int i = 0; i < k; i++) c->pinned[PIN_VTOK + 1 + i] = draft[i];
     std::string key = "V|" + std::to_string(k) + "|" + std::to_string(attention_splits(c->D, c->n + k, k + 1));
     const Tokens tok = {c->pinned + PIN_VTOK, c->small_i() + SM_TOK};
-    const bool fits = rows_step_fits(c->D, k + 1, c->n + k, c->step_blocks) && (size_t)2 * (k + 1) * c->step_blocks <= c->lay.part_floats;
+    const bool fits = rows_step_fits(c->D, k + 1, c->n + k, c->step_blocks, c->step_max_rows) && (size_t)2 * (k + 1) * c->step_blocks <= c->lay.part_floats;
     int rc = run_steps(c, key, fits, c->step_verify_count, 1, [&]() { return c->step_now ? verify_fused(c, k + 1, tok) : forward_rows(c, k + 1, 0, c->n - 1, true, tok); });
     if (rc) return rc;
     memcpy(target_out, c->pinned + PIN_TARGET, sizeof(int32_t) * (k + 1));

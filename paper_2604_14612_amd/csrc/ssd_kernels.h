@@ -98,7 +98,8 @@ constexpr long STEP_TICKS_PER_US = 100;   // of wait_ticks; < 0: whoever does no
 struct StepWeights { const void* p[9]; };   // attention norm gain, wq, wk, wv, wo, MLP norm gain, wg, wu, wd of a layer (device table)
 size_t step_scratch_bytes(const Dims& D);   // 0: shape not supported.  Cleared to zero before the first launch, weight table excepted
 size_t step_table_offset(const Dims& D);    // bytes from the scratch's start to the weight table [L]
-hipError_t step_device_blocks(const Dims& D, int device, int* blocks_out);   // blocks of a launch on this device, 0: not supported there
+// Blocks of a launch on this device (0: not supported there) and the most rows of a verification whose blocks are all resident.
+hipError_t step_device_blocks(const Dims& D, int device, int* blocks_out, int* max_rows_out);
 bool step_plan_fits(const Dims& D, int ctx, int blocks);   // attention over ctx positions has enough blocks
 struct StepLaunch {
     int blocks;
@@ -115,7 +116,7 @@ hipError_t step_fused(const Dims& D, const StepLaunch& a, const StepOut& o, hipS
 
 // The M rows of a verification in one launch and their greedy tokens in a second one: x holds the embedding rows; K and V rows
 // *pos_dev .. + M - 1, taps [M][L][2][d], logits [M][V] are written.  Blocks, scratch, waits and *err_host as above.
-bool rows_step_fits(const Dims& D, int M, int ctx, int blocks);   // ctx: positions the last row sees
+bool rows_step_fits(const Dims& D, int M, int ctx, int blocks, int max_rows);   // ctx: positions the last row sees
 struct RowsStepLaunch {
     int blocks; void* scratch; long wait_ticks;
     int M, ctx;

@@ -4835,9 +4835,32 @@ static size_t step_lds_bytes(const Dims& D)
     return (size_t)2 * ST_CF * 64 * (D.wt == WT_F32 ? 4 : 8) * sizeof(float) + (size_t)D.L * sizeof(StepWeights);
 }
 
-hipError_t step_device_blocks(const Dims& D, int device, int* blocks_out)
+// The verification kernel that computes R rows, enabled for its LDS.
+template <typename WT, typename KT, int HD>
+static hipError_t rows_step_fn(const Dims& D, int R, const void** fn, size_t* lds)
 {
-    *blocks_out = 0;
+    constexpr size_t XF = (size_t)ST_CF * 64 * Elem<WT>::VEC;
+    static std::atomic<size_t> lds_limit[3];   // per instantiation
+    *fn = R == 3 ? (const void*)rows_step_kernel<WT, KT, HD, 3> : R == 5 ? (const void*)rows_step_kernel<WT, KT, HD, 5>
+                                                                         : (const void*)rows_step_kernel<WT, KT, HD, RS_ROWS>;
+    *lds = R * XF * sizeof(float) + (size_t)D.L * sizeof(StepWeights);
+    return ensure_lds(*fn, *lds, lds_limit[R == 3 ? 0 : R == 5 ? 1 : 2]);
+}
+template <typename WT, typename KT>
+static hipError_t rows_step_fn(const Dims& D, int R, const void** fn, size_t* lds)
+{
+    return D.hd == 64 ? rows_step_fn<WT, KT, 64>(D, R, fn, lds) : rows_step_fn<WT, KT, 128>(D, R, fn, lds);
+}
+static hipError_t rows_step_fn(const Dims& D, int R, const void** fn, size_t* lds)
+{
+    if (D.wt == WT_F32) return rows_step_fn<float, float>(D, R, fn, lds);
+    if (D.wt == WT_BF16) return D.kt == WT_F32 ? rows_step_fn<uint16_t, float>(D, R, fn, lds) : rows_step_fn<uint16_t, uint16_t>(D, R, fn, lds);
+    return D.kt == WT_F32 ? rows_step_fn<f16_t, float>(D, R, fn, lds) : rows_step_fn<f16_t, f16_t>(D, R, fn, lds);
+}
+
+hipError_t step_device_blocks(const Dims& D, int device, int* blocks_out, int* max_rows_out)
+{
+    *blocks_out = *max_rows_out = 0;
     if (!step_scratch_bytes(D)) return hipSuccess;
     int cus = 0, per_cu = 0;
     hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
@@ -4846,6 +4869,17 @@ hipError_t step_device_blocks(const Dims& D, int device, int* blocks_out)
     e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, step_fn(D), ST_THREADS, lds);
     if (e != hipSuccess) return e;
     if (per_cu >= 1) *blocks_out = step_blocks(step_shape(D), cus);
+    // the verification kernels ask for more registers and four to five times the LDS: up to the widest that fits
+    for (int R : {3, 5, RS_ROWS}) {
+        const void* fn;
+        size_t rows_lds;
+        if (*blocks_out == 0 || rows_step_fn(D, R, &fn, &rows_lds) != hipSuccess ||
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, ST_THREADS, rows_lds) != hipSuccess || per_cu < 1) {
+            (void)hipGetLastError();   // a kernel that does not fit is no error of this call
+            break;
+        }
+        *max_rows_out = R;
+    }
     return hipSuccess;
 }
 
@@ -4884,31 +4918,14 @@ hipError_t step_fused(const Dims& D, const StepLaunch& a, const StepOut& o, hipS
     return step_finish(D, a.vstat, a.blocks, out, s);
 }
 
-template <typename WT, typename KT, int HD>
-static hipError_t rows_step_launch(const RowsStepP& p, int blocks, hipStream_t s)
+bool rows_step_fits(const Dims& D, int M, int ctx, int blocks, int max_rows)
 {
-    constexpr size_t XF = (size_t)ST_CF * 64 * Elem<WT>::VEC;
-    const int R = p.M <= 3 ? 3 : p.M <= 5 ? 5 : RS_ROWS;
-    const size_t lds = R * XF * sizeof(float) + (size_t)p.L * sizeof(StepWeights);
-    const void* fn = R == 3 ? (const void*)rows_step_kernel<WT, KT, HD, 3> : R == 5 ? (const void*)rows_step_kernel<WT, KT, HD, 5>
-                                                                                    : (const void*)rows_step_kernel<WT, KT, HD, RS_ROWS>;
-    static std::atomic<size_t> lds_limit[3];   // per instantiation
-    hipError_t e = ensure_lds(fn, lds, lds_limit[R == 3 ? 0 : R == 5 ? 1 : 2]);
-    if (e != hipSuccess) return e;
-    void* args[] = {const_cast<RowsStepP*>(&p)};
-    return hipLaunchKernel(fn, dim3(blocks), dim3(ST_THREADS), args, lds, s);
+    return ctx <= D.max_seq && rows_step_fits(step_shape(D), M, ctx, blocks, max_rows);
 }
-template <typename WT, typename KT>
-static hipError_t rows_step_launch(const Dims& D, const RowsStepP& p, int blocks, hipStream_t s)
-{
-    return D.hd == 64 ? rows_step_launch<WT, KT, 64>(p, blocks, s) : rows_step_launch<WT, KT, 128>(p, blocks, s);
-}
-
-bool rows_step_fits(const Dims& D, int M, int ctx, int blocks) { return ctx <= D.max_seq && rows_step_fits(step_shape(D), M, ctx, blocks); }
 
 hipError_t rows_step_fused(const Dims& D, const RowsStepLaunch& a, hipStream_t s)
 {
-    if (!rows_step_fits(D, a.M, a.ctx, a.blocks) || a.blocks != step_blocks(step_shape(D), a.blocks) || !a.tok_out || !a.tok_host || !a.err_host ||
+    if (!rows_step_fits(D, a.M, a.ctx, a.blocks, RS_ROWS) || a.blocks != step_blocks(step_shape(D), a.blocks) || !a.tok_out || !a.tok_host || !a.err_host ||
         !a.taps || !a.vmax) return hipErrorInvalidValue;
     RowsStepP p = {};
     p.ctrl = static_cast<unsigned*>(a.scratch);
@@ -4920,10 +4937,12 @@ hipError_t rows_step_fused(const Dims& D, const RowsStepLaunch& a, hipStream_t s
     p.logits = a.logits; p.taps = a.taps; p.tap_ld = (size_t)D.L * 2 * D.d; p.vmax = a.vmax; p.clamp = a.clamp;
     p.d = D.d; p.dq = D.dq; p.dkv = D.dkv; p.f = D.f; p.V = D.V; p.H = D.H; p.Hkv = D.Hkv; p.max_seq = D.max_seq; p.eps = D.eps;
     p.wait_ticks = a.wait_ticks;
-    hipError_t e;
-    if (D.wt == WT_F32) e = rows_step_launch<float, float>(D, p, a.blocks, s);
-    else if (D.wt == WT_BF16) e = D.kt == WT_F32 ? rows_step_launch<uint16_t, float>(D, p, a.blocks, s) : rows_step_launch<uint16_t, uint16_t>(D, p, a.blocks, s);
-    else e = D.kt == WT_F32 ? rows_step_launch<f16_t, float>(D, p, a.blocks, s) : rows_step_launch<f16_t, f16_t>(D, p, a.blocks, s);
+    const void* fn;
+    size_t lds;
+    hipError_t e = rows_step_fn(D, rows_step_rows(a.M), &fn, &lds);
+    if (e != hipSuccess) return e;
+    void* args[] = {&p};
+    e = hipLaunchKernel(fn, dim3(a.blocks), dim3(ST_THREADS), args, lds, s);
     if (e != hipSuccess) return e;
     return argmax_tiles(a.vmax, a.M, a.blocks, a.tok_out, a.tok_host, s, p.ctrl, 5 * D.L, a.err_host);
 }

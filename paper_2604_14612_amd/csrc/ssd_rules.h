@@ -159,10 +159,14 @@ inline StepMail step_mail(const StepShape& s)
 constexpr int RS_ROWS = 9;                     // rows that fit LDS beside each other (16-bit weights: 12 KB each) and the registers
 constexpr int RS_KEY_BYTES = 128 * 1024;       // K bytes of a head that one block walks
 
-// One block per head and row walks the whole context.
-inline bool rows_step_fits(const StepShape& s, int M, int ctx, int blocks)
+// Rows that the kernel for M rows computes.
+SSD_HD int rows_step_rows(int M) { return M <= 3 ? 3 : M <= 5 ? 5 : RS_ROWS; }
+
+// One block per head and row walks the whole context.  max_rows: rows of the widest kernel whose blocks are resident on the device.
+inline bool rows_step_fits(const StepShape& s, int M, int ctx, int blocks, int max_rows)
 {
-    return M >= 2 && M <= RS_ROWS && ctx >= M && s.H * M <= blocks && (long)ctx * s.hd * (s.kt == 0 ? 4 : 2) <= RS_KEY_BYTES;
+    return M >= 2 && M <= RS_ROWS && rows_step_rows(M) <= max_rows && ctx >= M && s.H * M <= blocks &&
+           (long)ctx * s.hd * (s.kt == 0 ? 4 : 2) <= RS_KEY_BYTES;
 }
 
 // Hand-over words, RS_ROWS of each: residual rows twice, q / k / v, attention output, FFN activations.

@@ -24,7 +24,8 @@ void rmail(const int* s, long* o) {
     const RowsMail m = rows_mail(StepShape{s[0], s[1], s[2], s[3], s[4], s[5], s[6], s[7], s[8], s[9]});
     o[0] = m.x; o[1] = m.qkv; o[2] = m.att; o[3] = m.act; o[4] = m.total;
 }
-int rows_fit(const int* s, int M, int ctx, int nb) { return rows_step_fits(StepShape{s[0], s[1], s[2], s[3], s[4], s[5], s[6], s[7], s[8], s[9]}, M, ctx, nb); }
+int rows_fit(const int* s, int M, int ctx, int nb, int max_rows) { return rows_step_fits(StepShape{s[0], s[1], s[2], s[3], s[4], s[5], s[6], s[7], s[8], s[9]}, M, ctx, nb, max_rows); }
+int rows_of(int M) { return rows_step_rows(M); }
 int limits(int i) { const int v[] = {ST_WAVES, ST_GU, ST_CD, ST_CF, AW_MAX_RANGES, ST_WAIT_WORDS, RS_ROWS}; return v[i]; }
 }
 """
@@ -81,7 +82,11 @@ def test_every_unit_has_one_owner_within_the_limits(rules, shape, cus):
     sizes = (2 * rows * d, rows * (dq + 2 * dkv), rows * dq, rows * f)
     assert o[0] == 0 and all(o[i] + sizes[i] <= o[i + 1] for i in range(4)) and all(v % 2 == 0 for v in o[:4])
     for M in range(rows + 2):   # a block per head and row; no row count beyond the layout
-        assert rules.rows_fit(s, M, 64, nb) == int(2 <= M <= rows and H * M <= nb)
+        assert rules.rows_fit(s, M, 64, nb, rows) == int(2 <= M <= rows and H * M <= nb)
+        # .. and none whose kernel would not be resident
+        for most in (0, 3, 5, rows):
+            assert rules.rows_fit(s, M, 64, nb, most) == int(2 <= M <= most and H * M <= nb)
+    assert [rules.rows_of(M) for M in range(2, rows + 1)] == [3, 3, 5, 5] + [rows] * (rows - 5)
 
 
 @pytest.mark.parametrize("shape", [(1040, 1024, 1024, 2816, 32000, 64, 16, 16, 1, 0), (1024, 1024, 1024, 3088, 32000, 64, 16, 16, 1, 0),
