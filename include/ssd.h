@@ -316,7 +316,8 @@ SSD_API int ssd_profile_read(ssd_ctx *ctx, int64_t *launches_out, double *total_
  * every call while ssd_profile_select times a kernel.  The two add in different orders, so the last bits of a call's logits, and a
  * token whose arg-max hangs on them, can depend on what other contexts do at that time.  A wait inside that takes longer than
  * wait_us (CUs held by another process or stream) ends the launch; the call then does its work again with a launch per
- * matrix and returns those results, and so do the calls behind it until ssd_reset.
+ * matrix and returns those results, and so do the calls behind it until ssd_reset, or until a growing number of resets where
+ * the next tries end the same way.
  *   enable   0: this context always uses a launch per matrix (the same bits whatever runs beside it; other streams' kernels find
  *            free CUs sooner); 1 (default): one launch where the shape allows it
  *   wait_us  bound of one wait; 0: 50 ms (default); < 0: whoever does not find its data at the first look gives up (tests)

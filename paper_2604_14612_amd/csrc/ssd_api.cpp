@@ -162,7 +162,7 @@ struct ssd_ctx {
     int step_blocks;   // blocks of a single-row step in one launch, 0 = not for this shape or device
     int step_max_rows; // most rows of a verification in one launch there
     bool step_table;   // its weight table is on the device
-    bool step_off;     // a wait gave up since the last reset: launches per matrix
+    StepBackoff step_try;   // a wait gave up: launches per matrix for a while
     bool step_on;      // the caller wants it (ssd_set_one_launch)
     long step_ticks;   // bound of its waits
     int64_t step_count, step_verify_count, step_gave_up;   // steps and verifications that ran so, calls that did not end so
@@ -625,7 +625,7 @@ template <typename F>
 int run_steps(ssd_ctx* c, const std::string& key, bool fits, int64_t& counter, int n, F&& body)
 {
     {
-        StepSlot slot(c, c->step_on && c->step_blocks > 0 && c->step_table && !c->step_off && fits && c->prof_kid < 0);
+        StepSlot slot(c, c->step_on && c->step_blocks > 0 && c->step_table && c->step_try.on() && fits && c->prof_kid < 0);
         if (c->step_now) {
             c->pinned[PIN_STEP] = 0;
             int rc = run_sequence(c, "P" + key, body);
@@ -634,10 +634,11 @@ int run_steps(ssd_ctx* c, const std::string& key, bool fits, int64_t& counter, i
             if (rs) return rs;
             if (!c->pinned[PIN_STEP]) {
                 counter += n;
+                c->step_try.ran = true;
                 return SSD_OK;
             }
             c->step_gave_up++;
-            c->step_off = true;
+            c->step_try.gave_up();
             HIPCHK(hipMemsetAsync(c->ws + c->lay.step + 4, 0, 4, c->stream), "step error clear");
         }
     }
@@ -785,7 +786,7 @@ int ssd_create(const ssd_config* cfg, void* hip_stream, ssd_ctx** out)
     c->n = 0; c->k_pending = 0; c->tap_rows = 0; c->tap_row0 = 0; c->logit_rows = 0; c->ring_count = 0; c->pinned = nullptr; c->device = -1; c->static_scratch = nullptr;
     memset(&c->st, 0, sizeof(c->st));
     memset(&c->w, 0, sizeof(c->w));
-    c->step_blocks = c->step_max_rows = 0; c->step_table = c->step_off = c->step_now = false;
+    c->step_blocks = c->step_max_rows = 0; c->step_table = c->step_now = false;
     c->step_on = true; c->step_ticks = STEP_WAIT_US * STEP_TICKS_PER_US;
     c->step_count = c->step_verify_count = c->step_gave_up = 0;
     c->prof_kid = -1; c->prof_used = 0;
@@ -869,7 +870,7 @@ int ssd_reset(ssd_ctx* c)
     if (c->state == ST_CREATED) return fail(c, SSD_ESTATE, "nothing to reset");
     c->state = ST_READY;
     c->n = 0; c->k_pending = 0; c->tap_rows = 0; c->logit_rows = 0; c->ring_count = 0;
-    c->step_off = false;
+    c->step_try.reset();
     memset(&c->st, 0, sizeof(c->st));
     return SSD_OK;
 }
@@ -1228,7 +1229,7 @@ int ssd_set_one_launch(ssd_ctx* c, int enable, int wait_us)
     if (ticks != c->step_ticks) drop_graphs(c);   // the bound is an argument of the captured launches
     c->step_ticks = ticks;
     c->step_on = enable != 0;
-    c->step_off = false;
+    c->step_try = StepBackoff();
     return SSD_OK;
 }
 

@@ -154,6 +154,30 @@ inline StepMail step_mail(const StepShape& s)
     return m;
 }
 
+// When a context tries one launch again behind one that gave up, which cost it the bound of a wait (50 ms; requests of these models
+// take 2 to 20).  Not before the next reset; and where it fails again, because another process keeps the CUs or the stream may not
+// use all of them, only behind 3, 7, .. 1023 more: a thousand requests lose at most ten waits instead of a thousand.  Sixteen
+// sequences that went well make up for one give-up.
+struct StepBackoff {
+    int fails = 0;       // give-ups not made up for
+    int skip = 0;        // resets until the next try
+    int good = 0;        // sequences in a row that went well
+    bool ran = false;    // a call of this sequence ended as one launch
+    bool on() const { return skip == 0; }
+    void gave_up()
+    {
+        if (fails < 10) fails++;
+        skip = (1 << fails) - 1;
+        good = 0;
+    }
+    void reset()
+    {
+        if (skip > 0) skip--;
+        else if (ran && ++good == 16) { good = 0; if (fails > 0) fails--; }
+        ran = false;
+    }
+};
+
 // ---- whole verifications in one launch -----------------------------------------------------------------------------------
 // The same for the k + 1 rows of a verification, see rows_step_kernel.
 constexpr int RS_ROWS = 9;                     // rows that fit LDS beside each other (16-bit weights: 12 KB each) and the registers

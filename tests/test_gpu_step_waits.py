@@ -70,3 +70,18 @@ def test_calls_that_give_up_return_the_results_of_the_other_path(name, graphs):
     assert d == o.draft(mask, 3) and ctx.ssd_verify(d) == o.verify(d)
     rows(4, o.last_logits, "verify behind")
     assert ctx.ssd_get_one_launch() == (steps + 6, verifications + 1, gave_up)
+
+
+def test_requests_of_a_context_whose_launches_keep_giving_up():
+    """Every request of a context that cannot have all CUs used to wait its bound out once."""
+    shape, kv = SHAPES["fp32"]
+    orc, ctx = make_pair(shape, 21, 64, norm_gain_std=0.1, kv_dtype=kv)
+    ctx.ssd_set_one_launch(True, -1)
+    prompt = make_prompt(shape.vocab, 8, 6).tolist()
+    o = OracleSSD(orc)
+    want = [o.prefill(prompt)] + [o.decode() for _ in range(3)]
+    for _ in range(100):
+        assert [ctx.ssd_prefill(prompt)] + [ctx.ssd_decode() for _ in range(3)] == want
+        ctx.ssd_reset()
+    steps, _, gave_up = ctx.ssd_get_one_launch()
+    assert 1 <= gave_up <= 7 + steps // 16, (steps, gave_up)

@@ -26,6 +26,19 @@ void rmail(const int* s, long* o) {
 }
 int rows_fit(const int* s, int M, int ctx, int nb, int max_rows) { return rows_step_fits(StepShape{s[0], s[1], s[2], s[3], s[4], s[5], s[6], s[7], s[8], s[9]}, M, ctx, nb, max_rows); }
 int rows_of(int M) { return rows_step_rows(M); }
+int tries(int resets, int bad, int seqs_behind) {   // launches that give up in `resets` sequences whose first `bad` tries fail
+    StepBackoff b;
+    int gave_up = 0, first_good = -1;
+    for (int r = 0; r < resets; r++) {
+        if (b.on()) {
+            if (gave_up < bad) { b.gave_up(); gave_up++; }
+            else { b.ran = true; if (first_good < 0) first_good = r; }
+        }
+        b.reset();
+        if (first_good >= 0 && r - first_good + 1 == seqs_behind) return b.fails;
+    }
+    return seqs_behind ? -1 : gave_up;
+}
 int limits(int i) { const int v[] = {ST_WAVES, ST_GU, ST_CD, ST_CF, AW_MAX_RANGES, ST_WAIT_WORDS, RS_ROWS}; return v[i]; }
 }
 """
@@ -87,6 +100,15 @@ def test_every_unit_has_one_owner_within_the_limits(rules, shape, cus):
         for most in (0, 3, 5, rows):
             assert rules.rows_fit(s, M, 64, nb, most) == int(2 <= M <= most and H * M <= nb)
     assert [rules.rows_of(M) for M in range(2, rows + 1)] == [3, 3, 5, 5] + [rows] * (rows - 5)
+
+
+def test_a_launch_that_keeps_giving_up_is_tried_ever_more_rarely(rules):
+    assert rules.tries(1, 10 ** 6, 0) == 1 and rules.tries(2, 10 ** 6, 0) == 2      # tried again behind the first reset
+    assert rules.tries(1000, 10 ** 6, 0) <= 10
+    assert rules.tries(20000, 10 ** 6, 0) <= 10 + 20000 // 1023 + 1                 # never given up for good
+    for bad in (1, 2, 5):                                                           # and forgotten where it goes well again
+        assert rules.tries(10 ** 5, bad, 15) == bad and rules.tries(10 ** 5, bad, 16) == bad - 1
+        assert rules.tries(10 ** 5, bad, 16 * bad) == 0 == rules.tries(10 ** 5, bad, 16 * bad + 1000)
 
 
 @pytest.mark.parametrize("shape", [(1040, 1024, 1024, 2816, 32000, 64, 16, 16, 1, 0), (1024, 1024, 1024, 3088, 32000, 64, 16, 16, 1, 0),
