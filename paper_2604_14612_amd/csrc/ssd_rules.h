@@ -181,7 +181,10 @@ struct StepBackoff {
 // ---- whole verifications in one launch -----------------------------------------------------------------------------------
 // The same for the k + 1 rows of a verification, see rows_step_kernel.
 constexpr int RS_ROWS = 9;                     // rows that fit LDS beside each other (16-bit weights: 12 KB each) and the registers
-constexpr int RS_KEY_BYTES = 128 * 1024;       // K bytes of a head that one block walks
+// K bytes of a head that one block walks.  Measured up to there, one launch against a launch per matrix, us per verification, 2 and 9
+// rows, 8 layers: 16-bit cache of 64-wide heads, 1000 positions 195 / 315 and 296 / 364; fp32 cache, 256 positions 182 / 293 and
+// 272 / 328, of 128-wide heads, 128 positions (16 layers) 322 / 542 and 487 / 624.  It is no line where the two meet.
+constexpr int RS_KEY_BYTES = 128 * 1024;
 
 // Rows that the kernel for M rows computes.
 SSD_HD int rows_step_rows(int M) { return M <= 3 ? 3 : M <= 5 ? 5 : RS_ROWS; }
@@ -189,6 +192,14 @@ SSD_HD int rows_step_rows(int M) { return M <= 3 ? 3 : M <= 5 ? 5 : RS_ROWS; }
 // One block per head and row walks the whole context.  max_rows: rows of the widest kernel whose blocks are resident on the device.
 inline bool rows_step_fits(const StepShape& s, int M, int ctx, int blocks, int max_rows)
 {
+    // Six to eight rows cost what nine do, and up to AT_CHUNK positions a launch per matrix has its cheapest attention (16-bit caches of
+    // 64-wide heads: one range, no fold).  There the two are within 2 % of each other for bf16 weights, and a launch per matrix is ahead
+    // where the FFN, whose activations are most of what is handed over, is wide for the model (us, 6 rows, 16 layers, one launch / per
+    // matrix: 512 x 2560 414 / 408, 256 x 3072 405 / 396, 768 x 3072 463 / 460; but 1024 x 2816 466 / 486, 512 x 2048 395 / 397) and for
+    // fp16 weights, whose conversion costs more (1024 x 2816 510 / 479, 768 x 2048 467 / 435, 512 x 1408 401 / 388).  Shapes outside its
+    // tiling have no such attention to lose to (256 x 688, fp16: 382 / 514), nor have 128-wide heads (fp16 507 / 504, 8 rows 508 / 529).
+    const bool tiled = s.d % 64 == 0 && s.dq % 64 == 0 && s.f % 64 == 0;
+    if (M > 5 && M < RS_ROWS && ctx <= AT_CHUNK && s.wt != 0 && s.kt != 0 && s.hd == 64 && tiled && (s.wt == 2 || s.f >= 4 * s.d)) return false;
     return M >= 2 && M <= RS_ROWS && rows_step_rows(M) <= max_rows && ctx >= M && s.H * M <= blocks &&
            (long)ctx * s.hd * (s.kt == 0 ? 4 : 2) <= RS_KEY_BYTES;
 }

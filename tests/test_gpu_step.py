@@ -42,7 +42,8 @@ def test_drafts_and_verification_at_the_limits(name, plen):
     mask[1] = 1
     st = lockstep_ssd(ctx, orc, prompt, 0, [6, 1, 4], mask, shape.dtype)
     assert st["unpinned_cycles"] <= 1 and st["draft_rows"] >= 5
-    assert ctx.ssd_get_one_launch() == (0 if name in STEPS_PER_MATRIX else 11, 0 if name in VERIFICATIONS_PER_MATRIX else 3, 0)
+    verifications = 0 if name in VERIFICATIONS_PER_MATRIX else 2 if name == "widest16" and plen == 1 else 3   # (seven rows of fp16 over 8 positions)
+    assert ctx.ssd_get_one_launch() == (0 if name in STEPS_PER_MATRIX else 11, verifications, 0)
 
 
 # rows of a verification around what the kernel is compiled for (3, 5, 9; 10 take the launches per matrix), contexts of one pass over

@@ -95,11 +95,25 @@ def test_every_unit_has_one_owner_within_the_limits(rules, shape, cus):
     sizes = (2 * rows * d, rows * (dq + 2 * dkv), rows * dq, rows * f)
     assert o[0] == 0 and all(o[i] + sizes[i] <= o[i + 1] for i in range(4)) and all(v % 2 == 0 for v in o[:4])
     for M in range(rows + 2):   # a block per head and row; no row count beyond the layout
-        assert rules.rows_fit(s, M, 64, nb, rows) == int(2 <= M <= rows and H * M <= nb)
+        assert rules.rows_fit(s, M, 100, nb, rows) == int(2 <= M <= rows and H * M <= nb)
         # .. and none whose kernel would not be resident
         for most in (0, 3, 5, rows):
-            assert rules.rows_fit(s, M, 64, nb, most) == int(2 <= M <= most and H * M <= nb)
+            assert rules.rows_fit(s, M, 100, nb, most) == int(2 <= M <= most and H * M <= nb)
     assert [rules.rows_of(M) for M in range(2, rows + 1)] == [3, 3, 5, 5] + [rows] * (rows - 5)
+
+
+# where six to eight rows are faster with a launch per matrix: measured at these shapes on both sides of every edge
+@pytest.mark.parametrize("shape,wt,kt,slow", [
+    ((1024, 1024, 1024, 2816, 32000, 64, 16, 16), 2, 2, True), ((1024, 1024, 1024, 2816, 32000, 64, 16, 16), 1, 1, False),
+    ((1024, 1024, 1024, 2816, 32000, 64, 16, 16), 2, 0, False), ((256, 256, 256, 688, 1024, 64, 4, 4), 2, 2, False),
+    ((512, 512, 512, 2560, 1024, 64, 8, 8), 1, 1, True), ((512, 512, 512, 1984, 1024, 64, 8, 8), 1, 1, False),
+    ((768, 768, 768, 3072, 1024, 64, 12, 12), 1, 1, True), ((512, 512, 512, 3072, 1024, 64, 8, 8), 1, 0, False),
+    ((1024, 1024, 1024, 2816, 32000, 128, 8, 8), 2, 2, False), ((512, 512, 512, 1536, 1024, 64, 8, 8), 0, 0, False)])
+def test_six_to_eight_rows_over_short_contexts(rules, shape, wt, kt, slow):
+    s = (C.c_int * 10)(*shape, wt, kt)
+    for M in range(2, 10):
+        for ctx in (10, 96, 97, 200):
+            assert rules.rows_fit(s, M, ctx, 256, 9) == int(not (slow and M in (6, 7, 8) and ctx <= 96)), (M, ctx)
 
 
 def test_a_launch_that_keeps_giving_up_is_tried_ever_more_rarely(rules):
