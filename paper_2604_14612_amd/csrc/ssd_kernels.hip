@@ -3797,7 +3797,7 @@ __device__ __forceinline__ void mail_take(const int (&pair)[N], float2 (&v)[N], 
 #pragma unroll
         for (int u = 0; u < N; u++) ok = ok && ((w[u].y == tag && w[u].w == tag) || pair[u] >= n_pairs);
         if (__all(ok) || !alive) break;
-        if ((++spins & 63) == 0 || wait_ticks < 0) {   // (negative: nobody waits longer than one look)
+        if ((++spins & 63) == 0) {
             const long now = wall_clock64();
             if (t0 == 0) t0 = now;
             if (__hip_atomic_load(ctrl + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) alive = false;

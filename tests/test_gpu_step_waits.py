@@ -1,12 +1,12 @@
-"""GPU: one-launch steps and verifications whose waits give up.  With a negative bound every wait that does not find its words at
-the first look gives up: the launches drain by themselves, nothing of them may be committed, and the call's results are those of
-the launches per matrix."""
+"""GPU: one-launch steps and verifications that give up, because the caller asks for it (a negative bound: the error word is set
+when the launch begins) or because a neighbour holds CUs for longer than a bound of some 100 us.  The launches drain by
+themselves, nothing of them may be committed, and the call's results are those of the launches per matrix."""
 import numpy as np
 import pytest
 
 from oracle import OracleSSD
 from synth import ModelShape, make_prompt
-from tests._parity import assert_logits_close, make_pair
+from tests._parity import assert_logits_close, decisive, make_pair
 
 pytestmark = pytest.mark.gpu
 
@@ -59,8 +59,7 @@ def test_calls_that_give_up_return_the_results_of_the_other_path(name, graphs):
         assert ctx.ssd_accept(d, y) == o.accept(d, y)
         assert ctx.ssd_get_stats()["n_tokens"] == o.n
     steps, verifications, gave_up = ctx.ssd_get_one_launch()
-    # (a call may end as one launch after all: where every wait found its words at once)
-    assert gave_up >= calls // 2 and steps + verifications <= 4 * (calls - gave_up), (calls, steps, verifications, gave_up)
+    assert (steps, verifications, gave_up) == (0, 0, calls)
     # with the usual bound the same context goes on in one launch per step
     ctx.ssd_set_one_launch(True)
     for _ in range(3):
@@ -70,6 +69,34 @@ def test_calls_that_give_up_return_the_results_of_the_other_path(name, graphs):
     assert d == o.draft(mask, 3) and ctx.ssd_verify(d) == o.verify(d)
     rows(4, o.last_logits, "verify behind")
     assert ctx.ssd_get_one_launch() == (steps + 6, verifications + 1, gave_up)
+
+
+def test_a_neighbour_that_holds_the_compute_units():
+    """Matrix products on another stream: blocks of a step come to their CUs one after the other, and the ones that are there wait
+    for longer than the bound."""
+    import torch
+    shape, kv = SHAPES["bf16"]
+    orc, ctx = make_pair(shape, 21, 128, norm_gain_std=0.1, kv_dtype=kv)
+    ctx.ssd_set_one_launch(True, 1)
+    prompt = make_prompt(shape.vocab, 40, 6).tolist()
+    o = OracleSSD(orc)
+    assert ctx.ssd_prefill(prompt) == o.prefill(prompt)
+    a = torch.randn(8192, 8192, device="cuda", dtype=torch.bfloat16)
+    out, side = torch.empty_like(a), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for step in range(60):
+        if step % 10 == 0:
+            torch.cuda.synchronize()
+            with torch.cuda.stream(side):
+                for _ in range(20):             # about 20 ms
+                    torch.mm(a, a, out=out)
+        ctx.ssd_set_one_launch(True, 1)         # one launch again, whatever the step before did
+        want, got = o.decode(), ctx.ssd_decode()
+        assert_logits_close(ctx.ssd_copy_logits(0, 1)[0], o.last_logits[0], shape.dtype, "step %d" % step)
+        assert got == want, "a tie below the tolerance: pick another seed" if not decisive(o.last_logits[0], shape.dtype) else step
+    torch.cuda.synchronize()
+    steps, _, gave_up = ctx.ssd_get_one_launch()
+    assert steps + gave_up == 60 and gave_up >= 1, (steps, gave_up)
 
 
 def test_requests_of_a_context_whose_launches_keep_giving_up():
@@ -84,4 +111,4 @@ def test_requests_of_a_context_whose_launches_keep_giving_up():
         assert [ctx.ssd_prefill(prompt)] + [ctx.ssd_decode() for _ in range(3)] == want
         ctx.ssd_reset()
     steps, _, gave_up = ctx.ssd_get_one_launch()
-    assert 1 <= gave_up <= 7 + steps // 16, (steps, gave_up)
+    assert steps == 0 and 4 <= gave_up <= 7
