@@ -4804,7 +4804,7 @@ __global__ __launch_bounds__(ST_THREADS) void rows_step_kernel(RowsStepP p)
     }
 }
 
-static StepShape step_shape(const Dims& D) { return {D.d, D.dq, D.dkv, D.f, D.V, D.hd, D.H, D.Hkv, D.wt, D.kt}; }
+static StepShape step_shape(const Dims& D) { return {D.d, D.dq, D.dkv, D.f, D.V, D.hd, D.H, D.Hkv, D.wt, D.kt, D.L}; }
 
 size_t step_scratch_bytes(const Dims& D)
 {

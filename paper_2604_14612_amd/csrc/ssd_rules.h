@@ -117,7 +117,7 @@ constexpr int ST_CD = 2, ST_CF = 6;     // 16-byte loads per lane and row that a
 constexpr int ST_BLOCKS = 256;
 constexpr int ST_WAIT_WORDS = 8;        // control words in front of the hand-over words: launch number, error flag
 
-struct StepShape { int d, dq, dkv, f, V, hd, H, Hkv; int wt, kt; };   // wt, kt: WeightType codes
+struct StepShape { int d, dq, dkv, f, V, hd, H, Hkv; int wt, kt; int L; };   // wt, kt: WeightType codes
 
 // First of the n units (row pairs, rows) that block b of nb owns; it owns those up to the next block's first.
 SSD_HD int step_begin(int n, int b, int nb) { return (int)((long)n * b / nb); }
@@ -136,6 +136,11 @@ inline int step_blocks(const StepShape& s, int cus)
     int nb = cus < ST_BLOCKS ? cus : ST_BLOCKS;
     if (nb > s.d) nb = s.d;
     if (nb < 1) return 0;
+    // Models of less width than the device has CUs: the LM head streams through d of them only.  A wave's row pairs beyond some 24 cost 0.4 us
+    // each, a layer in one launch gains 8 to 9 (us per step, one launch / per matrix, 1 layer and 4: 64 x 32000 53 / 51 and 79 / 105,
+    // 64 x 128256 96 / 62 and 124 / 116, 128 x 128256 69 / 62 and 96 / 117, 192 x 128256 60 / 62 and 89 / 117); 14 pairs per layer, since a
+    // draft leaves layers out.
+    if (nb < cus && s.V / 2 > nb * ST_WAVES * (24 + 14 * (s.L - 1))) return 0;
     if (ceil_div(s.d, nb) > ST_WAVES || ceil_div((s.dq + 2 * s.dkv) / 2, nb) > ST_WAVES || ceil_div(s.f, nb) > ST_GU * ST_WAVES) return 0;
     return nb;
 }
@@ -182,8 +187,8 @@ struct StepBackoff {
 // The same for the k + 1 rows of a verification, see rows_step_kernel.
 constexpr int RS_ROWS = 9;                     // rows that fit LDS beside each other (16-bit weights: 12 KB each) and the registers
 // K bytes of a head that one block walks.  Measured up to there, one launch against a launch per matrix, us per verification, 2 and 9
-// rows, 8 layers: 16-bit cache of 64-wide heads, 1000 positions 195 / 315 and 296 / 364; fp32 cache, 256 positions 182 / 293 and
-// 272 / 328, of 128-wide heads, 128 positions (16 layers) 322 / 542 and 487 / 624.  It is no line where the two meet.
+// rows, 8 layers: 16-bit cache of 64-wide heads, 1000 positions 194 / 315 and 297 / 363; fp32 cache, 256 positions 182 / 294 and
+// 275 / 330, of 128-wide heads, 128 positions (16 layers) 322 / 542 and 487 / 624.  It is no line where the two meet.
 constexpr int RS_KEY_BYTES = 128 * 1024;
 
 // Rows that the kernel for M rows computes.
@@ -195,9 +200,9 @@ inline bool rows_step_fits(const StepShape& s, int M, int ctx, int blocks, int m
     // Six to eight rows cost what nine do, and up to AT_CHUNK positions a launch per matrix has its cheapest attention (16-bit caches of
     // 64-wide heads: one range, no fold).  There the two are within 2 % of each other for bf16 weights, and a launch per matrix is ahead
     // where the FFN, whose activations are most of what is handed over, is wide for the model (us, 6 rows, 16 layers, one launch / per
-    // matrix: 512 x 2560 414 / 408, 256 x 3072 405 / 396, 768 x 3072 463 / 460; but 1024 x 2816 466 / 486, 512 x 2048 395 / 397) and for
-    // fp16 weights, whose conversion costs more (1024 x 2816 510 / 479, 768 x 2048 467 / 435, 512 x 1408 401 / 388).  Shapes outside its
-    // tiling have no such attention to lose to (256 x 688, fp16: 382 / 514), nor have 128-wide heads (fp16 507 / 504, 8 rows 508 / 529).
+    // matrix: 512 x 2560 413 / 411, 256 x 3072 409 / 398, 768 x 3072 463 / 452; but 1024 x 2816 466 / 492, 512 x 2048 394 / 395) and for
+    // fp16 weights, whose conversion costs more (1024 x 2816 513 / 486, 768 x 2048 467 / 431, 512 x 1408 399 / 388).  Shapes outside its
+    // tiling have no such attention to lose to (256 x 688, fp16: 384 / 503), nor have 128-wide heads (fp16 507 / 512, 8 rows 507 / 529).
     const bool tiled = s.d % 64 == 0 && s.dq % 64 == 0 && s.f % 64 == 0;
     if (M > 5 && M < RS_ROWS && ctx <= AT_CHUNK && s.wt != 0 && s.kt != 0 && s.hd == 64 && tiled && (s.wt == 2 || s.f >= 4 * s.d)) return false;
     return M >= 2 && M <= RS_ROWS && rows_step_rows(M) <= max_rows && ctx >= M && s.H * M <= blocks &&

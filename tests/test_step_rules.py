@@ -13,18 +13,20 @@ CSRC = os.path.join(ROOT, "paper_2604_14612_amd", "csrc")
 WRAPPERS = r"""
 #include "ssd_rules.h"
 using namespace ssdk;
+static int layers = 4;
 extern "C" {
-int blocks(const int* s, int cus) { return step_blocks(StepShape{s[0], s[1], s[2], s[3], s[4], s[5], s[6], s[7], s[8], s[9]}, cus); }
+void set_layers(int n) { layers = n; }
+int blocks(const int* s, int cus) { return step_blocks(StepShape{s[0], s[1], s[2], s[3], s[4], s[5], s[6], s[7], s[8], s[9], layers}, cus); }
 int begin(int n, int b, int nb) { return step_begin(n, b, nb); }
 void mail(const int* s, long* o) {
-    const StepMail m = step_mail(StepShape{s[0], s[1], s[2], s[3], s[4], s[5], s[6], s[7], s[8], s[9]});
+    const StepMail m = step_mail(StepShape{s[0], s[1], s[2], s[3], s[4], s[5], s[6], s[7], s[8], s[9], layers});
     o[0] = m.x; o[1] = m.qkv; o[2] = m.part; o[3] = m.act; o[4] = m.total;
 }
 void rmail(const int* s, long* o) {
-    const RowsMail m = rows_mail(StepShape{s[0], s[1], s[2], s[3], s[4], s[5], s[6], s[7], s[8], s[9]});
+    const RowsMail m = rows_mail(StepShape{s[0], s[1], s[2], s[3], s[4], s[5], s[6], s[7], s[8], s[9], layers});
     o[0] = m.x; o[1] = m.qkv; o[2] = m.att; o[3] = m.act; o[4] = m.total;
 }
-int rows_fit(const int* s, int M, int ctx, int nb, int max_rows) { return rows_step_fits(StepShape{s[0], s[1], s[2], s[3], s[4], s[5], s[6], s[7], s[8], s[9]}, M, ctx, nb, max_rows); }
+int rows_fit(const int* s, int M, int ctx, int nb, int max_rows) { return rows_step_fits(StepShape{s[0], s[1], s[2], s[3], s[4], s[5], s[6], s[7], s[8], s[9], layers}, M, ctx, nb, max_rows); }
 int rows_of(int M) { return rows_step_rows(M); }
 int tries(int resets, int bad, int seqs_behind) {   // launches that give up in `resets` sequences whose first `bad` tries fail
     StepBackoff b;
@@ -114,6 +116,21 @@ def test_six_to_eight_rows_over_short_contexts(rules, shape, wt, kt, slow):
     for M in range(2, 10):
         for ctx in (10, 96, 97, 200):
             assert rules.rows_fit(s, M, ctx, 256, 9) == int(not (slow and M in (6, 7, 8) and ctx <= 96)), (M, ctx)
+
+
+# fewer blocks than CUs: an LM head that is large for the width and depth streams through too few of them
+@pytest.mark.parametrize("d,V,layers,fits", [(64, 32000, 1, False), (64, 32000, 4, True), (64, 128256, 4, False), (64, 128256, 12, True),
+                                             (128, 32000, 1, True), (128, 128256, 1, False), (128, 128256, 4, True), (240, 128256, 2, True),
+                                             (256, 128256, 1, True), (1024, 256000, 1, True)])
+def test_narrow_models_with_large_vocabularies(rules, d, V, layers, fits):
+    s = (C.c_int * 10)(d, 64, 64, 176, V, 64, 1, 1, 1, 0)
+    try:
+        rules.set_layers(layers)
+        assert rules.blocks(s, 256) == (min(d, 256) if fits else 0)
+        if fits:
+            assert rules.blocks(s, min(d, 256)) == min(d, 256)      # what a launch is checked with
+    finally:
+        rules.set_layers(4)
 
 
 def test_a_launch_that_keeps_giving_up_is_tried_ever_more_rarely(rules):
