@@ -161,7 +161,7 @@ struct ssd_ctx {
     ssd_stats st;
     int step_blocks;   // blocks of a single-row step in one launch, 0 = not for this shape or device
     int step_max_rows; // most rows of a verification in one launch there
-    bool step_table;   // its weight table is on the device
+    bool step_table;   // its words are cleared, its weight table is on the device
     StepBackoff step_try;   // a wait gave up: launches per matrix for a while
     bool step_on;      // the caller wants it (ssd_set_one_launch)
     long step_ticks;   // bound of its waits
@@ -632,8 +632,10 @@ int run_steps(ssd_ctx* c, const std::string& key, bool fits, int64_t& counter, i
             if (c->step_give_up) HIPCHK(hipMemsetAsync(c->ws + c->lay.step + 4, 1, 4, c->stream), "step error set");
             int rc = run_sequence(c, "P" + key, body);
             const int rs = sync_results(c);   // the slot is free again when the launches are done
-            if (rc) return rc;
-            if (rs) return rs;
+            if (rc || rs) {
+                c->step_table = false;   // a step without its end leaves words whose tags come again: none before the next prefill clears them
+                return rc ? rc : rs;
+            }
             if (!c->pinned[PIN_STEP]) {
                 counter += n;
                 c->step_try.ran = true;
@@ -829,7 +831,6 @@ int ssd_set_workspace(ssd_ctx* c, void* dev, size_t bytes)
     HIPCHK(hipMemsetAsync(c->ws + c->lay.small, 0, 4096, c->stream), "state clear");
     HIPCHK(step_device_blocks(c->D, c->device, &c->step_blocks, &c->step_max_rows), "step occupancy");
     c->step_table = false;
-    if (c->step_blocks > 0) HIPCHK(hipMemsetAsync(c->ws + c->lay.step, 0, step_scratch_bytes(c->D), c->stream), "step clear");
     HIPCHK(hipStreamSynchronize(c->stream), "workspace sync");  // tab goes out of scope
     if (c->have_w) c->state = ST_READY;
     return SSD_OK;
@@ -905,7 +906,8 @@ int ssd_prefill(ssd_ctx* c, const int32_t* tokens, int n, int32_t* first_token_o
     for (int i = 0; i < n; i++)
         if (tokens[i] < 0 || tokens[i] >= c->D.V) return fail(c, SSD_EINVAL, "prompt token id out of range");
     HIPCHK(set_state(c->small_i() + SM_TOK, 0, c->pos_dev(), 0, c->stream), "set_state");
-    if (c->step_blocks > 0 && !c->step_table) {   // once per set of weights
+    if (c->step_blocks > 0 && !c->step_table) {   // once per workspace and set of weights
+        HIPCHK(hipMemsetAsync(c->ws + c->lay.step, 0, step_table_offset(c->D), c->stream), "step clear");
         c->step_rows.resize(c->D.L);
         for (int l = 0; l < c->D.L; l++)
             c->step_rows[l] = {{c->attn_norm[l], c->wq[l], c->wk[l], c->wv[l], c->wo[l], c->mlp_norm[l], c->wg[l], c->wu[l], c->wd[l]}};
