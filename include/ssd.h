@@ -320,7 +320,8 @@ SSD_API int ssd_profile_read(ssd_ctx *ctx, int64_t *launches_out, double *total_
  * the next tries end the same way.
  *   enable   0: this context always uses a launch per matrix (the same bits whatever runs beside it; other streams' kernels find
  *            free CUs sooner); 1 (default): one launch where the shape allows it
- *   wait_us  bound of one wait (about 100 us at least); 0: 50 ms (default); < 0: every such launch gives up at once (tests)
+ *   wait_us  bound of one wait (some 100 us at least); 0: 50 ms (default); < 0: the least, and every such launch of an fp32 model
+ *            with 64-wide heads lacks a block, so that its waits do end at the bound (test hook)
  * Forgets earlier waits that took too long.  Not while another call of the context runs, as everywhere. */
 SSD_API int ssd_set_one_launch(ssd_ctx *ctx, int enable, int wait_us);
 /* Since ssd_create: single-row steps and verifications that ran as one launch, and calls whose launch gave up. */

@@ -165,7 +165,6 @@ struct ssd_ctx {
     StepBackoff step_try;   // a wait gave up: launches per matrix for a while
     bool step_on;      // the caller wants it (ssd_set_one_launch)
     long step_ticks;   // bound of its waits
-    bool step_give_up; // every such launch is to give up at once (tests)
     int64_t step_count, step_verify_count, step_gave_up;   // steps and verifications that ran so, calls that did not end so
     bool step_now;     // the sequence being enqueued takes it
     std::vector<StepWeights> step_rows;   // host copy of the table
@@ -629,7 +628,6 @@ int run_steps(ssd_ctx* c, const std::string& key, bool fits, int64_t& counter, i
         StepSlot slot(c, c->step_on && c->step_blocks > 0 && c->step_table && c->step_try.on() && fits && c->prof_kid < 0);
         if (c->step_now) {
             c->pinned[PIN_STEP] = 0;
-            if (c->step_give_up) HIPCHK(hipMemsetAsync(c->ws + c->lay.step + 4, 1, 4, c->stream), "step error set");
             int rc = run_sequence(c, "P" + key, body);
             const int rs = sync_results(c);   // the slot is free again when the launches are done
             if (rc || rs) {
@@ -791,7 +789,7 @@ int ssd_create(const ssd_config* cfg, void* hip_stream, ssd_ctx** out)
     memset(&c->st, 0, sizeof(c->st));
     memset(&c->w, 0, sizeof(c->w));
     c->step_blocks = c->step_max_rows = 0; c->step_table = c->step_now = false;
-    c->step_on = true; c->step_give_up = false; c->step_ticks = STEP_WAIT_US * STEP_TICKS_PER_US;
+    c->step_on = true; c->step_ticks = STEP_WAIT_US * STEP_TICKS_PER_US;
     c->step_count = c->step_verify_count = c->step_gave_up = 0;
     c->prof_kid = -1; c->prof_used = 0;
     c->use_graphs = true;
@@ -1229,10 +1227,9 @@ int ssd_set_graphs(ssd_ctx* c, int enable)
 int ssd_set_one_launch(ssd_ctx* c, int enable, int wait_us)
 {
     if (!c) return SSD_EINVAL;
-    const long ticks = (wait_us <= 0 ? STEP_WAIT_US : wait_us) * STEP_TICKS_PER_US;
+    const long ticks = wait_us < 0 ? -1 : (wait_us == 0 ? STEP_WAIT_US : wait_us) * STEP_TICKS_PER_US;
     if (ticks != c->step_ticks) drop_graphs(c);   // the bound is an argument of the captured launches
     c->step_ticks = ticks;
-    c->step_give_up = wait_us < 0;
     c->step_on = enable != 0;
     c->step_try = StepBackoff();
     return SSD_OK;

@@ -93,8 +93,8 @@ hipError_t gemv_lmhead_argmax(const Dims& D, const void* wlm, const float* gain,
 // Layers, LM head and the end of the step as gemv_lmhead_argmax leaves it, by resident blocks that hand the activations to
 // each other through memory.  Blocks wait for each other: two such launches in flight on a device would each hold CUs that the other
 // one needs.  A wait that takes longer than wait_ticks (blocks that are not resident, CUs held by others) ends the launch with
-// *step_err_host = 1, nothing committed; scratch[1] (32-bit words) has to be cleared before the next launch then.  Set, it makes
-// a launch do so without waiting at all.
+// *step_err_host = 1, nothing committed; scratch[1] (32-bit words) has to be cleared before the next launch then.  wait_ticks < 0
+// (fp32, 64-wide heads): the last block leaves at once, so that the others wait in vain (tests of that path).
 constexpr long STEP_TICKS_PER_US = 100;   // of wait_ticks (looked at every 64 polls, so no bound is below some 100 us)
 struct StepWeights { const void* p[9]; };   // attention norm gain, wq, wk, wv, wo, MLP norm gain, wg, wu, wd of a layer (device table)
 size_t step_scratch_bytes(const Dims& D);   // 0: shape not supported.  Cleared to zero before the first launch, weight table excepted

@@ -3853,7 +3853,7 @@ template <int LPP> __device__ __forceinline__ float seg_max_fast(float v)
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
-template <typename WT, typename KT, int HD>
+template <typename WT, typename KT, int HD, bool LACK = false>
 __global__ __launch_bounds__(ST_THREADS) void step_kernel(StepP p)
 {
     constexpr int VEC = Elem<WT>::VEC, CH = 64 * VEC, CD = ST_CD, CF = ST_CF, XF = CF * CH;
@@ -3873,6 +3873,7 @@ __global__ __launch_bounds__(ST_THREADS) void step_kernel(StepP p)
     auto fresh = [&]() { asm volatile("" : "+v"(tid)); lane = tid & 63; };
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int b = blockIdx.x, NB = gridDim.x;
+    if (LACK && b + 1 == NB) return;   // (a test's launch: the others wait in vain.  As a run-time switch it cost a step 0.8 %)
     const int d = p.d, dq = p.dq, dkv = p.dkv, f = p.f;
     unsigned* ctrl = reinterpret_cast<unsigned*>(p.mail);
     unsigned long long* const mx = p.mail + p.off.x;
@@ -4359,7 +4360,7 @@ __device__ __forceinline__ float wave_sums(const float (&v)[N], int lane)
     return out;
 }
 
-template <typename WT, typename KT, int HD, int R>
+template <typename WT, typename KT, int HD, int R, bool LACK = false>
 __global__ __launch_bounds__(ST_THREADS) void rows_step_kernel(RowsStepP p)
 {
     constexpr int VEC = Elem<WT>::VEC, CH = 64 * VEC, CD = ST_CD, CF = ST_CF, XF = CF * CH;
@@ -4379,6 +4380,7 @@ __global__ __launch_bounds__(ST_THREADS) void rows_step_kernel(RowsStepP p)
     auto fresh = [&]() { asm volatile("" : "+v"(tid)); lane = tid & 63; };   // as above
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int b = blockIdx.x, NB = gridDim.x;
+    if (LACK && b + 1 == NB) return;
     const int d = p.d, dq = p.dq, dkv = p.dkv, f = p.f, M = p.M, nqkv = dq + 2 * dkv;
     unsigned* ctrl = p.ctrl;
     unsigned long long* const mx = p.mail + p.off.x;
@@ -4819,13 +4821,17 @@ size_t step_table_offset(const Dims& D)
     return (step_mail(s).total + rows_mail(s).total) * 8;
 }
 
+// Kernels whose last block leaves at once exist for one type and head size, which is enough to test what the others do then.
+static bool step_can_lack(const Dims& D) { return D.wt == WT_F32 && D.hd == 64; }
+
 template <typename WT, typename KT>
 static const void* step_fn(const Dims& D)
 {
     return D.hd == 64 ? (const void*)step_kernel<WT, KT, 64> : (const void*)step_kernel<WT, KT, 128>;
 }
-static const void* step_fn(const Dims& D)
+static const void* step_fn(const Dims& D, bool lack)
 {
+    if (lack && step_can_lack(D)) return (const void*)step_kernel<float, float, 64, true>;
     if (D.wt == WT_F32) return step_fn<float, float>(D);
     if (D.wt == WT_BF16) return D.kt == WT_F32 ? step_fn<uint16_t, float>(D) : step_fn<uint16_t, uint16_t>(D);
     return D.kt == WT_F32 ? step_fn<f16_t, float>(D) : step_fn<f16_t, f16_t>(D);
@@ -4836,13 +4842,13 @@ static size_t step_lds_bytes(const Dims& D)
 }
 
 // The verification kernel that computes R rows, enabled for its LDS.
-template <typename WT, typename KT, int HD>
+template <typename WT, typename KT, int HD, bool LACK = false>
 static hipError_t rows_step_fn(const Dims& D, int R, const void** fn, size_t* lds)
 {
     constexpr size_t XF = (size_t)ST_CF * 64 * Elem<WT>::VEC;
     static std::atomic<size_t> lds_limit[3];   // per instantiation
-    *fn = R == 3 ? (const void*)rows_step_kernel<WT, KT, HD, 3> : R == 5 ? (const void*)rows_step_kernel<WT, KT, HD, 5>
-                                                                         : (const void*)rows_step_kernel<WT, KT, HD, RS_ROWS>;
+    *fn = R == 3 ? (const void*)rows_step_kernel<WT, KT, HD, 3, LACK> : R == 5 ? (const void*)rows_step_kernel<WT, KT, HD, 5, LACK>
+                                                                               : (const void*)rows_step_kernel<WT, KT, HD, RS_ROWS, LACK>;
     *lds = R * XF * sizeof(float) + (size_t)D.L * sizeof(StepWeights);
     return ensure_lds(*fn, *lds, lds_limit[R == 3 ? 0 : R == 5 ? 1 : 2]);
 }
@@ -4851,8 +4857,9 @@ static hipError_t rows_step_fn(const Dims& D, int R, const void** fn, size_t* ld
 {
     return D.hd == 64 ? rows_step_fn<WT, KT, 64>(D, R, fn, lds) : rows_step_fn<WT, KT, 128>(D, R, fn, lds);
 }
-static hipError_t rows_step_fn(const Dims& D, int R, const void** fn, size_t* lds)
+static hipError_t rows_step_fn(const Dims& D, int R, bool lack, const void** fn, size_t* lds)
 {
+    if (lack && step_can_lack(D)) return rows_step_fn<float, float, 64, true>(D, R, fn, lds);
     if (D.wt == WT_F32) return rows_step_fn<float, float>(D, R, fn, lds);
     if (D.wt == WT_BF16) return D.kt == WT_F32 ? rows_step_fn<uint16_t, float>(D, R, fn, lds) : rows_step_fn<uint16_t, uint16_t>(D, R, fn, lds);
     return D.kt == WT_F32 ? rows_step_fn<f16_t, float>(D, R, fn, lds) : rows_step_fn<f16_t, f16_t>(D, R, fn, lds);
@@ -4866,14 +4873,14 @@ hipError_t step_device_blocks(const Dims& D, int device, int* blocks_out, int* m
     hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
     if (e != hipSuccess) return e;
     const size_t lds = step_lds_bytes(D);   // below 64 KB
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, step_fn(D), ST_THREADS, lds);
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, step_fn(D, false), ST_THREADS, lds);
     if (e != hipSuccess) return e;
     if (per_cu >= 1) *blocks_out = step_blocks(step_shape(D), cus);
     // the verification kernels ask for more registers and four to five times the LDS: up to the widest that fits
     for (int R : {3, 5, RS_ROWS}) {
         const void* fn;
         size_t rows_lds;
-        if (*blocks_out == 0 || rows_step_fn(D, R, &fn, &rows_lds) != hipSuccess ||
+        if (*blocks_out == 0 || rows_step_fn(D, R, false, &fn, &rows_lds) != hipSuccess ||
             hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, ST_THREADS, rows_lds) != hipSuccess || per_cu < 1) {
             (void)hipGetLastError();   // a kernel that does not fit is no error of this call
             break;
@@ -4913,7 +4920,8 @@ hipError_t step_fused(const Dims& D, const StepLaunch& a, const StepOut& o, hipS
     p.n_splits = pl.n_splits; p.chunk = pl.chunk;
     p.wait_ticks = a.wait_ticks;
     void* args[] = {&p};
-    hipError_t e = hipLaunchKernel(step_fn(D), dim3(a.blocks), dim3(ST_THREADS), args, step_lds_bytes(D), s);
+    const void* fn = step_fn(D, a.wait_ticks < 0 && out.step_hops > 0);   // (without a layer nobody waits for anybody)
+    hipError_t e = hipLaunchKernel(fn, dim3(a.blocks), dim3(ST_THREADS), args, step_lds_bytes(D), s);
     if (e != hipSuccess) return e;
     return step_finish(D, a.vstat, a.blocks, out, s);
 }
@@ -4939,7 +4947,7 @@ hipError_t rows_step_fused(const Dims& D, const RowsStepLaunch& a, hipStream_t s
     p.wait_ticks = a.wait_ticks;
     const void* fn;
     size_t lds;
-    hipError_t e = rows_step_fn(D, rows_step_rows(a.M), &fn, &lds);
+    hipError_t e = rows_step_fn(D, rows_step_rows(a.M), a.wait_ticks < 0, &fn, &lds);
     if (e != hipSuccess) return e;
     void* args[] = {&p};
     e = hipLaunchKernel(fn, dim3(a.blocks), dim3(ST_THREADS), args, lds, s);
