@@ -171,7 +171,8 @@ hipError_t rows_plain(const Dims& D, const RowsPlain& g, hipStream_t s);
 // or a RESID projection with gain_out).
 //   mode 0 store fp32, 1 residual add into y (+ tap), 2 SwiGLU of two matrices written as hi/lo to
 //   oh/ol, 3 QKV: rotary on q and k at positions *pos_dev + pos_off + r, q -> y [M][dq] fp32,
-//   k and v -> cache rows.
+//   k and v -> cache rows.  n[0] = 0 (rows_wide, rows_big: keys and values only) and n[1] = n[2] = 0 (rows_fused: queries only)
+//   leave out the others.
 // RMSNorm without a kernel: a mode-1 call with gain_out set also writes split(y * gain_out) to oh/ol
 // [M][ldo] and the sums of y^2 over each 16-column tile to ssq_out [M][n/16]; a mode-0/2/3 call with
 // ssq set treats bh/bl as such un-normalised rows and scales its results by

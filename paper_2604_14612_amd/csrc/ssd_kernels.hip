@@ -2322,7 +2322,7 @@ static void fill_rows_params(const Dims& D, const RowsFused& f, RowsP2& p)
     for (int i = 0; i < 3; i++) { p.w[i] = f.w[i]; p.n[i] = f.n[i]; }
     p.K = f.K; p.bh = f.bh; p.bl = f.bl; p.ldb = f.ldb; p.y = f.y; p.ldy = f.ldy; p.oh = f.oh; p.ol = f.ol; p.ldo = f.ldo;
     p.tap = f.tap; p.tap_ld = f.tap_ld; p.M = f.M; p.rope = f.rope; p.pos_dev = f.pos_dev; p.pos_off = f.pos_off;
-    p.hd = D.hd; p.dq = D.dq; p.dkv = D.dkv; p.max_seq = D.max_seq; p.kc = f.kc; p.vc = f.vc; p.kt = D.kt;
+    p.hd = D.hd; p.dq = f.mode == RM_QKV ? f.n[0] : D.dq; p.dkv = D.dkv; p.max_seq = D.max_seq; p.kc = f.kc; p.vc = f.vc; p.kt = D.kt;
     p.ssq = f.ssq; p.n_ssq = f.n_ssq; p.eps = D.eps; p.gain_out = f.gain_out; p.ssq_out = f.ssq_out;
     p.tap_only = f.tap_only; p.vmax = f.vmax; p.clamp = f.clamp;
 }
@@ -2333,7 +2333,7 @@ hipError_t rows_wide(const Dims& D, const RowsFused& f, hipStream_t s)
     if (f.n[0] % 64 || f.n[1] % 64 || f.n[2] % 64) return hipErrorInvalidValue;
     if (f.ssq && (f.mode == RM_RESID || f.n_ssq < 1)) return hipErrorInvalidValue;
     if (f.gain_out && (f.mode != RM_RESID || !f.oh || !f.ol || !f.ssq_out)) return hipErrorInvalidValue;
-    if (f.mode == RM_QKV && (f.n[0] != D.dq || f.n[1] != D.dkv || f.n[2] != D.dkv || (D.hd != 64 && D.hd != 128)))
+    if (f.mode == RM_QKV && ((f.n[0] && f.n[0] != D.dq) || f.n[1] != D.dkv || f.n[2] != D.dkv || (D.hd != 64 && D.hd != 128)))
         return hipErrorInvalidValue;
     RowsP2 p = {};
     fill_rows_params(D, f, p);
@@ -2396,7 +2396,7 @@ hipError_t rows_big(const Dims& D, const RowsFused& f, hipStream_t s)
         return hipErrorInvalidValue;
     if (f.ssq && (f.mode == RM_RESID || f.n_ssq < 1)) return hipErrorInvalidValue;
     if (f.gain_out && (f.mode != RM_RESID || !f.oh || !f.ol || !f.ssq_out)) return hipErrorInvalidValue;
-    if (f.mode == RM_QKV && (f.n[0] != D.dq || f.n[1] != D.dkv || f.n[2] != D.dkv || (D.hd != 64 && D.hd != 128)))
+    if (f.mode == RM_QKV && ((f.n[0] && f.n[0] != D.dq) || f.n[1] != D.dkv || f.n[2] != D.dkv || (D.hd != 64 && D.hd != 128)))
         return hipErrorInvalidValue;
     RowsP2 p = {};
     fill_rows_params(D, f, p);

@@ -3,8 +3,9 @@ groups end inside a batch, against the CPU oracle: the cache rows a prompt wrote
 import numpy as np
 import pytest
 
+from oracle import OracleSSD
 from synth import ModelShape, make_prompt
-from tests._parity import lockstep_ssd, make_pair
+from tests._parity import CONF_TOL, assert_logits_close, decisive, lockstep_ssd, make_pair
 
 pytestmark = pytest.mark.gpu
 
@@ -25,3 +26,20 @@ def test_cache_rows_of_a_prompt(name, kv, plen):
     prompt = make_prompt(shape.vocab, plen, 3).tolist()
     st = lockstep_ssd(ctx, orc, prompt, 0, [4], np.array([0, 1], np.uint8), shape.dtype)
     assert st["unpinned_cycles"] <= 1 and st["verify_rows"] == 5
+
+
+# The last layer of a prompt block leaves keys and values of all rows and the rest for the last row only: one layer and several, the
+# 64-row blocks of shapes outside the large tiles, last blocks of one row, of 16 (the 16-row path behind a block of 512) and of more.
+@pytest.mark.parametrize("shape", [ModelShape(1, 512, 4, 4, 1408, 528), ModelShape(2, 256, 4, 1, 704, 640, dtype="fp16"),
+                                   ModelShape(2, 256, 2, 2, 640, 576)], ids=["one_layer", "gqa", "blocks_of_64"])
+@pytest.mark.parametrize("plen", [17, 64, 80, 81, 513, 530])
+def test_last_layer_of_a_prompt(shape, plen):
+    orc, ctx = make_pair(shape, 9, plen + 16, max_k=4, norm_gain_std=0.1, init_std=0.08)
+    prompt = make_prompt(shape.vocab, plen, 3).tolist()
+    o = OracleSSD(orc)
+    assert ctx.ssd_prefill(prompt) == o.prefill(prompt) or not decisive(o.last_logits[0], shape.dtype)
+    assert_logits_close(ctx.ssd_copy_logits(0, 1)[0], o.last_logits[0], shape.dtype, "prompt")
+    np.testing.assert_allclose(ctx.ssd_layer_confidence(0, 1)[0], o.layer_confidence(0)[0], atol=CONF_TOL[shape.dtype])
+    ctx.ssd_reset()
+    st = lockstep_ssd(ctx, orc, prompt, 0, [4, 1], np.zeros(shape.n_layers, np.uint8), shape.dtype)   # reads the cache rows
+    assert st["unpinned_cycles"] <= 1
