@@ -230,65 +230,7 @@ struct GemvP {
     int hd, dq, dkv, max_seq;
     float* vstat;       // STORE only, may be null: per block (max, sum of exp relative to it, arg-max) of the clamped outputs
     float clamp;
-    // Chained launches (all null / 0 = an ordinary launch).  A chained kernel may start while its producer is still
-    // running: it issues its first weight loads, then waits until *wait_flag has reached wait_count * *gen (every
-    // block of the producer adds 1 to its done_flag once its outputs are visible device-wide), and only then reads
-    // its input vector -- with device-coherent loads, as the producer's stores were device-coherent write-throughs.
-    unsigned* wait_flag; unsigned wait_count;
-    unsigned* done_flag;
-    const unsigned* gen;     // replay generation (1, 2, ...): the counters are never reset
-    unsigned* err;           // set to 1 if a wait gave up (every wait is bounded)
 };
-
-// Device-coherent accesses for data handed from one running kernel to another (each XCD has its own L2: ordinary
-// loads may hit a stale line, ordinary stores stay in the writer's L2 until its kernel ends).
-__device__ __forceinline__ float coh_load(const float* p)
-{
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ float4 coh_load4(const float* p)   // p 16-byte aligned
-{
-    const unsigned long long a = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED,
-                                                   __HIP_MEMORY_SCOPE_AGENT);
-    const unsigned long long b = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p) + 1, __ATOMIC_RELAXED,
-                                                   __HIP_MEMORY_SCOPE_AGENT);
-    return make_float4(__uint_as_float((unsigned)a), __uint_as_float((unsigned)(a >> 32)), __uint_as_float((unsigned)b),
-                       __uint_as_float((unsigned)(b >> 32)));
-}
-__device__ __forceinline__ void coh_store(float* p, float v)
-{
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-constexpr int CHAIN_SPIN_MAX = 1 << 20;   // polls before a chained wait gives up (seconds; a healthy wait takes microseconds)
-
-// Block-wide wait for the producer of a chained launch.  Ends for certain: the poll count is bounded.
-__device__ __forceinline__ void chain_wait(const GemvP& p)
-{
-    if (p.wait_flag) {
-        if (threadIdx.x == 0) {
-            const unsigned target = p.wait_count * p.gen[0];
-            int spins = 0;
-            // The counter is polled with a read-modify-write (adding 0): device-scope RMW atomics are carried out at
-            // the memory side, whereas a load may keep hitting a stale line in this XCD's L2.
-            while (__hip_atomic_fetch_add(p.wait_flag, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
-                if (++spins >= CHAIN_SPIN_MAX) { __hip_atomic_store(p.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); break; }
-                __builtin_amdgcn_s_sleep(4);
-            }
-            // one acquire per block: drops this CU's L1 and the XCD's stale L2 lines before the inputs are read
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        }
-        __syncthreads();
-    }
-}
-// Block-wide signal at the end of a chained launch: all of the block's write-through stores have been acknowledged.
-__device__ __forceinline__ void chain_signal(const GemvP& p)
-{
-    if (p.done_flag) {
-        __builtin_amdgcn_s_waitcnt(0);   // vmcnt(0): this wave's stores have completed
-        __syncthreads();
-        if (threadIdx.x == 0) __hip_atomic_fetch_add(p.done_flag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-}
 
 typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
 
@@ -405,8 +347,7 @@ __device__ __forceinline__ void gv_epilogue(const GemvP& p, int j0, const float 
                 const float ra = a * c - b * sn, rb = b * c + a * sn;
                 if (is_q) {
                     float* q = p.y + (size_t)head * p.hd + i;
-                    if (p.done_flag) { coh_store(q, ra); coh_store(q + half, rb); }
-                    else { q[0] = ra; q[half] = rb; }
+                    q[0] = ra; q[half] = rb;
                 } else {
                     const size_t o = ((size_t)head * p.max_seq + pos) * p.hd + i;
                     kv_put(p.kc, o, ra, p.kt);
@@ -424,16 +365,13 @@ __device__ __forceinline__ void gv_epilogue(const GemvP& p, int j0, const float 
         for (int t = 0; t < R; t += 2) {
             const float g = s[t] * sc, u = s[t + 1] * sc;
             const float a = g / (1.0f + __expf(-g)) * u;
-            if (p.done_flag) coh_store(p.y + ((j0 + t) >> 1), a);
-            else p.y[(j0 + t) >> 1] = a;
+            p.y[(j0 + t) >> 1] = a;
         }
     } else if (EPI == EPI_RESID) {
 #pragma unroll
         for (int t = 0; t < R; t++) {
-            // chained: the residual was written by a kernel that may still have been running when this one started
-            const float v = (res ? res[t] : p.wait_flag ? coh_load(p.y + j0 + t) : p.y[j0 + t]) + s[t];
-            if (p.done_flag) coh_store(p.y + j0 + t, v);
-            else p.y[j0 + t] = v;
+            const float v = (res ? res[t] : p.y[j0 + t]) + s[t];
+            p.y[j0 + t] = v;
             if (p.tap) p.tap[j0 + t] = v;
         }
     } else {
@@ -446,16 +384,17 @@ __device__ __forceinline__ void gv_epilogue(const GemvP& p, int j0, const float 
     }
 }
 
-// staged input of a projection that folds attention partials: element i = sum_s e^(m_s - m) o_s[i] / sum_s e^(m_s - m) l_s
-template <int VEC, int NF>
-__device__ __forceinline__ void gv_fold(const GemvP& p, int K, float* xs)
-{
-    const int hs = p.hd + 4, ns = p.n_splits;
-    for (int i = threadIdx.x * 4; i < K; i += GV_THREADS * 4) {
+// Four elements (i ..) of the input of a projection that folds attention partials: sum_s e^(m_s - m) o_s / sum_s e^(m_s - m) l_s.  All
+// partials of an element are requested by independent, unconditional loads (index clamped, weight zeroed past n_splits), so that
+// the fold costs one cache round trip, not one per partial.  NF: two, four or eight, the smallest that covers n_splits.
+template <int NF>
+struct GvFold {
+    float mm[NF], ll[NF];
+    float4 oo[NF];
+    __device__ __forceinline__ void request(const GemvP& p, int i)
+    {
+        const int hs = p.hd + 4, ns = p.n_splits, d = i % p.hd;
         const float* base = p.part + (size_t)(i / p.hd) * ns * hs;
-        const int d = i % p.hd;
-        float mm[NF], ll[NF];
-        float4 oo[NF];
 #pragma unroll
         for (int sp = 0; sp < NF; sp++) {
             const float* ps = base + min(sp, ns - 1) * hs;
@@ -463,6 +402,9 @@ __device__ __forceinline__ void gv_fold(const GemvP& p, int K, float* xs)
             ll[sp] = ps[p.hd + 1];
             oo[sp] = *reinterpret_cast<const float4*>(ps + d);
         }
+    }
+    __device__ __forceinline__ float4 result(int ns) const
+    {
         float gm = -INFINITY;
 #pragma unroll
         for (int sp = 0; sp < NF; sp++) gm = fmaxf(gm, mm[sp]);   // clamped duplicates do not change the max
@@ -475,11 +417,12 @@ __device__ __forceinline__ void gv_fold(const GemvP& p, int K, float* xs)
             num.z = fmaf(w, oo[sp].z, num.z); num.w = fmaf(w, oo[sp].w, num.w);
             den = fmaf(w, ll[sp], den);
         }
-        *reinterpret_cast<float4*>(xs + gv_xpos<VEC>(i)) = make_float4(num.x / den, num.y / den, num.z / den, num.w / den);
+        return make_float4(num.x / den, num.y / den, num.z / den, num.w / den);
     }
-}
+};
 
-template <typename WT, int EPI, int R, int D, int KS>
+// FOLD: 0 = the input is p.in, else the fold of up to FOLD attention partials
+template <typename WT, int EPI, int R, int D, int KS, int FOLD = 0>
 __global__ __launch_bounds__(GV_THREADS) void gemv_kernel(GemvP p)
 {
     extern __shared__ __align__(16) float xs[];
@@ -539,51 +482,73 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_kernel(GemvP p)
         for (int r = 0; r < R; r++) buf[s][r] = gv_load(wi[r] + off);
         if (++ci == S) { ci = 0; ++ri; set_issue_rows(); }
     };
-    // the first weight loads do not depend on the activations: start them before staging the input
-#pragma unroll
-    for (int s = 0; s < D; s++) issue(s);
-
-    chain_wait(p);
-    // stage the input vector (times gain); the sum of squares gives the RMS scale
-    float ss = 0.f;
-    if (EPI == EPI_RESID && p.part) {
-        // attention output folded on the fly: out = sum_s e^(m_s - m) o_s / sum_s e^(m_s - m) l_s per head.
-        // All partials of an element are fetched by independent, unconditional loads (index clamped, weight
-        // zeroed past n_splits) so that the fold costs one cache round trip, not one per partial.
-        // (two, four or eight per element: the smallest that covers n_splits)
-        if (p.n_splits <= 2) gv_fold<VEC, 2>(p, K, xs);
-        else if (p.n_splits <= 4) gv_fold<VEC, 4>(p, K, xs);
-        else gv_fold<VEC, GV_FOLD_MAX>(p, K, xs);
-    } else
-    for (int i = threadIdx.x * 4; i < K; i += GV_THREADS * 4) {
-        float4 v = p.wait_flag ? coh_load4(p.in + i) : *reinterpret_cast<const float4*>(p.in + i);
-        ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
-        if (p.gain) {
-            const float4 g = *reinterpret_cast<const float4*>(p.gain + i);
-            v.x *= g.x; v.y *= g.y; v.z *= g.z; v.w *= g.w;
-        }
-        *reinterpret_cast<float4*>(xs + gv_xpos<VEC>(i)) = v;
-    }
+    // What the block reads besides weights is requested in front of them: loads return in order, and behind the first
+    // weights of all blocks (100 KB per CU) the input arrives when these are through, with nothing of the stream in
+    // flight until it is staged and the next loads are out.  The first XN four-element pieces per thread (addresses
+    // clamped), the rest of a longer input behind.  In the steps of a 7B model, us, input behind / in front: QKV 19.3 / 18.2,
+    // output projection with two or three partials 9.0 / 8.0, with seven 11.0 / 10.1, gate/up 28.9 / 28.5, down 17.9 / 16.5; 70B down 74.5 / 72.3.
+    constexpr bool GAIN = EPI != EPI_RESID;
+    constexpr int XN = FOLD ? 2 : EPI == EPI_STORE ? 2 : EPI == EPI_RESID ? 7 : 4;
     int pos = 0;
     if (EPI == EPI_QKV) {
         pos = p.pos_dev[0] + p.pos_off;
         if ((int)threadIdx.x < p.hd) rope_row[threadIdx.x] = p.rope_row[threadIdx.x];   // hd / 2 pairs
     }
+    float res_r = 0.f;
+    constexpr int NRES = GPB * GV_RES_ROUNDS * R;
+    static_assert(NRES <= GV_THREADS, "a residual value per thread");
     if (EPI == EPI_RESID) {
-        for (int i = threadIdx.x; i < GPB * GV_RES_ROUNDS * R; i += GV_THREADS) {
-            const int r = i % R, rnd = (i / R) % GV_RES_ROUNDS, gs = i / (R * GV_RES_ROUNDS);
-            const int g = ((int)blockIdx.x + rnd * (int)gridDim.x) * GPB + gs;
-            if (rnd < n_rounds && g < n_groups)
-                res_s[(gs * GV_RES_ROUNDS + rnd) * R + r] = p.wait_flag ? coh_load(p.y + g * R + r) : p.y[g * R + r];
+        const int i = min((int)threadIdx.x, NRES - 1), r = i % R, rnd = (i / R) % GV_RES_ROUNDS, gs = i / (R * GV_RES_ROUNDS);
+        res_r = p.y[min(((int)blockIdx.x + rnd * (int)gridDim.x) * GPB + gs, n_groups - 1) * R + r];
+    }
+    float4 xv[XN], xg[XN];
+    GvFold<FOLD ? FOLD : 1> xf[FOLD ? XN : 1];
+#pragma unroll
+    for (int u = 0; u < XN; u++) {
+        const int i = min(((int)threadIdx.x + u * GV_THREADS) * 4, K - 4);
+        if constexpr (FOLD) xf[u].request(p, i);
+        else xv[u] = *reinterpret_cast<const float4*>(p.in + i);
+        if (GAIN) xg[u] = *reinterpret_cast<const float4*>(p.gain + i);
+    }
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int s = 0; s < D; s++) issue(s);
+
+    // stage the input vector (times gain); the sum of squares gives the RMS scale
+    float ss = 0.f;
+    auto stage = [&](int i, float4 v, float4 g) {
+        if (GAIN) {
+            ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+            v.x *= g.x; v.y *= g.y; v.z *= g.z; v.w *= g.w;
+        }
+        *reinterpret_cast<float4*>(xs + gv_xpos<VEC>(i)) = v;
+    };
+    if (EPI == EPI_RESID && (int)threadIdx.x < NRES) res_s[threadIdx.x] = res_r;   // [group of the block][round][row]
+#pragma unroll
+    for (int u = 0; u < XN; u++) {
+        const int i = ((int)threadIdx.x + u * GV_THREADS) * 4;
+        if (i < K) {
+            if constexpr (FOLD) stage(i, xf[u].result(p.n_splits), make_float4(0.f, 0.f, 0.f, 0.f));
+            else stage(i, xv[u], GAIN ? xg[u] : xv[u]);
+        }
+    }
+    for (int i = ((int)threadIdx.x + XN * GV_THREADS) * 4; i < K; i += GV_THREADS * 4) {
+        if constexpr (FOLD) {
+            GvFold<FOLD ? FOLD : 1> f;
+            f.request(p, i);
+            stage(i, f.result(p.n_splits), make_float4(0.f, 0.f, 0.f, 0.f));
+        } else {
+            const float4 v = *reinterpret_cast<const float4*>(p.in + i);
+            stage(i, v, GAIN ? *reinterpret_cast<const float4*>(p.gain + i) : v);
         }
     }
     float sc = 1.0f;
-    if (p.gain) {
+    if (GAIN) {
         ss = wave_sum(ss);
         if (lane == 0) red[wave] = ss;
     }
-    __syncthreads();
-    if (p.gain) {
+    lds_barrier();   // (the weights in flight are not waited for)
+    if (GAIN) {
         float t = 0.f;
 #pragma unroll
         for (int i = 0; i < GV_WAVES; i++) t += red[i];
@@ -651,7 +616,6 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_kernel(GemvP p)
     }
 #pragma unroll
     for (int s = 0; s < D; s++) consume(s);
-    chain_signal(p);
     if (EPI == EPI_STORE && p.vstat) {   // block partial of the soft-max statistics: lane 0 of every wave holds one
         __shared__ float vred[GV_WAVES * 3];
         if (lane == 0) { vred[wave * 3] = vs.m; vred[wave * 3 + 1] = vs.z; vred[wave * 3 + 2] = __int_as_float(vs.arg); }
@@ -757,13 +721,13 @@ static int gemv_rounds(const GemvP& p, const LaunchOpts* opt)
 }
 
 // blocks_out (may be null) receives the grid size of the launch
-template <typename WT, int EPI, int R, int D, int KS>
-static hipError_t launch_gemv_cfg(const GemvP& p, hipStream_t s, LaunchOpts* opt, int* blocks_out)
+template <typename WT, int EPI, int R, int D, int KS, int FOLD>
+static hipError_t launch_gemv_fold(const GemvP& p, hipStream_t s, LaunchOpts* opt, int* blocks_out)
 {
     const size_t lds = (size_t)gemv_lds_floats(p.K, Elem<WT>::VEC) * sizeof(float);
     static std::atomic<size_t> lds_limit{0};  // per instantiation
     {
-        hipError_t e = ensure_lds((const void*)gemv_kernel<WT, EPI, R, D, KS>, lds, lds_limit);
+        hipError_t e = ensure_lds((const void*)gemv_kernel<WT, EPI, R, D, KS, FOLD>, lds, lds_limit);
         if (e != hipSuccess) return e;
     }
     // equal work per block: with r rounds needed, use just enough blocks for r full rounds (gate/up at 7B:
@@ -772,14 +736,27 @@ static hipError_t launch_gemv_cfg(const GemvP& p, hipStream_t s, LaunchOpts* opt
     if (blocks_out) *blocks_out = blocks;
     if (opt && opt->time_start) {
         // timing request for this one launch: the events take the kernel's own begin and end timestamps
-        hipExtLaunchKernelGGL((gemv_kernel<WT, EPI, R, D, KS>), dim3(blocks), dim3(GV_THREADS), lds, s, opt->time_start,
+        hipExtLaunchKernelGGL((gemv_kernel<WT, EPI, R, D, KS, FOLD>), dim3(blocks), dim3(GV_THREADS), lds, s, opt->time_start,
                               opt->time_stop, 0, p);
         opt->time_start = nullptr;
         opt->time_stop = nullptr;
     } else {
-        hipLaunchKernelGGL((gemv_kernel<WT, EPI, R, D, KS>), dim3(blocks), dim3(GV_THREADS), lds, s, p);
+        hipLaunchKernelGGL((gemv_kernel<WT, EPI, R, D, KS, FOLD>), dim3(blocks), dim3(GV_THREADS), lds, s, p);
     }
     return hipGetLastError();
+}
+
+template <typename WT, int EPI, int R, int D, int KS>
+static hipError_t launch_gemv_cfg(const GemvP& p, hipStream_t s, LaunchOpts* opt, int* blocks_out)
+{
+    if constexpr (EPI == EPI_RESID) {
+        if (p.part) {
+            if (p.n_splits <= 2) return launch_gemv_fold<WT, EPI, R, D, KS, 2>(p, s, opt, blocks_out);
+            if (p.n_splits <= 4) return launch_gemv_fold<WT, EPI, R, D, KS, 4>(p, s, opt, blocks_out);
+            return launch_gemv_fold<WT, EPI, R, D, KS, GV_FOLD_MAX>(p, s, opt, blocks_out);
+        }
+    }
+    return launch_gemv_fold<WT, EPI, R, D, KS, 0>(p, s, opt, blocks_out);
 }
 
 // Work split: many rows -> one wave per row pair, deep pipeline; few rows -> split K over the waves
@@ -789,19 +766,19 @@ static hipError_t launch_gemv_t(const GemvP& p, hipStream_t s, LaunchOpts* opt, 
 {
     const int ch = ceil_div(p.K, 64 * Elem<WT>::VEC);
     if constexpr (EPI == EPI_RESID && sizeof(WT) == 2) {   // tuning hook (kernel_bench sweeps)
-        switch (opt ? opt->gemv_resid_cfg : 0) {
-            case 241: return launch_gemv_cfg<WT, EPI, 2, 4, 1>(p, s, opt, blocks_out);
-            case 242: return launch_gemv_cfg<WT, EPI, 2, 4, 2>(p, s, opt, blocks_out);
-            case 244: return launch_gemv_cfg<WT, EPI, 2, 4, 4>(p, s, opt, blocks_out);
-            case 248: return launch_gemv_cfg<WT, EPI, 2, 4, 8>(p, s, opt, blocks_out);
-            case 222: return launch_gemv_cfg<WT, EPI, 2, 2, 2>(p, s, opt, blocks_out);
-            case 224: return launch_gemv_cfg<WT, EPI, 2, 2, 4>(p, s, opt, blocks_out);
-            case 228: return launch_gemv_cfg<WT, EPI, 2, 2, 8>(p, s, opt, blocks_out);
-            case 422: return launch_gemv_cfg<WT, EPI, 4, 2, 2>(p, s, opt, blocks_out);
-            case 424: return launch_gemv_cfg<WT, EPI, 4, 2, 4>(p, s, opt, blocks_out);
-            case 428: return launch_gemv_cfg<WT, EPI, 4, 2, 8>(p, s, opt, blocks_out);
-            case 442: return launch_gemv_cfg<WT, EPI, 4, 4, 2>(p, s, opt, blocks_out);
-            case 444: return launch_gemv_cfg<WT, EPI, 4, 4, 4>(p, s, opt, blocks_out);
+        switch (opt && !p.part ? opt->gemv_resid_cfg : 0) {
+            case 241: return launch_gemv_fold<WT, EPI, 2, 4, 1, 0>(p, s, opt, blocks_out);
+            case 242: return launch_gemv_fold<WT, EPI, 2, 4, 2, 0>(p, s, opt, blocks_out);
+            case 244: return launch_gemv_fold<WT, EPI, 2, 4, 4, 0>(p, s, opt, blocks_out);
+            case 248: return launch_gemv_fold<WT, EPI, 2, 4, 8, 0>(p, s, opt, blocks_out);
+            case 222: return launch_gemv_fold<WT, EPI, 2, 2, 2, 0>(p, s, opt, blocks_out);
+            case 224: return launch_gemv_fold<WT, EPI, 2, 2, 4, 0>(p, s, opt, blocks_out);
+            case 228: return launch_gemv_fold<WT, EPI, 2, 2, 8, 0>(p, s, opt, blocks_out);
+            case 422: return launch_gemv_fold<WT, EPI, 4, 2, 2, 0>(p, s, opt, blocks_out);
+            case 424: return launch_gemv_fold<WT, EPI, 4, 2, 4, 0>(p, s, opt, blocks_out);
+            case 428: return launch_gemv_fold<WT, EPI, 4, 2, 8, 0>(p, s, opt, blocks_out);
+            case 442: return launch_gemv_fold<WT, EPI, 4, 4, 2, 0>(p, s, opt, blocks_out);
+            case 444: return launch_gemv_fold<WT, EPI, 4, 4, 4, 0>(p, s, opt, blocks_out);
             default: break;
         }
     }
@@ -820,9 +797,10 @@ static hipError_t launch_gemv_t(const GemvP& p, hipStream_t s, LaunchOpts* opt, 
         if constexpr (EPI == EPI_RESID) {
             // Few chunks: two waves per pair.  Folding the attention partials: a wave per pair with four steps in flight, since
             // every block re-reads the partials and there is one block per CU only (7B 9.4 against 10.9 with four waves per
-            // pair; at 8192 rows, where a block has two rounds, 27.2 against 28.5 the other way round).  Everything else: four
+            // pair, both with the input requested behind the weights; at 8192 rows, where a block has two rounds, 27.2 against 28.5 the other
+            // way round).  Everything else: four
             // waves per pair; four steps in flight where a wave's share of a pair is longer than that and its items need no
-            // padding (7B down projection, 12 items: 18.1 against 18.8 with two, behind the gate/up launch; 70B, 112: 71.8
+            // padding (7B down projection, 12 items: 16.5 against 16.7 with two; 70B, 112: 71.8
             // against 72.8), else two (Llama-3-8B, 14 items: 22.9 -> 21.4, 13B, 21: 26.7 -> 25.7, 1024-wide, 2: 5.4 -> 5.0; 70B
             // output projection, four steps per pair: 25.3 against 29.4).
             if (ch <= 4) return launch_gemv_cfg<WT, EPI, 2, 2, 2>(p, s, opt, blocks_out);
@@ -861,33 +839,23 @@ static hipError_t launch_gemv(const Dims& D, const GemvP& p, hipStream_t s, int*
     return launch_gemv_t<float, EPI>(p, s, D.opt, blocks_out);
 }
 
-static void set_chain(GemvP& p, const Chain* ch)
-{
-    if (!ch) return;
-    p.wait_flag = ch->wait_flag; p.wait_count = ch->wait_count; p.done_flag = ch->done_flag; p.gen = ch->gen; p.err = ch->err;
-}
-
 hipError_t gemv_qkv(const Dims& D, const void* wq, const void* wk, const void* wv, const float* gain, const float* x,
-                    const float* rope_row, const int* pos_dev, int pos_off, float* qbuf, void* kc, void* vc, hipStream_t s,
-                    const Chain* ch, int* blocks_out)
+                    const float* rope_row, const int* pos_dev, int pos_off, float* qbuf, void* kc, void* vc, hipStream_t s)
 {
-    if (D.hd > 128 || D.hd % 2) return hipErrorInvalidValue;   // the kernel stages one rotary row of hd floats in a 128-float LDS array
+    if (!gain || D.hd > 128 || D.hd % 2) return hipErrorInvalidValue;   // the kernel stages one rotary row of hd floats in a 128-float LDS array
     GemvP p = {};
-    set_chain(p, ch);
     p.w0 = wq; p.w1 = wk; p.w2 = wv; p.in = x; p.gain = gain; p.eps = D.eps; p.K = D.d;
     p.n_rows = D.dq + 2 * D.dkv;
     p.y = qbuf; p.kc = kc; p.vc = vc; p.kt = D.kt; p.rope_row = rope_row; p.pos_dev = pos_dev; p.pos_off = pos_off;
     p.hd = D.hd; p.dq = D.dq; p.dkv = D.dkv; p.max_seq = D.max_seq;
-    return launch_gemv<EPI_QKV>(D, p, s, blocks_out);
+    return launch_gemv<EPI_QKV>(D, p, s);
 }
 
-hipError_t gemv_resid(const Dims& D, const void* w, int N, int K, const float* in, float* x, float* tap, hipStream_t s,
-                      const Chain* ch, int* blocks_out)
+hipError_t gemv_resid(const Dims& D, const void* w, int N, int K, const float* in, float* x, float* tap, hipStream_t s)
 {
     GemvP p = {};
-    set_chain(p, ch);
     p.w0 = w; p.in = in; p.gain = nullptr; p.eps = D.eps; p.K = K; p.n_rows = N; p.y = x; p.tap = tap;
-    return launch_gemv<EPI_RESID>(D, p, s, blocks_out);
+    return launch_gemv<EPI_RESID>(D, p, s);
 }
 
 hipError_t gemv_resid_attn(const Dims& D, const void* w, const float* part, int n_splits, float* x, float* tap,
@@ -901,12 +869,11 @@ hipError_t gemv_resid_attn(const Dims& D, const void* w, const float* part, int 
 }
 
 hipError_t gemv_swiglu(const Dims& D, const void* wg, const void* wu, const float* gain, const float* x, float* act,
-                       hipStream_t s, const Chain* ch, int* blocks_out)
+                       hipStream_t s)
 {
     GemvP p = {};
-    set_chain(p, ch);
     p.w0 = wg; p.w1 = wu; p.in = x; p.gain = gain; p.eps = D.eps; p.K = D.d; p.n_rows = 2 * D.f; p.y = act;
-    return launch_gemv<EPI_SWIGLU>(D, p, s, blocks_out);
+    return launch_gemv<EPI_SWIGLU>(D, p, s);
 }
 
 hipError_t gemv_lmhead(const Dims& D, const void* wlm, const float* gain, const float* x, float* logits, hipStream_t s)

@@ -4,7 +4,7 @@ import pytest
 
 from oracle import OracleSSD
 from synth import ModelShape, make_prompt, make_weights
-from tests._parity import CONF_TOL, PROB_RTOL, assert_logits_close, decisive, make_pair, to_gpu
+from tests._parity import CONF_TOL, PROB_RTOL, assert_logits_close, decisive, lockstep_ssd, make_pair, to_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -185,3 +185,17 @@ def test_plain_rows_over_several_trips_of_k(d, heads, f, dtype, k):
     assert_logits_close(ctx.ssd_copy_logits(0, k + 1), o.last_logits, dtype, "verify")
     conf_o, _ = o.layer_confidence(0)
     np.testing.assert_allclose(ctx.ssd_layer_confidence(0, 1)[0], conf_o, atol=CONF_TOL[dtype])
+
+
+# Single-row products whose input is longer than what a block requests in front of its weights (8192 elements of a normalised one, 4096 at
+# the LM head and where attention partials are folded, 14336 of the FFN's), and shorter than one piece per thread.
+@pytest.mark.parametrize("shape,plen", [(ModelShape(1, 4352, 34, 2, 512, 528), 70), (ModelShape(1, 8448, 66, 2, 256, 528, dtype="fp16"), 5),
+                                        (ModelShape(1, 1088, 17, 17, 14464, 528), 5), (ModelShape(1, 704, 11, 11, 14464, 528, dtype="fp32"), 70),
+                                        (ModelShape(2, 1152, 9, 3, 320, 528, dtype="fp16"), 150)],
+                         ids=["fold", "norm", "ffn", "ffn32", "short"])
+def test_products_of_a_single_row(shape, plen):
+    orc, ctx = make_pair(shape, 13, plen + 12, max_k=3, norm_gain_std=0.1)
+    prompt = make_prompt(shape.vocab, plen, 5).tolist()
+    st = lockstep_ssd(ctx, orc, prompt, 0, [3, 1], np.zeros(shape.n_layers, np.uint8), shape.dtype)
+    assert st["unpinned_cycles"] <= 1 and st["draft_rows"] >= 3
+    assert ctx.ssd_get_one_launch() == (0, 0, 0)
