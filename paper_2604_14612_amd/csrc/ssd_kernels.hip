@@ -1521,26 +1521,41 @@ __global__ __launch_bounds__(512, (M3_D * (MODE == RM_SWIGLU ? 4 + NU : 2 + NU) 
     // K = 8192).
     const int rot = (tile / 8) % NC;
     auto sidx = [&](int i) { const int c = min(i, NC - 1) + rot; return c >= NC ? c - NC : c; };
+    // RMS scale of every activation row from the producer's per-tile sums of squares (read by the epilogue).  They are requested
+    // in front of the weights: loads return in order, and behind the first stripes of all blocks the scales would hold up the
+    // first multiplication until these are all there; summed behind the weight stream they cost their latency at the end.
+    // Verifications at 7B, 5 rows bf16 / 9 rows fp16, us, before and now: QKV 20.6 -> 20.2 / 23.5 -> 23.0, gate/up 33.2 -> 33.0 /
+    // 35.4 -> 34.0, LM head 44.0 -> 42.8 / 52.7 -> 50.0.
+    // Every entry, the 1 of a row without a scale included, has a single writer (rows_of_wave): no initial pass by other
+    // threads, which would need a barrier of its own before the scales go in.
+    constexpr int SQR = NU > 2 ? 2 : 1, SQN = 8;   // rows of a wave that may have a scale (NU = 2: up to 8 rows in all), sums per lane requested here
+    const bool scaled = MODE != RM_RESID && p.ssq;
+    float sq[SQR][SQN];
+    if (scaled) {
+#pragma unroll
+        for (int r = 0; r < SQR; r++)
+#pragma unroll
+            for (int u = 0; u < SQN; u++) sq[r][u] = p.ssq[(size_t)min(wave + 8 * r, M - 1) * p.n_ssq + min(lane + u * 64, p.n_ssq - 1)];
+    }
+    asm volatile("" ::: "memory");
 #pragma unroll
     for (int sl = 0; sl < M3_D; sl++) gload(sl, sidx(sl));
     const M2Pre pre = m2_preload<MODE>(p, tile);
-    // RMS scale of every activation row from the producer's per-tile sums of squares (read by the epilogue).
-    // Measured per mode: gate/up (long-lived blocks, two stripes in flight) loses least when the partials are
-    // summed after the weight stream, the short-lived blocks of QKV and the LM head when it happens up front.
-    // Every entry, the 1 of a row without a scale included, has a single writer (rows_of_wave): no initial pass by other
-    // threads, which would need a barrier of its own before the scales go in.
-    auto row_scales = [&]() {
-        rows_of_wave(wave, [&](int c) {
-            float s = 1.0f;
-            if (MODE != RM_RESID && p.ssq && c < M) {
-                float sq = 0.f;
-                for (int i = lane; i < p.n_ssq; i += 64) sq += p.ssq[(size_t)c * p.n_ssq + i];
-                s = 1.0f / sqrtf(wave_sum(sq) / (float)K + p.eps);
-            }
-            if (lane == 0) rs[c] = s;
-        });
-    };
-    if (MODE != RM_SWIGLU) row_scales();
+    rows_of_wave(wave, [&](int c) {
+        float v = 1.0f;
+        if (scaled && c < M) {
+            float t = 0.f;
+#pragma unroll
+            for (int r = 0; r < SQR; r++)
+                if (c == wave + 8 * r) {
+#pragma unroll
+                    for (int u = 0; u < SQN; u++) t += lane + u * 64 < p.n_ssq ? sq[r][u] : 0.f;
+                }
+            for (int i = lane + SQN * 64; i < p.n_ssq; i += 64) t += p.ssq[(size_t)c * p.n_ssq + i];
+            v = 1.0f / sqrtf(wave_sum(t) / (float)K + p.eps);
+        }
+        if (lane == 0) rs[c] = v;
+    });
     // steady state: every step stores its slot's stripe, refills the slot and multiplies; the stripe count is padded
     // to a multiple of M3_D (a padding request re-reads the last stripe and is never stored); the last M3_D steps
     // request nothing
@@ -1561,7 +1576,6 @@ __global__ __launch_bounds__(512, (M3_D * (MODE == RM_SWIGLU ? 4 + NU : 2 + NU) 
             multiply(sidx(ck0 + sl));
         }
     }
-    if (MODE == RM_SWIGLU) row_scales();
     __syncthreads();
     float* red = reinterpret_cast<float*>(sm3);  // [8][NT][256] floats fit inside the weight stripe area
 #pragma unroll
@@ -1600,8 +1614,9 @@ static hipError_t rows_fused_mode(const RowsP2& p, hipStream_t s, const LaunchOp
     const int forced = opt ? opt->rows_depth : 0;
     const int n_tiles = MODE == RM_SWIGLU ? p.n[0] / 16 : (p.n[0] + p.n[1] + p.n[2]) / 16;
     // measured (`KB_ROWS=1 kernel_bench`, and at the 13B / 70B / Llama-3-8B shapes): two stripes in flight are best or
-    // equal everywhere (down projection, 5 rows: 18.0 us against 23.3 with one, 18.0 with three) except gate/up, whose ring for
-    // two stripes of two matrices does not fit the registers of three blocks per CU (32.9 us with one stripe, 38.7 with two)
+    // equal everywhere (down projection, 5 rows: 17.6 us against 23.2 with one, 19.1 with three) except gate/up, whose ring for
+    // two stripes of two matrices is too large for the registers of three blocks per CU from nine rows on, and gains nothing below
+    // (in verifications of five rows 32.8 against 33.0 us at 7B, 153.8 against 148.5 at 70B)
     const int depth = forced > 0 ? forced : (MODE == RM_SWIGLU ? 1 : 2);
     switch (depth) {
         case 1: return launch_mfma3<MODE, 1, F16>(p, n_tiles, s);
