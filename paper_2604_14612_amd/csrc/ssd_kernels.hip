@@ -1333,6 +1333,8 @@ __device__ __forceinline__ const uint16_t* m2_row(const RowsP2& p, int tile, int
     return (const uint16_t*)p.w[2] + (size_t)(row - p.n[1]) * p.K;
 }
 
+// position of activation row 0
+template <int MODE> __device__ __forceinline__ int m6_pos0(const RowsP2& p) { return MODE == RM_QKV ? p.pos_dev[0] + p.pos_off : 0; }
 // Final step of a tile: sum the KS per-wave partial tiles held in LDS (layout [wave][NT][256], element
 // row*16 + column) and apply the mode's epilogue.  Executed by the whole block (it contains barriers in QKV mode).
 // rs: per-column (= activation row) RMS scale in LDS, 1 where no norm applies.
@@ -1340,13 +1342,13 @@ __device__ __forceinline__ const uint16_t* m2_row(const RowsP2& p, int tile, int
 // costs its whole latency, about 1 us, and for the rotary pair two: the position comes first).
 struct M2Pre { float a, b; int pos; };
 template <int MODE>
-__device__ __forceinline__ M2Pre m2_preload(const RowsP2& p, int t)
+__device__ __forceinline__ M2Pre m2_preload(const RowsP2& p, int t, int pos0)   // pos0: position of row 0 (QKV)
 {
     M2Pre r = {0.f, 0.f, 0};
     const int tid = threadIdx.x, rr = tid & 15, c = min((tid >> 4) & 15, p.M - 1);
     if (MODE == RM_QKV) {
         const int tq = p.dq >> 4, tk = p.dkv >> 4;
-        r.pos = p.pos_dev[0] + p.pos_off + c;
+        r.pos = pos0 + c;
         if (t < tq + tk) {
             const int tt = t < tq ? t : t - tq, th = tt % (p.hd >> 4), half = p.hd >> 1;
             const float* cs = p.rope + ((size_t)r.pos * half + th * 8 + (rr & 7)) * 2;
@@ -1530,17 +1532,20 @@ __global__ __launch_bounds__(512, (M3_D * (MODE == RM_SWIGLU ? 4 + NU : 2 + NU) 
     // threads, which would need a barrier of its own before the scales go in.
     constexpr int SQR = NU > 2 ? 2 : 1, SQN = 8;   // rows of a wave that may have a scale (NU = 2: up to 8 rows in all), sums per lane requested here
     const bool scaled = MODE != RM_RESID && p.ssq;
+    const int pos0 = m6_pos0<MODE>(p);   // (the rotary pairs are requested once it is there)
     float sq[SQR][SQN];
-    if (scaled) {
+    if (MODE != RM_RESID) {   // (rows without sums re-read an activation: a condition here would make the compiler wait for the first load)
+        const float* src = scaled ? p.ssq : reinterpret_cast<const float*>(p.bh);
+        const int n = scaled ? p.n_ssq : 1;
 #pragma unroll
         for (int r = 0; r < SQR; r++)
 #pragma unroll
-            for (int u = 0; u < SQN; u++) sq[r][u] = p.ssq[(size_t)min(wave + 8 * r, M - 1) * p.n_ssq + min(lane + u * 64, p.n_ssq - 1)];
+            for (int u = 0; u < SQN; u++) sq[r][u] = src[(size_t)min(wave + 8 * r, M - 1) * n + min(lane + u * 64, n - 1)];
     }
     asm volatile("" ::: "memory");
 #pragma unroll
     for (int sl = 0; sl < M3_D; sl++) gload(sl, sidx(sl));
-    const M2Pre pre = m2_preload<MODE>(p, tile);
+    const M2Pre pre = m2_preload<MODE>(p, tile, pos0);
     rows_of_wave(wave, [&](int c) {
         float v = 1.0f;
         if (scaled && c < M) {
@@ -1672,8 +1677,6 @@ __device__ __forceinline__ const uint16_t* m6_row(const RowsP2& p, int tile, int
 // Measured, 7B, 512 rows, in the prompt pass: QKV 135 -> 120 us, residual finishing pass 12.2 -> 11.5; 13B QKV 181 -> 164.
 struct M6Col { size_t off; int stride; int kind; float gain; const float* rope; };   // kind: QKV 0 q, 1 k, 2 v
 struct M6Pre { float a, b; };
-// position of activation row 0
-template <int MODE> __device__ __forceinline__ int m6_pos0(const RowsP2& p) { return MODE == RM_QKV ? p.pos_dev[0] + p.pos_off : 0; }
 template <int MODE>
 __device__ __forceinline__ M6Col m6_col(const RowsP2& p, int tile, int nn, int pos0)
 {
@@ -2794,20 +2797,33 @@ __global__ __launch_bounds__(AT_THREADS) void attn_kernel(const float* __restric
 // type), B = K rows read from LDS in fragment order.  P.V: A = the 16 x 96 exponentials (hi + lo), B = V, which
 // is therefore staged transposed ([dim][position]) so that a fragment is one 128-bit LDS read.
 constexpr int AM_VPITCH = AT_CHUNK * 2 + 16;   // bytes per row of the transposed V tile
+// One block fits a CU (120 KB of LDS for an fp32 cache), and what it does with a wave per SIMD is a chain of latencies.  Hence
+// eight waves instead of four, conversions two at a time, and the position by the scalar path instead of behind all of K and V:
+// 7B, 5 rows behind 550 positions of an fp32 cache 9.5 -> 8.8 us; 70B, 1 and 5 rows behind 300 7.9 -> 6.8.
+constexpr int AM_WAVES = 8, AM_THREADS = AM_WAVES * 64;
 
-// 8 fp32 values -> two packed fragments hi = rne(x), lo = rne(x - hi)
+// hi = rne(x), lo = rne(x - hi) of two fp32 values, packed with the first one in the low half: one conversion instruction takes both
+template <bool F16>
+__device__ __forceinline__ void pair_hi_lo(float a, float b, unsigned& hi, unsigned& lo)
+{
+    if (F16) {
+        const f16_t ha = (f16_t)a, hb = (f16_t)b;
+        hi = __builtin_bit_cast(uint16_t, ha) | ((unsigned)__builtin_bit_cast(uint16_t, hb) << 16);
+        lo = __builtin_bit_cast(uint16_t, (f16_t)(a - (float)ha)) | ((unsigned)__builtin_bit_cast(uint16_t, (f16_t)(b - (float)hb)) << 16);
+    } else {
+        hi = __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2_t{a, b}, bf16x2_t));
+        lo = __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2_t{a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xffff0000u)}, bf16x2_t));
+    }
+}
+// 8 fp32 values -> two packed fragments hi, lo
 template <bool F16>
 __device__ __forceinline__ void pack_hi_lo(const float (&v)[8], u32x4_t& hi, u32x4_t& lo)
 {
-    unsigned h[8], l[8];
+    unsigned h[4], l[4];
 #pragma unroll
-    for (int i = 0; i < 8; i++) {
-        const uint16_t hb = f32_to_h16_bits(v[i], F16);
-        h[i] = hb;
-        l[i] = f32_to_h16_bits(v[i] - h16_bits_to_f32(hb, F16), F16);
-    }
-    hi = u32x4_t{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
-    lo = u32x4_t{l[0] | (l[1] << 16), l[2] | (l[3] << 16), l[4] | (l[5] << 16), l[6] | (l[7] << 16)};
+    for (int i = 0; i < 4; i++) pair_hi_lo<F16>(v[2 * i], v[2 * i + 1], h[i], l[i]);
+    hi = u32x4_t{h[0], h[1], h[2], h[3]};
+    lo = u32x4_t{l[0], l[1], l[2], l[3]};
 }
 // the same for 8 consecutive values in LDS
 template <bool F16>
@@ -2829,20 +2845,18 @@ __device__ __forceinline__ void store_v4(const u32x4_t (&v)[4], unsigned char* d
     for (int i = 0; i < 4; i++) { w[i][0] = v[i].x; w[i][1] = v[i].y; w[i][2] = v[i].z; w[i][3] = v[i].w; }
 #pragma unroll
     for (int e = 0; e < 16 / (int)sizeof(KT); e++) {
-        unsigned h[4], l[4];
+        if constexpr (sizeof(KT) == 4) {
+            uint2 h, l;
+            pair_hi_lo<false>(__uint_as_float(w[0][e]), __uint_as_float(w[1][e]), h.x, l.x);
+            pair_hi_lo<false>(__uint_as_float(w[2][e]), __uint_as_float(w[3][e]), h.y, l.y);
+            *reinterpret_cast<uint2*>(dst + e * pitch) = h;
+            *reinterpret_cast<uint2*>(dst + plane + e * pitch) = l;
+        } else {
+            unsigned h[4];
 #pragma unroll
-        for (int i = 0; i < 4; i++) {
-            if constexpr (sizeof(KT) == 4) {
-                const float y = __uint_as_float(w[i][e]);
-                h[i] = f32_to_bf16_bits(y);
-                l[i] = f32_to_bf16_bits(y - bf16_bits_to_f32(h[i]));
-            } else {
-                h[i] = (w[i][e >> 1] >> ((e & 1) * 16)) & 0xffffu;
-            }
+            for (int i = 0; i < 4; i++) h[i] = (w[i][e >> 1] >> ((e & 1) * 16)) & 0xffffu;
+            *reinterpret_cast<uint2*>(dst + e * pitch) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
         }
-        *reinterpret_cast<uint2*>(dst + e * pitch) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
-        if constexpr (sizeof(KT) == 4)
-            *reinterpret_cast<uint2*>(dst + plane + e * pitch) = make_uint2(l[0] | (l[1] << 16), l[2] | (l[3] << 16));
     }
 }
 
@@ -2850,9 +2864,9 @@ __device__ __forceinline__ void store_v4(const u32x4_t (&v)[4], unsigned char* d
 // (hi = rne(x), lo = rne(x - hi), 16 mantissa bits together), and each contraction becomes three MFMAs
 // (hi.hi + lo.hi + hi.lo; the lo.lo term is below the 16 bits the planes carry).
 template <typename KT, int HD>
-__global__ __launch_bounds__(AT_THREADS) void attn_mfma_kernel(const float* __restrict__ q, int ldq,
+__global__ __launch_bounds__(AM_THREADS) void attn_mfma_kernel(const float* __restrict__ q, int ldq,
                                                                const KT* __restrict__ kc, const KT* __restrict__ vc,
-                                                               const int* pos_dev, int pos_off, int M, int H, int Hkv,
+                                                               const int* __restrict__ pos_dev, int pos_off, int M, int H, int Hkv,
                                                                int max_seq, int n_splits, float* __restrict__ part,
                                                                float* __restrict__ outp, int dq,
                                                                uint16_t* __restrict__ out_hi, uint16_t* __restrict__ out_lo,
@@ -2868,7 +2882,6 @@ __global__ __launch_bounds__(AT_THREADS) void attn_mfma_kernel(const float* __re
     constexpr int PT = AT_CHUNK / 16;          // position tiles of the chunk (6)
     constexpr int PS = AT_CHUNK / 32;          // k-steps of P.V (3)
     constexpr int DT = HD / 16;                // output dim tiles (8 or 4)
-    constexpr int DTW = DT / 4;                // dim tiles per wave
     constexpr int KPLANE = AT_CHUNK * ROWB, VPLANE = HD * AM_VPITCH;
     extern __shared__ __align__(16) unsigned char smem[];
     unsigned char* ktile = smem;                                       // [NP][AT_CHUNK][ROWB]
@@ -2885,10 +2898,10 @@ __global__ __launch_bounds__(AT_THREADS) void attn_mfma_kernel(const float* __re
     // the block's group of 16 query vectors (blockIdx.z)
     const int q0 = blockIdx.z * AT_QPASS;
     const int nq = min(AT_QPASS, Q - q0);
-    constexpr int QPT = AT_QPASS * HD / AT_THREADS;   // query elements per thread
+    constexpr int QPT = AT_QPASS * HD / AM_THREADS;   // query elements per thread
     float qreg[QPT];
-    constexpr int NV = (AT_CHUNK * VPR + AT_THREADS - 1) / AT_THREADS;
-    constexpr int VU = AT_CHUNK / 4 * VPR, NVU = (VU + AT_THREADS - 1) / AT_THREADS;   // V units of 4 positions x EPV dims; per thread
+    constexpr int NV = (AT_CHUNK * VPR + AM_THREADS - 1) / AM_THREADS;
+    constexpr int VU = AT_CHUNK / 4 * VPR, NVU = (VU + AM_THREADS - 1) / AM_THREADS;   // V units of 4 positions x EPV dims; per thread
     u32x4_t kr[NV], vr[NVU][4];
     // Query vectors, K and V are all requested before the position is known (one memory latency less on the way through the
     // kernel): cache rows past it may hold anything and are replaced by zeros when they are stored to LDS.
@@ -2897,22 +2910,23 @@ __global__ __launch_bounds__(AT_THREADS) void attn_mfma_kernel(const float* __re
     // 11.4 us against 9.5, 7B, 5 rows behind 540 positions of an fp32 cache.)
     auto v_unit = [](int u, int& pg, int& dg) { const int w = u >> 2; pg = w % (AT_CHUNK / 4); dg = w / (AT_CHUNK / 4) * 4 + (u & 3); };
     {
-#pragma unroll
-        for (int t = 0; t < QPT; t++) {
-            const int e = tid + t * AT_THREADS, qg = q0 + min(e / HD, nq - 1);
-            qreg[t] = q[(size_t)(qg / G) * ldq + (size_t)(kvh * G + qg % G) * HD + (e % HD)];
-        }
         const KT* kbase = kc + (size_t)kvh * max_seq * HD;
         const KT* vbase = vc + (size_t)kvh * max_seq * HD;
 #pragma unroll
         for (int t = 0; t < NV; t++) {
-            const int v = min(tid + t * AT_THREADS, AT_CHUNK * VPR - 1);
+            const int v = min(tid + t * AM_THREADS, AT_CHUNK * VPR - 1);
             kr[t] = *reinterpret_cast<const u32x4_t*>(kbase + (size_t)min(j0 + v / VPR, max_seq - 1) * HD + (v % VPR) * EPV);
+        }
+        asm volatile("" ::: "memory");   // (the divisions of the queries' addresses behind the requests for K)
+#pragma unroll
+        for (int t = 0; t < QPT; t++) {
+            const int e = tid + t * AM_THREADS, qg = q0 + min(e / HD, nq - 1);
+            qreg[t] = q[(size_t)(qg / G) * ldq + (size_t)(kvh * G + qg % G) * HD + (e % HD)];
         }
 #pragma unroll
         for (int t = 0; t < NVU; t++) {
             int pg, dg;
-            v_unit(min(tid + t * AT_THREADS, VU - 1), pg, dg);
+            v_unit(min(tid + t * AM_THREADS, VU - 1), pg, dg);
 #pragma unroll
             for (int i = 0; i < 4; i++)
                 vr[t][i] = *reinterpret_cast<const u32x4_t*>(vbase + (size_t)min(j0 + pg * 4 + i, max_seq - 1) * HD + dg * EPV);
@@ -2924,7 +2938,7 @@ __global__ __launch_bounds__(AT_THREADS) void attn_mfma_kernel(const float* __re
     // A chunk that lies wholly behind the causal horizon of the block's LAST query row contributes nothing (in a
     // prompt pass that is half of all blocks): leave empty partials and go.  Uniform over the block.
     if (n_splits > 1 && (n <= 0 || j0 > p0 + (q0 + nq - 1) / G)) {
-        for (int f = tid; f < nq * (HD / 4); f += AT_THREADS) {
+        for (int f = tid; f < nq * (HD / 4); f += AM_THREADS) {
             const int qi = f / (HD / 4), dd = (f % (HD / 4)) * 4;
             const int qg = q0 + qi, r = qg / G, head = kvh * G + qg % G;
             float* mine = part + (((size_t)r * H + head) * n_splits + split) * (HD + 4);
@@ -2938,21 +2952,16 @@ __global__ __launch_bounds__(AT_THREADS) void attn_mfma_kernel(const float* __re
         const u32x4_t zero = {0u, 0u, 0u, 0u};   // positions past the chunk: zero keys and values
 #pragma unroll
         for (int t = 0; t < NV; t++) {
-            const int v = tid + t * AT_THREADS;
+            const int v = tid + t * AM_THREADS;
             if (v < AT_CHUNK * VPR) {
                 const int pos = v / VPR, d0 = (v % VPR) * EPV;
                 const u32x4_t kk = v <= vmax ? kr[t] : zero;
                 if constexpr (F32) {
-                    const unsigned kw[4] = {kk.x, kk.y, kk.z, kk.w};
-                    unsigned kh[4], kl[4];
-#pragma unroll
-                    for (int e = 0; e < 4; e++) {
-                        const float x = __uint_as_float(kw[e]);
-                        kh[e] = f32_to_bf16_bits(x);
-                        kl[e] = f32_to_bf16_bits(x - bf16_bits_to_f32(kh[e]));
-                    }
-                    *reinterpret_cast<uint2*>(ktile + pos * ROWB + d0 * 2) = make_uint2(kh[0] | (kh[1] << 16), kh[2] | (kh[3] << 16));
-                    *reinterpret_cast<uint2*>(ktile + KPLANE + pos * ROWB + d0 * 2) = make_uint2(kl[0] | (kl[1] << 16), kl[2] | (kl[3] << 16));
+                    uint2 h, l;
+                    pair_hi_lo<false>(__uint_as_float(kk.x), __uint_as_float(kk.y), h.x, l.x);
+                    pair_hi_lo<false>(__uint_as_float(kk.z), __uint_as_float(kk.w), h.y, l.y);
+                    *reinterpret_cast<uint2*>(ktile + pos * ROWB + d0 * 2) = h;
+                    *reinterpret_cast<uint2*>(ktile + KPLANE + pos * ROWB + d0 * 2) = l;
                 } else {
                     *reinterpret_cast<u32x4_t*>(ktile + pos * ROWB + d0 * 2) = kk;
                 }
@@ -2960,8 +2969,8 @@ __global__ __launch_bounds__(AT_THREADS) void attn_mfma_kernel(const float* __re
         }
 #pragma unroll
         for (int t = 0; t < NVU; t++) {
-            const int u = tid + t * AT_THREADS;
-            if (VU % AT_THREADS == 0 || u < VU) {
+            const int u = tid + t * AM_THREADS;
+            if (VU % AM_THREADS == 0 || u < VU) {
                 int pg, dg;
                 v_unit(u, pg, dg);
                 const u32x4_t w4[4] = {pg * 4 < n ? vr[t][0] : zero, pg * 4 + 1 < n ? vr[t][1] : zero, pg * 4 + 2 < n ? vr[t][2] : zero,
@@ -2975,16 +2984,16 @@ __global__ __launch_bounds__(AT_THREADS) void attn_mfma_kernel(const float* __re
         // one after the other, each re-staging the chunk out of the cache
 #pragma unroll
         for (int t = 0; t < QPT; t++) {   // rows past nq: zero queries (their results are never stored)
-            const int e = tid + t * AT_THREADS;
+            const int e = tid + t * AM_THREADS;
             qs[e] = e / HD < nq ? qreg[t] * scale : 0.f;
         }
         __syncthreads();   // K, V^T and the query vectors are staged
         if (n > 0) {
-            // phase A: scores.  Wave w takes position tiles w, w + 4; D: lane (c = position, g) holds queries 4g .. 4g+3
+            // phase A: scores.  Wave w takes position tile w (w + 8, ..); D: lane (c = position, g) holds queries 4g .. 4g+3
             u32x4_t qh[KSTEPS], ql[KSTEPS];
 #pragma unroll
             for (int st = 0; st < KSTEPS; st++) split8<F16>(qs + r16 * HD + st * 32 + g * 8, qh[st], ql[st]);
-            for (int pt = wave; pt < PT; pt += 4) {
+            for (int pt = wave; pt < PT; pt += AM_WAVES) {
                 f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int st = 0; st < KSTEPS; st++) {
@@ -2999,9 +3008,9 @@ __global__ __launch_bounds__(AT_THREADS) void attn_mfma_kernel(const float* __re
             }
         }
         __syncthreads();
-        // phase B: causal mask, max, exp, sum.  Wave w owns queries 4w .. 4w+3, one per 16-lane row, so the two
+        // phase B: causal mask, max, exp, sum.  Wave w < 4 owns queries 4w .. 4w+3, one per 16-lane row, so the two
         // reductions are DPP row operations; entries past the visible range (and rows past nq) become 0
-        {
+        if (wave < 4) {
             const int qi = wave * 4 + g;
             int vis = 0;
             if (qi < nq) vis = min(n, p0 + (q0 + qi) / G + 1 - j0);   // positions of this chunk the row may see
@@ -3026,14 +3035,13 @@ __global__ __launch_bounds__(AT_THREADS) void attn_mfma_kernel(const float* __re
             if (r16 == 0) { ml[qi * 2] = mx; ml[qi * 2 + 1] = ls; }
         }
         __syncthreads();
-        // phase C: O = P.V.  Wave w takes output dim tiles w, w + 4, ...; A: lane (r = query, g) holds P[r][32 s + 8g ..],
+        // phase C: O = P.V.  Wave w takes output dim tile w; A: lane (r = query, g) holds P[r][32 s + 8g ..],
         // B: lane (c = dim, g) holds V^T[dim][32 s + 8g ..]; D: lane (c = dim, g) holds queries 4g .. 4g+3
         u32x4_t ph[PS], pl[PS];
 #pragma unroll
         for (int st = 0; st < PS; st++) split8<F16>(sc + r16 * AT_CHUNK + st * 32 + g * 8, ph[st], pl[st]);
 #pragma unroll
-        for (int t = 0; t < DTW; t++) {
-            const int dt = wave + 4 * t;
+        for (int dt = wave; dt < DT; dt += AM_WAVES) {
             f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
             if (n > 0) {
 #pragma unroll
@@ -3051,7 +3059,7 @@ __global__ __launch_bounds__(AT_THREADS) void attn_mfma_kernel(const float* __re
             for (int jx = 0; jx < 4; jx++) qs[(g * 4 + jx) * HD + dt * 16 + r16] = acc[jx];
         }
         __syncthreads();
-        for (int f = tid; f < nq * (HD / 4); f += AT_THREADS) {
+        for (int f = tid; f < nq * (HD / 4); f += AM_THREADS) {
             const int qi = f / (HD / 4), dd = (f % (HD / 4)) * 4;
             const float4 o = *reinterpret_cast<const float4*>(qs + qi * HD + dd);
             const int qg = q0 + qi, r = qg / G, head = kvh * G + qg % G;
@@ -3102,7 +3110,7 @@ static constexpr size_t attn_prompt_lds_bytes()
 template <typename KT, int HD>
 __global__ __launch_bounds__(AP_THREADS, 2) void attn_prompt_kernel(const float* __restrict__ q, int ldq,
                                                                  const KT* __restrict__ kc, const KT* __restrict__ vc,
-                                                                 const int* pos_dev, int pos_off, int M, int H, int Hkv,
+                                                                 const int* __restrict__ pos_dev, int pos_off, int M, int H, int Hkv,
                                                                  int max_seq, float* __restrict__ outp, int dq,
                                                                  uint16_t* __restrict__ out_hi, uint16_t* __restrict__ out_lo,
                                                                  bool out_f16)
@@ -3168,16 +3176,11 @@ __global__ __launch_bounds__(AP_THREADS, 2) void attn_prompt_kernel(const float*
             const int v = tid + t * AP_THREADS, pos = v / VPR, d0 = (v % VPR) * EPV;
             const u32x4_t kk = pos < n ? kr[t] : zero;
             if constexpr (F32) {
-                const unsigned kw[4] = {kk.x, kk.y, kk.z, kk.w};
-                unsigned kh[4], kl[4];
-#pragma unroll
-                for (int e = 0; e < 4; e++) {
-                    const float x = __uint_as_float(kw[e]);
-                    kh[e] = f32_to_bf16_bits(x);
-                    kl[e] = f32_to_bf16_bits(x - bf16_bits_to_f32(kh[e]));
-                }
-                *reinterpret_cast<uint2*>(ktile + pos * ROWB + d0 * 2) = make_uint2(kh[0] | (kh[1] << 16), kh[2] | (kh[3] << 16));
-                *reinterpret_cast<uint2*>(ktile + KPLANE + pos * ROWB + d0 * 2) = make_uint2(kl[0] | (kl[1] << 16), kl[2] | (kl[3] << 16));
+                uint2 h, l;
+                pair_hi_lo<false>(__uint_as_float(kk.x), __uint_as_float(kk.y), h.x, l.x);
+                pair_hi_lo<false>(__uint_as_float(kk.z), __uint_as_float(kk.w), h.y, l.y);
+                *reinterpret_cast<uint2*>(ktile + pos * ROWB + d0 * 2) = h;
+                *reinterpret_cast<uint2*>(ktile + KPLANE + pos * ROWB + d0 * 2) = l;
             } else {
                 *reinterpret_cast<u32x4_t*>(ktile + pos * ROWB + d0 * 2) = kk;
             }
@@ -3638,7 +3641,7 @@ static void launch_attn_staged(const Dims& D, const float* q, int ldq, const voi
             if (ensure_lds((const void*)attn_mfma_kernel<KT, HD>, lds, lds_limit) != hipSuccess)
                 return;   // the launch below then fails and reports
             const int Q = (D.H / D.Hkv) * M;
-            hipLaunchKernelGGL((attn_mfma_kernel<KT, HD>), dim3(n_splits, D.Hkv, ceil_div(Q, AT_QPASS)), dim3(AT_THREADS), lds, s, q, ldq,
+            hipLaunchKernelGGL((attn_mfma_kernel<KT, HD>), dim3(n_splits, D.Hkv, ceil_div(Q, AT_QPASS)), dim3(AM_THREADS), lds, s, q, ldq,
                                (const KT*)kc, (const KT*)vc, pos_dev, pos_off, M, D.H, D.Hkv, D.max_seq, n_splits, part, out, D.dq,
                                out_hi, out_lo, D.wt == WT_F16);
             return;

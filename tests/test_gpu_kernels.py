@@ -199,3 +199,16 @@ def test_products_of_a_single_row(shape, plen):
     st = lockstep_ssd(ctx, orc, prompt, 0, [3, 1], np.zeros(shape.n_layers, np.uint8), shape.dtype)
     assert st["unpinned_cycles"] <= 1 and st["draft_rows"] >= 3
     assert ctx.ssd_get_one_launch() == (0, 0, 0)
+
+
+# Verifications on the matrix-core attention: fewer rows than a wave's four queries, groups that fill several blocks of 16, heads of 64
+# (four of eight waves have output dims), contexts that end inside the first position tile, at the chunk's end and one behind it.
+@pytest.mark.parametrize("heads,kv_heads,kv", [(10, 10, "fp32"), (10, 2, "bf16"), (20, 20, "bf16"), (20, 4, "fp32")])
+@pytest.mark.parametrize("plen", [11, 91, 92, 187])
+def test_attention_of_a_verification(heads, kv_heads, kv, plen):
+    shape = ModelShape(2, 1280, heads, kv_heads, 192, 528)      # head_dim 128 (10 heads) or 64 (20 heads)
+    orc, ctx = make_pair(shape, 17, plen + 40, max_k=7, norm_gain_std=0.1, kv_dtype=kv)
+    prompt = make_prompt(shape.vocab, plen, 7).tolist()
+    st = lockstep_ssd(ctx, orc, prompt, 0, [4, 7], np.array([0, 1], np.uint8), shape.dtype)
+    assert st["unpinned_cycles"] <= 1
+    assert ctx.ssd_get_one_launch() == (0, 0, 0)
