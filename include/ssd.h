@@ -130,6 +130,9 @@ SSD_API int ssd_prefill(ssd_ctx *ctx, const int32_t *tokens, int n, int32_t *fir
 /* One vanilla autoregressive step with the full model (the baseline of Section 4.1.1):
  * feeds the pending token, commits and returns the greedy next token. */
 SSD_API int ssd_decode(ssd_ctx *ctx, int32_t *token_out);
+/* count such steps (count >= 1), their tokens to tokens_out[0 .. count): the results and the state of as many ssd_decode calls, but
+ * the host waits once per 32 steps.  SSD_ECAPACITY when the sequence is full before that; the steps up to there are committed. */
+SSD_API int ssd_decode_many(ssd_ctx *ctx, int count, int32_t *tokens_out);
 
 /* Draft model of Section 3: the target model without the layers in the skip set S
  * (skip_mask[l] != 0 means layer l is in S; a skipped layer leaves the residual stream

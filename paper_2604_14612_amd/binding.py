@@ -77,6 +77,7 @@ SYMBOLS = {
     "ssd_get_stats": (C.c_int, [_P, C.POINTER(ssd_stats)]),
     "ssd_prefill": (C.c_int, [_P, _P, C.c_int, _P]),
     "ssd_decode": (C.c_int, [_P, _P]),
+    "ssd_decode_many": (C.c_int, [_P, C.c_int, _P]),
     "ssd_draft_step": (C.c_int, [_P, _P, C.c_int, _P, _P]),
     "ssd_draft_step_sub": (C.c_int, [_P, _P, C.c_int, _P, _P]),
     "ssd_draft_adaptive": (C.c_int, [_P, _P, C.c_int, C.c_float, _P, _P, _P]),
@@ -356,6 +357,11 @@ class Context:
         out = C.c_int32()
         self._check(self._l.ssd_decode(self._h, C.addressof(out)))
         return out.value
+
+    def ssd_decode_many(self, count: int):
+        out = np.empty(max(int(count), 1), np.int32)
+        self._check(self._l.ssd_decode_many(self._h, int(count), _np_ptr(out)))
+        return out.tolist()
 
     def ssd_draft_step(self, skip_mask, k: int, want_maxprob: bool = False):
         m = np.ascontiguousarray(np.asarray(skip_mask, dtype=np.uint8))

@@ -131,7 +131,7 @@ enum { SM_POS = 0, SM_TOK = 8 /* 17 ints: pending + drafts */, SM_SINK = 96, SM_
 // call that uses a region synchronises before it returns, so the next one may write it.
 enum { PIN_TOK = 0 /* 17: slot i + 1 = token of draft step i */, PIN_PROB = 32 /* 16 */, PIN_STEP = 48 /* 1: a wait of the step in one launch gave up */, PIN_TARGET = 64 /* 64 */,
        PIN_VTOK = 128 /* 17: row 0 unused, drafts */, PIN_RES = 256 /* 3 x 2 x SSD_MAX_LAYERS */,
-       PIN_PROMPT = 256 + 6 * SSD_MAX_LAYERS /* max_seq */ };
+       PIN_PROMPT = 256 + 6 * SSD_MAX_LAYERS /* max_seq: prompt; tokens of decode steps that are waited for together */ };
 
 }  // namespace
 
@@ -246,6 +246,7 @@ static inline bool is_gemv_kid(int kid)
 // One launch whose blocks wait for each other may be in flight per device and process: two of them would each hold CUs that the
 // other one needs.  Whoever finds the device's slot taken uses the launches per matrix.  Other processes are not seen: against
 // theirs there is the bound of the waits.
+constexpr int DECODE_BATCH = 32;      // decode steps enqueued before their tokens are waited for
 constexpr int STEP_WAIT_US = 50000;   // longer than what other streams' kernels usually hold CUs for
 std::atomic<bool> step_slots[64];
 struct StepSlot {
@@ -293,8 +294,9 @@ int layer_single(ssd_ctx* c, int l, int pos_off, int plan_ctx, bool do_attn, boo
 // tok slot `slot_out` (device and PIN_TOK), its logits to logits row `lrow`, its max-probability to PIN_PROB[lrow].
 // sub (may be null): two entries per layer, [2l] != 0 leaves out the attention sub-block, [2l+1] != 0 the MLP sub-block.
 // flags: STEP_CHAINED = the previous step of the same sequence left this token's embedding in x; STEP_CHAIN_NEXT = leave
-// the new token's embedding there; STEP_COMMIT = the new token becomes the pending one and *pos advances.
-enum { STEP_CHAINED = 1, STEP_CHAIN_NEXT = 2, STEP_COMMIT = 4 };
+// the new token's embedding there; STEP_COMMIT = the new token becomes the pending one and *pos advances; STEP_LOG = it also goes
+// to PIN_PROMPT, at its predecessor's position.
+enum { STEP_CHAINED = 1, STEP_CHAIN_NEXT = 2, STEP_COMMIT = 4, STEP_LOG = 8 };
 int forward_single(ssd_ctx* c, const uint8_t* sub, int slot, int slot_out, int pos_off, int plan_ctx, int lrow, int flags)
 {
     const Dims& D = c->D;
@@ -307,6 +309,7 @@ int forward_single(ssd_ctx* c, const uint8_t* sub, int slot, int slot_out, int p
     out.tok_host = c->pinned + PIN_TOK + slot_out;
     out.maxprob_host = c->pin_f(PIN_PROB + lrow);
     if (flags & STEP_COMMIT) { out.pos_dev = c->pos_dev(); out.tok0 = c->small_i() + SM_TOK; }
+    if (flags & STEP_LOG) out.tok_log = c->pinned + PIN_PROMPT;
     if (flags & STEP_CHAIN_NEXT) {
         out.embed = c->w.embed; out.x_next = c->f(c->lay.x);
         out.rope = c->f(c->lay.rope); out.rope_pos = c->pos_dev(); out.rope_off = pos_off + 1; out.rope_row = c->small_f() + SM_ROPE;
@@ -1001,6 +1004,72 @@ int ssd_decode(ssd_ctx* c, int32_t* token_out)
     c->tap_rows = 0;
     c->st.decode_steps++; c->st.committed++;
     return SSD_OK;
+}
+
+// b steps whose results are waited for once: each leaves the embedding row of its token to the next one, and its token in the
+// pinned log.  done receives how many were committed: fewer than b where a wait of a step in one launch gave up (those behind it
+// commit nothing either).
+static int decode_batch(ssd_ctx* c, int b, int32_t* tokens_out, int& done)
+{
+    const int n = c->n;
+    bool fits = true;
+    for (int i = 0; i < b; i++) fits = fits && step_plan_fits(c->D, n + i, c->step_blocks);
+    StepSlot slot(c, c->step_on && c->step_blocks > 0 && c->step_table && c->step_try.on() && fits);
+    c->pinned[PIN_STEP] = 0;
+    auto run = [&]() -> int {
+        HIPCHK(embed_rows(c->D, c->w.embed, Tokens{c->small_i() + SM_TOK, nullptr}, 1, c->f(c->lay.x), c->stream, c->f(c->lay.rope), c->pos_dev(), 0,
+                          c->small_f() + SM_ROPE), "embed");
+        for (int i = 0; i < b; i++) {
+            if (c->graphs.size() >= 256) {   // run_sequence drops the sequences then: none may be in flight
+                const int rs = sync_results(c);
+                if (rs) return rs;
+            }
+            const int rc = run_sequence(c, (c->step_now ? "PN|" : "N|") + std::to_string(attention_splits(c->D, n + i, 1)), [&]() {
+                return forward_single(c, nullptr, 0, 1, 0, n + i, 0, STEP_CHAINED | STEP_CHAIN_NEXT | STEP_COMMIT | STEP_LOG); });
+            if (rc) return rc;
+        }
+        return SSD_OK;
+    };
+    const int rc = run(), rs = sync_results(c);
+    if (rc || rs) {
+        c->step_table = false;   // as in run_steps
+        return rc ? rc : rs;
+    }
+    done = b;
+    if (c->step_now) {
+        if (c->pinned[PIN_STEP]) {
+            int32_t pos = 0;
+            HIPCHK(hipMemcpyAsync(&pos, c->pos_dev(), 4, hipMemcpyDeviceToHost, c->stream), "position");
+            HIPCHK(hipMemsetAsync(c->ws + c->lay.step + 4, 0, 4, c->stream), "step error clear");
+            HIPCHK(hipStreamSynchronize(c->stream), "position");
+            done = pos - (n - 1);
+            c->step_gave_up++;
+            c->step_try.gave_up();
+        } else {
+            c->step_try.ran = true;
+        }
+        c->step_count += done;
+    }
+    memcpy(tokens_out, c->pinned + PIN_PROMPT + n - 1, sizeof(int32_t) * done);
+    c->n += done;
+    if (done > 0) { c->logit_rows = 1; c->tap_rows = 0; }
+    c->st.decode_steps += done; c->st.committed += done;
+    return SSD_OK;
+}
+
+int ssd_decode_many(ssd_ctx* c, int count, int32_t* tokens_out)
+{
+    if (!c || !tokens_out || count < 1) return c ? fail(c, SSD_EINVAL, "decode_many: bad argument") : SSD_EINVAL;
+    if (c->state != ST_IDLE) return fail(c, SSD_ESTATE, "decode needs a prefilled sequence with no draft in flight");
+    const int fit = std::min(count, c->D.max_seq - c->n);
+    for (int i = 0; i < fit;) {
+        int done = 1;
+        const int b = std::min(fit - i, DECODE_BATCH);
+        const int rc = b == 1 || c->prof_kid >= 0 ? ssd_decode(c, tokens_out + i) : decode_batch(c, b, tokens_out + i, done);
+        if (rc) return rc;
+        i += done;
+    }
+    return fit < count ? fail(c, SSD_ECAPACITY, "sequence would exceed max_seq") : SSD_OK;
 }
 
 // Keys of the replayed sequences of a draft, sub having two entries per layer: all k steps, and step i of an adaptive one.

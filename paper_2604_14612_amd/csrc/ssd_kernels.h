@@ -71,8 +71,9 @@ struct StepOut {
     int32_t* tok_out;                            // device slot
     int32_t* tok_host; float* maxprob_host;      // host-pinned: the host reads them after synchronising, no copy is enqueued
     int* pos_dev; int32_t* tok0;   // decode: *pos_dev += 1, *tok0 = token (both null: left alone)
+    int32_t* tok_log;              // decode, may be null (host-pinned): tok_log[*pos_dev before that] = token
     const void* embed; float* x_next;   // x_next set: x_next[0..d) = embedding row of the token
-    const float* rope; const int* rope_pos; int rope_off; float* rope_row;   // rope_row set: rotary row *rope_pos + rope_off of the next step
+    const float* rope; const int* rope_pos; int rope_off; float* rope_row;   // rope_row set: rotary row *rope_pos + rope_off of the next step (the table's last one at most)
     unsigned* step_ctrl; unsigned step_hops; int32_t* step_err_host;   // of step_fused: its control words, the hand-overs of the step, set to 1 (host-pinned) where a wait gave up
 };
 constexpr int GEMV_MAX_BLOCKS = 1024;

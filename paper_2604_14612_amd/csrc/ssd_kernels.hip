@@ -167,8 +167,8 @@ __device__ __forceinline__ void lds_barrier()
 // The rotary row of a single-row step's position is copied to a fixed place by whatever starts the step, so that the QKV
 // launches of its layers do not have to fetch the position before they can fetch the row.
 struct RopeRow {
-    const float* table; const int* pos_dev; int pos_off; int hd; float* out;   // out null: nothing to copy
-    __device__ __forceinline__ void copy(int t) const { out[t] = table[(size_t)(pos_dev[0] + pos_off) * hd + t]; }
+    const float* table; const int* pos_dev; int pos_off; int hd; int rows; float* out;   // out null: nothing to copy; rows of the table
+    __device__ __forceinline__ void copy(int t) const { out[t] = table[(size_t)min(pos_dev[0] + pos_off, rows - 1) * hd + t]; }
 };
 
 __device__ __forceinline__ int token_of(const Tokens& t, int r) { return r == 0 && t.first ? t.first[0] : t.ids[r]; }
@@ -186,7 +186,7 @@ __global__ void embed_kernel(const WT* __restrict__ E, Tokens tok, int d, int V,
 hipError_t embed_rows(const Dims& D, const void* embed, Tokens tok, int M, float* x, hipStream_t s, const float* rope,
                       const int* pos_dev, int pos_off, float* rope_row)
 {
-    const RopeRow rr = {rope, pos_dev, pos_off, D.hd, rope_row};
+    const RopeRow rr = {rope, pos_dev, pos_off, D.hd, D.max_seq, rope_row};
     dim3 grid(ceil_div(D.d, 256), M);
     if (D.wt == WT_BF16)
         hipLaunchKernelGGL(embed_kernel<uint16_t>, grid, dim3(256), 0, s, (const uint16_t*)embed, tok, D.d, D.V, x, rr);
@@ -672,7 +672,11 @@ __global__ __launch_bounds__(SF_THREADS) void step_finish_kernel(const float* __
                 o.step_ctrl[0] += o.step_hops;
                 if (!ok) o.step_err_host[0] = 1;
             }
-            if (o.pos_dev && ok) { o.pos_dev[0] += 1; o.tok0[0] = a.arg; }
+            if (o.pos_dev && ok) {
+                const int pos = o.pos_dev[0];   // (the next rotary row was copied before the barrier above)
+                if (o.tok_log) o.tok_log[pos] = a.arg;
+                o.pos_dev[0] = pos + 1; o.tok0[0] = a.arg;
+            }
         }
     }
     if (!o.x_next) return;   // uniform
@@ -685,7 +689,7 @@ __global__ __launch_bounds__(SF_THREADS) void step_finish_kernel(const float* __
 
 static hipError_t step_finish(const Dims& D, const float* vstat, int blocks, const StepOut& o, hipStream_t s)
 {
-    const RopeRow rr = {o.rope, o.rope_pos, o.rope_off, D.hd, o.rope_row};
+    const RopeRow rr = {o.rope, o.rope_pos, o.rope_off, D.hd, D.max_seq, o.rope_row};
     if (D.wt == WT_BF16) hipLaunchKernelGGL(step_finish_kernel<uint16_t>, dim3(1), dim3(SF_THREADS), 0, s, vstat, blocks, o, D.d, D.V, rr);
     else if (D.wt == WT_F16) hipLaunchKernelGGL(step_finish_kernel<f16_t>, dim3(1), dim3(SF_THREADS), 0, s, vstat, blocks, o, D.d, D.V, rr);
     else hipLaunchKernelGGL(step_finish_kernel<float>, dim3(1), dim3(SF_THREADS), 0, s, vstat, blocks, o, D.d, D.V, rr);

@@ -18,8 +18,8 @@ from .binding import Context, Search, search_defaults, select_defaults
 def generate_vanilla(ctx: Context, prompt: Sequence[int], n_new: int) -> List[int]:
     """n_new greedy tokens from the full model, one per step."""
     out = [ctx.ssd_prefill(prompt)]
-    while len(out) < n_new:
-        out.append(ctx.ssd_decode())
+    if n_new > 1:
+        out += ctx.ssd_decode_many(n_new - 1)
     return out[:n_new]
 
 
