@@ -29,7 +29,7 @@ struct Layout {
     size_t rope, kv, x, h, qkv, att, act, part, logits, taps, tapn, hi, lo, ssq, small, ring, ring_conf, step, total;
     int rows;       // activation rows: max(max_k + 1, prompt rows per pass)
     int prefill_rows;  // prompt rows per pass: SSD_PREFILL_ROWS where the shape fits the 128 x 128 tiling, 64 where only the
-                       // 64-row one, else 16
+                       // 64-row one or with fp32 weights, else 16
     int tap_rows;   // rows of the tap buffer: a verify block, or the 16 rows of a short prompt (a longer prompt keeps
                     // the taps of its last row only)
     int conf_rows;  // rows of one confidence pass: 2 * L
@@ -77,7 +77,7 @@ Layout make_layout(const ssd_config& c)
     Dims D = make_dims(c);
     Layout l;
     size_t esz = c.kv_dtype == 0 ? 4 : 2;
-    l.prefill_rows = rows_big_supported(D) ? SSD_PREFILL_ROWS : rows_wide_supported(D) ? 64 : 16;
+    l.prefill_rows = rows_big_supported(D) ? SSD_PREFILL_ROWS : rows_wide_supported(D) ? 64 : !rows_fused_supported(D) && rows_plain_supported(D) ? PLAIN_ROWS : 16;
     {   // no more rows per pass than a prompt can have (rounded up to whole 64-row groups)
         const int cap = (c.max_seq + 63) / 64 * 64;
         if (l.prefill_rows > 64 && l.prefill_rows > cap) l.prefill_rows = cap;
@@ -404,7 +404,7 @@ int forward_rows(ssd_ctx* c, int M, int pos_off, int pos_host, bool want_logits,
     float* x = c->f(Y.x);
     float* h = c->f(Y.h);
     const int tap_ld = D.L * 2 * D.d;
-    if (M > 16) {
+    if (M > 16 && rows_fused_supported(D)) {
         // prompt block: the same sequence as the 16-row path below, on 128 x 128 tiles over all rows of the block at
         // once (up to SSD_PREFILL_ROWS), or on 64-row weight tiles (up to 64 rows) where the shape does not fit those.
         // Only the last row of the last block leaves taps (in tap row 0), logits (row 0) and its greedy token
@@ -513,34 +513,44 @@ int forward_rows(ssd_ctx* c, int M, int pos_off, int pos_host, bool want_logits,
     HIPCHK(embed_rows(D, c->w.embed, tok, M, x, c->stream), "embed");
     if (rows_plain_supported(D)) {
         // fp32 weights (and fp16 shapes outside the tiling): fp32 rows between the launches, norms, rotary embedding and
-        // cache rows inside them
+        // cache rows inside them.  A prompt block of more than 16 rows leaves its last row's results in row 0, and of its last layer
+        // cache rows of all rows and the rest of that row (32 rows, 4 layers of 256: 382 us in blocks of 16, 187 so).
+        if (M > Y.rows) return fail(c, SSD_ECAPACITY, "row block too large for this shape");
+        const bool block = M > 16;
+        int R = M, r0 = 0;                                  // rows that go on, the first of them
+        float* taps = block && !want_logits ? nullptr : c->f(Y.taps);
         for (int l = 0; l < D.L; l++) {
             RowsPlain q = {};
             q.w[0] = c->wq[l]; q.w[1] = c->wk[l]; q.w[2] = c->wv[l]; q.n[0] = D.dq; q.n[1] = D.dkv; q.n[2] = D.dkv;
             q.K = D.d; q.x = x; q.gain = c->attn_norm[l]; q.y = c->f(Y.qkv); q.ldy = D.dq; q.M = M; q.mode = 3;
             q.rope = c->f(Y.rope); q.pos_dev = c->pos_dev(); q.pos_off = pos_off; q.kc = c->kcache(l); q.vc = c->vcache(l);
             TIMED(SSD_K_ROWS_QKV, rows_plain(D, q, c->stream), "plain_qkv");
-            TIMED(SSD_K_ATTENTION, attention(D, c->f(Y.qkv), D.dq, c->kcache(l), c->vcache(l), c->pos_dev(), pos_off, pos_host, M,
+            if (block && l + 1 == D.L) {
+                if (!want_logits) return SSD_OK;
+                R = 1; r0 = M - 1;
+            }
+            float* xr = x + (size_t)r0 * D.d;
+            TIMED(SSD_K_ATTENTION, attention(D, c->f(Y.qkv) + (size_t)r0 * D.dq, D.dq, c->kcache(l), c->vcache(l), c->pos_dev(), pos_off + r0, pos_host, R,
                                              c->f(Y.part), c->f(Y.att), nullptr, nullptr, c->stream), "attention");
             RowsPlain o = {};
-            o.w[0] = c->wo[l]; o.n[0] = D.d; o.K = D.dq; o.x = c->f(Y.att); o.y = x; o.ldy = D.d; o.M = M; o.mode = 1;
-            o.tap = c->f(Y.taps) + ((size_t)l * 2 + 0) * D.d; o.tap_ld = tap_ld;
+            o.w[0] = c->wo[l]; o.n[0] = D.d; o.K = D.dq; o.x = c->f(Y.att); o.y = xr; o.ldy = D.d; o.M = R; o.mode = 1;
+            o.tap = taps ? taps + ((size_t)l * 2 + 0) * D.d : nullptr; o.tap_ld = tap_ld; o.tap_only = block ? R : 0;
             TIMED(SSD_K_ROWS_O, rows_plain(D, o, c->stream), "plain_o");
             RowsPlain gu = {};
-            gu.w[0] = c->wg[l]; gu.w[1] = c->wu[l]; gu.n[0] = D.f; gu.n[1] = D.f; gu.K = D.d; gu.x = x; gu.gain = c->mlp_norm[l];
-            gu.y = c->f(Y.act); gu.ldy = D.f; gu.M = M; gu.mode = 2;
+            gu.w[0] = c->wg[l]; gu.w[1] = c->wu[l]; gu.n[0] = D.f; gu.n[1] = D.f; gu.K = D.d; gu.x = xr; gu.gain = c->mlp_norm[l];
+            gu.y = c->f(Y.act); gu.ldy = D.f; gu.M = R; gu.mode = 2;
             TIMED(SSD_K_ROWS_GATEUP, rows_plain(D, gu, c->stream), "plain_gateup");
             RowsPlain dn = {};
-            dn.w[0] = c->wd[l]; dn.n[0] = D.d; dn.K = D.f; dn.x = c->f(Y.act); dn.y = x; dn.ldy = D.d; dn.M = M; dn.mode = 1;
-            dn.tap = c->f(Y.taps) + ((size_t)l * 2 + 1) * D.d; dn.tap_ld = tap_ld;
+            dn.w[0] = c->wd[l]; dn.n[0] = D.d; dn.K = D.f; dn.x = c->f(Y.act); dn.y = xr; dn.ldy = D.d; dn.M = R; dn.mode = 1;
+            dn.tap = taps ? taps + ((size_t)l * 2 + 1) * D.d : nullptr; dn.tap_ld = tap_ld; dn.tap_only = block ? R : 0;
             TIMED(SSD_K_ROWS_DOWN, rows_plain(D, dn, c->stream), "plain_down");
         }
         if (want_logits) {
             RowsPlain lm = {};
-            lm.w[0] = c->w.lm_head; lm.n[0] = D.V; lm.K = D.d; lm.x = x; lm.gain = c->w.final_norm; lm.y = c->f(Y.logits);
-            lm.ldy = D.V; lm.M = M; lm.mode = 0;
+            lm.w[0] = c->w.lm_head; lm.n[0] = D.V; lm.K = D.d; lm.x = x + (size_t)r0 * D.d; lm.gain = c->w.final_norm; lm.y = c->f(Y.logits);
+            lm.ldy = D.V; lm.M = R; lm.mode = 0;
             TIMED(SSD_K_ROWS_LMHEAD, rows_plain(D, lm, c->stream), "plain_lmhead");
-            HIPCHK(vocab_reduce(c->f(Y.logits), M, D.V, c->cfg.conf_clamp, c->cfg.conf_eps, c->small_i() + SM_TARGET, c->pinned + PIN_TARGET,
+            HIPCHK(vocab_reduce(c->f(Y.logits), R, D.V, c->cfg.conf_clamp, c->cfg.conf_eps, c->small_i() + SM_TARGET, c->pinned + PIN_TARGET,
                                 nullptr, nullptr, nullptr, c->stream), "vocab_reduce");
         }
         return SSD_OK;

@@ -150,11 +150,13 @@ struct RowsPlain {
     const float* gain;   // null: rows as they are
     float* y; int ldy;
     float* tap; int tap_ld;
-    int M;
+    int M;               // up to PLAIN_ROWS
     int mode;
     const float* rope; const int* pos_dev; int pos_off;
     void* kc; void* vc;
+    int tap_only;        // > 0: only row tap_only - 1 writes its tap, into tap row 0
 };
+constexpr int PLAIN_ROWS = 64;
 bool rows_plain_supported(const Dims& D);
 hipError_t rows_plain(const Dims& D, const RowsPlain& g, hipStream_t s);
 // Multi-row MFMA GEMM for bf16 / fp16 weights with K a multiple of 64.  Activations come pre-split into

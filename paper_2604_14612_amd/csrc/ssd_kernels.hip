@@ -1068,7 +1068,7 @@ struct RowsPlainP {
     const float* x; // [M][K]
     const float* gain; float eps;   // RMSNorm of the rows folded in (null: rows as they are)
     float* y; int ldy;
-    float* tap; int tap_ld;
+    float* tap; int tap_ld; int tap_only;
     int M;
     const float* rope; const int* pos_dev; int pos_off;   // QKV
     int hd, dq, dkv, max_seq;
@@ -1200,7 +1200,10 @@ __global__ __launch_bounds__(256) void rows_plain_kernel(RowsPlainP p)
             float* y = p.y + (size_t)r * p.ldy + 2 * u;
             if (MODE == RM_RESID) {
                 a += y[0]; b += y[1];
-                if (p.tap) { float* tp = p.tap + (size_t)r * p.tap_ld + 2 * u; tp[0] = a; tp[1] = b; }
+                if (p.tap && (p.tap_only <= 0 || r == p.tap_only - 1)) {
+                    float* tp = p.tap + (size_t)(p.tap_only > 0 ? 0 : r) * p.tap_ld + 2 * u;
+                    tp[0] = a; tp[1] = b;
+                }
             }
             y[0] = a; y[1] = b;
         }
@@ -1226,12 +1229,12 @@ bool rows_plain_supported(const Dims& D) { return D.wt != WT_BF16; }
 
 hipError_t rows_plain(const Dims& D, const RowsPlain& g, hipStream_t s)
 {
-    if (!rows_plain_supported(D) || g.M < 1 || g.M > 16 || g.K % 8) return hipErrorInvalidValue;
+    if (!rows_plain_supported(D) || g.M < 1 || g.M > PLAIN_ROWS || g.K % 8) return hipErrorInvalidValue;
     if (g.mode != RM_QKV && g.mode != RM_SWIGLU && (g.n[1] || g.n[2])) return hipErrorInvalidValue;
     if (g.mode == RM_QKV && (g.n[0] != D.dq || g.n[1] != D.dkv || g.n[2] != D.dkv)) return hipErrorInvalidValue;
     RowsPlainP p = {};
     for (int i = 0; i < 3; i++) { p.w[i] = g.w[i]; p.n[i] = g.n[i]; }
-    p.K = g.K; p.x = g.x; p.gain = g.gain; p.eps = D.eps; p.y = g.y; p.ldy = g.ldy; p.tap = g.tap; p.tap_ld = g.tap_ld; p.M = g.M;
+    p.K = g.K; p.x = g.x; p.gain = g.gain; p.eps = D.eps; p.y = g.y; p.ldy = g.ldy; p.tap = g.tap; p.tap_ld = g.tap_ld; p.tap_only = g.tap_only; p.M = g.M;
     p.rope = g.rope; p.pos_dev = g.pos_dev; p.pos_off = g.pos_off; p.hd = D.hd; p.dq = D.dq; p.dkv = D.dkv; p.max_seq = D.max_seq;
     p.kc = g.kc; p.vc = g.vc; p.kt = D.kt;
     const bool f16 = D.wt == WT_F16;
@@ -2702,7 +2705,7 @@ __global__ __launch_bounds__(AT_THREADS) void attn_kernel(const float* __restric
         }
     }
     const float scale = 1.0f / sqrtf((float)HD);
-    for (int q0 = 0; q0 < Q; q0 += AT_QPASS) {   // uniform over the block
+    for (int q0 = blockIdx.z * AT_QPASS; q0 < Q; q0 += gridDim.z * AT_QPASS) {   // uniform over the block
         const int nq = min(AT_QPASS, Q - q0);
         __syncthreads();                         // staged tiles visible / previous pass done with qs, sc
         for (int e = tid; e < nq * HD; e += AT_THREADS) {
@@ -3654,7 +3657,8 @@ static void launch_attn_staged(const Dims& D, const float* q, int ldq, const voi
     const size_t lds = attn_lds_bytes<KT, HD>();
     static std::atomic<size_t> lds_limit{0};  // per instantiation
     if (ensure_lds((const void*)attn_kernel<KT, HD>, lds, lds_limit) != hipSuccess) return;
-    hipLaunchKernelGGL((attn_kernel<KT, HD>), dim3(n_splits, D.Hkv, 1), dim3(AT_THREADS), lds, s, q, ldq, (const KT*)kc,
+    // groups of 16 query vectors side by side, each staging the chunk for itself (one after the other in a block they took 12 us each)
+    hipLaunchKernelGGL((attn_kernel<KT, HD>), dim3(n_splits, D.Hkv, ceil_div((D.H / D.Hkv) * M, AT_QPASS)), dim3(AT_THREADS), lds, s, q, ldq, (const KT*)kc,
                        (const KT*)vc, pos_dev, pos_off, M, D.H, D.Hkv, D.max_seq, n_splits, part, out, D.dq, out_hi, out_lo,
                        D.wt == WT_F16);
 }

@@ -31,8 +31,10 @@ def test_cache_rows_of_a_prompt(name, kv, plen):
 # The last layer of a prompt block leaves keys and values of all rows and the rest for the last row only: one layer and several, the
 # 64-row blocks of shapes outside the large tiles, last blocks of one row, of 16 (the 16-row path behind a block of 512) and of more.
 @pytest.mark.parametrize("shape", [ModelShape(1, 512, 4, 4, 1408, 528), ModelShape(2, 256, 4, 1, 704, 640, dtype="fp16"),
-                                   ModelShape(2, 256, 2, 2, 640, 576)], ids=["one_layer", "gqa", "blocks_of_64"])
-@pytest.mark.parametrize("plen", [17, 64, 80, 81, 513, 530])
+                                   ModelShape(2, 256, 2, 2, 640, 576), ModelShape(3, 192, 3, 1, 336, 528, dtype="fp32"),
+                                   ModelShape(1, 256, 2, 2, 688, 528, dtype="fp32"), ModelShape(2, 256, 2, 1, 688, 528, dtype="fp16")],
+                         ids=["one_layer", "gqa", "blocks_of_64", "fp32", "fp32_one_layer", "fp16_untiled"])
+@pytest.mark.parametrize("plen", [17, 64, 65, 80, 81, 513, 530])
 def test_last_layer_of_a_prompt(shape, plen):
     orc, ctx = make_pair(shape, 9, plen + 16, max_k=4, norm_gain_std=0.1, init_std=0.08)
     prompt = make_prompt(shape.vocab, plen, 3).tolist()
