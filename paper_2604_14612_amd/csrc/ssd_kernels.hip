@@ -1744,6 +1744,35 @@ __device__ __forceinline__ void m6_row(const RowsP2& p, const M6Col& c, int tile
     }
 }
 
+// RMS scales of activation rows from the producer's sums of squares [M][n_ssq]: a wave takes NR rows, row0 + u * step, and requests the
+// sums of all of them together -- in front of its first weights, since loads return in order.  One row after the other, each
+// waiting for its own load, 16 rows took a wave of the large-tile kernel 16 us, before anything was multiplied.
+template <int NR>
+struct RowScales {
+    float v[NR];
+    __device__ __forceinline__ void load(const float* ssq, int n_ssq, int row0, int step, int M, int i0, int lane)
+    {
+        const int i = min(i0 + lane, n_ssq - 1);
+#pragma unroll
+        for (int u = 0; u < NR; u++) v[u] = ssq[(size_t)min(row0 + u * step, M - 1) * n_ssq + i];
+    }
+    // put(u, scale): called by all lanes, rows past M repeat the last one
+    template <typename F>
+    __device__ __forceinline__ void finish(const float* ssq, int n_ssq, int row0, int step, int M, int lane, int K, float eps, F&& put)
+    {
+        float t[NR];
+#pragma unroll
+        for (int u = 0; u < NR; u++) t[u] = lane < n_ssq ? v[u] : 0.f;
+        for (int i0 = 64; i0 < n_ssq; i0 += 64) {
+            load(ssq, n_ssq, row0, step, M, i0, lane);
+#pragma unroll
+            for (int u = 0; u < NR; u++) t[u] += i0 + lane < n_ssq ? v[u] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < NR; u++) put(u, 1.0f / sqrtf(wave_sum(t[u]) / (float)K + eps));
+    }
+};
+
 template <int MODE, bool F16, int M6_D>  // M6_D = stripes in flight per block
 __global__ __launch_bounds__(512) void rows_wide_kernel(RowsP2 p)
 {
@@ -1841,20 +1870,16 @@ __global__ __launch_bounds__(512) void rows_wide_kernel(RowsP2 p)
             }
         }
     };
+    // RMS scale of every activation row (read by the epilogue); a K-split launch leaves the scaling to its finishing kernel
+    const bool scaled = MODE != RM_RESID && p.ssq && S == 1;
+    RowScales<8> scales;
+    if (scaled) scales.load(p.ssq, p.n_ssq, wave, 8, M, 0, lane);
+    asm volatile("" ::: "memory");
 #pragma unroll
     for (int sl = 0; sl < M6_D; sl++)
         if (sl < NC) gload(sl, sl);
-    // RMS scale of every activation row from the producer's per-tile sums of squares (read by the epilogue)
-    if (tid < 64) rs[tid] = 1.0f;
-    if (MODE != RM_RESID && p.ssq && S == 1) {   // (a K-split launch leaves the scaling to its finishing kernel)
-        __syncthreads();
-        for (int c = wave; c < M; c += 8) {
-            float sq = 0.f;
-            for (int i = lane; i < p.n_ssq; i += 64) sq += p.ssq[(size_t)c * p.n_ssq + i];
-            sq = wave_sum(sq);
-            if (lane == 0) rs[c] = 1.0f / sqrtf(sq / (float)K + p.eps);
-        }
-    }
+    if (scaled) scales.finish(p.ssq, p.n_ssq, wave, 8, M, lane, K, p.eps, [&](int u, float v) { if (lane == 0) rs[wave + 8 * u] = v; });
+    else if (tid < 64) rs[tid] = 1.0f;
     int ck0 = 0;
     for (; ck0 + 2 * M6_D <= NC; ck0 += M6_D) {   // steady state: every step refills its slot
 #pragma unroll
@@ -1934,33 +1959,44 @@ __global__ __launch_bounds__(64) void rows_finish_kernel(RowsP2 p)
     const int mbase = blockIdx.y * FIN_ROWS;
     const size_t nt = (size_t)gridDim.x * 64, colx = (size_t)blockIdx.x * 64 + lane;
     const M6Col col = m6_col<MODE>(p, tile, lane, m6_pos0<MODE>(p));
-    float v[FIN_ROWS], v2[FIN_ROWS], sq[FIN_ROWS];
+    const bool scaled = MODE != RM_RESID && p.ssq;
+    RowScales<FIN_ROWS> scales;
+    if (scaled) scales.load(p.ssq, p.n_ssq, mbase, 1, p.M, 0, lane);
+    float v[FIN_ROWS], v2[FIN_ROWS], sc[FIN_ROWS];
     M6Pre pre[FIN_ROWS];
 #pragma unroll
     for (int r = 0; r < FIN_ROWS; r++) {
         const int m = min(mbase + r, p.M - 1);   // rows past M re-read the last row, never written
-        v[r] = v2[r] = sq[r] = 0.f;
-        if (MODE != RM_RESID && p.ssq)
-            for (int i = lane; i < p.n_ssq; i += 64) sq[r] += p.ssq[(size_t)m * p.n_ssq + i];
+        v[r] = v2[r] = 0.f;
         pre[r] = m6_pre<MODE>(p, col, m);
     }
-    for (int sl = 0; sl < p.ksplit; sl++) {
+    // two slices of all rows are requested together (slices past the last one re-read it, never added)
+    for (int s0 = 0; s0 < p.ksplit; s0 += 2) {
+        float a[2][FIN_ROWS], b[2][FIN_ROWS];
 #pragma unroll
-        for (int r = 0; r < FIN_ROWS; r++) {
-            const int m = min(mbase + r, p.M - 1);
-            v[r] += p.kpart[(((size_t)sl * NT + 0) * p.M + m) * nt + colx];
-            if (MODE == RM_SWIGLU) v2[r] += p.kpart[(((size_t)sl * NT + 1) * p.M + m) * nt + colx];
-        }
+        for (int u = 0; u < 2; u++)
+#pragma unroll
+            for (int r = 0; r < FIN_ROWS; r++) {
+                const int m = min(mbase + r, p.M - 1), sl = min(s0 + u, p.ksplit - 1);
+                a[u][r] = p.kpart[(((size_t)sl * NT + 0) * p.M + m) * nt + colx];
+                if (MODE == RM_SWIGLU) b[u][r] = p.kpart[(((size_t)sl * NT + 1) * p.M + m) * nt + colx];
+            }
+#pragma unroll
+        for (int u = 0; u < 2; u++)
+#pragma unroll
+            for (int r = 0; r < FIN_ROWS; r++)
+                if (s0 + u < p.ksplit) {   // uniform
+                    v[r] += a[u][r];
+                    if (MODE == RM_SWIGLU) v2[r] += b[u][r];
+                }
     }
+    if (scaled) scales.finish(p.ssq, p.n_ssq, mbase, 1, p.M, lane, p.K, p.eps, [&](int u, float x) { sc[u] = x; });
 #pragma unroll
     for (int r = 0; r < FIN_ROWS; r++) {
         const int m = mbase + r;
         if (m >= p.M) break;   // uniform
         float a = v[r], b = v2[r];
-        if (MODE != RM_RESID && p.ssq) {
-            const float sc = 1.0f / sqrtf(wave_sum(sq[r]) / (float)p.K + p.eps);
-            a *= sc; b *= sc;
-        }
+        if (scaled) { a *= sc[r]; b *= sc[r]; }
         m6_row<MODE, F16>(p, col, tile, m, lane, a, b, pre[r]);
     }
 }
@@ -2076,20 +2112,15 @@ __global__ __launch_bounds__(TN == 128 ? 256 : 512, 2) void rows_big_kernel(Rows
     const unsigned char* wfrag = Ws + (wn * WR + r16) * MB_PITCH + g * 16;
     const unsigned char* hfrag = Bh + (wm * 64 + r16) * MB_PITCH + g * 16;
     const unsigned char* lfrag = Bl + (wm * 64 + r16) * MB_PITCH + g * 16;
-    // RMS scale of the block's activation rows from the producer's per-tile sums of squares (a K-split launch leaves
-    // the scaling to its finishing kernel)
+    // RMS scale of the block's activation rows (a K-split launch leaves the scaling to its finishing kernel)
+    constexpr int SR = MB_TM / (NTH / 64);   // rows of a wave
+    const bool scaled = MODE != RM_RESID && p.ssq && S == 1;
+    RowScales<SR> scales;
+    if (scaled) scales.load(p.ssq, p.n_ssq, m0 + wave, NTH / 64, M, 0, lane);
+    asm volatile("" ::: "memory");
     auto row_scales = [&]() {
-        if (tid < MB_TM) rs[tid] = 1.0f;
-        if (MODE != RM_RESID && p.ssq && S == 1) {
-            __syncthreads();
-            for (int c = wave; c < MB_TM; c += NTH / 64) {
-                const int m = min(m0 + c, M - 1);
-                float sq = 0.f;
-                for (int i = lane; i < p.n_ssq; i += 64) sq += p.ssq[(size_t)m * p.n_ssq + i];
-                sq = wave_sum(sq);
-                if (lane == 0) rs[c] = 1.0f / sqrtf(sq / (float)K + p.eps);
-            }
-        }
+        if (scaled) scales.finish(p.ssq, p.n_ssq, m0 + wave, NTH / 64, M, lane, K, p.eps, [&](int u, float v) { if (lane == 0) rs[wave + NTH / 64 * u] = v; });
+        else if (tid < MB_TM) rs[tid] = 1.0f;
     };
     if constexpr (!BIG) {
         // One stripe = 2 k-steps x 4 groups of 16 activation rows.  The weight fragments of both k-steps are read up
