@@ -2435,43 +2435,29 @@ hipError_t rows_big(const Dims& D, const RowsFused& f, hipStream_t s)
     const int n_tiles = n_total / tn;
     p.n_tiles = n_tiles;
     const bool f16 = D.wt == WT_F16;
-    // a residual projection with fewer blocks than resident slots (two per CU for the small tile, one for the large)
-    // is cut along K (its raw sums go to kpart and rows_finish_kernel adds the slices in a fixed order)
+    // A residual projection or a QKV launch that leaves resident slots empty (two per CU for the small tile, one for the
+    // large) is cut along K: its raw sums go to kpart, rows_finish_kernel adds the slices in a fixed order and runs the epilogue.
     p.ksplit = 1; p.kpart = nullptr;
     const int force_ks = D.opt ? D.opt->wide_ksplit : 0;
-    if (f.kpart && f.mode == RM_RESID && force_ks != 1) {
+    const int slots = tn != 128 ? 256 : 512, nc = f.K / MB_CK;
+    if (f.kpart && (f.mode == RM_RESID || f.mode == RM_QKV) && force_ks != 1) {
         const size_t per_slice = (size_t)f.M * n_tiles * tn;
-        int ks = force_ks > 1 ? force_ks : (tn != 128 ? 256 : 512) / (n_tiles * m_blocks);
-        const int nc = f.K / MB_CK;
-        if (ks > 8) ks = 8;
-        if (ks > nc) ks = nc;
-        if ((size_t)ks * per_slice > f.kpart_floats) ks = (int)(f.kpart_floats / per_slice);
-        if (ks > 1) { p.ksplit = ks; p.kpart = f.kpart; }
-    }
-    // A QKV launch with blocks for at most half of the slots (prompts of up to 256 rows at the 7B shape) is cut along K
-    // as well; its finishing kernel rotates and writes the cache rows.
-    if (f.kpart && f.mode == RM_QKV && force_ks != 1) {
-        const int slots = tn != 128 ? 256 : 512, nc = f.K / MB_CK;
-        const size_t per_slice = (size_t)f.M * n_tiles * tn;
-        int ks = force_ks > 1 ? force_ks : slots / (n_tiles * m_blocks);
-        if (ks > 4) ks = 4;
+        int ks = force_ks > 1 ? force_ks : k_slices(n_tiles * m_blocks, slots, nc, 4.0 * (double)per_slice, f.mode == RM_QKV ? 4 : 8);
         if (ks > nc) ks = nc;
         if ((size_t)ks * per_slice > f.kpart_floats) ks = (int)(f.kpart_floats / per_slice);
         if (ks > 1) { p.ksplit = ks; p.kpart = f.kpart; }
     }
     // Gate / up with a last round that would leave most CUs idle (7B, 512 rows: 344 blocks for 256 slots): the tiles
-    // of the whole rounds run as they are, the rest (all of them when there is no whole round) are cut along K into as
-    // many slices as fill the slots once more, and the finishing kernel adds the slices and applies SwiGLU
-    // (1 + 1/2 block times instead of 2).
+    // of the whole rounds run as they are, the rest (all of them when there is no whole round) are cut along K, and the
+    // finishing kernel adds the slices and applies SwiGLU (there 1 + 1/2 block times instead of 2).
     if (f.kpart && f.mode == RM_SWIGLU && force_ks != 1) {
-        const int slots = tn != 128 ? 256 : 512, units = n_tiles * m_blocks;
+        const int units = n_tiles * m_blocks;
         const int whole_tiles = units / slots * slots / m_blocks, tail_tiles = n_tiles - whole_tiles;
-        const int tail_units = tail_tiles * m_blocks, nc = f.K / MB_CK;
+        const int tail_units = tail_tiles * m_blocks;
         if (tail_tiles > 0) {
-            int ks = slots / tail_units;
-            if (ks > 4) ks = 4;
-            if (ks > nc) ks = nc;
             const size_t per_slice = (size_t)2 * f.M * tail_tiles * (tn / 2);
+            int ks = force_ks > 1 ? force_ks : k_slices(tail_units, slots, nc, 4.0 * (double)per_slice, 4);
+            if (ks > nc) ks = nc;
             if ((size_t)ks * per_slice > f.kpart_floats) ks = (int)(f.kpart_floats / per_slice);
             if (ks > 1) {
                 if (whole_tiles > 0) {

@@ -45,6 +45,23 @@ SSD_HD int qkv_tile_rows(int n_total, int m_blocks)
     return best;
 }
 
+// K slices of a large-tile launch of `blocks` blocks for `slots` of them at a time, `stripes` 64-wide stripes long: the least of an
+// estimate of the launch and its finishing launch, in us.  A block costs 8 and 1.9 per stripe (128-row tiles, two to a CU: 2.85), the
+// finishing launch 6 and its slices, of slice_bytes, at 4 TB/s.  More slices than fill the slots once pay where a last round would be
+// nearly empty.  Measured, us, launch and finish, filling the slots at most once / so: 70B, 300 rows, gate/up 661 / 603, output and down
+// projection 238 / 215 on average; 13B, 512 rows, keys and values 203 / 147.
+SSD_HD int k_slices(int blocks, int slots, int stripes, double slice_bytes, int most)
+{
+    const double stripe = slots > 256 ? 2.85 : 1.9;
+    int best = 1;
+    double best_us = 0.0;
+    for (int ks = 1; ks <= most && ks <= stripes; ks++) {
+        const double us = ceil_div(blocks * ks, slots) * (8.0 + stripe * ceil_div(stripes, ks)) + (ks > 1 ? 6.0 + ks * slice_bytes / 4e6 : 0.0);
+        if (ks == 1 || us < best_us) { best = ks; best_us = us; }
+    }
+    return best;
+}
+
 // ---- attention launch plan ---------------------------------------------------------------------------------------------
 // Few query vectors per KV head (M x group size <= AW_MAXQ_TOTAL): the register-resident kernel over ranges of 64 positions
 // and more -- a single CU pulls only a few tens of GB/s, so a head's cache is spread over many blocks even though that

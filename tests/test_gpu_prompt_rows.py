@@ -45,3 +45,12 @@ def test_last_layer_of_a_prompt(shape, plen):
     ctx.ssd_reset()
     st = lockstep_ssd(ctx, orc, prompt, 0, [4, 1], np.zeros(shape.n_layers, np.uint8), shape.dtype)   # reads the cache rows
     assert st["unpinned_cycles"] <= 1
+
+
+# K slices of unequal length and more blocks than slots: 20 and 53 stripes of K, an odd number of 128-row tiles
+@pytest.mark.parametrize("shape", [ModelShape(2, 1280, 10, 2, 3392, 640), ModelShape(2, 1152, 9, 9, 3392, 640, dtype="fp16")], ids=["gqa", "mha"])
+def test_uneven_k_slices(shape):
+    orc, ctx = make_pair(shape, 9, 320, max_k=2, norm_gain_std=0.1, init_std=0.03)
+    prompt = make_prompt(shape.vocab, 300, 3).tolist()
+    st = lockstep_ssd(ctx, orc, prompt, 0, [2], np.zeros(shape.n_layers, np.uint8), shape.dtype)
+    assert st["unpinned_cycles"] <= 1 and st["verify_rows"] == 3

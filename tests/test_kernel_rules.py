@@ -14,6 +14,7 @@ WRAPPERS = r"""
 #include "ssd_rules.h"
 using namespace ssdk;
 extern "C" {
+int k_slices_of(int blocks, int slots, int stripes, double slice_bytes, int most) { return ssdk::k_slices(blocks, slots, stripes, slice_bytes, most); }
 void attention_plan(int G, int Hkv, int hd, int kv_f32, int w_f32, int ctx, int M, int* out) {
     const AttnPlan p = attn_plan(AttnShape{G, Hkv, hd, kv_f32 != 0, w_f32 != 0}, ctx, M, 0, 0);
     out[0] = p.wide; out[1] = p.n_splits; out[2] = p.chunk;
@@ -117,3 +118,23 @@ def test_qkv_tiles_are_the_faster_ones_where_both_were_measured(rules):
         for mb in (1, 2, 3, 4):
             t = rules.qkv_tile(n, mb)
             assert t in (128, 192, 256) and n % t == 0
+
+
+def test_k_slices_of_the_large_tiles(rules):
+    """The cut is the faster one where two were measured, every slice has a stripe, and a launch that fills its slots is not cut."""
+    rules.k_slices_of.argtypes = [C.c_int, C.c_int, C.c_int, C.c_double, C.c_int]
+    measured = {(64, 64, 512 * 4096, 8): 4,            # 7B, 512 rows, output projection
+                (64, 172, 512 * 4096, 8): 4,           # .. down projection
+                (128, 64, 512 * 8192, 4): 2,           # .. keys and values
+                (160, 80, 512 * 10240, 4): 3,          # 13B, keys and values
+                (162, 128, 2 * 300 * 6912, 4): 3,      # 70B, 300 rows, the last tiles of gate/up
+                (96, 128, 300 * 8192, 8): 5}           # .. output projection
+    for (blocks, stripes, sums, most), ks in measured.items():
+        assert rules.k_slices_of(blocks, 256, stripes, 4.0 * sums, most) == ks, (blocks, stripes)
+    for slots in (256, 512):
+        for blocks in range(1, 3 * slots, 7):
+            for stripes in (1, 2, 3, 16, 64, 448):
+                ks = rules.k_slices_of(blocks, slots, stripes, 4e6, 8)
+                assert 1 <= ks <= min(8, stripes)
+                if blocks % slots == 0:
+                    assert ks == 1
