@@ -136,6 +136,34 @@ __device__ __forceinline__ float row16_max(float v)
     return dpp_max<0x121>(v);
 }
 
+// exchanges between the 16-lane rows of a wave without the LDS crossbar: sum / max over rows 0 + 1 and 2 + 3, over both halves
+__device__ __forceinline__ float rows_swap_sum(float v)
+{
+    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float rows_swap_max(float v)
+{
+    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float wave_sum_fast(float v) { return rows_swap_sum(row16_sum(v)); }
+// maximum of a wave, and of the integers of its lanes the least one, without the LDS crossbar; every lane gets them
+__device__ __forceinline__ float wave_max_fast(float v) { return rows_swap_max(row16_max(v)); }
+template <int CTRL> __device__ __forceinline__ int dpp_min_i(int v) { return min(v, __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, false)); }
+__device__ __forceinline__ int wave_min_fast(int v)
+{
+    v = dpp_min_i<0x121>(dpp_min_i<0x122>(dpp_min_i<0x124>(dpp_min_i<0x128>(v))));
+    auto r = __builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false);
+    v = min((int)r[0], (int)r[1]);
+    r = __builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false);
+    return min((int)r[0], (int)r[1]);
+}
+
 // Block-wide sum for blocks of NW waves; red must hold NW values. All threads get the result.
 template <int NW, typename T>
 __device__ __forceinline__ T block_sum(T v, T* red)
@@ -643,12 +671,13 @@ __global__ __launch_bounds__(SF_THREADS) void step_finish_kernel(const float* __
     __shared__ VStat sm[SF_THREADS / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (rr.out && tid < rr.hd) rr.copy(tid);   // of the next step
+    // (three reductions over the lanes, an exponential each; merging pairs of records takes six rounds of shuffles and
+    // exponentials: 1000 records of a 7B step 5.2 -> 4.3 us, what the shortest launch of a replayed sequence takes)
     auto wave_merge = [](VStat& a) {
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            const VStat b = {__shfl_xor(a.m, o, 64), __shfl_xor(a.z, o, 64), __shfl_xor(a.arg, o, 64)};
-            vstat_merge(a, b);
-        }
+        const float m = wave_max_fast(a.m);
+        a.z = wave_sum_fast(a.m > -INFINITY ? a.z * __expf(a.m - m) : 0.f);
+        a.arg = wave_min_fast(a.m == m ? a.arg : 0x7fffffff);
+        a.m = m;
     };
     VStat a = {-INFINITY, 0.f, 0x7fffffff};
     for (int i = tid; i < n_blocks; i += SF_THREADS) {
@@ -3831,22 +3860,6 @@ __device__ __forceinline__ int next_layer(uint64_t lo, uint64_t hi, int l)
     const unsigned long long b = l < 128 ? hi >> (l - 64) << (l - 64) : 0;
     return b ? 63 + __ffsll(b) : -1;
 }
-// exchanges between the 16-lane rows of a wave without the LDS crossbar: sum / max over rows 0 + 1 and 2 + 3, over both halves
-__device__ __forceinline__ float rows_swap_sum(float v)
-{
-    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-    r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-__device__ __forceinline__ float rows_swap_max(float v)
-{
-    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-    r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-__device__ __forceinline__ float wave_sum_fast(float v) { return rows_swap_sum(row16_sum(v)); }
 // the same over the segments of LPP lanes of a wave, for values that are uniform inside each segment or belong to its lanes
 template <int LPP> __device__ __forceinline__ float seg_sum_fast(float v)
 {
@@ -4973,12 +4986,9 @@ constexpr int VR_THREADS = 1024;
 // maximum of a wave and its lowest index
 __device__ __forceinline__ void argmax_wave(float& m, int& mi)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const float om = __shfl_xor(m, o, 64);
-        const int oi = __shfl_xor(mi, o, 64);
-        if (om > m || (om == m && oi < mi)) { m = om; mi = oi; }
-    }
+    const float wm = wave_max_fast(m);
+    mi = wave_min_fast(m == wm ? mi : 0x7fffffff);
+    m = wm;
 }
 
 __global__ __launch_bounds__(VR_THREADS) void vocab_reduce_kernel(const float* __restrict__ logits, int V, float clamp,
