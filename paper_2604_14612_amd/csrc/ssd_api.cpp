@@ -26,7 +26,7 @@ constexpr size_t ALIGN = 256;
 size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 
 struct Layout {
-    size_t rope, kv, x, h, qkv, att, act, part, logits, taps, tapn, hi, lo, ssq, small, ring, ring_conf, step, total;
+    size_t rope, kv, x, h, qkv, att, act, part, logits, taps, tapn, hi, lo, ssq, small, ring, ring_conf, step, arrive, total;
     int rows;       // activation rows: max(max_k + 1, prompt rows per pass)
     int prefill_rows;  // prompt rows per pass: SSD_PREFILL_ROWS where the shape fits the 128 x 128 tiling, 64 where only the
                        // 64-row one or with fp32 weights, else 16
@@ -118,6 +118,7 @@ Layout make_layout(const ssd_config& c)
     l.ring = o;       o += align_up((size_t)c.conf_window * 2 * D.L * D.d * sizeof(float));
     l.ring_conf = o;  o += align_up((size_t)c.conf_window * 2 * D.L * sizeof(float));
     l.step = o;       o += align_up(step_scratch_bytes(D));   // hand-over words and weight table of the single-row step in one launch
+    l.arrive = o;     o += align_up(ATTN_COUNTERS * 4);
     l.total = o;
     return l;
 }
@@ -180,6 +181,7 @@ struct ssd_ctx {
     float* small_f() const { return reinterpret_cast<float*>(ws + lay.small); }
     float* pin_f(int word) const { return reinterpret_cast<float*>(pinned + word); }
     int* pos_dev() const { return small_i() + SM_POS; }
+    unsigned* arrive() const { return reinterpret_cast<unsigned*>(ws + lay.arrive); }
     void* kcache(int l) const
     {
         size_t esz = cfg.kv_dtype == 0 ? 4 : 2;
@@ -437,7 +439,7 @@ int forward_rows(ssd_ctx* c, int M, int pos_off, int pos_host, bool want_logits,
             }
             TIMED(SSD_K_ROWS_QKV, gemm(q), "wide_qkv");
             TIMED(SSD_K_ATTENTION, attention(D, c->f(Y.qkv), D.dq, c->kcache(l), c->vcache(l), c->pos_dev(), pos_off,
-                                             pos_host, M, c->f(Y.part), nullptr, hi, lo, c->stream), "attention");
+                                             pos_host, M, c->f(Y.part), nullptr, hi, lo, c->stream, nullptr, c->arrive()), "attention");
             RowsFused o = {};
             o.w[0] = c->wo[l]; o.n[0] = D.d; o.K = D.dq; o.bh = hi; o.bl = lo; o.ldb = D.dq; o.y = x; o.ldy = D.d; o.M = M;
             o.mode = 1; o.tap = want_logits ? c->f(Y.taps) + ((size_t)l * 2 + 0) * D.d : nullptr; o.tap_ld = tap_ld; o.tap_only = M;
@@ -480,7 +482,7 @@ int forward_rows(ssd_ctx* c, int M, int pos_off, int pos_host, bool want_logits,
             q.rope = c->f(Y.rope); q.pos_dev = c->pos_dev(); q.pos_off = pos_off; q.kc = c->kcache(l); q.vc = c->vcache(l);
             TIMED(SSD_K_ROWS_QKV, rows_fused(D, q, c->stream), "rows_qkv");
             TIMED(SSD_K_ATTENTION, attention(D, c->f(Y.qkv), D.dq, c->kcache(l), c->vcache(l), c->pos_dev(), pos_off,
-                                             pos_host, M, c->f(Y.part), nullptr, hi, lo, c->stream), "attention");
+                                             pos_host, M, c->f(Y.part), nullptr, hi, lo, c->stream, nullptr, c->arrive()), "attention");
             RowsFused o = {};
             o.w[0] = c->wo[l]; o.n[0] = D.d; o.K = D.dq; o.bh = hi; o.bl = lo; o.ldb = D.dq; o.y = x; o.ldy = D.d; o.M = M;
             o.mode = 1; o.tap = c->f(Y.taps) + ((size_t)l * 2 + 0) * D.d; o.tap_ld = tap_ld;
@@ -531,7 +533,7 @@ int forward_rows(ssd_ctx* c, int M, int pos_off, int pos_host, bool want_logits,
             }
             float* xr = x + (size_t)r0 * D.d;
             TIMED(SSD_K_ATTENTION, attention(D, c->f(Y.qkv) + (size_t)r0 * D.dq, D.dq, c->kcache(l), c->vcache(l), c->pos_dev(), pos_off + r0, pos_host, R,
-                                             c->f(Y.part), c->f(Y.att), nullptr, nullptr, c->stream), "attention");
+                                             c->f(Y.part), c->f(Y.att), nullptr, nullptr, c->stream, nullptr, c->arrive()), "attention");
             RowsPlain o = {};
             o.w[0] = c->wo[l]; o.n[0] = D.d; o.K = D.dq; o.x = c->f(Y.att); o.y = xr; o.ldy = D.d; o.M = R; o.mode = 1;
             o.tap = taps ? taps + ((size_t)l * 2 + 0) * D.d : nullptr; o.tap_ld = tap_ld; o.tap_only = block ? R : 0;
@@ -565,7 +567,7 @@ int forward_rows(ssd_ctx* c, int M, int pos_off, int pos_host, bool want_logits,
         HIPCHK(rope_kv_rows(D, c->f(Y.qkv), c->f(Y.rope), c->pos_dev(), pos_off, M, c->kcache(l), c->vcache(l),
                             c->stream), "rope_kv");
         TIMED(SSD_K_ATTENTION, attention(D, c->f(Y.qkv), D.dq + 2 * D.dkv, c->kcache(l), c->vcache(l), c->pos_dev(),
-                                         pos_off, pos_host, M, c->f(Y.part), c->f(Y.att), nullptr, nullptr, c->stream), "attention");
+                                         pos_off, pos_host, M, c->f(Y.part), c->f(Y.att), nullptr, nullptr, c->stream, nullptr, c->arrive()), "attention");
         RowsGemm o = {};
         o.w[0] = c->wo[l]; o.n[0] = D.d; o.K = D.dq; o.x = c->f(Y.att); o.y = x; o.ldy = D.d; o.M = M; o.mode = 1;
         o.tap = c->f(Y.taps) + ((size_t)l * 2 + 0) * D.d; o.tap_ld = tap_ld;
@@ -878,6 +880,7 @@ int ssd_set_workspace(ssd_ctx* c, void* dev, size_t bytes)
     HIPCHK(hipMemcpyAsync(c->ws + c->lay.rope, tab.data(), tab.size() * sizeof(float), hipMemcpyHostToDevice, c->stream),
            "rope upload");
     HIPCHK(hipMemsetAsync(c->ws + c->lay.small, 0, 4096, c->stream), "state clear");
+    HIPCHK(hipMemsetAsync(c->ws + c->lay.arrive, 0, ATTN_COUNTERS * 4, c->stream), "counter clear");
     HIPCHK(step_device_blocks(c->D, c->device, &c->step_blocks, &c->step_max_rows), "step occupancy");
     c->step_table = false;
     HIPCHK(hipStreamSynchronize(c->stream), "workspace sync");  // tab goes out of scope

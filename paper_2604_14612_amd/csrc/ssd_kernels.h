@@ -222,10 +222,13 @@ hipError_t rope_kv_rows(const Dims& D, float* qkv, const float* rope, const int*
 // hi/lo pair [M][dq] instead.  part: scratch for the split partials.
 hipError_t attention(const Dims& D, const float* q, int ldq, const void* kcache_l, const void* vcache_l,
                      const int* pos_dev, int pos_off, int pos_host_hint, int M, float* part, float* out,
-                     uint16_t* out_hi, uint16_t* out_lo, hipStream_t s, int* deferred_splits = nullptr);
+                     uint16_t* out_hi, uint16_t* out_lo, hipStream_t s, int* deferred_splits = nullptr, unsigned* arrive = nullptr);
 // deferred_splits (single row only): when the positions are split over several blocks the fold is left to
 // the consumer; *deferred_splits = the number of partials per head to pass to gemv_resid_attn, or 0 when
 // out already holds the result.
+// arrive (may be null): ATTN_COUNTERS words that are zero before the first launch and after every one; where the launch has several ranges
+// and its kernel can, the last block of a head folds them and no second launch does.
+constexpr int ATTN_COUNTERS = 1024;
 size_t attention_scratch_floats(const Dims& D, int max_rows);
 // launch shape attention() uses when the last of M rows sees ctx positions: the number of position ranges,
 // negated and joined with their length for the register-resident kernel (two calls with equal values enqueue identical launches)

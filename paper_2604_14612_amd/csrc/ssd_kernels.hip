@@ -2913,6 +2913,56 @@ __device__ __forceinline__ void store_v4(const u32x4_t (&v)[4], unsigned char* d
     }
 }
 
+// Elements dd .. dd + 3 of the output of (row, head) rh from its n_splits partials part[rh][n_splits][HD + 4] (unnormalised output,
+// maximum, sum), eight of them requested together.  DEV: they come from blocks of the same launch and are loaded at device
+// scope (each XCD has its own L2); the partials of all n_rows are less than 2 GiB then.
+template <int HD, bool DEV>
+__device__ __forceinline__ float4 attn_fold(const float* part, int n_rows, int rh, int n_splits, int dd)
+{
+    constexpr int ROW = HD + 4;
+    const float* p = part + (size_t)rh * n_splits * ROW;
+    const auto r = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(part), 0, DEV ? n_rows * n_splits * ROW * 4 : 0, 0x00020000);
+    float gm = -INFINITY, den = 0.f;
+    float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int s0 = 0; s0 < n_splits; s0 += 8) {
+        u32x4_t o[8], ml[8];
+#pragma unroll
+        for (int u = 0; u < 8; u++) {   // (past the last one it is read again and weighs nothing)
+            const int sl = min(s0 + u, n_splits - 1);
+            if (DEV) {
+                const int b = (rh * n_splits + sl) * ROW * 4;
+                ml[u] = __builtin_amdgcn_raw_buffer_load_b128(r, b + HD * 4, 0, 16 /* sc1: device scope */);
+                o[u] = __builtin_amdgcn_raw_buffer_load_b128(r, b + dd * 4, 0, 16);
+            } else {
+                ml[u] = *reinterpret_cast<const u32x4_t*>(p + sl * ROW + HD);
+                o[u] = *reinterpret_cast<const u32x4_t*>(p + sl * ROW + dd);
+            }
+        }
+        float m = gm;
+#pragma unroll
+        for (int u = 0; u < 8; u++) m = fmaxf(m, __uint_as_float(ml[u].x));
+        const float c = gm > -INFINITY ? __expf(gm - m) : 0.f;
+        num.x *= c; num.y *= c; num.z *= c; num.w *= c; den *= c;
+        gm = m;
+#pragma unroll
+        for (int u = 0; u < 8; u++) {
+            const float l = __uint_as_float(ml[u].y), w = s0 + u < n_splits && l > 0.f ? __expf(__uint_as_float(ml[u].x) - m) : 0.f;
+            num.x = fmaf(w, __uint_as_float(o[u].x), num.x); num.y = fmaf(w, __uint_as_float(o[u].y), num.y);
+            num.z = fmaf(w, __uint_as_float(o[u].z), num.z); num.w = fmaf(w, __uint_as_float(o[u].w), num.w);
+            den = fmaf(w, l, den);
+        }
+    }
+    return make_float4(num.x / den, num.y / den, num.z / den, num.w / den);
+}
+__device__ __forceinline__ void attn_put4(float4 o, size_t i, float* out, uint16_t* out_hi, uint16_t* out_lo, bool f16)
+{
+    if (!out_hi) { *reinterpret_cast<float4*>(out + i) = o; return; }
+    uint2 h, l;
+    if (f16) { pair_hi_lo<true>(o.x, o.y, h.x, l.x); pair_hi_lo<true>(o.z, o.w, h.y, l.y); }
+    else { pair_hi_lo<false>(o.x, o.y, h.x, l.x); pair_hi_lo<false>(o.z, o.w, h.y, l.y); }
+    *reinterpret_cast<uint2*>(out_hi + i) = h;
+    *reinterpret_cast<uint2*>(out_lo + i) = l;
+}
 // fp32 caches take the same kernel: while a chunk is staged every K / V element is split into two bf16 planes
 // (hi = rne(x), lo = rne(x - hi), 16 mantissa bits together), and each contraction becomes three MFMAs
 // (hi.hi + lo.hi + hi.lo; the lo.lo term is below the 16 bits the planes carry).
@@ -2923,7 +2973,7 @@ __global__ __launch_bounds__(AM_THREADS) void attn_mfma_kernel(const float* __re
                                                                int max_seq, int n_splits, float* __restrict__ part,
                                                                float* __restrict__ outp, int dq,
                                                                uint16_t* __restrict__ out_hi, uint16_t* __restrict__ out_lo,
-                                                               bool out_f16)
+                                                               bool out_f16, unsigned* arrive)
 {
     constexpr bool F32 = sizeof(KT) == 4;
     constexpr bool F16 = IsF16<KT>::value;     // operand type of the MFMAs: fp16 for fp16 caches, else bf16
@@ -2988,6 +3038,32 @@ __global__ __launch_bounds__(AM_THREADS) void attn_mfma_kernel(const float* __re
     const int p0 = pos_dev[0] + pos_off;
     const int total = p0 + M;
     const int n = min(AT_CHUNK, total - j0);                   // may be <= 0
+    // The block of a (KV head, group of queries) that arrives last folds the partials of all of them; nobody waits.  A block counts
+    // itself in when its stores, made at device scope, are acknowledged; the last one sets the counter back to zero for the next launch.
+    // This launch and the one that folded, before / this launch now: 7B, 5 rows behind 550 positions 8.8 + 5.4 / 10.8 us, 9 rows behind
+    // 100 of an fp16 cache 5.9 + 4.7 / 8.7.  (Fences in place of device-scope accesses write whole L2s back and cost more than the launch.)
+    __shared__ int last;
+    const auto prsrc = __builtin_amdgcn_make_buffer_rsrc(part, 0, arrive ? M * H * n_splits * (HD + 4) * 4 : 0, 0x00020000);
+    auto put_partial = [&](float* to, float4 v) {
+        if (arrive) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v), prsrc, (int)(to - part) * 4, 0, 16 /* sc1: device scope */);
+        else *reinterpret_cast<float4*>(to) = v;
+    };
+    auto fold = [&]() {
+        if (!arrive) return;
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        if (tid == 0) {
+            unsigned* c = arrive + blockIdx.y * gridDim.z + blockIdx.z;
+            last = __hip_atomic_fetch_add(c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+            if (last) __hip_atomic_store(c, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __syncthreads();
+        if (!last) return;
+        for (int f = tid; f < nq * (HD / 4); f += AM_THREADS) {
+            const int qg = q0 + f / (HD / 4), dd = f % (HD / 4) * 4, rh = qg / G * H + kvh * G + qg % G;
+            attn_put4(attn_fold<HD, true>(part, M * H, rh, n_splits, dd), (size_t)rh * HD + dd, outp, out_hi, out_lo, out_f16);
+        }
+    };
     // A chunk that lies wholly behind the causal horizon of the block's LAST query row contributes nothing (in a
     // prompt pass that is half of all blocks): leave empty partials and go.  Uniform over the block.
     if (n_splits > 1 && (n <= 0 || j0 > p0 + (q0 + nq - 1) / G)) {
@@ -2995,9 +3071,10 @@ __global__ __launch_bounds__(AM_THREADS) void attn_mfma_kernel(const float* __re
             const int qi = f / (HD / 4), dd = (f % (HD / 4)) * 4;
             const int qg = q0 + qi, r = qg / G, head = kvh * G + qg % G;
             float* mine = part + (((size_t)r * H + head) * n_splits + split) * (HD + 4);
-            *reinterpret_cast<float4*>(mine + dd) = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (dd == 0) { mine[HD] = -INFINITY; mine[HD + 1] = 0.f; }
+            put_partial(mine + dd, make_float4(0.f, 0.f, 0.f, 0.f));
+            if (dd == 0) put_partial(mine + HD, make_float4(-INFINITY, 0.f, 0.f, 0.f));
         }
+        fold();
         return;
     }
     if (n > 0) {  // stage K (row-major) and V (transposed)
@@ -3128,11 +3205,12 @@ __global__ __launch_bounds__(AM_THREADS) void attn_mfma_kernel(const float* __re
                 }
             } else {
                 float* mine = part + (((size_t)r * H + head) * n_splits + split) * (HD + 4);
-                *reinterpret_cast<float4*>(mine + dd) = o;
-                if (dd == 0) { mine[HD] = n > 0 ? mx : -INFINITY; mine[HD + 1] = n > 0 ? ls : 0.f; }
+                put_partial(mine + dd, o);
+                if (dd == 0) put_partial(mine + HD, make_float4(n > 0 ? mx : -INFINITY, n > 0 ? ls : 0.f, 0.f, 0.f));
             }
         }
     }
+    if (n_splits > 1) fold();
 }
 
 // ---- prompt passes: one block per KV head and 64 query vectors walks the whole causal range -----------------
@@ -3398,30 +3476,15 @@ static size_t attn_lds_bytes()
            (size_t)AT_QPASS * 2 * 4 + (size_t)AT_THREADS * AT_QPASS * 4;
 }
 
-// Folds the split partials of one (row, head) into the attention output.  (Folding inside the
-// attention kernel by the last-arriving block needs device-scope fences, which on this
-// multi-XCD part cost far more than this extra launch.)
+// Folds the split partials of one (row, head) into the attention output, where the attention launch does not do so itself.
 template <int HD>
-__global__ void attn_combine_kernel(const float* __restrict__ part, int H, int n_splits, float* __restrict__ out, int dq,
-                                    uint16_t* __restrict__ out_hi, uint16_t* __restrict__ out_lo, bool f16)
+__global__ __launch_bounds__(256) void attn_combine_kernel(const float* __restrict__ part, int n_rows, int n_splits, float* __restrict__ out,
+                                                           uint16_t* __restrict__ out_hi, uint16_t* __restrict__ out_lo, bool f16)
 {
-    const int head = blockIdx.x, r = blockIdx.y, d = threadIdx.x;
-    const float* p = part + ((size_t)r * H + head) * n_splits * (HD + 4);
-    float gm = -INFINITY;
-    for (int s = 0; s < n_splits; s++) gm = fmaxf(gm, p[(size_t)s * (HD + 4) + HD]);
-    float num = 0.f, den = 0.f;
-    for (int s = 0; s < n_splits; s++) {
-        const float* ps = p + (size_t)s * (HD + 4);
-        const float l = ps[HD + 1];
-        if (l > 0.f) {
-            const float w = __expf(ps[HD] - gm);
-            num = fmaf(w, ps[d], num);
-            den = fmaf(w, l, den);
-        }
-    }
-    const size_t o = (size_t)r * dq + (size_t)head * HD + d;
-    if (out_hi) split_store(num / den, out_hi, out_lo, o, f16);
-    else out[o] = num / den;
+    const int i = blockIdx.x * 256 + threadIdx.x, rh = i / (HD / 4), dd = i % (HD / 4) * 4;   // rh: (row, head)
+    if (rh >= n_rows) return;
+    const float4 o = attn_fold<HD, false>(part, n_rows, rh, n_splits, dd);
+    attn_put4(o, (size_t)rh * HD + dd, out, out_hi, out_lo, f16);
 }
 
 // ---- register-resident variant for few query vectors (decoding, short verification blocks) ----------
@@ -3683,7 +3746,7 @@ static void launch_attn_wide(const Dims& D, const float* q, int ldq, const void*
 template <typename KT, int HD>
 static void launch_attn_staged(const Dims& D, const float* q, int ldq, const void* kc, const void* vc, const int* pos_dev,
                                int pos_off, int n_splits, int M, float* part, float* out, uint16_t* out_hi, uint16_t* out_lo,
-                               hipStream_t s)
+                               unsigned* arrive, hipStream_t s)
 {
     {
         // MFMA form: 16-bit caches always; fp32 caches when the model's weights are 16-bit (its hi/lo planes carry 16
@@ -3696,7 +3759,7 @@ static void launch_attn_staged(const Dims& D, const float* q, int ldq, const voi
             const int Q = (D.H / D.Hkv) * M;
             hipLaunchKernelGGL((attn_mfma_kernel<KT, HD>), dim3(n_splits, D.Hkv, ceil_div(Q, AT_QPASS)), dim3(AM_THREADS), lds, s, q, ldq,
                                (const KT*)kc, (const KT*)vc, pos_dev, pos_off, M, D.H, D.Hkv, D.max_seq, n_splits, part, out, D.dq,
-                               out_hi, out_lo, D.wt == WT_F16);
+                               out_hi, out_lo, D.wt == WT_F16, arrive);
             return;
         }
     }
@@ -3712,9 +3775,14 @@ static void launch_attn_staged(const Dims& D, const float* q, int ldq, const voi
 template <typename KT, int HD>
 static hipError_t attention_t(const Dims& D, const float* q, int ldq, const void* kc, const void* vc, const int* pos_dev,
                               int pos_off, AttnPlan pl, int ctx, int M, float* part, float* out, uint16_t* out_hi,
-                              uint16_t* out_lo, hipStream_t s)
+                              uint16_t* out_lo, unsigned* arrive, hipStream_t s)
 {
     const int n_splits = pl.n_splits;
+    // the matrix-core kernel folds its partials itself where their sum goes to no other launch, a counter per group of blocks
+    const bool mfma = !pl.wide && !(D.opt && D.opt->attn_kernel == 3) && (sizeof(KT) == 2 || D.wt != WT_F32);
+    if (!mfma || n_splits == 1 || pl.defer_fold || D.Hkv * ceil_div((D.H / D.Hkv) * M, AT_QPASS) > ATTN_COUNTERS ||
+        (size_t)M * D.H * n_splits * (HD + 4) * 4 >= (size_t)1 << 31)
+        arrive = nullptr;
     if (n_splits < 1 || (n_splits > 64 && n_splits > ceil_div(D.max_seq, AT_CHUNK))) return hipErrorInvalidValue;
     // prompt passes (more than 16 rows) of models with 16-bit weights: one kernel over the whole causal range, where
     // it has blocks for a quarter of the CUs at least or the range is short (a block walks the range chunk by chunk:
@@ -3745,18 +3813,18 @@ static hipError_t attention_t(const Dims& D, const float* q, int ldq, const void
         else if (span <= 8 * 64 * 4) launch_attn_wide<KT, HD, 4, 8, 4>(D, q, ldq, kc, vc, pos_dev, pos_off, n_splits, pl.chunk, zq, M, part, out, out_hi, out_lo, s);
         else launch_attn_wide<KT, HD, 4, 8, 8>(D, q, ldq, kc, vc, pos_dev, pos_off, n_splits, pl.chunk, zq, M, part, out, out_hi, out_lo, s);
     } else {
-        launch_attn_staged<KT, HD>(D, q, ldq, kc, vc, pos_dev, pos_off, n_splits, M, part, out, out_hi, out_lo, s);
+        launch_attn_staged<KT, HD>(D, q, ldq, kc, vc, pos_dev, pos_off, n_splits, M, part, out, out_hi, out_lo, arrive, s);
     }
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess || n_splits == 1 || pl.defer_fold) return e;
-    hipLaunchKernelGGL((attn_combine_kernel<HD>), dim3(D.H, M), dim3(HD), 0, s, part, D.H, n_splits, out, D.dq, out_hi,
+    if (e != hipSuccess || n_splits == 1 || pl.defer_fold || arrive) return e;
+    hipLaunchKernelGGL((attn_combine_kernel<HD>), dim3(ceil_div(M * D.H * (HD / 4), 256)), dim3(256), 0, s, part, M * D.H, n_splits, out, out_hi,
                        out_lo, D.wt == WT_F16);
     return hipGetLastError();
 }
 
 hipError_t attention(const Dims& D, const float* q, int ldq, const void* kc, const void* vc, const int* pos_dev,
                      int pos_off, int pos_host_hint, int M, float* part, float* out, uint16_t* out_hi, uint16_t* out_lo,
-                     hipStream_t s, int* deferred_splits)
+                     hipStream_t s, int* deferred_splits, unsigned* arrive)
 {
     int ctx = pos_host_hint + pos_off + M;  // positions the last row sees
     if (ctx < 1 || ctx > D.max_seq || M < 1) return hipErrorInvalidValue;
@@ -3767,14 +3835,14 @@ hipError_t attention(const Dims& D, const float* q, int ldq, const void* kc, con
         *deferred_splits = pl.defer_fold ? pl.n_splits : 0;
     }
     if (D.kt == WT_BF16) {
-        if (D.hd == 128) return attention_t<uint16_t, 128>(D, q, ldq, kc, vc, pos_dev, pos_off, pl, ctx, M, part, out, out_hi, out_lo, s);
-        if (D.hd == 64) return attention_t<uint16_t, 64>(D, q, ldq, kc, vc, pos_dev, pos_off, pl, ctx, M, part, out, out_hi, out_lo, s);
+        if (D.hd == 128) return attention_t<uint16_t, 128>(D, q, ldq, kc, vc, pos_dev, pos_off, pl, ctx, M, part, out, out_hi, out_lo, arrive, s);
+        if (D.hd == 64) return attention_t<uint16_t, 64>(D, q, ldq, kc, vc, pos_dev, pos_off, pl, ctx, M, part, out, out_hi, out_lo, arrive, s);
     } else if (D.kt == WT_F16) {
-        if (D.hd == 128) return attention_t<f16_t, 128>(D, q, ldq, kc, vc, pos_dev, pos_off, pl, ctx, M, part, out, out_hi, out_lo, s);
-        if (D.hd == 64) return attention_t<f16_t, 64>(D, q, ldq, kc, vc, pos_dev, pos_off, pl, ctx, M, part, out, out_hi, out_lo, s);
+        if (D.hd == 128) return attention_t<f16_t, 128>(D, q, ldq, kc, vc, pos_dev, pos_off, pl, ctx, M, part, out, out_hi, out_lo, arrive, s);
+        if (D.hd == 64) return attention_t<f16_t, 64>(D, q, ldq, kc, vc, pos_dev, pos_off, pl, ctx, M, part, out, out_hi, out_lo, arrive, s);
     } else {
-        if (D.hd == 128) return attention_t<float, 128>(D, q, ldq, kc, vc, pos_dev, pos_off, pl, ctx, M, part, out, out_hi, out_lo, s);
-        if (D.hd == 64) return attention_t<float, 64>(D, q, ldq, kc, vc, pos_dev, pos_off, pl, ctx, M, part, out, out_hi, out_lo, s);
+        if (D.hd == 128) return attention_t<float, 128>(D, q, ldq, kc, vc, pos_dev, pos_off, pl, ctx, M, part, out, out_hi, out_lo, arrive, s);
+        if (D.hd == 64) return attention_t<float, 64>(D, q, ldq, kc, vc, pos_dev, pos_off, pl, ctx, M, part, out, out_hi, out_lo, arrive, s);
     }
     return hipErrorInvalidValue;
 }

@@ -212,3 +212,15 @@ def test_attention_of_a_verification(heads, kv_heads, kv, plen):
     st = lockstep_ssd(ctx, orc, prompt, 0, [4, 7], np.array([0, 1], np.uint8), shape.dtype)
     assert st["unpinned_cycles"] <= 1
     assert ctx.ssd_get_one_launch() == (0, 0, 0)
+
+
+# Folds of many attention partials: two ranges, the eight that are requested together, nine and more, with rows whose first ranges are all
+# there is (the last ranges of a chunked context are empty for earlier rows), in one launch and -- replayed -- one after the other
+@pytest.mark.parametrize("kv", ["fp32", "bf16"])
+@pytest.mark.parametrize("plen", [95, 190, 760, 772, 1250])
+def test_partials_folded_by_the_last_block(kv, plen):
+    shape = ModelShape(2, 1280, 10, 5, 192, 528)
+    orc, ctx = make_pair(shape, 19, plen + 40, max_k=7, norm_gain_std=0.1, kv_dtype=kv)
+    prompt = make_prompt(shape.vocab, plen, 7).tolist()
+    st = lockstep_ssd(ctx, orc, prompt, 0, [7, 7, 7, 2], np.array([0, 1], np.uint8), shape.dtype)
+    assert st["unpinned_cycles"] <= 2
