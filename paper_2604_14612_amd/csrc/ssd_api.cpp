@@ -277,7 +277,7 @@ int layer_single(ssd_ctx* c, int l, int pos_off, int plan_ctx, bool do_attn, boo
                                    pos_off, c->f(c->lay.qkv), c->kcache(l), c->vcache(l), c->stream), "gemv_qkv");
     int fold = 0;  // > 0: attention left that many partials per head for the output projection to fold
     TIMED(SSD_K_ATTENTION, attention(D, c->f(c->lay.qkv), D.dq, c->kcache(l), c->vcache(l), c->pos_dev(), pos_off,
-                                     plan_ctx - 1 - pos_off, 1, c->f(c->lay.part), c->f(c->lay.att), nullptr, nullptr, c->stream, &fold),
+                                     plan_ctx - 1 - pos_off, 1, c->f(c->lay.part), c->f(c->lay.att), nullptr, nullptr, c->stream, &fold, c->arrive()),
           "attention");
     if (fold > 0) {
         TIMED(SSD_K_GEMV_O, gemv_resid_attn(D, c->wo[l], c->f(c->lay.part), fold, x, nullptr, c->stream), "gemv_o");

@@ -231,8 +231,9 @@ hipError_t attention(const Dims& D, const float* q, int ldq, const void* kcache_
 constexpr int ATTN_COUNTERS = 1024;
 size_t attention_scratch_floats(const Dims& D, int max_rows);
 // launch shape attention() uses when the last of M rows sees ctx positions: the number of position ranges,
-// negated and joined with their length for the register-resident kernel (two calls with equal values enqueue identical launches)
-int attention_splits(const Dims& D, int ctx, int M);
+// negated and joined with their length, without and with arrive, for the register-resident kernel (two calls with equal values enqueue
+// identical launches)
+long attention_splits(const Dims& D, int ctx, int M);
 int attention_ranges(const Dims& D, int ctx, int M);   // the number of position ranges itself
 
 // ---- vocabulary reduction ------------------------------------------------------------------------

@@ -2913,22 +2913,30 @@ __device__ __forceinline__ void store_v4(const u32x4_t (&v)[4], unsigned char* d
     }
 }
 
-// Elements dd .. dd + 3 of the output of (row, head) rh from its n_splits partials part[rh][n_splits][HD + 4] (unnormalised output,
-// maximum, sum), eight of them requested together.  DEV: they come from blocks of the same launch and are loaded at device
-// scope (each XCD has its own L2); the partials of all n_rows are less than 2 GiB then.
+// Elements dd .. dd + 3 of the output of (row, head) rh, folded from partials part[rh][n_splits][HD + 4] (unnormalised output, maximum,
+// sum), eight of them requested together.  DEV: they come from blocks of the same launch and are loaded at device scope (each XCD
+// has its own L2); the partials of all n_rows are less than 2 GiB then.
+struct AttnAcc { float4 num; float m, den; };   // output relative to maximum m
+__device__ __forceinline__ void attn_acc_add(AttnAcc& a, const AttnAcc& b)
+{
+    const float m = fmaxf(a.m, b.m), ca = a.m > -INFINITY ? __expf(a.m - m) : 0.f, cb = b.m > -INFINITY ? __expf(b.m - m) : 0.f;
+    a.num = make_float4(a.num.x * ca + b.num.x * cb, a.num.y * ca + b.num.y * cb, a.num.z * ca + b.num.z * cb, a.num.w * ca + b.num.w * cb);
+    a.den = a.den * ca + b.den * cb;
+    a.m = m;
+}
+__device__ __forceinline__ float4 attn_acc_out(const AttnAcc& a) { return make_float4(a.num.x / a.den, a.num.y / a.den, a.num.z / a.den, a.num.w / a.den); }
 template <int HD, bool DEV>
-__device__ __forceinline__ float4 attn_fold(const float* part, int n_rows, int rh, int n_splits, int dd)
+__device__ __forceinline__ AttnAcc attn_fold(const float* part, int n_rows, int rh, int n_splits, int first, int end, int dd)   // ranges first .. end - 1
 {
     constexpr int ROW = HD + 4;
     const float* p = part + (size_t)rh * n_splits * ROW;
     const auto r = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(part), 0, DEV ? n_rows * n_splits * ROW * 4 : 0, 0x00020000);
-    float gm = -INFINITY, den = 0.f;
-    float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int s0 = 0; s0 < n_splits; s0 += 8) {
+    AttnAcc a = {make_float4(0.f, 0.f, 0.f, 0.f), -INFINITY, 0.f};
+    for (int s0 = first; s0 < end; s0 += 8) {
         u32x4_t o[8], ml[8];
 #pragma unroll
         for (int u = 0; u < 8; u++) {   // (past the last one it is read again and weighs nothing)
-            const int sl = min(s0 + u, n_splits - 1);
+            const int sl = min(s0 + u, end - 1);
             if (DEV) {
                 const int b = (rh * n_splits + sl) * ROW * 4;
                 ml[u] = __builtin_amdgcn_raw_buffer_load_b128(r, b + HD * 4, 0, 16 /* sc1: device scope */);
@@ -2938,21 +2946,19 @@ __device__ __forceinline__ float4 attn_fold(const float* part, int n_rows, int r
                 o[u] = *reinterpret_cast<const u32x4_t*>(p + sl * ROW + dd);
             }
         }
-        float m = gm;
+        AttnAcc b = {make_float4(0.f, 0.f, 0.f, 0.f), -INFINITY, 0.f};
 #pragma unroll
-        for (int u = 0; u < 8; u++) m = fmaxf(m, __uint_as_float(ml[u].x));
-        const float c = gm > -INFINITY ? __expf(gm - m) : 0.f;
-        num.x *= c; num.y *= c; num.z *= c; num.w *= c; den *= c;
-        gm = m;
+        for (int u = 0; u < 8; u++) b.m = fmaxf(b.m, __uint_as_float(ml[u].x));
 #pragma unroll
         for (int u = 0; u < 8; u++) {
-            const float l = __uint_as_float(ml[u].y), w = s0 + u < n_splits && l > 0.f ? __expf(__uint_as_float(ml[u].x) - m) : 0.f;
-            num.x = fmaf(w, __uint_as_float(o[u].x), num.x); num.y = fmaf(w, __uint_as_float(o[u].y), num.y);
-            num.z = fmaf(w, __uint_as_float(o[u].z), num.z); num.w = fmaf(w, __uint_as_float(o[u].w), num.w);
-            den = fmaf(w, l, den);
+            const float l = __uint_as_float(ml[u].y), w = s0 + u < end && l > 0.f ? __expf(__uint_as_float(ml[u].x) - b.m) : 0.f;
+            b.num.x = fmaf(w, __uint_as_float(o[u].x), b.num.x); b.num.y = fmaf(w, __uint_as_float(o[u].y), b.num.y);
+            b.num.z = fmaf(w, __uint_as_float(o[u].z), b.num.z); b.num.w = fmaf(w, __uint_as_float(o[u].w), b.num.w);
+            b.den = fmaf(w, l, b.den);
         }
+        attn_acc_add(a, b);
     }
-    return make_float4(num.x / den, num.y / den, num.z / den, num.w / den);
+    return a;
 }
 __device__ __forceinline__ void attn_put4(float4 o, size_t i, float* out, uint16_t* out_hi, uint16_t* out_lo, bool f16)
 {
@@ -2963,6 +2969,54 @@ __device__ __forceinline__ void attn_put4(float4 o, size_t i, float* out, uint16
     *reinterpret_cast<uint2*>(out_hi + i) = h;
     *reinterpret_cast<uint2*>(out_lo + i) = l;
 }
+// The block of a (KV head, group of queries) = (blockIdx.y, blockIdx.z) that arrives last folds the partials of all ranges; nobody
+// waits.  A block counts itself in when its stores, made at device scope, are acknowledged; the last one sets the counter back to
+// zero for the next launch.  Called by the whole block.  Attention and the launch that folded, before / attention now: 7B, 5 rows behind
+// 550 positions 8.8 + 5.4 / 10.8 us, 9 rows behind 100 of an fp16 cache 5.9 + 4.7 / 8.7.  (Fences in place of device-scope
+// accesses write whole L2s back and cost more than the launch.)
+__device__ __forceinline__ bool attn_last(unsigned* arrive)
+{
+    __shared__ int last;
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned* c = arrive + blockIdx.y * gridDim.z + blockIdx.z;
+        last = __hip_atomic_fetch_add(c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+        if (last) __hip_atomic_store(c, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    return last;
+}
+
+// The fold for query vectors q0 .. q0 + nq - 1 (vector qg: row qg / G, head kvh G + qg % G), by the last block.  Threads that the outputs
+// leave over share the ranges, eight and more each, and meet in LDS.
+template <int HD, int NT>
+__device__ __forceinline__ void attn_fold_block(const float* part, int M, int H, int G, int kvh, int q0, int nq, int n_splits, float* outp, uint16_t* out_hi,
+                                                uint16_t* out_lo, bool out_f16)
+{
+    __shared__ AttnAcc acc[NT];
+    const int items = nq * (HD / 4), tid = threadIdx.x;
+    int shares = 1;
+    while (shares * 2 * items <= NT && shares * 16 <= n_splits + 8) shares *= 2;
+    const int per = (n_splits + shares - 1) / shares;
+    auto row = [&](int f) { const int qg = q0 + f / (HD / 4); return qg / G * H + kvh * G + qg % G; };
+    if (shares == 1) {
+        for (int f = tid; f < items; f += NT) {
+            const int rh = row(f), dd = f % (HD / 4) * 4;
+            attn_put4(attn_acc_out(attn_fold<HD, true>(part, M * H, rh, n_splits, 0, n_splits, dd)), (size_t)rh * HD + dd, outp, out_hi, out_lo, out_f16);
+        }
+        return;
+    }
+    const int f = tid % items, sh = tid / items, rh = row(f), dd = f % (HD / 4) * 4;
+    if (sh < shares) acc[tid] = attn_fold<HD, true>(part, M * H, rh, n_splits, min(sh * per, n_splits), min(sh * per + per, n_splits), dd);
+    __syncthreads();
+    if (sh == 0) {
+        AttnAcc a = acc[f];
+        for (int u = 1; u < shares; u++) attn_acc_add(a, acc[u * items + f]);
+        attn_put4(attn_acc_out(a), (size_t)rh * HD + dd, outp, out_hi, out_lo, out_f16);
+    }
+}
+
 // fp32 caches take the same kernel: while a chunk is staged every K / V element is split into two bf16 planes
 // (hi = rne(x), lo = rne(x - hi), 16 mantissa bits together), and each contraction becomes three MFMAs
 // (hi.hi + lo.hi + hi.lo; the lo.lo term is below the 16 bits the planes carry).
@@ -3038,31 +3092,13 @@ __global__ __launch_bounds__(AM_THREADS) void attn_mfma_kernel(const float* __re
     const int p0 = pos_dev[0] + pos_off;
     const int total = p0 + M;
     const int n = min(AT_CHUNK, total - j0);                   // may be <= 0
-    // The block of a (KV head, group of queries) that arrives last folds the partials of all of them; nobody waits.  A block counts
-    // itself in when its stores, made at device scope, are acknowledged; the last one sets the counter back to zero for the next launch.
-    // This launch and the one that folded, before / this launch now: 7B, 5 rows behind 550 positions 8.8 + 5.4 / 10.8 us, 9 rows behind
-    // 100 of an fp16 cache 5.9 + 4.7 / 8.7.  (Fences in place of device-scope accesses write whole L2s back and cost more than the launch.)
-    __shared__ int last;
     const auto prsrc = __builtin_amdgcn_make_buffer_rsrc(part, 0, arrive ? M * H * n_splits * (HD + 4) * 4 : 0, 0x00020000);
     auto put_partial = [&](float* to, float4 v) {
         if (arrive) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v), prsrc, (int)(to - part) * 4, 0, 16 /* sc1: device scope */);
         else *reinterpret_cast<float4*>(to) = v;
     };
     auto fold = [&]() {
-        if (!arrive) return;
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        if (tid == 0) {
-            unsigned* c = arrive + blockIdx.y * gridDim.z + blockIdx.z;
-            last = __hip_atomic_fetch_add(c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
-            if (last) __hip_atomic_store(c, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        __syncthreads();
-        if (!last) return;
-        for (int f = tid; f < nq * (HD / 4); f += AM_THREADS) {
-            const int qg = q0 + f / (HD / 4), dd = f % (HD / 4) * 4, rh = qg / G * H + kvh * G + qg % G;
-            attn_put4(attn_fold<HD, true>(part, M * H, rh, n_splits, dd), (size_t)rh * HD + dd, outp, out_hi, out_lo, out_f16);
-        }
+        if (arrive && attn_last(arrive)) attn_fold_block<HD, AM_THREADS>(part, M, H, G, kvh, q0, nq, n_splits, outp, out_hi, out_lo, out_f16);
     };
     // A chunk that lies wholly behind the causal horizon of the block's LAST query row contributes nothing (in a
     // prompt pass that is half of all blocks): leave empty partials and go.  Uniform over the block.
@@ -3483,8 +3519,7 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float* __restri
 {
     const int i = blockIdx.x * 256 + threadIdx.x, rh = i / (HD / 4), dd = i % (HD / 4) * 4;   // rh: (row, head)
     if (rh >= n_rows) return;
-    const float4 o = attn_fold<HD, false>(part, n_rows, rh, n_splits, dd);
-    attn_put4(o, (size_t)rh * HD + dd, out, out_hi, out_lo, f16);
+    attn_put4(attn_acc_out(attn_fold<HD, false>(part, n_rows, rh, n_splits, 0, n_splits, dd)), (size_t)rh * HD + dd, out, out_hi, out_lo, f16);
 }
 
 // ---- register-resident variant for few query vectors (decoding, short verification blocks) ----------
@@ -3554,7 +3589,7 @@ __global__ __launch_bounds__(NW * 64) void attn_wide_kernel(const float* __restr
                                                             int max_seq, int n_splits, int chunk, float* __restrict__ part,
                                                             float* __restrict__ outp, int dq,
                                                             uint16_t* __restrict__ out_hi, uint16_t* __restrict__ out_lo,
-                                                            bool out_f16)
+                                                            bool out_f16, unsigned* arrive)
 {
     constexpr int EPV = 16 / (int)sizeof(KT), LPP = HD / EPV, PPL = 64 / LPP, NT = NW * 64;
     constexpr int PASS = NL * NW * PPL;  // positions one pass of the block covers
@@ -3683,6 +3718,7 @@ __global__ __launch_bounds__(NW * 64) void attn_wide_kernel(const float* __restr
         if (lane == 0) { wml[(wave * NQ + qi) * 2] = m[qi]; wml[(wave * NQ + qi) * 2 + 1] = l[qi]; }
     }
     __syncthreads();
+    const auto prsrc = __builtin_amdgcn_make_buffer_rsrc(part, 0, arrive ? M * H * n_splits * (HD + 4) * 4 : 0, 0x00020000);
     for (int e = tid; e < nq * HD; e += NT) {
         const int qi = e / HD, d = e % HD;
         float gm = -INFINITY;
@@ -3705,22 +3741,33 @@ __global__ __launch_bounds__(NW * 64) void attn_wide_kernel(const float* __restr
             else outp[oo] = num / den;
         } else {
             float* mine = part + (((size_t)r * H + head) * n_splits + split) * (HD + 4);
-            mine[d] = num;
-            if (d == 0) { mine[HD] = gm; mine[HD + 1] = den; }
+            if (arrive) {   // at device scope: see the fold below
+                const int o = (int)(mine - part) * 4;
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(num), prsrc, o + d * 4, 0, 16);
+                if (d < 2) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(d == 0 ? gm : den), prsrc, o + (HD + d) * 4, 0, 16);
+            } else {
+                mine[d] = num;
+                if (d == 0) { mine[HD] = gm; mine[HD + 1] = den; }
+            }
         }
     }
+    if (arrive && n_splits > 1 && attn_last(arrive)) attn_fold_block<HD, NT>(part, M, H, G, kvh, q0, nq, n_splits, outp, out_hi, out_lo, out_f16);
 }
 
-static AttnPlan attn_plan(const Dims& D, int ctx, int M)
+// folds: the launch can fold its partials itself
+static AttnPlan attn_plan(const Dims& D, int ctx, int M, bool folds = false)
 {
     const AttnShape a = {D.H / D.Hkv, D.Hkv, D.hd, D.kt == WT_F32, D.wt == WT_F32};
-    return attn_plan(a, ctx, M, D.opt ? D.opt->attn_splits : 0, D.opt ? D.opt->attn_kernel : 0);
+    const int splits = D.opt ? D.opt->attn_splits : 0, kernel = D.opt ? D.opt->attn_kernel : 0;
+    return folds && M == 1 && D.H <= ATTN_COUNTERS ? attn_plan_many(a, ctx, splits, kernel) : attn_plan(a, ctx, M, splits, kernel);
 }
 
-int attention_splits(const Dims& D, int ctx, int M)
+long attention_splits(const Dims& D, int ctx, int M)
 {
     const AttnPlan pl = attn_plan(D, ctx, M);
-    return pl.wide ? -(pl.n_splits + 64 * pl.chunk) : pl.n_splits;  // distinct values for distinct launch shapes
+    if (!pl.wide) return pl.n_splits;
+    const AttnPlan many = attn_plan(D, ctx, M, true);
+    return -((long)pl.n_splits + 64 * (long)pl.chunk + ((long)many.n_splits + 128 * (long)many.chunk) * (1l << 32));  // distinct values for distinct launch shapes
 }
 
 int attention_ranges(const Dims& D, int ctx, int M) { return attn_plan(D, ctx, M).n_splits; }
@@ -3735,11 +3782,11 @@ size_t attention_scratch_floats(const Dims& D, int max_rows)
 template <typename KT, int HD, int NQ, int NW, int NL>
 static void launch_attn_wide(const Dims& D, const float* q, int ldq, const void* kc, const void* vc, const int* pos_dev,
                              int pos_off, int n_splits, int chunk, int zq, int M, float* part, float* out, uint16_t* out_hi,
-                             uint16_t* out_lo, hipStream_t s)
+                             uint16_t* out_lo, unsigned* arrive, hipStream_t s)
 {
     hipLaunchKernelGGL((attn_wide_kernel<KT, HD, NQ, NW, NL>), dim3(n_splits, D.Hkv, zq), dim3(NW * 64), 0, s, q, ldq,
                        (const KT*)kc, (const KT*)vc, pos_dev, pos_off, M, D.H, D.Hkv, D.max_seq, n_splits, chunk, part, out, D.dq,
-                       out_hi, out_lo, D.wt == WT_F16);
+                       out_hi, out_lo, D.wt == WT_F16, arrive);
 }
 
 // LDS-staged kernel: MFMA form for 16-bit caches, plain form for fp32 caches
@@ -3778,9 +3825,9 @@ static hipError_t attention_t(const Dims& D, const float* q, int ldq, const void
                               uint16_t* out_lo, unsigned* arrive, hipStream_t s)
 {
     const int n_splits = pl.n_splits;
-    // the matrix-core kernel folds its partials itself where their sum goes to no other launch, a counter per group of blocks
+    // the matrix-core and the register-resident kernel fold their partials themselves unless another launch does, a counter per group of blocks
     const bool mfma = !pl.wide && !(D.opt && D.opt->attn_kernel == 3) && (sizeof(KT) == 2 || D.wt != WT_F32);
-    if (!mfma || n_splits == 1 || pl.defer_fold || D.Hkv * ceil_div((D.H / D.Hkv) * M, AT_QPASS) > ATTN_COUNTERS ||
+    if (!(mfma || pl.wide) || n_splits == 1 || pl.defer_fold || D.H * M > ATTN_COUNTERS ||
         (size_t)M * D.H * n_splits * (HD + 4) * 4 >= (size_t)1 << 31)
         arrive = nullptr;
     if (n_splits < 1 || (n_splits > 64 && n_splits > ceil_div(D.max_seq, AT_CHUNK))) return hipErrorInvalidValue;
@@ -3806,12 +3853,12 @@ static hipError_t attention_t(const Dims& D, const float* q, int ldq, const void
             zq = M * (G / Q);
         }
         const int span = pl.chunk * (HD / (16 / (int)sizeof(KT)));  // lanes' worth of 16-byte vectors per range
-        if (Q == 1 && span <= 8 * 64 * 4) launch_attn_wide<KT, HD, 1, 8, 4>(D, q, ldq, kc, vc, pos_dev, pos_off, n_splits, pl.chunk, zq, M, part, out, out_hi, out_lo, s);
-        else if (Q == 1 && span <= 16 * 64 * 4) launch_attn_wide<KT, HD, 1, 16, 4>(D, q, ldq, kc, vc, pos_dev, pos_off, n_splits, pl.chunk, zq, M, part, out, out_hi, out_lo, s);
-        else if (Q == 1) launch_attn_wide<KT, HD, 1, 8, 16>(D, q, ldq, kc, vc, pos_dev, pos_off, n_splits, pl.chunk, zq, M, part, out, out_hi, out_lo, s);
-        else if (Q == 2) launch_attn_wide<KT, HD, 2, 16, 4>(D, q, ldq, kc, vc, pos_dev, pos_off, n_splits, pl.chunk, zq, M, part, out, out_hi, out_lo, s);
-        else if (span <= 8 * 64 * 4) launch_attn_wide<KT, HD, 4, 8, 4>(D, q, ldq, kc, vc, pos_dev, pos_off, n_splits, pl.chunk, zq, M, part, out, out_hi, out_lo, s);
-        else launch_attn_wide<KT, HD, 4, 8, 8>(D, q, ldq, kc, vc, pos_dev, pos_off, n_splits, pl.chunk, zq, M, part, out, out_hi, out_lo, s);
+        if (Q == 1 && span <= 8 * 64 * 4) launch_attn_wide<KT, HD, 1, 8, 4>(D, q, ldq, kc, vc, pos_dev, pos_off, n_splits, pl.chunk, zq, M, part, out, out_hi, out_lo, arrive, s);
+        else if (Q == 1 && span <= 16 * 64 * 4) launch_attn_wide<KT, HD, 1, 16, 4>(D, q, ldq, kc, vc, pos_dev, pos_off, n_splits, pl.chunk, zq, M, part, out, out_hi, out_lo, arrive, s);
+        else if (Q == 1) launch_attn_wide<KT, HD, 1, 8, 16>(D, q, ldq, kc, vc, pos_dev, pos_off, n_splits, pl.chunk, zq, M, part, out, out_hi, out_lo, arrive, s);
+        else if (Q == 2) launch_attn_wide<KT, HD, 2, 16, 4>(D, q, ldq, kc, vc, pos_dev, pos_off, n_splits, pl.chunk, zq, M, part, out, out_hi, out_lo, arrive, s);
+        else if (span <= 8 * 64 * 4) launch_attn_wide<KT, HD, 4, 8, 4>(D, q, ldq, kc, vc, pos_dev, pos_off, n_splits, pl.chunk, zq, M, part, out, out_hi, out_lo, arrive, s);
+        else launch_attn_wide<KT, HD, 4, 8, 8>(D, q, ldq, kc, vc, pos_dev, pos_off, n_splits, pl.chunk, zq, M, part, out, out_hi, out_lo, arrive, s);
     } else {
         launch_attn_staged<KT, HD>(D, q, ldq, kc, vc, pos_dev, pos_off, n_splits, M, part, out, out_hi, out_lo, arrive, s);
     }
@@ -3828,7 +3875,7 @@ hipError_t attention(const Dims& D, const float* q, int ldq, const void* kc, con
 {
     int ctx = pos_host_hint + pos_off + M;  // positions the last row sees
     if (ctx < 1 || ctx > D.max_seq || M < 1) return hipErrorInvalidValue;
-    AttnPlan pl = attn_plan(D, ctx, M);
+    AttnPlan pl = attn_plan(D, ctx, M, arrive != nullptr);
     if (deferred_splits) {  // single row: the consumer (gemv_resid_attn) folds the partials itself
         if (M != 1) return hipErrorInvalidValue;
         pl.defer_fold = pl.n_splits > 1 && pl.n_splits <= GV_FOLD_MAX;

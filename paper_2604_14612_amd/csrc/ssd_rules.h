@@ -120,6 +120,30 @@ inline AttnPlan attn_plan(const AttnShape& a, int ctx, int M, int force_splits, 
     return pl;
 }
 
+// The same for a single row whose launch folds its partials itself (the last block of a head does): few KV heads leave most of the
+// device idle with the eight ranges that the output projection folds, so a long context gets ranges of one pass, as many as
+// give every CU a block, and longer ones beyond that.  Their number goes in steps of four (ranges behind the position are empty): one
+// launch plan per four ranges.  Llama-3-8B widths (8 KV heads), us per layer beyond what 600 positions take, before / so: 16-bit cache, 2200
+// positions 7.5 / 4, 3000 8 / 5.5, 4000 7.5 / 7, 6000 17.5 / 10, 9000 23.5 / 14.5; fp32 cache, 4000 13 / 8, 9000 26 / 15.5.
+constexpr int AW_MANY_FROM = 12;   // one-pass ranges beyond which this plan is taken (up to there the eight ranges are one pass of a wider block)
+constexpr int AW_MANY_MAX = 64;
+inline AttnPlan attn_plan_many(const AttnShape& a, int ctx, int force_splits, int force_kernel)
+{
+    const AttnPlan pl = attn_plan(a, ctx, 1, force_splits, force_kernel);
+    const int base = AW_RANGE_BYTES / (a.hd * (a.kv_f32 ? 4 : 2)), want = ceil_div(ctx, base);
+    const int limit = 256 / a.Hkv < AW_MANY_MAX ? 256 / a.Hkv : AW_MANY_MAX;
+    if (!pl.wide || force_splits > 0 || want <= AW_MANY_FROM || limit < 12) return pl;
+    AttnPlan many = pl;
+    many.n_splits = ceil_div(want, 4) * 4;
+    many.chunk = base;
+    if (many.n_splits > limit) {
+        const int even = ceil_div(ceil_div(ctx, limit), 16) * 16;
+        if (even > base) many.chunk = even;
+        many.n_splits = ceil_div(ctx, many.chunk);
+    }
+    return many.n_splits > pl.n_splits ? many : pl;
+}
+
 // Context that the steps of a draft of up to k tokens behind n committed ones are planned for: the last step's, for all of
 // them, so that a draft has one plan and not a mixture of two where it changes inside the draft (k = 4, positions 600 to 4086,
 // 128-wide fp32 heads: 30 launch sequences instead of 117, each of which runs kernel by kernel once and is then captured).

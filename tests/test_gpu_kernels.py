@@ -224,3 +224,22 @@ def test_partials_folded_by_the_last_block(kv, plen):
     prompt = make_prompt(shape.vocab, plen, 7).tolist()
     st = lockstep_ssd(ctx, orc, prompt, 0, [7, 7, 7, 2], np.array([0, 1], np.uint8), shape.dtype)
     assert st["unpinned_cycles"] <= 2
+
+
+# Single rows over contexts long enough for more ranges than the output projection folds: heads in groups of four and alone, both sides of the
+# rule, more ranges than one share of the fold takes
+@pytest.mark.parametrize("heads,kv_heads,plen", [(20, 5, 1530), (20, 5, 2950), (20, 20, 1530), (10, 10, 1300), (10, 5, 1700)])
+def test_single_rows_fold_many_ranges(heads, kv_heads, plen):
+    shape = ModelShape(1, 1280, heads, kv_heads, 192, 528)
+    orc, ctx = make_pair(shape, 23, plen + 24, max_k=8, norm_gain_std=0.1)
+    prompt = make_prompt(shape.vocab, plen, 7).tolist()
+    o = OracleSSD(orc)
+    o.prefill(prompt)
+    ctx.ssd_prefill(prompt)
+    for i in range(3):                      # kernel by kernel, captured, replayed
+        o.decode()
+        got = ctx.ssd_decode()
+        assert_logits_close(ctx.ssd_copy_logits(0, 1)[0], o.last_logits[0], shape.dtype, "decode %d" % i)
+        if got != o.tokens[-1]:
+            assert not decisive(o.last_logits[0], shape.dtype)
+            break

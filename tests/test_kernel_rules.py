@@ -19,6 +19,10 @@ void attention_plan(int G, int Hkv, int hd, int kv_f32, int w_f32, int ctx, int 
     const AttnPlan p = attn_plan(AttnShape{G, Hkv, hd, kv_f32 != 0, w_f32 != 0}, ctx, M, 0, 0);
     out[0] = p.wide; out[1] = p.n_splits; out[2] = p.chunk;
 }
+void attention_plan_many(int G, int Hkv, int hd, int kv_f32, int w_f32, int ctx, int* out) {
+    const AttnPlan p = attn_plan_many(AttnShape{G, Hkv, hd, kv_f32 != 0, w_f32 != 0}, ctx, 0, 0);
+    out[0] = p.wide; out[1] = p.n_splits; out[2] = p.chunk;
+}
 int qkv_tile(int n_total, int m_blocks) { return qkv_tile_rows(n_total, m_blocks); }
 int draft_ctx(int n, int k) { return draft_plan_ctx(n, k); }
 size_t embedding_row(int tok, int V) { return embed_row(tok, V); }
@@ -138,3 +142,24 @@ def test_k_slices_of_the_large_tiles(rules):
                 assert 1 <= ks <= min(8, stripes)
                 if blocks % slots == 0:
                     assert ks == 1
+
+
+@pytest.mark.parametrize("shape", ATTN_SHAPES + [(1, 17, 64, 1, 0), (4, 2, 128, 0, 0), (2, 1, 64, 1, 1)])
+def test_ranges_of_a_single_row_that_folds_them_itself(rules, shape):
+    """They cover the context, fit the scratch and the device, differ from the ranges the output projection folds only where those would
+    be long, and change as rarely as those do."""
+    G, Hkv, hd, kv_f32, _ = shape
+    base, plans = 32 * 1024 // (hd * (4 if kv_f32 else 2)), []
+    for ctx in list(range(1, 5000)) + list(range(5000, 33000, 61)):
+        out = (C.c_int * 3)()
+        rules.attention_plan_many(*shape, ctx, out)
+        wide, ns, chunk = out
+        plans.append(tuple(out))
+        assert ns * chunk >= ctx and chunk >= 1
+        if plan(rules, *shape, ctx, 1) == tuple(out):
+            continue
+        assert wide and -(-ctx // base) > 12 and chunk % 16 == 0 and chunk >= base
+        assert plan(rules, *shape, ctx, 1)[1] < ns <= min(64, 256 // Hkv)
+        assert (ns - 1) * chunk < ctx + 3 * base        # at most three empty ranges
+    if plans[0][0]:
+        assert len(set(plans[600:4091])) <= 36
