@@ -308,7 +308,7 @@ enum {
 };
 SSD_API int ssd_profile_select(ssd_ctx *ctx, int kernel_id);
 /* Launch mode: 1 (default) replays decode / draft / verify launch sequences as HIP graphs once a
- * sequence has been seen twice (needs a non-default stream); 0 launches kernel by kernel.  Both
+ * sequence has been seen twice (needs a non-default stream; steps and verifications in one launch are launched as they are); 0 launches kernel by kernel.  Both
  * modes run the same kernels with the same arguments and give bit-identical results. */
 SSD_API int ssd_set_graphs(ssd_ctx *ctx, int enable);
 SSD_API int ssd_profile_read(ssd_ctx *ctx, int64_t *launches_out, double *total_ms_out);

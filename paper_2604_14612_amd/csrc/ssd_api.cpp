@@ -624,11 +624,13 @@ void drop_graphs(ssd_ctx* c)
 // second time it is captured into a HIP graph, and from then on the graph is replayed (one
 // submission instead of hundreds of launches).  Everything position-dependent is read from
 // device memory by the kernels, so a graph stays valid as the sequence grows; what is baked into
-// it (skip mask, k, attention split counts) is part of the key.
+// it (skip mask, k, attention split counts) is part of the key.  Steps and verifications in one launch are two or three kernels
+// each, which the host submits faster than a graph starts: us per call, replayed / launched, four layers of 256: draft of four
+// 144 / 135, decode step 68 / 61; eight of 1024: 316 / 307, 144 / 137.
 template <typename F>
 int run_sequence(ssd_ctx* c, const std::string& key, F&& body)
 {
-    if (!c->use_graphs || c->prof_kid >= 0 || c->stream == nullptr) return body();
+    if (!c->use_graphs || c->prof_kid >= 0 || c->stream == nullptr || c->step_now) return body();
     auto it = c->graphs.find(key);
     if (it == c->graphs.end()) {
         if (c->graphs.size() >= 256) drop_graphs(c);   // masks change during the search: keep the cache bounded
@@ -725,8 +727,16 @@ int conf_batch(ssd_ctx* c, const ConfScratch& sc, const float* taps, int nb, flo
             TIMED(SSD_K_ROWS_LMHEAD, rows_big(D, lm, c->stream), "rows conf lmhead");
         } else if (rows_many_supported(D, D.V, D.d)) {
             for (int b = 0; b < nb; b += 64) {   // the LM head is streamed once per 64 tap rows
+                const int n = nb - b < 64 ? nb - b : 64;
+                if (n <= 16) {   // (eight rows of 7B 50 us against 53, six of 70B 85 against 97, 16 of a 1024-wide model 15 against 16)
+                    RowsFused lm = {};
+                    lm.w[0] = c->w.lm_head; lm.n[0] = D.V; lm.K = D.d; lm.bh = sc.hi + (size_t)b * D.d; lm.bl = sc.lo + (size_t)b * D.d;
+                    lm.ldb = D.d; lm.y = sc.logits + (size_t)b * D.V; lm.ldy = D.V; lm.M = n; lm.mode = 0;
+                    TIMED(SSD_K_ROWS_LMHEAD, rows_fused(D, lm, c->stream), "rows conf lmhead");
+                    continue;
+                }
                 TIMED(SSD_K_ROWS_LMHEAD, rows_many(D, c->w.lm_head, D.V, D.d, sc.hi + (size_t)b * D.d, sc.lo + (size_t)b * D.d,
-                                                   D.d, nb - b < 64 ? nb - b : 64, sc.logits + (size_t)b * D.V, D.V, c->stream),
+                                                   D.d, n, sc.logits + (size_t)b * D.V, D.V, c->stream),
                       "rows conf lmhead");
             }
         } else {
