@@ -374,7 +374,7 @@ int prompt_last_row(ssd_ctx* c, int M, int pos_off, int pos_host)
     q.y = c->f(Y.qkv); q.ldy = D.dq; q.M = 1; q.mode = 3; q.rope = c->f(Y.rope); q.pos_dev = c->pos_dev(); q.pos_off = pos;
     TIMED(SSD_K_ROWS_QKV, rows_fused(D, q, c->stream), "last_q");
     TIMED(SSD_K_ATTENTION, attention(D, c->f(Y.qkv), D.dq, c->kcache(l), c->vcache(l), c->pos_dev(), pos, pos_host, 1, c->f(Y.part),
-                                     nullptr, hi, lo, c->stream), "attention");
+                                     nullptr, hi, lo, c->stream, nullptr, c->arrive()), "attention");
     RowsFused o = {};
     o.w[0] = c->wo[l]; o.n[0] = D.d; o.K = D.dq; o.bh = hi; o.bl = lo; o.ldb = D.dq; o.y = x; o.ldy = D.d; o.M = 1; o.mode = 1;
     o.tap = c->f(Y.taps) + ((size_t)l * 2 + 0) * D.d; o.tap_ld = D.L * 2 * D.d;

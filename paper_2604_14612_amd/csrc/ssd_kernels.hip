@@ -246,7 +246,7 @@ struct GemvP {
     const float* in;    // [K]
     const float* part;  // when set (RESID only): the input is the fold of n_splits attention partials of row 0
     int n_splits;       //   laid out [K / hd heads][n_splits][hd + 4] as the attention kernels write them
-    const float* gain;  // rmsnorm gain or nullptr (input used as is)
+    const float* gain;  // rmsnorm gain (RESID: none, the input is used as it is)
     float eps;
     int K;
     int n_rows;         // logical rows (QKV: dq + 2 dkv; SWIGLU: 2 f; else N)
@@ -904,6 +904,7 @@ hipError_t gemv_resid_attn(const Dims& D, const void* w, const float* part, int 
 hipError_t gemv_swiglu(const Dims& D, const void* wg, const void* wu, const float* gain, const float* x, float* act,
                        hipStream_t s)
 {
+    if (!gain) return hipErrorInvalidValue;
     GemvP p = {};
     p.w0 = wg; p.w1 = wu; p.in = x; p.gain = gain; p.eps = D.eps; p.K = D.d; p.n_rows = 2 * D.f; p.y = act;
     return launch_gemv<EPI_SWIGLU>(D, p, s);
@@ -911,6 +912,7 @@ hipError_t gemv_swiglu(const Dims& D, const void* wg, const void* wu, const floa
 
 hipError_t gemv_lmhead(const Dims& D, const void* wlm, const float* gain, const float* x, float* logits, hipStream_t s)
 {
+    if (!gain) return hipErrorInvalidValue;
     GemvP p = {};
     p.w0 = wlm; p.in = x; p.gain = gain; p.eps = D.eps; p.K = D.d; p.n_rows = D.V; p.y = logits;
     return launch_gemv<EPI_STORE>(D, p, s);
@@ -919,7 +921,7 @@ hipError_t gemv_lmhead(const Dims& D, const void* wlm, const float* gain, const 
 hipError_t gemv_lmhead_argmax(const Dims& D, const void* wlm, const float* gain, const float* x, float* logits, float clamp,
                               float* vstat, const StepOut& o, hipStream_t s)
 {
-    if (!vstat || !o.tok_out || !o.tok_host || !o.maxprob_host || (o.pos_dev && !o.tok0) || (o.x_next && !o.embed)) return hipErrorInvalidValue;
+    if (!gain || !vstat || !o.tok_out || !o.tok_host || !o.maxprob_host || (o.pos_dev && !o.tok0) || (o.x_next && !o.embed)) return hipErrorInvalidValue;
     GemvP p = {};
     p.w0 = wlm; p.in = x; p.gain = gain; p.eps = D.eps; p.K = D.d; p.n_rows = D.V; p.y = logits;
     p.vstat = vstat; p.clamp = clamp;
