@@ -1031,7 +1031,7 @@ int ssd_decode(ssd_ctx* c, int32_t* token_out)
 
 // b steps whose results are waited for once: each leaves the embedding row of its token to the next one, and its token in the
 // pinned log.  done receives how many were committed: fewer than b where a wait of a step in one launch gave up (those behind it
-// commit nothing either).
+// commit nothing either) and, with an error, where a step could not be enqueued behind others.
 static int decode_batch(ssd_ctx* c, int b, int32_t* tokens_out, int& done)
 {
     const int n = c->n;
@@ -1053,31 +1053,38 @@ static int decode_batch(ssd_ctx* c, int b, int32_t* tokens_out, int& done)
         }
         return SSD_OK;
     };
-    const int rc = run(), rs = sync_results(c);
-    if (rc || rs) {
-        c->step_table = false;   // as in run_steps
-        return rc ? rc : rs;
+    int32_t pos = n - 1 + b;
+    auto settle = [&](bool all) -> int {   // waits; the device's position says what was committed
+        const int rs = sync_results(c);
+        if (rs || all) return rs;
+        HIPCHK(hipMemcpyAsync(&pos, c->pos_dev(), 4, hipMemcpyDeviceToHost, c->stream), "position");
+        return sync_results(c);
+    };
+    int rc = run(), rs = settle(!rc);
+    const bool gave_up = !rc && !rs && c->step_now && c->pinned[PIN_STEP];
+    if (gave_up) rs = settle(false);
+    if (rc || rs) c->step_table = false;   // as in run_steps
+    if (rs) {   // what was committed is not known: the sequence is over
+        c->state = ST_READY;
+        c->n = 0; c->tap_rows = 0; c->logit_rows = 0;
+        return rs;
     }
-    done = b;
+    done = pos - (n - 1);
+    memcpy(tokens_out, c->pinned + PIN_PROMPT + n - 1, sizeof(int32_t) * done);
+    c->n += done;
+    if (done > 0) { c->logit_rows = rc ? 0 : 1; c->tap_rows = 0; }   // (with an error a step behind the committed ones may have begun)
+    c->st.decode_steps += done; c->st.committed += done;
     if (c->step_now) {
-        if (c->pinned[PIN_STEP]) {
-            int32_t pos = 0;
-            HIPCHK(hipMemcpyAsync(&pos, c->pos_dev(), 4, hipMemcpyDeviceToHost, c->stream), "position");
-            HIPCHK(hipMemsetAsync(c->ws + c->lay.step + 4, 0, 4, c->stream), "step error clear");
-            HIPCHK(hipStreamSynchronize(c->stream), "position");
-            done = pos - (n - 1);
+        c->step_count += done;
+        if (gave_up) {
             c->step_gave_up++;
             c->step_try.gave_up();
+            HIPCHK(hipMemsetAsync(c->ws + c->lay.step + 4, 0, 4, c->stream), "step error clear");
         } else {
             c->step_try.ran = true;
         }
-        c->step_count += done;
     }
-    memcpy(tokens_out, c->pinned + PIN_PROMPT + n - 1, sizeof(int32_t) * done);
-    c->n += done;
-    if (done > 0) { c->logit_rows = 1; c->tap_rows = 0; }
-    c->st.decode_steps += done; c->st.committed += done;
-    return SSD_OK;
+    return rc;
 }
 
 int ssd_decode_many(ssd_ctx* c, int count, int32_t* tokens_out)
