@@ -611,8 +611,15 @@ int verify_fused(ssd_ctx* c, int M, Tokens tok)
     return SSD_OK;
 }
 
-// Captured sequences hold the addresses of the weights and of the workspace: whoever changes those drops the sequences.  None is
-// in flight then, every call that replays one waits for it.
+// Waits for the results a call's kernels leave in the pinned buffer.
+int sync_results(ssd_ctx* c)
+{
+    HIPCHK(hipStreamSynchronize(c->stream), "result sync");
+    return SSD_OK;
+}
+
+// Captured sequences hold the addresses of the weights and of the workspace: whoever changes those drops the sequences.  None may be
+// in flight then: every call that replays one waits for it before it returns.
 void drop_graphs(ssd_ctx* c)
 {
     for (auto& e : c->graphs)
@@ -633,7 +640,11 @@ int run_sequence(ssd_ctx* c, const std::string& key, F&& body)
     if (!c->use_graphs || c->prof_kid >= 0 || c->stream == nullptr || c->step_now) return body();
     auto it = c->graphs.find(key);
     if (it == c->graphs.end()) {
-        if (c->graphs.size() >= 256) drop_graphs(c);   // masks change during the search: keep the cache bounded
+        if (c->graphs.size() >= 256) {   // masks change during the search: keep the cache bounded
+            const int rc = sync_results(c);   // (a batch of decode steps has sequences in flight)
+            if (rc) return rc;
+            drop_graphs(c);
+        }
         c->graphs[key] = nullptr;
         return body();
     }
@@ -654,13 +665,6 @@ int run_sequence(ssd_ctx* c, const std::string& key, F&& body)
         it->second = exec;
     }
     HIPCHK(hipGraphLaunch(it->second, c->stream), "graph launch");
-    return SSD_OK;
-}
-
-// Waits for the results a call's kernels leave in the pinned buffer.
-int sync_results(ssd_ctx* c)
-{
-    HIPCHK(hipStreamSynchronize(c->stream), "result sync");
     return SSD_OK;
 }
 
@@ -1043,10 +1047,6 @@ static int decode_batch(ssd_ctx* c, int b, int32_t* tokens_out, int& done)
         HIPCHK(embed_rows(c->D, c->w.embed, Tokens{c->small_i() + SM_TOK, nullptr}, 1, c->f(c->lay.x), c->stream, c->f(c->lay.rope), c->pos_dev(), 0,
                           c->small_f() + SM_ROPE), "embed");
         for (int i = 0; i < b; i++) {
-            if (c->graphs.size() >= 256) {   // run_sequence drops the sequences then: none may be in flight
-                const int rs = sync_results(c);
-                if (rs) return rs;
-            }
             const int rc = run_sequence(c, (c->step_now ? "PN|" : "N|") + std::to_string(attention_splits(c->D, n + i, 1)), [&]() {
                 return forward_single(c, nullptr, 0, 1, 0, n + i, 0, STEP_CHAINED | STEP_CHAIN_NEXT | STEP_COMMIT | STEP_LOG); });
             if (rc) return rc;

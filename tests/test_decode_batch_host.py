@@ -261,3 +261,20 @@ def test_a_step_that_gives_up_inside_a_batch(sim, at):
     s["give_up_at"] = at
     assert s.many(40) == (0, s.expect(40))
     assert s.one_launch() == [at, 0, 1] and s.stats().decode_steps == 40 and s.stats().n_tokens == 44
+
+
+def test_a_full_cache_of_sequences_costs_no_waits(sim):
+    """Sequences are dropped, behind a wait, where a new one finds the cache full, and nowhere else."""
+    s = sim(replay=True)
+    assert s.many(33) == (0, s.expect(33))
+    s.l.t_fill_cache(s.h, 256)
+    for _ in range(3):
+        before = s["syncs"]
+        assert s.many(4) == (0, s.expect(4)) and s["syncs"] == before + 1
+    assert s.l.t_cached(s.h) == 256
+    assert s.many(300) == (0, s.expect(300)) and s.l.t_cached(s.h) < 256     # plans that were not seen yet
+    assert s["dropped_in_flight"] == 0
+    narrow = sim(replay=True, blocks=256)
+    narrow.l.t_fill_cache(narrow.h, 256)
+    before = narrow["syncs"]
+    assert narrow.many(32) == (0, narrow.expect(32)) and narrow["syncs"] == before + 1
