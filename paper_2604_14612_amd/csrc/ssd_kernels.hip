@@ -2185,9 +2185,12 @@ __global__ __launch_bounds__(TN == 128 ? 256 : 512, 2) void rows_big_kernel(Rows
             put(slot, 0);
             lds_barrier();
         };
+        // In front of the weights: a wave has 32 rows here, and their sums beside two stripes in flight are more than its registers
+        // hold (36 bytes of scratch per lane in SwiGLU launches, also those cut along K, which scale nothing).  us, behind the first
+        // requests / so: 2048 x 5440, 512 rows, uncut 90.0 / 85.3; 1000 rows, the last tiles cut 79.5 / 75.2; 1024 x 2752 26.5 / 25.0.
+        row_scales();
 #pragma unroll
         for (int sl = 0; sl < MB_D; sl++) gload(sl, sl);
-        row_scales();
         int ck0 = 0;
         for (; ck0 + 2 * MB_D <= NC; ck0 += MB_D) {   // steady state: every step refills its slot, no conditions
 #pragma unroll
