@@ -518,9 +518,10 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_kernel(GemvP p)
     constexpr bool GAIN = EPI != EPI_RESID;
     constexpr int XN = FOLD ? 2 : EPI == EPI_STORE ? 2 : EPI == EPI_RESID ? 7 : 4;
     int pos = 0;
+    float rope_r = 0.f;
     if (EPI == EPI_QKV) {
         pos = p.pos_dev[0] + p.pos_off;
-        if ((int)threadIdx.x < p.hd) rope_row[threadIdx.x] = p.rope_row[threadIdx.x];   // hd / 2 pairs
+        rope_r = p.rope_row[min((int)threadIdx.x, p.hd - 1)];   // hd / 2 pairs
     }
     float res_r = 0.f;
     constexpr int NRES = GPB * GV_RES_ROUNDS * R;
@@ -552,6 +553,7 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_kernel(GemvP p)
         *reinterpret_cast<float4*>(xs + gv_xpos<VEC>(i)) = v;
     };
     if (EPI == EPI_RESID && (int)threadIdx.x < NRES) res_s[threadIdx.x] = res_r;   // [group of the block][round][row]
+    if (EPI == EPI_QKV && (int)threadIdx.x < p.hd) rope_row[threadIdx.x] = rope_r;
 #pragma unroll
     for (int u = 0; u < XN; u++) {
         const int i = ((int)threadIdx.x + u * GV_THREADS) * 4;

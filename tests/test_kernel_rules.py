@@ -60,6 +60,14 @@ def test_every_row_scale_of_the_16_row_kernel_has_one_writer(rules):
     assert len(re.findall(r"\brs\[[^]]*\]\s*=[^=]", kernel_source("rows_mfma3_kernel"))) == 1
 
 
+def test_single_row_products_request_their_first_weights_before_they_wait():
+    """A value that goes to LDS in front of the first requests is waited for in front of them (loads return in order)."""
+    src = kernel_source("gemv_kernel")
+    first = src.index("for (int s = 0; s < D; s++) issue(s);")
+    stores = [m.start() for m in re.finditer(r"\b(rope_row|res_s|red|part)\[[^]]*\](\[[^]]*\])?\s*=[^=]|reinterpret_cast<float4\*>\(xs", src)]
+    assert len(stores) >= 4 and min(stores) > first
+
+
 @pytest.mark.parametrize("vocab", [16, 1024, 128256])
 def test_embedding_gathers_stay_inside_the_table(rules, vocab):
     """An id is a row, any other value reads the first or the last one: 0x7fffffff is what a row of NaN logits leaves as arg-max."""
