@@ -14,12 +14,14 @@ from typing import List, Optional, Sequence
 
 from .binding import Context, Search, search_defaults, select_defaults
 
+DECODE_BATCH = 32    # decode steps that ssd_decode_many waits for together
+
 
 def generate_vanilla(ctx: Context, prompt: Sequence[int], n_new: int) -> List[int]:
     """n_new greedy tokens from the full model, one per step."""
     out = [ctx.ssd_prefill(prompt)]
-    if n_new > 1:
-        out += ctx.ssd_decode_many(n_new - 1)
+    while len(out) < n_new:     # as many as the library waits for together: an interrupt gets through in between
+        out += ctx.ssd_decode_many(min(n_new - len(out), DECODE_BATCH))
     return out[:n_new]
 
 

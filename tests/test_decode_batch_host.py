@@ -278,3 +278,21 @@ def test_a_full_cache_of_sequences_costs_no_waits(sim):
     narrow.l.t_fill_cache(narrow.h, 256)
     before = narrow["syncs"]
     assert narrow.many(32) == (0, narrow.expect(32)) and narrow["syncs"] == before + 1
+
+
+@pytest.mark.parametrize("n_new", [0, 1, 2, 33, 34, 100])
+def test_a_request_can_be_interrupted_between_batches(n_new):
+    """Python sees a signal when a call has returned: no call of a request makes more steps than are waited for together."""
+    class Steps:
+        def __init__(self):
+            self.made = []
+
+        def ssd_prefill(self, prompt):
+            return 100
+
+        def ssd_decode_many(self, count):
+            self.made.append(count)
+            return [101 + i for i in range(sum(self.made) - count, sum(self.made))]
+    s = Steps()
+    assert ssd.generate_vanilla(s, PROMPT, n_new) == list(range(100, 100 + n_new))
+    assert sum(s.made) == max(n_new - 1, 0) and all(1 <= m <= 32 for m in s.made) and len(s.made) == -(-max(n_new - 1, 0) // 32)
