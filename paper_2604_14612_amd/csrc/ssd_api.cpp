@@ -631,13 +631,13 @@ void drop_graphs(ssd_ctx* c)
 // second time it is captured into a HIP graph, and from then on the graph is replayed (one
 // submission instead of hundreds of launches).  Everything position-dependent is read from
 // device memory by the kernels, so a graph stays valid as the sequence grows; what is baked into
-// it (skip mask, k, attention split counts) is part of the key.  Steps and verifications in one launch are two or three kernels
-// each, which the host submits faster than a graph starts: us per call, replayed / launched, four layers of 256: draft of four
-// 144 / 135, decode step 68 / 61; eight of 1024: 316 / 307, 144 / 137.
+// it (skip mask, k, attention split counts) is part of the key.  Steps and verifications in one launch do not come here: they are two or
+// three kernels each, which the host submits faster than a graph starts: us per call, replayed / launched, four layers of 256: draft of
+// four 144 / 135, decode step 68 / 61; eight of 1024: 316 / 307, 144 / 137.
 template <typename F>
 int run_sequence(ssd_ctx* c, const std::string& key, F&& body)
 {
-    if (!c->use_graphs || c->prof_kid >= 0 || c->stream == nullptr || c->step_now) return body();
+    if (!c->use_graphs || c->prof_kid >= 0 || c->stream == nullptr) return body();
     auto it = c->graphs.find(key);
     if (it == c->graphs.end()) {
         if (c->graphs.size() >= 256) {   // masks change during the search: keep the cache bounded
@@ -679,15 +679,15 @@ bool whole_layers(const ssd_ctx* c, const uint8_t* sub)
 // Runs the launch sequence of a call of single-row steps or of a verification and waits for its results.  fits: it can take
 // one launch per step.  Where it does and a wait inside gave up, everything from the pending token on is done
 // again by the launches per matrix (nothing was committed, cache rows of uncommitted positions are written anew).
-// counter += n where the call ended as one launch per step.
-template <typename F>
-int run_steps(ssd_ctx* c, const std::string& key, bool fits, int64_t& counter, int n, F&& body)
+// counter += n where the call ended as one launch per step.  key(): of the sequence of launches per matrix.
+template <typename K, typename F>
+int run_steps(ssd_ctx* c, K&& key, bool fits, int64_t& counter, int n, F&& body)
 {
     {
         StepSlot slot(c, c->step_on && c->step_blocks > 0 && c->step_table && c->step_try.on() && fits && c->prof_kid < 0);
         if (c->step_now) {
             c->pinned[PIN_STEP] = 0;
-            int rc = run_sequence(c, "P" + key, body);
+            int rc = body();
             const int rs = sync_results(c);   // the slot is free again when the launches are done
             if (rc || rs) {
                 c->step_table = false;   // a step without its end leaves words whose tags come again: none before the next prefill clears them
@@ -703,7 +703,7 @@ int run_steps(ssd_ctx* c, const std::string& key, bool fits, int64_t& counter, i
             HIPCHK(hipMemsetAsync(c->ws + c->lay.step + 4, 0, 4, c->stream), "step error clear");
         }
     }
-    int rc = run_sequence(c, key, body);
+    int rc = run_sequence(c, key(), body);
     return rc ? rc : sync_results(c);
 }
 
@@ -1021,7 +1021,7 @@ int ssd_decode(ssd_ctx* c, int32_t* token_out)
     if (c->state != ST_IDLE) return fail(c, SSD_ESTATE, "decode needs a prefilled sequence with no draft in flight");
     if (c->n + 1 > c->D.max_seq) return fail(c, SSD_ECAPACITY, "sequence would exceed max_seq");
     // pending token sits in tok slot 0; its successor is written to slot 1, then promoted
-    std::string key = "D|" + std::to_string(attention_splits(c->D, c->n, 1));
+    auto key = [&]() { return "D|" + std::to_string(attention_splits(c->D, c->n, 1)); };
     int rc = run_steps(c, key, step_plan_fits(c->D, c->n, c->step_blocks), c->step_count, 1,
                        [&]() { return forward_single(c, nullptr, 0, 1, 0, c->n, 0, STEP_COMMIT); });
     if (rc) return rc;
@@ -1047,8 +1047,8 @@ static int decode_batch(ssd_ctx* c, int b, int32_t* tokens_out, int& done)
         HIPCHK(embed_rows(c->D, c->w.embed, Tokens{c->small_i() + SM_TOK, nullptr}, 1, c->f(c->lay.x), c->stream, c->f(c->lay.rope), c->pos_dev(), 0,
                           c->small_f() + SM_ROPE), "embed");
         for (int i = 0; i < b; i++) {
-            const int rc = run_sequence(c, (c->step_now ? "PN|" : "N|") + std::to_string(attention_splits(c->D, n + i, 1)), [&]() {
-                return forward_single(c, nullptr, 0, 1, 0, n + i, 0, STEP_CHAINED | STEP_CHAIN_NEXT | STEP_COMMIT | STEP_LOG); });
+            auto step = [&]() { return forward_single(c, nullptr, 0, 1, 0, n + i, 0, STEP_CHAINED | STEP_CHAIN_NEXT | STEP_COMMIT | STEP_LOG); };
+            const int rc = c->step_now ? step() : run_sequence(c, "N|" + std::to_string(attention_splits(c->D, n + i, 1)), step);
             if (rc) return rc;
         }
         return SSD_OK;
@@ -1120,7 +1120,7 @@ static int draft_fixed(ssd_ctx* c, const std::vector<uint8_t>& sub, int k, int32
     if (k > c->cfg.max_k) return fail(c, SSD_ECAPACITY, "k exceeds max_k");
     if (c->n + k > c->D.max_seq) return fail(c, SSD_ECAPACITY, "draft + verification would exceed max_seq");
     const bool fits = whole_layers(c, sub.data()) && step_plan_fits(c->D, draft_plan_ctx(c->n, k), c->step_blocks);
-    int rc = run_steps(c, draft_key(c->D, sub, c->n, k), fits, c->step_count, k, [&]() {
+    int rc = run_steps(c, [&]() { return draft_key(c->D, sub, c->n, k); }, fits, c->step_count, k, [&]() {
         for (int i = 0; i < k; i++) {
             int r = forward_single(c, sub.data(), i, i + 1, i, draft_plan_ctx(c->n, k), i, (i ? STEP_CHAINED : 0) | (i + 1 < k ? STEP_CHAIN_NEXT : 0));
             if (r) return r;
@@ -1175,7 +1175,7 @@ int ssd_draft_adaptive(ssd_ctx* c, const uint8_t* skip_mask, int k_max, float ga
         // one draft step per submission: the host reads the step's max-probability before deciding on the next
         const int i = k;
         const bool fits = whole_layers(c, sub.data()) && step_plan_fits(c->D, draft_plan_ctx(c->n, k_max), c->step_blocks);
-        int rc = run_steps(c, adaptive_key(c->D, sub, c->n, k_max, i), fits, c->step_count, 1,
+        int rc = run_steps(c, [&]() { return adaptive_key(c->D, sub, c->n, k_max, i); }, fits, c->step_count, 1,
                            [&]() { return forward_single(c, sub.data(), i, i + 1, i, draft_plan_ctx(c->n, k_max), i, 0); });
         if (rc) return rc;
         const float p = c->pin_f(PIN_PROB)[i];
@@ -1201,7 +1201,7 @@ int ssd_verify(ssd_ctx* c, const int32_t* draft, int k, int32_t* target_out)
     for (int i = 0; i < k; i++)
         if (draft[i] < 0 || draft[i] >= c->D.V) return fail(c, SSD_EINVAL, "draft token id out of range");
     for (int i = 0; i < k; i++) c->pinned[PIN_VTOK + 1 + i] = draft[i];
-    std::string key = "V|" + std::to_string(k) + "|" + std::to_string(attention_splits(c->D, c->n + k, k + 1));
+    auto key = [&]() { return "V|" + std::to_string(k) + "|" + std::to_string(attention_splits(c->D, c->n + k, k + 1)); };
     const Tokens tok = {c->pinned + PIN_VTOK, c->small_i() + SM_TOK};
     const bool fits = rows_step_fits(c->D, k + 1, c->n + k, c->step_blocks, c->step_max_rows) && (size_t)2 * (k + 1) * c->step_blocks <= c->lay.part_floats;
     int rc = run_steps(c, key, fits, c->step_verify_count, 1, [&]() { return c->step_now ? verify_fused(c, k + 1, tok) : forward_rows(c, k + 1, 0, c->n - 1, true, tok); });
@@ -1364,9 +1364,7 @@ int ssd_set_graphs(ssd_ctx* c, int enable)
 int ssd_set_one_launch(ssd_ctx* c, int enable, int wait_us)
 {
     if (!c) return SSD_EINVAL;
-    const long ticks = wait_us < 0 ? -1 : (wait_us == 0 ? STEP_WAIT_US : wait_us) * STEP_TICKS_PER_US;
-    if (ticks != c->step_ticks) drop_graphs(c);   // the bound is an argument of the captured launches
-    c->step_ticks = ticks;
+    c->step_ticks = wait_us < 0 ? -1 : (wait_us == 0 ? STEP_WAIT_US : wait_us) * STEP_TICKS_PER_US;
     c->step_on = enable != 0;
     c->step_try = StepBackoff();
     return SSD_OK;

@@ -138,7 +138,7 @@ def host(tmp_path_factory):
     assert r.returncode == 0, r.stderr[-4000:]
     l = C.CDLL(lib)
     for name in ("ssd_create", "ssd_workspace_bytes", "ssd_set_workspace", "ssd_load_weights", "ssd_reset", "ssd_destroy", "ssd_prefill", "ssd_decode",
-                 "ssd_decode_many", "ssd_get_stats", "ssd_get_one_launch", "ssd_last_error"):
+                 "ssd_decode_many", "ssd_get_stats", "ssd_get_one_launch", "ssd_set_one_launch", "ssd_last_error"):
         getattr(l, name).restype, getattr(l, name).argtypes = SYMBOLS[name]
     l.t_sim.restype = C.POINTER(C.c_int)
     l.t_fill_cache.argtypes = [C.c_void_p, C.c_int]
@@ -278,6 +278,22 @@ def test_a_full_cache_of_sequences_costs_no_waits(sim):
     narrow.l.t_fill_cache(narrow.h, 256)
     before = narrow["syncs"]
     assert narrow.many(32) == (0, narrow.expect(32)) and narrow["syncs"] == before + 1
+
+
+def test_steps_in_one_launch_and_the_cache_of_sequences(sim):
+    """They are never captured, so they leave nothing there, and a new bound of their waits takes nothing out."""
+    s = sim(replay=True, blocks=256)
+    assert s.many(40) == (0, s.expect(40)) and s.decode() == (0, s.expect(1)[0])
+    assert s.l.t_cached(s.h) == 0
+    assert s.l.ssd_set_one_launch(s.h, 0, 0) == 0
+    assert s.many(40) == (0, s.expect(40))
+    cached = s.l.t_cached(s.h)
+    assert cached > 0
+    for bound in (-1, 1000, 0):
+        assert s.l.ssd_set_one_launch(s.h, 1, bound) == 0 and s.l.t_cached(s.h) == cached
+    before = s.one_launch()[0]
+    assert s.many(3) == (0, s.expect(3)) and s.decode() == (0, s.expect(1)[0])
+    assert s.l.t_cached(s.h) == cached and s.one_launch()[0] == before + 4
 
 
 @pytest.mark.parametrize("n_new", [0, 1, 2, 33, 34, 100])
