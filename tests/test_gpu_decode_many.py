@@ -11,27 +11,30 @@ SHAPES = {
     "one_launch": (ModelShape(2, 256, 4, 2, 688, 528, dtype="fp32"), True),    # each step one launch
     "per_matrix": (ModelShape(2, 1280, 10, 2, 192, 528), False),
     "untiled": (ModelShape(2, 1088, 17, 17, 176, 528, dtype="fp16"), False),
+    "one_launch_off": (ModelShape(2, 256, 4, 2, 688, 528, dtype="fp32"), False),
 }
+# replayed or launched makes a difference to the launches per matrix only
+CASES = [("one_launch", True)] + [(name, graphs) for name in ("one_launch_off", "per_matrix", "untiled") for graphs in (True, False)]
 
 
 # one step, two, whole batches of 32 and what is left over; positions that cross a change of attention's plan; the sequence full before the
 # count, on its last position and with the rotary row behind it outside the table
-@pytest.mark.parametrize("name", sorted(SHAPES))
+@pytest.mark.parametrize("name,graphs", CASES)
 @pytest.mark.parametrize("plen,count,room", [(1, 1, 5), (60, 2, 3), (60, 32, 40), (50, 70, 70), (118, 33, 33), (30, 40, 10), (30, 34, 1)])
-@pytest.mark.parametrize("graphs", [True, False])
-def test_same_as_single_steps(name, plen, count, room, graphs):
+def test_same_as_single_steps(name, graphs, plen, count, room):
     import paper_2604_14612_amd as ssd
     shape, one_launch = SHAPES[name]
     max_seq = plen + 1 + room          # committed tokens after the prompt: plen + 1
     ctx = ssd.Context(shape, to_gpu(make_weights(shape, 7, init_std=0.08)), max_seq, 4)
     ctx.ssd_set_graphs(graphs)
+    ctx.ssd_set_one_launch(name != "one_launch_off")
     prompt = make_prompt(shape.vocab, plen, 3).tolist()
     want, fit = [], min(count, room)
     ctx.ssd_prefill(prompt)
     for _ in range(fit):
         want.append(ctx.ssd_decode())
     z, stats = ctx.ssd_copy_logits(0, 1), ctx.ssd_get_stats()
-    for rep in range(3):               # kernel by kernel, captured, replayed
+    for rep in range(3):               # kernel by kernel, captured, replayed; steps in one launch are launched each time
         before = ctx.ssd_get_one_launch()
         ctx.ssd_reset()
         ctx.ssd_prefill(prompt)

@@ -227,11 +227,13 @@ def test_partials_folded_by_the_last_block(kv, plen):
 
 
 # Single rows over contexts long enough for more ranges than the output projection folds: heads in groups of four and alone, both sides of the
-# rule, more ranges than one share of the fold takes
-@pytest.mark.parametrize("heads,kv_heads,plen", [(20, 5, 1530), (20, 5, 2950), (20, 20, 1530), (10, 10, 1300), (10, 5, 1700)])
-def test_single_rows_fold_many_ranges(heads, kv_heads, plen):
+# rule, more ranges than one share of the fold takes, ranges made longer because there would be more than blocks (22 of 80 positions, 23 of
+# 144), 16-bit caches
+@pytest.mark.parametrize("heads,kv_heads,plen,kv", [(20, 5, 1530, "fp32"), (20, 5, 2950, "fp32"), (20, 20, 1530, "fp32"), (10, 10, 1300, "fp32"), (10, 5, 1700, "fp32"),
+                                                    (10, 10, 1700, "fp32"), (10, 5, 1700, "bf16"), (20, 5, 3400, "bf16"), (10, 10, 3220, "bf16")])
+def test_single_rows_fold_many_ranges(heads, kv_heads, plen, kv):
     shape = ModelShape(1, 1280, heads, kv_heads, 192, 528)
-    orc, ctx = make_pair(shape, 23, plen + 24, max_k=8, norm_gain_std=0.1)
+    orc, ctx = make_pair(shape, 23, plen + 24, max_k=8, norm_gain_std=0.1, kv_dtype=kv)
     prompt = make_prompt(shape.vocab, plen, 7).tolist()
     o = OracleSSD(orc)
     o.prefill(prompt)

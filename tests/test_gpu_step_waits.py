@@ -15,6 +15,7 @@ SHAPES = {
 }
 
 
+# graphs: how the launches per matrix that do the work again are enqueued (steps in one launch are launched as they are)
 @pytest.mark.parametrize("graphs", [False, True])
 @pytest.mark.parametrize("name", sorted(SHAPES))
 def test_calls_that_give_up_return_the_results_of_the_other_path(name, graphs):
@@ -39,7 +40,7 @@ def test_calls_that_give_up_return_the_results_of_the_other_path(name, graphs):
         for j in range(n):
             assert_logits_close(z[j], ref[j], shape.dtype, "%s row %d" % (what, j))
 
-    for rnd in range(4):                      # kernel by kernel, captured, replayed twice
+    for rnd in range(4):                      # the other path: kernel by kernel, captured, replayed twice
         d = call(lambda: ctx.ssd_draft_step(mask, 3))
         assert d == o.draft(mask, 3), rnd
         rows(3, o.last_draft_logits, "draft %d" % rnd)
