@@ -14,6 +14,7 @@
 #include <cstring>
 #include <map>
 #include <string>
+#include <thread>
 #include <vector>
 
 using namespace ssdk;
@@ -168,6 +169,7 @@ struct ssd_ctx {
     long step_ticks;   // bound of its waits
     int64_t step_count, step_verify_count, step_gave_up;   // steps and verifications that ran so, calls that did not end so
     bool step_now;     // the sequence being enqueued takes it
+    int calls;         // calls that are being counted, one inside the other
     std::vector<StepWeights> step_rows;   // host copy of the table
     bool use_graphs;   // replay captured launch sequences instead of launching kernel by kernel
     std::map<std::string, hipGraphExec_t> graphs;  // nullptr = sequence seen once, not captured yet
@@ -248,7 +250,7 @@ static inline bool is_gemv_kid(int kid)
 // One launch whose blocks wait for each other may be in flight per device and process: two of them would each hold CUs that the
 // other one needs.  Whoever finds the device's slot taken uses the launches per matrix.  Other processes are not seen: against
 // theirs there is the bound of the waits.
-constexpr int DECODE_BATCH = 32;      // decode steps enqueued before their tokens are waited for
+constexpr int DECODE_BATCH = 32;      // decode steps between two waits for the stream
 constexpr int STEP_WAIT_US = 50000;   // longer than what other streams' kernels usually hold CUs for
 std::atomic<bool> step_slots[64];
 struct StepSlot {
@@ -263,6 +265,32 @@ struct StepSlot {
     {
         c->step_now = false;
         if (slot) slot->store(false, std::memory_order_release);
+    }
+};
+
+// Calls of the process that have work on a device: in flight, begun so far.  A context that sees other ones' leaves the device after every
+// step, where their launches get in between and the slot above changes hands.  Two contexts of 24 layers of 1024 decoding, us per step:
+// 565 and 607 where every step is waited for, 390 and 1088 with batches beside each other.
+std::atomic<int> calls_in_flight[64];
+std::atomic<unsigned> calls_begun[64];
+struct InCall {
+    ssd_ctx* c;
+    unsigned seen = 0;
+    explicit InCall(ssd_ctx* ctx) : c(ctx)
+    {
+        if (c->calls++ || !counted()) return;   // (a call of the same context around this one counts)
+        calls_in_flight[c->device].fetch_add(1, std::memory_order_relaxed);
+        seen = calls_begun[c->device].fetch_add(1, std::memory_order_relaxed) + 1;
+    }
+    ~InCall() { if (!--c->calls && counted()) calls_in_flight[c->device].fetch_sub(1, std::memory_order_relaxed); }
+    bool counted() const { return c->device >= 0 && c->device < 64; }
+    // no other call is in flight, and none was begun since this was asked before
+    bool alone()
+    {
+        if (!counted()) return true;
+        const unsigned was = seen;
+        seen = calls_begun[c->device].load(std::memory_order_relaxed);
+        return seen == was && calls_in_flight[c->device].load(std::memory_order_relaxed) == 1;
     }
 };
 
@@ -683,6 +711,7 @@ bool whole_layers(const ssd_ctx* c, const uint8_t* sub)
 template <typename K, typename F>
 int run_steps(ssd_ctx* c, K&& key, bool fits, int64_t& counter, int n, F&& body)
 {
+    InCall in(c);
     {
         StepSlot slot(c, c->step_on && c->step_blocks > 0 && c->step_table && c->step_try.on() && fits && c->prof_kid < 0);
         if (c->step_now) {
@@ -781,6 +810,7 @@ int conf_batch(ssd_ctx* c, const ConfScratch& sc, const float* taps, int nb, flo
 int confidence_rows(ssd_ctx* c, const ConfScratch& sc, int row_begin, int n_rows, float* conf_out, float* tap_conf_out,
                     float* tap_maxprob_out, int32_t* tap_argmax_out, bool timed)
 {
+    InCall in(c);
     const Dims& D = c->D;
     const Layout& Y = c->lay;
     const int R = 2 * D.L;
@@ -855,7 +885,7 @@ int ssd_create(const ssd_config* cfg, void* hip_stream, ssd_ctx** out)
     c->n = 0; c->k_pending = 0; c->tap_rows = 0; c->tap_row0 = 0; c->logit_rows = 0; c->ring_count = 0; c->pinned = nullptr; c->device = -1; c->static_scratch = nullptr;
     memset(&c->st, 0, sizeof(c->st));
     memset(&c->w, 0, sizeof(c->w));
-    c->step_blocks = c->step_max_rows = 0; c->step_table = c->step_now = false;
+    c->step_blocks = c->step_max_rows = 0; c->step_table = c->step_now = false; c->calls = 0;
     c->step_on = true; c->step_ticks = STEP_WAIT_US * STEP_TICKS_PER_US;
     c->step_count = c->step_verify_count = c->step_gave_up = 0;
     c->prof_kid = -1; c->prof_used = 0;
@@ -971,6 +1001,7 @@ int ssd_prefill(ssd_ctx* c, const int32_t* tokens, int n, int32_t* first_token_o
     if (n + 1 > c->D.max_seq) return fail(c, SSD_ECAPACITY, "prompt does not fit max_seq");
     for (int i = 0; i < n; i++)
         if (tokens[i] < 0 || tokens[i] >= c->D.V) return fail(c, SSD_EINVAL, "prompt token id out of range");
+    InCall in(c);
     HIPCHK(set_state(c->small_i() + SM_TOK, 0, c->pos_dev(), 0, c->stream), "set_state");
     if (c->step_blocks > 0 && !c->step_table) {   // once per workspace and set of weights
         HIPCHK(hipMemsetAsync(c->ws + c->lay.step, 0, step_table_offset(c->D), c->stream), "step clear");
@@ -1033,12 +1064,30 @@ int ssd_decode(ssd_ctx* c, int32_t* token_out)
     return SSD_OK;
 }
 
-// b steps whose results are waited for once: each leaves the embedding row of its token to the next one, and its token in the
-// pinned log.  done receives how many were committed: fewer than b where a wait of a step in one launch gave up (those behind it
-// commit nothing either) and, with an error, where a step could not be enqueued behind others.
-static int decode_batch(ssd_ctx* c, int b, int32_t* tokens_out, int& done)
+// Waits until a step has left its token in the pinned log; false where it will not, since it gave up or nothing is on the stream
+// any more.
+static bool wait_token(ssd_ctx* c, const volatile int32_t* token)
+{
+    const volatile int32_t* gave_up = c->pinned + PIN_STEP;
+    for (int spins = 1; *token < 0; spins++) {
+        if (*gave_up) return false;   // (the query, every millisecond or two, is for a stream that has ended in an error)
+        if (spins % 4096 == 0 && hipStreamQuery(c->stream) != hipErrorNotReady) return *token >= 0;
+        std::this_thread::yield();
+    }
+    return true;
+}
+
+// Up to b steps, one behind the other on the device: each leaves the embedding row of its token to the next one, and its token in the
+// pinned log.  Two are on the stream at a time, one of which runs while the host enqueues the other: a stream that shares
+// the hardware queue is served behind them (four 4096^3 products beside 24 layers of 1024: 0.76 ms where every step is waited for, 8.9
+// behind all 32 of a batch, 1.1 so).  done receives how many were committed: fewer than b where another context came (see InCall), where a wait of a step
+// in one launch gave up (those behind it commit nothing either) and, with an error, where a step could not be enqueued behind others.
+static int decode_batch(ssd_ctx* c, int b, InCall& in, int32_t* tokens_out, int& done)
 {
     const int n = c->n;
+    volatile int32_t* log = c->pinned + PIN_PROMPT + n - 1;   // of step 0
+    int enqueued = 0;
+    bool as_enqueued = true;
     bool fits = true;
     for (int i = 0; i < b; i++) fits = fits && step_plan_fits(c->D, n + i, c->step_blocks);
     StepSlot slot(c, c->step_on && c->step_blocks > 0 && c->step_table && c->step_try.on() && fits);
@@ -1047,22 +1096,27 @@ static int decode_batch(ssd_ctx* c, int b, int32_t* tokens_out, int& done)
         HIPCHK(embed_rows(c->D, c->w.embed, Tokens{c->small_i() + SM_TOK, nullptr}, 1, c->f(c->lay.x), c->stream, c->f(c->lay.rope), c->pos_dev(), 0,
                           c->small_f() + SM_ROPE), "embed");
         for (int i = 0; i < b; i++) {
+            if (i > 0 && !in.alone()) break;
+            if (i > 1 && !wait_token(c, log + i - 2)) { as_enqueued = false; break; }
+            log[i] = -1;
             auto step = [&]() { return forward_single(c, nullptr, 0, 1, 0, n + i, 0, STEP_CHAINED | STEP_CHAIN_NEXT | STEP_COMMIT | STEP_LOG); };
             const int rc = c->step_now ? step() : run_sequence(c, "N|" + std::to_string(attention_splits(c->D, n + i, 1)), step);
             if (rc) return rc;
+            enqueued = i + 1;
         }
         return SSD_OK;
     };
-    int32_t pos = n - 1 + b;
+    int32_t pos = n - 1;
     auto settle = [&](bool all) -> int {   // waits; the device's position says what was committed
         const int rs = sync_results(c);
-        if (rs || all) return rs;
+        if (rs) return rs;
+        if (all) { pos = n - 1 + enqueued; return SSD_OK; }
         HIPCHK(hipMemcpyAsync(&pos, c->pos_dev(), 4, hipMemcpyDeviceToHost, c->stream), "position");
         return sync_results(c);
     };
-    int rc = run(), rs = settle(!rc);
+    int rc = run(), rs = settle(!rc && as_enqueued);
     const bool gave_up = !rc && !rs && c->step_now && c->pinned[PIN_STEP];
-    if (gave_up) rs = settle(false);
+    if (gave_up && as_enqueued) rs = settle(false);
     if (rc || rs) c->step_table = false;   // as in run_steps
     if (rs) {   // what was committed is not known: the sequence is over
         c->state = ST_READY;
@@ -1092,10 +1146,11 @@ int ssd_decode_many(ssd_ctx* c, int count, int32_t* tokens_out)
     if (!c || !tokens_out || count < 1) return c ? fail(c, SSD_EINVAL, "decode_many: bad argument") : SSD_EINVAL;
     if (c->state != ST_IDLE) return fail(c, SSD_ESTATE, "decode needs a prefilled sequence with no draft in flight");
     const int fit = std::min(count, c->D.max_seq - c->n);
+    InCall in(c);
     for (int i = 0; i < fit;) {
         int done = 1;
         const int b = std::min(fit - i, DECODE_BATCH);
-        const int rc = b == 1 || c->prof_kid >= 0 ? ssd_decode(c, tokens_out + i) : decode_batch(c, b, tokens_out + i, done);
+        const int rc = b == 1 || c->prof_kid >= 0 || !in.alone() ? ssd_decode(c, tokens_out + i) : decode_batch(c, b, in, tokens_out + i, done);
         if (rc) return rc;
         i += done;
     }
@@ -1324,6 +1379,7 @@ int ssd_window_confidence(ssd_ctx* c, float* conf_out, float* tap_conf_out, int3
     if (!c || !conf_out) return c ? fail(c, SSD_EINVAL, "window_confidence: bad argument") : SSD_EINVAL;
     if (c->cfg.conf_window == 0) return fail(c, SSD_ESTATE, "window_confidence: the context was created with conf_window = 0");
     if (c->state != ST_IDLE || c->ring_count == 0) return fail(c, SSD_ESTATE, "window_confidence needs an idle prefilled sequence");
+    InCall in(c);
     const Dims& D = c->D;
     const Layout& Y = c->lay;
     const int R = 2 * D.L;

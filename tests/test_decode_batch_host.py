@@ -1,7 +1,8 @@
 """CPU: the host side of ssd_decode_many (steps that are waited for together) where a step of a batch fails or gives up.
 
 ssd_api.cpp is compiled against stand-ins for the launches of a step and for the runtime: a step's successor is a fixed function of its
-token and position, it commits what step_finish_kernel commits, and the n-th one can be made to fail or to give up."""
+token and position, it commits what step_finish_kernel commits, and the n-th one can be made to fail or to give up.  What is enqueued
+runs when the host waits, or step by step while it asks whether the stream is through."""
 import ctypes as C
 import os
 import shutil
@@ -21,13 +22,24 @@ STANDINS = r"""
 #include "%(csrc)s/ssd_kernels.h"
 #include <cstdlib>
 #include <cstring>
+#include <deque>
 #include <functional>
 #include <vector>
 using namespace ssdk;
 namespace sim {
-int V = 1024, steps_left = -1, fail_sync = 0, syncs = 0, in_flight = 0, dropped_in_flight = 0, short_plans = 0, blocks = 0, give_up_at = -1, step = 0, captures = 0;
-std::vector<std::function<void()>>* rec = nullptr;      // of the sequence being captured
-template <typename F> hipError_t run(F f) { if (rec) rec->push_back(f); else { in_flight = 1; f(); } return hipSuccess; }
+int V = 1024, steps_left = -1, fail_sync = 0, syncs = 0, dropped_in_flight = 0, short_plans = 0, blocks = 0, give_up_at = -1, step = 0, captures = 0, most_steps = 0, steps_enqueued = 0, step_ends = 0;
+struct Launch { std::function<void()> f; bool step; };   // step: the last one of a step
+using Sequence = std::vector<Launch>;
+Sequence* rec = nullptr;            // of the sequence being captured
+std::deque<Launch> stream;
+void enqueue(const Launch& l)
+{
+    stream.push_back(l);
+    if (l.step) { steps_enqueued++; if (steps_enqueued > most_steps) most_steps = steps_enqueued; }
+}
+void run_one() { const Launch l = stream.front(); stream.pop_front(); if (l.step) { steps_enqueued--; step_ends++; } l.f(); }
+void drain() { while (!stream.empty()) run_one(); }
+template <typename F> hipError_t run(F f, bool ends_step = false) { if (rec) rec->push_back({f, ends_step}); else enqueue({f, ends_step}); return hipSuccess; }
 int next(int tok, int pos) { return (int)(((long)tok * 31 + pos * 7 + 3) %% V); }
 void finish(float tok, const StepOut& o, bool ok)
 {
@@ -54,12 +66,12 @@ SIM sim_attention(const Dims&, const float*, int, const void*, const void*, cons
 SIM sim_gemv_lmhead_argmax(const Dims&, const void*, const float*, const float* x, float*, float, float*, const StepOut& o, hipStream_t)
 {
     if (sim::counted_out()) return hipErrorOutOfMemory;
-    return sim::run([=] { sim::finish(x[0], o, true); });
+    return sim::run([=] { sim::finish(x[0], o, true); }, true);
 }
 SIM sim_step_fused(const Dims&, const StepLaunch& a, const StepOut& o, hipStream_t)
 {
     if (sim::counted_out()) return hipErrorOutOfMemory;
-    return sim::run([=] { if (sim::step++ == sim::give_up_at) o.step_ctrl[1] = 1; sim::finish(a.x[0], o, o.step_ctrl[1] == 0); });
+    return sim::run([=] { if (sim::step++ == sim::give_up_at) o.step_ctrl[1] = 1; sim::finish(a.x[0], o, o.step_ctrl[1] == 0); }, true);
 }
 SIM sim_vocab_reduce(const float*, int M, int, float, float, int32_t* out, int32_t* host, int32_t*, float*, float*, hipStream_t)
 { return sim::run([=] { for (int r = 0; r < M; r++) out[r] = host[r] = 5; }); }
@@ -71,15 +83,20 @@ SIM sim_static(int, void** p) { *p = nullptr; return hipSuccess; }
 SIM sim_malloc(void** p, size_t n, unsigned) { *p = calloc(1, n); return hipSuccess; }
 SIM sim_free(void* p) { free(p); return hipSuccess; }
 SIM sim_device(int* d) { *d = 0; return hipSuccess; }
-SIM sim_copy(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { memcpy(d, s, n); return hipSuccess; }
-SIM sim_fill(void* d, int v, size_t n, hipStream_t) { memset(d, v, n); return hipSuccess; }
-SIM sim_sync(hipStream_t) { sim::syncs++; sim::in_flight = 0; return sim::fail_sync ? hipErrorUnknown : hipSuccess; }
-SIM sim_begin(hipStream_t, hipStreamCaptureMode) { sim::rec = new std::vector<std::function<void()>>; return hipSuccess; }
+SIM sim_copy(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { sim::drain(); memcpy(d, s, n); return hipSuccess; }
+SIM sim_fill(void* d, int v, size_t n, hipStream_t) { sim::drain(); memset(d, v, n); return hipSuccess; }
+SIM sim_sync(hipStream_t) { sim::syncs++; sim::drain(); return sim::fail_sync ? hipErrorUnknown : hipSuccess; }
+SIM sim_query(hipStream_t)
+{
+    for (const int was = sim::step_ends; !sim::stream.empty() && sim::step_ends == was;) sim::run_one();
+    return sim::stream.empty() ? hipSuccess : hipErrorNotReady;
+}
+SIM sim_begin(hipStream_t, hipStreamCaptureMode) { sim::rec = new sim::Sequence; return hipSuccess; }
 SIM sim_end(hipStream_t, hipGraph_t* g) { *g = (hipGraph_t)sim::rec; sim::rec = nullptr; sim::captures++; return hipSuccess; }
-SIM sim_inst(hipGraphExec_t* e, hipGraph_t g, hipGraphNode_t*, char*, size_t) { *e = (hipGraphExec_t) new std::vector<std::function<void()>>(*(std::vector<std::function<void()>>*)g); return hipSuccess; }
-SIM sim_gdel(hipGraph_t g) { delete (std::vector<std::function<void()>>*)g; return hipSuccess; }
-SIM sim_edel(hipGraphExec_t e) { sim::dropped_in_flight += sim::in_flight; delete (std::vector<std::function<void()>>*)e; return hipSuccess; }
-SIM sim_launch(hipGraphExec_t e, hipStream_t) { sim::in_flight = 1; for (auto& f : *(std::vector<std::function<void()>>*)e) f(); return hipSuccess; }
+SIM sim_inst(hipGraphExec_t* e, hipGraph_t g, hipGraphNode_t*, char*, size_t) { *e = (hipGraphExec_t) new sim::Sequence(*(sim::Sequence*)g); return hipSuccess; }
+SIM sim_gdel(hipGraph_t g) { delete (sim::Sequence*)g; return hipSuccess; }
+SIM sim_edel(hipGraphExec_t e) { sim::dropped_in_flight += !sim::stream.empty(); delete (sim::Sequence*)e; return hipSuccess; }
+SIM sim_launch(hipGraphExec_t e, hipStream_t) { for (auto& l : *(sim::Sequence*)e) sim::enqueue(l); return hipSuccess; }
 #define embed_rows sim_embed_rows
 #define rows_plain sim_rows_plain
 #define gemv_qkv sim_gemv_qkv
@@ -100,6 +117,7 @@ SIM sim_launch(hipGraphExec_t e, hipStream_t) { sim::in_flight = 1; for (auto& f
 #define hipMemcpyAsync sim_copy
 #define hipMemsetAsync sim_fill
 #define hipStreamSynchronize sim_sync
+#define hipStreamQuery sim_query
 #define hipStreamBeginCapture sim_begin
 #define hipStreamEndCapture sim_end
 #define hipGraphInstantiate sim_inst
@@ -109,13 +127,14 @@ SIM sim_launch(hipGraphExec_t e, hipStream_t) { sim::in_flight = 1; for (auto& f
 #include "%(csrc)s/ssd_api.cpp"
 extern "C" {
 #define T_API __attribute__((visibility("default")))
-T_API int* t_sim(int i) { int* v[] = {&sim::steps_left, &sim::fail_sync, &sim::syncs, &sim::dropped_in_flight, &sim::short_plans, &sim::blocks, &sim::give_up_at, &sim::step, &sim::captures}; return v[i]; }
+T_API int* t_sim(int i) { int* v[] = {&sim::steps_left, &sim::fail_sync, &sim::syncs, &sim::dropped_in_flight, &sim::short_plans, &sim::blocks, &sim::give_up_at, &sim::step, &sim::captures, &sim::most_steps}; return v[i]; }
 T_API int t_next(int tok, int pos) { return sim::next(tok, pos); }
 T_API void t_fill_cache(ssd_ctx* c, int n) { for (int i = (int)c->graphs.size(); i < n; i++) c->graphs["filler " + std::to_string(i)] = nullptr; }
+T_API void t_other_calls(int n) { calls_in_flight[0] += n; calls_begun[0] += n > 0; }
 T_API int t_cached(ssd_ctx* c) { return (int)c->graphs.size(); }
 }
 """
-NAMES = ("steps_left", "fail_sync", "syncs", "dropped_in_flight", "short_plans", "blocks", "give_up_at", "step", "captures")
+NAMES = ("steps_left", "fail_sync", "syncs", "dropped_in_flight", "short_plans", "blocks", "give_up_at", "step", "captures", "most_steps")
 SHAPE = ModelShape(2, 256, 4, 4, 688, 1024, dtype="fp32")
 PROMPT = [1, 2, 3]
 
@@ -278,6 +297,26 @@ def test_a_full_cache_of_sequences_costs_no_waits(sim):
     narrow.l.t_fill_cache(narrow.h, 256)
     before = narrow["syncs"]
     assert narrow.many(32) == (0, narrow.expect(32)) and narrow["syncs"] == before + 1
+
+
+@pytest.mark.parametrize("replay", [False, True])
+@pytest.mark.parametrize("blocks", [0, 256])
+def test_a_batch_leaves_the_device_to_others(sim, replay, blocks):
+    """Two steps are on the stream at most; while another context's call has work on the device every step is waited for."""
+    s = sim(replay=replay, blocks=blocks)
+    before = s["syncs"]
+    assert s.many(64) == (0, s.expect(64))
+    assert s["most_steps"] == 2 and s["syncs"] == before + 2
+    s["most_steps"] = 0
+    s.l.t_other_calls(1)
+    try:
+        before = s["syncs"]
+        assert s.many(40) == (0, s.expect(40))
+        assert s["most_steps"] == 1 and s["syncs"] == before + 40
+    finally:
+        s.l.t_other_calls(-1)
+    before = s["syncs"]
+    assert s.many(32) == (0, s.expect(32)) and s["syncs"] == before + 1
 
 
 def test_steps_in_one_launch_and_the_cache_of_sequences(sim):
