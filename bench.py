@@ -263,7 +263,8 @@ def main():
     ctx.ssd_prefill(prompt)            # (the prompt pass, timed for the record: not part of `value`)
     sync(); prefill_s = time.perf_counter() - t0
     layer_params = 2 * shape.d_model * shape.n_heads * shape.head_dim + 2 * shape.d_model * shape.d_kv + 3 * shape.d_model * shape.d_ffn
-    prefill_flops = 2.0 * L * layer_params * wl.prompt_len
+    kv_params = 2 * shape.d_model * shape.d_kv     # of the last layer a prompt needs keys and values of all rows, the rest of its last row
+    prefill_flops = 2.0 * ((L - 1) * layer_params * wl.prompt_len + kv_params * wl.prompt_len + layer_params - kv_params)
     search2 = ssd.Search(L, ssd.search_defaults(opt_interval=interval), sel)
     run_cycles(ctx, W, k, search2)
     ctx.ssd_profile_select(KERNEL_IDS["gemv_gateup"])

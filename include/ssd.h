@@ -132,9 +132,10 @@ SSD_API int ssd_prefill(ssd_ctx *ctx, const int32_t *tokens, int n, int32_t *fir
 SSD_API int ssd_decode(ssd_ctx *ctx, int32_t *token_out);
 /* count such steps (count >= 1), their tokens to tokens_out[0 .. count): the results and the state of as many ssd_decode calls, but
  * the device finds the next step enqueued when it ends one, and the host waits for the stream once per 32 steps.  While another context
- * of the process is in a call on the device every step is waited for.  SSD_ECAPACITY when the sequence is full before that; the steps up to there are committed, their
- * tokens are in tokens_out.  So are those in front of a step that fails with SSD_EHIP (ssd_stats.n_tokens counts them); where the
- * device does not answer any more the sequence is over instead, and ssd_prefill starts the next one. */
+ * of the process is in a call on the device every step is waited for.  SSD_ECAPACITY when the sequence is full before that; the steps up
+ * to there are committed, their tokens are in tokens_out.  So are those in front of a step that fails with SSD_EHIP
+ * (ssd_stats.n_tokens counts them); where the device does not answer any more the sequence is over instead, and ssd_prefill starts
+ * the next one. */
 SSD_API int ssd_decode_many(ssd_ctx *ctx, int count, int32_t *tokens_out);
 
 /* Draft model of Section 3: the target model without the layers in the skip set S

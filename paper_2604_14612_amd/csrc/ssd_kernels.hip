@@ -513,7 +513,10 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_kernel(GemvP p)
     // What the block reads besides weights is requested in front of them: loads return in order, and behind the first
     // weights of all blocks (100 KB per CU) the input arrives when these are through, with nothing of the stream in
     // flight until it is staged and the next loads are out.  The first XN four-element pieces per thread (addresses
-    // clamped), the rest of a longer input behind.  In the steps of a 7B model, us, input behind / in front: QKV 19.3 / 18.2,
+    // clamped), the rest of a longer input behind: up to 4096 elements of the LM head's and of a folded input, 8192 of a normalised
+    // one, 14336 of a plain one, the widths up to 8B and 70B's normalised rows.  A piece past the input's end is requested all the
+    // same; with 8192 folded and 28672 plain ones steps of 70B take 0.9 % less (down 71.1 / 69.6 us, folding output projection 25.2 / 24.7),
+    // those of 7B, 8B and 13B 0.7 to 1.6 % more (13B down 24.1 / 24.6, folding output projection 13.4 / 14.1).  In the steps of a 7B model, us, input behind / in front: QKV 19.3 / 18.2,
     // output projection with two or three partials 9.0 / 8.0, with seven 11.0 / 10.1, gate/up 28.9 / 28.5, down 17.9 / 16.5; 70B down 74.5 / 72.3.
     constexpr bool GAIN = EPI != EPI_RESID;
     constexpr int XN = FOLD ? 2 : EPI == EPI_STORE ? 2 : EPI == EPI_RESID ? 7 : 4;
