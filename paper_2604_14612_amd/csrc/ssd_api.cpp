@@ -1070,8 +1070,9 @@ static bool wait_token(ssd_ctx* c, const volatile int32_t* token)
 {
     const volatile int32_t* gave_up = c->pinned + PIN_STEP;
     for (int spins = 1; *token < 0; spins++) {
-        if (*gave_up) return false;   // (the query, every millisecond or two, is for a stream that has ended in an error)
-        if (spins % 4096 == 0 && hipStreamQuery(c->stream) != hipErrorNotReady) return *token >= 0;
+        if (*gave_up) return false;
+        // for a stream that has ended in an error; seldom, since a query takes the device 4 us
+        if (spins % (1 << 16) == 0 && hipStreamQuery(c->stream) != hipErrorNotReady) return *token >= 0;
         std::this_thread::yield();
     }
     return true;

@@ -2,7 +2,7 @@
 
 ssd_api.cpp is compiled against stand-ins for the launches of a step and for the runtime: a step's successor is a fixed function of its
 token and position, it commits what step_finish_kernel commits, and the n-th one can be made to fail or to give up.  What is enqueued
-runs when the host waits, or step by step while it asks whether the stream is through."""
+runs when the host waits, or step by step while it polls."""
 import ctypes as C
 import os
 import shutil
@@ -24,6 +24,7 @@ STANDINS = r"""
 #include <cstring>
 #include <deque>
 #include <functional>
+#include <thread>
 #include <vector>
 using namespace ssdk;
 namespace sim {
@@ -86,11 +87,8 @@ SIM sim_device(int* d) { *d = 0; return hipSuccess; }
 SIM sim_copy(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { sim::drain(); memcpy(d, s, n); return hipSuccess; }
 SIM sim_fill(void* d, int v, size_t n, hipStream_t) { sim::drain(); memset(d, v, n); return hipSuccess; }
 SIM sim_sync(hipStream_t) { sim::syncs++; sim::drain(); return sim::fail_sync ? hipErrorUnknown : hipSuccess; }
-SIM sim_query(hipStream_t)
-{
-    for (const int was = sim::step_ends; !sim::stream.empty() && sim::step_ends == was;) sim::run_one();
-    return sim::stream.empty() ? hipSuccess : hipErrorNotReady;
-}
+SIM sim_query(hipStream_t) { return sim::stream.empty() ? hipSuccess : hipErrorNotReady; }
+namespace std { namespace this_thread { inline void sim_yield() { for (const int was = sim::step_ends; !sim::stream.empty() && sim::step_ends == was;) sim::run_one(); } } }
 SIM sim_begin(hipStream_t, hipStreamCaptureMode) { sim::rec = new sim::Sequence; return hipSuccess; }
 SIM sim_end(hipStream_t, hipGraph_t* g) { *g = (hipGraph_t)sim::rec; sim::rec = nullptr; sim::captures++; return hipSuccess; }
 SIM sim_inst(hipGraphExec_t* e, hipGraph_t g, hipGraphNode_t*, char*, size_t) { *e = (hipGraphExec_t) new sim::Sequence(*(sim::Sequence*)g); return hipSuccess; }
@@ -118,6 +116,7 @@ SIM sim_launch(hipGraphExec_t e, hipStream_t) { for (auto& l : *(sim::Sequence*)
 #define hipMemsetAsync sim_fill
 #define hipStreamSynchronize sim_sync
 #define hipStreamQuery sim_query
+#define yield sim_yield
 #define hipStreamBeginCapture sim_begin
 #define hipStreamEndCapture sim_end
 #define hipGraphInstantiate sim_inst
