@@ -1,4 +1,6 @@
 """GPU: decode steps that are waited for together give what as many single ones give."""
+import threading
+
 import numpy as np
 import pytest
 
@@ -56,6 +58,28 @@ def test_same_as_single_steps(name, graphs, plen, count, room):
 def _again(ctx):
     ctx.ssd_reset()
     return ctx
+
+
+@pytest.mark.parametrize("name", ["one_launch", "per_matrix"])
+def test_contexts_beside_each_other(name):
+    """Steps are waited for one by one then, and the slot of the one-launch steps goes from hand to hand."""
+    import paper_2604_14612_amd as ssd
+    shape = SHAPES[name][0]
+    ctxs = [ssd.Context(shape, to_gpu(make_weights(shape, 7 + i, init_std=0.08)), 400, 4) for i in range(2)]
+    prompt = make_prompt(shape.vocab, 20, 3).tolist()
+    want = [ssd.generate_vanilla(c, prompt, 300) for c in ctxs]
+    got = [None, None]
+
+    def run(i):
+        for _ in range(3):
+            got[i] = ssd.generate_vanilla(_again(ctxs[i]), prompt, 300)
+    threads = [threading.Thread(target=run, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert got == want
+    assert all(c.ssd_get_stats()["n_tokens"] == 320 and c.ssd_get_one_launch()[2] == 0 for c in ctxs)
 
 
 def test_bad_arguments_and_order():
